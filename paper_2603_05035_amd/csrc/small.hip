@@ -12,6 +12,7 @@
 // Both replace chains of 4 - 8 launches of the general kernels, each of which costs more in launch latency
 // than in work at this size.
 #include "gelo_internal.h"
+#include "small_qr.h"
 
 namespace gelo {
 namespace {
@@ -21,48 +22,46 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-// leading dimension (floats) of a column in LDS: a multiple of 4 (16-byte reads), four times an odd number so
-// that the 16-byte reads of 16 neighbouring columns fall on distinct banks
-__host__ __device__ inline int small_ldc(int n) { return 4 * (2 * ((n + 7) / 8) + 1); }
+// pitch (floats) of a row of the Gaussian in LDS: 16 neighbouring columns of four neighbouring rows (what a wave moves
+// between LDS and its registers at a time) fall on distinct banks, and the pitch is odd for the transposing read
+__host__ __device__ inline int small_pitch(int n) { return (n + 63) / 64 * 64 + 17; }
 
 struct SmallSampleArgs {
     SmallSampleTargets t;
     uint32_t key0, key1, c1_mix, c1_shield;
     uint64_t first_batch;
-    int n, k, d;
+    int count, n, k, d;
     int64_t ldk;
 };
 
-// Thread c owns column c of W = [G | I] (n x 2 n, column-major in LDS).  Step j applies the reflector of column
-// j to every later column: each thread walks rows j + 1 .. n - 1 of the pivot column (the same address for all
-// threads: a broadcast) and of its own column twice - once for v^T a and |x|^2, once for the update - and
-// needs nobody else's result: one barrier per column, no reductions.  The right half ends as Q^T.
-__global__ __launch_bounds__(256)
+// Workgroup of role 0: one matrix.  The Gaussian goes through LDS once (its elements are drawn in row order, four per
+// Philox block) into the registers of small_householder; Q^T comes back through the same LDS and leaves as rows of A and
+// A^T, 16 (float) or 8 (bf16) bytes per lane.  The columns and the identity beside them lived in LDS before, one thread
+// walking down its column twice per reflector: 94 us at 68 rows.
+template <int NR>
+__global__ __launch_bounds__(32 * NR < 256 ? 256 : (32 * NR + 63) / 64 * 64)
 void small_sample_kernel(SmallSampleArgs a) {
     extern __shared__ __attribute__((aligned(16))) float W[];
-    __shared__ float rdiag[kSmallMaxN];
+    __shared__ SmallQrShared<NR> sh;
     __shared__ float wave_part[4];
-    const int per_item = 1 + a.k;
-    const int item = blockIdx.x / per_item, role = blockIdx.x - item * per_item;
+    // the matrices first: their workgroups run longest
+    const int item = blockIdx.x < a.count ? blockIdx.x : (blockIdx.x - a.count) / a.k;
+    const int role = blockIdx.x < a.count ? 0 : 1 + (blockIdx.x - a.count) % a.k;
     const uint64_t batch = a.first_batch + (uint64_t)item;
+    const int tid = threadIdx.x, nthr = blockDim.x;
     PhiloxStream ps;
     ps.key0 = a.key0; ps.key1 = a.key1; ps.c2 = (uint32_t)batch; ps.c3 = (uint32_t)(batch >> 32);
     char* block = (char*)a.t.block[item];
     if (role > 0) {
+        if (tid >= 256) return;                                  // a row of shield directions is the work of 256 threads
         ps.c1 = a.c1_shield;
         shield_direction_row((float*)(block + a.t.off_GS), a.d, role - 1, ps, (float*)(block + a.t.off_gsnorm), wave_part);
         return;
     }
-    const int n = a.n, ldc = small_ldc(n), tid = threadIdx.x;
-    // G: element e = r n + c is output e % 4 of Philox block e / 4; the right half starts as the identity;
-    // rows n .. ldc - 1 of every column are zero (the 16-byte reads of a column's tail run into them)
-    for (int i = tid; i < 2 * n * ldc; i += 256) {
-        const int c = i / ldc, r = i - c * ldc;
-        W[i] = (c >= n && r == c - n) ? 1.f : 0.f;
-    }
-    __syncthreads();
+    const int n = a.n, pitch = small_pitch(n);
+    // G: element e = r n + c is output e % 4 of Philox block e / 4
     const int total = n * n;
-    for (int q = tid; q * 4 < total; q += 256) {
+    for (int q = tid; q * 4 < total; q += nthr) {
         uint32_t c0 = (uint32_t)q, c1 = a.c1_mix, c2 = ps.c2, c3 = ps.c3;
         philox4x32_10(c0, c1, c2, c3, ps.key0, ps.key1);
         float z[4];
@@ -72,98 +71,54 @@ void small_sample_kernel(SmallSampleArgs a) {
         int r = e / n, c = e - r * n;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            if (e + t < total) W[c * ldc + r] = z[t];
+            if (e + t < total) W[r * pitch + c] = z[t];
             if (++c == n) { c = 0; ++r; }
         }
     }
     __syncthreads();
-
-    const int c = tid;
-    float* mine = W + c * ldc;
-    for (int j = 0; j < n; ++j) {
-        const float* piv = W + j * ldc;
-        if (c > j && c < 2 * n) {
-            const float alpha = piv[j];
-            const float top = mine[j];
-            const int r0 = (j + 1) & ~3;
-            // four independent partial sums each, and the loop unrolled: a lone wave per SIMD has nothing else to hide
-            // the LDS latency behind
-            f32x4_t sp = {0.f, 0.f, 0.f, 0.f}, qp = {0.f, 0.f, 0.f, 0.f};
-            {
-                // only the first chunk can reach above the tail
-                f32x4_t x = *reinterpret_cast<const f32x4_t*>(piv + r0);
-                const f32x4_t y = *reinterpret_cast<const f32x4_t*>(mine + r0);
+    const int c = tid >> 2, q = tid & 3;
+    float x[NR];
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float xt = r0 + t > j ? x[t] : 0.f;
-                    sp[t] = xt * y[t];
-                    qp[t] = xt * xt;
-                }
-            }
-#pragma unroll 4
-            for (int r = r0 + 4; r < n; r += 4) {
-                const f32x4_t x = *reinterpret_cast<const f32x4_t*>(piv + r);
-                const f32x4_t y = *reinterpret_cast<const f32x4_t*>(mine + r);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    sp[t] = fmaf(x[t], y[t], sp[t]);
-                    qp[t] = fmaf(x[t], x[t], qp[t]);
-                }
-            }
-            const float s = (sp[0] + sp[1]) + (sp[2] + sp[3]);
-            const float q = (qp[0] + qp[1]) + (qp[2] + qp[3]);
-            // beta = -sign(alpha) sqrt(alpha^2 + |x|^2), tau = (beta - alpha) / beta, v = x / (alpha - beta) below a
-            // unit entry; a zero tail gives the identity (tau = 0)
-            const bool tail = q > 0.f;
-            const float nrm = __builtin_amdgcn_sqrtf(fmaf(alpha, alpha, q));
-            const float beta = tail ? -copysignf(nrm, alpha) : alpha;
-            const float tau = tail ? (beta - alpha) * __builtin_amdgcn_rcpf(beta) : 0.f;      // hardware reciprocals (1 ulp), as in the
-            const float scale = tail ? __builtin_amdgcn_rcpf(alpha - beta) : 0.f;             // panel kernel of the blocked QR
-            const float w = fmaf(scale, s, top);                       // v^T (column c)
-            const float tw = tau * w;
-            mine[j] = top - tw;
-            const float f = tw * scale;
-            {
-                const f32x4_t x = *reinterpret_cast<const f32x4_t*>(piv + r0);
-                f32x4_t y = *reinterpret_cast<const f32x4_t*>(mine + r0);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) y[t] = r0 + t > j ? fmaf(-f, x[t], y[t]) : y[t];
-                *reinterpret_cast<f32x4_t*>(mine + r0) = y;
-            }
-#pragma unroll 4
-            for (int r = r0 + 4; r < n; r += 4) {
-                const f32x4_t x = *reinterpret_cast<const f32x4_t*>(piv + r);
-                f32x4_t y = *reinterpret_cast<const f32x4_t*>(mine + r);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) y[t] = fmaf(-f, x[t], y[t]);
-                *reinterpret_cast<f32x4_t*>(mine + r) = y;
-            }
-            if (c == j + 1) rdiag[j] = beta;                           // the diagonal of R: (alpha, x) becomes (beta, 0)
-        }
-        __syncthreads();
+    for (int i = 0; i < NR; ++i) {
+        const int r = 4 * i + q;
+        x[i] = c < n ? (r < n ? W[r * pitch + c] : 0.f) : (r == c - n ? 1.f : 0.f);
     }
-
-    // column n + i of W is row i of Q.  A = Q diag(sign r_ii); A^-1 = A^T; both zero beyond column n.
+    small_householder<NR>(x, n, sh);
+    // W[r][i] = A[i][r] = Q[i][r] sign(r_rr)
+    if (c >= n && c < 2 * n) {
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const int r = 4 * i + q;
+            if (r < n) W[r * pitch + (c - n)] = sh.rdiag[r] < 0.f ? -x[i] : x[i];
+        }
+    }
+    __syncthreads();
+    // A and A^-1 = A^T, zero beyond column n
     float* A32 = (float*)(block + a.t.off_A32);
     float* Ai32 = (float*)(block + a.t.off_Ainv32);
     uint16_t* A16 = a.t.off_A16 >= 0 ? (uint16_t*)(block + a.t.off_A16) : nullptr;
     uint16_t* Ai16 = a.t.off_A16 >= 0 ? (uint16_t*)(block + a.t.off_Ainv16) : nullptr;
-    const int ldk = (int)a.ldk;
-    for (int e = tid; e < n * ldk; e += 256) {
-        const int i = e / ldk, cc = e - i * ldk;
-        float x = 0.f, xt = 0.f;
-        if (cc < n) {
-            x = W[(n + i) * ldc + cc];
-            if (rdiag[cc] < 0.f) x = -x;
-            xt = W[(n + cc) * ldc + i];
-            if (rdiag[i] < 0.f) xt = -xt;
+    const int ldk = (int)a.ldk, quads = ldk / 4;
+    auto pack4 = [](f32x4_t v) {
+        typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+        const bf16x4_t h = {(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
+        return __builtin_bit_cast(uint2, h);
+    };
+    for (int e = tid; e < n * quads; e += nthr) {
+        const int i = e / quads, cc = (e - i * quads) * 4;
+        f32x4_t v, vt;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const bool in = cc + t < n;
+            v[t] = in ? W[(cc + t) * pitch + i] : 0.f;
+            vt[t] = in ? W[i * pitch + cc + t] : 0.f;
         }
-        A32[e] = x;
-        Ai32[e] = xt;
+        const int64_t at = (int64_t)i * ldk + cc;
+        *reinterpret_cast<f32x4_t*>(A32 + at) = v;
+        *reinterpret_cast<f32x4_t*>(Ai32 + at) = vt;
         if (A16) {
-            const __bf16 h = (__bf16)x, ht = (__bf16)xt;
-            A16[e] = __builtin_bit_cast(uint16_t, h);
-            Ai16[e] = __builtin_bit_cast(uint16_t, ht);
+            *reinterpret_cast<uint2*>(A16 + at) = pack4(v);
+            *reinterpret_cast<uint2*>(Ai16 + at) = pack4(vt);
         }
     }
 }
@@ -314,24 +269,47 @@ void small_mix_kernel(SmallMixArgs a) {
 
 }  // namespace
 
+namespace {
+// rows per lane of a quad: 20, 36, 68, 100 and 128 rows (a workgroup of eight threads per row; a step costs what its
+// longest walk over the registers costs, so the walk is sized for the matrix)
+template <class F>
+hipError_t for_small_rows(int n, F&& f) {
+    if (n <= 20) return f(std::integral_constant<int, 5>{});
+    if (n <= 36) return f(std::integral_constant<int, 9>{});
+    if (n <= 68) return f(std::integral_constant<int, 17>{});
+    if (n <= 100) return f(std::integral_constant<int, 25>{});
+    return f(std::integral_constant<int, 32>{});
+}
+size_t small_lds_bytes(int n) { return (size_t)n * small_pitch(n) * sizeof(float); }
+}  // namespace
+
 hipError_t small_init() {
-    const int ldc = small_ldc(kSmallMaxN);
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&small_sample_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               2 * kSmallMaxN * ldc * (int)sizeof(float));
+    for (int n : {20, 36, 68, 100, kSmallMaxN}) {
+        const hipError_t e = for_small_rows(n, [&](auto R) {
+            return hipFuncSetAttribute(reinterpret_cast<const void*>(&small_sample_kernel<decltype(R)::value>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)small_lds_bytes(n));
+        });
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t small_sample(const SmallSampleTargets& t, int count, uint64_t first_batch, PhiloxStream ps, uint32_t c1_shield,
                         int n, int k, int d, int64_t ldk, hipStream_t stream) {
     if (count <= 0) return hipSuccess;
-    if (count > kSmallMaxBatch || n < 1 || n > kSmallMaxN || k < 0 || ldk < n) return hipErrorInvalidValue;
+    if (count > kSmallMaxBatch || n < 1 || n > kSmallMaxN || k < 0 || ldk < n || ldk % 4 != 0) return hipErrorInvalidValue;
     SmallSampleArgs a;
     a.t = t;
     a.key0 = ps.key0; a.key1 = ps.key1; a.c1_mix = ps.c1; a.c1_shield = c1_shield;
     a.first_batch = first_batch;
-    a.n = n; a.k = k; a.d = d; a.ldk = ldk;
-    const size_t lds = (size_t)2 * n * small_ldc(n) * sizeof(float);
-    hipLaunchKernelGGL(small_sample_kernel, dim3((unsigned)(count * (1 + k))), dim3(256), lds, stream, a);
-    return hipGetLastError();
+    a.count = count; a.n = n; a.k = k; a.d = d; a.ldk = ldk;
+    // at least 256 threads: what a row of shield directions takes
+    const int threads = 8 * n < 256 ? 256 : (8 * n + 63) / 64 * 64;
+    return for_small_rows(n, [&](auto R) {
+        hipLaunchKernelGGL(small_sample_kernel<decltype(R)::value>, dim3((unsigned)(count * (1 + k))), dim3(threads), small_lds_bytes(n),
+                           stream, a);
+        return hipGetLastError();
+    });
 }
 
 hipError_t small_mix(const uint16_t* A16, int64_t ldk, const uint16_t* H, int64_t ldh, const float* GS, const float* gsnorm,

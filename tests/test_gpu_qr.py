@@ -1,0 +1,40 @@
+"""The QR kernels at the sizes where they change: A against LAPACK's QR of the oracle's Gaussian (positive diagonal of
+R makes the factor unique).  Bounds: A^T A = I to c sqrt(n) roundings of float in the Frobenius norm, A itself to that
+times the condition number of the Gaussian."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import gelo_oracle as o
+from paper_2603_05035_amd import binding as g
+
+pytestmark = pytest.mark.gpu
+EPS = 2.0 ** -24
+
+
+@pytest.fixture()
+def ctx():
+    c = g.gelo_create(0, 0xC0FFEE, allow_batch_reuse=False)
+    yield c
+    g.gelo_destroy(c)
+
+
+def check_orthogonal(A, n, batch):
+    G = o.gaussian_matrix(0xC0FFEE, batch, o.STREAM_MIXING, 0, n, n)
+    Q, R = np.linalg.qr(G)
+    ref = Q * np.sign(np.diag(R))
+    assert np.linalg.norm(A.T @ A - np.eye(n)) / math.sqrt(n) < 20 * EPS * math.sqrt(n) + 1e-7
+    assert np.linalg.norm(A - ref) / math.sqrt(n) < 10 * np.linalg.cond(G) * EPS
+
+
+# rows per lane of the one-workgroup factorisation change behind 20, 36, 68 and 100 rows; one, two and the most rows
+@pytest.mark.parametrize("n", [1, 2, 3, 20, 21, 36, 37, 67, 68, 69, 100, 101, 127, 128])
+def test_one_workgroup_factorisation(ctx, n):
+    m = g.gelo_sample_mixing(ctx, g.GELO_ORTHOGONAL, n, 0, 64, g.GELO_F32, 1e3, 64, batch_id=n)
+    A, A_inv, _, _, _ = g.gelo_mixing_export(ctx, m, n, 0, 64)
+    torch.cuda.synchronize()
+    g.gelo_mixing_free(ctx, m)
+    assert torch.equal(A_inv, A.t())
+    check_orthogonal(A.double().cpu().numpy(), n, n)
