@@ -3,9 +3,9 @@
 // with the LU path.  Everything is float and deterministic: reductions run in a fixed order, no
 // atomics.
 //
-// Column panels are 16 wide.  A panel is factorised by ONE workgroup that keeps its rows in
-// registers (thread t owns rows t, t+NTHR, ...), so the per-column reductions cost one barrier
-// and no memory traffic; the block reflectors are applied on the matrix cores.
+// Column panels are 16 wide.  A panel is factorised by ONE workgroup, from its 16 x 16 Gram matrix while it is tall
+// (gram_panel_body), by a loop over its columns at the end (qr_panel_body); the block reflectors are applied on the
+// matrix cores.
 #include <type_traits>
 #include <utility>
 
@@ -227,6 +227,7 @@ __device__ __forceinline__ void qr_panel_body(float* Mp, float* Vr, float* Vt, f
     }
 }
 
+// a matrix of one short panel, or the first panel of such a matrix
 template <int NTHR, int R>
 __global__ __launch_bounds__(NTHR)
 void qr_panel_kernel(float* Mp, float* Vr, float* Vt, float* Tg, float* rdiag, int m, int64_t batch_stride) {
@@ -258,6 +259,7 @@ void direct_panels_kernel(float* M, float* Vc, float* Tmat, float* rdiag, int nb
 // rows 4 g .. 4 g + 3 a lane owns are adjacent), the reflectors come in the same tiles (Vt) for the
 // first product and as Vr[r * 16 + i] for the second.
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
 // One block reflector I - V op(T) V^T as a strip sees it: V in both layouts, its triangle, and `shift`, the
 // number of 16-row blocks by which its first row lies below the strip's first row (a strip that applies several
@@ -268,7 +270,7 @@ struct Reflector { const float* Vr; const float* Vt; const float* T; int shift; 
 // (the pointers are those of the first matrix of a batch; `off` below is the distance to this workgroup's matrix)
 
 constexpr int kBulkFromCount = 2;         // from this many factorisations side by side the block strips get launches of their own
-constexpr int kPanelRows256 = 1024;      // panels of up to this many rows are factorised by 256 threads, longer ones by 512
+constexpr int kPanelRows256 = 1024;      // panels of directly drawn reflectors: up to this many rows by 256 threads, longer ones by 512
 constexpr int kMaxDelay = 4;             // panels per block of the delayed update: most reflectors a strip pass of the factorisation applies
 constexpr int kMaxProduct = 8;           // most reflectors a strip pass applies while Q is formed (qr_bulk_kernel: all reflectors exist by then,
                                          // so the passes can be longer: measured 10% less time for the same reflectors than passes of four)
@@ -281,12 +283,18 @@ __device__ __attribute__((aligned(1024))) float g_zero_tile[256];
 // wave fetches feeds twice the matrix instructions, at twice the registers; measured equal to two one-strip
 // workgroups per compute unit (reflect_strip_lds_body), which is what the launches of many matrices use, so only
 // NS = 1 is instantiated at present.  Each strip's arithmetic is the same whichever way strips are grouped.
-template <int NBLK, int NS>
-__device__ __forceinline__ void reflect_strip_body(const Reflector* refl, int count, int64_t off, float* Cs,
-                                                   int64_t strip_stride, int strips, int nblocks) {
-    constexpr int NC = NB * NS;                              // columns per workgroup
-    __shared__ float Wp[2][8][NB][NC];                       // the waves' partial W, alternating between reflectors
-    __shared__ float Ts[2][NB][NB];
+// `done` gets the strip's registers behind the last reflector: block wave + 8 b of strip st in cr[st][b].
+template <int NS>
+struct StripShared {
+    float Wp[2][8][NB][NB * NS];                             // the waves' partial W, alternating between reflectors
+    float Ts[2][NB][NB];
+};
+
+template <int NBLK, int NS, class Done>
+__device__ __forceinline__ void reflect_strip_body(StripShared<NS>& sh, const Reflector* refl, int count, int64_t off, float* Cs,
+                                                   int64_t strip_stride, int strips, int nblocks, Done&& done) {
+    auto& Wp = sh.Wp;
+    auto& Ts = sh.Ts;
     // the wave index as a scalar: block numbers and their offsets then live in scalar registers
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g = lane >> 4;
@@ -422,17 +430,28 @@ __device__ __forceinline__ void reflect_strip_body(const Reflector* refl, int co
             request_behind(std::integral_constant<int, j>{});
         });
     });
+    done(cr);
+}
+
+// the same, the strip written back in place
+template <int NBLK, int NS>
+__device__ __forceinline__ void reflect_strip_in_place(StripShared<NS>& sh, const Reflector* refl, int count, int64_t off, float* Cs,
+                                                       int64_t strip_stride, int strips, int nblocks) {
+    reflect_strip_body<NBLK, NS>(sh, refl, count, off, Cs, strip_stride, strips, nblocks, [&](f32x4_t (&cr)[NS][NBLK]) {
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        float* Cl = Cs + (lane & 15) * 16 + 4 * (lane >> 4);
 #pragma unroll
-    for (int st = 0; st < NS; ++st) {
-        if (st < strips) {
-            float* Csl = Cl + st * strip_stride;
+        for (int st = 0; st < NS; ++st) {
+            if (st < strips) {
+                float* Csl = Cl + st * strip_stride;
 #pragma unroll
-            for (int b = 0; b < NBLK; ++b) {
-                const int blk = wave + 8 * b;
-                if (blk < nblocks) *reinterpret_cast<f32x4_t*>(Csl + 256 * blk) = cr[st][b];
+                for (int b = 0; b < NBLK; ++b) {
+                    const int blk = wave + 8 * b;
+                    if (blk < nblocks) *reinterpret_cast<f32x4_t*>(Csl + 256 * blk) = cr[st][b];
+                }
             }
         }
-    }
+    });
 }
 
 // The same strip for launches that hold nothing but strips (several factorisations side by side: see
@@ -627,7 +646,251 @@ template <int NBLK>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void qr_long_strips_kernel(QrBulkArgs a) {
     const int64_t off = (int64_t)blockIdx.y * a.batch_stride;
-    reflect_strip_body<NBLK, 1>(a.refl, a.pending, off, a.X + off + (int64_t)blockIdx.x * a.strip_stride, a.strip_stride, 1, a.nb_block);
+    __shared__ StripShared<1> sh;
+    reflect_strip_in_place<NBLK, 1>(sh, a.refl, a.pending, off, a.X + off + (int64_t)blockIdx.x * a.strip_stride, a.strip_stride, 1, a.nb_block);
+}
+
+// ------------------------------------------------------------- panel from its Gram matrix --
+// The Householder reflectors of a tall panel without a reduction per column.  Householder's step j needs of the columns
+// below its row only their inner products with column j; those of all steps follow from the panel's 16 x 16 Gram matrix,
+// because a reflector keeps inner products: with G the Gram matrix of rows j onward, beta = -sign(alpha) sqrt(G[j][j]),
+// row j of R is G[j][s] / beta, column s loses f_s = (P[j][s] - G[j][s] / beta) / (alpha - beta) times column j, and the
+// Gram matrix of the rows below j is G[i][s] - G[i][j] G[j][s] / G[j][j].  All of it happens on 16 x 16 matrices - G, the
+// panel's top tile and the column operations X accumulated so far - which every wave keeps for itself, lane (., s) holding
+// column s of each: one step is "column s -= coefficient(s) x column j", the broadcast of column j a DPP modifier of the
+// multiply-add.  Then V = [L ; P2 X]: one product of the rows below the top tile with X, on the matrix cores, straight
+// from the accumulator layout the strip is in.  The triangle T is the inverse of V^T V's upper triangle with half its
+// diagonal (what makes I - V T V^T orthogonal for ANY V), V^T V = L^T L + X^T (P2^T P2) X.
+// The Gram matrix squares the panel's condition number, which for m x 16 independent Gaussians is about
+// (sqrt(m) + 4) / (sqrt(m) - 4): 3 at 64 rows, 1.2 at 2000.  So this is for tall panels of a matrix drawn as independent
+// Gaussians (a panel behind its reflectors is such a matrix again); the last panels take qr_panel_body.
+// Bound by the latency of one workgroup.  With the strip in front, per launch: 22 us at 2100 rows (30 with a reduction and a
+// barrier per column), 9 us at 500 rows (15), of which the launch itself is 4; a whole draw alone: 2150 rows 3.91 -> 2.68 ms,
+// 543 rows 591 -> 412 us, 4096 rows 15 -> 9.3 ms.  Against 64 bits A is as close as before (3e-6 at 2150 rows), A^T A = I closer.
+constexpr int kGramPanelRows = 64;       // panels of more rows than this are built from their Gram matrix
+
+// value of lane J of the row of 16 lanes
+template <int J>
+__device__ __forceinline__ float row_bcast(float v) {                                      // row_newbcast:J
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x150 + J, 0xF, 0xF, true));
+}
+
+// col[i] += k x (col[i] of lane J of the row of 16), rows FROM <= i < TO: one instruction each, which the compiler does not
+// form by itself (it leaves a move with the broadcast and a multiply-add: twice the issue slots of the loop below).  The
+// register a broadcast reads must not have been written by one of the two preceding instructions: the leading wait covers
+// what the compiler put in front, inside each register is read and written once, the trailing one covers what follows.
+#define GELO_ROW(i) ".if (" #i " >= %c18) && (" #i " < %c19)\n\tv_fmac_f32_dpp %" #i ", %" #i ", %16 row_newbcast:%c17 row_mask:0xf bank_mask:0xf\n.endif\n\t"
+template <int J, int FROM, int TO>
+__device__ __forceinline__ void add_column(float (&col)[NB], float k) {
+    if constexpr (FROM < TO)
+        asm("s_nop 1\n\t"
+            GELO_ROW(0) GELO_ROW(1) GELO_ROW(2) GELO_ROW(3) GELO_ROW(4) GELO_ROW(5) GELO_ROW(6) GELO_ROW(7)
+            GELO_ROW(8) GELO_ROW(9) GELO_ROW(10) GELO_ROW(11) GELO_ROW(12) GELO_ROW(13) GELO_ROW(14) GELO_ROW(15)
+            "s_nop 1"
+            : "+v"(col[0]), "+v"(col[1]), "+v"(col[2]), "+v"(col[3]), "+v"(col[4]), "+v"(col[5]), "+v"(col[6]), "+v"(col[7]),
+              "+v"(col[8]), "+v"(col[9]), "+v"(col[10]), "+v"(col[11]), "+v"(col[12]), "+v"(col[13]), "+v"(col[14]), "+v"(col[15])
+            : "v"(k), "n"(J), "n"(FROM), "n"(TO));
+}
+#undef GELO_ROW
+
+constexpr int kTilePitch = NB + 4;       // floats per row of a 16 x 16 tile in LDS: row-wise 16-byte reads and column-wise 4-byte
+                                         // writes of a wave are then both free of bank conflicts
+constexpr int kPanelGroup = 2;           // tiles a wave turns around in LDS at a time
+template <int NBLK>
+struct GramShared {
+    __attribute__((aligned(16))) float part[8][64][4];                      // the waves' partial Gram matrices of the rows below the top tile
+    __attribute__((aligned(16))) float top[64][4];                          // the top tile, as it lies in its wave's registers
+    __attribute__((aligned(16))) float X[64][4], L[64][4];                  // the column operations and the top of V, lane (g, c): rows 4 g ..
+    __attribute__((aligned(16))) float turn[8][kPanelGroup][NB * kTilePitch];
+    __attribute__((aligned(16))) float first[NBLK][NB * kTilePitch];        // wave 0's tiles: its registers go to the 16 x 16 matrices
+};
+
+// lane (g, c) of a wave with all 16 rows of column c (the same in its four groups g) -> rows 4 g .. 4 g + 3
+__device__ __forceinline__ f32x4_t rows_of_group(const float (&col)[NB], int g) {
+    f32x4_t r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float c0 = col[e], c1 = col[4 + e], c2 = col[8 + e], c3 = col[12 + e];
+        const float lo = g & 1 ? c1 : c0, hi = g & 1 ? c3 : c2;
+        r[e] = g & 2 ? hi : lo;
+    }
+    return r;
+}
+
+// The panel is the strip cr (block wave + 8 b in cr[b], accumulator layout) from block FIRST on (its top tile) to block
+// `last`.  Outputs as qr_panel_body's: block FIRST of the panel goes to tile 0 of Vr and Vt.  512 threads.
+// The steps on the 16 x 16 matrices are the work of wave 0 alone (on every wave they took twice as long: two waves share
+// a SIMD's issue slots); the others turn their tiles around meanwhile.
+template <int NBLK, int FIRST>
+__device__ __forceinline__ void gram_panel_body(GramShared<NBLK>& sh, f32x4_t (&cr)[NBLK], int last, float* Vr, float* Vt, float* Tg, float* rdiag) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, g = lane >> 4;
+    // P2^T P2 of this wave's blocks: register e of a block is row 4 g + e of column c, which is what lane (g, c) supplies
+    // for either operand of the instruction that contracts rows 4 g + e
+    {
+        f32x4_t sum[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int b = 0; b < NBLK; ++b) {
+            const int blk = wave + 8 * b;
+            if (blk > last || blk <= FIRST) continue;         // wave-uniform
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(cr[b][e], cr[b][e], sum[e], 0, 0, 0);
+        }
+        *reinterpret_cast<f32x4_t*>(sh.part[wave][lane]) = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+        if (wave == FIRST) *reinterpret_cast<f32x4_t*>(sh.top[lane]) = cr[0];
+    }
+    __syncthreads();
+    float* mine = sh.turn[wave][0];
+    // every lane gets the whole column c of a matrix in accumulator layout (symmetric or not)
+    auto columns = [&](f32x4_t v, float (&col)[NB]) {
+        *reinterpret_cast<f32x4_t*>(mine + c * kTilePitch + 4 * g) = v;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f32x4_t x = *reinterpret_cast<const f32x4_t*>(mine + c * kTilePitch + 4 * q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) col[4 * q + e] = x[e];
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    // rows instead of columns: block b becomes lane (g, i): row i, columns 4 g .. 4 g + 3 (the A operand of P2 X)
+    auto put = [&](float* t, f32x4_t v) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[(4 * g + e) * kTilePitch + c] = v[e];
+    };
+    auto get = [&](const float* t) { return *reinterpret_cast<const f32x4_t*>(t + c * kTilePitch + 4 * g); };
+    f32x4_t gb = {0.f, 0.f, 0.f, 0.f}, xd, ld, xs;
+    float scale_c = 0.f, beta_c = 0.f;                        // of this lane's own column (wave 0)
+    if (wave == 0) {
+#pragma unroll
+        for (int b = 0; b < NBLK; ++b) if (8 * b <= last) put(sh.first[b], cr[b]);
+        f32x4_t pw[8];
+#pragma unroll
+        for (int w = 0; w < 8; ++w) pw[w] = *reinterpret_cast<const f32x4_t*>(sh.part[w][lane]);
+        gb = ((pw[0] + pw[1]) + (pw[2] + pw[3])) + ((pw[4] + pw[5]) + (pw[6] + pw[7]));
+        const f32x4_t p1 = *reinterpret_cast<const f32x4_t*>(sh.top[lane]);
+        f32x4_t gf = gb;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) gf = __builtin_amdgcn_mfma_f32_16x16x4f32(p1[e], p1[e], gf, 0, 0, 0);
+        float Gc[NB], Pc[NB], Xc[NB];
+        columns(gf, Gc);
+        columns(p1, Pc);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) Xc[i] = i == c ? 1.f : 0.f;
+        static_for<NB>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            const float gjj = row_bcast<j>(Gc[j]), alpha = row_bcast<j>(Pc[j]);
+            const bool some = gjj > 0.f;                      // a column of zeros needs no reflector
+            // hardware reciprocals and root (1 ulp), as in qr_panel_body
+            const float irn = some ? __builtin_amdgcn_rsqf(gjj) : 0.f;
+            const float beta = -copysignf(gjj * irn, alpha), ibeta = -copysignf(irn, alpha);
+            const float scale = some ? __builtin_amdgcn_rcpf(alpha - beta) : 0.f;
+            const float h = c > j ? -Gc[j] * (irn * irn) : 0.f;
+            const float f = c > j ? fmaf(Gc[j], ibeta, -Pc[j]) * scale : 0.f;
+            if (c == j) { scale_c = scale; beta_c = beta; }
+            add_column<j, j + 1, NB>(Gc, h);
+            add_column<j, j + 1, NB>(Pc, f);
+            add_column<j, 0, j + 1>(Xc, f);
+        });
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            Xc[i] *= scale_c;
+            Pc[i] = i > c ? Pc[i] * scale_c : (i == c ? 1.f : 0.f);
+        }
+        xd = rows_of_group(Xc, g);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float x0 = Xc[4 * v], x1 = Xc[4 * v + 1], x2 = Xc[4 * v + 2], x3 = Xc[4 * v + 3];
+            const float lo = g & 1 ? x1 : x0, hi = g & 1 ? x3 : x2;
+            xs[v] = g & 2 ? hi : lo;                          // rows 4 v + g
+        }
+        ld = rows_of_group(Pc, g);
+        *reinterpret_cast<f32x4_t*>(sh.X[lane]) = xd;
+        *reinterpret_cast<f32x4_t*>(sh.L[lane]) = ld;
+    } else {
+#pragma unroll
+        for (int b0 = 0; b0 < NBLK; b0 += kPanelGroup) {
+            if (wave + 8 * b0 > last) continue;
+#pragma unroll
+            for (int k = 0; k < kPanelGroup; ++k) if (b0 + k < NBLK) put(sh.turn[wave][k], cr[b0 + k < NBLK ? b0 + k : 0]);
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int k = 0; k < kPanelGroup; ++k) if (b0 + k < NBLK) cr[b0 + k < NBLK ? b0 + k : 0] = get(sh.turn[wave][k]);
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    __syncthreads();
+    if (wave == 0) {
+        // T, while the other waves form V (this one has a block less than they have).  V^T V in double precision, from the
+        // float Gram matrix: its rounding would be what the orthogonality of I - V T V^T is lost to (1.1e-6 per panel in
+        // the Frobenius norm with float products, 0.6e-6 this way, 0.9e-6 with the sums of qr_panel_body).  The double
+        // instruction leaves row 4 v + g of column c in element v.
+        f64x4_t gx = {0., 0., 0., 0.}, m = {0., 0., 0., 0.};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) gx = __builtin_amdgcn_mfma_f64_16x16x4f64((double)gb[e], (double)xd[e], gx, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m = __builtin_amdgcn_mfma_f64_16x16x4f64((double)ld[e], (double)ld[e], m, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) m = __builtin_amdgcn_mfma_f64_16x16x4f64((double)xs[v], gx[v], m, 0, 0, 0);
+        float Mc[NB], Tc[NB];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) mine[c * kTilePitch + 4 * v + g] = (float)m[v];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f32x4_t x = *reinterpret_cast<const f32x4_t*>(mine + c * kTilePitch + 4 * q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) Mc[4 * q + e] = x[e];
+        }
+        float tau_c = 0.f;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) { Tc[i] = i == c ? 1.f : 0.f; tau_c = i == c ? Mc[i] : tau_c; }
+        tau_c = scale_c != 0.f ? 2.f / tau_c : 0.f;
+        static_for<NB - 1>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            const float tau = row_bcast<j>(tau_c);            // (outside of the selection: all lanes have to be active)
+            add_column<j, 0, j + 1>(Tc, c > j ? -Mc[j] * tau : 0.f);
+        });
+        const f32x4_t td = rows_of_group(Tc, g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) Tg[(4 * g + e) * NB + c] = td[e] * tau_c;
+        if (g == 0) rdiag[c] = beta_c;
+#pragma unroll
+        for (int b = 0; b < NBLK; ++b) if (8 * b <= last) cr[b] = get(sh.first[b]);
+    } else {
+        xd = *reinterpret_cast<const f32x4_t*>(sh.X[lane]);
+    }
+    // V = P2 X below the top tile, written in both layouts
+#pragma unroll
+    for (int b = 0; b < NBLK; ++b) {
+        const int blk = wave + 8 * b;
+        if (blk > last || blk < FIRST) continue;
+        f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v = __builtin_amdgcn_mfma_f32_16x16x4f32(cr[b][e], xd[e], v, 0, 0, 0);
+        if (blk == FIRST) v = *reinterpret_cast<const f32x4_t*>(sh.L[lane]);
+        *reinterpret_cast<f32x4_t*>(Vt + 256 * (blk - FIRST) + c * 16 + 4 * g) = v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) Vr[256 * (blk - FIRST) + (4 * g + e) * NB + c] = v[e];
+    }
+}
+
+// panel 0: the strip as it stands, nothing to apply first
+template <int NBLK>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void gram_panel_kernel(float* Mp, float* Vr, float* Vt, float* Tg, float* rdiag, int nblocks, int64_t batch_stride) {
+    __shared__ GramShared<NBLK> sh;
+    const int64_t off = (int64_t)blockIdx.y * batch_stride;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    f32x4_t cr[NBLK];
+#pragma unroll
+    for (int b = 0; b < NBLK; ++b) {
+        const int blk = wave + 8 * b < nblocks ? wave + 8 * b : nblocks - 1;
+        cr[b] = *reinterpret_cast<const f32x4_t*>(Mp + off + 256 * blk + (lane & 15) * 16 + 4 * (lane >> 4));
+    }
+    gram_panel_body<NBLK, 0>(sh, cr, nblocks - 1, Vr + off, Vt + off, Tg + off, rdiag + off);
 }
 
 // One launch per QR step p.  The chain of panel factorisations (one workgroup each) is the critical path, so
@@ -645,9 +908,9 @@ void qr_long_strips_kernel(QrBulkArgs a) {
 // no strip of this launch reads, and its own T: the workgroups of one launch never touch the same data.  Waves
 // of workgroup 0 that the panel does not use leave after the strip.  Q is formed afterwards (householder_qr).
 struct QrStepArgs {
-    Reflector refl[kMaxDelay];           // the current block's reflectors so far; shift = position in the block
-    int pending;                         // how many of them (the newest is refl[pending - 1], reflector p)
-    int block_done;                      // panel p is the last of its block (or of the matrix)
+    Reflector newest;                    // reflector p, shift 0
+    Reflector refl[kMaxDelay];           // what the `outer` strips apply: reflectors of the current block; shift = position in the block
+    int pending;                         // how many of them
     float* C0;                           // the columns of panel p + 1: tile (row block p, column block p + 1)
     float* Cin;                          // tile (row block p, column block p + 2): `inner` strips from here
     float* Cout;                         // tile (row block of the block's first panel, column block p + 2): `outer` strips
@@ -659,34 +922,37 @@ struct QrStepArgs {
     int64_t batch_stride;                // floats from one matrix's workspace to the next one's (grid y = matrix)
 };
 
-template <int NTHR, int R, int NBLK, int NS>
+template <int NBLK>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBLK >= 10 ? 2 : 4, NBLK >= 10 ? 2 : 4)))
 void qr_step_kernel(QrStepArgs a) {
+    __shared__ StripShared<1> strip;
     const int b = blockIdx.x;
     const int64_t off = (int64_t)blockIdx.y * a.batch_stride;
-    const Reflector* newest = a.refl + (a.pending - 1);
     if (b == 0) {
         if (a.m_next <= 0) return;
-        {
-            Reflector single = *newest; single.shift = 0;
-            reflect_strip_body<NBLK, 1>(&single, 1, off, a.C0 + off, 0, 1, a.nb_single);
-        }
-        __threadfence_block();
-        __syncthreads();                 // the strip's stores are visible to the whole workgroup
-        if (threadIdx.x >= NTHR) return;
         // the panel starts one tile (16 rows) below reflector p's first row
-        float* Mp = a.C0 + off + 256;
-        qr_panel_body<NTHR, R>(Mp, a.Vr_next + off, a.Vt_next + off, a.Tnext + off, a.rdiag_next + off, a.m_next);
+        if (a.m_next > kGramPanelRows) {
+            __shared__ GramShared<NBLK> gram;
+            reflect_strip_body<NBLK, 1>(strip, &a.newest, 1, off, a.C0 + off, 0, 1, a.nb_single, [&](f32x4_t (&cr)[1][NBLK]) {
+                gram_panel_body<NBLK, 1>(gram, cr[0], a.nb_single - 1, a.Vr_next + off, a.Vt_next + off, a.Tnext + off, a.rdiag_next + off);
+            });
+            return;
+        }
+        if constexpr (NBLK <= 5) {
+            reflect_strip_in_place<NBLK, 1>(strip, &a.newest, 1, off, a.C0 + off, 0, 1, a.nb_single);
+            __threadfence_block();
+            __syncthreads();             // the strip's stores are visible to the whole workgroup
+            if (threadIdx.x >= kGramPanelRows) return;
+            qr_panel_body<kGramPanelRows, 1>(a.C0 + off + 256, a.Vr_next + off, a.Vt_next + off, a.Tnext + off, a.rdiag_next + off, a.m_next);
+        }
         return;
     }
     if (b <= a.inner) {
-        Reflector single = *newest; single.shift = 0;
-        reflect_strip_body<NBLK, 1>(&single, 1, off, a.Cin + off + (int64_t)(b - 1) * a.strip_stride, 0, 1, a.nb_single);
+        reflect_strip_in_place<NBLK, 1>(strip, &a.newest, 1, off, a.Cin + off + (int64_t)(b - 1) * a.strip_stride, 0, 1, a.nb_single);
         return;
     }
-    // the strips behind the block, NS neighbours per workgroup
-    const int first = (b - 1 - a.inner) * NS, strips = a.outer - first < NS ? a.outer - first : NS;
-    reflect_strip_body<NBLK, NS>(a.refl, a.pending, off, a.Cout + off + (int64_t)first * a.strip_stride, a.strip_stride, strips, a.nb_block);
+    reflect_strip_in_place<NBLK, 1>(strip, a.refl, a.pending, off, a.Cout + off + (int64_t)(b - 1 - a.inner) * a.strip_stride, 0, 1,
+                                    a.nb_block);
 }
 
 // zeroes what lies beyond n x n of the tiled matrix M (n_pad x n_pad) and sets the tiled X to the identity
@@ -715,19 +981,6 @@ void pad_matrix_kernel(float* M, int64_t ld, int n, int n_pad, int identity_bloc
     const int r = blockIdx.y;
     if (c >= ld || r >= n_pad) return;
     if (r >= n || c >= n) M[(int64_t)r * ld + c] = (identity_block && r == c) ? 1.f : 0.f;
-}
-
-template <int NTHR>
-hipError_t launch_qr_panel(int rows_per_thread, float* Mp, float* Vr, float* Vt, float* Tg, float* rdiag, int m,
-                           int count, int64_t batch_stride, hipStream_t s) {
-    switch (rows_per_thread) {
-#define GELO_CASE(RR) case RR: hipLaunchKernelGGL((qr_panel_kernel<NTHR, RR>), dim3(1, count), dim3(NTHR), 0, s, Mp, Vr, Vt, Tg, rdiag, m, batch_stride); break;
-        GELO_CASE(1) GELO_CASE(2) GELO_CASE(3) GELO_CASE(4) GELO_CASE(5)
-        GELO_CASE(6) GELO_CASE(7) GELO_CASE(8) GELO_CASE(9) GELO_CASE(10)
-#undef GELO_CASE
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
 }
 
 template <int NTHR>
@@ -795,27 +1048,34 @@ hipError_t pad_matrix(float* M, int64_t ld, int n, int n_pad, int identity_block
 
 namespace {
 
-template <int NTHR, int R, int NBLK>
+template <int NBLK>
 hipError_t launch_qr_step_t(const QrStepArgs& a, int count, hipStream_t s) {
-    hipLaunchKernelGGL((qr_step_kernel<NTHR, R, NBLK, 1>), dim3(1 + a.inner + a.outer, count), dim3(512), 0, s, a);
+    hipLaunchKernelGGL((qr_step_kernel<NBLK>), dim3(1 + a.inner + a.outer, count), dim3(512), 0, s, a);
     return hipGetLastError();
 }
 
-// Can a panel with R rows per thread (NTHR threads) meet strips with NBLK blocks per wave (PREV: the next
-// smaller strip variant)?  The next panel has 16 (nb_single - 1) rows and the longest strip of the launch
-// nb_single .. nb_single + kMaxDelay - 1 blocks, so only a few pairs occur.
-constexpr bool qr_step_pair_occurs(int NTHR, int R, int NBLK, int PREV) {
-    const int min_nb = (R - 1) * NTHR / NB + 2, max_nb = R * NTHR / NB + 1 + (kMaxDelay - 1);
-    return (min_nb + 7) / 8 <= NBLK && (max_nb + 7) / 8 > PREV;
+// strip blocks per wave the step and panel kernels are built for: 5, 10, 15, 20, 30, 40
+template <class F>
+hipError_t for_strip_blocks(int per_wave, F&& f) {
+    if (per_wave <= 5) return f(std::integral_constant<int, 5>{});
+    if (per_wave <= 10) return f(std::integral_constant<int, 10>{});
+    if (per_wave <= 15) return f(std::integral_constant<int, 15>{});
+    if (per_wave <= 20) return f(std::integral_constant<int, 20>{});
+    if (per_wave <= 30) return f(std::integral_constant<int, 30>{});
+    if (per_wave <= 40) return f(std::integral_constant<int, 40>{});
+    return hipErrorInvalidValue;
 }
 
-template <int NTHR, int R>
-hipError_t launch_qr_step_r(int per_wave, const QrStepArgs& a, int count, hipStream_t s) {
-    if (per_wave <= 5) { if constexpr (qr_step_pair_occurs(NTHR, R, 5, 0)) return launch_qr_step_t<NTHR, R, 5>(a, count, s); }
-    else if (per_wave <= 10) { if constexpr (qr_step_pair_occurs(NTHR, R, 10, 5)) return launch_qr_step_t<NTHR, R, 10>(a, count, s); }
-    else if (per_wave <= 20) { if constexpr (qr_step_pair_occurs(NTHR, R, 20, 10)) return launch_qr_step_t<NTHR, R, 20>(a, count, s); }
-    else if (per_wave <= 40) { if constexpr (qr_step_pair_occurs(NTHR, R, 40, 20)) return launch_qr_step_t<NTHR, R, 40>(a, count, s); }
-    return hipErrorInvalidValue;
+hipError_t launch_first_panel(float* Mp, float* Vr, float* Vt, float* Tg, float* rdiag, int m, int count, int64_t batch_stride, hipStream_t s) {
+    if (m <= kGramPanelRows) {
+        hipLaunchKernelGGL((qr_panel_kernel<kGramPanelRows, 1>), dim3(1, count), dim3(kGramPanelRows), 0, s, Mp, Vr, Vt, Tg, rdiag, m, batch_stride);
+        return hipGetLastError();
+    }
+    const int nblocks = m / NB;
+    return for_strip_blocks((nblocks + 7) / 8, [&](auto nblk) {
+        hipLaunchKernelGGL((gram_panel_kernel<decltype(nblk)::value>), dim3(1, count), dim3(512), 0, s, Mp, Vr, Vt, Tg, rdiag, nblocks, batch_stride);
+        return hipGetLastError();
+    });
 }
 
 template <int NBLK>
@@ -851,30 +1111,8 @@ hipError_t launch_qr_bulk(const QrBulkArgs& b, int count, hipStream_t s) {
 }
 
 hipError_t launch_qr_step(const QrStepArgs& a, int count, hipStream_t s) {
-    const int longest = (a.block_done && a.outer > 0) ? a.nb_block : a.nb_single;
-    const int per_wave = (longest + 7) / 8;
-    const int m = a.m_next;
-    // (256 or 512 threads per panel made no difference at 2150 rows: what a column costs beyond its rows -
-    // reduction, broadcast, the scalar chain - is latency, not issue slots)
-    if (m <= kPanelRows256) {
-        switch ((m + 255) / 256) {
-            case 0: case 1: return launch_qr_step_r<256, 1>(per_wave, a, count, s);
-            case 2: return launch_qr_step_r<256, 2>(per_wave, a, count, s);
-            case 3: return launch_qr_step_r<256, 3>(per_wave, a, count, s);
-            default: return launch_qr_step_r<256, 4>(per_wave, a, count, s);
-        }
-    }
-    switch ((m + 511) / 512) {
-        case 3: return launch_qr_step_r<512, 3>(per_wave, a, count, s);
-        case 4: return launch_qr_step_r<512, 4>(per_wave, a, count, s);
-        case 5: return launch_qr_step_r<512, 5>(per_wave, a, count, s);
-        case 6: return launch_qr_step_r<512, 6>(per_wave, a, count, s);
-        case 7: return launch_qr_step_r<512, 7>(per_wave, a, count, s);
-        case 8: return launch_qr_step_r<512, 8>(per_wave, a, count, s);
-        case 9: return launch_qr_step_r<512, 9>(per_wave, a, count, s);
-        case 10: return launch_qr_step_r<512, 10>(per_wave, a, count, s);
-        default: return hipErrorInvalidValue;
-    }
+    const int longest = a.outer > 0 ? a.nb_block : a.nb_single;
+    return for_strip_blocks((longest + 7) / 8, [&](auto nblk) { return launch_qr_step_t<decltype(nblk)::value>(a, count, s); });
 }
 
 }  // namespace
@@ -911,29 +1149,31 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
     }
     // panel 0 on its own; then one launch per step
     if (!direct) {
-        const int m = n_pad;
-        if (m <= kPanelRows256) GELO_TRY(launch_qr_panel<256>((m + 255) / 256, ws.M, Vr_of(0), Vt_of(0), ws.Tmat, ws.rdiag, m, count, batch_stride, s));
-        else GELO_TRY(launch_qr_panel<512>((m + 511) / 512, ws.M, Vr_of(0), Vt_of(0), ws.Tmat, ws.rdiag, m, count, batch_stride, s));
+        GELO_TRY(launch_first_panel(ws.M, Vr_of(0), Vt_of(0), ws.Tmat, ws.rdiag, n_pad, count, batch_stride, s));
     }
     for (int p = 0; p < panels && !direct; ++p) {
-        const int p0 = p / D * D, i = p - p0;                 // first panel of p's block, p's position in it
+        const int p0 = p / D * D;                             // first panel of p's block
         const bool last = p + 1 == panels;
         const int block_end = p0 + D < panels ? p0 + D : panels;     // one past the block's last panel
         QrStepArgs a;
-        a.pending = i + 1;
-        for (int q = 0; q <= i; ++q) {
-            a.refl[q].Vr = Vr_of(p0 + q); a.refl[q].Vt = Vt_of(p0 + q);
-            a.refl[q].T = ws.Tmat + (int64_t)(p0 + q) * NB * NB; a.refl[q].shift = q; a.refl[q].plain_t = 0;
-        }
-        a.block_done = (p + 1 == block_end) ? 1 : 0;
+        auto reflector = [&](int q, int shift) { return Reflector{Vr_of(q), Vt_of(q), ws.Tmat + (int64_t)q * NB * NB, shift, 0}; };
+        const bool block_done = p + 1 == block_end;           // panel p is the last of its block (or of the matrix)
+        a.newest = reflector(p, 0);
         a.strip_stride = strip_stride;
         a.nb_single = nbr - p; a.nb_block = nbr - p0;
         a.C0 = last ? ws.M : ws.M + (int64_t)(p + 1) * strip_stride + (int64_t)p * 256;
         a.Cin = ws.M + (int64_t)(p + 2 < nbr ? p + 2 : 0) * strip_stride + (int64_t)p * 256;
-        a.Cout = ws.M + (int64_t)(p + 2 < nbr ? p + 2 : 0) * strip_stride + (int64_t)p0 * 256;
         // the block's panels behind p + 1 and the first panel of the next block
-        a.inner = a.block_done ? 0 : (block_end < nbr ? block_end : nbr - 1) - (p + 1);
-        a.outer = (a.block_done && p + 2 < nbr) ? nbr - (p + 2) : 0;
+        a.inner = block_done ? 0 : (block_end < nbr ? block_end : nbr - 1) - (p + 1);
+        // The columns behind the block.  Several matrices: all the block's reflectors in one pass, once it is complete.
+        // One matrix alone: each reflector at once - the strips of a launch then take less time than the panel beside
+        // them, where a strip of four reflectors takes twice as long (the traffic saved does not matter there).
+        const bool delayed = count >= kBulkFromCount;
+        const int from = block_done ? p + 2 : block_end + 1, oldest = delayed ? p0 : p;
+        a.outer = ((block_done || !delayed) && from < nbr) ? nbr - from : 0;
+        a.Cout = ws.M + (int64_t)(from < nbr ? from : 0) * strip_stride + (int64_t)p0 * 256;
+        a.pending = p - oldest + 1;
+        for (int q = 0; q < kMaxDelay; ++q) a.refl[q] = reflector(q < a.pending ? oldest + q : p, (q < a.pending ? oldest + q : p) - p0);
         a.Vr_next = Vr_of(p + 1); a.Vt_next = Vt_of(p + 1);
         a.Tnext = ws.Tmat + (int64_t)(p + 1) * NB * NB; a.rdiag_next = ws.rdiag + (p + 1) * NB;
         a.m_next = last ? 0 : n_pad - (p + 1) * NB;
@@ -942,15 +1182,15 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
         // workgroups per compute unit, which the panel's registers rule out in the step kernel).  One matrix
         // alone keeps them beside workgroup 0: there the launch count and the chain of panels are what matters.
         // Either way every column sees the same arithmetic.
-        if (count >= kBulkFromCount && a.block_done && a.outer > 0 && a.nb_block <= kBulkMaxBlocks) {
+        if (delayed && a.outer > 0 && a.nb_block <= kBulkMaxBlocks) {
             QrBulkArgs b;
             for (int q = 0; q < kMaxProduct; ++q) b.refl[q] = a.refl[q < a.pending ? q : 0];
             b.pending = a.pending; b.Cout = a.Cout; b.X = a.Cout; b.outer = a.outer; b.acc = 0;
             b.strip_stride = strip_stride; b.nb_block = a.nb_block; b.batch_stride = batch_stride; b.count = count;
             GELO_TRY(launch_qr_bulk(b, count, s));
             a.outer = 0;
-            if (last) continue;                               // no panel left: the step launch would be empty
         }
+        if (last) break;                                      // no panel and no column left
         GELO_TRY(launch_qr_step(a, count, s));
     }
     {

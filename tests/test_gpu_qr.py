@@ -38,3 +38,19 @@ def test_one_workgroup_factorisation(ctx, n):
     g.gelo_mixing_free(ctx, m)
     assert torch.equal(A_inv, A.t())
     check_orthogonal(A.double().cpu().numpy(), n, n)
+
+
+# panels built from their Gram matrix down to 64 rows: one and two of them, whole and broken tiles, and where the strips'
+# blocks per wave change (640, 1280, 1920, 2560 and 3840 rows).  One matrix alone applies each reflector to all columns at
+# once, several side by side a block of them in one pass: the same bits
+@pytest.mark.parametrize("n", [129, 143, 144, 145, 160, 161, 191, 192, 640, 641, 1280, 1281, 1920, 1921, 2561, 3841])
+def test_panels_from_gram_matrices(ctx, n):
+    first, count = 10 * n, 2
+    pair = g.gelo_sample_mixing_batch(ctx, g.GELO_ORTHOGONAL, n, 0, 64, g.GELO_F32, first, count)
+    pair = [g.gelo_mixing_export(ctx, m, n, 0, 64)[0] for m in pair]
+    other = g.gelo_create(0, 0xC0FFEE, allow_batch_reuse=False)
+    alone = g.gelo_mixing_export(other, g.gelo_sample_mixing(other, g.GELO_ORTHOGONAL, n, 0, 64, g.GELO_F32, 1e3, 64, batch_id=first + 1), n, 0, 64)[0]
+    torch.cuda.synchronize()
+    g.gelo_destroy(other)
+    assert torch.equal(pair[1], alone)
+    check_orthogonal(alone.double().cpu().numpy(), n, first + 1)
