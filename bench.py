@@ -2,7 +2,7 @@
 """Benchmark of the GELO obfuscated QKV projection on one MI355X.
 
 A "step" is one pass of the whole hot path over one batch of synthetic input that already
-sits in HBM: draw a fresh mixing matrix A (Philox + Householder QR, or LU for the
+sits in HBM: draw a fresh mixing matrix A (Philox + Householder QR, or QR and inverse for the
 non-orthogonal kinds), build the shield rows, mix U = A[H;S], project Y = U W, unmix
 Z = A^-1 Y.  Prints ONE JSON line:
   value      whole-step throughput: algorithmic FLOP of the step (chain + A generation) / time
@@ -650,8 +650,8 @@ def main() -> int:
         # A generation against the float matrix peak: the factorisations' trailing updates run on the float MFMA
         # path; their panels are bound by the latency of one workgroup, which is what keeps the fraction low
         t_gen = stage["sample"] * 1e-3
-        result["a_gen"] = {"kernel": {0: "Philox + Householder QR with explicit Q", 1: "Philox + pivoted LU + inverse + condition estimate (per accepted draw)",
-                                      2: "Householder QR + pivoted LU + inverse + condition estimate",
+        result["a_gen"] = {"kernel": {0: "Philox + Householder QR with explicit Q", 1: "Philox + Householder QR + inverse from it + condition estimate (per accepted draw)",
+                                      2: "Householder QR of the orthogonal part + QR, inverse and condition estimate of A",
                                       5: "Philox + reflectors from the raw columns + their product"}[w.kind],
                            "bound": "mfma", "flop": f_gen, "ms": t_gen * 1e3, "achieved": f_gen / t_gen / 1e12, "peak": PEAK_TFLOPS["f32"],
                            "unit": "TFLOP/s", "frac": f_gen / t_gen / 1e12 / PEAK_TFLOPS["f32"],

@@ -72,8 +72,8 @@ typedef enum { GELO_F32 = 0, GELO_BF16 = 1 } gelo_dtype;
 
 /* How A is drawn (Section 3.2 step 1.2; Section 3.2.1).
  *  ORTHOGONAL   A = Q diag(sign r_ii) from the Householder QR of a Philox Gaussian; A^-1 = A^T.
- *  GAUSSIAN     A = G/sqrt(n); redrawn until kappa_2(A) <= cond_max; A^-1 from a pivoted LU.
- *  CONDITIONED  A = Q + 0.25 G2/sqrt(n): dense, A^T A != I, kappa of a few; A^-1 from a pivoted LU.
+ *  GAUSSIAN     A = G/sqrt(n); redrawn until kappa_2(A) <= cond_max; A^-1 from its QR factors.
+ *  CONDITIONED  A = Q + 0.25 G2/sqrt(n): dense, A^T A != I, kappa of a few; A^-1 from its QR factors.
  *  STRUCTURED   A = P_3 (B D_2 P_2)(B D_1 P_1)(B D_0 P_0): Philox-drawn row permutations P_r and sign
  *               flips D_r around B, the normalised Walsh-Hadamard transform on the row blocks of the
  *               binary expansion of n.  Orthogonal (A^-1 = A^T), never formed: mix and unmix apply it in

@@ -351,7 +351,7 @@ gelo_status gelo_create(gelo_ctx** out, int device, uint64_t seed, int allow_bat
     ctx->use_graphs = std::getenv("GELO_EAGER_ATTEMPTS") == nullptr;
     if (hipHostMalloc((void**)&ctx->host_scalars, 64, hipHostMallocDefault) != hipSuccess) { delete ctx; return GELO_ENOMEM; }
     ctx->host_flag = (int*)(ctx->host_scalars + 8);
-    if (gemm_bf16_init() != hipSuccess || gemm_f32_init() != hipSuccess || lu_init() != hipSuccess ||
+    if (gemm_bf16_init() != hipSuccess || gemm_f32_init() != hipSuccess || inverse_init() != hipSuccess ||
         structured_init() != hipSuccess || small_init() != hipSuccess || gemm_fp8_init() != hipSuccess ||
         factor_init() != hipSuccess || sampler_init() != hipSuccess) {
         hipHostFree(ctx->host_scalars); delete ctx; return GELO_EHIP;
@@ -506,15 +506,13 @@ static gelo_status sample_into(gelo_ctx* ctx, gelo_mixing* m, FactorWorkspace ws
         GELO_HIP(ctx, emit_matrix(ws.X, ws.n_pad / 16, 1, ws.rdiag, n, ldk, m->A32, m->A16, m->Ainv32, m->Ainv16, s));
     } else if (kind == GELO_CONDITIONED) {
         GELO_HIP(ctx, orthogonal_into_X(false));
-        GELO_HIP(ctx, emit_matrix(ws.X, ws.n_pad / 16, 1, ws.rdiag, n, ldk, m->A32, nullptr, nullptr, nullptr, s));
         ps.c1 = kStreamPerturb << 8;
-        GELO_HIP(ctx, fill_normal(ws.M, ld, n, n, ps, 1.0f, 0, s));
-        GELO_HIP(ctx, axpy_matrix(m->A32, ldk, ws.M, ld, n, n, kConditionedBeta / std::sqrt((float)n), s));
-        GELO_HIP(ctx, emit_matrix(m->A32, ldk, 0, nullptr, n, ld, ws.M, nullptr, nullptr, nullptr, s));
-        if (bf) GELO_HIP(ctx, emit_matrix(m->A32, ldk, 0, nullptr, n, ldk, nullptr, m->A16, nullptr, nullptr, s));
-        GELO_HIP(ctx, pad_matrix(ws.M, ld, n, ws.n_pad, 1, s));
-        GELO_HIP(ctx, lu_inverse(ws, s));
-        GELO_HIP(ctx, emit_matrix(ws.X, ld, 0, nullptr, n, ldk, m->Ainv32, m->Ainv16, nullptr, nullptr, s));
+        GELO_HIP(ctx, fill_normal(ws.M, ws.n_pad / 16, n, n, ps, 1.0f, 1, s));
+        GELO_HIP(ctx, perturb_tiles(ws.M, ws.X, ws.rdiag, ws.n_pad, kConditionedBeta / std::sqrt((float)n), s));
+        GELO_HIP(ctx, emit_matrix(ws.M, ws.n_pad / 16, 1, nullptr, n, ldk, m->A32, m->A16, nullptr, nullptr, s));
+        GELO_HIP(ctx, householder_qr(ws, n, 1, 0, s));
+        GELO_HIP(ctx, inverse_from_qr(ws, n, s));
+        GELO_HIP(ctx, emit_matrix(ws.M, ld, 0, nullptr, n, ldk, m->Ainv32, m->Ainv16, nullptr, nullptr, s));
         GELO_HIP(ctx, kappa_estimate(m->A32, m->Ainv32, ldk, n, ws, kKappaSteps, s));
         GELO_HIP(ctx, hipMemcpyAsync(m->stat + 1, ws.scalars, sizeof(float), hipMemcpyDeviceToDevice, s));
         m->kappa = -1.0f;                                     // stays on the device until someone asks
@@ -551,13 +549,13 @@ static gelo_status sample_into(gelo_ctx* ctx, gelo_mixing* m, FactorWorkspace ws
                     lw[i] = ws; cA32[i] = m->A32; cAi32[i] = m->Ainv32; cA16[i] = m->A16; cAi16[i] = m->Ainv16;
                 }
                 ps.c1 = (kStreamMixing << 8) | (uint32_t)(base + i);
-                GELO_HIP(ctx, fill_normal(lw[i].M, ld, n, n, ps, 1.0f / std::sqrt((float)n), 0, ls));
+                GELO_HIP(ctx, fill_normal(lw[i].M, lw[i].n_pad / 16, n, n, ps, 1.0f / std::sqrt((float)n), 1, ls));
                 // everything behind the fill: the same launches for every attempt of this lane
                 auto factorise = [&]() -> hipError_t {
-                    hipError_t e = emit_matrix(lw[i].M, ld, 0, nullptr, n, ldk, cA32[i], cA16[i], nullptr, nullptr, ls);
-                    if (e == hipSuccess) e = pad_matrix(lw[i].M, ld, n, lw[i].n_pad, 1, ls);
-                    if (e == hipSuccess) e = lu_inverse(lw[i], ls);
-                    if (e == hipSuccess) e = emit_matrix(lw[i].X, ld, 0, nullptr, n, ldk, cAi32[i], cAi16[i], nullptr, nullptr, ls);
+                    hipError_t e = emit_matrix(lw[i].M, lw[i].n_pad / 16, 1, nullptr, n, ldk, cA32[i], cA16[i], nullptr, nullptr, ls);
+                    if (e == hipSuccess) e = householder_qr(lw[i], n, 1, 0, ls);
+                    if (e == hipSuccess) e = inverse_from_qr(lw[i], n, ls);
+                    if (e == hipSuccess) e = emit_matrix(lw[i].M, ld, 0, nullptr, n, ldk, cAi32[i], cAi16[i], nullptr, nullptr, ls);
                     if (e == hipSuccess) e = kappa_estimate(cA32[i], cAi32[i], ldk, n, lw[i], kKappaSteps, ls);
                     if (e == hipSuccess) e = hipMemcpyAsync(ctx->host_scalars + i, lw[i].scalars, sizeof(float), hipMemcpyDeviceToHost, ls);
                     if (e == hipSuccess) e = hipMemcpyAsync(ctx->host_flag + i, lw[i].flag, sizeof(int), hipMemcpyDeviceToHost, ls);

@@ -1,6 +1,6 @@
 // Blocked Householder QR with explicit Q: the orthogonal mixing matrix the trusted side draws
 // for every batch (Section 3.2 step 1.2; Table 3's "A-gen (QR)" step), and the workspace shared
-// with the LU path.  Everything is float and deterministic: reductions run in a fixed order, no
+// with the inverse of the non-orthogonal kinds, which is built on the same factorisation.  Everything is float and deterministic: reductions run in a fixed order, no
 // atomics.
 //
 // Column panels are 16 wide.  A panel is factorised by ONE workgroup, from its 16 x 16 Gram matrix while it is tall
@@ -96,7 +96,7 @@ __device__ __forceinline__ float lane_value(float v) {
 // not see the earlier reflectors - which is what the product of directly drawn reflectors needs (householder_qr with
 // `direct`): the same reflector formulas, the same T, no factorisation.
 template <int NTHR, int R, bool UPDATE = true>
-__device__ __forceinline__ void qr_panel_body(float* Mp, float* Vr, float* Vt, float* Tg, float* rdiag, int m) {
+__device__ __forceinline__ void qr_panel_body(float* Mp, float* Vr, float* Vt, float* Tg, float* Rd, float* rdiag, int m) {
     constexpr int NW = NTHR / 64;
     __shared__ float red[2][NW][NB];
     __shared__ float prow[2][NB];
@@ -206,8 +206,16 @@ __device__ __forceinline__ void qr_panel_body(float* Mp, float* Vr, float* Vt, f
                 make_float4(Trow[c4 * 4], Trow[c4 * 4 + 1], Trow[c4 * 4 + 2], Trow[c4 * 4 + 3]);
     }
 
-    // write the clean reflector block in its two layouts (the factored panel itself - R and the reflector tails -
-    // is not stored: nobody reads these columns again, the diagonal of R went to rdiag)
+    // R's diagonal tile: thread t < 16 has row t in its first register row
+    if constexpr (UPDATE) {
+        if (tid < NB) {
+#pragma unroll
+            for (int s = 0; s < NB; ++s) Rd[tid * NB + s] = s >= tid ? P[0][s] : 0.f;
+        }
+    }
+
+    // write the clean reflector block in its two layouts, in place of the factored panel (nobody reads these columns
+    // again; R's tile went to Rd, its diagonal to rdiag)
 #pragma unroll
     for (int i = 0; i < R; ++i) {
         const int r = tid + i * NTHR;
@@ -230,9 +238,9 @@ __device__ __forceinline__ void qr_panel_body(float* Mp, float* Vr, float* Vt, f
 // a matrix of one short panel, or the first panel of such a matrix
 template <int NTHR, int R>
 __global__ __launch_bounds__(NTHR)
-void qr_panel_kernel(float* Mp, float* Vr, float* Vt, float* Tg, float* rdiag, int m, int64_t batch_stride) {
+void qr_panel_kernel(float* Mp, float* Vr, float* Vt, float* Tg, float* Rd, float* rdiag, int m, int64_t batch_stride) {
     const int64_t off = (int64_t)blockIdx.y * batch_stride;
-    qr_panel_body<NTHR, R>(Mp + off, Vr + off, Vt + off, Tg + off, rdiag + off, m);
+    qr_panel_body<NTHR, R>(Mp + off, Vr + off, Vt + off, Tg + off, Rd + off, rdiag + off, m);
 }
 
 // All the panels of a matrix at once, every reflector from the raw column (grid x = panel, grid y = matrix): panel p
@@ -244,7 +252,7 @@ void direct_panels_kernel(float* M, float* Vc, float* Tmat, float* rdiag, int nb
     const int p = blockIdx.x;
     const int64_t off = (int64_t)blockIdx.y * batch_stride;
     float* Mp = M + off + (int64_t)p * nbr * 256 + (int64_t)p * 256;
-    qr_panel_body<NTHR, R, false>(Mp, Vc + off + (int64_t)p * nbr * 16 * NB, Mp, Tmat + off + (int64_t)p * NB * NB, rdiag + off + p * NB, (nbr - p) * NB);
+    qr_panel_body<NTHR, R, false>(Mp, Vc + off + (int64_t)p * nbr * 16 * NB, Mp, Tmat + off + (int64_t)p * NB * NB, nullptr, rdiag + off + p * NB, (nbr - p) * NB);
 }
 
 // ------------------------------------------------- fused block-reflector update --
@@ -722,7 +730,7 @@ __device__ __forceinline__ f32x4_t rows_of_group(const float (&col)[NB], int g) 
 // The steps on the 16 x 16 matrices are the work of wave 0 alone (on every wave they took twice as long: two waves share
 // a SIMD's issue slots); the others turn their tiles around meanwhile.
 template <int NBLK, int FIRST>
-__device__ __forceinline__ void gram_panel_body(GramShared<NBLK>& sh, f32x4_t (&cr)[NBLK], int last, float* Vr, float* Vt, float* Tg, float* rdiag) {
+__device__ __forceinline__ void gram_panel_body(GramShared<NBLK>& sh, f32x4_t (&cr)[NBLK], int last, float* Vr, float* Vt, float* Tg, float* Rd, float* rdiag) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g = lane >> 4;
     // P2^T P2 of this wave's blocks: register e of a block is row 4 g + e of column c, which is what lane (g, c) supplies
@@ -761,7 +769,7 @@ __device__ __forceinline__ void gram_panel_body(GramShared<NBLK>& sh, f32x4_t (&
         for (int e = 0; e < 4; ++e) t[(4 * g + e) * kTilePitch + c] = v[e];
     };
     auto get = [&](const float* t) { return *reinterpret_cast<const f32x4_t*>(t + c * kTilePitch + 4 * g); };
-    f32x4_t gb = {0.f, 0.f, 0.f, 0.f}, xd, ld, xs;
+    f32x4_t gb = {0.f, 0.f, 0.f, 0.f}, xd, ld, xs, rd;
     float scale_c = 0.f, beta_c = 0.f;                        // of this lane's own column (wave 0)
     if (wave == 0) {
 #pragma unroll
@@ -790,6 +798,7 @@ __device__ __forceinline__ void gram_panel_body(GramShared<NBLK>& sh, f32x4_t (&
             const float h = c > j ? -Gc[j] * (irn * irn) : 0.f;
             const float f = c > j ? fmaf(Gc[j], ibeta, -Pc[j]) * scale : 0.f;
             if (c == j) { scale_c = scale; beta_c = beta; }
+            Gc[j] = c > j ? Gc[j] * ibeta : (c == j ? beta : 0.f);      // row j of R: nobody reads row j of G again
             add_column<j, j + 1, NB>(Gc, h);
             add_column<j, j + 1, NB>(Pc, f);
             add_column<j, 0, j + 1>(Xc, f);
@@ -809,6 +818,7 @@ __device__ __forceinline__ void gram_panel_body(GramShared<NBLK>& sh, f32x4_t (&
         ld = rows_of_group(Pc, g);
         *reinterpret_cast<f32x4_t*>(sh.X[lane]) = xd;
         *reinterpret_cast<f32x4_t*>(sh.L[lane]) = ld;
+        rd = rows_of_group(Gc, g);
     } else {
 #pragma unroll
         for (int b0 = 0; b0 < NBLK; b0 += kPanelGroup) {
@@ -855,7 +865,7 @@ __device__ __forceinline__ void gram_panel_body(GramShared<NBLK>& sh, f32x4_t (&
         });
         const f32x4_t td = rows_of_group(Tc, g);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) Tg[(4 * g + e) * NB + c] = td[e] * tau_c;
+        for (int e = 0; e < 4; ++e) { Tg[(4 * g + e) * NB + c] = td[e] * tau_c; Rd[(4 * g + e) * NB + c] = rd[e]; }
         if (g == 0) rdiag[c] = beta_c;
 #pragma unroll
         for (int b = 0; b < NBLK; ++b) if (8 * b <= last) cr[b] = get(sh.first[b]);
@@ -880,7 +890,7 @@ __device__ __forceinline__ void gram_panel_body(GramShared<NBLK>& sh, f32x4_t (&
 // panel 0: the strip as it stands, nothing to apply first
 template <int NBLK>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void gram_panel_kernel(float* Mp, float* Vr, float* Vt, float* Tg, float* rdiag, int nblocks, int64_t batch_stride) {
+void gram_panel_kernel(float* Mp, float* Vr, float* Vt, float* Tg, float* Rd, float* rdiag, int nblocks, int64_t batch_stride) {
     __shared__ GramShared<NBLK> sh;
     const int64_t off = (int64_t)blockIdx.y * batch_stride;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -890,7 +900,7 @@ void gram_panel_kernel(float* Mp, float* Vr, float* Vt, float* Tg, float* rdiag,
         const int blk = wave + 8 * b < nblocks ? wave + 8 * b : nblocks - 1;
         cr[b] = *reinterpret_cast<const f32x4_t*>(Mp + off + 256 * blk + (lane & 15) * 16 + 4 * (lane >> 4));
     }
-    gram_panel_body<NBLK, 0>(sh, cr, nblocks - 1, Vr + off, Vt + off, Tg + off, rdiag + off);
+    gram_panel_body<NBLK, 0>(sh, cr, nblocks - 1, Vr + off, Vt + off, Tg + off, Rd + off, rdiag + off);
 }
 
 // One launch per QR step p.  The chain of panel factorisations (one workgroup each) is the critical path, so
@@ -917,7 +927,7 @@ struct QrStepArgs {
     int64_t strip_stride;                // floats between the tiles of neighbouring column blocks
     int nb_single, nb_block;             // rows / 16 below the first row of reflector p / of the block's first reflector
     int inner, outer;                    // strip counts
-    float* Vr_next; float* Vt_next; float* Tnext; float* rdiag_next;   // outputs of panel p + 1
+    float* Vr_next; float* Vt_next; float* Tnext; float* Rd_next; float* rdiag_next;   // outputs of panel p + 1
     int m_next;                          // its row count (0: no further panel)
     int64_t batch_stride;                // floats from one matrix's workspace to the next one's (grid y = matrix)
 };
@@ -934,7 +944,9 @@ void qr_step_kernel(QrStepArgs a) {
         if (a.m_next > kGramPanelRows) {
             __shared__ GramShared<NBLK> gram;
             reflect_strip_body<NBLK, 1>(strip, &a.newest, 1, off, a.C0 + off, 0, 1, a.nb_single, [&](f32x4_t (&cr)[1][NBLK]) {
-                gram_panel_body<NBLK, 1>(gram, cr[0], a.nb_single - 1, a.Vr_next + off, a.Vt_next + off, a.Tnext + off, a.rdiag_next + off);
+                // block 0 is a finished tile of R; the rest becomes the reflectors
+                if (threadIdx.x < 64) *reinterpret_cast<f32x4_t*>(a.C0 + off + (threadIdx.x & 15) * 16 + 4 * (threadIdx.x >> 4)) = cr[0][0];
+                gram_panel_body<NBLK, 1>(gram, cr[0], a.nb_single - 1, a.Vr_next + off, a.Vt_next + off, a.Tnext + off, a.Rd_next + off, a.rdiag_next + off);
             });
             return;
         }
@@ -943,7 +955,7 @@ void qr_step_kernel(QrStepArgs a) {
             __threadfence_block();
             __syncthreads();             // the strip's stores are visible to the whole workgroup
             if (threadIdx.x >= kGramPanelRows) return;
-            qr_panel_body<kGramPanelRows, 1>(a.C0 + off + 256, a.Vr_next + off, a.Vt_next + off, a.Tnext + off, a.rdiag_next + off, a.m_next);
+            qr_panel_body<kGramPanelRows, 1>(a.C0 + off + 256, a.Vr_next + off, a.Vt_next + off, a.Tnext + off, a.Rd_next + off, a.rdiag_next + off, a.m_next);
         }
         return;
     }
@@ -976,11 +988,11 @@ void set_identity_kernel(float* X, int64_t ld, int n_pad) {
 }
 
 __global__ __launch_bounds__(256)
-void pad_matrix_kernel(float* M, int64_t ld, int n, int n_pad, int identity_block) {
+void pad_matrix_kernel(float* M, int64_t ld, int n, int n_pad) {
     const int c = blockIdx.x * 256 + threadIdx.x;
     const int r = blockIdx.y;
     if (c >= ld || r >= n_pad) return;
-    if (r >= n || c >= n) M[(int64_t)r * ld + c] = (identity_block && r == c) ? 1.f : 0.f;
+    if (r >= n || c >= n) M[(int64_t)r * ld + c] = 0.f;
 }
 
 template <int NTHR>
@@ -1001,8 +1013,8 @@ hipError_t launch_direct_panels(int rows_per_thread, const FactorWorkspace& ws, 
 
 size_t factor_workspace_bytes(int n) {
     const int64_t n_pad = round_up(n, NB), ld = round_up(n, 64);
-    const int64_t floats = 3 * n_pad * ld + n_pad * NB + 2 * n_pad * kLuBlock + n_pad + 8 * ld + 256 + 64;
-    return (size_t)floats * sizeof(float) + (size_t)(n_pad + 256) * sizeof(int) + 8192;
+    const int64_t floats = 3 * n_pad * ld + 2 * n_pad * NB + n_pad * kInvBlock + n_pad + 8 * ld + 256 + 64;
+    return (size_t)floats * sizeof(float) + 8192;
 }
 
 void factor_workspace_carve(void* base, int n, FactorWorkspace* ws) {
@@ -1013,13 +1025,12 @@ void factor_workspace_carve(void* base, int n, FactorWorkspace* ws) {
     ws->X = take(n_pad * ld);
     ws->Vc = take(n_pad * ld);
     ws->Tmat = take(n_pad * NB);
-    ws->Dinv = take(2 * n_pad * kLuBlock);
+    ws->Rd = take(n_pad * NB);
+    ws->Dinv = take(n_pad * kInvBlock);
     ws->rdiag = take(n_pad);
     ws->vec = take(8 * ld);
     ws->tri = take(128);
     ws->scalars = take(16);
-    ws->perm = (int*)take(n_pad);
-    ws->gat = (int*)take(128);
     ws->flag = (int*)take(16);
     ws->n_pad = (int)n_pad;
     ws->ld = ld;
@@ -1040,9 +1051,9 @@ hipError_t set_identity(float* X, int64_t ld, int n_pad, hipStream_t stream) {
     return hipGetLastError();
 }
 
-hipError_t pad_matrix(float* M, int64_t ld, int n, int n_pad, int identity_block, hipStream_t stream) {
+hipError_t pad_matrix(float* M, int64_t ld, int n, int n_pad, hipStream_t stream) {
     hipLaunchKernelGGL(pad_matrix_kernel, dim3((unsigned)((ld + 255) / 256), n_pad), dim3(256), 0, stream,
-                       M, ld, n, n_pad, identity_block);
+                       M, ld, n, n_pad);
     return hipGetLastError();
 }
 
@@ -1066,14 +1077,14 @@ hipError_t for_strip_blocks(int per_wave, F&& f) {
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_first_panel(float* Mp, float* Vr, float* Vt, float* Tg, float* rdiag, int m, int count, int64_t batch_stride, hipStream_t s) {
+hipError_t launch_first_panel(float* Mp, float* Vr, float* Vt, float* Tg, float* Rd, float* rdiag, int m, int count, int64_t batch_stride, hipStream_t s) {
     if (m <= kGramPanelRows) {
-        hipLaunchKernelGGL((qr_panel_kernel<kGramPanelRows, 1>), dim3(1, count), dim3(kGramPanelRows), 0, s, Mp, Vr, Vt, Tg, rdiag, m, batch_stride);
+        hipLaunchKernelGGL((qr_panel_kernel<kGramPanelRows, 1>), dim3(1, count), dim3(kGramPanelRows), 0, s, Mp, Vr, Vt, Tg, Rd, rdiag, m, batch_stride);
         return hipGetLastError();
     }
     const int nblocks = m / NB;
     return for_strip_blocks((nblocks + 7) / 8, [&](auto nblk) {
-        hipLaunchKernelGGL((gram_panel_kernel<decltype(nblk)::value>), dim3(1, count), dim3(512), 0, s, Mp, Vr, Vt, Tg, rdiag, nblocks, batch_stride);
+        hipLaunchKernelGGL((gram_panel_kernel<decltype(nblk)::value>), dim3(1, count), dim3(512), 0, s, Mp, Vr, Vt, Tg, Rd, rdiag, nblocks, batch_stride);
         return hipGetLastError();
     });
 }
@@ -1149,7 +1160,7 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
     }
     // panel 0 on its own; then one launch per step
     if (!direct) {
-        GELO_TRY(launch_first_panel(ws.M, Vr_of(0), Vt_of(0), ws.Tmat, ws.rdiag, n_pad, count, batch_stride, s));
+        GELO_TRY(launch_first_panel(ws.M, Vr_of(0), Vt_of(0), ws.Tmat, ws.Rd, ws.rdiag, n_pad, count, batch_stride, s));
     }
     for (int p = 0; p < panels && !direct; ++p) {
         const int p0 = p / D * D;                             // first panel of p's block
@@ -1175,7 +1186,7 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
         a.pending = p - oldest + 1;
         for (int q = 0; q < kMaxDelay; ++q) a.refl[q] = reflector(q < a.pending ? oldest + q : p, (q < a.pending ? oldest + q : p) - p0);
         a.Vr_next = Vr_of(p + 1); a.Vt_next = Vt_of(p + 1);
-        a.Tnext = ws.Tmat + (int64_t)(p + 1) * NB * NB; a.rdiag_next = ws.rdiag + (p + 1) * NB;
+        a.Tnext = ws.Tmat + (int64_t)(p + 1) * NB * NB; a.Rd_next = ws.Rd + (int64_t)(p + 1) * NB * NB; a.rdiag_next = ws.rdiag + (p + 1) * NB;
         a.m_next = last ? 0 : n_pad - (p + 1) * NB;
         a.batch_stride = batch_stride;
         // Several matrices side by side: the strips that apply a finished block get a launch of their own (two

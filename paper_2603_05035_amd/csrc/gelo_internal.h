@@ -11,9 +11,9 @@
 
 namespace gelo {
 
-constexpr int kPanel = 16;          // column-panel width of the QR / LU factorisations
+constexpr int kPanel = 16;          // column-panel width of the QR
 constexpr int kMaxN = 5120;         // 512 threads x 10 register-resident rows in the panel kernels
-constexpr int kLuBlock = 128;       // outer block width of the LU: trailing updates are GEMMs with K = 128
+constexpr int kInvBlock = 128;      // block width of the inverse's back substitution: its updates are GEMMs with K = 128
 
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
@@ -54,7 +54,7 @@ hipError_t gemm_bf16_batched(const GemmOperands* g, int count, hipStream_t strea
 hipError_t gemm_f32(const GemmOperands& g, hipStream_t stream);
 hipError_t gemm_bf16_init();        // one-time kernel attribute set-up (large dynamic LDS)
 hipError_t gemm_f32_init();
-hipError_t lu_init();
+hipError_t inverse_init();
 hipError_t factor_init();
 hipError_t sampler_init();
 
@@ -147,9 +147,8 @@ hipError_t matrix_rate_launch(int fp8, int iters, float* scratch, double* flop, 
 hipError_t philox_words(uint32_t* words, uint32_t first_block, uint32_t blocks, PhiloxStream ps, hipStream_t stream);
 // GS[k x d] (pitch d) = N(0,1) with fill_normal's element order, gsnorm[i] = || GS[i, :] ||_2; d % 8 == 0
 hipError_t shield_directions(float* GS, int k, int d, PhiloxStream ps, float* gsnorm, hipStream_t stream);
-// dst[r * ldd + c] += scale * src[r * lds + c] over an rows x cols block
-hipError_t axpy_matrix(float* dst, int64_t ldd, const float* src, int64_t lds, int rows, int cols,
-                       float scale, hipStream_t stream);
+// tiles of A = Q diag(sign rdiag) + scale G: G (in 16 x 16 tiles with n_pad / 16 tile rows) is overwritten by A
+hipError_t perturb_tiles(float* G, const float* Q, const float* rdiag, int n_pad, float scale, hipStream_t stream);
 // norms[r] = || X[r, 0:cols] ||_2, X float or bf16
 hipError_t row_norms(const void* X, int is_bf16, int64_t ld, int rows, int cols, float* norms,
                      hipStream_t stream);
@@ -224,12 +223,11 @@ struct FactorWorkspace {
     float* X;        // the result being accumulated (Q, or A^-1)
     float* Vc;       // QR: two alternating pairs of compact reflector blocks (n_pad x 16 and 16 x n_pad)
     float* Tmat;     // per panel: the 16 x 16 triangle T of the block reflector I - V T V^T
-    float* Dinv;     // LU: inverses of the diagonal blocks of L, then of U (pitch kLuBlock, n_pad rows each)
+    float* Rd;       // QR: the 16 x 16 diagonal tiles of R, row-major (its other tiles stay in M, above the reflectors)
+    float* Dinv;     // inverses of R's diagonal blocks (pitch kInvBlock, n_pad rows)
     float* rdiag;    // n_pad: diagonal of R
     float* vec;      // 8 * ld floats: the Lanczos vectors of the condition estimate
     float* tri;      // its tridiagonal coefficients (2 operators x (alpha, beta) x 32)
-    int*   perm;     // LU: perm[i] = row of the input that the interchanges brought to row i
-    int*   gat;      // LU: two alternating lists of 32 (destination, source) row pairs, one per panel
     int*   flag;     // singular-pivot flag
     float* scalars;  // [0] kappa estimate, [1] sigma_max, [2] 1 / sigma_min
     int n_pad; int64_t ld;
@@ -246,9 +244,9 @@ void factor_workspace_carve(void* base, int n, FactorWorkspace* ws);
 // stands (rows k onward), so ws.X becomes the product H_0 H_1 ... H_{n-1} of directly drawn reflectors and
 // ws.rdiag the values beta_k those reflectors map their columns to; no chain of dependent panels.
 hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t batch_stride, hipStream_t stream, bool direct = false);
-// ws.M holds an n_pad x n_pad matrix with an identity block in the padding.  On return ws.X holds
-// its inverse (via row-pivoted LU), *ws.flag != 0 if a zero pivot was met.
-hipError_t lu_inverse(const FactorWorkspace& ws, hipStream_t stream);
+// Behind householder_qr(ws, n, 1, ..., direct = false) of a matrix A: leaves A^-1 = R^-1 Q^T in ws.M, row-major with pitch
+// ws.ld (zero in rows [n, n_pad)); *ws.flag != 0 if R has a zero on its diagonal.  Overwrites ws.Vc and ws.Dinv.
+hipError_t inverse_from_qr(const FactorWorkspace& ws, int n, hipStream_t stream);
 // kappa_2 estimate of the n x n matrix A (lda) with inverse Ainv: sigma_max of both by `steps`
 // (at most 32) Lanczos steps on A^T A and Ainv^T Ainv; uses ws.M / ws.X as scratch for the two
 // transposes; result in ws.scalars[0].
@@ -256,7 +254,7 @@ hipError_t kappa_estimate(const float* A, const float* Ainv, int64_t lda, int n,
                           int steps, hipStream_t stream);
 hipError_t set_identity(float* X, int64_t ld, int n_pad, hipStream_t stream);
 hipError_t zero_ints(int* p, int count, hipStream_t stream);
-// zero rows/cols [n, n_pad) of M; optionally put ones on that part of the diagonal
-hipError_t pad_matrix(float* M, int64_t ld, int n, int n_pad, int identity_block, hipStream_t stream);
+// zero rows/cols [n, n_pad) of M
+hipError_t pad_matrix(float* M, int64_t ld, int n, int n_pad, hipStream_t stream);
 
 }  // namespace gelo

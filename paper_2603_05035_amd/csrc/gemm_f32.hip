@@ -2,7 +2,7 @@
 // single-precision GELO chain (Section 3.2, eqs. 1-3): C[M x N] = A[M x K] * B[K x N],
 // all row-major, B optionally split into two row segments ([H ; S]); optionally C <- C - A * B.
 // A tile reads all of its B columns before it stores, so with M <= 128 the product may
-// overwrite B in place (C == B0, K == M): the LU path's multiplications by a diagonal-block inverse
+// overwrite B in place (C == B0, K == M): the back substitution's multiplications by a diagonal-block inverse
 // (those shapes take the short kernel at the end of this file, which has the same property).
 //
 // A workgroup of 4 waves owns a 128 x 96, 128 x 128 or 128 x 192 tile (whichever fills whole
@@ -29,7 +29,7 @@ struct F32Args {
     float* C;        int64_t ldc;
     int M, N, K;
     int tiles_m, tiles_n;
-    int subtract;              // C <- C - A B (the LU's trailing and substitution updates)
+    int subtract;              // C <- C - A B (the back substitution's updates)
 };
 
 // BN = 96, 128 or 192: the tile width is picked per shape so that the tile count fills whole rounds of the chip's CUs.
@@ -198,7 +198,7 @@ void gemm_f32_kernel(F32Args g) {
         }
 }
 
-// M <= 128 and K <= 128 (K a multiple of 16): the LU path's multiplications by the inverse of a
+// M <= 128 and K <= 128 (K a multiple of 16): the back substitution's multiplications by the inverse of a
 // diagonal block.  One 128 x 128 tile per 128 columns would leave most of the chip idle and each
 // tile bound by the float MFMA rate of its one CU, so the tiles here are 128 x 32 (four times as
 // many workgroups, a wave owns 32 x 32), and with so few K steps both panels of the tile are
@@ -297,7 +297,7 @@ hipError_t gemm_f32(const GemmOperands& o, hipStream_t stream) {
         return hipGetLastError();
     }
     // Tile width.  Large K: 128 x 96 tiles, two workgroups per CU (cost: rounds of 512 tiles), unless a wider
-    // tile wastes less of its last round over the 256 CUs; short K (the LU's updates, bound by the
+    // tile wastes less of its last round over the 256 CUs; short K (the back substitution's updates, bound by the
     // read-modify-write of C): the wide tiles only.
     constexpr int kCus = 256;
     auto tiles = [&](int bn) { return a.tiles_m * ((o.N + bn - 1) / bn); };

@@ -1,0 +1,327 @@
+// The explicit inverse and the kappa_2 estimate (Lanczos) behind the non-orthogonal mixing matrices (Section 3.2.1,
+// Mitigation 1: a well-conditioned non-orthogonal A, generated and verified; Section 3.2 eq. 3 needs A^-1 explicitly so
+// that un-mixing is one GEMM).  Everything is float and deterministic: reductions run in a fixed order, no atomics.
+//
+// A^-1 = R^-1 Q^T from the Householder QR of A (factor.hip): no pivot searches and row interchanges, whose chain - two
+// barriers per column, 1.1 us of one workgroup - bounded a row-pivoted LU in this place (512 rows: 1.1 ms of kernels
+// without the condition estimate, here 0.45; 4096 rows: 15.5 ms, here 11).  Q^T is the right-hand side of a block back
+// substitution with R: the inverses of R's 128 x 128 diagonal blocks come from one launch, everything else is float GEMMs
+// with K = 128.  The QR needs no pivots for its accuracy, whatever A is, except that its panels are built from Gram
+// matrices (gram_panel_body): a panel's condition number is at most A's, times a panel of Gaussians' for the GAUSSIAN kind.
+#include "gelo_internal.h"
+
+namespace gelo {
+namespace {
+
+constexpr int NB = kPanel;
+constexpr int BW = kInvBlock;
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ float wave_sum(float v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+// ------------------------------------------------ inverses of R's diagonal blocks --
+// One workgroup per 128 x 128 diagonal block of R (upper triangular; tiles above the diagonal in M, diagonal tiles in Rd;
+// the identity beyond n).  The 16 x 16 diagonal tiles are inverted by back substitution, one thread per column; then
+// twice the size at a time: [A B; 0 C]^-1 = [A^-1, -A^-1 B C^-1; 0, C^-1].  Dinv: row-major, pitch BW, zeros below the diagonal.
+constexpr int IP = BW + 4;                                // LDS pitch, floats
+constexpr size_t kDiagLds = 2 * (size_t)BW * IP * sizeof(float);
+
+__global__ __launch_bounds__(512)
+void diag_inverse_kernel(const float* M, const float* Rd, float* Dinv, int nbr, int n, int* flag) {
+    extern __shared__ __attribute__((aligned(16))) float diag_lds[];
+    float* U = diag_lds;
+    float* I = diag_lds + BW * IP;
+    constexpr int TB = BW / NB;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int t0 = blockIdx.x * TB;                       // the block's first tile
+    for (int t = wave; t < TB * TB; t += 8) {
+        const int i = t / TB, j = t % TB;                 // tile (i, j) of the block
+        if (j < i) continue;
+        const int c = lane & 15, g = lane >> 4;
+        if (i < j) {
+            f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+            if (t0 + j < nbr) v = *reinterpret_cast<const f32x4_t*>(M + ((int64_t)(t0 + j) * nbr + t0 + i) * 256 + c * 16 + 4 * g);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) U[(i * NB + 4 * g + e) * IP + j * NB + c] = v[e];
+        } else {
+            const int r = lane >> 2, q = (lane & 3) * 4;
+            f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+            if (t0 + i < nbr) v = *reinterpret_cast<const f32x4_t*>(Rd + (int64_t)(t0 + i) * 256 + r * NB + q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) if ((t0 + i) * NB + r >= n) v[e] = q + e == r ? 1.f : 0.f;
+            *reinterpret_cast<f32x4_t*>(&U[(i * NB + r) * IP + j * NB + q]) = v;
+        }
+    }
+    __syncthreads();
+    if (tid < BW) {
+        const int o = tid & ~15, j = tid & 15;
+        float x[NB];
+#pragma unroll
+        for (int i = NB - 1; i >= 0; --i) {
+            float t = i == j ? 1.f : 0.f;
+#pragma unroll
+            for (int k = i + 1; k < NB; ++k) t = fmaf(-U[(o + i) * IP + o + k], x[k], t);
+            const float u = U[(o + i) * IP + o + i];
+            if (i == j && !(fabsf(u) > 0.f)) *flag = 1;
+            x[i] = t / u;
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) I[(o + i) * IP + o + j] = x[i];
+    }
+    __syncthreads();
+    // a thread owns 8 rows of one column; B C^-1 waits in the unused lower triangle
+    for (int s = NB; s < BW; s *= 2) {
+        const int outs = BW * s / 16;                     // (BW / 2 s) pairs x s columns x s / 8 row groups
+        const int c = tid % s, r0 = tid / s % (s / 8) * 8, o1 = tid / (s * s / 8) * 2 * s, o2 = o1 + s;
+        float acc[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+        if (tid < outs) {
+            for (int k = 0; k < s; k += 4) {
+                float x[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { const float y = I[(o2 + k + e) * IP + o2 + c]; x[e] = k + e <= c ? y : 0.f; }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const f32x4_t a = *reinterpret_cast<const f32x4_t*>(&U[(o1 + r0 + i) * IP + o2 + k]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[i] = fmaf(a[e], x[e], acc[i]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) I[(o2 + r0 + i) * IP + o1 + c] = acc[i];
+        }
+        __syncthreads();
+        if (tid < outs) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+            for (int k = 0; k < s; k += 4) {
+                float x[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = I[(o2 + k + e) * IP + o1 + c];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const f32x4_t a = *reinterpret_cast<const f32x4_t*>(&I[(o1 + r0 + i) * IP + o1 + k]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[i] = fmaf(k + e >= r0 + i ? a[e] : 0.f, x[e], acc[i]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) I[(o1 + r0 + i) * IP + o2 + c] = -acc[i];
+        }
+        __syncthreads();
+    }
+    for (int id = tid; id < BW * BW; id += 512) {
+        const int r = id / BW, c = id % BW;
+        if (t0 * NB + r < nbr * NB) Dinv[((int64_t)t0 * NB + r) * BW + c] = c >= r ? I[r * IP + c] : 0.f;
+    }
+}
+
+// ------------------------------------------------------------------ Lanczos --
+// sigma_max of a matrix M from a few steps of the Lanczos recurrence on M^T M (no
+// reorthogonalisation: the largest Ritz value converges first and never overshoots).  The two
+// operators the condition number needs, A and A^-1, share every launch.
+constexpr int kLanczosMax = 32;      // coefficient slots per operator
+
+// Two matrix-vector products per launch, one wave per row: rows [0, n) give ya = Ma xa,
+// rows [n, 2n) give yb = Mb xb.
+__global__ __launch_bounds__(256)
+void matvec_pair_kernel(const float* Ma, int64_t lda, const float* xa, float* ya,
+                        const float* Mb, int64_t ldb, const float* xb, float* yb, int n) {
+    int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (row >= 2 * n) return;
+    const bool second = row >= n;
+    row -= second ? n : 0;
+    const float* mr = second ? Mb + (int64_t)row * ldb : Ma + (int64_t)row * lda;
+    const float* x = second ? xb : xa;
+    float dot = 0.f;
+    for (int c = lane; c < n; c += 64) dot = fmaf(mr[c], x[c], dot);
+    dot = wave_sum(dot);
+    if (lane == 0) (second ? yb : ya)[row] = dot;
+}
+
+// sum over the 1024 threads of a workgroup, the same value in every thread, fixed order
+__device__ __forceinline__ float block_sum_1024(float v, float* red) {
+    v = wave_sum(v);
+    __syncthreads();                                   // red may still be read from the previous call
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) s += red[w];
+    return s;
+}
+
+constexpr int kVecPerThread = kMaxN / 1024;            // 5
+
+// Workgroup o (0: A, 1: A^-1) owns the vectors at vec + o * 4 * ld: v, v_prev, y, w.
+// step < 0: v = a fixed pseudo-random unit vector, v_prev = 0.
+// step >= 0: alpha = w . v, r = w - alpha v - beta_prev v_prev, beta = |r|, v_prev = v, v = r / beta;
+//            tri[o][0][step] = alpha, tri[o][1][step] = beta.
+__global__ __launch_bounds__(1024)
+void lanczos_vector_kernel(float* vec, int64_t ld, int n, float* tri, int step) {
+    __shared__ float red[16];
+    const int tid = threadIdx.x, o = blockIdx.x;
+    float* v = vec + (int64_t)o * 4 * ld;
+    float* vp = v + ld;
+    const float* w = v + 3 * ld;
+    float* tr = tri + o * 2 * kLanczosMax;
+    float x[kVecPerThread], xp[kVecPerThread], r[kVecPerThread];
+    if (step < 0) {
+        float ss = 0.f;
+#pragma unroll
+        for (int k = 0; k < kVecPerThread; ++k) {
+            const int i = tid + 1024 * k;
+            uint32_t h = (uint32_t)i * 2654435761u + 0x9E3779B9u;   // fixed pseudo-random signs and sizes
+            h ^= h >> 15; h *= 2246822519u; h ^= h >> 13;
+            x[k] = i < n ? ((h & 1u) ? 1.f : -1.f) * (0.5f + (float)((h >> 8) & 0xFFFF) * (1.0f / 65536.0f)) : 0.f;
+            ss = fmaf(x[k], x[k], ss);
+        }
+        const float inv = rsqrtf(block_sum_1024(ss, red));
+#pragma unroll
+        for (int k = 0; k < kVecPerThread; ++k) {
+            const int i = tid + 1024 * k;
+            if (i < n) { v[i] = x[k] * inv; vp[i] = 0.f; }
+        }
+        return;
+    }
+    float dot = 0.f;
+#pragma unroll
+    for (int k = 0; k < kVecPerThread; ++k) {
+        const int i = tid + 1024 * k;
+        x[k] = i < n ? v[i] : 0.f;
+        xp[k] = i < n ? vp[i] : 0.f;
+        r[k] = i < n ? w[i] : 0.f;
+        dot = fmaf(r[k], x[k], dot);
+    }
+    const float alpha = block_sum_1024(dot, red);
+    const float beta_prev = step > 0 ? tr[kLanczosMax + step - 1] : 0.f;
+    float ss = 0.f;
+#pragma unroll
+    for (int k = 0; k < kVecPerThread; ++k) {
+        r[k] = fmaf(-beta_prev, xp[k], fmaf(-alpha, x[k], r[k]));
+        ss = fmaf(r[k], r[k], ss);
+    }
+    const float beta = sqrtf(block_sum_1024(ss, red));
+    const float inv = beta > 0.f ? 1.0f / beta : 0.f;
+#pragma unroll
+    for (int k = 0; k < kVecPerThread; ++k) {
+        const int i = tid + 1024 * k;
+        if (i < n) { vp[i] = x[k]; v[i] = r[k] * inv; }
+    }
+    if (tid == 0) { tr[step] = alpha; tr[kLanczosMax + step] = beta; }
+}
+
+// Largest eigenvalue of the symmetric tridiagonal matrix (alpha[0..k), beta[0..k-1)) by sectioning on
+// the Sturm count: one wave, lanes 0..31 work on A, lanes 32..63 on A^-1; each round every lane counts
+// the eigenvalues below its own trial value (32 trial values per bracket), and the bracket shrinks to
+// the interval between the last trial with an eigenvalue at or above it and the first one above all.
+// out[0] = sqrt(lambda_A lambda_Ainv) = the kappa_2 estimate, out[1], out[2] its factors.
+__global__ __launch_bounds__(64)
+void lanczos_finish_kernel(const float* tri, int k, float* out) {
+    __shared__ float co[2 * 2 * kLanczosMax];
+    const int lane = threadIdx.x, o = lane >> 5, l = lane & 31;
+    co[lane] = tri[lane]; co[lane + 64] = tri[lane + 64];
+    __syncthreads();
+    const float* al = co + o * 2 * kLanczosMax;
+    const float* be = al + kLanczosMax;
+    float hi = 0.f;
+    for (int i = 0; i < k; ++i) {
+        const float gsh = fabsf(al[i]) + (i > 0 ? fabsf(be[i - 1]) : 0.f) + (i + 1 < k ? fabsf(be[i]) : 0.f);
+        hi = fmaxf(hi, gsh);
+    }
+    float lo = 0.f;
+    for (int round = 0; round < 6; ++round) {
+        const float step = (hi - lo) * (1.0f / 32.0f);
+        const float x = lo + step * (float)(l + 1);        // l = 31: the current upper end
+        int below = 0;                                     // eigenvalues below x
+        float d = 1.f;
+        for (int i = 0; i < k; ++i) {
+            const float b2 = i > 0 ? be[i - 1] * be[i - 1] : 0.f;
+            d = al[i] - x - b2 * __builtin_amdgcn_rcpf(d);
+            if (fabsf(d) < 1e-30f) d = -1e-30f;
+            below += d < 0.f;
+        }
+        const unsigned long long all = __ballot(below == k);
+        const unsigned half = (unsigned)(all >> (32 * o));  // this operator's lanes
+        const int first = half ? __ffs(half) - 1 : 31;      // first trial above every eigenvalue
+        hi = lo + step * (float)(first + 1);
+        lo = lo + step * (float)first;
+    }
+    const float sigma = sqrtf(0.5f * (lo + hi));
+    const float s0 = __shfl(sigma, 0, 64), s1 = __shfl(sigma, 32, 64);
+    if (lane == 0) { out[1] = s0; out[2] = s1; out[0] = s0 * s1; }
+}
+
+#define GELO_TRY(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) return e_; } while (0)
+
+hipError_t gemm(const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, int M, int N, int K,
+                bool subtract, hipStream_t s) {
+    if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
+    GemmOperands g;
+    g.A = A; g.lda = lda;
+    g.B0 = B; g.ldb0 = ldb; g.K0 = K;
+    g.B1 = B; g.ldb1 = ldb;
+    g.C = C; g.ldc = ldc;
+    g.M = M; g.N = N; g.K = K;
+    g.subtract = subtract;
+    return gemm_f32(g, s);
+}
+
+}  // namespace
+
+hipError_t inverse_init() {    // brings this file's code onto the device (see factor_init)
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&diag_inverse_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDiagLds);
+}
+
+hipError_t inverse_from_qr(const FactorWorkspace& ws, int n, hipStream_t s) {
+    const int n_pad = ws.n_pad, nbr = n_pad / NB;
+    const int64_t ld = ws.ld;
+    float* R = ws.Vc;                                         // row-major (read above its diagonal blocks only)
+    float* X = ws.M;
+    GELO_TRY(zero_ints(ws.flag, 1, s));
+    hipLaunchKernelGGL(diag_inverse_kernel, dim3((n_pad + BW - 1) / BW), dim3(512), kDiagLds, s, ws.M, ws.Rd, ws.Dinv, nbr, n, ws.flag);
+    GELO_TRY(hipGetLastError());
+    GELO_TRY(emit_matrix(ws.M, nbr, 1, nullptr, n, ld, R, nullptr, nullptr, nullptr, s));
+    GELO_TRY(emit_matrix(ws.X, nbr, 1, nullptr, n, ld, nullptr, nullptr, X, nullptr, s));
+    if (n < n_pad) GELO_TRY(pad_matrix(X, ld, n, n_pad, s));
+    for (int c0 = (n_pad - 1) / BW * BW; c0 >= 0; c0 -= BW) {
+        const int w = n_pad - c0 < BW ? n_pad - c0 : BW;
+        GELO_TRY(gemm(ws.Dinv + (int64_t)c0 * BW, BW, X + (int64_t)c0 * ld, ld, X + (int64_t)c0 * ld, ld, w, n_pad, w, false, s));
+        GELO_TRY(gemm(R + c0, ld, X + (int64_t)c0 * ld, ld, X, ld, c0, n_pad, w, true, s));
+    }
+    return hipSuccess;
+}
+
+hipError_t kappa_estimate(const float* A, const float* Ainv, int64_t lda, int n, const FactorWorkspace& ws,
+                          int steps, hipStream_t s) {
+    const int64_t ld = ws.ld;
+    if (steps < 1 || steps > kLanczosMax) return hipErrorInvalidValue;
+    if (steps > n) steps = n;
+    // transposes into the (now free) factorisation buffers
+    GELO_TRY(emit_matrix(A, lda, 0, nullptr, n, ld, nullptr, nullptr, ws.M, nullptr, s));
+    GELO_TRY(emit_matrix(Ainv, lda, 0, nullptr, n, ld, nullptr, nullptr, ws.X, nullptr, s));
+    const dim3 grid((2 * n + 3) / 4), block(256);
+    float* va = ws.vec;            float* ya = va + 2 * ld;   float* wa = va + 3 * ld;
+    float* vi = ws.vec + 4 * ld;   float* yi = vi + 2 * ld;   float* wi = vi + 3 * ld;
+    hipLaunchKernelGGL(lanczos_vector_kernel, dim3(2), dim3(1024), 0, s, ws.vec, ld, n, ws.tri, -1);
+    GELO_TRY(hipGetLastError());
+    for (int j = 0; j < steps; ++j) {
+        // w = M^T (M v) for M = A and M = Ainv, then one step of the recurrence for both
+        hipLaunchKernelGGL(matvec_pair_kernel, grid, block, 0, s, A, lda, va, ya, Ainv, lda, vi, yi, n);
+        GELO_TRY(hipGetLastError());
+        hipLaunchKernelGGL(matvec_pair_kernel, grid, block, 0, s, ws.M, ld, ya, wa, ws.X, ld, yi, wi, n);
+        GELO_TRY(hipGetLastError());
+        hipLaunchKernelGGL(lanczos_vector_kernel, dim3(2), dim3(1024), 0, s, ws.vec, ld, n, ws.tri, j);
+        GELO_TRY(hipGetLastError());
+    }
+    hipLaunchKernelGGL(lanczos_finish_kernel, dim3(1), dim3(64), 0, s, ws.tri, steps, ws.scalars);
+    return hipGetLastError();
+}
+
+}  // namespace gelo

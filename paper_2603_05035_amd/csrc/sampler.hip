@@ -95,10 +95,11 @@ void shield_directions_kernel(float* GS, int d, PhiloxStream ps, float* gsnorm) 
 }
 
 __global__ __launch_bounds__(256)
-void axpy_matrix_kernel(float* dst, int64_t ldd, const float* src, int64_t lds, int rows, int cols, float scale) {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    const int r = blockIdx.y;
-    if (c < cols && r < rows) dst[(int64_t)r * ldd + c] += scale * src[(int64_t)r * lds + c];
+void perturb_tiles_kernel(float* G, const float* Q, const float* rdiag, int tile_rows, float scale) {
+    // a workgroup per 16 x 16 tile; column within the tile = thread / 16
+    const int64_t i = ((int64_t)blockIdx.y * tile_rows + blockIdx.x) * 256 + threadIdx.x;
+    const float q = rdiag[blockIdx.y * 16 + (threadIdx.x >> 4)] < 0.f ? -Q[i] : Q[i];
+    G[i] = fmaf(scale, G[i], q);
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -334,11 +335,9 @@ hipError_t shield_directions(float* GS, int k, int d, PhiloxStream ps, float* gs
     return hipGetLastError();
 }
 
-hipError_t axpy_matrix(float* dst, int64_t ldd, const float* src, int64_t lds, int rows, int cols,
-                       float scale, hipStream_t stream) {
-    if (rows <= 0 || cols <= 0) return hipSuccess;
-    hipLaunchKernelGGL(axpy_matrix_kernel, dim3((cols + 255) / 256, rows), dim3(256), 0, stream,
-                       dst, ldd, src, lds, rows, cols, scale);
+hipError_t perturb_tiles(float* G, const float* Q, const float* rdiag, int n_pad, float scale, hipStream_t stream) {
+    const int t = n_pad / 16;
+    hipLaunchKernelGGL(perturb_tiles_kernel, dim3(t, t), dim3(256), 0, stream, G, Q, rdiag, t, scale);
     return hipGetLastError();
 }
 

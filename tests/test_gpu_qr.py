@@ -54,3 +54,19 @@ def test_panels_from_gram_matrices(ctx, n):
     g.gelo_destroy(other)
     assert torch.equal(pair[1], alone)
     check_orthogonal(alone.double().cpu().numpy(), n, first + 1)
+
+
+# A^-1 = R^-1 Q^T by blocks of 128: whole and broken blocks and tiles.  kappa(A) is 2 to 4 here; a backward stable inverse
+# leaves A A^-1 = I to kappa c sqrt(n) roundings (rows scaled to 1)
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 64, 65, 127, 128, 129, 144, 255, 256, 257, 400, 641, 1301])
+def test_inverse_of_a_conditioned_matrix(ctx, n):
+    m = g.gelo_sample_mixing(ctx, g.GELO_CONDITIONED, n, 0, 64, g.GELO_F32, 1e3, 64, batch_id=n)
+    A, A_inv, _, _, kappa = g.gelo_mixing_export(ctx, m, n, 0, 64)
+    torch.cuda.synchronize()
+    g.gelo_mixing_free(ctx, m)
+    A, A_inv = A.double().cpu().numpy(), A_inv.double().cpu().numpy()
+    exact = np.linalg.cond(A)
+    assert np.linalg.norm(A @ A_inv - np.eye(n)) / math.sqrt(n) < exact * EPS * (2 * math.sqrt(n) + 4)
+    assert np.linalg.norm(A_inv - np.linalg.inv(A)) / np.linalg.norm(A_inv) < exact * EPS * (2 * math.sqrt(n) + 4)
+    if n >= 16:
+        assert abs(kappa - exact) < 0.02 * exact
