@@ -18,7 +18,7 @@ namespace {
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int BM = 128, BK = 32;
+constexpr int kTileM = 128, BK = 32;   // rows of a tile (64 where the tile is 64 x 64); K step
 constexpr int NT = 256;
 constexpr int A_PITCH = BK + 4;    // floats: 144-byte rows, conflict-free 16-byte reads down a column of rows
 
@@ -35,9 +35,11 @@ struct F32Args {
 // BN = 96, 128 or 192: the tile width is picked per shape so that the tile count fills whole rounds of the chip's CUs.
 // WAVES_M x (4 / WAVES_M) waves: 2 x 2 for the wide tiles, 4 x 1 (a wave owns 32 rows x 96 columns) for the narrow one,
 // whose LDS footprint lets two workgroups share a CU and cover each other's barrier and LDS-store phases.
-template <int BN, int WAVES_M>
+// 64 x 64 tiles (2 x 2 waves of 32 x 32) for products whose large tiles leave half of the chip idle.
+template <int BM, int BN, int WAVES_M>
 __global__ __launch_bounds__(NT)
 void gemm_f32_kernel(F32Args g) {
+    constexpr int ALD = BM * (BK / 4) / NT;      // A chunks per thread and K step
     constexpr int B_PITCH = BN + 4;
     constexpr int WAVES_N = 4 / WAVES_M;
     constexpr int WROWS = BM / WAVES_M, WCOLS = BN / WAVES_N;
@@ -70,14 +72,14 @@ void gemm_f32_kernel(F32Args g) {
     const int64_t ldb0 = g.ldb0, ldb1 = g.ldb1;
     const int K0 = g.K0, Kd = g.K, Nd = g.N;
 
-    f32x4_t a_stage[4], b_stage[BLD];
+    f32x4_t a_stage[ALD], b_stage[BLD];
 
     auto load_global = [&](int kt) {
         const int k0 = kt * BK;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < ALD; ++i) {
             const int id = tid + i * NT;
-            {   // A: 128 rows x 8 chunks
+            {   // A: BM rows x 8 chunks
                 const int r = id >> 3, c = id & 7;
                 int row = m0 + r;
                 row = row < g.M ? row : g.M - 1;
@@ -122,7 +124,7 @@ void gemm_f32_kernel(F32Args g) {
     };
     auto store_lds = [&](int buf) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < ALD; ++i) {
             const int id = tid + i * NT;
             *reinterpret_cast<f32x4_t*>(&As[buf][(id >> 3) * A_PITCH + (id & 7) * 4]) = a_stage[i];
         }
@@ -206,13 +208,13 @@ void gemm_f32_kernel(F32Args g) {
 constexpr int SN = 32;             // tile width
 constexpr int KP = 132;            // LDS pitch of the A panel, floats (conflict-free as A_PITCH is)
 constexpr int SP = SN + 4;         // LDS pitch of the B panel
-constexpr size_t kShortLds = ((size_t)BM * KP + (size_t)BM * SP) * sizeof(float);
+constexpr size_t kShortLds = ((size_t)kTileM * KP + (size_t)kTileM * SP) * sizeof(float);
 
 __global__ __launch_bounds__(NT)
 void gemm_f32_short_kernel(F32Args g) {
     extern __shared__ __attribute__((aligned(16))) float panels[];
     float* As = panels;                 // [row][k]
-    float* Bs = panels + BM * KP;       // [k][col]
+    float* Bs = panels + kTileM * KP;       // [k][col]
     const int n0 = blockIdx.x * SN;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -226,7 +228,7 @@ void gemm_f32_short_kernel(F32Args g) {
         const int r = id / kc, c = id - r * kc;
         const int row = r < g.M ? r : g.M - 1;
         f32x4_t v = {0.f, 0.f, 0.f, 0.f};
-        if (r < BM) v = *reinterpret_cast<const f32x4_t*>(g.A + (int64_t)row * g.lda + c * 4);
+        if (r < kTileM) v = *reinterpret_cast<const f32x4_t*>(g.A + (int64_t)row * g.lda + c * 4);
         a_st[i] = v;
     }
 #pragma unroll
@@ -242,7 +244,7 @@ void gemm_f32_short_kernel(F32Args g) {
     for (int i = 0; i < 16; ++i) {
         const int id = tid + i * NT;
         const int r = id / kc, c = id - r * kc;
-        if (r < BM) *reinterpret_cast<f32x4_t*>(&As[r * KP + c * 4]) = a_st[i];
+        if (r < kTileM) *reinterpret_cast<f32x4_t*>(&As[r * KP + c * 4]) = a_st[i];
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -289,9 +291,9 @@ hipError_t gemm_f32(const GemmOperands& o, hipStream_t stream) {
     a.B1 = (const float*)o.B1; a.ldb1 = o.ldb1;
     a.C = (float*)o.C;         a.ldc = o.ldc;
     a.M = o.M; a.N = o.N; a.K = o.K;
-    a.tiles_m = (o.M + BM - 1) / BM;
+    a.tiles_m = (o.M + kTileM - 1) / kTileM;
     a.subtract = o.subtract ? 1 : 0;
-    if (o.M <= BM && o.K <= 128 && o.K % 16 == 0 && o.K0 >= o.K) {
+    if (o.M <= kTileM && o.K <= 128 && o.K % 16 == 0 && o.K0 >= o.K) {
         a.tiles_n = (o.N + SN - 1) / SN;
         hipLaunchKernelGGL(gemm_f32_short_kernel, dim3(a.tiles_n), dim3(NT), kShortLds, stream, a);
         return hipGetLastError();
@@ -303,15 +305,20 @@ hipError_t gemm_f32(const GemmOperands& o, hipStream_t stream) {
     auto tiles = [&](int bn) { return a.tiles_m * ((o.N + bn - 1) / bn); };
     const int64_t cost96 = (int64_t)((tiles(96) + 2 * kCus - 1) / (2 * kCus)) * 2 * 96 * 85 / 100;      // measured: 15% faster per flop
     const int64_t cost128 = (int64_t)((tiles(128) + kCus - 1) / kCus) * 128, cost192 = (int64_t)((tiles(192) + kCus - 1) / kCus) * 192;
-    if (o.K >= 512 && cost96 <= cost128 && cost96 <= cost192) {
+    if (tiles(128) * 2 <= kCus) {
+        // Half of the chip or more would be idle, and a 128 x 128 tile keeps its one CU's matrix cores busy for 1.3 us per K
+        // step: four times as many tiles of a quarter of the work (543 x 1544 x 776: 33 us against 74, 1024 x 2048 x 2048: 107 against 183).  The sums run in the same order.
+        a.tiles_m = (o.M + 63) / 64; a.tiles_n = (o.N + 63) / 64;
+        hipLaunchKernelGGL((gemm_f32_kernel<64, 64, 2>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
+    } else if (o.K >= 512 && cost96 <= cost128 && cost96 <= cost192) {
         a.tiles_n = (o.N + 95) / 96;
-        hipLaunchKernelGGL((gemm_f32_kernel<96, 4>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
+        hipLaunchKernelGGL((gemm_f32_kernel<kTileM, 96, 4>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
     } else if (cost192 < cost128) {
         a.tiles_n = (o.N + 191) / 192;
-        hipLaunchKernelGGL((gemm_f32_kernel<192, 2>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
+        hipLaunchKernelGGL((gemm_f32_kernel<kTileM, 192, 2>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
     } else {
         a.tiles_n = (o.N + 127) / 128;
-        hipLaunchKernelGGL((gemm_f32_kernel<128, 2>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
+        hipLaunchKernelGGL((gemm_f32_kernel<kTileM, 128, 2>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
     }
     return hipGetLastError();
 }
