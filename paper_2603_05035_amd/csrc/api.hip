@@ -432,6 +432,38 @@ static gelo_status check_sample_args(gelo_ctx* ctx, gelo_kind kind, int n_data, 
     return GELO_OK;
 }
 
+// The blocks of `count` BLOCK_ORTHOGONAL objects (targets t, batch ids from `first` on; base: their factorisation workspaces,
+// object-major, the full blocks first): the full blocks share the launches of one batched factorisation, the last, shorter
+// ones those of a second one - or, up to kSmallMaxN rows, one launch of the one-workgroup factorisation (102 rows: 45 us
+// against 100 for the blocked one's launches).
+static hipError_t draw_blocks(const SmallSampleTargets& t, int count, uint64_t first, PhiloxStream ps, int n, int d, int64_t ldk, char* base,
+                              hipStream_t s) {
+    constexpr int B = GELO_BLOCK_ROWS;
+    const int full = n / B, rest = n % B;
+    const size_t wb = up256(factor_workspace_bytes(B)), wr = rest ? up256(factor_workspace_bytes(rest)) : 0;
+    ps.c2 = (uint32_t)first; ps.c3 = (uint32_t)(first >> 32);
+    auto draw = [&](char* at, size_t ws_bytes, int rows, int per_object, int first_block) -> hipError_t {
+        FactorWorkspace w;
+        factor_workspace_carve(at, rows, &w);
+        const int64_t stride = (int64_t)(ws_bytes / sizeof(float));
+        ps.c1 = (kStreamBlock << 8) | (uint32_t)first_block;
+        hipError_t e = fill_normal_batched(w.M, stride, w.n_pad / 16, rows, rows, ps, per_object, per_object * count, false, s);
+        if (e == hipSuccess) e = householder_qr(w, rows, per_object * count, stride, s);
+        if (e == hipSuccess)
+            e = emit_batched(w.X, w.rdiag, stride, w.n_pad / 16, rows, ldk, t, count, per_object, (int64_t)first_block * B * ldk, (int64_t)B * ldk, s);
+        return e;
+    };
+    hipError_t e = full > 0 ? draw(base, wb, B, full, 0) : hipSuccess;
+    if (e != hipSuccess || rest == 0) return e;
+    if (rest > kSmallMaxN) return draw(base + wb * (size_t)full * count, wr, rest, 1, full);
+    SmallSampleTargets r = t;
+    const int64_t at = (int64_t)full * B * ldk;
+    r.off_A32 += 4 * at; r.off_Ainv32 += 4 * at;
+    if (r.off_A16 >= 0) { r.off_A16 += 2 * at; r.off_Ainv16 += 2 * at; }
+    ps.c1 = (kStreamBlock << 8) | (uint32_t)full;
+    return small_sample(r, count, first, ps, 0, rest, 0, d, ldk, s);
+}
+
 // Enqueues the draw of batch `batch_id` into the buffers `m` points at, with `ws` as factorisation
 // workspace (not used by STRUCTURED).  `lanes` > 1 (GAUSSIAN only) uses the context's lane buffers, which
 // the caller has sized.  Allocates nothing.
@@ -468,38 +500,11 @@ static gelo_status sample_into(gelo_ctx* ctx, gelo_mixing* m, FactorWorkspace ws
     if (structured) {
         GELO_HIP(ctx, structured_tables(m->table, n, kStructuredRounds, ps, s));
     } else if (kind == GELO_BLOCK_ORTHOGONAL) {
-        // ws.M is the start of the blocks' workspaces here (block_workspace_bytes): the full blocks, whose
-        // factorisations share their launches, then the last, shorter one
-        constexpr int B = GELO_BLOCK_ROWS;
-        char* base = (char*)ws.M;
-        const int full = n / B, rest = n % B;
-        const size_t wb = up256(factor_workspace_bytes(B));
-        auto emit_block = [&](const FactorWorkspace& w, int i, int rows) {
-            const int64_t at = (int64_t)i * B * ldk;
-            return emit_matrix(w.X, w.n_pad / 16, 1, w.rdiag, rows, ldk, m->A32 + at, m->A16 ? m->A16 + at : nullptr,
-                               m->Ainv32 + at, m->Ainv16 ? m->Ainv16 + at : nullptr, s);
-        };
-        FactorWorkspace w;
-        for (int i = 0; i < full; ++i) {
-            factor_workspace_carve(base + wb * i, B, &w);
-            ps.c1 = (kStreamBlock << 8) | (uint32_t)i;
-            GELO_HIP(ctx, fill_normal(w.M, w.n_pad / 16, B, B, ps, 1.0f, 1, s));
-        }
-        if (full > 0) {
-            factor_workspace_carve(base, B, &w);
-            GELO_HIP(ctx, householder_qr(w, B, full, (int64_t)(wb / sizeof(float)), s));
-        }
-        for (int i = 0; i < full; ++i) {
-            factor_workspace_carve(base + wb * i, B, &w);
-            GELO_HIP(ctx, emit_block(w, i, B));
-        }
-        if (rest > 0) {
-            factor_workspace_carve(base + wb * full, rest, &w);
-            ps.c1 = (kStreamBlock << 8) | (uint32_t)full;
-            GELO_HIP(ctx, fill_normal(w.M, w.n_pad / 16, rest, rest, ps, 1.0f, 1, s));
-            GELO_HIP(ctx, householder_qr(w, rest, 1, 0, s));
-            GELO_HIP(ctx, emit_block(w, full, rest));
-        }
+        // ws.M is the start of the blocks' workspaces here (block_workspace_bytes)
+        SmallSampleTargets t;
+        small_targets_layout(m, &t);
+        t.block[0] = m->block;
+        GELO_HIP(ctx, draw_blocks(t, 1, batch_id, ps, n, d, ldk, (char*)ws.M, s));
     } else if (kind == GELO_ORTHOGONAL || kind == GELO_REFLECTOR_PRODUCT) {
         GELO_HIP(ctx, orthogonal_into_X(kind == GELO_REFLECTOR_PRODUCT));
         // A = Q diag(sign r_ii) (sign beta_k for the product of reflectors); A^-1 = A^T
@@ -902,75 +907,31 @@ gelo_status gelo_sample_mixing_batch(gelo_ctx* ctx, gelo_kind kind, int n_data, 
         if (e != hipSuccess) st = hip_fail(ctx, e, "small_sample");
     }
     if (st == GELO_OK && blocked) {
-        // all full blocks of all objects share the launches of ONE batched factorisation (workspaces: object-major,
-        // then block), the last, shorter blocks of all objects those of a second one
-        constexpr int B = GELO_BLOCK_ROWS;
-        const int full = n / B, rest = n % B;
-        const size_t wb = up256(factor_workspace_bytes(B)), wr = rest ? up256(factor_workspace_bytes(rest)) : 0;
-        char* base_full = (char*)ctx->factor_ws;
-        char* base_rest = base_full + wb * (size_t)full * count;
-        hipError_t e = hipSuccess;
-        FactorWorkspace w;
-        for (int o = 0; o < count && e == hipSuccess; ++o) {
-            const uint64_t id = first_batch_id + (uint64_t)o;
-            ps.c2 = (uint32_t)id; ps.c3 = (uint32_t)(id >> 32);
-            for (int i = 0; i < full && e == hipSuccess; ++i) {
-                factor_workspace_carve(base_full + wb * ((size_t)o * full + i), B, &w);
-                ps.c1 = (kStreamBlock << 8) | (uint32_t)i;
-                e = fill_normal(w.M, w.n_pad / 16, B, B, ps, 1.0f, 1, s);
-            }
-            if (rest > 0 && e == hipSuccess) {
-                factor_workspace_carve(base_rest + wr * o, rest, &w);
-                ps.c1 = (kStreamBlock << 8) | (uint32_t)full;
-                e = fill_normal(w.M, w.n_pad / 16, rest, rest, ps, 1.0f, 1, s);
-            }
-        }
-        if (full > 0 && e == hipSuccess) {
-            factor_workspace_carve(base_full, B, &w);
-            e = householder_qr(w, B, full * count, (int64_t)(wb / sizeof(float)), s);
-        }
-        if (rest > 0 && e == hipSuccess) {
-            factor_workspace_carve(base_rest, rest, &w);
-            e = householder_qr(w, rest, count, (int64_t)(wr / sizeof(float)), s);
-        }
-        for (int o = 0; o < count && e == hipSuccess; ++o) {
-            gelo_mixing* m = got[o];
-            const uint64_t id = first_batch_id + (uint64_t)o;
-            for (int i = 0; i < full + (rest ? 1 : 0) && e == hipSuccess; ++i) {
-                const int rows = i < full ? B : rest;
-                if (i < full) factor_workspace_carve(base_full + wb * ((size_t)o * full + i), B, &w);
-                else factor_workspace_carve(base_rest + wr * o, rest, &w);
-                const int64_t at = (int64_t)i * B * m->ldk;
-                e = emit_matrix(w.X, w.n_pad / 16, 1, w.rdiag, rows, m->ldk, m->A32 + at, m->A16 ? m->A16 + at : nullptr,
-                                m->Ainv32 + at, m->Ainv16 ? m->Ainv16 + at : nullptr, s);
-            }
-            if (e == hipSuccess && k_shield > 0) {
-                ps.c1 = kStreamShield << 8; ps.c2 = (uint32_t)id; ps.c3 = (uint32_t)(id >> 32);
-                e = shield_directions(m->GS, k_shield, d, ps, m->gsnorm, s);
-            }
+        small_targets_layout(got[0], &t);
+        hipError_t e = draw_blocks(t, count, first_batch_id, ps, n, d, got[0]->ldk, (char*)ctx->factor_ws, s);
+        if (e == hipSuccess) {
+            ps.c1 = kStreamShield << 8; ps.c2 = (uint32_t)first_batch_id; ps.c3 = (uint32_t)(first_batch_id >> 32);
+            e = shield_directions_batched(t, count, k_shield, d, ps, s);
         }
         if (e != hipSuccess) st = hip_fail(ctx, e, "batched block-orthogonal draw");
     }
     for (int base = 0; st == GELO_OK && !small && !blocked && base < count; base += side) {
         const int c = count - base < side ? count - base : side;
-        FactorWorkspace lw[kQrSideBySide];
-        hipError_t e = hipSuccess;
-        for (int i = 0; i < c && e == hipSuccess; ++i) {
-            factor_workspace_carve((char*)ctx->factor_ws + ws_bytes * i, n, &lw[i]);
-            const uint64_t id = first_batch_id + (uint64_t)(base + i);
-            ps.c1 = kStreamMixing << 8; ps.c2 = (uint32_t)id; ps.c3 = (uint32_t)(id >> 32);
-            e = fill_normal(lw[i].M, lw[i].n_pad / 16, n, n, ps, 1.0f, kind == GELO_REFLECTOR_PRODUCT ? 2 : 1, s);      // straight into the QR's tiles
-        }
-        if (e == hipSuccess) e = householder_qr(lw[0], n, c, (int64_t)(ws_bytes / sizeof(float)), s, kind == GELO_REFLECTOR_PRODUCT);
-        for (int i = 0; i < c && e == hipSuccess; ++i) {
-            gelo_mixing* m = got[base + i];
-            const uint64_t id = first_batch_id + (uint64_t)(base + i);
-            // A = Q diag(sign r_ii); A^-1 = A^T
-            e = emit_matrix(lw[i].X, lw[i].n_pad / 16, 1, lw[i].rdiag, n, m->ldk, m->A32, m->A16, m->Ainv32, m->Ainv16, s);
-            if (e == hipSuccess && k_shield > 0) {
-                ps.c1 = kStreamShield << 8; ps.c2 = (uint32_t)id; ps.c3 = (uint32_t)(id >> 32);
-                e = shield_directions(m->GS, k_shield, d, ps, m->gsnorm, s);
-            }
+        const bool direct = kind == GELO_REFLECTOR_PRODUCT;
+        const int64_t stride = (int64_t)(ws_bytes / sizeof(float)), ldk = got[base]->ldk;
+        const uint64_t id = first_batch_id + (uint64_t)base;
+        FactorWorkspace w;
+        factor_workspace_carve(ctx->factor_ws, n, &w);
+        small_targets_layout(got[base], &t);
+        for (int i = 0; i < c; ++i) t.block[i] = got[base + i]->block;
+        ps.c1 = kStreamMixing << 8; ps.c2 = (uint32_t)id; ps.c3 = (uint32_t)(id >> 32);
+        hipError_t e = fill_normal_batched(w.M, stride, w.n_pad / 16, n, n, ps, 1, c, direct, s);      // straight into the QR's tiles
+        if (e == hipSuccess) e = householder_qr(w, n, c, stride, s, direct);
+        // A = Q diag(sign r_ii); A^-1 = A^T
+        if (e == hipSuccess) e = emit_batched(w.X, w.rdiag, stride, w.n_pad / 16, n, ldk, t, c, 1, 0, 0, s);
+        if (e == hipSuccess) {
+            ps.c1 = kStreamShield << 8;
+            e = shield_directions_batched(t, c, k_shield, d, ps, s);
         }
         if (e != hipSuccess) st = hip_fail(ctx, e, "batched orthogonal draw");
     }

@@ -178,6 +178,16 @@ struct SmallSampleTargets {
     void* block[kSmallMaxBatch];
     int64_t off_A32, off_Ainv32, off_A16, off_Ainv16, off_GS, off_gsnorm;    // off_A16 < 0: no bf16 copies
 };
+// The pieces of a batched draw, one launch each for all its matrices (one at a time they cost a launch's 4 us each, 2150 rows
+// 13 - 15).  Matrix z belongs to object z / per_batch, whose batch id is z / per_batch after ps.c3:c2.
+// fill: matrix z at out + z out_stride, tiled like fill_normal's, stream word ps.c1 + z % per_batch
+hipError_t fill_normal_batched(float* out, int64_t out_stride, int tile_rows, int rows, int cols, PhiloxStream ps, int per_batch, int count,
+                               bool lower_only, hipStream_t stream);
+// emit: matrix z (tiles at src + z src_stride, column signs at rdiag + z src_stride) and its transpose into A32, Ainv32 (A16,
+// Ainv16) of its object, dst_first + (z % per_batch) dst_stride elements behind their start; `count` objects
+hipError_t emit_batched(const float* src, const float* rdiag, int64_t src_stride, int tile_rows, int n, int64_t ldd, const SmallSampleTargets& t,
+                        int count, int per_batch, int64_t dst_first, int64_t dst_stride, hipStream_t stream);
+hipError_t shield_directions_batched(const SmallSampleTargets& t, int count, int k, int d, PhiloxStream ps, hipStream_t stream);
 // For item i < count: batch id = first_batch + i; A = Q diag(sign r_ii) of the Householder QR of its n x n Philox
 // Gaussian (stream c1 of ps; ps.c2 / ps.c3 are ignored), written with its transpose (float, and bf16 if wanted;
 // ldk elements per row, zero beyond column n), and the k x d shield directions with their norms (stream c1_shield).

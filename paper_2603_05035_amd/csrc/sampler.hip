@@ -33,9 +33,15 @@ void fill_normal_kernel(float* out, int64_t ld, int rows, int cols, PhiloxStream
 // row than the segment holds when its ends fall inside blocks), sets the values down in LDS and writes the 16
 // tiles out as they lie in memory, 16 bytes per lane.
 __global__ __launch_bounds__(256)
-void fill_normal_tiled_kernel(float* out, int tile_rows, int rows, int cols, PhiloxStream ps, float scale, int lower_only) {
+void fill_normal_tiled_kernel(float* out, int64_t out_stride, int per_batch, int tile_rows, int rows, int cols, PhiloxStream ps, float scale, int lower_only) {
     constexpr int CW = 256, PITCH = CW + 1, PER_ROW = CW / 4 + 1;
     __shared__ float tile[16 * PITCH];
+    {   // matrix z of the launch: the per_batch matrices of batch id c3:c2, of the id after it, ...
+        const int item = blockIdx.z / per_batch;
+        const uint64_t id = (((uint64_t)ps.c3 << 32) | ps.c2) + (uint64_t)item;
+        ps.c1 += blockIdx.z - item * per_batch; ps.c2 = (uint32_t)id; ps.c3 = (uint32_t)(id >> 32);
+        out += (int64_t)blockIdx.z * out_stride;
+    }
     const int tid = threadIdx.x;
     const int r0 = blockIdx.y * 16, c0 = blockIdx.x * CW;
     if (lower_only && c0 >= r0 + 16) return;                 // every column of this piece lies to the right of every row's diagonal entry
@@ -92,6 +98,16 @@ __global__ __launch_bounds__(256)
 void shield_directions_kernel(float* GS, int d, PhiloxStream ps, float* gsnorm) {
     __shared__ float wave_part[4];
     shield_direction_row(GS, d, blockIdx.x, ps, gsnorm, wave_part);
+}
+
+// grid y = mixing object, its batch id counted up from c3:c2
+__global__ __launch_bounds__(256)
+void shield_directions_batched_kernel(SmallSampleTargets t, int d, PhiloxStream ps) {
+    __shared__ float wave_part[4];
+    const uint64_t id = (((uint64_t)ps.c3 << 32) | ps.c2) + (uint64_t)blockIdx.y;
+    ps.c2 = (uint32_t)id; ps.c3 = (uint32_t)(id >> 32);
+    char* block = (char*)t.block[blockIdx.y];
+    shield_direction_row((float*)(block + t.off_GS), d, blockIdx.x, ps, (float*)(block + t.off_gsnorm), wave_part);
 }
 
 __global__ __launch_bounds__(256)
@@ -249,9 +265,8 @@ void emit_matrix_kernel(const float* src, int64_t lds, int src_tiled, const floa
 // The same for a source in the factorisations' 16 x 16 tiles, 64 x 64 elements per workgroup: a wave reads a whole
 // source tile at a time (one contiguous kilobyte, 16 bytes per lane: four rows of a column), and both the matrix and
 // its transpose leave in pieces of four elements per lane over whole 64-element row segments.  ldd % 64 == 0.
-__global__ __launch_bounds__(256)
-void emit_tiled_kernel(const float* src, int tile_rows, const float* rdiag, int n, int64_t ldd,
-                       float* dst32, uint16_t* dst16, float* dstT32, uint16_t* dstT16) {
+__device__ __forceinline__ void emit_tiled_body(const float* src, int tile_rows, const float* rdiag, int n, int64_t ldd,
+                                                float* dst32, uint16_t* dst16, float* dstT32, uint16_t* dstT16) {
     __shared__ float tile[64][65];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
@@ -295,6 +310,25 @@ void emit_tiled_kernel(const float* src, int tile_rows, const float* rdiag, int 
     }
 }
 
+__global__ __launch_bounds__(256)
+void emit_tiled_kernel(const float* src, int tile_rows, const float* rdiag, int n, int64_t ldd,
+                       float* dst32, uint16_t* dst16, float* dstT32, uint16_t* dstT16) {
+    emit_tiled_body(src, tile_rows, rdiag, n, ldd, dst32, dst16, dstT32, dstT16);
+}
+
+// grid z = matrix: per_batch of them (dst_stride elements apart) for every mixing object
+__global__ __launch_bounds__(256)
+void emit_tiled_batched_kernel(const float* src, const float* rdiag, int64_t src_stride, int tile_rows, int n, int64_t ldd,
+                               SmallSampleTargets t, int per_batch, int64_t dst_first, int64_t dst_stride) {
+    const int item = blockIdx.z / per_batch, sub = blockIdx.z - item * per_batch;
+    char* block = (char*)t.block[item];
+    const int64_t at = dst_first + sub * dst_stride;
+    const bool bf = t.off_A16 >= 0;
+    emit_tiled_body(src + blockIdx.z * src_stride, tile_rows, rdiag + blockIdx.z * src_stride, n, ldd, (float*)(block + t.off_A32) + at,
+                    bf ? (uint16_t*)(block + t.off_A16) + at : nullptr, (float*)(block + t.off_Ainv32) + at,
+                    bf ? (uint16_t*)(block + t.off_Ainv16) + at : nullptr);
+}
+
 template <bool BF16>
 __global__ __launch_bounds__(256)
 void export_dense_kernel(const void* src, int64_t ld, int rows, int cols, float* out) {
@@ -315,11 +349,20 @@ hipError_t fill_normal(float* out, int64_t ld, int rows, int cols, PhiloxStream 
     if (quads == 0) return hipSuccess;
     if (tiled && (int64_t)rows * cols < ((int64_t)1 << 32)) {
         hipLaunchKernelGGL(fill_normal_tiled_kernel, dim3((cols + 255) / 256, (rows + 15) / 16), dim3(256), 0, stream,
-                           out, (int)ld, rows, cols, ps, scale, tiled == 2 ? 1 : 0);
+                           out, (int64_t)0, 1, (int)ld, rows, cols, ps, scale, tiled == 2 ? 1 : 0);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(fill_normal_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream,
                        out, ld, rows, cols, ps, scale, tiled);
+    return hipGetLastError();
+}
+
+hipError_t fill_normal_batched(float* out, int64_t out_stride, int tile_rows, int rows, int cols, PhiloxStream ps, int per_batch, int count,
+                               bool lower_only, hipStream_t stream) {
+    if (rows <= 0 || cols <= 0 || count <= 0) return hipSuccess;
+    if (count > 65535 || per_batch < 1 || (int64_t)rows * cols >= ((int64_t)1 << 32)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(fill_normal_tiled_kernel, dim3((cols + 255) / 256, (rows + 15) / 16, count), dim3(256), 0, stream,
+                       out, out_stride, per_batch, tile_rows, rows, cols, ps, 1.0f, lower_only ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -332,6 +375,13 @@ hipError_t philox_words(uint32_t* words, uint32_t first_block, uint32_t blocks, 
 hipError_t shield_directions(float* GS, int k, int d, PhiloxStream ps, float* gsnorm, hipStream_t stream) {
     if (k <= 0) return hipSuccess;
     hipLaunchKernelGGL(shield_directions_kernel, dim3(k), dim3(256), 0, stream, GS, d, ps, gsnorm);
+    return hipGetLastError();
+}
+
+hipError_t shield_directions_batched(const SmallSampleTargets& t, int count, int k, int d, PhiloxStream ps, hipStream_t stream) {
+    if (k <= 0) return hipSuccess;
+    if (count < 1 || count > kSmallMaxBatch) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(shield_directions_batched_kernel, dim3(k, count), dim3(256), 0, stream, t, d, ps);
     return hipGetLastError();
 }
 
@@ -378,6 +428,15 @@ hipError_t emit_matrix(const float* src, int64_t lds, int src_tiled, const float
     const int t = (int)((ldd + 31) / 32);
     hipLaunchKernelGGL(emit_matrix_kernel, dim3(t, t), dim3(256), 0, stream,
                        src, lds, src_tiled, rdiag, n, ldd, dst32, dst16, dstT32, dstT16);
+    return hipGetLastError();
+}
+
+hipError_t emit_batched(const float* src, const float* rdiag, int64_t src_stride, int tile_rows, int n, int64_t ldd, const SmallSampleTargets& t,
+                        int count, int per_batch, int64_t dst_first, int64_t dst_stride, hipStream_t stream) {
+    if (count < 1 || count > kSmallMaxBatch || per_batch < 1 || count * per_batch > 65535) return hipErrorInvalidValue;
+    const int t64 = (int)((ldd + 63) / 64);
+    hipLaunchKernelGGL(emit_tiled_batched_kernel, dim3(t64, t64, count * per_batch), dim3(256), 0, stream,
+                       src, rdiag, src_stride, tile_rows, n, ldd, t, per_batch, dst_first, dst_stride);
     return hipGetLastError();
 }
 
