@@ -282,20 +282,23 @@ template <int BN> __device__ __forceinline__ int b_chunk_of_pos(int r, int pos) 
     return c < 0 ? c + BN / 8 : c;
 }
 
-template <int BN>
+// TM = 256 or 128 rows: 4 x 2 waves of 64 x BN / 2, or 2 x 4 of 64 x BN / 4.
+template <int BN, int TM = BM>
 __device__ __forceinline__ void tile_body(const Bf16Args& g, uint8_t* lds, int m0, int n0) {
-    constexpr int NCT = BN / 64;
+    constexpr int WN = TM == BM ? 2 : 4;                         // waves side by side
+    constexpr int NCT = BN / 32 / WN;
+    constexpr int NAD = TM / 64;                                 // A fetches per wave and K step
     constexpr int ROWB = BN * 2;
     constexpr int B_BYTES = BKS * ROWB;
     constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
     constexpr int NBD = B_BYTES / 8192;
     constexpr int CPR = ROWB / 16;
-    constexpr int EPI_PITCH = BN + 16;
+    constexpr int EPI_PITCH = NCT * 64 + 16;
     const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)lds);
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = wave / WN, wn = wave % WN;
     const int j = lane & 31, grp = lane >> 5;
     auto uni32 = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
     auto uni64 = [&](int64_t x) {
@@ -308,13 +311,13 @@ __device__ __forceinline__ void tile_body(const Bf16Args& g, uint8_t* lds, int m
     const uint16_t* B0p = (const uint16_t*)uni64((int64_t)g.B0);
     const uint16_t* B1p = (const uint16_t*)uni64((int64_t)g.B1);
 
-    const uint16_t* a_src[4];
+    const uint16_t* a_src[NAD];
     const uint16_t* b0_src[NBD];
     const uint16_t* b1_src[NBD];
     int b_krow[NBD], b_gn[NBD];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int blk = wave * 4 + i;
+    for (int i = 0; i < NAD; ++i) {
+        const int blk = wave * NAD + i;
         const int row = blk * 8 + (lane >> 3), cp = lane & 7;
         const int c = cp ^ ((row ^ (row >> 3)) & 7);
         int grow = m0 + row; grow = grow < g.M ? grow : g.M - 1;
@@ -335,7 +338,7 @@ __device__ __forceinline__ void tile_body(const Bf16Args& g, uint8_t* lds, int m
         const int k0 = t * BKS;
         const uint32_t st = lds_base + (t & 1) * STAGE_BYTES;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) dma16(a_src[i] + k0, st + (wave * 4 + i) * 1024);
+        for (int i = 0; i < NAD; ++i) dma16(a_src[i] + k0, st + (wave * NAD + i) * 1024);
         const uint32_t sb = st + A_BYTES + wave * NBD * 1024;
         if (k0 + BKS <= K0) {
             const int64_t off = (int64_t)k0 * ldb0;
@@ -445,7 +448,7 @@ __device__ __forceinline__ void tile_body(const Bf16Args& g, uint8_t* lds, int m
     __builtin_amdgcn_s_barrier();
     uint8_t* patch = lds + wave * (32 * EPI_PITCH);
     const int rr = lane >> 4, cc = lane & 15;
-    const int col = n0 + wn * (BN / 2) + cc * 8;
+    const int col = n0 + wn * (NCT * 32) + cc * 8;
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
 #pragma unroll
@@ -458,7 +461,7 @@ __device__ __forceinline__ void tile_body(const Bf16Args& g, uint8_t* lds, int m
                 *reinterpret_cast<u32x2_t*>(patch + j * EPI_PITCH + (ct * 32 + 8 * q + 4 * grp) * 2) = out;
             }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (cc < BN / 16) {
+        if (cc < NCT * 4) {
 #pragma unroll
             for (int it = 0; it < 8; ++it) {
                 const int r = it * 4 + rr;
@@ -494,6 +497,24 @@ void gemm_bf16_dma_mixed_kernel(Bf16Args g) {
     } else {
         tile_of_block(blockIdx.x - wide_tiles, g.tiles_m, g.narrow_cols, &tm, &tn);
         tile_body<192>(g, lds, tm * BM, g.tiles_n * 256 + tn * 192);
+    }
+}
+
+// Whole tile rows (tiles_m of them) in both widths as above, then the at most 128 rows that are left as tiles of 128 x 256:
+// a 256-row tile with half of its rows beyond the matrix takes as long as a full one.
+__global__ __launch_bounds__(512)
+void gemm_bf16_dma_rest_kernel(Bf16Args g) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    const int wide_tiles = g.tiles_m * g.tiles_n, whole = wide_tiles + g.tiles_m * g.narrow_cols;
+    int tm, tn;
+    if ((int)blockIdx.x < wide_tiles) {
+        tile_of_block(blockIdx.x, g.tiles_m, g.tiles_n, &tm, &tn);
+        tile_body<256>(g, lds, tm * BM, tn * 256);
+    } else if ((int)blockIdx.x < whole) {
+        tile_of_block(blockIdx.x - wide_tiles, g.tiles_m, g.narrow_cols, &tm, &tn);
+        tile_body<192>(g, lds, tm * BM, g.tiles_n * 256 + tn * 192);
+    } else {
+        tile_body<256, 128>(g, lds, g.tiles_m * BM, ((int)blockIdx.x - whole) * 256);
     }
 }
 
@@ -892,6 +913,9 @@ hipError_t gemm_bf16_init() {
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dma::gemm_bf16_dma_mixed_kernel),
                             hipFuncAttributeMaxDynamicSharedMemorySize, dma::lds_bytes<256>());
     if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dma::gemm_bf16_dma_rest_kernel),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, dma::lds_bytes<256>());
+    if (e != hipSuccess) return e;
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dma::gemm_bf16_dma_batched_kernel<256>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, dma::lds_bytes<256>());
     if (e != hipSuccess) return e;
@@ -941,29 +965,63 @@ hipError_t gemm_bf16(const GemmOperands& o, hipStream_t stream) {
     if (o.M > 128 && o.N >= 8 && (o.a_zero_padded || o.K % dma::BKS == 0)) {
         constexpr int kCus = 256;
         constexpr double kNarrow = 0.87;         // measured cost of a 192-wide tile relative to a 256-wide one
+        constexpr double kHalf = 0.6;            // and of a 128 x 256 one
         const int64_t tiles_m = (o.M + dma::BM - 1) / dma::BM;
         const int64_t t256 = tiles_m * ((o.N + 255) / 256), t192 = tiles_m * ((o.N + 191) / 192);
         const double cost256 = (double)((t256 + kCus - 1) / kCus), cost192 = kNarrow * (double)((t192 + kCus - 1) / kCus);
         // mixed: at most one round of wide tiles and two rounds in all, so that every CU runs at most wide + narrow
-        int best_a = -1, best_b = 0;
-        if (t256 > kCus && tiles_m <= kCus) {
+        auto mixed_widths = [&](int64_t rows, int* wide, int* narrow) {
+            *wide = -1; *narrow = 0;
+            if (rows * ((o.N + 255) / 256) <= kCus || rows > kCus) return;
             int64_t best_width = 0;
-            for (int64_t a = std::min<int64_t>(o.N / 256, kCus / tiles_m); a >= 1; --a) {
+            for (int64_t a = std::min<int64_t>(o.N / 256, kCus / rows); a >= 1; --a) {
                 const int64_t rest = o.N - a * 256;
                 const int64_t b = rest > 0 ? (rest + 191) / 192 : 0;
-                if (b == 0 || tiles_m * (a + b) > 2 * kCus) continue;
+                if (b == 0 || rows * (a + b) > 2 * kCus) continue;
                 const int64_t width = a * 256 + b * 192;
-                if (best_a < 0 || width < best_width) { best_a = (int)a; best_b = (int)b; best_width = width; }
+                if (*wide < 0 || width < best_width) { *wide = (int)a; *narrow = (int)b; best_width = width; }
+            }
+        };
+        int best_a, best_b;
+        mixed_widths(tiles_m, &best_a, &best_b);
+        const double cost_mixed = best_a > 0 ? 1.0 + kNarrow : 1e30;
+        const double cost_whole = std::min(std::min(cost256, cost192), cost_mixed);
+        Bf16Args a;
+        a.A = (const uint16_t*)o.A;   a.lda = o.lda;
+        a.B0 = (const uint16_t*)o.B0; a.ldb0 = o.ldb0; a.K0 = o.K0;
+        a.B1 = (const uint16_t*)o.B1; a.ldb1 = o.ldb1;
+        a.C = (uint16_t*)o.C;         a.ldc = o.ldc;
+        a.M = o.M; a.N = o.N; a.K = o.K;
+        // At most 128 rows behind the last whole tile row: those as half tiles, dispatched last.  They run on the CUs that
+        // the last round of whole tiles leaves idle (one each within the round, a second one ends a little behind it) or
+        // in a round of their own.
+        const int64_t rows = o.M / dma::BM, left = o.M % dma::BM;
+        if (rows > 0 && left > 0 && left <= 128) {
+            const int64_t halves = (o.N + 255) / 256;
+            auto with_halves = [&](int64_t tiles, double rounds, double last) {
+                const int64_t idle = (kCus - tiles % kCus) % kCus;
+                if (halves <= idle) return rounds;
+                if (halves <= 2 * idle) return rounds + std::max(0.0, 2 * kHalf - last);
+                return rounds + kHalf * (double)((halves - idle + kCus - 1) / kCus);
+            };
+            const int64_t w256 = rows * ((o.N + 255) / 256), w192 = rows * ((o.N + 191) / 192);
+            const double c256 = with_halves(w256, (double)((w256 + kCus - 1) / kCus), 1.0);
+            const double c192 = with_halves(w192, kNarrow * (double)((w192 + kCus - 1) / kCus), kNarrow);
+            int wide, narrow;
+            mixed_widths(rows, &wide, &narrow);
+            const double cm = wide > 0 ? with_halves(rows * (wide + narrow), 1.0 + kNarrow, kNarrow) : 1e30;
+            const double cost_rest = std::min(std::min(c256, c192), cm);
+            if (cost_rest < 0.97 * cost_whole) {
+                a.tiles_m = (int)rows;
+                if (cost_rest == c256) { a.tiles_n = (int)halves; a.narrow_cols = 0; }
+                else if (cost_rest == c192) { a.tiles_n = 0; a.narrow_cols = (o.N + 191) / 192; }
+                else { a.tiles_n = wide; a.narrow_cols = narrow; }
+                hipLaunchKernelGGL(dma::gemm_bf16_dma_rest_kernel, dim3((unsigned)(rows * (a.tiles_n + a.narrow_cols) + halves)), dim3(512),
+                                   (size_t)dma::lds_bytes<256>(), stream, a);
+                return hipGetLastError();
             }
         }
-        const double cost_mixed = best_a > 0 ? 1.0 + kNarrow : 1e30;
         if (cost_mixed < cost256 && cost_mixed < cost192) {
-            Bf16Args a;
-            a.A = (const uint16_t*)o.A;   a.lda = o.lda;
-            a.B0 = (const uint16_t*)o.B0; a.ldb0 = o.ldb0; a.K0 = o.K0;
-            a.B1 = (const uint16_t*)o.B1; a.ldb1 = o.ldb1;
-            a.C = (uint16_t*)o.C;         a.ldc = o.ldc;
-            a.M = o.M; a.N = o.N; a.K = o.K;
             a.tiles_m = (int)tiles_m; a.tiles_n = best_a; a.narrow_cols = best_b;
             hipLaunchKernelGGL(dma::gemm_bf16_dma_mixed_kernel, dim3((unsigned)(tiles_m * (best_a + best_b))), dim3(512),
                                (size_t)dma::lds_bytes<256>(), stream, a);

@@ -35,7 +35,7 @@ struct F32Args {
 // BN = 96, 128 or 192: the tile width is picked per shape so that the tile count fills whole rounds of the chip's CUs.
 // WAVES_M x (4 / WAVES_M) waves: 2 x 2 for the wide tiles, 4 x 1 (a wave owns 32 rows x 96 columns) for the narrow one,
 // whose LDS footprint lets two workgroups share a CU and cover each other's barrier and LDS-store phases.
-// 64 x 64 tiles (2 x 2 waves of 32 x 32) for products whose large tiles leave half of the chip idle.
+// 64 x 64 tiles (2 x 2 waves of 32 x 32) for products of at most one round of large tiles.
 template <int BM, int BN, int WAVES_M>
 __global__ __launch_bounds__(NT)
 void gemm_f32_kernel(F32Args g) {
@@ -305,9 +305,11 @@ hipError_t gemm_f32(const GemmOperands& o, hipStream_t stream) {
     auto tiles = [&](int bn) { return a.tiles_m * ((o.N + bn - 1) / bn); };
     const int64_t cost96 = (int64_t)((tiles(96) + 2 * kCus - 1) / (2 * kCus)) * 2 * 96 * 85 / 100;      // measured: 15% faster per flop
     const int64_t cost128 = (int64_t)((tiles(128) + kCus - 1) / kCus) * 128, cost192 = (int64_t)((tiles(192) + kCus - 1) / kCus) * 192;
-    if (tiles(128) * 2 <= kCus) {
-        // Half of the chip or more would be idle, and a 128 x 128 tile keeps its one CU's matrix cores busy for 1.3 us per K
-        // step: four times as many tiles of a quarter of the work (543 x 1544 x 776: 33 us against 74, 1024 x 2048 x 2048: 107 against 183).  The sums run in the same order.
+    if (tiles(128) <= kCus) {
+        // At most one round of large tiles: each keeps its one CU's matrix cores busy for 1.3 us per K step however many CUs are
+        // idle, and nothing runs beside its barriers.  Tiles of a quarter of the work (543 x 1544 x 776: 33 us against 74,
+        // 1024 x 2048 x 2048: 107 against 183, a full round, 2048 x 2048 x 1000: 86 against 98; beyond one round the large
+        // tiles win, 512 x 12288 x 4096: 485 against 536).  The sums run in the same order.
         a.tiles_m = (o.M + 63) / 64; a.tiles_n = (o.N + 63) / 64;
         hipLaunchKernelGGL((gemm_f32_kernel<64, 64, 2>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
     } else if (o.K >= 512 && cost96 <= cost128 && cost96 <= cost192) {

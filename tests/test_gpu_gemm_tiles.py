@@ -1,0 +1,41 @@
+"""The GEMMs at the sizes where their tiles change, against float64 products of the same operands.  Bound per element: one
+rounding of the result to its type plus K roundings of float on the sum of the absolute products."""
+import pytest
+import torch
+
+from paper_2603_05035_amd import binding as g
+
+pytestmark = pytest.mark.gpu
+
+
+def check(m, k, n, dtype):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m + 7 * k + 31 * n)
+    U = torch.randn((m, k), generator=gen, device="cuda").to(dtype)
+    W = torch.randn((k, n), generator=gen, device="cuda").to(dtype)
+    Y = torch.full((m + 2, n), float("nan"), device="cuda", dtype=dtype)
+    ctx = g.gelo_create(0, 1)
+    g.gelo_project(ctx, U, W, Y[1:m + 1])
+    torch.cuda.synchronize()
+    g.gelo_destroy(ctx)
+    assert torch.isnan(Y[0]).all() and torch.isnan(Y[-1]).all()
+    ref, size = U.double() @ W.double(), U.double().abs() @ W.double().abs()
+    # rounding to nearest with p significant bits errs by at most 2^-p of the value; bfloat16 has 8 (7 stored), float 24
+    half_unit = 2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -24
+    assert bool(((Y[1:m + 1].double() - ref).abs() <= half_unit * 1.01 * ref.abs() + k * 2.0 ** -24 * size).all())
+
+
+# whole 256-row tiles and up to 128 rows more: those as tiles of 128 rows behind wide, narrow or both kinds of whole tiles
+# (1, 102 and 128 rows left), 129 left (a whole tile again); widths that fill no tile
+@pytest.mark.parametrize("m,n", [(2150, 22016), (2049, 22008), (2176, 21768), (2177, 22016), (2150, 12288), (384, 49152), (257, 33800),
+                                 (1100, 16392), (1152, 11008), (4301, 12288), (640, 22016)])
+@pytest.mark.parametrize("k", [64, 192])
+def test_bf16_rows_behind_the_last_whole_tile(m, n, k):
+    check(m, k, n, torch.bfloat16)
+
+
+# 64 x 64 tiles up to one round of 128 x 128 ones, the large tiles beyond; broken tiles, and K that fills no step
+@pytest.mark.parametrize("m,k,n", [(1, 136, 8), (63, 136, 72), (64, 264, 64), (65, 136, 200), (543, 776, 1544), (1000, 64, 776),
+                                   (2048, 40, 2048), (2049, 40, 2048), (2048, 40, 2056), (129, 512, 2304)])
+def test_float_tiles(m, k, n):
+    check(m, k, n, torch.float32)
