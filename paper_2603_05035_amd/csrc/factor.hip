@@ -627,8 +627,10 @@ inline int qr_bulk_slots(int strips, int count) {
     return slots;
 }
 
+// Up to 160 blocks a strip fits the 128 registers of two workgroups per CU; longer ones (20 to 40 blocks per wave) have a CU
+// to themselves.
 template <int NBLK>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4)))
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBLK <= 20 ? 4 : 2, NBLK <= 20 ? 4 : 2)))
 void qr_bulk_kernel(QrBulkArgs a) {
     const int die = blockIdx.x & 7, slot = blockIdx.x >> 3, strips = a.outer + a.acc;
     const int rounds = a.count >> 3, rest = a.count & 7;
@@ -647,16 +649,6 @@ void qr_bulk_kernel(QrBulkArgs a) {
     reflect_strip_lds_body<NBLK>(a.refl, a.pending, off, Cs + off, a.nb_block);
 }
 
-// Strips of more than 160 blocks (columns of more than 2560 rows) do not fit the 128 registers of qr_bulk_kernel:
-// the same pass with the strip and the reflector groups in registers (reflect_strip_body), one workgroup per
-// compute unit; grid x = strip of X, grid y = matrix.
-template <int NBLK>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void qr_long_strips_kernel(QrBulkArgs a) {
-    const int64_t off = (int64_t)blockIdx.y * a.batch_stride;
-    __shared__ StripShared<1> sh;
-    reflect_strip_in_place<NBLK, 1>(sh, a.refl, a.pending, off, a.X + off + (int64_t)blockIdx.x * a.strip_stride, a.strip_stride, 1, a.nb_block);
-}
 
 // ------------------------------------------------------------- panel from its Gram matrix --
 // The Householder reflectors of a tall panel without a reduction per column.  Householder's step j needs of the columns
@@ -1065,7 +1057,7 @@ hipError_t launch_qr_step_t(const QrStepArgs& a, int count, hipStream_t s) {
     return hipGetLastError();
 }
 
-// strip blocks per wave the step and panel kernels are built for: 5, 10, 15, 20, 30, 40
+// strip blocks per wave the step and panel kernels are built for: 5, 10, 15, 20, 30, 35, 40
 template <class F>
 hipError_t for_strip_blocks(int per_wave, F&& f) {
     if (per_wave <= 5) return f(std::integral_constant<int, 5>{});
@@ -1073,6 +1065,7 @@ hipError_t for_strip_blocks(int per_wave, F&& f) {
     if (per_wave <= 15) return f(std::integral_constant<int, 15>{});
     if (per_wave <= 20) return f(std::integral_constant<int, 20>{});
     if (per_wave <= 30) return f(std::integral_constant<int, 30>{});
+    if (per_wave <= 35) return f(std::integral_constant<int, 35>{});
     if (per_wave <= 40) return f(std::integral_constant<int, 40>{});
     return hipErrorInvalidValue;
 }
@@ -1095,8 +1088,6 @@ hipError_t launch_qr_bulk_t(const QrBulkArgs& b, int count, hipStream_t s) {
     return hipGetLastError();
 }
 
-// strips of at most 160 blocks only (20 per wave: what fits 128 registers)
-constexpr int kBulkMaxBlocks = 160;
 hipError_t launch_qr_bulk(const QrBulkArgs& b, int count, hipStream_t s) {
     // blocks per wave in steps of two: a strip kernel sized for 20 blocks spends a third more time on a strip of 11
     // than one sized for 12 (it still requests and waits for the blocks that do not exist)
@@ -1112,13 +1103,13 @@ hipError_t launch_qr_bulk(const QrBulkArgs& b, int count, hipStream_t s) {
         case 8: return launch_qr_bulk_t<16>(b, count, s);
         case 9: return launch_qr_bulk_t<18>(b, count, s);
         case 10: return launch_qr_bulk_t<20>(b, count, s);
-        default: break;
+        case 11: case 12: return launch_qr_bulk_t<24>(b, count, s);
+        case 13: case 14: return launch_qr_bulk_t<28>(b, count, s);
+        case 15: case 16: return launch_qr_bulk_t<32>(b, count, s);
+        case 17: case 18: return launch_qr_bulk_t<36>(b, count, s);
+        case 19: case 20: return launch_qr_bulk_t<40>(b, count, s);
+        default: return hipErrorInvalidValue;
     }
-    if (per_wave <= 40 && b.outer == 0) {
-        hipLaunchKernelGGL((qr_long_strips_kernel<40>), dim3(b.acc, count), dim3(512), 0, s, b);
-        return hipGetLastError();
-    }
-    return hipErrorInvalidValue;
 }
 
 hipError_t launch_qr_step(const QrStepArgs& a, int count, hipStream_t s) {
@@ -1193,7 +1184,7 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
         // workgroups per compute unit, which the panel's registers rule out in the step kernel).  One matrix
         // alone keeps them beside workgroup 0: there the launch count and the chain of panels are what matters.
         // Either way every column sees the same arithmetic.
-        if (delayed && a.outer > 0 && a.nb_block <= kBulkMaxBlocks) {
+        if (delayed && a.outer > 0) {
             QrBulkArgs b;
             for (int q = 0; q < kMaxProduct; ++q) b.refl[q] = a.refl[q < a.pending ? q : 0];
             b.pending = a.pending; b.Cout = a.Cout; b.X = a.Cout; b.outer = a.outer; b.acc = 0;
@@ -1207,10 +1198,9 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
     {
         // X = I so far.  Block by block from the last: X[p0:, p0:] <- H_p0 (H_p0+1 (... X[p0:, p0:])), one 16-column
         // strip per workgroup, the block's reflectors newest first, each as I - V T V^T.
-        // (passes of kMaxProduct reflectors where the strips fit qr_bulk_kernel; the longer strips' kernel takes kMaxDelay.
-        // Columns that a pass meets before their own block's turn hold the identity below the pass's first row: the
+        // (Columns that a pass meets before their own block's turn hold the identity below the pass's first row: the
         // reflectors beyond their block leave them as they are, bit for bit, so the grouping does not show in Q.)
-        const int Dq = nbr <= kBulkMaxBlocks ? (ws.ld >= 64 * kMaxProduct ? kMaxProduct : D) : D;
+        const int Dq = ws.ld >= 64 * kMaxProduct ? kMaxProduct : D;
         for (int p0 = (panels - 1) / Dq * Dq; p0 >= 0; p0 -= Dq) {
             const int pend = panels - p0 < Dq ? panels - p0 : Dq;
             QrBulkArgs b;
