@@ -285,6 +285,7 @@ size_t small_lds_bytes(int n) { return (size_t)n * small_pitch(n) * sizeof(float
 
 hipError_t small_init() {
     for (int n : {20, 36, 68, 100, kSmallMaxN}) {
+        if (small_lds_bytes(n) <= 60 * 1024) continue;       // with the static part below 64 KB: no attribute needed
         const hipError_t e = for_small_rows(n, [&](auto R) {
             return hipFuncSetAttribute(reinterpret_cast<const void*>(&small_sample_kernel<decltype(R)::value>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)small_lds_bytes(n));
