@@ -666,7 +666,8 @@ void qr_bulk_kernel(QrBulkArgs a) {
 // Gaussians (a panel behind its reflectors is such a matrix again); the last panels take qr_panel_body.
 // Bound by the latency of one workgroup.  With the strip in front, per launch: 22 us at 2100 rows (30 with a reduction and a
 // barrier per column), 9 us at 500 rows (15), of which the launch itself is 4; a whole draw alone: 2150 rows 3.91 -> 2.68 ms,
-// 543 rows 591 -> 412 us, 4096 rows 15 -> 9.3 ms.  Against 64 bits A is as close as before (3e-6 at 2150 rows), A^T A = I closer.
+// 543 rows 591 -> 412 us, 4096 rows 15 -> 9.3 (8.6 with the long strips through
+// qr_bulk_kernel).  Against 64 bits, six seeds: A as close as before (2.3e-6 at 1000 rows), A^T A = I closer (8.83e-7 -> 8.66e-7).
 constexpr int kGramPanelRows = 64;       // panels of more rows than this are built from their Gram matrix
 
 // value of lane J of the row of 16 lanes
