@@ -171,7 +171,7 @@ hipError_t export_dense(const void* src, int is_bf16, int64_t ld, int rows, int 
                         hipStream_t stream);
 
 // ------------------------------------------- decode-shaped batches (n <= 128) --
-constexpr int kSmallMaxN = 128;      // one workgroup holds [G | I] (n x 2 n floats) in LDS up to this n
+constexpr int kSmallMaxN = 128;      // one workgroup holds [G | I] (n x 2 n floats) in its registers up to this n
 constexpr int kSmallMaxBatch = 48;   // mixing objects one launch of small_sample draws
 // Buffers of the mixing objects a batched draw fills, all of one shape: the same offsets into each block.
 struct SmallSampleTargets {
