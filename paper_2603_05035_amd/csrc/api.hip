@@ -475,7 +475,7 @@ static gelo_status sample_into(gelo_ctx* ctx, gelo_mixing* m, FactorWorkspace ws
     PhiloxStream ps;
     ps.key0 = (uint32_t)ctx->seed; ps.key1 = (uint32_t)(ctx->seed >> 32);
     ps.c2 = (uint32_t)batch_id; ps.c3 = (uint32_t)(batch_id >> 32);
-    const int64_t ld = ws.ld, ldk = m->ldk;
+    const int64_t ldk = m->ldk;
     const bool bf = m->dtype == GELO_BF16;
     m->kind = kind; m->attempt = 0; m->kappa = 1.0f;
 
@@ -516,8 +516,7 @@ static gelo_status sample_into(gelo_ctx* ctx, gelo_mixing* m, FactorWorkspace ws
         GELO_HIP(ctx, perturb_tiles(ws.M, ws.X, ws.rdiag, ws.n_pad, kConditionedBeta / std::sqrt((float)n), s));
         GELO_HIP(ctx, emit_matrix(ws.M, ws.n_pad / 16, 1, nullptr, n, ldk, m->A32, m->A16, nullptr, nullptr, s));
         GELO_HIP(ctx, householder_qr(ws, n, 1, 0, s));
-        GELO_HIP(ctx, inverse_from_qr(ws, n, s));
-        GELO_HIP(ctx, emit_matrix(ws.M, ld, 0, nullptr, n, ldk, m->Ainv32, m->Ainv16, nullptr, nullptr, s));
+        GELO_HIP(ctx, inverse_from_qr(ws, n, m->A32, ldk, m->Ainv32, m->Ainv16, s));
         GELO_HIP(ctx, kappa_estimate(m->A32, m->Ainv32, ldk, n, ws, kKappaSteps, s));
         GELO_HIP(ctx, hipMemcpyAsync(m->stat + 1, ws.scalars, sizeof(float), hipMemcpyDeviceToDevice, s));
         m->kappa = -1.0f;                                     // stays on the device until someone asks
@@ -559,8 +558,7 @@ static gelo_status sample_into(gelo_ctx* ctx, gelo_mixing* m, FactorWorkspace ws
                 auto factorise = [&]() -> hipError_t {
                     hipError_t e = emit_matrix(lw[i].M, lw[i].n_pad / 16, 1, nullptr, n, ldk, cA32[i], cA16[i], nullptr, nullptr, ls);
                     if (e == hipSuccess) e = householder_qr(lw[i], n, 1, 0, ls);
-                    if (e == hipSuccess) e = inverse_from_qr(lw[i], n, ls);
-                    if (e == hipSuccess) e = emit_matrix(lw[i].M, ld, 0, nullptr, n, ldk, cAi32[i], cAi16[i], nullptr, nullptr, ls);
+                    if (e == hipSuccess) e = inverse_from_qr(lw[i], n, cA32[i], ldk, cAi32[i], cAi16[i], ls);
                     if (e == hipSuccess) e = kappa_estimate(cA32[i], cAi32[i], ldk, n, lw[i], kKappaSteps, ls);
                     if (e == hipSuccess) e = hipMemcpyAsync(ctx->host_scalars + i, lw[i].scalars, sizeof(float), hipMemcpyDeviceToHost, ls);
                     if (e == hipSuccess) e = hipMemcpyAsync(ctx->host_flag + i, lw[i].flag, sizeof(int), hipMemcpyDeviceToHost, ls);

@@ -254,9 +254,10 @@ void factor_workspace_carve(void* base, int n, FactorWorkspace* ws);
 // stands (rows k onward), so ws.X becomes the product H_0 H_1 ... H_{n-1} of directly drawn reflectors and
 // ws.rdiag the values beta_k those reflectors map their columns to; no chain of dependent panels.
 hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t batch_stride, hipStream_t stream, bool direct = false);
-// Behind householder_qr(ws, n, 1, ..., direct = false) of a matrix A: leaves A^-1 = R^-1 Q^T in ws.M, row-major with pitch
-// ws.ld (zero in rows [n, n_pad)); *ws.flag != 0 if R has a zero on its diagonal.  Overwrites ws.Vc and ws.Dinv.
-hipError_t inverse_from_qr(const FactorWorkspace& ws, int n, hipStream_t stream);
+// Behind householder_qr(ws, n, 1, ..., direct = false) of the matrix A (n rows of pitch ldk, ldk % 64 == 0, zero beyond column n;
+// read up to 128 rows only): A^-1 = R^-1 Q^T into Ainv32 and, unless it is null, rounded into Ainv16, laid out like A;
+// *ws.flag != 0 if R has a zero on its diagonal.  Overwrites ws.M, ws.Vc and ws.Dinv.
+hipError_t inverse_from_qr(const FactorWorkspace& ws, int n, const float* A, int64_t ldk, float* Ainv32, uint16_t* Ainv16, hipStream_t stream);
 // kappa_2 estimate of the n x n matrix A (lda) with inverse Ainv: sigma_max of both by `steps`
 // (at most 32) Lanczos steps on A^T A and Ainv^T Ainv; uses ws.M / ws.X as scratch for the two
 // transposes; result in ws.scalars[0].

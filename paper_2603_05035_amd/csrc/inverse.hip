@@ -4,10 +4,11 @@
 //
 // A^-1 = R^-1 Q^T from the Householder QR of A (factor.hip): no pivot searches and row interchanges, whose chain - two
 // barriers per column, 1.1 us of one workgroup - bounded a row-pivoted LU in this place (512 rows: 1.1 ms of kernels
-// without the condition estimate, here 0.48; 4096 rows: 15.5 ms, here 10.7).  Q^T is the right-hand side of a block back
-// substitution with R: the inverses of R's 128 x 128 diagonal blocks come from one launch, everything else is float GEMMs
-// with K = 128.  The QR needs no pivots for its accuracy, whatever A is, except that its panels are built from Gram
-// matrices (gram_panel_body): a panel's condition number is at most A's, times a panel of Gaussians' for the GAUSSIAN kind.
+// without the condition estimate, here 0.48; 4096 rows: 15.5 ms, here 10.7).  Up to 128 rows everything behind the QR is one
+// launch (small_inverse_kernel).  Beyond, Q^T is the right-hand side of a block back substitution with R: the inverses of
+// R's 128 x 128 diagonal blocks come from one launch, everything else is float GEMMs with K = 128.  The QR needs no pivots
+// for its accuracy, whatever A is, except that its panels are built from Gram matrices (gram_panel_body): a panel's
+// condition number is at most A's, times a panel of Gaussians' for the GAUSSIAN kind.
 #include "gelo_internal.h"
 
 namespace gelo {
@@ -15,7 +16,10 @@ namespace {
 
 constexpr int NB = kPanel;
 constexpr int BW = kInvBlock;
+constexpr int TB = BW / NB;                               // tiles across a diagonal block
+constexpr int TP = NB + 4;                                // LDS pitch of a row-major tile, floats
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
@@ -35,7 +39,6 @@ void diag_inverse_kernel(const float* M, const float* Rd, float* Dinv, int nbr, 
     extern __shared__ __attribute__((aligned(16))) float diag_lds[];
     float* U = diag_lds;
     float* I = diag_lds + BW * IP;
-    constexpr int TB = BW / NB;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int t0 = blockIdx.x * TB;                       // the block's first tile
     for (int t = wave; t < TB * TB; t += 8) {
@@ -118,6 +121,161 @@ void diag_inverse_kernel(const float* M, const float* Rd, float* Dinv, int nbr, 
     for (int id = tid; id < BW * BW; id += 512) {
         const int r = id / BW, c = id % BW;
         if (t0 * NB + r < nbr * NB) Dinv[((int64_t)t0 * NB + r) * BW + c] = c >= r ? I[r * IP + c] : 0.f;
+    }
+}
+
+// ------------------------------------------------ the inverse of a matrix of at most 128 rows --
+// One launch, a workgroup per 16 columns of A^-1: X = R^-1 (Q^T)'s columns by back substitution over 16 x 16 tiles, then one
+// step of iterative refinement, X += R^-1 Q^T (I - A X) with the residual in double precision, and the rows go out in both
+// types.  Everything a workgroup needs of the other columns is in A, Q and R, so the workgroups are independent.
+// The products keep the accumulator layout throughout: what the matrix instructions leave in a lane (column c, rows 4 g ..)
+// is what they take as right operand when instruction e contracts the rows 4 g + e.
+// Bound by latency: a chain of at most 8 tile rows, twice; the other waves only load and form residuals.  Without the
+// refinement R^-1 Q^T is further off than a row-pivoted LU's inverse up to 40 rows (rms over 48 matrices: GAUSSIAN 16 rows,
+// |A^-1 A - I| 2.2 times, H recovered from A H 1.9 times as far off, CONDITIONED 8 rows 1.7 and 1.5 times), and with R^-1 as a
+// GEMM operand it takes seven launches.  With it, against the LU: |A^-1 A - I| 0.19 and 0.23, H recovered 0.57 and 0.59, at
+// 128 rows 0.04 and 0.31 (GAUSSIAN).  CONDITIONED draw (LU, seven launches, one): 16 rows 246, 236, 204 us; 64 rows 383, 366, 334;
+// 128 rows 545, 466, 458.
+
+__global__ __launch_bounds__(256)
+void small_inverse_kernel(const float* M, const float* Rd, const float* Q, const float* A, int nbr, int n, int64_t ldk,
+                          float* dst32, uint16_t* dst16, int* flag) {
+    __shared__ __attribute__((aligned(16))) float Rt[TB * (TB + 1) / 2][NB * TP];   // R's tiles (t, s), t <= s, at s (s + 1) / 2 + t
+    __shared__ __attribute__((aligned(16))) float Di[TB][NB * TP];                  // inverses of the diagonal ones
+    __shared__ __attribute__((aligned(16))) float Xs[TB][64][4];                    // X, later the refinement's right-hand side
+    __shared__ __attribute__((aligned(16))) float Es[TB][NB * NB];                  // I - A X, column by column
+    __shared__ int singular, far;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, g = lane >> 4, cb = blockIdx.x;
+    if (tid == 0) { singular = 0; far = 0; }
+    for (int s = wave; s < nbr; s += 4)
+        for (int t = 0; t <= s; ++t) {
+            float* tile = Rt[s * (s + 1) / 2 + t];
+            if (t < s) {
+                const f32x4_t v = *reinterpret_cast<const f32x4_t*>(M + ((int64_t)s * nbr + t) * 256 + c * 16 + 4 * g);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) tile[(4 * g + e) * TP + c] = v[e];
+            } else {                                      // row-major in Rd; the identity beyond n
+                const int r = lane >> 2, q = (lane & 3) * 4;
+                f32x4_t v = *reinterpret_cast<const f32x4_t*>(Rd + (int64_t)t * 256 + r * NB + q);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) if (t * NB + r >= n) v[e] = q + e == r ? 1.f : 0.f;
+                *reinterpret_cast<f32x4_t*>(&tile[r * TP + q]) = v;
+            }
+        }
+    __syncthreads();
+    if (tid < nbr * NB) {                                 // back substitution in a diagonal tile, a thread per column
+        const int o = tid / NB, j = tid % NB;
+        const float* U = Rt[o * (o + 1) / 2 + o];
+        float x[NB];
+#pragma unroll
+        for (int i = NB - 1; i >= 0; --i) {
+            float t = i == j ? 1.f : 0.f;
+#pragma unroll
+            for (int k = i + 1; k < NB; ++k) t = fmaf(-U[i * TP + k], x[k], t);
+            const float u = U[i * TP + i];
+            if (i == j && !(fabsf(u) > 0.f)) singular = 1;
+            x[i] = t / u;
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) Di[o][i * TP + j] = x[i];
+    }
+    __syncthreads();
+    if (tid == 0 && cb == 0) *flag = singular;
+    // b <- R^-1 b (wave 0)
+    auto row_operand = [&](const float* tile) { return *reinterpret_cast<const f32x4_t*>(tile + c * TP + 4 * g); };
+    auto solve = [&](f32x4_t (&b)[TB]) {
+#pragma unroll
+        for (int s = TB - 1; s >= 0; --s) {
+            if (s >= nbr) continue;
+            const f32x4_t d = row_operand(Di[s]);
+            f32x4_t x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x = __builtin_amdgcn_mfma_f32_16x16x4f32(d[e], b[s][e], x, 0, 0, 0);
+            b[s] = x;
+#pragma unroll
+            for (int t = s - 1; t >= 0; --t) {
+                const f32x4_t r = row_operand(Rt[s * (s + 1) / 2 + t]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) b[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(-r[e], x[e], b[t], 0, 0, 0);
+            }
+        }
+    };
+    f32x4_t X[TB];
+    if (wave == 0) {
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+            X[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if (t >= nbr) continue;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) X[t][e] = Q[((int64_t)t * nbr + cb) * 256 + (4 * g + e) * 16 + c];     // Q^T[4 g + e][c]
+        }
+        solve(X);
+#pragma unroll
+        for (int t = 0; t < TB; ++t) if (t < nbr) *reinterpret_cast<f32x4_t*>(Xs[t][lane]) = X[t];
+    }
+    __syncthreads();
+    // I - A X in double precision (its instruction leaves row 4 v + g of column c in element v)
+    bool big = false;
+    for (int t = wave; t < nbr; t += 4) {
+        f64x4_t acc;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[v] = t == cb && 4 * v + g == c && t * NB + c < n ? 1. : 0.;
+        const int row = t * NB + c;
+        for (int s = 0; s < nbr; ++s) {
+            f32x4_t a = {0.f, 0.f, 0.f, 0.f};
+            if (row < n) a = *reinterpret_cast<const f32x4_t*>(A + (int64_t)row * ldk + s * NB + 4 * g);
+            const f32x4_t x = *reinterpret_cast<const f32x4_t*>(Xs[s][lane]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-(double)a[e], (double)x[e], acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float e = (float)acc[v];
+            big = big || !(fabsf(e) < 0.1f);
+            Es[t][c * NB + 4 * v + g] = e;
+        }
+    }
+    if (big) far = 1;
+    __syncthreads();
+    // A correction is taken from a residual that is small: beyond that X is a first approximation of nothing (condition
+    // numbers around 1e6 and more, NaN), and stays as it is
+    if (far == 0) {                                       // the same for the whole workgroup
+        for (int t = wave; t < nbr; t += 4) {
+            f32x4_t y = {0.f, 0.f, 0.f, 0.f};
+            for (int s = 0; s < nbr; ++s) {
+                const f32x4_t q = *reinterpret_cast<const f32x4_t*>(Q + ((int64_t)t * nbr + s) * 256 + c * 16 + 4 * g);    // Q^T[c][4 g ..]
+                const f32x4_t r = *reinterpret_cast<const f32x4_t*>(&Es[s][c * NB + 4 * g]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y = __builtin_amdgcn_mfma_f32_16x16x4f32(q[e], r[e], y, 0, 0, 0);
+            }
+            *reinterpret_cast<f32x4_t*>(Xs[t][lane]) = y;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            f32x4_t y[TB];
+#pragma unroll
+            for (int t = 0; t < TB; ++t) { y[t] = f32x4_t{0.f, 0.f, 0.f, 0.f}; if (t < nbr) y[t] = *reinterpret_cast<const f32x4_t*>(Xs[t][lane]); }
+            solve(y);
+#pragma unroll
+            for (int t = 0; t < TB; ++t) if (t < nbr) *reinterpret_cast<f32x4_t*>(Xs[t][lane]) = X[t] + y[t];
+        }
+        __syncthreads();
+    }
+    // rows of A^-1, zero beyond column n; the last workgroup also writes the columns beyond its own
+    const int quads = cb + 1 < nbr ? NB / 4 : (int)(ldk - (int64_t)cb * NB) / 4;
+    for (int i = tid; i < n * quads; i += 256) {
+        const int r = i / quads, q = (i - r * quads) * 4;
+        f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) if (q + e < NB && cb * NB + q + e < n) v[e] = Xs[r / NB][(r % NB) / 4 * 16 + q + e][r % 4];
+        const int64_t at = (int64_t)r * ldk + cb * NB + q;
+        *reinterpret_cast<f32x4_t*>(dst32 + at) = v;
+        if (dst16) {
+            typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+            const bf16x4_t h = {(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
+            *reinterpret_cast<uint2*>(dst16 + at) = __builtin_bit_cast(uint2, h);
+        }
     }
 }
 
@@ -279,8 +437,12 @@ hipError_t inverse_init() {    // brings this file's code onto the device (see f
     return hipFuncSetAttribute(reinterpret_cast<const void*>(&diag_inverse_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDiagLds);
 }
 
-hipError_t inverse_from_qr(const FactorWorkspace& ws, int n, hipStream_t s) {
+hipError_t inverse_from_qr(const FactorWorkspace& ws, int n, const float* A, int64_t ldk, float* Ainv32, uint16_t* Ainv16, hipStream_t s) {
     const int n_pad = ws.n_pad, nbr = n_pad / NB;
+    if (n <= BW) {
+        hipLaunchKernelGGL(small_inverse_kernel, dim3(nbr), dim3(256), 0, s, ws.M, ws.Rd, ws.X, A, nbr, n, ldk, Ainv32, Ainv16, ws.flag);
+        return hipGetLastError();
+    }
     const int64_t ld = ws.ld;
     float* R = ws.Vc;                                         // row-major (read above its diagonal blocks only)
     float* X = ws.M;
@@ -295,7 +457,7 @@ hipError_t inverse_from_qr(const FactorWorkspace& ws, int n, hipStream_t s) {
         GELO_TRY(gemm(ws.Dinv + (int64_t)c0 * BW, BW, X + (int64_t)c0 * ld, ld, X + (int64_t)c0 * ld, ld, w, n_pad, w, false, s));
         GELO_TRY(gemm(R + c0, ld, X + (int64_t)c0 * ld, ld, X, ld, c0, n_pad, w, true, s));
     }
-    return hipSuccess;
+    return emit_matrix(X, ld, 0, nullptr, n, ldk, Ainv32, Ainv16, nullptr, nullptr, s);
 }
 
 hipError_t kappa_estimate(const float* A, const float* Ainv, int64_t lda, int n, const FactorWorkspace& ws,

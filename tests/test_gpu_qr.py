@@ -90,3 +90,28 @@ def loss_of_orthogonality(ctx, n, first, count):
 @pytest.mark.parametrize("n,bound", [(36, 3.08e-7), (68, 3.53e-7), (100, 3.92e-7), (128, 4.23e-7)])
 def test_one_workgroup_factorisation_keeps_orthogonality(ctx, n, bound):
     assert loss_of_orthogonality(ctx, n, 1000 * n, 32) < bound
+
+
+# up to 128 rows the inverse is refined once with a residual in double precision: what is left is the rounding of its elements
+# (at most half a unit each, so EPS of the norm) and the square of the unrefined inverse's error, taken as 8 kappa roundings.
+# One to eight tiles, whole and broken; every row is written up to the pitch, so bf16 copies and later columns are zero there
+@pytest.mark.parametrize("kind", [g.GELO_CONDITIONED, g.GELO_GAUSSIAN])
+@pytest.mark.parametrize("n", [1, 2, 8, 15, 16, 17, 32, 40, 63, 64, 65, 100, 127, 128])
+def test_small_inverse_is_correct_to_its_rounding(ctx, n, kind):
+    cond_max = 1e4
+    m = g.gelo_sample_mixing(ctx, kind, n, 0, 64, g.GELO_F32, cond_max, 64, batch_id=n)
+    A, A_inv, _, _, kappa = g.gelo_mixing_export(ctx, m, n, 0, 64)
+    # A^-1 acts on all n rows of U = A H: garbage or NaN behind column n of a row would show here
+    H = torch.randn((n, 64), generator=torch.Generator(device="cuda").manual_seed(n), device="cuda")
+    U, Z = torch.empty_like(H), torch.empty_like(H)
+    g.gelo_mix(ctx, m, H, U)
+    g.gelo_unmix(ctx, m, U, Z)
+    torch.cuda.synchronize()
+    g.gelo_mixing_free(ctx, m)
+    A, A_inv = A.double().cpu().numpy(), A_inv.double().cpu().numpy()
+    exact = np.linalg.cond(A)
+    assert np.linalg.norm(A_inv - np.linalg.inv(A)) / np.linalg.norm(A_inv) < EPS + (8 * exact * EPS) ** 2
+    err = float((Z.double() - H.double()).norm() / H.double().norm())
+    assert err < exact * EPS * (2 * math.sqrt(n) + 4)
+    if n >= 16:
+        assert abs(kappa - exact) < 0.02 * exact
