@@ -1,15 +1,17 @@
 // float GEMM on the gfx950 matrix cores (v_mfma_f32_32x32x2_f32), used by the
 // single-precision GELO chain (Section 3.2, eqs. 1-3): C[M x N] = A[M x K] * B[K x N],
 // all row-major, B optionally split into two row segments ([H ; S]); optionally C <- C - A * B.
-// A tile reads all of its B columns before it stores, so with M <= 128 the product may
-// overwrite B in place (C == B0, K == M): the back substitution's multiplications by a diagonal-block inverse
-// (those shapes take the short kernel at the end of this file, which has the same property).
+// A tile reads all of its operands before it stores, so the product may overwrite B in place with M <= 128 (C == B0, K0 == K:
+// the back substitution's multiplications by a diagonal-block inverse, a caller's un-mix into its Y) and A where one tile
+// spans N.  The 64 x 64 tiles would read what their neighbours have stored: they are not taken where C meets an operand.
 //
-// A workgroup of 4 waves owns a 128 x 96, 128 x 128 or 128 x 192 tile (whichever fills whole
-// rounds of the chip's CUs best) and walks K in steps of 32 through double-buffered LDS.  A lane
+// A workgroup of 4 waves owns a 64 x 64 tile (products of at most one round of large ones), else a 128 x 96, 128 x 128 or 128 x 192
+// tile (whichever fills whole rounds of the chip's CUs best) and walks K in steps of 32 through double-buffered LDS.  A lane
 // reads four consecutive k of its A row with one 16-byte LDS read and spends them on four
 // successive MFMAs; the matching B values are single dwords, contiguous across lanes; the
 // fragments of the next 8 k are read while the MFMAs of the current 8 run.
+#include <algorithm>
+
 #include "gelo_internal.h"
 
 namespace gelo {
@@ -298,18 +300,26 @@ hipError_t gemm_f32(const GemmOperands& o, hipStream_t stream) {
         hipLaunchKernelGGL(gemm_f32_short_kernel, dim3(a.tiles_n), dim3(NT), kShortLds, stream, a);
         return hipGetLastError();
     }
-    // Tile width.  Large K: 128 x 96 tiles, two workgroups per CU (cost: rounds of 512 tiles), unless a wider
-    // tile wastes less of its last round over the 256 CUs; short K (the back substitution's updates, bound by the
-    // read-modify-write of C): the wide tiles only.
+    // does C share memory with an operand (as far as the ranges from the first to the last element tell)?
+    auto meets_c = [&](const void* p, int64_t ld, int64_t rows, int64_t cols) {
+        const uintptr_t lo = (uintptr_t)p, hi = lo + ((rows - 1) * ld + cols) * sizeof(float);
+        const uintptr_t c_lo = (uintptr_t)o.C, c_hi = c_lo + ((o.M - 1) * o.ldc + o.N) * sizeof(float);
+        return rows > 0 && lo < c_hi && c_lo < hi;
+    };
+    const bool in_place = meets_c(o.A, o.lda, o.M, o.K) || meets_c(o.B0, o.ldb0, std::min(o.K0, o.K), o.N) || meets_c(o.B1, o.ldb1, o.K - o.K0, o.N);
+    // Tile width beyond one round of 128 x 128 tiles.  K of 512 and more: 128 x 96 tiles, two workgroups per CU (cost: rounds of
+    // 512 tiles), unless a wider tile wastes less of its last round over the 256 CUs; below (the back substitution's updates,
+    // K = 128, bound by the read-modify-write of C): the wide tiles only.
     constexpr int kCus = 256;
     auto tiles = [&](int bn) { return a.tiles_m * ((o.N + bn - 1) / bn); };
     const int64_t cost96 = (int64_t)((tiles(96) + 2 * kCus - 1) / (2 * kCus)) * 2 * 96 * 85 / 100;      // measured: 15% faster per flop
     const int64_t cost128 = (int64_t)((tiles(128) + kCus - 1) / kCus) * 128, cost192 = (int64_t)((tiles(192) + kCus - 1) / kCus) * 192;
-    if (tiles(128) <= kCus) {
+    if (tiles(128) <= kCus && !in_place) {
         // At most one round of large tiles: each keeps its one CU's matrix cores busy for 1.3 us per K step however many CUs are
         // idle, and nothing runs beside its barriers.  Tiles of a quarter of the work (543 x 1544 x 776: 33 us against 74,
         // 1024 x 2048 x 2048: 107 against 183, a full round, 2048 x 2048 x 1000: 86 against 98; beyond one round the large
-        // tiles win, 512 x 12288 x 4096: 485 against 536).  The sums run in the same order.
+        // tiles win, 512 x 12288 x 4096: 485 against 536; with K = 128, 512 x 512: 10.7 against 16.3, 1536 x 2048: 13.0 against 17.9).
+        // The sums run in the same order.
         a.tiles_m = (o.M + 63) / 64; a.tiles_n = (o.N + 63) / 64;
         hipLaunchKernelGGL((gemm_f32_kernel<64, 64, 2>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
     } else if (o.K >= 512 && cost96 <= cost128 && cost96 <= cost192) {

@@ -39,3 +39,36 @@ def test_bf16_rows_behind_the_last_whole_tile(m, n, k):
                                    (2048, 40, 2048), (2049, 40, 2048), (2048, 40, 2056), (129, 512, 2304)])
 def test_float_tiles(m, k, n):
     check(m, k, n, torch.float32)
+
+
+# A result that takes its operand's place: one tile has to read all of it before it stores.  Up to 128 rows of B (un-mix into Y,
+# mix into the buffer of H, with and without shield rows), up to 96 columns of A (projection into U); the same bits as elsewhere
+@pytest.mark.parametrize("n_data,k", [(64, 0), (65, 0), (100, 0), (121, 6), (127, 0), (128, 0)])
+@pytest.mark.parametrize("p", [8, 72, 1000])
+def test_float_results_in_place_of_their_operands(n_data, k, p):
+    n = n_data + k
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n_data + p)
+    ctx = g.gelo_create(0, 1, allow_batch_reuse=True)
+    m = g.gelo_sample_mixing(ctx, g.GELO_CONDITIONED, n_data, k, p, g.GELO_F32, batch_id=1)
+    H = torch.randn((n_data, p), generator=gen, device="cuda")
+    U, Z = torch.empty((n, p), device="cuda"), torch.empty((n_data, p), device="cuda")
+    g.gelo_mix(ctx, m, H, U)
+    g.gelo_unmix(ctx, m, U, Z)
+    buf = torch.zeros((n, p), device="cuda")
+    buf[:n_data] = H
+    g.gelo_mix(ctx, m, buf[:n_data], buf)
+    torch.cuda.synchronize()
+    assert torch.equal(buf, U)
+    g.gelo_unmix(ctx, m, buf, buf[:n_data])
+    torch.cuda.synchronize()
+    assert torch.equal(buf[:n_data], Z)
+    g.gelo_mixing_free(ctx, m)
+    if p <= 96:
+        X = torch.randn((300, p), generator=gen, device="cuda")
+        W, Y = torch.randn((p, p), generator=gen, device="cuda"), torch.empty((300, p), device="cuda")
+        g.gelo_project(ctx, X, W, Y)
+        g.gelo_project(ctx, X, W, X)
+        torch.cuda.synchronize()
+        assert torch.equal(X, Y)
+    g.gelo_destroy(ctx)
