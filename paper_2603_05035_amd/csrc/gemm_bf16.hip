@@ -965,7 +965,10 @@ hipError_t gemm_bf16(const GemmOperands& o, hipStream_t stream) {
     if (o.M > 128 && o.N >= 8 && (o.a_zero_padded || o.K % dma::BKS == 0)) {
         constexpr int kCus = 256;
         constexpr double kNarrow = 0.87;         // measured cost of a 192-wide tile relative to a 256-wide one
-        constexpr double kHalf = 0.6;            // and of a 128 x 256 one
+        // and of a 128 x 256 one, from products whose last round it replaces: M = 2150, 640, 4224 at N = 16384, 22016, 12288,
+        // K = 4096, 3 -> 2 + h rounds 1.107 times as fast, 1.74 -> 2 h 1.194, 4 -> 3 + h 1.067: h = 0.71 to 0.75.  (At 0.6 the
+        // rule also took 1.74 -> 1 + h: 2150 x 8192 and 4224 x 4096 lost up to 2% at K = 4096, 4% at 512.)
+        constexpr double kHalf = 0.72;
         const int64_t tiles_m = (o.M + dma::BM - 1) / dma::BM;
         const int64_t t256 = tiles_m * ((o.N + 255) / 256), t192 = tiles_m * ((o.N + 191) / 192);
         const double cost256 = (double)((t256 + kCus - 1) / kCus), cost192 = kNarrow * (double)((t192 + kCus - 1) / kCus);
