@@ -401,10 +401,11 @@ static BlockPiece block_piece(int n_data, int k, int i) {
     b.data0 = r0 - s0; b.data_rows = b.rows - b.shield_rows;
     return b;
 }
-// factorisation workspaces of all blocks, one behind the other: the full blocks first (they share their launches)
+// factorisation workspaces of the blocks, one behind the other: the full blocks first (they share their launches), then the
+// last one if it is too large for the one-workgroup factorisation, which needs none (draw_blocks)
 static size_t block_workspace_bytes(int n) {
     const int full = n / GELO_BLOCK_ROWS, rest = n % GELO_BLOCK_ROWS;
-    return (size_t)full * up256(factor_workspace_bytes(GELO_BLOCK_ROWS)) + (rest ? up256(factor_workspace_bytes(rest)) : 0);
+    return (size_t)full * up256(factor_workspace_bytes(GELO_BLOCK_ROWS)) + (rest > kSmallMaxN ? up256(factor_workspace_bytes(rest)) : 0);
 }
 
 // Argument checks shared by the sampling entry points; on success *n_out = n_data + k_shield.
@@ -440,7 +441,7 @@ static hipError_t draw_blocks(const SmallSampleTargets& t, int count, uint64_t f
                               hipStream_t s) {
     constexpr int B = GELO_BLOCK_ROWS;
     const int full = n / B, rest = n % B;
-    const size_t wb = up256(factor_workspace_bytes(B)), wr = rest ? up256(factor_workspace_bytes(rest)) : 0;
+    const size_t wb = up256(factor_workspace_bytes(B));
     ps.c2 = (uint32_t)first; ps.c3 = (uint32_t)(first >> 32);
     auto draw = [&](char* at, size_t ws_bytes, int rows, int per_object, int first_block) -> hipError_t {
         FactorWorkspace w;
@@ -455,7 +456,7 @@ static hipError_t draw_blocks(const SmallSampleTargets& t, int count, uint64_t f
     };
     hipError_t e = full > 0 ? draw(base, wb, B, full, 0) : hipSuccess;
     if (e != hipSuccess || rest == 0) return e;
-    if (rest > kSmallMaxN) return draw(base + wb * (size_t)full * count, wr, rest, 1, full);
+    if (rest > kSmallMaxN) return draw(base + wb * (size_t)full * count, up256(factor_workspace_bytes(rest)), rest, 1, full);
     SmallSampleTargets r = t;
     const int64_t at = (int64_t)full * B * ldk;
     r.off_A32 += 4 * at; r.off_Ainv32 += 4 * at;

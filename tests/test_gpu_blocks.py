@@ -169,3 +169,23 @@ def test_batched_draw_equals_single_draws(ctx, nd, k, d, count, picks):
         assert g.STATUS_NAMES[e.value.status] == "GELO_EREUSE"
     finally:
         g.gelo_destroy(single)
+
+
+def test_short_block_takes_no_scratch_for_a_workspace(ctx):
+    """A batch of at most 128 rows is one block of the one-workgroup factorisation.  Its matrices and shield rows fill the
+    static buffer here to within 150 KB: a factorisation workspace of 260 KB beside them would not fit."""
+    nd, k, d, p = 50, 50, 54400, 8
+    H = dev(wl.make_hidden(nd, d, 5, 4), "bf16")
+    W = dev(wl.make_weight(d, p, 6), "bf16")
+    Z, U, Y = (torch.empty(s, dtype=H.dtype, device="cuda") for s in ((nd, p), (nd + k, d), (nd + k, p)))
+    # shield rows of the data's own norm: at ten times, with half of the rows shields, U is sqrt(50.5) = 7 times the data and
+    # its rounding (2^-9 / sqrt(3) rms, likewise A, Y and A^T) 7 times a data row's: 0.023 in Z
+    g.gelo_qkv_forward_static(ctx, g.GELO_BLOCK_ORTHOGONAL, H, W, Z, U, Y, k_shield=k, shield_scale=1.0, batch_id=3)
+    other = g.gelo_create(0, SEED, allow_batch_reuse=False)
+    Z1, U1 = torch.empty_like(Z), torch.empty_like(U)
+    g.gelo_qkv_forward(other, g.GELO_BLOCK_ORTHOGONAL, H, W, Z1, k_shield=k, shield_scale=1.0, batch_id=3, U=U1)
+    torch.cuda.synchronize()
+    g.gelo_destroy(other)
+    assert torch.equal(U, U1)
+    ref = f64(H) @ f64(W)
+    assert np.linalg.norm(f64(Z) - ref) / np.linalg.norm(ref) < TOL_END["bf16"]
