@@ -270,194 +270,139 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
 // One block reflector I - V op(T) V^T as a strip sees it: V in both layouts, its triangle, and `shift`, the
-// number of 16-row blocks by which its first row lies below the strip's first row (a strip that applies several
-// reflectors of a block of panels in one pass starts at the oldest one's first row).
+// number of 16-row blocks by which its first row lies below the strip's first row (a strip behind a block of panels
+// starts at the first row of the block's oldest reflector).
 struct Reflector { const float* Vr; const float* Vt; const float* T; int shift; int plain_t; };
 // plain_t: op(T) = T (the reflector itself, I - V T V^T: what forming Q applies) instead of T^T (its transpose: what
-// the factorisation applies to the columns behind it); honoured by reflect_strip_lds_body only
+// the factorisation applies to the columns behind it); reflect_strip_body takes T^T only
 // (the pointers are those of the first matrix of a batch; `off` below is the distance to this workgroup's matrix)
 
 constexpr int kBulkFromCount = 2;         // from this many factorisations side by side the block strips get launches of their own
 constexpr int kPanelRows256 = 1024;      // panels of directly drawn reflectors: up to this many rows by 256 threads, longer ones by 512
-constexpr int kMaxDelay = 4;             // panels per block of the delayed update: most reflectors a strip pass of the factorisation applies
+constexpr int kMaxDelay = 4;             // panels per block: most reflectors a strip pass of the factorisation applies (several matrices)
 constexpr int kMaxProduct = 8;           // most reflectors a strip pass applies while Q is formed (qr_bulk_kernel: all reflectors exist by then,
                                          // so the passes can be longer: measured 10% less time for the same reflectors than passes of four)
 
 // a tile of zeros: what a strip block reads in place of a reflector block that does not exist for it
 __device__ __attribute__((aligned(1024))) float g_zero_tile[256];
 
-// NS neighbouring 16-column strips per workgroup (`strips` of them exist: the last may be missing at the end of a
-// range; the tiles of neighbouring strips lie `strip_stride` floats apart).  With two strips every reflector block a
-// wave fetches feeds twice the matrix instructions, at twice the registers; measured equal to two one-strip
-// workgroups per compute unit (reflect_strip_lds_body), which is what the launches of many matrices use, so only
-// NS = 1 is instantiated at present.  Each strip's arithmetic is the same whichever way strips are grouped.
-// `done` gets the strip's registers behind the last reflector: block wave + 8 b of strip st in cr[st][b].
-template <int NS>
+// One strip, one reflector.  (Two strips per workgroup, so that every reflector block a wave fetches feeds twice the matrix
+// instructions, measured equal to two one-strip workgroups per compute unit, reflect_strip_lds_body.)
+// `done` gets the strip's registers behind the reflector: block wave + 8 b in cr[b].
 struct StripShared {
-    float Wp[2][8][NB][NB * NS];                             // the waves' partial W, alternating between reflectors
-    float Ts[2][NB][NB];
+    float Wp[8][NB][NB];                                     // the waves' partial W
+    float Ts[NB][NB];
 };
 
-template <int NBLK, int NS, class Done>
-__device__ __forceinline__ void reflect_strip_body(StripShared<NS>& sh, const Reflector* refl, int count, int64_t off, float* Cs,
-                                                   int64_t strip_stride, int strips, int nblocks, Done&& done) {
-    auto& Wp = sh.Wp;
-    auto& Ts = sh.Ts;
+template <int NBLK, class Done>
+__device__ __forceinline__ void reflect_strip_body(StripShared& sh, const Reflector& R, int64_t off, float* Cs, int nblocks, Done&& done) {
     // the wave index as a scalar: block numbers and their offsets then live in scalar registers
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g = lane >> 4;
 
     float* Cl = Cs + c * 16 + 4 * g;                         // this lane's column, its first row of tile 0
-    // Blocks past the end take no part: their strip registers are zero, they meet the zero tile instead of a
-    // reflector block (so they are still zero when the next reflector of a block of panels comes), and they are
-    // not stored; their loads are clamped to the last block (a valid address, no branch).  A missing second
-    // strip is all zeros and not stored either.
+    // Blocks past the end take no part: their strip registers are zero and they are not stored; their loads are
+    // clamped to the last block (a valid address, no branch).
     const int last = nblocks - 1;
-    f32x4_t cr[NS][NBLK];
+    f32x4_t cr[NBLK];
 #pragma unroll
-    for (int st = 0; st < NS; ++st) {
-        const bool have = st < strips;
-        const float* Csl = Cl + (have ? st * strip_stride : 0);
-#pragma unroll
-        for (int b = 0; b < NBLK; ++b) {
-            const int blk = wave + 8 * b;
-            const f32x4_t v = *reinterpret_cast<const f32x4_t*>(Csl + 256 * (blk < nblocks ? blk : last));
-            const bool valid = have && blk < nblocks;
-            cr[st][b] = f32x4_t{valid ? v[0] : 0.f, valid ? v[1] : 0.f, valid ? v[2] : 0.f, valid ? v[3] : 0.f};
-        }
+    for (int b = 0; b < NBLK; ++b) {
+        const int blk = wave + 8 * b;
+        const f32x4_t v = *reinterpret_cast<const f32x4_t*>(Cl + 256 * (blk < nblocks ? blk : last));
+        const bool valid = blk < nblocks;
+        cr[b] = f32x4_t{valid ? v[0] : 0.f, valid ? v[1] : 0.f, valid ? v[2] : 0.f, valid ? v[3] : 0.f};
     }
-    // The reflector operands stream through two register groups of GRP blocks.  Per reflector there are 2 NG
-    // groups, first those of the tiled layout (W = V^T C), then those of the row layout (C += V W'); group j
-    // uses register group j % 2, and as soon as a group has been consumed the group two places further on -
-    // of the next reflector, if this one has no more - is requested into the same registers.  Two groups are
-    // always on their way, across the barriers and from one reflector to the next: a load consumed right behind
-    // its issue would expose one memory latency per group.
-    constexpr int GRP = (NBLK == 20 && NS == 1) ? 10 : 5, NG = NBLK / GRP;
+    // The reflector's operands stream through two register groups of GRP blocks: 2 NG groups, first those of the
+    // tiled layout (W = V^T C), then those of the row layout (C += V W'); group j uses register group j % 2, and as
+    // soon as a group has been consumed the group two places further on is requested into the same registers.  Two
+    // groups are always on their way, across the barrier too: a load consumed right behind its issue would expose
+    // one memory latency per group.
+    constexpr int GRP = NBLK == 20 ? 10 : 5, NG = NBLK / GRP;
     static_assert(NBLK % GRP == 0, "blocks per wave must be a multiple of the load group");
     f32x4_t va[2][GRP];
     const float* zero_l = g_zero_tile + c * 16 + 4 * g;
-    auto request = [&](const Reflector& R, auto jc) {
+    auto request = [&](auto jc) {
         constexpr int j = decltype(jc)::value, phase = j / NG, grp = j % NG;
-        // Vt: reflector c, this lane's four rows of the block; Vr: row c of the block, reflectors 4 g ..
-        const float* base = (phase == 0 ? R.Vt : R.Vr) + off + c * 16 + 4 * g;
+        if constexpr (j < 2 * NG) {
+            // Vt: reflector c, this lane's four rows of the block; Vr: row c of the block, reflectors 4 g ..
+            const float* base = (phase == 0 ? R.Vt : R.Vr) + off + c * 16 + 4 * g;
 #pragma unroll
-        for (int k = 0; k < GRP; ++k) {
-            const int blk = wave + 8 * (grp * GRP + k), vb = blk - R.shift;      // strip block blk meets reflector block blk - shift
-            const float* src = (vb >= 0 && blk <= last) ? base + 256 * vb : zero_l;
-            va[j & 1][k] = *reinterpret_cast<const f32x4_t*>(src);
+            for (int k = 0; k < GRP; ++k) {
+                const int blk = wave + 8 * (grp * GRP + k), vb = blk - R.shift;      // strip block blk meets reflector block blk - shift
+                const float* src = (vb >= 0 && blk <= last) ? base + 256 * vb : zero_l;
+                va[j & 1][k] = *reinterpret_cast<const f32x4_t*>(src);
+            }
         }
     };
-    // the triangle of a reflector is fetched one reflector ahead (needed behind its second barrier only), so that
-    // no wait for it ever stands between a request and the products that use older requests
-    float t_next = tid < NB * NB ? refl[0].T[off + tid] : 0.f;
-    request(refl[0], std::integral_constant<int, 0>{});
-    request(refl[0], std::integral_constant<int, 1>{});
-    // (the loop over the reflectors is unrolled: the waits for the requests then count exactly what is outstanding)
-    static_for<kMaxDelay>([&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        if (q >= count) return;
-        const Reflector R = refl[q];
-        const bool more = q + 1 < count;
-        const Reflector Rn = more ? refl[q + 1] : R;
-        auto request_behind = [&](auto jc) {                  // the group two places behind group j
-            constexpr int j = decltype(jc)::value;
-            if constexpr (j + 2 < 2 * NG) request(R, std::integral_constant<int, j + 2>{});
-            else if (more) request(Rn, std::integral_constant<int, j + 2 - 2 * NG>{});
-        };
-        const float t_mine = t_next;
-        // W_partial[i][col] = sum over this wave's rows of V[r][i] C[r][col]; MFMA (b, v) contracts the four
-        // rows 16 blk + 4 kk + v (kk = lane / 16): A = V[row][lane % 16], B = the strip register itself.
-        f32x4_t w0[NS], w1[NS];
+    // (the triangle is needed behind the barrier only: fetched first, no wait for it ever stands between a request
+    // and the products that use older requests)
+    const float t_mine = tid < NB * NB ? R.T[off + tid] : 0.f;
+    request(std::integral_constant<int, 0>{});
+    request(std::integral_constant<int, 1>{});
+    // W_partial[i][col] = sum over this wave's rows of V[r][i] C[r][col]; MFMA (b, v) contracts the four
+    // rows 16 blk + 4 kk + v (kk = lane / 16): A = V[row][lane % 16], B = the strip register itself.
+    f32x4_t w0 = {0.f, 0.f, 0.f, 0.f}, w1 = {0.f, 0.f, 0.f, 0.f};
+    static_for<NG>([&](auto gc) {
+        constexpr int grp = decltype(gc)::value;
 #pragma unroll
-        for (int st = 0; st < NS; ++st) { w0[st] = f32x4_t{0.f, 0.f, 0.f, 0.f}; w1[st] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
-        static_for<NG>([&](auto gc) {
-            constexpr int grp = decltype(gc)::value;
-#pragma unroll
-            for (int k = 0; k < GRP; ++k) {
-                const int b = grp * GRP + k;
-                const f32x4_t a = va[grp & 1][k];
-                if (wave + 8 * b > last) continue;            // a block past the end (wave-uniform): nothing to add
-#pragma unroll
-                for (int st = 0; st < NS; ++st) {
-                    w0[st] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], cr[st][b][0], w0[st], 0, 0, 0);
-                    w1[st] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], cr[st][b][1], w1[st], 0, 0, 0);
-                }
-#pragma unroll
-                for (int st = 0; st < NS; ++st) {
-                    w0[st] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], cr[st][b][2], w0[st], 0, 0, 0);
-                    w1[st] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], cr[st][b][3], w1[st], 0, 0, 0);
-                }
-            }
-            request_behind(gc);
-        });
-        if (tid < NB * NB) { if (R.plain_t) Ts[q & 1][tid & 15][tid >> 4] = t_mine; else Ts[q & 1][tid >> 4][tid & 15] = t_mine; }
-        if (more && tid < NB * NB) t_next = Rn.T[off + tid];
-#pragma unroll
-        for (int st = 0; st < NS; ++st)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) Wp[q & 1][wave][4 * g + v][st * NB + c] = w0[st][v] + w1[st][v];     // accumulator row 4 g + v, column c
-        __syncthreads();
-        // ONE barrier per reflector: every wave adds the eight partial W (in wave order) for the entries it needs as
-        // an operand and forms W' = -T^T W itself, on the matrix cores: step s contracts reflectors 4 s + kk,
-        // A = T[4 s + kk][lane % 16], B = W[4 s + kk][lane % 16]; the result arrives in the accumulator layout,
-        // which is the operand layout of the second product.  (The partial sums and the triangle alternate between
-        // two buffers: a wave may be a whole reflector ahead of another one that is still reading.)
-        // C_block += V_block W': MFMA k contracts reflectors 4 kk + k; A = V[16 blk + lane % 16][4 kk + k]
-        float bq[NS][4];
-        {
-            float ta[4];
-#pragma unroll
-            for (int sx = 0; sx < 4; ++sx) ta[sx] = Ts[q & 1][4 * sx + g][c];
-#pragma unroll
-            for (int st = 0; st < NS; ++st) {
-                f32x4_t wn = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int sx = 0; sx < 4; ++sx) {
-                    float sum = Wp[q & 1][0][4 * sx + g][st * NB + c];
-#pragma unroll
-                    for (int w = 1; w < 8; ++w) sum += Wp[q & 1][w][4 * sx + g][st * NB + c];
-                    wn = __builtin_amdgcn_mfma_f32_16x16x4f32(ta[sx], sum, wn, 0, 0, 0);
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k) bq[st][k] = -wn[k];
-            }
+        for (int k = 0; k < GRP; ++k) {
+            const int b = grp * GRP + k;
+            const f32x4_t a = va[grp & 1][k];
+            if (wave + 8 * b > last) continue;                // a block past the end (wave-uniform): nothing to add
+            w0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], cr[b][0], w0, 0, 0, 0);
+            w1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], cr[b][1], w1, 0, 0, 0);
+            w0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], cr[b][2], w0, 0, 0, 0);
+            w1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], cr[b][3], w1, 0, 0, 0);
         }
-        static_for<NG>([&](auto gc) {
-            constexpr int grp = decltype(gc)::value, j = NG + grp;
+        request(std::integral_constant<int, grp + 2>{});
+    });
+    if (tid < NB * NB) sh.Ts[tid >> 4][tid & 15] = t_mine;
 #pragma unroll
-            for (int k = 0; k < GRP; ++k) {
-                const int b = grp * GRP + k;
-                const f32x4_t a4 = va[j & 1][k];
-                if (wave + 8 * b > last) continue;
+    for (int v = 0; v < 4; ++v) sh.Wp[wave][4 * g + v][c] = w0[v] + w1[v];     // accumulator row 4 g + v, column c
+    __syncthreads();
+    // ONE barrier: every wave adds the eight partial W (in wave order) for the entries it needs as an operand and
+    // forms W' = -T^T W itself, on the matrix cores: step s contracts reflectors 4 s + kk,
+    // A = T[4 s + kk][lane % 16], B = W[4 s + kk][lane % 16]; the result arrives in the accumulator layout,
+    // which is the operand layout of the second product.
+    // C_block += V_block W': MFMA k contracts reflectors 4 kk + k; A = V[16 blk + lane % 16][4 kk + k]
+    float bq[4];
+    {
+        f32x4_t wn = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk)
+        for (int sx = 0; sx < 4; ++sx) {
+            float sum = sh.Wp[0][4 * sx + g][c];
 #pragma unroll
-                    for (int st = 0; st < NS; ++st)
-                        cr[st][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[kk], bq[st][kk], cr[st][b], 0, 0, 0);
-            }
-            request_behind(std::integral_constant<int, j>{});
-        });
+            for (int w = 1; w < 8; ++w) sum += sh.Wp[w][4 * sx + g][c];
+            wn = __builtin_amdgcn_mfma_f32_16x16x4f32(sh.Ts[4 * sx + g][c], sum, wn, 0, 0, 0);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) bq[k] = -wn[k];
+    }
+    static_for<NG>([&](auto gc) {
+        constexpr int grp = decltype(gc)::value, j = NG + grp;
+#pragma unroll
+        for (int k = 0; k < GRP; ++k) {
+            const int b = grp * GRP + k;
+            const f32x4_t a4 = va[j & 1][k];
+            if (wave + 8 * b > last) continue;
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) cr[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[kk], bq[kk], cr[b], 0, 0, 0);
+        }
+        request(std::integral_constant<int, j + 2>{});
     });
     done(cr);
 }
 
 // the same, the strip written back in place
-template <int NBLK, int NS>
-__device__ __forceinline__ void reflect_strip_in_place(StripShared<NS>& sh, const Reflector* refl, int count, int64_t off, float* Cs,
-                                                       int64_t strip_stride, int strips, int nblocks) {
-    reflect_strip_body<NBLK, NS>(sh, refl, count, off, Cs, strip_stride, strips, nblocks, [&](f32x4_t (&cr)[NS][NBLK]) {
+template <int NBLK>
+__device__ __forceinline__ void reflect_strip_in_place(StripShared& sh, const Reflector& R, int64_t off, float* Cs, int nblocks) {
+    reflect_strip_body<NBLK>(sh, R, off, Cs, nblocks, [&](f32x4_t (&cr)[NBLK]) {
         const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         float* Cl = Cs + (lane & 15) * 16 + 4 * (lane >> 4);
 #pragma unroll
-        for (int st = 0; st < NS; ++st) {
-            if (st < strips) {
-                float* Csl = Cl + st * strip_stride;
-#pragma unroll
-                for (int b = 0; b < NBLK; ++b) {
-                    const int blk = wave + 8 * b;
-                    if (blk < nblocks) *reinterpret_cast<f32x4_t*>(Csl + 256 * blk) = cr[st][b];
-                }
-            }
+        for (int b = 0; b < NBLK; ++b) {
+            const int blk = wave + 8 * b;
+            if (blk < nblocks) *reinterpret_cast<f32x4_t*>(Cl + 256 * blk) = cr[b];
         }
     });
 }
@@ -897,26 +842,33 @@ void gram_panel_kernel(float* Mp, float* Vr, float* Vt, float* Tg, float* Rd, fl
 }
 
 // One launch per QR step p.  The chain of panel factorisations (one workgroup each) is the critical path, so
-// the launch that follows the factorisation of panel p also factorises panel p + 1.  Panels come in blocks of
-// D (delayed update): inside a block only the block's own columns see each new reflector at once; the rest of
-// the matrix is read and written ONCE per block, by strips that apply the block's D reflectors in a row while
-// they hold their columns in registers.  That divides the memory traffic of the factorisation, which is what
-// bounds several factorisations running side by side, by almost D.
+// the launch that follows the factorisation of panel p also factorises panel p + 1.  Panels come in blocks of D.
 //   workgroup 0          applies reflector p to the 16 columns of panel p + 1, then factorises them;
 //   `inner` workgroups   (inside a block) apply reflector p to the block's later panels and to the first panel
 //                        of the next block: its columns then lack only the newest reflector when workgroup 0
 //                        gets to them, as everywhere else on the chain;
-//   `outer`              (a block has just been finished) apply its reflectors to the columns beyond panel p + 1.
+//   `outer`              (one matrix alone) apply reflector p to the columns further on.
+// One matrix alone meets every reflector at once, everywhere: the strips of a launch then take less time than the panel
+// beside them, where strips of four reflectors took twice as long.  With several matrices side by side the columns behind a
+// block wait until it is complete (delayed update) and get all its reflectors in one pass over the strip, in a launch of
+// strips only (qr_bulk_kernel, two workgroups per compute unit, which the panel's registers rule out here): that divides the
+// memory traffic, which is what bounds several factorisations side by side, by almost D.
+// One matrix at once / delayed: 517 rows 401 / 478 us, 2150 rows 2.66 / 3.32 ms, CONDITIONED 4096 rows 20.6 / 24.0 ms.
+// Draws of one matrix each that overlap on streams keep that order up to 2150 rows (two, three, four streams: 8, 12, 16
+// matrices in 12.5 / 15.3, 13.9 / 16.4, 15.6 / 18.7 ms) and at 4096 rows on two; there three streams are even and four
+// delayed ones 4 % ahead (8 matrices 34.1 / 32.8 ms, CONDITIONED 92.3 / 86.6).
+// Either way a column sees the same sums in the same order, so the bits are the same: that is why the outer strips start at
+// the block's first row, although only reflector p meets them (the blocks of a strip are dealt to the waves from its
+// first row on, and each wave sums its own).
 // Every strip reads only reflectors and its own columns; panel p + 1 writes its own columns, reflector buffers
 // no strip of this launch reads, and its own T: the workgroups of one launch never touch the same data.  Waves
 // of workgroup 0 that the panel does not use leave after the strip.  Q is formed afterwards (householder_qr).
 struct QrStepArgs {
     Reflector newest;                    // reflector p, shift 0
-    Reflector refl[kMaxDelay];           // what the `outer` strips apply: reflectors of the current block; shift = position in the block
-    int pending;                         // how many of them
+    int block_shift;                     // its shift as the outer strips see it: p's position in its block
     float* C0;                           // the columns of panel p + 1: tile (row block p, column block p + 1)
     float* Cin;                          // tile (row block p, column block p + 2): `inner` strips from here
-    float* Cout;                         // tile (row block of the block's first panel, column block p + 2): `outer` strips
+    float* Cout;                         // `outer` strips from here: tile (row block of the block's first panel, first column block they take)
     int64_t strip_stride;                // floats between the tiles of neighbouring column blocks
     int nb_single, nb_block;             // rows / 16 below the first row of reflector p / of the block's first reflector
     int inner, outer;                    // strip counts
@@ -928,7 +880,7 @@ struct QrStepArgs {
 template <int NBLK>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBLK >= 10 ? 2 : 4, NBLK >= 10 ? 2 : 4)))
 void qr_step_kernel(QrStepArgs a) {
-    __shared__ StripShared<1> strip;
+    __shared__ StripShared strip;
     const int b = blockIdx.x;
     const int64_t off = (int64_t)blockIdx.y * a.batch_stride;
     if (b == 0) {
@@ -936,15 +888,15 @@ void qr_step_kernel(QrStepArgs a) {
         // the panel starts one tile (16 rows) below reflector p's first row
         if (a.m_next > kGramPanelRows) {
             __shared__ GramShared<NBLK> gram;
-            reflect_strip_body<NBLK, 1>(strip, &a.newest, 1, off, a.C0 + off, 0, 1, a.nb_single, [&](f32x4_t (&cr)[1][NBLK]) {
+            reflect_strip_body<NBLK>(strip, a.newest, off, a.C0 + off, a.nb_single, [&](f32x4_t (&cr)[NBLK]) {
                 // block 0 is a finished tile of R; the rest becomes the reflectors
-                if (threadIdx.x < 64) *reinterpret_cast<f32x4_t*>(a.C0 + off + (threadIdx.x & 15) * 16 + 4 * (threadIdx.x >> 4)) = cr[0][0];
-                gram_panel_body<NBLK, 1>(gram, cr[0], a.nb_single - 1, a.Vr_next + off, a.Vt_next + off, a.Tnext + off, a.Rd_next + off, a.rdiag_next + off);
+                if (threadIdx.x < 64) *reinterpret_cast<f32x4_t*>(a.C0 + off + (threadIdx.x & 15) * 16 + 4 * (threadIdx.x >> 4)) = cr[0];
+                gram_panel_body<NBLK, 1>(gram, cr, a.nb_single - 1, a.Vr_next + off, a.Vt_next + off, a.Tnext + off, a.Rd_next + off, a.rdiag_next + off);
             });
             return;
         }
         if constexpr (NBLK <= 5) {
-            reflect_strip_in_place<NBLK, 1>(strip, &a.newest, 1, off, a.C0 + off, 0, 1, a.nb_single);
+            reflect_strip_in_place<NBLK>(strip, a.newest, off, a.C0 + off, a.nb_single);
             __threadfence_block();
             __syncthreads();             // the strip's stores are visible to the whole workgroup
             if (threadIdx.x >= kGramPanelRows) return;
@@ -953,11 +905,12 @@ void qr_step_kernel(QrStepArgs a) {
         return;
     }
     if (b <= a.inner) {
-        reflect_strip_in_place<NBLK, 1>(strip, &a.newest, 1, off, a.Cin + off + (int64_t)(b - 1) * a.strip_stride, 0, 1, a.nb_single);
+        reflect_strip_in_place<NBLK>(strip, a.newest, off, a.Cin + off + (int64_t)(b - 1) * a.strip_stride, a.nb_single);
         return;
     }
-    reflect_strip_in_place<NBLK, 1>(strip, a.refl, a.pending, off, a.Cout + off + (int64_t)(b - 1 - a.inner) * a.strip_stride, 0, 1,
-                                    a.nb_block);
+    Reflector behind = a.newest;
+    behind.shift = a.block_shift;
+    reflect_strip_in_place<NBLK>(strip, behind, off, a.Cout + off + (int64_t)(b - 1 - a.inner) * a.strip_stride, a.nb_block);
 }
 
 // zeroes what lies beyond n x n of the tiled matrix M (n_pad x n_pad) and sets the tiled X to the identity
@@ -1126,9 +1079,7 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
     const int nbr = n_pad / NB;                               // tile rows (= tile columns)
     const int64_t strip_stride = (int64_t)nbr * 256;
     const int panels = nbr;
-    // Panels per block of the delayed update; the reflectors of two blocks are alive at a time (the finished
-    // block is being applied while the next one's first panel is written), each n_pad x 16 in two layouts, all
-    // inside the n_pad x ld floats of ws.Vc.
+    // panels per block
     const int D = ws.ld >= 64 * kMaxDelay ? kMaxDelay : (ws.ld >= 128 ? 2 : 1);
     // Every panel's reflector block is kept until the end: the row-major copies side by side in ws.Vc (n_pad x 16 each,
     // n_pad x n_pad in all), the tiled copies IN PLACE of the panels they came from (a factored panel is dead: nobody
@@ -1168,30 +1119,24 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
         a.Cin = ws.M + (int64_t)(p + 2 < nbr ? p + 2 : 0) * strip_stride + (int64_t)p * 256;
         // the block's panels behind p + 1 and the first panel of the next block
         a.inner = block_done ? 0 : (block_end < nbr ? block_end : nbr - 1) - (p + 1);
-        // The columns behind the block.  Several matrices: all the block's reflectors in one pass, once it is complete.
-        // One matrix alone: each reflector at once - the strips of a launch then take less time than the panel beside
-        // them, where a strip of four reflectors takes twice as long (the traffic saved does not matter there).
+        // the columns further on: one matrix alone, at once; several matrices, once the block is complete (see QrStepArgs)
         const bool delayed = count >= kBulkFromCount;
-        const int from = block_done ? p + 2 : block_end + 1, oldest = delayed ? p0 : p;
-        a.outer = ((block_done || !delayed) && from < nbr) ? nbr - from : 0;
-        a.Cout = ws.M + (int64_t)(from < nbr ? from : 0) * strip_stride + (int64_t)p0 * 256;
-        a.pending = p - oldest + 1;
-        for (int q = 0; q < kMaxDelay; ++q) a.refl[q] = reflector(q < a.pending ? oldest + q : p, (q < a.pending ? oldest + q : p) - p0);
+        const int from = block_done ? p + 2 : block_end + 1;
+        float* behind = ws.M + (int64_t)(from < nbr ? from : 0) * strip_stride + (int64_t)p0 * 256;
+        a.outer = !delayed && from < nbr ? nbr - from : 0;
+        a.Cout = behind;
+        a.block_shift = p - p0;
         a.Vr_next = Vr_of(p + 1); a.Vt_next = Vt_of(p + 1);
         a.Tnext = ws.Tmat + (int64_t)(p + 1) * NB * NB; a.Rd_next = ws.Rd + (int64_t)(p + 1) * NB * NB; a.rdiag_next = ws.rdiag + (p + 1) * NB;
         a.m_next = last ? 0 : n_pad - (p + 1) * NB;
         a.batch_stride = batch_stride;
-        // Several matrices side by side: the strips that apply a finished block get a launch of their own (two
-        // workgroups per compute unit, which the panel's registers rule out in the step kernel).  One matrix
-        // alone keeps them beside workgroup 0: there the launch count and the chain of panels are what matters.
-        // Either way every column sees the same arithmetic.
-        if (delayed && a.outer > 0) {
+        if (delayed && block_done && from < nbr) {
             QrBulkArgs b;
-            for (int q = 0; q < kMaxProduct; ++q) b.refl[q] = a.refl[q < a.pending ? q : 0];
-            b.pending = a.pending; b.Cout = a.Cout; b.X = a.Cout; b.outer = a.outer; b.acc = 0;
+            b.pending = p - p0 + 1;
+            for (int q = 0; q < kMaxProduct; ++q) { const int i = q < b.pending ? q : 0; b.refl[q] = reflector(p0 + i, i); }
+            b.Cout = behind; b.X = behind; b.outer = nbr - from; b.acc = 0;
             b.strip_stride = strip_stride; b.nb_block = a.nb_block; b.batch_stride = batch_stride; b.count = count;
             GELO_TRY(launch_qr_bulk(b, count, s));
-            a.outer = 0;
         }
         if (last) break;                                      // no panel and no column left
         GELO_TRY(launch_qr_step(a, count, s));
