@@ -1011,7 +1011,8 @@ hipError_t launch_qr_step_t(const QrStepArgs& a, int count, hipStream_t s) {
     return hipGetLastError();
 }
 
-// strip blocks per wave the step and panel kernels are built for: 5, 10, 15, 20, 30, 35, 40
+// strip blocks per wave the step and panel kernels are built for: 5, 10, 15, 20, 30, 35, 40.  (A kernel that is too large still
+// requests and waits for the blocks that do not exist, but few: one for 25 took 0.4% less at 2600 rows, 1.5% at 3200.)
 template <class F>
 hipError_t for_strip_blocks(int per_wave, F&& f) {
     if (per_wave <= 5) return f(std::integral_constant<int, 5>{});

@@ -13,7 +13,9 @@ __device__ __forceinline__ float quad_sum(float v) {
 
 template <int NR>
 struct SmallQrShared {
-    static constexpr int SEG = (NR + 3) / 4 * 4 + 4;     // pitch of one quad lane's share of the reflector
+    // pitch of one quad lane's share of the reflector: the four shares fall on distinct banks (not with a multiple of 32: at 25
+    // rows per lane 84 rows took 54 us with a pitch of 32, 51 with 36)
+    static constexpr int SEG = (NR + 3) / 4 * 4 + ((NR + 3) / 4 * 4 % 32 == 28 ? 8 : 4);
     __attribute__((aligned(16))) float u[2][4][SEG];
     float inv[2];
     float rdiag[4 * NR];
@@ -30,8 +32,8 @@ struct SmallQrShared {
 // norm carries; with 1 / (norm (norm + |top|)) by the bare hardware reciprocal each step stretched its direction by up to
 // three roundings), and the product walks upward, so that u's large top entry is added last instead of lifting every
 // partial sum.  A^T A - I, rms over 96 draws: 8% less than with a thread per column at 33 to 128 rows (6% at 16), where
-// without the two it was 2 to 7% more; R = A^T G below the diagonal 2% less to 1% more (4 to 9% more without).  Cost: nothing at 68 rows,
-// 3 of 65 us at 100.
+// without the two it was 2 to 7% more; R = A^T G below the diagonal 2% less to 1% more (4 to 9% more without).  Cost: 0.3 of
+// 38 us at 68 rows, 2 of 58 at 100.
 // On return the columns c >= n hold Q^T (thread (n + i, q): Q[i][q + 4 t] in x[t]) and sh.rdiag the diagonal of R.
 template <int NR>
 __device__ __forceinline__ void small_householder(float (&x)[NR], int n, SmallQrShared<NR>& sh) {
