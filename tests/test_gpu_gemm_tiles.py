@@ -34,6 +34,33 @@ def test_bf16_rows_behind_the_last_whole_tile(m, n, k):
     check(m, k, n, torch.bfloat16)
 
 
+
+# the same rows in mix and un-mix: B in two segments (data rows, then shield rows) that meet inside a K step, and a K that fills no
+# step (572 + 28 rows: 600 = 9 x 64 + 24).  The operands are the library's own, read back: A and A^-1 rounded as it rounds them,
+# the shield rows as they are stored
+@pytest.mark.parametrize("width", [16384, 22016])
+def test_bf16_rows_behind_the_last_whole_tile_of_a_mix(width):
+    n_data, k = 572, 28
+    n = n_data + k
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(width)
+    H = torch.randn((n_data, width), generator=gen, device="cuda").to(torch.bfloat16)
+    Y = torch.randn((n, width), generator=gen, device="cuda").to(torch.bfloat16)
+    U, Z = torch.full((n + 2, width), float("nan"), device="cuda", dtype=torch.bfloat16), torch.full((n_data + 2, width), float("nan"), device="cuda", dtype=torch.bfloat16)
+    ctx = g.gelo_create(0, 1)
+    m = g.gelo_sample_mixing(ctx, g.GELO_REFLECTOR_PRODUCT, n_data, k, width, g.GELO_BF16, batch_id=1)
+    g.gelo_mix(ctx, m, H, U[1:n + 1])
+    g.gelo_unmix(ctx, m, Y, Z[1:n_data + 1])
+    A, A_inv, S, _, _ = g.gelo_mixing_export(ctx, m, n, k, width)
+    torch.cuda.synchronize()
+    g.gelo_mixing_free(ctx, m)
+    g.gelo_destroy(ctx)
+    for out, rows, left, right in ((U, n, A, torch.cat([H.double(), S.double()])), (Z, n_data, A_inv[:n_data], Y.double())):
+        left = left.to(torch.bfloat16).double()
+        assert torch.isnan(out[0]).all() and torch.isnan(out[-1]).all()
+        ref, size = left @ right, left.abs() @ right.abs()
+        assert bool(((out[1:rows + 1].double() - ref).abs() <= 2.0 ** -8 * 1.01 * ref.abs() + n * 2.0 ** -24 * size).all())
+
 # 64 x 64 tiles up to one round of 128 x 128 ones, the large tiles beyond; broken tiles, and K that fills no step
 @pytest.mark.parametrize("m,k,n", [(1, 136, 8), (63, 136, 72), (64, 264, 64), (65, 136, 200), (543, 776, 1544), (1000, 64, 776),
                                    (2048, 40, 2048), (2049, 40, 2048), (2048, 40, 2056), (129, 512, 2304)])
