@@ -58,11 +58,11 @@ def chain_flops(w):
 def gen_flops(w, attempts=1):
     n = float(w.n)
     qr = 8.0 / 3.0 * n ** 3            # Householder QR with explicit Q
-    lu = 2.0 * n ** 3                  # LU + explicit inverse
+    inv = 2.0 * n ** 3                 # explicit inverse of a given matrix by the fewest operations (an LU); the library's QR takes 11/3 n^3
     if w.kind == 4:
         return sum(8.0 / 3.0 * float(r) ** 3 for r, _ in block_rows(w.n_data, w.k_shield))
     # structured: sorting keys, no arithmetic to count; product of directly drawn reflectors: only Q is formed
-    return {0: qr, 1: lu * attempts, 2: qr + lu, 3: 0.0, 5: 4.0 / 3.0 * n ** 3}[w.kind]
+    return {0: qr, 1: inv * attempts, 2: qr + inv, 3: 0.0, 5: 4.0 / 3.0 * n ** 3}[w.kind]
 
 
 CAL_ELEMS = 1 << 28                                   # fp32 elements of the calibration copy: 1 GiB read, 1 GiB written

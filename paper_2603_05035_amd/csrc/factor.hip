@@ -601,7 +601,7 @@ void qr_bulk_kernel(QrBulkArgs a) {
 // because a reflector keeps inner products: with G the Gram matrix of rows j onward, beta = -sign(alpha) sqrt(G[j][j]),
 // row j of R is G[j][s] / beta, column s loses f_s = (P[j][s] - G[j][s] / beta) / (alpha - beta) times column j, and the
 // Gram matrix of the rows below j is G[i][s] - G[i][j] G[j][s] / G[j][j].  All of it happens on 16 x 16 matrices - G, the
-// panel's top tile and the column operations X accumulated so far - which every wave keeps for itself, lane (., s) holding
+// panel's top tile and the column operations X accumulated so far - which wave 0 keeps in registers, lane (., s) holding
 // column s of each: one step is "column s -= coefficient(s) x column j", the broadcast of column j a DPP modifier of the
 // multiply-add.  Then V = [L ; P2 X]: one product of the rows below the top tile with X, on the matrix cores, straight
 // from the accumulator layout the strip is in.  The triangle T is the inverse of V^T V's upper triangle with half its
@@ -612,7 +612,9 @@ void qr_bulk_kernel(QrBulkArgs a) {
 // Bound by the latency of one workgroup.  With the strip in front, per launch: 22 us at 2100 rows (30 with a reduction and a
 // barrier per column), 9 us at 500 rows (15), of which the launch itself is 4; a whole draw alone: 2150 rows 3.91 -> 2.68 ms,
 // 543 rows 591 -> 412 us, 4096 rows 15 -> 9.3 (8.6 with the long strips through
-// qr_bulk_kernel).  Against 64 bits, six seeds: A as close as before (2.3e-6 at 1000 rows), A^T A = I closer (8.83e-7 -> 8.66e-7).
+// qr_bulk_kernel).  Against 64 bits, compared with a reduction per column on the same Gaussians (24 draws at each of 12 sizes from
+// 129 to 517 rows, 8 at 1000, 4 at 2150, 2 at 4096): |A^T A - I| 0.95 to 0.99 of it, part of A^T G below the diagonal 0.99 to 1.00,
+// distance of A from the exact factor 0.90 to 1.05 (geometric means; the factor itself moves by the Gaussian's condition number).
 constexpr int kGramPanelRows = 64;       // panels of more rows than this are built from their Gram matrix
 
 // value of lane J of the row of 16 lanes
@@ -772,9 +774,9 @@ __device__ __forceinline__ void gram_panel_body(GramShared<NBLK>& sh, f32x4_t (&
     __syncthreads();
     if (wave == 0) {
         // T, while the other waves form V (this one has a block less than they have).  V^T V in double precision, from the
-        // float Gram matrix: its rounding would be what the orthogonality of I - V T V^T is lost to (1.1e-6 per panel in
-        // the Frobenius norm with float products, 0.6e-6 this way, 0.9e-6 with the sums of qr_panel_body).  The double
-        // instruction leaves row 4 v + g of column c in element v.
+        // float Gram matrix: its rounding would be what the orthogonality of I - V T V^T is lost to (|A^T A - I| / sqrt(n) at
+        // 129, 300 and 1000 rows: 4.8e-7, 5.9e-7, 9.1e-7 with float products, 4.2e-7, 5.3e-7, 8.65e-7 this way, 4.3e-7, 5.5e-7,
+        // 8.8e-7 with the sums of qr_panel_body).  The double instruction leaves row 4 v + g of column c in element v.
         f64x4_t gx = {0., 0., 0., 0.}, m = {0., 0., 0., 0.};
 #pragma unroll
         for (int e = 0; e < 4; ++e) gx = __builtin_amdgcn_mfma_f64_16x16x4f64((double)gb[e], (double)xd[e], gx, 0, 0, 0);

@@ -12,7 +12,7 @@
 namespace gelo {
 
 constexpr int kPanel = 16;          // column-panel width of the QR
-constexpr int kMaxN = 5120;         // 512 threads x 10 register-resident rows in the panel kernels
+constexpr int kMaxN = 5120;         // 512 threads x 10 register-resident rows in the panel kernels, 8 waves x 40 blocks of 16 in the strips
 constexpr int kInvBlock = 128;      // block width of the inverse's back substitution: its updates are GEMMs with K = 128
 
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
@@ -229,16 +229,16 @@ int structured_max_rows();
 // --------------------------------------------------------- factorisations --
 // Workspace for one n_pad x ld float problem (n_pad = round_up(n, kPanel), ld = round_up(n, 64)).
 struct FactorWorkspace {
-    float* M;        // the matrix being factorised (G, then R + reflectors / L\U)
-    float* X;        // the result being accumulated (Q, or A^-1)
-    float* Vc;       // QR: two alternating pairs of compact reflector blocks (n_pad x 16 and 16 x n_pad)
+    float* M;        // the matrix being factorised: G, then R above its diagonal tiles and the reflectors (tiled) from them down; A^-1 (beyond 128 rows)
+    float* X;        // Q
+    float* Vc;       // every panel's reflectors row by row (n_pad x 16 each), later R row by row
     float* Tmat;     // per panel: the 16 x 16 triangle T of the block reflector I - V T V^T
     float* Rd;       // QR: the 16 x 16 diagonal tiles of R, row-major (its other tiles stay in M, above the reflectors)
-    float* Dinv;     // inverses of R's diagonal blocks (pitch kInvBlock, n_pad rows)
+    float* Dinv;     // inverses of R's diagonal blocks (pitch kInvBlock, n_pad rows; beyond 128 rows)
     float* rdiag;    // n_pad: diagonal of R
     float* vec;      // 8 * ld floats: the Lanczos vectors of the condition estimate
     float* tri;      // its tridiagonal coefficients (2 operators x (alpha, beta) x 32)
-    int*   flag;     // singular-pivot flag
+    int*   flag;     // R has a zero on its diagonal
     float* scalars;  // [0] kappa estimate, [1] sigma_max, [2] 1 / sigma_min
     int n_pad; int64_t ld;
 };
@@ -247,8 +247,8 @@ void factor_workspace_carve(void* base, int n, FactorWorkspace* ws);
 
 // ws.M holds an n x n matrix in 16 x 16 tiles (qr_tile_index with n_pad / 16 tile rows; what lies
 // beyond n need not be initialised).  On return ws.X holds the orthogonal factor Q of its Householder
-// QR in the same tiled layout (identity in the padding block), ws.M and ws.Vc the reflectors, and
-// ws.rdiag the diagonal of R.  `count` > 1 factorises that many matrices side by side in the same launches (grid y):
+// QR in the same tiled layout (identity in the padding block), ws.M and ws.Vc the reflectors, ws.M
+// and ws.Rd the triangle R and ws.rdiag its diagonal.  `count` > 1 factorises that many matrices side by side in the same launches (grid y):
 // matrix i's workspace is the one carved at `batch_stride` floats times i behind ws's (same n for all).
 // `direct`: the reflectors are NOT those of a factorisation: reflector k is built from column k of ws.M as it
 // stands (rows k onward), so ws.X becomes the product H_0 H_1 ... H_{n-1} of directly drawn reflectors and

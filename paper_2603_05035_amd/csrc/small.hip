@@ -3,9 +3,9 @@
 //
 //   small_sample   draws the secrets of MANY batches at once (Section 3.2 step 1.2: a fresh A per batch; a
 //                  decode step needs one per layer, and A does not depend on the data, so a whole step's
-//                  worth is drawn ahead in one launch).  One workgroup per matrix: Philox Gaussian straight
-//                  into LDS, unblocked Householder QR there, A = Q diag(sign r_ii) and its transpose written
-//                  out; one more workgroup per shield direction row.
+//                  worth is drawn ahead in one launch).  One workgroup per matrix: Philox Gaussian into
+//                  LDS, unblocked Householder QR in registers (small_qr.h), A = Q diag(sign r_ii) and its
+//                  transpose written out; one more workgroup per shield direction row.
 //   small_mix      shield rows (row-norm statistic of H, exact-norm scaling; Section 3.2.1 eqs. 7-8) and
 //                  U = A [H ; S] (eq. 1) in one launch.
 //

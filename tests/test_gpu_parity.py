@@ -198,8 +198,8 @@ def test_orthogonal_mixing_matrix_at_the_largest_n(ctx):
 
 
 def test_conditioned_inverse_at_the_largest_n(ctx):
-    """n = GELO_MAX_N through the pivoted LU: ten register rows per thread in the panels, forty column
-    windows, forty outer blocks.  A^-1 is pinned by what defines it (both products give the identity to
+    """n = GELO_MAX_N through the QR and the inverse from it: forty blocks per wave in the strips and panels, forty
+    blocks of 128 in the back substitution.  A^-1 is pinned by what defines it (both products give the identity to
     float rounding times n), the condition estimate by the bounds of the construction
     (singular values within 1 +- 2 * 0.25 up to fluctuations) and by ||A||_2 ||A^-1||_2 from a few
     float64 power iterations on the exported matrices."""
@@ -458,10 +458,10 @@ def test_conditioned_matrix_construction(ctx):
 
 @pytest.mark.parametrize("n", [16, 130, 928, 1100, 2070])
 def test_pivoted_lu_inverse_across_block_boundaries(ctx, n):
-    """The explicit inverse behind the non-orthogonal kinds, at sizes that cross the boundaries of the
-    blocked LU (a single panel; a 128-column outer block plus a short one; eight column windows; panels of
-    more than 1024 and of more than 2048 rows): A^-1 against the float64 inverse of the SAME matrix, the
-    residual of the product, and the condition estimate against numpy's."""
+    """The explicit inverse behind the non-orthogonal kinds (R^-1 Q^T from the QR, where a pivoted LU stood), at one
+    tile, just beyond the 128 rows of the one-launch inverse (a block of 128 and a broken tile), and with 8, 9 and 17
+    blocks of 128, the last one broken: A^-1 against the float64 inverse of the SAME matrix, the residual of
+    the product, and the condition estimate against numpy's."""
     for kind, cond_max in ((g.GELO_CONDITIONED, 0.0), (g.GELO_GAUSSIAN, 1e12)):
         if kind == g.GELO_GAUSSIAN and n > 1000:
             continue          # kappa ~ n: the float inverse itself is then too inexact to pin the estimate to 5%
@@ -471,7 +471,7 @@ def test_pivoted_lu_inverse_across_block_boundaries(ctx, n):
         A, A_inv = f64(A), f64(A_inv)
         kappa_ref = np.linalg.cond(A)
         assert abs(kappa - kappa_ref) / kappa_ref < 0.05
-        # float LU + substitution: error ~ n eps32 kappa (eps32 = 2^-24)
+        # float QR + substitution: error ~ n eps32 kappa (eps32 = 2^-24)
         assert o.rel_frobenius(A_inv, np.linalg.inv(A)) < max(n, 64) * 2.0 ** -24 * kappa_ref
         assert np.linalg.norm(A @ A_inv - np.eye(n)) / math.sqrt(n) < max(n, 64) * 2.0 ** -24 * kappa_ref
 
@@ -532,7 +532,7 @@ def test_full_size_sweep_layers(ctx, name, layer):
     print(name, "rel err", err, "kappa", r["kappa"])
     n = w.n
     A = f64(r["A"])
-    # float LU + substitution: residual per row ~ n * eps32 * kappa (eps32 = 2^-24)
+    # float QR + substitution: residual per row ~ n * eps32 * kappa (eps32 = 2^-24)
     assert np.linalg.norm(A @ f64(r["A_inv"]) - np.eye(n)) / math.sqrt(n) < n * 2.0 ** -24 * max(r["kappa"], 1.0)
     if name == "sweep_bf16_cond":
         assert r["kappa"] < 100.0
