@@ -131,7 +131,7 @@ void diag_inverse_kernel(const float* M, const float* Rd, float* Dinv, int nbr, 
 // The products keep the accumulator layout throughout: what the matrix instructions leave in a lane (column c, rows 4 g ..)
 // is what they take as right operand when instruction e contracts the rows 4 g + e.
 // Bound by latency: a chain of at most 8 tile rows, twice; the other waves only load and form residuals.  Without the
-// refinement R^-1 Q^T is further off than a row-pivoted LU's inverse up to 40 rows (rms over 48 matrices: GAUSSIAN 16 rows,
+// refinement R^-1 Q^T is further off than a row-pivoted LU's inverse up to 40 rows (geometric means over 48 matrices: GAUSSIAN 16 rows,
 // |A^-1 A - I| 2.2 times, H recovered from A H 1.9 times as far off, CONDITIONED 8 rows 1.7 and 1.5 times), and with R^-1 as a
 // GEMM operand it takes seven launches.  With it, against the LU: |A^-1 A - I| 0.19 and 0.23, H recovered 0.57 and 0.59, at
 // 128 rows 0.04 and 0.31 (GAUSSIAN).  CONDITIONED draw (LU, seven launches, one): 16 rows 246, 236, 204 us; 64 rows 383, 366, 334;

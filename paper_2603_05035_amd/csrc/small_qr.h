@@ -31,7 +31,7 @@ struct SmallQrShared {
 // Two things keep A orthogonal: inv is 2 / u^T u of the u in LDS (I - inv u u^T is then a reflection whatever rounding the
 // norm carries; with 1 / (norm (norm + |top|)) by the bare hardware reciprocal each step stretched its direction by up to
 // three roundings), and the product walks upward, so that u's large top entry is added last instead of lifting every
-// partial sum.  A^T A - I, rms over 96 draws: 8% less than with a thread per column at 33 to 128 rows (6% at 16), where
+// partial sum.  A^T A - I, rms over 96 draws: 7 to 8% less than with a thread per column at 36 to 128 rows (4 to 6% at 16 to 33), where
 // without the two it was 2 to 7% more; R = A^T G below the diagonal 2% less to 1% more (4 to 9% more without).  Cost: 0.3 of
 // 38 us at 68 rows, 2 of 58 at 100.
 // On return the columns c >= n hold Q^T (thread (n + i, q): Q[i][q + 4 t] in x[t]) and sh.rdiag the diagonal of R.
