@@ -27,7 +27,7 @@ constexpr uint32_t kStreamMixing = 0, kStreamShield = 1, kStreamPerturb = 2, kSt
 // attempt order wins - the same matrix a one-at-a-time loop would return.
 constexpr int kLanes = 4;
 constexpr int kQrSideBySide = 32;       // batched ORTHOGONAL draws: factorisations that share each launch, at most
-constexpr size_t kQrSideBytes = (size_t)4 << 30;   // ... and no more of them than fit this much workspace
+constexpr size_t kQrSideBytes = (size_t)8 << 30;   // ... and no more of them than fit this much workspace
 // how many factorisations of an n x n matrix a batched draw of `count` runs side by side
 static int qr_side_by_side(int count, size_t ws_bytes) {
     int side = count < kQrSideBySide ? count : kQrSideBySide;
@@ -353,7 +353,7 @@ gelo_status gelo_create(gelo_ctx** out, int device, uint64_t seed, int allow_bat
     ctx->host_flag = (int*)(ctx->host_scalars + 8);
     if (gemm_bf16_init() != hipSuccess || gemm_f32_init() != hipSuccess || inverse_init() != hipSuccess ||
         structured_init() != hipSuccess || small_init() != hipSuccess || gemm_fp8_init() != hipSuccess ||
-        factor_init() != hipSuccess || sampler_init() != hipSuccess) {
+        factor_init() != hipSuccess || block_reflect_init() != hipSuccess || sampler_init() != hipSuccess) {
         hipHostFree(ctx->host_scalars); delete ctx; return GELO_EHIP;
     }
     *out = ctx;

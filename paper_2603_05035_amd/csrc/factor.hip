@@ -548,47 +548,20 @@ __device__ __forceinline__ void reflect_strip_lds_body(const Reflector* refl, in
 }
 
 // A block of panels applied to `outer` strips from Cout (the factorisation: the columns behind a finished block)
-// or to `acc` strips from X (forming Q), for `count` matrices, one strip per workgroup.  Which workgroup takes which strip of which matrix is chosen for the
-// L2s: workgroups are dealt to the 8 accelerator dies in turn (die = workgroup number mod 8), every strip of a matrix
-// reads that matrix's reflectors (1.1 MB for a block of four) and a die's L2 holds 4 MB - so a die works through
-// whole matrices one after the other (matrices die, die + 8, ...; with fewer than 8 matrices the dies that share a
-// matrix split its strips) instead of meeting all `count` sets of reflectors at once.  A count that is not a
-// multiple of 8 is dealt in two parts: whole rounds of 8 matrices, one per die, then the remaining count % 8
-// matrices with their strips split over the dies that share each (20 matrices: two rounds, then 4 matrices on two
-// dies each - a die works off 2.5 matrices' strips, not 3).
+// or to `acc` strips from X (forming Q), for `count` matrices, one strip per workgroup, dealt to the dies matrix by matrix
+// (deal_to_dies; a matrix's reflectors of a block of four panels are 1.1 MB).
 struct QrBulkArgs {
     Reflector refl[kMaxProduct]; int pending;
     float* Cout; float* X; int outer, acc;
     int64_t strip_stride; int nb_block; int64_t batch_stride; int count;
 };
-// workgroups per die that the deal needs
-inline int qr_bulk_slots(int strips, int count) {
-    const int rounds = count / 8, rest = count % 8;
-    int slots = rounds * strips;
-    if (rest > 0) {
-        const int dies = 8 / rest;                           // the fewest dies any of the remaining matrices gets
-        slots += (strips + dies - 1) / dies;
-    }
-    return slots;
-}
-
 // Up to 160 blocks a strip fits the 128 registers of two workgroups per CU; longer ones (20 to 40 blocks per wave) have a CU
 // to themselves.
 template <int NBLK>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBLK <= 20 ? 4 : 2, NBLK <= 20 ? 4 : 2)))
 void qr_bulk_kernel(QrBulkArgs a) {
-    const int die = blockIdx.x & 7, slot = blockIdx.x >> 3, strips = a.outer + a.acc;
-    const int rounds = a.count >> 3, rest = a.count & 7;
     int matrix, b;
-    if (slot < rounds * strips) { matrix = die + 8 * (slot / strips); b = slot % strips; }
-    else {
-        if (rest == 0) return;
-        const int mr = die % rest;
-        const int sharing = (8 - mr + rest - 1) / rest;      // dies with die % rest == mr
-        matrix = 8 * rounds + mr;
-        b = (slot - rounds * strips) * sharing + die / rest;
-    }
-    if (matrix >= a.count || b >= strips) return;
+    if (!deal_to_dies(blockIdx.x, a.outer + a.acc, a.count, &matrix, &b)) return;
     const int64_t off = (int64_t)matrix * a.batch_stride;
     float* Cs = b < a.outer ? a.Cout + (int64_t)b * a.strip_stride : a.X + (int64_t)(b - a.outer) * a.strip_stride;
     reflect_strip_lds_body<NBLK>(a.refl, a.pending, off, Cs + off, a.nb_block);
@@ -959,10 +932,20 @@ hipError_t launch_direct_panels(int rows_per_thread, const FactorWorkspace& ws, 
 
 }  // namespace
 
+// From here on Q is formed 256 reflectors at a time by block_reflect.hip, below 128 at a time by strips.  One product of
+// directly drawn reflectors alone: 640 rows 145 us by strips, 157 by blocks, 1024 rows 240 / 199, 2150 rows 725 / 450, 4301 rows
+// 2840 / 1450; 8 side by side 1024 rows 431 / 473, 1300 rows 747 / 741, 32 of 2150 rows 6916 / 6160.
+bool wide_rows(int n_pad) { return n_pad >= 1280; }
+
 size_t factor_workspace_bytes(int n) {
     const int64_t n_pad = round_up(n, NB), ld = round_up(n, 64);
     const int64_t floats = 3 * n_pad * ld + 2 * n_pad * NB + n_pad * kInvBlock + n_pad + 8 * ld + 256 + 64;
-    return (size_t)floats * sizeof(float) + 8192;
+    size_t bytes = (size_t)floats * sizeof(float) + 8192;
+    if (wide_rows((int)n_pad)) {
+        const int64_t nbr = n_pad / NB, blocks = (nbr + kWideTiles - 1) / kWideTiles, area = (int64_t)(kWideTiles * 16) * (kWideTiles * 16);
+        bytes += (size_t)wide_plane_values((int)n_pad) * 2 + (size_t)(nbr * 16 * kWideTiles * 16) * (3 * 2 + kWideChunks * 4) + (size_t)(blocks * area) * (4 + 8) + 4096;
+    }
+    return bytes;
 }
 
 void factor_workspace_carve(void* base, int n, FactorWorkspace* ws) {
@@ -980,6 +963,17 @@ void factor_workspace_carve(void* base, int n, FactorWorkspace* ws) {
     ws->tri = take(128);
     ws->scalars = take(16);
     ws->flag = (int*)take(16);
+    ws->Yp = ws->Yr = ws->Wp = nullptr; ws->Wpart = ws->Tbig = nullptr; ws->wide_gram = nullptr;
+    if (wide_rows((int)n_pad)) {
+        const int64_t nbr = n_pad / NB, blocks = (nbr + kWideTiles - 1) / kWideTiles, w = nbr * 16 * kWideTiles * 16, area = (int64_t)(kWideTiles * 16) * (kWideTiles * 16);
+        p = (float*)(((uintptr_t)p + 1023) & ~(uintptr_t)1023);
+        ws->Yp = (uint16_t*)take((wide_plane_values((int)n_pad) + 1) / 2);
+        ws->Yr = ws->Yp + wide_yr_offset((int)n_pad);
+        ws->Wp = (uint16_t*)take(w * 3 / 2);
+        ws->Wpart = take(w * kWideChunks);
+        ws->Tbig = take(blocks * area);
+        ws->wide_gram = (double*)take(blocks * area * 2);
+    }
     ws->n_pad = (int)n_pad;
     ws->ld = ld;
 }
@@ -1041,7 +1035,7 @@ hipError_t launch_first_panel(float* Mp, float* Vr, float* Vt, float* Tg, float*
 
 template <int NBLK>
 hipError_t launch_qr_bulk_t(const QrBulkArgs& b, int count, hipStream_t s) {
-    hipLaunchKernelGGL((qr_bulk_kernel<NBLK>), dim3(8 * qr_bulk_slots(b.outer + b.acc, count)), dim3(512), 0, s, b);
+    hipLaunchKernelGGL((qr_bulk_kernel<NBLK>), dim3(8 * dies_slots(b.outer + b.acc, count)), dim3(512), 0, s, b);
     return hipGetLastError();
 }
 
@@ -1144,6 +1138,7 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
         if (last) break;                                      // no panel and no column left
         GELO_TRY(launch_qr_step(a, count, s));
     }
+    if (wide_rows(n_pad)) return form_product_wide(ws, count, batch_stride, s);
     {
         // X = I so far.  Block by block from the last: X[p0:, p0:] <- H_p0 (H_p0+1 (... X[p0:, p0:])), one 16-column
         // strip per workgroup, the block's reflectors newest first, each as I - V T V^T.

@@ -25,6 +25,35 @@ __device__ __forceinline__ void static_for_impl(std::integer_sequence<int, Is...
 template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) { static_for_impl(std::make_integer_sequence<int, N>{}, f); }
 
+// Which workgroup of a launch over `count` matrices takes which of a matrix's `items`, chosen for the L2s: workgroups go to the
+// 8 accelerator dies in turn (die = workgroup number mod 8), the items of a matrix share its reflectors and a die's L2 holds
+// 4 MB - so a die works through whole matrices one after the other (matrices die, die + 8, ...; with fewer than 8 matrices
+// the dies that share a matrix split its items) instead of meeting all sets of reflectors at once.  A count that is not a
+// multiple of 8 is dealt in two parts: whole rounds of 8 matrices, one per die, then the remaining count % 8 matrices with
+// their items split over the dies that share each (20 matrices: two rounds, then 4 matrices on two dies each).
+// The launch has 8 * dies_slots(items, count) workgroups.
+inline int dies_slots(int items, int count) {
+    const int rounds = count / 8, rest = count % 8;
+    int slots = rounds * items;
+    if (rest > 0) {
+        const int dies = 8 / rest;                           // the fewest dies any of the remaining matrices gets
+        slots += (items + dies - 1) / dies;
+    }
+    return slots;
+}
+__device__ __forceinline__ bool deal_to_dies(int block, int items, int count, int* matrix, int* item) {
+    const int die = block & 7, slot = block >> 3, rounds = count >> 3, rest = count & 7;
+    if (slot < rounds * items) { *matrix = die + 8 * (slot / items); *item = slot % items; }
+    else {
+        if (rest == 0) return false;
+        const int mr = die % rest;
+        const int sharing = (8 - mr + rest - 1) / rest;      // dies with die % rest == mr
+        *matrix = 8 * rounds + mr;
+        *item = (slot - rounds * items) * sharing + die / rest;
+    }
+    return *matrix < count && *item < items;
+}
+
 // ---------------------------------------------------------------- GEMMs ----
 // C[M x N] = A[M x K] * B[K x N], row-major.  B is given as two row segments:
 // rows [0, K0) come from B0 (ldb0), rows [K0, K) from B1 (ldb1); this is how
@@ -56,6 +85,7 @@ hipError_t gemm_bf16_init();        // one-time kernel attribute set-up (large d
 hipError_t gemm_f32_init();
 hipError_t inverse_init();
 hipError_t factor_init();
+hipError_t block_reflect_init();
 hipError_t sampler_init();
 
 // 8-bit float projection (OCP FP8 E4M3 operands, float accumulation, bf16 result) --------------------------
@@ -240,8 +270,22 @@ struct FactorWorkspace {
     float* tri;      // its tridiagonal coefficients (2 operators x (alpha, beta) x 32)
     int*   flag;     // R has a zero on its diagonal
     float* scalars;  // [0] kappa estimate, [1] sigma_max, [2] 1 / sigma_min
+    // wide_rows(n_pad) only: products of 256 reflectors at a time (block_reflect.hip)
+    uint16_t* Yp; uint16_t* Yr;      // the reflectors taken apart for either product
+    uint16_t* Wp;                    // W' taken apart (n_pad / 16 tile columns)
+    float* Wpart;                    // sums of ranges of rows, up to kWideChunks of them
+    float* Tbig;                     // per wide block its 256 x 256 triangle
+    double* wide_gram;               // per wide block Y^T Y, tiles above the diagonal
     int n_pad; int64_t ld;
 };
+constexpr int kWideTiles = 16;       // tile columns of a wide block: 256 reflectors
+constexpr int kWideChunks = 8, kWideParts = 4;
+constexpr int kWideCus = 256;
+bool wide_rows(int n_pad);           // are the reflectors of such a matrix applied 256 at a time while Q is formed?
+int64_t wide_plane_values(int n_pad);        // 16-bit values of Yp and Yr together
+int64_t wide_yr_offset(int n_pad);           // Yr's start behind Yp's
+// ws.X <- H_0 H_1 ... ws.X for the panels' reflectors householder_qr has left in ws.M and ws.Tmat
+hipError_t form_product_wide(const FactorWorkspace& ws, int count, int64_t batch_stride, hipStream_t stream);
 size_t factor_workspace_bytes(int n);
 void factor_workspace_carve(void* base, int n, FactorWorkspace* ws);
 

@@ -221,3 +221,26 @@ def test_batched_draw_equals_single_draws(ctx, nd, k, d, count, picks):
             g.gelo_mixing_free(ctx, m)
     finally:
         g.gelo_destroy(single)
+
+
+# Reflectors applied 256 at a time (from 1280 rows of tiles on): the first such size, whole blocks, one tile and one row beyond
+# them, an odd number of tile rows and columns.  20 matrices take the kernels with Y in LDS (the smallest blocks of each matrix
+# still the others), one alone and the pair those with everything in registers; the sums run in the same order, so the bits agree
+@pytest.mark.parametrize("n", [1265, 1280, 1281, 1297, 1536, 1537, 1553])
+def test_blocks_of_256_reflectors(ctx, n):
+    first, count = 40 * n, 20
+    many = [g.gelo_mixing_export(ctx, m, n, 0, 64, want_shields=False)[0] for m in g.gelo_sample_mixing_batch(ctx, KIND, n, 0, 64, g.GELO_F32, first, count)]
+    other = g.gelo_create(0, SEED, allow_batch_reuse=False)
+    pair = [g.gelo_mixing_export(other, m, n, 0, 64, want_shields=False)[0] for m in g.gelo_sample_mixing_batch(other, KIND, n, 0, 64, g.GELO_F32, first, 2)]
+    m = g.gelo_sample_mixing(other, KIND, n, 0, 64, g.GELO_F32, 0.0, 1, batch_id=first + count - 1)
+    alone = g.gelo_mixing_export(other, m, n, 0, 64, want_shields=False)[0]
+    torch.cuda.synchronize()
+    g.gelo_destroy(other)
+    assert torch.equal(many[0], pair[0]) and torch.equal(many[1], pair[1]) and torch.equal(many[-1], alone)
+    cols = [0, 15, 16, 255, 256, n - 17, n - 2, n - 1]
+    ref = o.orthogonal_from_reflectors(o.gaussian_matrix(SEED, first + count - 1, o.STREAM_MIXING, 0, n, n), columns=cols)
+    got = f64(alone[:, cols])
+    assert o.rel_frobenius(got, ref) < product_bound(n)
+    assert np.abs(got - ref).max() < 16 * EPS
+    Ad = alone.to(torch.float64)
+    assert float((Ad.t().contiguous() @ Ad - torch.eye(n, device="cuda", dtype=torch.float64)).norm()) / math.sqrt(n) < product_bound(n)
