@@ -353,7 +353,7 @@ gelo_status gelo_create(gelo_ctx** out, int device, uint64_t seed, int allow_bat
     ctx->host_flag = (int*)(ctx->host_scalars + 8);
     if (gemm_bf16_init() != hipSuccess || gemm_f32_init() != hipSuccess || inverse_init() != hipSuccess ||
         structured_init() != hipSuccess || small_init() != hipSuccess || gemm_fp8_init() != hipSuccess ||
-        factor_init() != hipSuccess || block_reflect_init() != hipSuccess || sampler_init() != hipSuccess) {
+        factor_init() != hipSuccess || block_reflect_init() != hipSuccess || block_factor_init() != hipSuccess || sampler_init() != hipSuccess) {
         hipHostFree(ctx->host_scalars); delete ctx; return GELO_EHIP;
     }
     *out = ctx;

@@ -5,10 +5,7 @@
 //   W' = -T W                reflect_w_kernel
 //   X += Y W'                reflect_update_kernel  contraction over the 256 reflectors
 //
-// The two large products run on the bf16 matrix instructions with every float taken apart into three bf16 values,
-// x = h + m + l (each the rounding of what the ones before leave: 8 + 8 + 8 significant bits, nothing is lost), and six of
-// the nine products: h h, h m, m h, m m, h l, l h.  What is left out is below 2^-25 of |x y|; the sums are float.
-// Six bf16 instructions take 3/8 of the time of the float ones for the same contraction.
+// The two large products run on the bf16 matrix instructions with every float taken apart into three bf16 values (split_float.h).
 //
 // Everything stays in the 16 x 16 tiles of the factorisation (qr_tile_index): v_mfma_f32_16x16x32_bf16 leaves a tile in the
 // same accumulator layout as the float instruction, and a lane's eight values of the contraction are rows 4 g .. 4 g + 3 of
@@ -20,58 +17,12 @@
 // T of 256 reflectors: T^-1's upper triangle is Y^T Y's (contracted in double precision: its rounding is what the
 // orthogonality of I - Y T Y^T is lost to), its diagonal blocks are the 16 x 16 triangles of the panels.
 #include "gelo_internal.h"
+#include "block_reflect.h"
 
 namespace gelo {
 namespace {
 
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef double f64x4_t __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
 constexpr int WT = kWideTiles;                            // tile columns of a wide block
-constexpr int kFrag = 512;                                // bf16 values of a fragment
-constexpr int kUnitYp = 3 * WT * kFrag;                   // of a pair of tile rows in Yp
-constexpr int kUnitYr = 3 * (WT / 2) * kFrag;             // of a tile row in Yr, and of a tile column in Wp
-
-// pairs of tile rows / tile rows in the blocks before block q (block q has nbr - 16 q tile rows)
-__host__ __device__ inline int64_t pairs_before(int nbr, int q) { return (int64_t)q * ((nbr + 1) / 2) - (int64_t)(WT / 4) * q * (q - 1); }
-__host__ __device__ inline int64_t rows_before(int nbr, int q) { return (int64_t)q * nbr - (int64_t)(WT / 2) * q * (q - 1); }
-
-struct Split { bf16x8_t h, m, l; };
-__device__ __forceinline__ Split split3(f32x4_t a, f32x4_t b) {
-    Split s;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float x = e < 4 ? a[e] : b[e - 4];
-        s.h[e] = (__bf16)x;
-        const float r = x - (float)s.h[e];
-        s.m[e] = (__bf16)r;
-        s.l[e] = (__bf16)(r - (float)s.m[e]);
-    }
-    return s;
-}
-
-__device__ __forceinline__ bf16x8_t frag_of(const uint16_t* p) { return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(p)); }
-
-// acc += A B for FA x FB fragments: A's plane p of fragment f is load_a(p, f), B in registers.  Small products first.
-template <int FA, int FB, class LoadA>
-__device__ __forceinline__ void products(LoadA&& load_a, const Split (&b)[FB], f32x4_t (&acc)[FA][FB]) {
-    bf16x8_t a[FA];
-    auto load = [&](int plane) {
-#pragma unroll
-        for (int f = 0; f < FA; ++f) a[f] = load_a(plane, f);
-    };
-    auto times = [&](bf16x8_t Split::*plane) {
-#pragma unroll
-        for (int f = 0; f < FA; ++f)
-#pragma unroll
-            for (int n = 0; n < FB; ++n) acc[f][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[f], b[n].*plane, acc[f][n], 0, 0, 0);
-    };
-    load(2); times(&Split::h);
-    load(1); times(&Split::m); times(&Split::h);
-    load(0); times(&Split::l); times(&Split::m); times(&Split::h);
-}
 
 // ------------------------------------------------------------ Y^T Y and the triangles --
 // Tile (i, j), i < j, of every wide block's Y^T Y, in double: a workgroup has two by two of them, its eight waves share the
@@ -204,11 +155,6 @@ void wide_planes_kernel(const float* M, uint16_t* Yp, uint16_t* Yr, int nbr, int
     Yp += 2 * (int64_t)blockIdx.y * batch_stride + (pairs_before(nbr, q) + pair) * kUnitYp + lane * 8;
     Yr += 2 * (int64_t)blockIdx.y * batch_stride + (rows_before(nbr, q) + 2 * pair) * kUnitYr + lane * 8;
     auto tile_of = [&](int r, int f) { return M + ((int64_t)(t0 + f) * nbr + t0 + r) * 256; };
-    auto put = [&](uint16_t* at, int64_t plane, const Split& s) {
-        *reinterpret_cast<u32x4_t*>(at) = __builtin_bit_cast(u32x4_t, s.h);
-        *reinterpret_cast<u32x4_t*>(at + plane) = __builtin_bit_cast(u32x4_t, s.m);
-        *reinterpret_cast<u32x4_t*>(at + 2 * plane) = __builtin_bit_cast(u32x4_t, s.l);
-    };
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const int f = wave + 8 * k;                       // tile column
@@ -219,7 +165,7 @@ void wide_planes_kernel(const float* M, uint16_t* Yp, uint16_t* Yr, int nbr, int
             v[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             if (f < mt && r < mt && r >= f) v[e] = *reinterpret_cast<const f32x4_t*>(tile_of(r, f) + c * 16 + 4 * g);
         }
-        put(Yp + f * kFrag, (int64_t)WT * kFrag, split3(v[0], v[1]));
+        put_split(Yp + f * kFrag, (int64_t)WT * kFrag, split3(v[0], v[1]));
     }
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
@@ -235,36 +181,24 @@ void wide_planes_kernel(const float* M, uint16_t* Yp, uint16_t* Yr, int nbr, int
                 for (int x = 0; x < 4; ++x) v[e][x] = tile_of(r, f)[(4 * g + x) * 16 + c];
             }
         }
-        put(Yr + (int64_t)k * kUnitYr + u * 3 * kFrag, kFrag, split3(v[0], v[1]));
+        put_split(Yr + (int64_t)k * kUnitYr + u * 3 * kFrag, kFrag, split3(v[0], v[1]));
     }
 }
 
 // ------------------------------------------------------------ the three products --
-struct WideArgs {
-    const uint16_t* Yp; const uint16_t* Yr;               // of this block
-    const float* T;                                       // of this block, 256 x 256
-    float* X;                                             // the matrix the reflectors meet, from its tile (t0, t0) on
-    float* Wpart; uint16_t* Wp;
-    int nbr, t0, mt;                                      // tile rows of the matrix, the block's first one, those from it on (as many columns)
-    int nt;                                               // tile columns of the block
-    int chunks, per_chunk;                                // the rows are cut into so many ranges of pairs of tile rows
-    int part_chunks, parts;                               // ranges per part, parts
-    int by_part;                                          // Wpart holds sums of parts (many matrices), not of ranges
-    int groups;                                           // of eight tile columns (rows)
-    int64_t batch_stride; int count;
-};
-
 // W.  The rows are cut into ranges, those into parts of a few ranges; the sums are added range by range, part by part, here or by
 // reflect_w_kernel: the bits do not depend on which kernel took the product.
-// Many matrices: a workgroup has 128 reflectors x 128 columns of one part, a wave 128 x 32 (each float is taken apart once in a
+// TC: tile columns of the block (16, or 8 in the factorisation).  Many matrices: a workgroup has 128 reflectors x 128 columns of one part, a wave 128 x 32 (each float is taken apart once in a
 // workgroup), Y through LDS.
+template <int TC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void reflect_wt_kernel(WideArgs a) {
+    constexpr int HALVES = TC / 8;
     __shared__ __attribute__((aligned(1024))) uint16_t stage[2][24 * kFrag];      // [plane][8 tile columns of Y]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int matrix, b;
-    if (!deal_to_dies(blockIdx.x, 2 * a.groups * a.parts, a.count, &matrix, &b)) return;
-    const int half = b & 1, part = (b >> 1) % a.parts, cg = (b >> 1) / a.parts;
+    if (!deal_to_dies(blockIdx.x, HALVES * a.groups * a.parts, a.count, &matrix, &b)) return;
+    const int half = b % HALVES, part = b / HALVES % a.parts, cg = b / (HALVES * a.parts);
     const int units = (a.mt + 1) / 2, per_part = a.per_chunk * a.part_chunks;
     const int t_begin = part * per_part, t_end = t_begin + per_part < units ? t_begin + per_part : units;
     const uint16_t* yp = a.Yp + 2 * (int64_t)matrix * a.batch_stride + half * 8 * kFrag + lane * 8;
@@ -275,7 +209,7 @@ void reflect_wt_kernel(WideArgs a) {
         const int col = cg * 8 + wave * 2 + n < a.mt ? cg * 8 + wave * 2 + n : a.mt - 1;
         xc[n] = a.X + (int64_t)matrix * a.batch_stride + (int64_t)col * a.nbr * 256 + (lane & 15) * 16 + 4 * (lane >> 4);
         // as the lanes hold it: only reflect_w_kernel reads it
-        w[n] = a.Wpart + (int64_t)matrix * a.batch_stride + (((int64_t)part * a.mt + col) * WT + half * 8) * 256 + lane * 4;
+        w[n] = a.Wpart + (int64_t)matrix * a.batch_stride + (((int64_t)part * a.mt + col) * TC + half * 8) * 256 + lane * 4;
     }
     u32x4_t st[6];
     f32x4_t raw[2][2][2];
@@ -283,7 +217,7 @@ void reflect_wt_kernel(WideArgs a) {
 #pragma unroll
         for (int i = 0; i < 6; ++i) {
             const int id = wave * 6 + i;
-            st[i] = *reinterpret_cast<const u32x4_t*>(yp + (int64_t)t * kUnitYp + ((id >> 3) * WT + (id & 7)) * kFrag);
+            st[i] = *reinterpret_cast<const u32x4_t*>(yp + (int64_t)t * (3 * TC * kFrag) + ((id >> 3) * TC + (id & 7)) * kFrag);
         }
     };
     auto fetch_x = [&](int t, f32x4_t (&x)[2][2]) {
@@ -343,17 +277,19 @@ void reflect_wt_kernel(WideArgs a) {
     }
 }
 
-// Few matrices: a workgroup has 256 reflectors x 32 columns of one range of rows, a wave 64 x 32, everything two units ahead in
+// Few matrices: a workgroup has all reflectors x 32 columns (64 of a block of 128) of one range of rows, a wave 64 x 32, everything two units ahead in
 // registers: no barrier, and a launch takes little more than its few units.
+template <int TC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void reflect_wt_direct_kernel(WideArgs a) {
+    constexpr int RG = TC / 4, CP = 4 / RG;               // waves along the reflectors, along the columns
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int pairs = (a.mt + 1) / 2;
+    const int pairs = (a.mt + 1) / 2, sets = (pairs + CP - 1) / CP;
     int matrix, b;
-    if (!deal_to_dies(blockIdx.x, pairs * a.chunks, a.count, &matrix, &b)) return;
-    const int cp = b % pairs, chunk = b / pairs;
+    if (!deal_to_dies(blockIdx.x, sets * a.chunks, a.count, &matrix, &b)) return;
+    const int cp = b % sets * CP + wave / RG, fr = wave % RG * 4, chunk = b / sets;
     const int t_begin = chunk * a.per_chunk, t_end = t_begin + a.per_chunk < pairs ? t_begin + a.per_chunk : pairs;
-    const uint16_t* yp = a.Yp + 2 * (int64_t)matrix * a.batch_stride + wave * 4 * kFrag + lane * 8;
+    const uint16_t* yp = a.Yp + 2 * (int64_t)matrix * a.batch_stride + fr * kFrag + lane * 8;
     const float* xc[2];
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
@@ -374,7 +310,7 @@ void reflect_wt_direct_kernel(WideArgs a) {
 #pragma unroll
         for (int p = 2; p >= 0; --p)
 #pragma unroll
-            for (int f = 0; f < 4; ++f) yd[p][f] = frag_of(yp + (int64_t)tt * kUnitYp + (p * WT + f) * kFrag);
+            for (int f = 0; f < 4; ++f) yd[p][f] = frag_of(yp + (int64_t)tt * (3 * TC * kFrag) + (p * TC + f) * kFrag);
     };
     f32x4_t acc[4][2];
 #pragma unroll
@@ -401,7 +337,7 @@ void reflect_wt_direct_kernel(WideArgs a) {
         if (2 * cp + n >= a.mt) continue;
 #pragma unroll
         for (int f = 0; f < 4; ++f)
-            *reinterpret_cast<f32x4_t*>(a.Wpart + (int64_t)matrix * a.batch_stride + (((int64_t)chunk * a.mt + 2 * cp + n) * WT + wave * 4 + f) * 256 + lane * 4) = acc[f][n];
+            *reinterpret_cast<f32x4_t*>(a.Wpart + (int64_t)matrix * a.batch_stride + (((int64_t)chunk * a.mt + 2 * cp + n) * TC + fr + f) * 256 + lane * 4) = acc[f][n];
     }
 }
 
@@ -418,24 +354,9 @@ void reflect_w_kernel(WideArgs a) {
     for (int n = 0; n < NC; ++n) {
         const int col = col0 + n < a.mt ? col0 + n : a.mt - 1;
         const float* wp = a.Wpart + (int64_t)blockIdx.y * a.batch_stride + ((int64_t)col * WT + wave * 2) * 256 + lane * 4;
-        const int have = RANGES > kWideParts ? a.chunks : a.parts, per = RANGES > kWideParts ? a.part_chunks : 1;
-        f32x4_t s[2][RANGES];
 #pragma unroll
-        for (int ch = 0; ch < RANGES; ++ch)
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-                s[k][ch] = *reinterpret_cast<const f32x4_t*>(wp + (int64_t)(ch < have ? ch : have - 1) * a.mt * WT * 256 + k * 256);
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            f32x4_t part = s[k][0], total = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ch = 1; ch < RANGES; ++ch) {
-                if (ch >= have) break;
-                if (ch % per == 0) { total += part; part = s[k][ch]; }
-                else part += s[k][ch];
-            }
-            *reinterpret_cast<f32x4_t*>(&W[n][wave * 2 + k][lane * 4]) = total + part;
-        }
+        for (int k = 0; k < 2; ++k)
+            *reinterpret_cast<f32x4_t*>(&W[n][wave * 2 + k][lane * 4]) = sum_of_ranges<RANGES>(wp + k * 256, (int64_t)a.mt * WT * 256, a);
     }
     f32x4_t t[2][WT];                                     // its rows of T, all requested at once (zeros below the diagonal)
 #pragma unroll
@@ -458,12 +379,16 @@ void reflect_w_kernel(WideArgs a) {
                 for (int k = 0; k < 2; ++k) acc[k][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(t[k][s][e], w[e], acc[k][e & 1], 0, 0, 0);
         }
         if (col0 + n >= a.mt) break;
-        const Split s = split3(-(acc[0][0] + acc[0][1]), -(acc[1][0] + acc[1][1]));
-        uint16_t* out = a.Wp + 2 * (int64_t)blockIdx.y * a.batch_stride + ((int64_t)(col0 + n) * (WT / 2) + wave) * 3 * kFrag + lane * 8;
-        *reinterpret_cast<u32x4_t*>(out) = __builtin_bit_cast(u32x4_t, s.h);
-        *reinterpret_cast<u32x4_t*>(out + kFrag) = __builtin_bit_cast(u32x4_t, s.m);
-        *reinterpret_cast<u32x4_t*>(out + 2 * kFrag) = __builtin_bit_cast(u32x4_t, s.l);
+        put_split(a.Wp + 2 * (int64_t)blockIdx.y * a.batch_stride + ((int64_t)(col0 + n) * (WT / 2) + wave) * 3 * kFrag + lane * 8, kFrag,
+                  split3(-(acc[0][0] + acc[0][1]), -(acc[1][0] + acc[1][1])));
     }
+}
+
+// the first eight tile columns behind a block of the factorisation are its next panel: taken apart here, tile rows r and r + 1 of column cc
+__device__ __forceinline__ void next_panel(const WideArgs& a, int matrix, int r, int cc, f32x4_t v0, f32x4_t v1, int lane) {
+    if (r >= a.mt) return;
+    if (r + 1 >= a.mt) v1 = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    put_split(a.next + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(r / 2) * kUnitPanel + cc * kFrag + lane * 8, 8 * kFrag, split3(v0, v1));
 }
 
 // X += Y W', few matrices: a workgroup has 64 x 64 of X, a wave 32 x 32, two units ahead in registers
@@ -480,7 +405,7 @@ void reflect_update_direct_kernel(WideArgs a) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         ya[i] = a.Yr + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(r0 + i < a.mt ? r0 + i : a.mt - 1) * kUnitYr + lane * 8;
-        wb[i] = a.Wp + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(c0 + i < a.mt ? c0 + i : a.mt - 1) * kUnitYr + lane * 8;
+        wb[i] = a.Wp + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(c0 + i < a.mt ? c0 + i : a.mt - 1) * a.wp_unit + lane * 8;
     }
     bf16x8_t y[3][3][2];
     Split w[3][2];
@@ -518,6 +443,10 @@ void reflect_update_direct_kernel(WideArgs a) {
 #pragma unroll
         for (int n = 0; n < 2; ++n)
             if (r0 + f < a.mt && c0 + n < a.mt) *reinterpret_cast<f32x4_t*>(tile(f, n)) = acc[f][n];
+    if (a.next != nullptr && c0 < 8) {                    // wave-uniform
+#pragma unroll
+        for (int n = 0; n < 2; ++n) next_panel(a, matrix, r0, c0 + n, acc[0][n], acc[1][n], lane);
+    }
 }
 
 // X += Y W', many matrices: a workgroup has 128 rows x 128 columns of X, a wave 64 x 64.  One stage in LDS, the next one on its way to registers: two
@@ -536,7 +465,7 @@ void reflect_update_kernel(WideArgs a) {
     for (int i = 0; i < 2; ++i) {
         const int row = rg * 8 + wave * 2 + i, col = cg * 8 + wave * 2 + i;
         src[i] = a.Yr + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(row < a.mt ? row : a.mt - 1) * kUnitYr + lane * 8;
-        src[2 + i] = a.Wp + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(col < a.mt ? col : a.mt - 1) * kUnitYr + lane * 8;
+        src[2 + i] = a.Wp + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(col < a.mt ? col : a.mt - 1) * a.wp_unit + lane * 8;
     }
     u32x4_t st[4][3];
     auto fetch = [&](int u) {
@@ -579,6 +508,12 @@ void reflect_update_kernel(WideArgs a) {
         for (int n = 0; n < 4; ++n) {
             if (rg * 8 + wm * 4 + f < a.mt && cg * 8 + wn * 4 + n < a.mt) *reinterpret_cast<f32x4_t*>(tile(f, n)) = acc[f][n];
         }
+    if (a.next != nullptr && cg == 0) {
+#pragma unroll
+        for (int f = 0; f < 4; f += 2)
+#pragma unroll
+            for (int n = 0; n < 4; ++n) next_panel(a, matrix, rg * 8 + wm * 4 + f, wn * 4 + n, acc[f][n], acc[f + 1][n], lane);
+    }
 }
 
 #define GELO_TRY(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) return e_; } while (0)
@@ -599,6 +534,36 @@ hipError_t block_reflect_init() {    // brings this file's code onto the device 
     return hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&reflect_update_kernel));
 }
 
+void cut_into_ranges(WideArgs& a, int halves, int workgroups) {
+    // ranges of rows so that one matrix alone fills the chip about once, an even number of pairs of tile rows each
+    const int units = (a.mt + 1) / 2, want = kWideCus / workgroups;
+    const int chunks = want < 1 ? 1 : want > kWideChunks ? kWideChunks : want;
+    a.groups = (a.mt + 7) / 8;
+    a.per_chunk = ((units + chunks - 1) / chunks + 1) / 2 * 2;
+    a.chunks = (units + a.per_chunk - 1) / a.per_chunk;
+    a.part_chunks = (a.chunks + kWideParts - 1) / kWideParts;
+    a.parts = (a.chunks + a.part_chunks - 1) / a.part_chunks;
+    a.by_part = halves * a.groups * a.count >= kWideCus;
+}
+
+template <int TC>
+static hipError_t launch_wt(const WideArgs& a, hipStream_t s) {
+    const int pairs = (a.mt + 1) / 2;
+    constexpr int CP = 16 / TC;
+    if (a.by_part) hipLaunchKernelGGL((reflect_wt_kernel<TC>), dim3(8 * dies_slots(TC / 8 * a.groups * a.parts, a.count)), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((reflect_wt_direct_kernel<TC>), dim3(8 * dies_slots((pairs + CP - 1) / CP * a.chunks, a.count)), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+hipError_t launch_panel_products(const WideArgs& a, hipStream_t s) { return launch_wt<8>(a, s); }
+
+hipError_t launch_block_update(WideArgs a, hipStream_t s) {
+    a.groups = (a.mt + 7) / 8;
+    const int quads = (a.mt + 3) / 4;
+    if (a.groups * a.groups * a.count >= 2 * kWideCus) hipLaunchKernelGGL(reflect_update_kernel, dim3(8 * dies_slots(a.groups * a.groups, a.count)), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(reflect_update_direct_kernel, dim3(8 * dies_slots(quads * quads, a.count)), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
 hipError_t form_product_wide(const FactorWorkspace& ws, int count, int64_t batch_stride, hipStream_t s) {
     const int nbr = ws.n_pad / kPanel, blocks = (nbr + WT - 1) / WT;
     hipLaunchKernelGGL(wide_gram_kernel, dim3(blocks * kGramPairs, count), dim3(512), 0, s, ws.M, ws.wide_gram, nbr, batch_stride);
@@ -614,27 +579,14 @@ hipError_t form_product_wide(const FactorWorkspace& ws, int count, int64_t batch
         a.Yr = ws.Yr + rows_before(nbr, q) * kUnitYr;
         a.T = ws.Tbig + (int64_t)q * (WT * 16) * (WT * 16);
         a.X = ws.X + ((int64_t)a.t0 * nbr + a.t0) * 256;
-        a.Wpart = ws.Wpart; a.Wp = ws.Wp;
-        a.groups = (a.mt + 7) / 8;
-        // ranges of rows so that one matrix alone fills the chip once, an even number of pairs of tile rows each
-        const int units = (a.mt + 1) / 2, want = kWideCus / (2 * a.groups);
-        const int chunks = want < 1 ? 1 : want > kWideChunks ? kWideChunks : want;
-        a.per_chunk = ((units + chunks - 1) / chunks + 1) / 2 * 2;
-        a.chunks = (units + a.per_chunk - 1) / a.per_chunk;
-        a.part_chunks = (a.chunks + kWideParts - 1) / kWideParts;
-        a.parts = (a.chunks + a.part_chunks - 1) / a.part_chunks;
+        a.Wpart = ws.Wpart; a.Wp = ws.Wp; a.wp_unit = kUnitYr; a.next = nullptr;
         a.batch_stride = batch_stride; a.count = count;
-        a.by_part = 2 * a.groups * count >= kWideCus;
-        if (a.by_part) hipLaunchKernelGGL(reflect_wt_kernel, dim3(8 * dies_slots(2 * a.groups * a.parts, count)), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL(reflect_wt_direct_kernel, dim3(8 * dies_slots(units * a.chunks, count)), dim3(256), 0, s, a);
-        GELO_TRY(hipGetLastError());
+        cut_into_ranges(a, 2, 2 * ((a.mt + 7) / 8));
+        GELO_TRY(launch_wt<WT>(a, s));
         if (a.by_part) hipLaunchKernelGGL((reflect_w_kernel<4, kWideParts>), dim3((a.mt + 3) / 4, count), dim3(512), 0, s, a);
         else hipLaunchKernelGGL((reflect_w_kernel<1, kWideChunks>), dim3(a.mt, count), dim3(512), 0, s, a);
         GELO_TRY(hipGetLastError());
-        const int quads = (a.mt + 3) / 4;
-        if (a.groups * a.groups * count >= 2 * kWideCus) hipLaunchKernelGGL(reflect_update_kernel, dim3(8 * dies_slots(a.groups * a.groups, count)), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL(reflect_update_direct_kernel, dim3(8 * dies_slots(quads * quads, count)), dim3(256), 0, s, a);
-        GELO_TRY(hipGetLastError());
+        GELO_TRY(launch_block_update(a, s));
     }
     return hipSuccess;
 }

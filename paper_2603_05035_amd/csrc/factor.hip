@@ -3,6 +3,9 @@
 // with the inverse of the non-orthogonal kinds, which is built on the same factorisation.  Everything is float and deterministic: reductions run in a fixed order, no
 // atomics.
 //
+// Matrices from 720 rows on are factorised by blocks of 128 columns down to their last 256 rows (block_factor.hip), and their Q is
+// formed by blocks of 256 (block_reflect.hip); what follows is the rest and everything smaller.
+//
 // Column panels are 16 wide.  A panel is factorised by ONE workgroup, from its 16 x 16 Gram matrix while it is tall
 // (gram_panel_body), by a loop over its columns at the end (qr_panel_body); the block reflectors are applied on the
 // matrix cores.
@@ -10,6 +13,7 @@
 #include <utility>
 
 #include "gelo_internal.h"
+#include "wave_tile.h"
 
 namespace gelo {
 namespace {
@@ -266,8 +270,6 @@ void direct_panels_kernel(float* M, float* Vc, float* Tmat, float* rdiag, int nb
 // lane: the strip is a column of 16 x 16 tiles (256 floats each, [column][row] inside: the four
 // rows 4 g .. 4 g + 3 a lane owns are adjacent), the reflectors come in the same tiles (Vt) for the
 // first product and as Vr[r * 16 + i] for the second.
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
 // One block reflector I - V op(T) V^T as a strip sees it: V in both layouts, its triangle, and `shift`, the
 // number of 16-row blocks by which its first row lies below the strip's first row (a strip behind a block of panels
@@ -590,30 +592,6 @@ void qr_bulk_kernel(QrBulkArgs a) {
 // distance of A from the exact factor 0.90 to 1.05 (geometric means; the factor itself moves by the Gaussian's condition number).
 constexpr int kGramPanelRows = 64;       // panels of more rows than this are built from their Gram matrix
 
-// value of lane J of the row of 16 lanes
-template <int J>
-__device__ __forceinline__ float row_bcast(float v) {                                      // row_newbcast:J
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x150 + J, 0xF, 0xF, true));
-}
-
-// col[i] += k x (col[i] of lane J of the row of 16), rows FROM <= i < TO: one instruction each, which the compiler does not
-// form by itself (it leaves a move with the broadcast and a multiply-add: twice the issue slots of the loop below).  The
-// register a broadcast reads must not have been written by one of the two preceding instructions: the leading wait covers
-// what the compiler put in front, inside each register is read and written once, the trailing one covers what follows.
-#define GELO_ROW(i) ".if (" #i " >= %c18) && (" #i " < %c19)\n\tv_fmac_f32_dpp %" #i ", %" #i ", %16 row_newbcast:%c17 row_mask:0xf bank_mask:0xf\n.endif\n\t"
-template <int J, int FROM, int TO>
-__device__ __forceinline__ void add_column(float (&col)[NB], float k) {
-    if constexpr (FROM < TO)
-        asm("s_nop 1\n\t"
-            GELO_ROW(0) GELO_ROW(1) GELO_ROW(2) GELO_ROW(3) GELO_ROW(4) GELO_ROW(5) GELO_ROW(6) GELO_ROW(7)
-            GELO_ROW(8) GELO_ROW(9) GELO_ROW(10) GELO_ROW(11) GELO_ROW(12) GELO_ROW(13) GELO_ROW(14) GELO_ROW(15)
-            "s_nop 1"
-            : "+v"(col[0]), "+v"(col[1]), "+v"(col[2]), "+v"(col[3]), "+v"(col[4]), "+v"(col[5]), "+v"(col[6]), "+v"(col[7]),
-              "+v"(col[8]), "+v"(col[9]), "+v"(col[10]), "+v"(col[11]), "+v"(col[12]), "+v"(col[13]), "+v"(col[14]), "+v"(col[15])
-            : "v"(k), "n"(J), "n"(FROM), "n"(TO));
-}
-#undef GELO_ROW
-
 constexpr int kTilePitch = NB + 4;       // floats per row of a 16 x 16 tile in LDS: row-wise 16-byte reads and column-wise 4-byte
                                          // writes of a wave are then both free of bank conflicts
 constexpr int kPanelGroup = 2;           // tiles a wave turns around in LDS at a time
@@ -625,18 +603,6 @@ struct GramShared {
     __attribute__((aligned(16))) float turn[8][kPanelGroup][NB * kTilePitch];
     __attribute__((aligned(16))) float first[NBLK][NB * kTilePitch];        // wave 0's tiles: its registers go to the 16 x 16 matrices
 };
-
-// lane (g, c) of a wave with all 16 rows of column c (the same in its four groups g) -> rows 4 g .. 4 g + 3
-__device__ __forceinline__ f32x4_t rows_of_group(const float (&col)[NB], int g) {
-    f32x4_t r;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const float c0 = col[e], c1 = col[4 + e], c2 = col[8 + e], c3 = col[12 + e];
-        const float lo = g & 1 ? c1 : c0, hi = g & 1 ? c3 : c2;
-        r[e] = g & 2 ? hi : lo;
-    }
-    return r;
-}
 
 // The panel is the strip cr (block wave + 8 b in cr[b], accumulator layout) from block FIRST on (its top tile) to block
 // `last`.  Outputs as qr_panel_body's: block FIRST of the panel goes to tile 0 of Vr and Vt.  512 threads.
@@ -932,10 +898,13 @@ hipError_t launch_direct_panels(int rows_per_thread, const FactorWorkspace& ws, 
 
 }  // namespace
 
-// From here on Q is formed 256 reflectors at a time by block_reflect.hip, below 128 at a time by strips.  One product of
-// directly drawn reflectors alone: 640 rows 145 us by strips, 157 by blocks, 1024 rows 240 / 199, 2150 rows 725 / 450, 4301 rows
-// 2840 / 1450; 8 side by side 1024 rows 431 / 473, 1300 rows 747 / 741, 32 of 2150 rows 6916 / 6160.
-bool wide_rows(int n_pad) { return n_pad >= 1280; }
+// From here on the QR goes by blocks of 128 columns (block_factor.hip) and Q is formed 256 reflectors at a time (block_reflect.hip);
+// below, and for the last 256 columns, panel by panel and by strips.
+bool wide_rows(int n_pad) { return n_pad >= 720; }
+// the product of directly drawn reflectors, which has no chain of panels to lose: 256 at a time from here on.  One alone, strips / blocks:
+// 640 rows 145 / 157 us, 1024 rows 240 / 199, 2150 rows 725 / 450, 4301 rows 2840 / 1440; 8 side by side 1024 rows 431 / 473,
+// 1300 rows 747 / 741, 32 of 2150 rows 6916 / 6160.
+constexpr int kWideProduct = 1280;
 
 size_t factor_workspace_bytes(int n) {
     const int64_t n_pad = round_up(n, NB), ld = round_up(n, 64);
@@ -943,7 +912,8 @@ size_t factor_workspace_bytes(int n) {
     size_t bytes = (size_t)floats * sizeof(float) + 8192;
     if (wide_rows((int)n_pad)) {
         const int64_t nbr = n_pad / NB, blocks = (nbr + kWideTiles - 1) / kWideTiles, area = (int64_t)(kWideTiles * 16) * (kWideTiles * 16);
-        bytes += (size_t)wide_plane_values((int)n_pad) * 2 + (size_t)(nbr * 16 * kWideTiles * 16) * (3 * 2 + kWideChunks * 4) + (size_t)(blocks * area) * (4 + 8) + 4096;
+        bytes += (size_t)wide_plane_values((int)n_pad) * 2 + (size_t)(nbr * 16 * kWideTiles * 16) * (3 * 2 + kWideChunks * 4) + (size_t)(blocks * area) * (4 + 8)
+               + (size_t)block_panel_values((int)n_pad) * 2 + (size_t)kCoreFloats * 4 + 4096;
     }
     return bytes;
 }
@@ -963,7 +933,7 @@ void factor_workspace_carve(void* base, int n, FactorWorkspace* ws) {
     ws->tri = take(128);
     ws->scalars = take(16);
     ws->flag = (int*)take(16);
-    ws->Yp = ws->Yr = ws->Wp = nullptr; ws->Wpart = ws->Tbig = nullptr; ws->wide_gram = nullptr;
+    ws->Yp = ws->Yr = ws->Wp = nullptr; ws->panel = nullptr; ws->Wpart = ws->Tbig = ws->core = nullptr; ws->wide_gram = nullptr;
     if (wide_rows((int)n_pad)) {
         const int64_t nbr = n_pad / NB, blocks = (nbr + kWideTiles - 1) / kWideTiles, w = nbr * 16 * kWideTiles * 16, area = (int64_t)(kWideTiles * 16) * (kWideTiles * 16);
         p = (float*)(((uintptr_t)p + 1023) & ~(uintptr_t)1023);
@@ -973,6 +943,8 @@ void factor_workspace_carve(void* base, int n, FactorWorkspace* ws) {
         ws->Wpart = take(w * kWideChunks);
         ws->Tbig = take(blocks * area);
         ws->wide_gram = (double*)take(blocks * area * 2);
+        ws->panel = (uint16_t*)take((block_panel_values((int)n_pad) + 1) / 2);
+        ws->core = take(kCoreFloats);
     }
     ws->n_pad = (int)n_pad;
     ws->ld = ld;
@@ -1098,11 +1070,14 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
         if (m <= kPanelRows256) GELO_TRY(launch_direct_panels<256>((m + 255) / 256, ws, nbr, count, batch_stride, s));
         else GELO_TRY(launch_direct_panels<512>((m + 511) / 512, ws, nbr, count, batch_stride, s));
     }
-    // panel 0 on its own; then one launch per step
+    // large matrices: blocks of 128 columns down to the last rows; then the first panel on its own and one launch per step
+    int start = 0;
     if (!direct) {
-        GELO_TRY(launch_first_panel(ws.M, Vr_of(0), Vt_of(0), ws.Tmat, ws.Rd, ws.rdiag, n_pad, count, batch_stride, s));
+        if (wide_rows(n_pad)) GELO_TRY(factor_blocks(ws, count, batch_stride, &start, s));
+        GELO_TRY(launch_first_panel(Vt_of(start), Vr_of(start), Vt_of(start), ws.Tmat + (int64_t)start * NB * NB, ws.Rd + (int64_t)start * NB * NB, ws.rdiag + start * NB,
+                                    n_pad - start * NB, count, batch_stride, s));
     }
-    for (int p = 0; p < panels && !direct; ++p) {
+    for (int p = start; p < panels && !direct; ++p) {
         const int p0 = p / D * D;                             // first panel of p's block
         const bool last = p + 1 == panels;
         const int block_end = p0 + D < panels ? p0 + D : panels;     // one past the block's last panel
@@ -1138,7 +1113,7 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
         if (last) break;                                      // no panel and no column left
         GELO_TRY(launch_qr_step(a, count, s));
     }
-    if (wide_rows(n_pad)) return form_product_wide(ws, count, batch_stride, s);
+    if (direct ? n_pad >= kWideProduct : wide_rows(n_pad)) return form_product_wide(ws, count, batch_stride, s);
     {
         // X = I so far.  Block by block from the last: X[p0:, p0:] <- H_p0 (H_p0+1 (... X[p0:, p0:])), one 16-column
         // strip per workgroup, the block's reflectors newest first, each as I - V T V^T.

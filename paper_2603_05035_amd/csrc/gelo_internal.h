@@ -86,6 +86,7 @@ hipError_t gemm_f32_init();
 hipError_t inverse_init();
 hipError_t factor_init();
 hipError_t block_reflect_init();
+hipError_t block_factor_init();
 hipError_t sampler_init();
 
 // 8-bit float projection (OCP FP8 E4M3 operands, float accumulation, bf16 result) --------------------------
@@ -276,6 +277,8 @@ struct FactorWorkspace {
     float* Wpart;                    // sums of ranges of rows, up to kWideChunks of them
     float* Tbig;                     // per wide block its 256 x 256 triangle
     double* wide_gram;               // per wide block Y^T Y, tiles above the diagonal
+    uint16_t* panel;                 // the panel of the block being factorised, taken apart
+    float* core;                     // the 128 x 128 triangles of that block
     int n_pad; int64_t ld;
 };
 constexpr int kWideTiles = 16;       // tile columns of a wide block: 256 reflectors
@@ -284,6 +287,11 @@ constexpr int kWideCus = 256;
 bool wide_rows(int n_pad);           // are the reflectors of such a matrix applied 256 at a time while Q is formed?
 int64_t wide_plane_values(int n_pad);        // 16-bit values of Yp and Yr together
 int64_t wide_yr_offset(int n_pad);           // Yr's start behind Yp's
+int64_t block_panel_values(int n_pad);       // 16-bit values of `panel`
+constexpr int kCoreFloats = 3 * 128 * 128;
+// Factorises the columns down to the last 256 rows or a few more, 128 at a time: reflectors, R and its diagonal, T as
+// householder_qr's own panels leave them (but no row-major copies); *panels_done panels of 16
+hipError_t factor_blocks(const FactorWorkspace& ws, int count, int64_t batch_stride, int* panels_done, hipStream_t stream);
 // ws.X <- H_0 H_1 ... ws.X for the panels' reflectors householder_qr has left in ws.M and ws.Tmat
 hipError_t form_product_wide(const FactorWorkspace& ws, int count, int64_t batch_stride, hipStream_t stream);
 size_t factor_workspace_bytes(int n);

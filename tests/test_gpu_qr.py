@@ -56,9 +56,26 @@ def test_panels_from_gram_matrices(ctx, n):
     check_orthogonal(alone.double().cpu().numpy(), n, first + 1)
 
 
+# blocks of 128 columns, from 720 rows of tiles on: the first such size, one and several rows and tiles beyond whole blocks, odd
+# numbers of tile rows, the last size before the blocks.  24 matrices take the kernels for many (those with few rows left still the
+# others), one alone and the pair those for few: the same sums in the same order, so the same bits
+@pytest.mark.parametrize("n", [704, 705, 720, 721, 769, 784, 896, 897, 1025])
+def test_blocks_of_128_columns(ctx, n):
+    first, count = 100 * n, 24
+    many = [g.gelo_mixing_export(ctx, m, n, 0, 64, want_shields=False)[0] for m in g.gelo_sample_mixing_batch(ctx, g.GELO_ORTHOGONAL, n, 0, 64, g.GELO_F32, first, count)]
+    other = g.gelo_create(0, 0xC0FFEE, allow_batch_reuse=False)
+    pair = [g.gelo_mixing_export(other, m, n, 0, 64)[0] for m in g.gelo_sample_mixing_batch(other, g.GELO_ORTHOGONAL, n, 0, 64, g.GELO_F32, first, 2)]
+    m = g.gelo_sample_mixing(other, g.GELO_ORTHOGONAL, n, 0, 64, g.GELO_F32, 1e3, 64, batch_id=first + count - 1)
+    alone = g.gelo_mixing_export(other, m, n, 0, 64)[0]
+    torch.cuda.synchronize()
+    g.gelo_destroy(other)
+    assert torch.equal(many[0], pair[0]) and torch.equal(many[1], pair[1]) and torch.equal(many[-1], alone)
+    check_orthogonal(alone.double().cpu().numpy(), n, first + count - 1)
+
+
 # A^-1 = R^-1 Q^T by blocks of 128: whole and broken blocks and tiles.  kappa(A) is 2 to 4 here; a backward stable inverse
 # leaves A A^-1 = I to kappa c sqrt(n) roundings (rows scaled to 1)
-@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 64, 65, 127, 128, 129, 144, 255, 256, 257, 400, 641, 1301])
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 64, 65, 127, 128, 129, 144, 255, 256, 257, 400, 641, 721, 1301])
 def test_inverse_of_a_conditioned_matrix(ctx, n):
     m = g.gelo_sample_mixing(ctx, g.GELO_CONDITIONED, n, 0, 64, g.GELO_F32, 1e3, 64, batch_id=n)
     A, A_inv, _, _, kappa = g.gelo_mixing_export(ctx, m, n, 0, 64)
