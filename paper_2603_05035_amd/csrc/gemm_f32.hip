@@ -1,27 +1,28 @@
-// float GEMM on the gfx950 matrix cores (v_mfma_f32_32x32x2_f32), used by the
-// single-precision GELO chain (Section 3.2, eqs. 1-3): C[M x N] = A[M x K] * B[K x N],
-// all row-major, B optionally split into two row segments ([H ; S]); optionally C <- C - A * B.
-// A tile reads all of its operands before it stores, so the product may overwrite B in place with M <= 128 (C == B0, K0 == K:
-// the back substitution's multiplications by a diagonal-block inverse, a caller's un-mix into its Y) and A where one tile
-// spans N.  The 64 x 64 tiles would read what their neighbours have stored: they are not taken where C meets an operand.
+// float GEMM on the gfx950 matrix cores, used by the single-precision GELO chain (Section 3.2, eqs. 1-3) and the inverse:
+// C[M x N] = A[M x K] * B[K x N], all row-major, B optionally split into two row segments ([H ; S]); optionally C <- C - A * B.
+// Products of at least one 128 x 128 tile per CU go through the bf16 instructions (gemm_f32_split_kernel), smaller ones
+// through v_mfma_f32_32x32x2_f32 in 64 x 64 tiles.
+// A 128 x 128 tile of gemm_f32_kernel reads all of its operands before it stores, so the product may overwrite B in place with M <= 128
+// (C == B0, K0 == K: the back substitution's multiplications by a diagonal-block inverse, a caller's un-mix into its Y) and A where
+// one tile spans N.  Smaller tiles would read what their neighbours have stored, and the tiles taken apart read their
+// operands twice if need be: neither is taken where C meets an operand.
 //
-// A workgroup of 4 waves owns a 64 x 64 tile (products of at most one round of large ones), else a 128 x 96, 128 x 128 or 128 x 192
-// tile (whichever fills whole rounds of the chip's CUs best) and walks K in steps of 32 through double-buffered LDS.  A lane
-// reads four consecutive k of its A row with one 16-byte LDS read and spends them on four
-// successive MFMAs; the matching B values are single dwords, contiguous across lanes; the
-// fragments of the next 8 k are read while the MFMAs of the current 8 run.
+// gemm_f32_kernel: a workgroup of 4 waves walks K in steps of 32 through double-buffered LDS.  A lane reads four consecutive k of its A
+// row with one 16-byte LDS read and spends them on four successive MFMAs; the matching B values are single dwords,
+// contiguous across lanes; the fragments of the next 8 k are read while the MFMAs of the current 8 run.
 #include <algorithm>
 
 #include "gelo_internal.h"
+#include "split_float.h"
 
 namespace gelo {
 namespace {
 
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kTileM = 128, BK = 32;   // rows of a tile (64 where the tile is 64 x 64); K step
 constexpr int NT = 256;
+constexpr int kCus = 256;
 constexpr int A_PITCH = BK + 4;    // floats: 144-byte rows, conflict-free 16-byte reads down a column of rows
 
 struct F32Args {
@@ -34,13 +35,11 @@ struct F32Args {
     int subtract;              // C <- C - A B (the back substitution's updates)
 };
 
-// BN = 96, 128 or 192: the tile width is picked per shape so that the tile count fills whole rounds of the chip's CUs.
-// WAVES_M x (4 / WAVES_M) waves: 2 x 2 for the wide tiles, 4 x 1 (a wave owns 32 rows x 96 columns) for the narrow one,
-// whose LDS footprint lets two workgroups share a CU and cover each other's barrier and LDS-store phases.
-// 64 x 64 tiles (2 x 2 waves of 32 x 32) for products of at most one round of large tiles.
-template <int BM, int BN, int WAVES_M>
+// On the float instructions: 2 x 2 waves, 64 x 64 tiles where there are too few large ones, 128 x 128 where C meets an operand.
+template <int TILE>
 __global__ __launch_bounds__(NT)
 void gemm_f32_kernel(F32Args g) {
+    constexpr int BM = TILE, BN = TILE, WAVES_M = 2;
     constexpr int ALD = BM * (BK / 4) / NT;      // A chunks per thread and K step
     constexpr int B_PITCH = BN + 4;
     constexpr int WAVES_N = 4 / WAVES_M;
@@ -278,6 +277,143 @@ void gemm_f32_short_kernel(F32Args g) {
     }
 }
 
+// The same product on the bf16 matrix instructions, every float taken apart into three bf16 values (split_float.h).  A workgroup of four
+// waves has a 128 x 128 tile of C (a wave 64 x 64 of it) and walks K in steps of 32.  A thread takes apart eight
+// consecutive k of a row of A or a column of B at a time and leaves the three planes in LDS as the instructions take them
+// (fragments of 16 rows or columns x 32 k, lane (g, c): row c, k 8 g ..): one 16-byte write and one 16-byte read per plane, no
+// conflicts but of the writes for B, which go by column pairs.  One stage in LDS, the next step's floats on their way to
+// registers: two workgroups share a CU, one parks while the other multiplies.  The operands are swapped, so that a lane ends
+// up with four consecutive columns of a row of C.
+// Bound by what stands beside the matrix instructions, which take 45% of a step (1.66 us with a neighbour on the CU): the floats are
+// taken apart anew in every tile, and two barriers stand in a step.  Error against 64 bits 0.77 to 0.9 of the float instructions'
+// (K = 128 to 11008).
+// A product with an infinity in it comes out as NaN here (inf - inf when it is taken apart), as do sums past the largest float: a
+// tile that holds anything not finite is computed again with float multiply-adds, k by k.
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void gemm_f32_split_kernel(F32Args g) {
+    constexpr int TILE = kTileM, F = TILE / 16;           // fragments across the tile
+    constexpr int FW = F / 2;                             // across a wave's quarter
+    constexpr int ITEMS = TILE * 4 / NT;                  // rows of A (columns of B) x eight k per thread and step
+    __shared__ __attribute__((aligned(1024))) uint16_t stage[2][3 * F * kFrag];      // A, B: [fragment][plane]
+    const int total = g.tiles_m * g.tiles_n, bid = blockIdx.x;
+    const int xcd = bid & 7, slot = bid >> 3, share = total >> 3, rem = total & 7;
+    const int lid = xcd * share + (xcd < rem ? xcd : rem) + slot;
+    const int m0 = lid / g.tiles_n * TILE, n0 = lid % g.tiles_n * TILE;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, q = lane >> 4, wm = wave & 1, wn = wave >> 1;
+    const int steps = (g.K + BK - 1) / BK;
+    // A: item i of this thread is row 16 (wave + 4 i) + c, k 8 q ..; B: wave w has k 8 w .., lane l the columns ITEMS l ..
+    const float* arow[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const int row = m0 + 16 * (wave + 4 * i) + c;
+        arow[i] = g.A + (int64_t)(row < g.M ? row : g.M - 1) * g.lda;
+    }
+    const int col0 = n0 + ITEMS * lane < g.N ? n0 + ITEMS * lane : g.N - ITEMS;      // (N is a multiple of 8)
+    const float* B0 = g.B0;
+    const float* B1 = g.B1;
+    const int64_t ldb0 = g.ldb0, ldb1 = g.ldb1;
+    const int K0 = g.K0, Kd = g.K;
+    f32x4_t ra[ITEMS][2];
+    float rb[8][ITEMS];
+    auto fetch = [&](int t) {
+        const int k0 = t * BK, ka = k0 + 8 * q, kb = k0 + 8 * wave;
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const float* p = arow[i] + (ka < Kd ? ka : 0);
+            ra[i][0] = *reinterpret_cast<const f32x4_t*>(p);
+            ra[i][1] = *reinterpret_cast<const f32x4_t*>(p + 4);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {                     // (the row, and so which segment it lies in, is the same for the whole wave)
+            const int k = kb + e < Kd ? kb + e : Kd - 1;
+            const float* p = (k < K0 ? B0 + (int64_t)k * ldb0 : B1 + (int64_t)(k - K0) * ldb1) + col0;
+            static_assert(ITEMS == 2, "a lane's columns are read at once");
+            const float2 v = *reinterpret_cast<const float2*>(p);
+            rb[e][0] = v.x; rb[e][1] = v.y;
+        }
+    };
+    auto park = [&](int t) {
+        const int k0 = t * BK;
+        const bool a_in = k0 + 8 * q < Kd;                // (A is zero up to the next multiple of 8)
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            f32x4_t x = ra[i][0], y = ra[i][1];
+            if (k0 + BK > Kd) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { x[e] = a_in ? x[e] : 0.f; y[e] = a_in ? y[e] : 0.f; }
+            }
+            put_split(&stage[0][(wave + 4 * i) * 3 * kFrag + lane * 8], kFrag, split3(x, y));
+        }
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            f32x4_t x, y;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { x[e] = rb[e][i]; y[e] = rb[4 + e][i]; }
+            if (k0 + BK > Kd) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    x[e] = k0 + 8 * wave + e < Kd ? x[e] : 0.f;
+                    y[e] = k0 + 8 * wave + 4 + e < Kd ? y[e] : 0.f;
+                }
+            }
+            const int col = ITEMS * lane + i;
+            put_split(&stage[1][(col >> 4) * 3 * kFrag + (wave * 16 + (col & 15)) * 8], kFrag, split3(x, y));
+        }
+    };
+    f32x4_t acc[FW][FW];                                  // [columns][rows]
+#pragma unroll
+    for (int f = 0; f < FW; ++f)
+#pragma unroll
+        for (int n = 0; n < FW; ++n) acc[f][n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    fetch(0);
+    for (int t = 0; t < steps; ++t) {
+        if (t > 0) __syncthreads();                       // nobody reads the last stage any more
+        park(t);
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(t + 1 < steps ? t + 1 : t);                 // unconditional: a wait then counts what was issued behind what it waits for
+        __builtin_amdgcn_sched_barrier(0);
+        const uint16_t* fa = &stage[0][wm * FW * 3 * kFrag + lane * 8];
+        const uint16_t* fb = &stage[1][wn * FW * 3 * kFrag + lane * 8];
+        Split rows[FW];
+#pragma unroll
+        for (int n = 0; n < FW; ++n) { rows[n].h = frag_of(fa + n * 3 * kFrag); rows[n].m = frag_of(fa + (n * 3 + 1) * kFrag); rows[n].l = frag_of(fa + (n * 3 + 2) * kFrag); }
+        products([&](int plane, int f) { return frag_of(fb + (f * 3 + plane) * kFrag); }, rows, acc);
+    }
+    bool bad = false;
+#pragma unroll
+    for (int f = 0; f < FW; ++f)
+#pragma unroll
+        for (int n = 0; n < FW; ++n)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) bad = bad | !(fabsf(acc[f][n][v]) <= 3.402823466e38f);
+    if (__syncthreads_or(bad)) {
+        for (int i = tid; i < TILE * TILE; i += NT) {
+            const int row = m0 + i / TILE, col = n0 + i % TILE;
+            if (row >= g.M || col >= g.N) continue;
+            float sum = 0.f;
+            for (int k = 0; k < Kd; ++k)
+                sum = fmaf(g.A[(int64_t)row * g.lda + k], k < K0 ? B0[(int64_t)k * ldb0 + col] : B1[(int64_t)(k - K0) * ldb1 + col], sum);
+            float* cp = g.C + (int64_t)row * g.ldc + col;
+            *cp = g.subtract ? *cp - sum : sum;
+        }
+        return;
+    }
+#pragma unroll
+    for (int f = 0; f < FW; ++f) {
+        const int col = n0 + (wn * FW + f) * 16 + 4 * q;
+        if (col >= g.N) continue;
+#pragma unroll
+        for (int n = 0; n < FW; ++n) {
+            const int row = m0 + (wm * FW + n) * 16 + c;
+            if (row >= g.M) continue;
+            f32x4_t* cp = reinterpret_cast<f32x4_t*>(g.C + (int64_t)row * g.ldc + col);
+            *cp = g.subtract ? *cp - acc[f][n] : acc[f][n];
+        }
+    }
+}
+
 }  // namespace
 
 hipError_t gemm_f32_init() {
@@ -307,30 +443,22 @@ hipError_t gemm_f32(const GemmOperands& o, hipStream_t stream) {
         return rows > 0 && lo < c_hi && c_lo < hi;
     };
     const bool in_place = meets_c(o.A, o.lda, o.M, o.K) || meets_c(o.B0, o.ldb0, std::min(o.K0, o.K), o.N) || meets_c(o.B1, o.ldb1, o.K - o.K0, o.N);
-    // Tile width beyond one round of 128 x 128 tiles.  K of 512 and more: 128 x 96 tiles, two workgroups per CU (cost: rounds of
-    // 512 tiles), unless a wider tile wastes less of its last round over the 256 CUs; below (the back substitution's updates,
-    // K = 128, bound by the read-modify-write of C): the wide tiles only.
-    constexpr int kCus = 256;
-    auto tiles = [&](int bn) { return a.tiles_m * ((o.N + bn - 1) / bn); };
-    const int64_t cost96 = (int64_t)((tiles(96) + 2 * kCus - 1) / (2 * kCus)) * 2 * 96 * 85 / 100;      // measured: 15% faster per flop
-    const int64_t cost128 = (int64_t)((tiles(128) + kCus - 1) / kCus) * 128, cost192 = (int64_t)((tiles(192) + kCus - 1) / kCus) * 192;
-    if (tiles(128) <= kCus && !in_place) {
-        // At most one round of large tiles: each keeps its one CU's matrix cores busy for 1.3 us per K step however many CUs are
-        // idle, and nothing runs beside its barriers.  Tiles of a quarter of the work (543 x 1544 x 776: 33 us against 74,
-        // 1024 x 2048 x 2048: 107 against 183, a full round, 2048 x 2048 x 1000: 86 against 98; beyond one round the large
-        // tiles win, 512 x 12288 x 4096: 485 against 536; with K = 128, 512 x 512: 10.7 against 16.3, 1536 x 2048: 13.0 against 17.9).
-        // The sums run in the same order.
+    const int tiles = a.tiles_m * ((o.N + kTileM - 1) / kTileM);
+    if (in_place) {
+        a.tiles_n = (o.N + kTileM - 1) / kTileM;
+        hipLaunchKernelGGL((gemm_f32_kernel<kTileM>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
+    } else if (tiles < kCus) {
+        // Too few large tiles to give every CU one: 64 x 64 on the float instructions.  This / 128 x 128 taken apart: 543 x 1544 x 776
+        // (65 large tiles) 32 / 59 us, 1024 x 2048 x 2048 (128) 110 / 149, 700 x 4096 x 11008 (192) 697 / 764, 1900 x 2048 x 128 (240)
+        // 15.9 / 15.5.  (Taken apart in 64 x 64 tiles, where the taking apart weighs twice as much: 33, 111, 849.)
         a.tiles_m = (o.M + 63) / 64; a.tiles_n = (o.N + 63) / 64;
-        hipLaunchKernelGGL((gemm_f32_kernel<64, 64, 2>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
-    } else if (o.K >= 512 && cost96 <= cost128 && cost96 <= cost192) {
-        a.tiles_n = (o.N + 95) / 96;
-        hipLaunchKernelGGL((gemm_f32_kernel<kTileM, 96, 4>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
-    } else if (cost192 < cost128) {
-        a.tiles_n = (o.N + 191) / 192;
-        hipLaunchKernelGGL((gemm_f32_kernel<kTileM, 192, 2>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
+        hipLaunchKernelGGL((gemm_f32_kernel<64>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
     } else {
-        a.tiles_n = (o.N + 127) / 128;
-        hipLaunchKernelGGL((gemm_f32_kernel<kTileM, 128, 2>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
+        // Against 128 x 96, 128 x 128 or 128 x 192 tiles on the float instructions, us: 2048 x 2048 x 1000 (256 tiles) 93 / 82, 512 x 12288 x 4096
+        // (384) 520 / 410 (126 TFLOP/s), 300 x 11008 x 4096 (258) 440 / 315, 2150 x 12288 x 4096 2100 / 1510 (143), 4096 x 4096 x 4096 1330 /
+        // 792 (173), 640 x 8192 x 128 25 / 21.
+        a.tiles_n = (o.N + kTileM - 1) / kTileM;
+        hipLaunchKernelGGL(gemm_f32_split_kernel, dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
     }
     return hipGetLastError();
 }

@@ -99,3 +99,54 @@ def test_float_results_in_place_of_their_operands(n_data, k, p):
         torch.cuda.synchronize()
         assert torch.equal(X, Y)
     g.gelo_destroy(ctx)
+
+
+# float products taken apart into bf16 values (256 tiles of 128 x 128 and more; one tile less beside them): rows, columns and K that
+# fill no tile, fragment or step, the fewest k
+@pytest.mark.parametrize("m,k,n", [(2048, 32, 2048), (2047, 40, 2040), (2033, 8, 2048), (1921, 104, 2056), (513, 264, 8200), (130, 1000, 16392), (2048, 64, 1920)])
+def test_float_tiles_taken_apart(m, k, n):
+    check(m, k, n, torch.float32)
+
+
+# the same in mix and un-mix: segments of B that meet inside a K step and inside a thread's eight rows (1021 + 51 rows), K = 1072
+def test_float_tiles_taken_apart_in_a_mix():
+    n_data, k, width = 1021, 51, 4104
+    n = n_data + k
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    H = torch.randn((n_data, width), generator=gen, device="cuda")
+    Y = torch.randn((n, width), generator=gen, device="cuda")
+    U, Z = torch.empty((n, width), device="cuda"), torch.empty((n_data, width), device="cuda")
+    ctx = g.gelo_create(0, 1)
+    m = g.gelo_sample_mixing(ctx, g.GELO_REFLECTOR_PRODUCT, n_data, k, width, g.GELO_F32, batch_id=1)
+    g.gelo_mix(ctx, m, H, U)
+    g.gelo_unmix(ctx, m, Y, Z)
+    A, A_inv, S, _, _ = g.gelo_mixing_export(ctx, m, n, k, width)
+    torch.cuda.synchronize()
+    g.gelo_mixing_free(ctx, m)
+    g.gelo_destroy(ctx)
+    for out, left, right in ((U, A.double(), torch.cat([H.double(), S.double()])), (Z, A_inv[:n_data].double(), Y.double())):
+        bound = (n + 1) * 2.0 ** -24 * (left.abs() @ right.abs()) * 1.01
+        assert bool(((out.double() - left @ right).abs() <= bound).all())
+
+
+# infinities, NaN and sums past the largest float come out as float products give them: an infinity times a finite number is an
+# infinity, and the rest of the result is what it is without them
+def test_float_tiles_taken_apart_with_infinities():
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    U = torch.randn((2048, 64), generator=gen, device="cuda")
+    W = torch.randn((64, 2048), generator=gen, device="cuda")
+    U[3, 5], U[700, 1], U[1500, 60], W[10, 1999] = float("inf"), float("nan"), 3.3e38, -float("inf")
+    Y = torch.empty((2048, 2048), device="cuda")
+    ctx = g.gelo_create(0, 1)
+    g.gelo_project(ctx, U, W, Y)
+    torch.cuda.synchronize()
+    g.gelo_destroy(ctx)
+    ref = U.double() @ W.double()
+    size = U.double().abs() @ W.double().abs()
+    past = ref.abs() > 3.402823466e38
+    want = torch.where(past, ref.sign() * float("inf"), ref)
+    assert torch.equal(torch.isnan(Y), torch.isnan(ref))
+    sure = ~torch.isnan(ref) & ((ref.abs() > 3.5e38) | (size < 3.3e38))      # (in between a partial sum may or may not pass it)
+    assert torch.equal(torch.isinf(Y) & sure, torch.isinf(want) & sure)
+    fine = sure & torch.isfinite(want)
+    assert bool(((Y.double() - ref).abs()[fine] <= (65 * 2.0 ** -24 * size)[fine] * 1.01).all())
