@@ -72,8 +72,10 @@ struct CoreShared {
 // 16 columns of both eliminations; a, s: the diagonal tiles in accumulator layout.  One wave, lane (g, c) column c of matrix g, each
 // in place: S_ii, above whose diagonal the column operations grow that make R_ii^-1 of the identity; A_ii with those that make
 // U_ii^-1; A_ii again, below whose diagonal the row operations grow that make L_ii^-1.  A step adds multiples of column j to other
-// columns, all matrices in the same 15 instructions.
-__device__ __forceinline__ void core_diagonal(CoreShared& sh, int q, int i, f32x4_t a, f32x4_t s, float* Vtile, float* Rd, float* rdiag, int lane) {
+// columns, all matrices in the same 15 instructions.  `published` (the barrier) comes between what the other waves wait for and the
+// stores to memory.
+template <class Published>
+__device__ __forceinline__ void core_diagonal(CoreShared& sh, int q, int i, f32x4_t a, f32x4_t s, float* Vtile, float* Rd, float* rdiag, int lane, Published&& published) {
     const int c = lane & 15, g = lane >> 4;
     const int place = g * kCoreRow + c * 4;
     *reinterpret_cast<f32x4_t*>(sh.turn[0] + place) = s;
@@ -144,6 +146,7 @@ __device__ __forceinline__ void core_diagonal(CoreShared& sh, int q, int i, f32x
 #pragma unroll
         for (int k = 0; k < NB; ++k) base[turned + k * 4] = out[k];
     }
+    published();
     if (g == 1) {
 #pragma unroll
         for (int k = 0; k < NB; ++k) { const float one = k == c ? 1.f : 0.f; col[k] = k > c ? col[k] : one; }
@@ -195,8 +198,7 @@ void block_core_kernel(BlockArgs a) {
             }
             int here = lane;
             asm volatile("" : "+v"(here));                // (its comparisons with the column would all be kept across the loop)
-            core_diagonal(sh, q, i, da, ds, tile(i, i), a.Rd + off, a.rdiag + off, here);
-            __syncthreads();
+            core_diagonal(sh, q, i, da, ds, tile(i, i), a.Rd + off, a.rdiag + off, here, [&] { __syncthreads(); });
             __syncthreads();
         }
         return;
