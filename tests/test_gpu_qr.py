@@ -89,6 +89,18 @@ def test_inverse_of_a_conditioned_matrix(ctx, n):
         assert abs(kappa - exact) < 0.02 * exact
 
 
+# the condition estimate where its rows' registers change: one to twenty blocks of 256 columns, whole and broken
+@pytest.mark.parametrize("n", [129, 256, 257, 512, 513, 1025, 2049, 3073, 4097])
+def test_condition_estimate(ctx, n):
+    m = g.gelo_sample_mixing(ctx, g.GELO_CONDITIONED, n, 0, 64, g.GELO_F32, 1e3, 64, batch_id=n)
+    A, _, _, _, kappa = g.gelo_mixing_export(ctx, m, n, 0, 64)
+    torch.cuda.synchronize()
+    g.gelo_mixing_free(ctx, m)
+    top = torch.linalg.eigvalsh(A.double().t().contiguous() @ A.double()).cpu()
+    exact = math.sqrt(float(top[-1] / top[0]))
+    assert -0.01 * exact < kappa - exact < 1e-4 * exact       # a largest Ritz value comes from below: measured within 0.5 %
+
+
 def loss_of_orthogonality(ctx, n, first, count):
     """root mean square over `count` draws of |A^T A - I| / sqrt(n)"""
     total = 0.0
