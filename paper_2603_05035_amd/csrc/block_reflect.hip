@@ -25,58 +25,45 @@ namespace {
 constexpr int WT = kWideTiles;                            // tile columns of a wide block
 
 // ------------------------------------------------------------ Y^T Y and the triangles --
-// Tile (i, j), i < j, of every wide block's Y^T Y, in double: a workgroup has two by two of them, its eight waves share the
-// tile rows.  gram: [block][i][j][256], row-major tiles.
-constexpr int kGramPairs = (WT / 2) * (WT / 2 + 1) / 2;   // pairs of tile-column pairs a <= b
+// Tile (i, j), i < j, of every wide block's Y^T Y, in double: a workgroup has two of a column of them, its eight waves share the
+// tile rows.  gram: [block][i][j][256], row-major tiles.  (Two by two tiles per workgroup read a third less, but their longest
+// workgroup took 26 us at 2150 rows, and the taking apart 8 in a launch of its own: 22 together now, a draw of 2150 rows alone 1438 ->
+// 1422 us, 32 of them 10 900 -> 10 720.)
+constexpr int kGramPairs = WT * (WT + 2) / 4;             // pairs of tile columns a, tile columns b behind them: b / 2 + 1 for each b
 
-__global__ __launch_bounds__(512)
-void wide_gram_kernel(const float* M, double* gram, int nbr, int64_t batch_stride) {
-    __shared__ double part[8][4][256];
+__device__ __forceinline__ void wide_gram(const float* M, double* gram, int nbr, int item) {
+    __shared__ double part[8][2][256];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g = lane >> 4;
-    M += (int64_t)blockIdx.y * batch_stride;
-    gram += (int64_t)blockIdx.y * (batch_stride / 2);
-    const int q = blockIdx.x / kGramPairs;
-    int b = 0, a = blockIdx.x % kGramPairs;
-    while (a > b) { a -= b + 1; ++b; }                    // pair number -> (a, b), a <= b
+    const int q = item / kGramPairs;
+    int j = 0, a = item % kGramPairs;
+    while (a > j / 2) { a -= j / 2 + 1; ++j; }
     const int t0 = q * WT, mt = nbr - t0;                 // tile rows from the block's first one on
-    if (2 * b >= mt) return;
-    f64x4_t acc[2][2];
+    if (j >= mt) return;
+    f64x4_t acc[2];
+    acc[0] = acc[1] = f64x4_t{0., 0., 0., 0.};
+    for (int r = j + wave; r < mt; r += 8) {              // (column j starts in its tile row j, those before it higher up)
+        f32x4_t v[3];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f64x4_t{0., 0., 0., 0.};
-    for (int r = 2 * b + wave; r < mt; r += 8) {
-        f32x4_t v[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int f = k < 2 ? 2 * a + k : 2 * b + k - 2;      // the block's column f starts in its tile row f
-            v[k] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            if (f < mt && r >= f) v[k] = *reinterpret_cast<const f32x4_t*>(M + ((int64_t)(t0 + f) * nbr + t0 + r) * 256 + c * 16 + 4 * g);
+        for (int k = 0; k < 3; ++k) {
+            const int f = k < 2 ? (2 * a + k < j ? 2 * a + k : j) : j;
+            v[k] = *reinterpret_cast<const f32x4_t*>(M + ((int64_t)(t0 + f) * nbr + t0 + r) * 256 + c * 16 + 4 * g);
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)v[i][e], (double)v[2 + j][e], acc[i][j], 0, 0, 0);
+            for (int i = 0; i < 2; ++i) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)v[i][e], (double)v[2][e], acc[i], 0, 0, 0);
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) part[wave][i * 2 + j][(4 * v + g) * 16 + c] = acc[i][j][v];      // element v: row 4 v + g
+        for (int v = 0; v < 4; ++v) part[wave][i][(4 * v + g) * 16 + c] = acc[i][v];      // element v: row 4 v + g
     __syncthreads();
+    const int i = 2 * a + (tid >> 8), at = tid & 255;
+    double s = part[0][tid >> 8][at];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int id = tid + 512 * k, ij = id >> 8, at = id & 255;
-        const int i = 2 * a + (ij >> 1), j = 2 * b + (ij & 1);
-        double s = part[0][ij][at];
-#pragma unroll
-        for (int w = 1; w < 8; ++w) s += part[w][ij][at];
-        if (i < j && j < mt) gram[((int64_t)q * WT * WT + i * WT + j) * 256 + at] = s;
-    }
+    for (int w = 1; w < 8; ++w) s += part[w][tid >> 8][at];
+    if (i < j) gram[((int64_t)q * WT * WT + i * WT + j) * 256 + at] = s;
 }
 
 // T of a wide block, row of tiles by row of tiles, a wave each: T[i][j] = -(sum over i <= k < j of T[i][k] G[k][j]) T[j][j].
@@ -144,16 +131,14 @@ void wide_triangle_kernel(const double* gram, const float* Tmat, float* Tbig, in
 
 // ------------------------------------------------------------ Y taken apart --
 // one workgroup per pair of tile rows of a wide block
-__global__ __launch_bounds__(512)
-void wide_planes_kernel(const float* M, uint16_t* Yp, uint16_t* Yr, int nbr, int64_t batch_stride) {
+__device__ __forceinline__ void wide_planes(const float* M, uint16_t* Yp, uint16_t* Yr, int nbr, int item) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g = lane >> 4;
-    M += (int64_t)blockIdx.y * batch_stride;
     int q = 0;
-    while ((q + 1) * WT < nbr && pairs_before(nbr, q + 1) <= (int64_t)blockIdx.x) ++q;
-    const int pair = blockIdx.x - (int)pairs_before(nbr, q), t0 = q * WT, mt = nbr - t0;
-    Yp += 2 * (int64_t)blockIdx.y * batch_stride + (pairs_before(nbr, q) + pair) * kUnitYp + lane * 8;
-    Yr += 2 * (int64_t)blockIdx.y * batch_stride + (rows_before(nbr, q) + 2 * pair) * kUnitYr + lane * 8;
+    while ((q + 1) * WT < nbr && pairs_before(nbr, q + 1) <= (int64_t)item) ++q;
+    const int pair = item - (int)pairs_before(nbr, q), t0 = q * WT, mt = nbr - t0;
+    Yp += (pairs_before(nbr, q) + pair) * kUnitYp + lane * 8;
+    Yr += (rows_before(nbr, q) + 2 * pair) * kUnitYr + lane * 8;
     auto tile_of = [&](int r, int f) { return M + ((int64_t)(t0 + f) * nbr + t0 + r) * 256; };
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
@@ -183,6 +168,15 @@ void wide_planes_kernel(const float* M, uint16_t* Yp, uint16_t* Yr, int nbr, int
         }
         put_split(Yr + (int64_t)k * kUnitYr + u * 3 * kFrag, kFrag, split3(v[0], v[1]));
     }
+}
+
+// both, in one launch: neither needs the other
+__global__ __launch_bounds__(512)
+void wide_prepare_kernel(const float* M, double* gram, uint16_t* Yp, uint16_t* Yr, int nbr, int64_t batch_stride) {
+    const int blocks = (nbr + WT - 1) / WT, item = blockIdx.x;
+    const int64_t off = (int64_t)blockIdx.y * batch_stride;
+    if (item < blocks * kGramPairs) wide_gram(M + off, gram + off / 2, nbr, item);
+    else wide_planes(M + off, Yp + 2 * off, Yr + 2 * off, nbr, item - blocks * kGramPairs);
 }
 
 // ------------------------------------------------------------ the three products --
@@ -566,9 +560,8 @@ hipError_t launch_block_update(WideArgs a, hipStream_t s) {
 
 hipError_t form_product_wide(const FactorWorkspace& ws, int count, int64_t batch_stride, hipStream_t s) {
     const int nbr = ws.n_pad / kPanel, blocks = (nbr + WT - 1) / WT;
-    hipLaunchKernelGGL(wide_gram_kernel, dim3(blocks * kGramPairs, count), dim3(512), 0, s, ws.M, ws.wide_gram, nbr, batch_stride);
-    GELO_TRY(hipGetLastError());
-    hipLaunchKernelGGL(wide_planes_kernel, dim3((unsigned)pairs_before(nbr, blocks), count), dim3(512), 0, s, ws.M, ws.Yp, ws.Yr, nbr, batch_stride);
+    hipLaunchKernelGGL(wide_prepare_kernel, dim3((unsigned)(blocks * kGramPairs + pairs_before(nbr, blocks)), count), dim3(512), 0, s,
+                       ws.M, ws.wide_gram, ws.Yp, ws.Yr, nbr, batch_stride);
     GELO_TRY(hipGetLastError());
     hipLaunchKernelGGL(wide_triangle_kernel, dim3(blocks * WT, count), dim3(64), 0, s, ws.wide_gram, ws.Tmat, ws.Tbig, nbr, batch_stride);
     GELO_TRY(hipGetLastError());
