@@ -306,12 +306,12 @@ void normal_product_kernel(const float* Ma, const float* va, float* pa, const fl
 #pragma unroll
     for (int j = 0; j < CH; ++j) sum[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     for (int r = blockIdx.x * 4 + wave; r < n; r += gridDim.x * 4) {
-        const float* row = M + (int64_t)r * lda + lane * 4;
+        const float* row = M + (int64_t)r * lda;
         f32x4_t x[CH];
 #pragma unroll
         for (int j = 0; j < CH; ++j) {
-            const bool in = j * 256 + lane * 4 < lda;  // (beyond its end the row's start again: v is zero there and nobody reads the sums)
-            x[j] = *reinterpret_cast<const f32x4_t*>(row + (in ? j * 256 : 0));
+            const int c = j * 256 + lane * 4;          // (beyond its end the row's start again: v is zero there and nobody reads the sums)
+            x[j] = *reinterpret_cast<const f32x4_t*>(row + (c < lda ? c : 0));
         }
         float dot = 0.f;
 #pragma unroll

@@ -89,8 +89,8 @@ def test_inverse_of_a_conditioned_matrix(ctx, n):
         assert abs(kappa - exact) < 0.02 * exact
 
 
-# the condition estimate where its rows' registers change: one to twenty blocks of 256 columns, whole and broken
-@pytest.mark.parametrize("n", [129, 256, 257, 512, 513, 1025, 2049, 3073, 4097])
+# the condition estimate where its rows' registers change: rows of less than 256 columns, one to twenty blocks of them, whole and broken
+@pytest.mark.parametrize("n", [8, 64, 65, 129, 192, 193, 256, 257, 512, 513, 1025, 2049, 3073, 4097])
 def test_condition_estimate(ctx, n):
     m = g.gelo_sample_mixing(ctx, g.GELO_CONDITIONED, n, 0, 64, g.GELO_F32, 1e3, 64, batch_id=n)
     A, _, _, _, kappa = g.gelo_mixing_export(ctx, m, n, 0, 64)
