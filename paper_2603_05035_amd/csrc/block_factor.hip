@@ -15,10 +15,10 @@
 // (sqrt(m) + 11.3) / (sqrt(m) - 11.3): 1.6 at 2150 rows, 5.8 at 256, where the blocks end.  CONDITIONED matrices' panels are
 // no worse than A (2 to 4).
 //
-// A draw alone is bound by the chain of these four launches, 8 to 15 + 33 + 7 + 5 to 25 us per 128 columns at 2150 rows; panel by
+// A draw alone is bound by the chain of these four launches, 8 to 15 + 31.5 + 7 + 5 to 25 us per 128 columns at 2150 rows; panel by
 // panel it was eight launches of 9 to 28.  A whole draw, panels / blocks: 720 rows 582 / 495 us, 1024 rows 892 / 661, 2150 rows
-// 2673 / 1460, 4301 rows 9540 / 4050 (with Q formed as before: 8310 panel by panel); 32 side by side 720 rows 1507 / 1533, 1024 rows
-// 2662 / 2519, 2150 rows 14740 / 10740.  Against 64 bits, panels / blocks, 2150 rows: |A^T A - I| / sqrt(n) 1.24e-6 / 1.12e-6, part
+// 2673 / 1422, 4301 rows 9540 / 4000 (with Q formed as before: 8310 panel by panel); 32 side by side 720 rows 1507 / 1533, 1024 rows
+// 2662 / 2519, 2150 rows 14740 / 10720.  Against 64 bits, panels / blocks, 2150 rows: |A^T A - I| / sqrt(n) 1.24e-6 / 1.12e-6, part
 // of A^T G below the diagonal 7.2e-7 / 6.9e-7 of |G|, distance of A from the exact factor 3.1e-6 / 2.9e-6; 1300 rows 9.8e-7 / 9.2e-7,
 // 5.7e-7 / 5.8e-7, 2.5e-6 / 2.4e-6.
 #include "block_reflect.h"
@@ -50,7 +50,7 @@ struct BlockArgs {
 // transposed: then every operand is one 16-byte read.  The ninth wave eliminates the diagonal tiles: 16 columns each, column
 // operations on registers (as gram_panel_body's).  It is the critical path; the others update beside it.
 // Bound by that chain's latency: 8 x 16 dependent columns of about 290 cycles, and by 2000 cycles per tile for the two barriers,
-// what is done between them and the tile's way through LDS.  33 us; 50 with the four matrices of a diagonal tile in every lane's
+// what is done between them and the tile's way through LDS.  31.5 us; 50 with the four matrices of a diagonal tile in every lane's
 // registers one after the other, 45 with a matrix per row of lanes, 40 with a wave to itself and its code in a loop.
 __device__ __forceinline__ f32x4_t tile_product(f32x4_t x, f32x4_t y, f32x4_t acc) {
 #pragma unroll

@@ -902,8 +902,8 @@ hipError_t launch_direct_panels(int rows_per_thread, const FactorWorkspace& ws, 
 // below, and for the last 256 columns, panel by panel and by strips.
 bool wide_rows(int n_pad) { return n_pad >= 720; }
 // the product of directly drawn reflectors, which has no chain of panels to lose: 256 at a time from here on.  One alone, strips / blocks:
-// 640 rows 145 / 157 us, 1024 rows 240 / 199, 2150 rows 725 / 450, 4301 rows 2840 / 1440; 8 side by side 1024 rows 431 / 473,
-// 1300 rows 747 / 741, 32 of 2150 rows 6916 / 6160.
+// 640 rows 145 / 157 us, 1024 rows 240 / 199, 2150 rows 725 / 438, 4301 rows 2840 / 1440; 8 side by side 1024 rows 431 / 473,
+// 1300 rows 747 / 741, 32 of 2150 rows 6916 / 5860.
 constexpr int kWideProduct = 1280;
 
 size_t factor_workspace_bytes(int n) {
