@@ -319,7 +319,7 @@ __device__ __forceinline__ void reflect_strip_body(StripShared& sh, const Reflec
     // soon as a group has been consumed the group two places further on is requested into the same registers.  Two
     // groups are always on their way, across the barrier too: a load consumed right behind its issue would expose
     // one memory latency per group.
-    constexpr int GRP = NBLK == 20 ? 10 : 5, NG = NBLK / GRP;
+    constexpr int GRP = 5, NG = NBLK / GRP;
     static_assert(NBLK % GRP == 0, "blocks per wave must be a multiple of the load group");
     f32x4_t va[2][GRP];
     const float* zero_l = g_zero_tile + c * 16 + 4 * g;
@@ -557,10 +557,9 @@ struct QrBulkArgs {
     float* Cout; float* X; int outer, acc;
     int64_t strip_stride; int nb_block; int64_t batch_stride; int count;
 };
-// Up to 160 blocks a strip fits the 128 registers of two workgroups per CU; longer ones (20 to 40 blocks per wave) have a CU
-// to themselves.
+// A strip fits the 128 registers of two workgroups per CU.
 template <int NBLK>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBLK <= 20 ? 4 : 2, NBLK <= 20 ? 4 : 2)))
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void qr_bulk_kernel(QrBulkArgs a) {
     int matrix, b;
     if (!deal_to_dies(blockIdx.x, a.outer + a.acc, a.count, &matrix, &b)) return;
@@ -584,10 +583,8 @@ void qr_bulk_kernel(QrBulkArgs a) {
 // The Gram matrix squares the panel's condition number, which for m x 16 independent Gaussians is about
 // (sqrt(m) + 4) / (sqrt(m) - 4): 3 at 64 rows, 1.2 at 2000.  So this is for tall panels of a matrix drawn as independent
 // Gaussians (a panel behind its reflectors is such a matrix again); the last panels take qr_panel_body.
-// Bound by the latency of one workgroup.  With the strip in front, per launch: 22 us at 2100 rows (30 with a reduction and a
-// barrier per column), 9 us at 500 rows (15), of which the launch itself is 4; a whole draw alone: 2150 rows 3.91 -> 2.68 ms,
-// 543 rows 591 -> 412 us, 4096 rows 15 -> 9.3 (8.6 with the long strips through
-// qr_bulk_kernel).  Against 64 bits, compared with a reduction per column on the same Gaussians (24 draws at each of 12 sizes from
+// Bound by the latency of one workgroup.  With the strip in front, per launch: 9 us at 500 rows (15 with a reduction and a
+// barrier per column), of which the launch itself is 4; a whole draw alone, 543 rows: 591 -> 412 us.  Against 64 bits, compared with a reduction per column on the same Gaussians (24 draws at each of 12 sizes from
 // 129 to 517 rows, 8 at 1000, 4 at 2150, 2 at 4096): |A^T A - I| 0.95 to 0.99 of it, part of A^T G below the diagonal 0.99 to 1.00,
 // distance of A from the exact factor 0.90 to 1.05 (geometric means; the factor itself moves by the Gaussian's condition number).
 constexpr int kGramPanelRows = 64;       // panels of more rows than this are built from their Gram matrix
@@ -794,10 +791,7 @@ void gram_panel_kernel(float* Mp, float* Vr, float* Vt, float* Tg, float* Rd, fl
 // block wait until it is complete (delayed update) and get all its reflectors in one pass over the strip, in a launch of
 // strips only (qr_bulk_kernel, two workgroups per compute unit, which the panel's registers rule out here): that divides the
 // memory traffic, which is what bounds several factorisations side by side, by almost D.
-// One matrix at once / delayed: 517 rows 401 / 478 us, 2150 rows 2.66 / 3.32 ms, CONDITIONED 4096 rows 20.6 / 24.0 ms.
-// Draws of one matrix each that overlap on streams keep that order up to 2150 rows (two, three, four streams: 8, 12, 16
-// matrices in 12.5 / 15.3, 13.9 / 16.4, 15.6 / 18.7 ms) and at 4096 rows on two; there three streams are even and four
-// delayed ones 4 % ahead (8 matrices 34.1 / 32.8 ms, CONDITIONED 92.3 / 86.6).
+// One matrix at once / delayed: 517 rows 401 / 478 us; two, three, four streams of four draws each 1.77 / 2.24, 2.09 / 2.50, 2.36 / 2.74 ms.
 // Either way a column sees the same sums in the same order, so the bits are the same: that is why the outer strips start at
 // the block's first row, although only reflector p meets them (the blocks of a strip are dealt to the waves from its
 // first row on, and each wave sums its own).
@@ -979,17 +973,11 @@ hipError_t launch_qr_step_t(const QrStepArgs& a, int count, hipStream_t s) {
     return hipGetLastError();
 }
 
-// strip blocks per wave the step and panel kernels are built for: 5, 10, 15, 20, 30, 35, 40.  (A kernel that is too large still
-// requests and waits for the blocks that do not exist, but few: one for 25 took 0.4% less at 2600 rows, 1.5% at 3200.)
+// strip blocks per wave the step and panel kernels are built for: 5 and 10 (up to 704 rows, 44 tile rows, come here: wide_rows)
 template <class F>
 hipError_t for_strip_blocks(int per_wave, F&& f) {
     if (per_wave <= 5) return f(std::integral_constant<int, 5>{});
     if (per_wave <= 10) return f(std::integral_constant<int, 10>{});
-    if (per_wave <= 15) return f(std::integral_constant<int, 15>{});
-    if (per_wave <= 20) return f(std::integral_constant<int, 20>{});
-    if (per_wave <= 30) return f(std::integral_constant<int, 30>{});
-    if (per_wave <= 35) return f(std::integral_constant<int, 35>{});
-    if (per_wave <= 40) return f(std::integral_constant<int, 40>{});
     return hipErrorInvalidValue;
 }
 
@@ -1012,8 +1000,8 @@ hipError_t launch_qr_bulk_t(const QrBulkArgs& b, int count, hipStream_t s) {
 }
 
 hipError_t launch_qr_bulk(const QrBulkArgs& b, int count, hipStream_t s) {
-    // blocks per wave in steps of two: a strip kernel sized for 20 blocks spends a third more time on a strip of 11
-    // than one sized for 12 (it still requests and waits for the blocks that do not exist)
+    // blocks per wave in steps of two, up to 10 (below kWideProduct): a strip kernel sized for 20 blocks spends a third more time
+    // on a strip of 11 than one sized for 12 (it still requests and waits for the blocks that do not exist)
     const int per_wave = (b.nb_block + 7) / 8;
     switch ((per_wave + 1) / 2) {
         case 0: case 1: return launch_qr_bulk_t<2>(b, count, s);
@@ -1021,16 +1009,6 @@ hipError_t launch_qr_bulk(const QrBulkArgs& b, int count, hipStream_t s) {
         case 3: return launch_qr_bulk_t<6>(b, count, s);
         case 4: return launch_qr_bulk_t<8>(b, count, s);
         case 5: return launch_qr_bulk_t<10>(b, count, s);
-        case 6: return launch_qr_bulk_t<12>(b, count, s);
-        case 7: return launch_qr_bulk_t<14>(b, count, s);
-        case 8: return launch_qr_bulk_t<16>(b, count, s);
-        case 9: return launch_qr_bulk_t<18>(b, count, s);
-        case 10: return launch_qr_bulk_t<20>(b, count, s);
-        case 11: case 12: return launch_qr_bulk_t<24>(b, count, s);
-        case 13: case 14: return launch_qr_bulk_t<28>(b, count, s);
-        case 15: case 16: return launch_qr_bulk_t<32>(b, count, s);
-        case 17: case 18: return launch_qr_bulk_t<36>(b, count, s);
-        case 19: case 20: return launch_qr_bulk_t<40>(b, count, s);
         default: return hipErrorInvalidValue;
     }
 }

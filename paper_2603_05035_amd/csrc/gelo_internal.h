@@ -12,7 +12,7 @@
 namespace gelo {
 
 constexpr int kPanel = 16;          // column-panel width of the QR
-constexpr int kMaxN = 5120;         // 512 threads x 10 register-resident rows in the panel kernels, 8 waves x 40 blocks of 16 in the strips
+constexpr int kMaxN = 5120;         // 512 threads x 10 register-resident rows in the panel kernels, the condition estimate's 20 blocks of 256 columns
 constexpr int kInvBlock = 128;      // block width of the inverse's back substitution: its updates are GEMMs with K = 128
 
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
