@@ -287,8 +287,13 @@ void gemm_f32_short_kernel(F32Args g) {
 // Bound by what stands beside the matrix instructions, which take 45% of a step (1.66 us with a neighbour on the CU): the floats are
 // taken apart anew in every tile, and two barriers stand in a step.  Error against 64 bits 0.77 to 0.9 of the float instructions'
 // (K = 128 to 11008).
-// A product with an infinity in it comes out as NaN here (inf - inf when it is taken apart), as do sums past the largest float: a
-// tile that holds anything not finite is computed again with float multiply-adds, k by k.
+// Both operands are taken apart 2^16 times as large, and the sums scaled back: bf16 then holds every float down to the last bit of the
+// smallest one, where it would lose the low bits of operands below 2^-110 (1 to 2% of the time; keeping the smallest magnitude of every
+// step and sending small ones to the float instructions took 5 to 12%).
+// A product with an infinity in it comes out as NaN here (inf - inf when it is taken apart), as do operands from 2^112 on and sums from
+// 2^96 on: a tile that holds anything not finite is computed again with float multiply-adds, k by k.
+constexpr int kShift = 16;
+constexpr float kUnscale = 0x1p-32f;
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_f32_split_kernel(F32Args g) {
     constexpr int TILE = kTileM, F = TILE / 16;           // fragments across the tile
@@ -343,7 +348,7 @@ void gemm_f32_split_kernel(F32Args g) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) { x[e] = a_in ? x[e] : 0.f; y[e] = a_in ? y[e] : 0.f; }
             }
-            put_split(&stage[0][(wave + 4 * i) * 3 * kFrag + lane * 8], kFrag, split3(x, y));
+            put_split(&stage[0][(wave + 4 * i) * 3 * kFrag + lane * 8], kFrag, split3<kShift>(x, y));
         }
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
@@ -358,7 +363,7 @@ void gemm_f32_split_kernel(F32Args g) {
                 }
             }
             const int col = ITEMS * lane + i;
-            put_split(&stage[1][(col >> 4) * 3 * kFrag + (wave * 16 + (col & 15)) * 8], kFrag, split3(x, y));
+            put_split(&stage[1][(col >> 4) * 3 * kFrag + (wave * 16 + (col & 15)) * 8], kFrag, split3<kShift>(x, y));
         }
     };
     f32x4_t acc[FW][FW];                                  // [columns][rows]
@@ -409,7 +414,7 @@ void gemm_f32_split_kernel(F32Args g) {
             const int row = m0 + (wm * FW + n) * 16 + c;
             if (row >= g.M) continue;
             f32x4_t* cp = reinterpret_cast<f32x4_t*>(g.C + (int64_t)row * g.ldc + col);
-            *cp = g.subtract ? *cp - acc[f][n] : acc[f][n];
+            *cp = g.subtract ? *cp - acc[f][n] * kUnscale : acc[f][n] * kUnscale;
         }
     }
 }

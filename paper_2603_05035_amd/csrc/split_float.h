@@ -1,7 +1,7 @@
 // Float products on the bf16 matrix instructions: every float is taken apart into three bf16 values, x = h + m + l (each the
 // rounding of what the ones before leave: 8 + 8 + 8 significant bits, nothing is lost down to 2^-110), and six of the nine
-// products are taken, h h, h m, m h, m m, h l, l h.  What is left out is below 2^-25 of |x y|; the sums are float.  Six bf16
-// instructions take 3/8 of the time of the float ones for the same contraction.
+// products are taken, h h, h m, m h, m m, h l, l h.  What is left out, m l, l m and l l, is up to 2^-24 of |x y|; the sums are
+// float.  Six bf16 instructions take 3/8 of the time of the float ones for the same contraction.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -17,13 +17,17 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 constexpr int kFrag = 512;                                // bf16 values one v_mfma_f32_16x16x32_bf16 takes of an operand: 64 lanes x 8
 
 struct Split { bf16x8_t h, m, l; };
+// of 2^SHIFT times the values.  With 16 nothing is lost anywhere: the last bit of the smallest float, 2^-149, is a bf16 then, but values
+// from 2^112 on leave the range.
+template <int SHIFT = 0>
 __device__ __forceinline__ Split split3(f32x4_t a, f32x4_t b) {
+    constexpr float scale = 1 << SHIFT;
     Split s;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const float x = e < 4 ? a[e] : b[e - 4];
-        s.h[e] = (__bf16)x;
-        const float r = x - (float)s.h[e];
+        s.h[e] = (__bf16)(x * scale);
+        const float r = SHIFT == 0 ? x - (float)s.h[e] : fmaf(x, scale, -(float)s.h[e]);       // exact
         s.m[e] = (__bf16)r;
         s.l[e] = (__bf16)(r - (float)s.m[e]);
     }

@@ -129,6 +129,30 @@ def test_float_tiles_taken_apart_in_a_mix():
         assert bool(((out.double() - left @ right).abs() <= bound).all())
 
 
+# operands below 2^-110, whose last bits bf16 has no exponent for: everywhere, a row, a column, a K step or a single one of them, among zeros,
+# in the first and the last K step, in steps behind each other and apart.  The other operand is large, so that results are normal
+@pytest.mark.parametrize("k,at", [(40, slice(None)), (200, slice(None)), (200, slice(3, 4)), (200, slice(64, 96)), (200, slice(31, 65)), (200, slice(199, 200)), (200, slice(0, 200, 64))])
+@pytest.mark.parametrize("left", [True, False])
+def test_float_tiles_taken_apart_with_small_operands(k, at, left):
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    U, W = torch.randn((2048, k), generator=gen, device="cuda"), torch.randn((k, 2048), generator=gen, device="cuda")
+    small, large = (U, W.t()) if left else (W.t(), U)        # (K is the second dimension of either)
+    small[:, at] *= 2.0 ** -123
+    large *= 2.0 ** 30
+    small[100:200] *= torch.rand((100, k), generator=gen, device="cuda") < 0.5
+    small[300] = 0.0                                          # nothing else in these rows: no larger product hides what one loses
+    small[300, at] = 1.2345678e-37
+    small[301] = 0.0
+    small[301, k - 1] = -1.2345678e-36
+    Y = torch.empty((2048, 2048), device="cuda")
+    ctx = g.gelo_create(0, 1)
+    g.gelo_project(ctx, U, W, Y)
+    torch.cuda.synchronize()
+    g.gelo_destroy(ctx)
+    ref, size = U.double() @ W.double(), U.double().abs() @ W.double().abs()
+    assert bool(((Y.double() - ref).abs() <= 2.0 ** -24 * 1.01 * ref.abs() + k * 2.0 ** -24 * size).all())
+
+
 # infinities, NaN and sums past the largest float come out as float products give them: an infinity times a finite number is an
 # infinity, and the rest of the result is what it is without them
 def test_float_tiles_taken_apart_with_infinities():
