@@ -290,38 +290,41 @@ void gemm_f32_short_kernel(F32Args g) {
 // Both operands are taken apart 2^16 times as large, and the sums scaled back: bf16 then holds every float down to the last bit of the
 // smallest one, where it would lose the low bits of operands below 2^-110 (1 to 2% of the time; keeping the smallest magnitude of every
 // step and sending small ones to the float instructions took 5 to 12%).
-// A product with an infinity in it comes out as NaN here (inf - inf when it is taken apart), as do operands from 2^112 on and sums from
-// 2^96 on: a tile that holds anything not finite is computed again with float multiply-adds, k by k.
+// What meets an infinity or a NaN comes out as NaN here (inf - inf when it is taken apart), and so may what meets operands from
+// 2^112 on or sums from 2^96 on.  Such results are computed again on the float instructions, the finite ones of the tile keep their bits:
+// first over the K steps that hold anything not finite, which alone decide a result that meets one; if the tile has operands large
+// enough for sums to have left the range, over all steps.  Without / with a NaN or an infinity in every tile, on the float instructions
+// alone, us: 2048 x 12288 x 4096 1125 / 1340 to 1590, 1720; 512 x 12288 x 4096 327 / 515, 431; 2048 x 2048 x 1000 78 / 110, 87.  All sums past
+// 2^96: 3590, 1210, 214.
 constexpr int kShift = 16;
 constexpr float kUnscale = 0x1p-32f;
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void gemm_f32_split_kernel(F32Args g) {
-    constexpr int TILE = kTileM, F = TILE / 16;           // fragments across the tile
-    constexpr int FW = F / 2;                             // across a wave's quarter
-    constexpr int ITEMS = TILE * 4 / NT;                  // rows of A (columns of B) x eight k per thread and step
-    __shared__ __attribute__((aligned(1024))) uint16_t stage[2][3 * F * kFrag];      // A, B: [fragment][plane]
-    const int total = g.tiles_m * g.tiles_n, bid = blockIdx.x;
-    const int xcd = bid & 7, slot = bid >> 3, share = total >> 3, rem = total & 7;
-    const int lid = xcd * share + (xcd < rem ? xcd : rem) + slot;
-    const int m0 = lid / g.tiles_n * TILE, n0 = lid % g.tiles_n * TILE;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = lane & 15, q = lane >> 4, wm = wave & 1, wn = wave >> 1;
-    const int steps = (g.K + BK - 1) / BK;
+constexpr float kLarge = 0x1p32f;      // sums of less than 2^31 products of smaller operands stay below 2^95
+__device__ __forceinline__ bool finite(float x) { return fabsf(x) <= 3.402823466e38f; }
+constexpr int SF = kTileM / 16;                           // fragments across the tile
+constexpr int SFW = SF / 2;                               // across a wave's quarter
+
+// A thread's share of a step: eight consecutive k of two rows of A and of two columns of B
+struct SplitFeed {
+    static constexpr int ITEMS = kTileM * 4 / NT;
     // A: item i of this thread is row 16 (wave + 4 i) + c, k 8 q ..; B: wave w has k 8 w .., lane l the columns ITEMS l ..
     const float* arow[ITEMS];
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        const int row = m0 + 16 * (wave + 4 * i) + c;
-        arow[i] = g.A + (int64_t)(row < g.M ? row : g.M - 1) * g.lda;
-    }
-    const int col0 = n0 + ITEMS * lane < g.N ? n0 + ITEMS * lane : g.N - ITEMS;      // (N is a multiple of 8)
-    const float* B0 = g.B0;
-    const float* B1 = g.B1;
-    const int64_t ldb0 = g.ldb0, ldb1 = g.ldb1;
-    const int K0 = g.K0, Kd = g.K;
+    const float* B0;
+    const float* B1;
+    int64_t ldb0, ldb1;
+    int K0, Kd, col0, lane, wave, q;
     f32x4_t ra[ITEMS][2];
     float rb[8][ITEMS];
-    auto fetch = [&](int t) {
+    __device__ __forceinline__ SplitFeed(const F32Args& g, int m0, int n0, int tid) {
+        lane = tid & 63; wave = __builtin_amdgcn_readfirstlane(tid >> 6); q = lane >> 4;
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const int row = m0 + 16 * (wave + 4 * i) + (lane & 15);
+            arow[i] = g.A + (int64_t)(row < g.M ? row : g.M - 1) * g.lda;
+        }
+        col0 = n0 + ITEMS * lane < g.N ? n0 + ITEMS * lane : g.N - ITEMS;      // (N is a multiple of 8)
+        B0 = g.B0; B1 = g.B1; ldb0 = g.ldb0; ldb1 = g.ldb1; K0 = g.K0; Kd = g.K;
+    }
+    __device__ __forceinline__ void fetch(int t) {
         const int k0 = t * BK, ka = k0 + 8 * q, kb = k0 + 8 * wave;
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
@@ -329,30 +332,42 @@ void gemm_f32_split_kernel(F32Args g) {
             ra[i][0] = *reinterpret_cast<const f32x4_t*>(p);
             ra[i][1] = *reinterpret_cast<const f32x4_t*>(p + 4);
         }
+        static_assert(ITEMS == 2, "a lane's columns are read at once");
+        // (the rows, and so which segment they lie in, are the same for the whole wave)
+        const bool first = kb + 8 <= K0;
+        if (first || (kb >= K0 && kb + 8 <= Kd)) {
+            const float* p = (first ? B0 + (int64_t)kb * ldb0 : B1 + (int64_t)(kb - K0) * ldb1) + col0;
+            const int64_t ld = first ? ldb0 : ldb1;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {                     // (the row, and so which segment it lies in, is the same for the whole wave)
-            const int k = kb + e < Kd ? kb + e : Kd - 1;
-            const float* p = (k < K0 ? B0 + (int64_t)k * ldb0 : B1 + (int64_t)(k - K0) * ldb1) + col0;
-            static_assert(ITEMS == 2, "a lane's columns are read at once");
-            const float2 v = *reinterpret_cast<const float2*>(p);
-            rb[e][0] = v.x; rb[e][1] = v.y;
+            for (int e = 0; e < 8; ++e) { const float2 v = *reinterpret_cast<const float2*>(p + e * ld); rb[e][0] = v.x; rb[e][1] = v.y; }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int k = kb + e < Kd ? kb + e : Kd - 1;
+                const float* b = k < K0 ? B0 : B1;
+                const int64_t at = (k < K0 ? k : k - K0) * (k < K0 ? ldb0 : ldb1) + col0;
+                const float2 v = *reinterpret_cast<const float2*>(b + at);
+                rb[e][0] = v.x; rb[e][1] = v.y;
+            }
         }
-    };
-    auto park = [&](int t) {
+    }
+    // use(k .. k + 3, the next four, their place in the stage), cleared beyond K
+    template <class Use>
+    __device__ __forceinline__ void items(int t, uint16_t (*stage)[3 * SF * kFrag], Use&& use) {
         const int k0 = t * BK;
         const bool a_in = k0 + 8 * q < Kd;                // (A is zero up to the next multiple of 8)
+        f32x4_t x, y;
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
-            f32x4_t x = ra[i][0], y = ra[i][1];
+            x = ra[i][0]; y = ra[i][1];
             if (k0 + BK > Kd) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) { x[e] = a_in ? x[e] : 0.f; y[e] = a_in ? y[e] : 0.f; }
             }
-            put_split(&stage[0][(wave + 4 * i) * 3 * kFrag + lane * 8], kFrag, split3<kShift>(x, y));
+            use(x, y, &stage[0][(wave + 4 * i) * 3 * kFrag + lane * 8]);
         }
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
-            f32x4_t x, y;
 #pragma unroll
             for (int e = 0; e < 4; ++e) { x[e] = rb[e][i]; y[e] = rb[4 + e][i]; }
             if (k0 + BK > Kd) {
@@ -363,21 +378,126 @@ void gemm_f32_split_kernel(F32Args g) {
                 }
             }
             const int col = ITEMS * lane + i;
-            put_split(&stage[1][(col >> 4) * 3 * kFrag + (wave * 16 + (col & 15)) * 8], kFrag, split3<kShift>(x, y));
+            use(x, y, &stage[1][(col >> 4) * 3 * kFrag + (wave * 16 + (col & 15)) * 8]);
         }
+    }
+};
+
+// The results of a tile that came out not finite, on the float instructions.  The stage takes the floats where the planes h and m would be.
+// What it needs is formed anew from the arguments in memory and from numbers the compiler cannot tell from others, and half of a wave's
+// columns are taken at a time: kept in registers through the kernel's loop it cost that a tenth of its speed.
+constexpr int kTakenBits = 1024;
+__device__ __forceinline__ void float_results(uint16_t (*stage)[3 * SF * kFrag], uint32_t (&taken)[kTakenBits / 32], int m0, int n0, f32x4_t (&acc)[SFW][SFW]) {
+    typedef const __attribute__((address_space(4))) F32Args* KernelArgs;
+    KernelArgs args = (KernelArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    int tid = threadIdx.x;
+    asm volatile("" : "+s"(args), "+v"(tid), "+s"(m0), "+s"(n0));
+    F32Args g;
+    g.A = args->A; g.lda = args->lda; g.B0 = args->B0; g.ldb0 = args->ldb0; g.K0 = args->K0; g.B1 = args->B1; g.ldb1 = args->ldb1;
+    g.M = args->M; g.N = args->N; g.K = args->K;
+    SplitFeed in(g, m0, n0, tid);
+    const int steps = (g.K + BK - 1) / BK, per_bit = (steps + kTakenBits - 1) / kTakenBits;
+    // which steps hold anything not finite?
+    if (tid < kTakenBits / 32) taken[tid] = 0;
+    __syncthreads();
+    bool large = false;
+#pragma unroll 1
+    for (int t0 = 0; t0 < steps; t0 += 4) {               // four steps' reads on their way at a time
+        SplitFeed ahead[4] = {in, in, in, in};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ahead[i].fetch(t0 + i < steps ? t0 + i : steps - 1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int t = t0 + i < steps ? t0 + i : steps - 1;
+            uint32_t most = 0;                            // magnitudes as integers, twice
+            ahead[i].items(t, stage, [&](f32x4_t x, f32x4_t y, uint16_t*) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) most = max(max(most, 2 * __float_as_uint(x[e])), 2 * __float_as_uint(y[e]));
+            });
+            const bool odd = most >= 2 * 0x7f800000u;
+            if (!odd) large = large | (most >= 2 * __float_as_uint(kLarge));
+            else ahead[i].items(t, stage, [&](f32x4_t x, f32x4_t y, uint16_t*) {
+#pragma unroll 1
+                for (int e = 0; e < 4; ++e) large = large | (finite(x[e]) & (fabsf(x[e]) >= kLarge)) | (finite(y[e]) & (fabsf(y[e]) >= kLarge));
+            });
+            if (odd) atomicOr(&taken[t / per_bit / 32], 1u << (t / per_bit % 32));
+        }
+    }
+    const bool all = __syncthreads_or(large);
+    auto next = [&](int t) {                              // the next step that counts from t on (the same in all waves)
+        while (!all && t < steps && !(__builtin_amdgcn_readfirstlane(taken[t / per_bit / 32]) >> (t / per_bit % 32) & 1)) ++t;
+        return t;
     };
+    const uint16_t* fa = &stage[0][(in.wave & 1) * SFW * 3 * kFrag + in.lane * 8];
+    const uint16_t* fb = &stage[1][(in.wave >> 1) * SFW * 3 * kFrag + in.lane * 8];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+        f32x4_t sum[SFW / 2][SFW];
+#pragma unroll
+        for (int f = 0; f < SFW / 2; ++f)
+#pragma unroll
+            for (int n = 0; n < SFW; ++n) sum[f][n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        int t = next(0);
+        in.fetch(t < steps ? t : 0);
+#pragma unroll 1
+        while (t < steps) {
+            __syncthreads();                              // nobody reads the last stage any more
+            in.items(t, stage, [&](f32x4_t x, f32x4_t y, uint16_t* at) { *reinterpret_cast<f32x4_t*>(at) = x; *reinterpret_cast<f32x4_t*>(at + kFrag) = y; });
+            __syncthreads();
+            t = next(t + 1);
+            in.fetch(t < steps ? t : 0);
+#pragma unroll 1
+            for (int h = 0; h < 2; ++h) {
+                f32x4_t rows[SFW];
+#pragma unroll
+                for (int n = 0; n < SFW; ++n) rows[n] = *reinterpret_cast<const f32x4_t*>(fa + (n * 3 + h) * kFrag);
+#pragma unroll
+                for (int f = 0; f < SFW / 2; ++f) {
+                    const f32x4_t col = *reinterpret_cast<const f32x4_t*>(fb + ((half * SFW / 2 + f) * 3 + h) * kFrag);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int n = 0; n < SFW; ++n) sum[f][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(col[e], rows[n][e], sum[f][n], 0, 0, 0);
+                }
+            }
+        }
+#pragma unroll
+        for (int f = 0; f < SFW / 2; ++f)
+#pragma unroll
+            for (int n = 0; n < SFW; ++n)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float r = acc[half * SFW / 2 + f][n][v];
+                    acc[half * SFW / 2 + f][n][v] = finite(r) ? r : sum[f][n][v];
+                }
+    }
+    __syncthreads();                                      // everybody has read its operands
+}
+
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void gemm_f32_split_kernel(F32Args g) {
+    constexpr int FW = SFW;
+    __shared__ __attribute__((aligned(1024))) uint16_t stage[2][3 * SF * kFrag];     // A, B: [fragment][plane]
+    __shared__ uint32_t taken[kTakenBits / 32];
+    const int total = g.tiles_m * g.tiles_n, bid = blockIdx.x;
+    const int xcd = bid & 7, slot = bid >> 3, share = total >> 3, rem = total & 7;
+    const int lid = xcd * share + (xcd < rem ? xcd : rem) + slot;
+    const int m0 = lid / g.tiles_n * kTileM, n0 = lid % g.tiles_n * kTileM;
+    SplitFeed in(g, m0, n0, threadIdx.x);
+    const int lane = in.lane, c = lane & 15, q = in.q, wm = in.wave & 1, wn = in.wave >> 1;
+    const int steps = (g.K + BK - 1) / BK;
     f32x4_t acc[FW][FW];                                  // [columns][rows]
 #pragma unroll
     for (int f = 0; f < FW; ++f)
 #pragma unroll
         for (int n = 0; n < FW; ++n) acc[f][n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    fetch(0);
+    in.fetch(0);
     for (int t = 0; t < steps; ++t) {
         if (t > 0) __syncthreads();                       // nobody reads the last stage any more
-        park(t);
+        in.items(t, stage, [&](f32x4_t x, f32x4_t y, uint16_t* at) { put_split(at, kFrag, split3<kShift>(x, y)); });
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
-        fetch(t + 1 < steps ? t + 1 : t);                 // unconditional: a wait then counts what was issued behind what it waits for
+        in.fetch(t + 1 < steps ? t + 1 : t);              // unconditional: a wait then counts what was issued behind what it waits for
         __builtin_amdgcn_sched_barrier(0);
         const uint16_t* fa = &stage[0][wm * FW * 3 * kFrag + lane * 8];
         const uint16_t* fb = &stage[1][wn * FW * 3 * kFrag + lane * 8];
@@ -392,19 +512,8 @@ void gemm_f32_split_kernel(F32Args g) {
 #pragma unroll
         for (int n = 0; n < FW; ++n)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) bad = bad | !(fabsf(acc[f][n][v]) <= 3.402823466e38f);
-    if (__syncthreads_or(bad)) {
-        for (int i = tid; i < TILE * TILE; i += NT) {
-            const int row = m0 + i / TILE, col = n0 + i % TILE;
-            if (row >= g.M || col >= g.N) continue;
-            float sum = 0.f;
-            for (int k = 0; k < Kd; ++k)
-                sum = fmaf(g.A[(int64_t)row * g.lda + k], k < K0 ? B0[(int64_t)k * ldb0 + col] : B1[(int64_t)(k - K0) * ldb1 + col], sum);
-            float* cp = g.C + (int64_t)row * g.ldc + col;
-            *cp = g.subtract ? *cp - sum : sum;
-        }
-        return;
-    }
+            for (int v = 0; v < 4; ++v) { bad = bad | !finite(acc[f][n][v]); acc[f][n][v] *= kUnscale; }
+    if (__syncthreads_or(bad)) float_results(stage, taken, m0, n0, acc);       // (nothing is stored before everything has been read, here too)
 #pragma unroll
     for (int f = 0; f < FW; ++f) {
         const int col = n0 + (wn * FW + f) * 16 + 4 * q;
@@ -414,7 +523,7 @@ void gemm_f32_split_kernel(F32Args g) {
             const int row = m0 + (wm * FW + n) * 16 + c;
             if (row >= g.M) continue;
             f32x4_t* cp = reinterpret_cast<f32x4_t*>(g.C + (int64_t)row * g.ldc + col);
-            *cp = g.subtract ? *cp - acc[f][n] * kUnscale : acc[f][n] * kUnscale;
+            *cp = g.subtract ? *cp - acc[f][n] : acc[f][n];
         }
     }
 }

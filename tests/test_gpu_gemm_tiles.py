@@ -174,3 +174,44 @@ def test_float_tiles_taken_apart_with_infinities():
     assert torch.equal(torch.isinf(Y) & sure, torch.isinf(want) & sure)
     fine = sure & torch.isfinite(want)
     assert bool(((Y.double() - ref).abs()[fine] <= (65 * 2.0 ** -24 * size)[fine] * 1.01).all())
+
+
+# A value that is not finite changes what it meets and nothing else, to the bit: the results without it elsewhere, in tiles that are computed
+# again for its sake as well.  One value, a column of K, whole K steps, the last k; with operands large enough for a sum to pass 2^96 too
+@pytest.mark.parametrize("value", [float("inf"), -float("inf"), float("nan")])
+@pytest.mark.parametrize("k,at", [(40, slice(39, 40)), (104, slice(7, 8)), (104, slice(32, 64)), (200, slice(0, 200, 33))])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** 40])
+def test_float_tiles_taken_apart_keep_the_bits_beside_values_not_finite(value, k, at, scale):
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    U, W = torch.randn((2048, k), generator=gen, device="cuda") * scale, torch.randn((k, 2048), generator=gen, device="cuda") * scale
+    Y, Y0 = torch.empty((2048, 2048), device="cuda"), torch.empty((2048, 2048), device="cuda")
+    ctx = g.gelo_create(0, 1)
+    g.gelo_project(ctx, U, W, Y0)
+    U[130, at], U[2047, at], W[at, 777] = value, value, value
+    g.gelo_project(ctx, U, W, Y)
+    torch.cuda.synchronize()
+    g.gelo_destroy(ctx)
+    ref = U.double() @ W.double()
+    met = torch.zeros((2048, 2048), dtype=torch.bool, device="cuda")
+    met[130], met[2047], met[:, 777] = True, True, True
+    assert torch.equal(Y[~met], Y0[~met])
+    assert torch.equal(Y[met].double().nan_to_num(nan=7.0), ref[met].nan_to_num(nan=7.0))
+
+
+# operands and sums that leave the range of the operands taken apart (2^112, 2^96) but not that of float, among others in it
+def test_float_tiles_taken_apart_with_large_operands():
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    U, W = torch.randn((2048, 72), generator=gen, device="cuda"), torch.randn((72, 2048), generator=gen, device="cuda")
+    U[5], U[700, 3], U[1500] = U[5] * 2.0 ** 120, 1.5 * 2.0 ** 125, U[1500] * 2.0 ** 60
+    W[:, 30] *= 2.0 ** 50
+    W[:, 31] *= 2.0 ** -30
+    W[3] = W[3] * 2.0 ** -6
+    Y = torch.empty((2048, 2048), device="cuda")
+    ctx = g.gelo_create(0, 1)
+    g.gelo_project(ctx, U, W, Y)
+    torch.cuda.synchronize()
+    g.gelo_destroy(ctx)
+    ref, size = U.double() @ W.double(), U.double().abs() @ W.double().abs()
+    sure = size < 3.3e38                                     # (beyond, a partial sum may pass the largest float)
+    assert int((~sure).sum()) == 2
+    assert bool(((Y.double() - ref).abs() <= 2.0 ** -24 * 1.01 * ref.abs() + 72 * 2.0 ** -24 * size)[sure].all())
