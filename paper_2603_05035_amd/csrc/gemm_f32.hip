@@ -4,8 +4,8 @@
 // through v_mfma_f32_32x32x2_f32 in 64 x 64 tiles.
 // A 128 x 128 tile of gemm_f32_kernel reads all of its operands before it stores, so the product may overwrite B in place with M <= 128
 // (C == B0, K0 == K: the back substitution's multiplications by a diagonal-block inverse, a caller's un-mix into its Y) and A where
-// one tile spans N.  Smaller tiles would read what their neighbours have stored, and the tiles taken apart read their
-// operands twice if need be: neither is taken where C meets an operand.
+// one tile spans N.  So does a tile of gemm_f32_split_kernel.  Smaller tiles would read what their neighbours have stored: they are not
+// taken where C meets an operand.
 //
 // gemm_f32_kernel: a workgroup of 4 waves walks K in steps of 32 through double-buffered LDS.  A lane reads four consecutive k of its A
 // row with one 16-byte LDS read and spends them on four successive MFMAs; the matching B values are single dwords,
@@ -550,14 +550,18 @@ hipError_t gemm_f32(const GemmOperands& o, hipStream_t stream) {
         hipLaunchKernelGGL(gemm_f32_short_kernel, dim3(a.tiles_n), dim3(NT), kShortLds, stream, a);
         return hipGetLastError();
     }
-    // does C share memory with an operand (as far as the ranges from the first to the last element tell)?
+    // Does C share memory with an operand?  Slices of the columns of one buffer, which have the same pitch, do not where their columns
+    // are apart; with different pitches the ranges from the first to the last element tell.
     auto meets_c = [&](const void* p, int64_t ld, int64_t rows, int64_t cols) {
-        const uintptr_t lo = (uintptr_t)p, hi = lo + ((rows - 1) * ld + cols) * sizeof(float);
-        const uintptr_t c_lo = (uintptr_t)o.C, c_hi = c_lo + ((o.M - 1) * o.ldc + o.N) * sizeof(float);
-        return rows > 0 && lo < c_hi && c_lo < hi;
+        const intptr_t lo = (intptr_t)p, hi = lo + ((rows - 1) * ld + cols) * sizeof(float);
+        const intptr_t c_lo = (intptr_t)o.C, c_hi = c_lo + ((o.M - 1) * o.ldc + o.N) * sizeof(float);
+        if (rows <= 0 || lo >= c_hi || c_lo >= hi) return false;
+        const intptr_t pitch = ld * sizeof(float);
+        const intptr_t behind = ((lo - c_lo) % pitch + pitch) % pitch;       // from a row of C to the operand's next one
+        return ld != o.ldc || behind < (intptr_t)(o.N * sizeof(float)) || behind + (intptr_t)(cols * sizeof(float)) > pitch;
     };
-    const bool in_place = meets_c(o.A, o.lda, o.M, o.K) || meets_c(o.B0, o.ldb0, std::min(o.K0, o.K), o.N) || meets_c(o.B1, o.ldb1, o.K - o.K0, o.N);
     const int tiles = a.tiles_m * ((o.N + kTileM - 1) / kTileM);
+    const bool in_place = tiles < kCus && (meets_c(o.A, o.lda, o.M, o.K) || meets_c(o.B0, o.ldb0, std::min(o.K0, o.K), o.N) || meets_c(o.B1, o.ldb1, o.K - o.K0, o.N));
     if (in_place) {
         a.tiles_n = (o.N + kTileM - 1) / kTileM;
         hipLaunchKernelGGL((gemm_f32_kernel<kTileM>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);

@@ -215,3 +215,43 @@ def test_float_tiles_taken_apart_with_large_operands():
     sure = size < 3.3e38                                     # (beyond, a partial sum may pass the largest float)
     assert int((~sure).sum()) == 2
     assert bool(((Y.double() - ref).abs() <= 2.0 ** -24 * 1.01 * ref.abs() + 72 * 2.0 ** -24 * size)[sure].all())
+
+
+# The same product with its result in place of an operand (128 rows of B, so many columns that it is taken apart), and with operands and
+# result as slices of the columns of one buffer: the same bits
+@pytest.mark.parametrize("n_data,k", [(128, 0), (100, 28), (121, 6)])
+def test_float_tiles_taken_apart_in_place_of_their_operands(n_data, k):
+    n, p = n_data + k, 32776
+    gen = torch.Generator(device="cuda").manual_seed(n_data)
+    ctx = g.gelo_create(0, 1, allow_batch_reuse=True)
+    m = g.gelo_sample_mixing(ctx, g.GELO_CONDITIONED, n_data, k, p, g.GELO_F32, batch_id=1)
+    H = torch.randn((n_data, p), generator=gen, device="cuda")
+    H[3, 7], H[5, 9000] = float("inf"), float("nan")             # (computed again behind the loop, still before anything is stored)
+    U, Z = torch.empty((n, p), device="cuda"), torch.empty((n_data, p), device="cuda")
+    g.gelo_mix(ctx, m, H, U)
+    g.gelo_unmix(ctx, m, U, Z)
+    buf = torch.zeros((n, p), device="cuda")
+    buf[:n_data] = H
+    g.gelo_mix(ctx, m, buf[:n_data], buf)
+    torch.cuda.synchronize()
+    assert torch.equal(buf.view(torch.int32), U.view(torch.int32))
+    g.gelo_unmix(ctx, m, buf, buf[:n_data])
+    torch.cuda.synchronize()
+    assert torch.equal(buf[:n_data].view(torch.int32), Z.view(torch.int32))
+    g.gelo_mixing_free(ctx, m)
+    g.gelo_destroy(ctx)
+
+
+@pytest.mark.parametrize("m,k,n", [(2048, 104, 2056), (2048, 2048, 2048), (300, 104, 200)])
+def test_float_slices_of_one_buffer(m, k, n):
+    gen = torch.Generator(device="cuda").manual_seed(m + n)
+    wide = torch.randn((max(m, k), k + 2 * n), generator=gen, device="cuda")
+    U, W, Y = wide[:m, :k], wide[:k, k:k + n], wide[:m, k + n:]
+    apart = torch.empty((m, n), device="cuda")
+    ctx = g.gelo_create(0, 1)
+    g.gelo_project(ctx, U.contiguous(), W.contiguous(), apart)
+    before = wide[:, :k + n].clone()
+    g.gelo_project(ctx, U, W, Y)
+    torch.cuda.synchronize()
+    g.gelo_destroy(ctx)
+    assert torch.equal(Y, apart) and torch.equal(wide[:, :k + n], before)
