@@ -5,6 +5,9 @@
 //   W' = -T W                reflect_w_kernel
 //   X += Y W'                reflect_update_kernel  contraction over the 256 reflectors
 //
+// Y W' is summed by itself and added to X once: with X in the accumulator from the start every instruction rounds at its size, and
+// |A^T A - I| was 1.4 to 1.8 times what it is (720 to 2150 rows), the part of A^T G below the diagonal 1.3 to 1.7 times.
+//
 // The two large products run on the bf16 matrix instructions with every float taken apart into three bf16 values (split_float.h).
 //
 // Everything stays in the 16 x 16 tiles of the factorisation (qr_tile_index): v_mfma_f32_16x16x32_bf16 leaves a tile in the
@@ -416,7 +419,7 @@ void reflect_update_direct_kernel(WideArgs a) {
     };
     fetch(0, y[0], w[0]);
     fetch(1, y[1], w[1]);
-    f32x4_t acc[2][2];
+    f32x4_t x[2][2], acc[2][2];
     auto tile = [&](int f, int n) {
         const int r = r0 + f < a.mt ? r0 + f : a.mt - 1, c = c0 + n < a.mt ? c0 + n : a.mt - 1;
         return a.X + (int64_t)matrix * a.batch_stride + ((int64_t)c * a.nbr + r) * 256 + (lane & 15) * 16 + 4 * (lane >> 4);
@@ -424,7 +427,10 @@ void reflect_update_direct_kernel(WideArgs a) {
 #pragma unroll
     for (int f = 0; f < 2; ++f)
 #pragma unroll
-        for (int n = 0; n < 2; ++n) acc[f][n] = *reinterpret_cast<const f32x4_t*>(tile(f, n));
+        for (int n = 0; n < 2; ++n) {
+            x[f][n] = *reinterpret_cast<const f32x4_t*>(tile(f, n));
+            acc[f][n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
     static_for<WT / 2>([&](auto uc) {
         constexpr int u = decltype(uc)::value;
         if (u >= units) return;
@@ -435,8 +441,10 @@ void reflect_update_direct_kernel(WideArgs a) {
 #pragma unroll
     for (int f = 0; f < 2; ++f)
 #pragma unroll
-        for (int n = 0; n < 2; ++n)
+        for (int n = 0; n < 2; ++n) {
+            acc[f][n] = x[f][n] + acc[f][n];
             if (r0 + f < a.mt && c0 + n < a.mt) *reinterpret_cast<f32x4_t*>(tile(f, n)) = acc[f][n];
+        }
     if (a.next != nullptr && c0 < 8) {                    // wave-uniform
 #pragma unroll
         for (int n = 0; n < 2; ++n) next_panel(a, matrix, r0, c0 + n, acc[0][n], acc[1][n], lane);
@@ -444,7 +452,8 @@ void reflect_update_direct_kernel(WideArgs a) {
 }
 
 // X += Y W', many matrices: a workgroup has 128 rows x 128 columns of X, a wave 64 x 64.  One stage in LDS, the next one on its way to registers: two
-// workgroups share a CU, one waits and parks while the other multiplies.
+// workgroups share a CU, one waits and parks while the other multiplies.  X is on its way during the last products (read behind them: 32
+// draws of 2150 rows 11510 instead of 10570 us).
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void reflect_update_kernel(WideArgs a) {
     __shared__ __attribute__((aligned(1024))) uint16_t stage[2][24 * kFrag];      // [8 tile rows of Y][plane], [8 tile columns of W'][plane]
@@ -477,8 +486,8 @@ void reflect_update_kernel(WideArgs a) {
 #pragma unroll
     for (int f = 0; f < 4; ++f)
 #pragma unroll
-        for (int n = 0; n < 4; ++n) acc[f][n] = *reinterpret_cast<const f32x4_t*>(tile(f, n));
-    for (int u = 0; u < units; ++u) {
+        for (int n = 0; n < 4; ++n) acc[f][n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto step = [&](int u, auto&& request) {
         if (u > 0) __syncthreads();                       // nobody reads the last stage any more
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -487,7 +496,7 @@ void reflect_update_kernel(WideArgs a) {
                 *reinterpret_cast<u32x4_t*>(&stage[i >> 1][((wave * 2 + (i & 1)) * 3 + p) * kFrag + lane * 8]) = st[i][p];
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
-        fetch(u + 1 < units ? u + 1 : u);                 // unconditional: see reflect_wt_kernel
+        request();
         __builtin_amdgcn_sched_barrier(0);
         const uint16_t* ya = &stage[0][wm * 12 * kFrag + lane * 8];
         const uint16_t* wb = &stage[1][wn * 12 * kFrag + lane * 8];
@@ -495,11 +504,20 @@ void reflect_update_kernel(WideArgs a) {
 #pragma unroll
         for (int n = 0; n < 4; ++n) { x[n].h = frag_of(wb + n * 3 * kFrag); x[n].m = frag_of(wb + (n * 3 + 1) * kFrag); x[n].l = frag_of(wb + (n * 3 + 2) * kFrag); }
         products([&](int plane, int f) { return frag_of(ya + (f * 3 + plane) * kFrag); }, x, acc);
-    }
+    };
+    for (int u = 0; u + 1 < units; ++u) step(u, [&] { fetch(u + 1); });
+    f32x4_t before[4][4];
+    step(units - 1, [&] {
+#pragma unroll
+        for (int f = 0; f < 4; ++f)
+#pragma unroll
+            for (int n = 0; n < 4; ++n) before[f][n] = *reinterpret_cast<const f32x4_t*>(tile(f, n));
+    });
 #pragma unroll
     for (int f = 0; f < 4; ++f)
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
+            acc[f][n] = before[f][n] + acc[f][n];
             if (rg * 8 + wm * 4 + f < a.mt && cg * 8 + wn * 4 + n < a.mt) *reinterpret_cast<f32x4_t*>(tile(f, n)) = acc[f][n];
         }
     if (a.next != nullptr && cg == 0) {
