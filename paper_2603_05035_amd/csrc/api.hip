@@ -91,6 +91,7 @@ struct gelo_ctx {
     void* static_scratch;              // device address of `scratch` on this context's device
     std::string err;
     void* factor_ws; size_t factor_ws_bytes;
+    size_t factor_ws_refused;          // the smallest size of it for several matrices that the device did not have
     void* chain_ws;  size_t chain_ws_bytes;
     void* quant_ws;  size_t quant_ws_bytes;    // FP8 projection: codes and row scales of the current U
     void* project_ws; size_t project_ws_bytes; // bf16 projection of at most 128 rows: float partial sums of the K slices
@@ -166,9 +167,27 @@ gelo_status grow(gelo_ctx* ctx, void** buf, size_t* have, size_t need) {
         *buf = nullptr; *have = 0;
     }
     hipError_t e = hipMalloc(buf, need);
-    if (e != hipSuccess) { *buf = nullptr; return fail(ctx, GELO_ENOMEM, "hipMalloc(%zu) failed: %s", need, hipGetErrorString(e)); }
+    if (e != hipSuccess) {
+        *buf = nullptr;
+        (void)hipGetLastError();                    // or the next launch would be blamed for it
+        return fail(ctx, GELO_ENOMEM, "hipMalloc(%zu) failed: %s", need, hipGetErrorString(e));
+    }
     *have = need;
     return GELO_OK;
+}
+
+// Workspaces for *side factorisations side by side, for half as many where the device does not have the memory, and so on down to one.
+// (A size that was refused is not asked for again, so that what was got instead stays.)
+gelo_status grow_side_by_side(gelo_ctx* ctx, size_t ws_bytes, int* side) {
+    for (;;) {
+        const size_t need = ws_bytes * (size_t)*side;
+        if (*side == 1 || need < ctx->factor_ws_refused) {
+            const gelo_status st = grow(ctx, &ctx->factor_ws, &ctx->factor_ws_bytes, need);
+            if (st != GELO_ENOMEM || *side == 1) return st;
+            ctx->factor_ws_refused = need;
+        }
+        *side = (*side + 1) / 2;
+    }
 }
 
 // Sizes of the device block behind one mixing object and where its parts sit in it.
@@ -235,7 +254,11 @@ gelo_status acquire_mixing(gelo_ctx* ctx, int n_data, int k, int d, int dtype, M
     const MixingLayout L = mixing_layout(n_data, k, d, dtype, form);
     void* block = nullptr;
     hipError_t e = hipMalloc(&block, L.total);
-    if (e != hipSuccess) { delete m; return fail(ctx, GELO_ENOMEM, "hipMalloc(%zu) failed: %s", L.total, hipGetErrorString(e)); }
+    if (e != hipSuccess) {
+        delete m;
+        (void)hipGetLastError();
+        return fail(ctx, GELO_ENOMEM, "hipMalloc(%zu) failed: %s", L.total, hipGetErrorString(e));
+    }
     carve_mixing(m, block, n_data, k, d, dtype, form);
     if (hipEventCreateWithFlags(&m->ready, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&m->released, hipEventDisableTiming) != hipSuccess) {
@@ -342,6 +365,7 @@ gelo_status gelo_create(gelo_ctx** out, int device, uint64_t seed, int allow_bat
         if (device < kStaticMaxDevices) g_scratch_ptr[device] = ptr;
     }
     ctx->factor_ws = ctx->chain_ws = nullptr; ctx->factor_ws_bytes = ctx->chain_ws_bytes = 0;
+    ctx->factor_ws_refused = SIZE_MAX;
     ctx->quant_ws = nullptr; ctx->quant_ws_bytes = 0;
     ctx->project_ws = nullptr; ctx->project_ws_bytes = 0;
     ctx->host_scalars = nullptr; ctx->host_flag = nullptr;
@@ -879,8 +903,8 @@ gelo_status gelo_sample_mixing_batch(gelo_ctx* ctx, gelo_kind kind, int n_data, 
     const bool small = kind == GELO_ORTHOGONAL && n <= kSmallMaxN;
     // larger matrices: up to kQrSideBySide factorisations share every launch, each in a workspace of its own
     const size_t ws_bytes = up256(factor_workspace_bytes(n));
-    const int side = qr_side_by_side(count, ws_bytes);
-    gelo_status st = small ? GELO_OK : grow(ctx, &ctx->factor_ws, &ctx->factor_ws_bytes, blocked ? block_workspace_bytes(n) * count : ws_bytes * side);
+    int side = qr_side_by_side(count, ws_bytes);
+    gelo_status st = small ? GELO_OK : blocked ? grow(ctx, &ctx->factor_ws, &ctx->factor_ws_bytes, block_workspace_bytes(n) * count) : grow_side_by_side(ctx, ws_bytes, &side);
     if (st != GELO_OK) return st;
     SmallSampleTargets t;
     gelo_mixing* got[GELO_MAX_BATCH_DRAW];
@@ -1130,8 +1154,9 @@ gelo_status gelo_reserve(gelo_ctx* ctx, gelo_kind kind, gelo_dtype dtype, int n_
     }
     if (((kind == GELO_ORTHOGONAL && n > kSmallMaxN) || kind == GELO_REFLECTOR_PRODUCT) && mixings > 1) {
         // a batched draw of `mixings` matrices factorises up to kQrSideBySide of them side by side
-        const int side = qr_side_by_side(mixings, up256(factor_workspace_bytes(n)));
-        st = grow(ctx, &ctx->factor_ws, &ctx->factor_ws_bytes, up256(factor_workspace_bytes(n)) * side);
+        const size_t ws_bytes = up256(factor_workspace_bytes(n));
+        int side = qr_side_by_side(mixings, ws_bytes);
+        st = grow_side_by_side(ctx, ws_bytes, &side);
         if (st != GELO_OK) return st;
     }
     if (p > 0) {

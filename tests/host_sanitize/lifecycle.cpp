@@ -6,8 +6,18 @@
 #include <cstdlib>
 #include <cstring>
 #include <vector>
+#include <dlfcn.h>
 #include <hip/hip_runtime.h>
 #include "gelo.h"
+
+// The library's device allocations come through here: none of more than `malloc_most` bytes succeeds.
+static size_t malloc_most = SIZE_MAX;
+static int malloc_refused = 0;
+extern "C" hipError_t hipMalloc(void** ptr, size_t size) {
+    static const auto real = reinterpret_cast<hipError_t (*)(void**, size_t)>(dlsym(RTLD_NEXT, "hipMalloc"));
+    if (size > malloc_most) { ++malloc_refused; *ptr = nullptr; return hipErrorOutOfMemory; }
+    return real(ptr, size);
+}
 
 static int failures = 0;
 #define EXPECT(call, want) do { gelo_status got_ = (call); if (got_ != (want)) { \
@@ -127,6 +137,43 @@ int main() {
         for (int i = 0; i < 3; ++i) EXPECT(gelo_mixing_free(ctx, many[i]), GELO_OK);
         HIP_OK(hipDeviceSynchronize());
         HIP_OK(hipFree(BH)); HIP_OK(hipFree(BU)); HIP_OK(hipFree(BY)); HIP_OK(hipFree(BZ)); HIP_OK(hipFree(BA));
+    }
+
+    // a batched draw where the device has no memory for all workspaces: fewer at a time, the same matrices; with none for one it says so and
+    // the context goes on working
+    {
+        const int qn = 720, count = 12;
+        float *A0 = nullptr, *A1 = nullptr;
+        HIP_OK(hipMalloc(&A0, sizeof(float) * qn * qn)); HIP_OK(hipMalloc(&A1, sizeof(float) * qn * qn));
+        std::vector<float> a0((size_t)qn * qn), a1((size_t)qn * qn);
+        gelo_ctx* other = nullptr;
+        EXPECT(gelo_create(&other, 0, 0xC0FFEEull, 0), GELO_OK);
+        const uint64_t qid = 5000 + 4 * (uint64_t)GELO_BATCH_WINDOW;
+        malloc_most = (size_t)60 << 20;
+        EXPECT(gelo_reserve(other, GELO_ORTHOGONAL, GELO_F32, qn, 0, d, 0, 1, count), GELO_OK);
+        const int refused = malloc_refused;
+        EXPECT(gelo_sample_mixing_batch(other, GELO_ORTHOGONAL, qn, 0, d, GELO_F32, qid, count, many, nullptr), GELO_OK);
+        if (refused == 0 || malloc_refused != refused) { std::printf("%d allocations were refused, %d of them behind the reservation\n", malloc_refused, malloc_refused - refused); ++failures; }
+        malloc_most = SIZE_MAX;
+        EXPECT(gelo_sample_mixing(ctx, GELO_ORTHOGONAL, qn, 0, d, GELO_F32, 0.0, 1, qid + count - 1, &m, nullptr), GELO_OK);
+        EXPECT(gelo_mixing_export(ctx, m, A0, nullptr, nullptr, nullptr, nullptr, nullptr), GELO_OK);
+        EXPECT(gelo_mixing_export(other, many[count - 1], A1, nullptr, nullptr, nullptr, nullptr, nullptr), GELO_OK);
+        HIP_OK(hipDeviceSynchronize());
+        HIP_OK(hipMemcpy(a0.data(), A0, sizeof(float) * a0.size(), hipMemcpyDeviceToHost));
+        HIP_OK(hipMemcpy(a1.data(), A1, sizeof(float) * a1.size(), hipMemcpyDeviceToHost));
+        if (std::memcmp(a0.data(), a1.data(), sizeof(float) * a0.size()) != 0) { std::printf("a batched draw in parts differs from a single one\n"); ++failures; }
+        for (int i = 0; i < count; ++i) EXPECT(gelo_mixing_free(other, many[i]), GELO_OK);
+        EXPECT(gelo_mixing_free(ctx, m), GELO_OK);
+        malloc_most = (size_t)1 << 20;
+        EXPECT(gelo_sample_mixing_batch(other, GELO_ORTHOGONAL, 1000, 0, d, GELO_F32, qid + 100, 2, many, nullptr), GELO_ENOMEM);
+        EXPECT(gelo_sample_mixing(other, GELO_ORTHOGONAL, 20, 2, d, GELO_F32, 0.0, 1, qid + 102, &m, nullptr), GELO_OK);
+        malloc_most = SIZE_MAX;
+        EXPECT(gelo_mixing_free(other, m), GELO_OK);
+        EXPECT(gelo_sample_mixing_batch(other, GELO_ORTHOGONAL, qn, 0, d, GELO_F32, qid + 103, 2, many, nullptr), GELO_OK);
+        for (int i = 0; i < 2; ++i) EXPECT(gelo_mixing_free(other, many[i]), GELO_OK);
+        HIP_OK(hipDeviceSynchronize());
+        EXPECT(gelo_destroy(other), GELO_OK);
+        HIP_OK(hipFree(A0)); HIP_OK(hipFree(A1));
     }
 
     size_t bytes = 0;
