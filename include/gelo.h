@@ -171,7 +171,7 @@ gelo_status gelo_sample_mixing(gelo_ctx* ctx, gelo_kind kind, int n_data, int k_
  *  larger n                up to 32 factorisations share every launch of the Householder QR, each in a workspace of its own (the
  *                          chain of panel factorisations leaves most of the chip idle when one matrix is factorised alone; side
  *                          by side the strips of all of them fill it); fewer where 32 workspaces would exceed 8 GiB (one takes
- *                          0.6 MB at 200 rows, 22 at 720, 119 at 2150, 405 at 4301) or the device does not have the memory.
+ *                          0.8 MB at 200 rows, 22 at 720, 119 at 2150, 405 at 4301) or the device does not have the memory.
  * Object i is what gelo_sample_mixing returns for its batch id, bit for bit.  out: HOST array of `count`
  * pointers; on an argument error nothing is drawn and no id is consumed. */
 gelo_status gelo_sample_mixing_batch(gelo_ctx* ctx, gelo_kind kind, int n_data, int k_shield, int d, gelo_dtype dtype,

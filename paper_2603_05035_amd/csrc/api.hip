@@ -659,7 +659,7 @@ static gelo_status prepare_sampling(gelo_ctx* ctx, gelo_kind kind, int n, gelo_d
     *lanes_out = lanes;
     if (kind == GELO_STRUCTURED) return GELO_OK;
     if (kind == GELO_BLOCK_ORTHOGONAL) return grow(ctx, &ctx->factor_ws, &ctx->factor_ws_bytes, block_workspace_bytes(n));
-    gelo_status st = grow(ctx, &ctx->factor_ws, &ctx->factor_ws_bytes, up256(factor_workspace_bytes(n)) * lanes);
+    gelo_status st = grow(ctx, &ctx->factor_ws, &ctx->factor_ws_bytes, up256(factor_workspace_bytes(n, kind == GELO_REFLECTOR_PRODUCT)) * lanes);
     if (st != GELO_OK || lanes == 1) return st;
     const int64_t ldk = round_up(n, 64);
     const size_t mat32 = up256((size_t)n * ldk * 4), mat16 = dtype == GELO_BF16 ? up256((size_t)n * ldk * 2) : 0;
@@ -683,9 +683,9 @@ gelo_status gelo_sample_mixing(gelo_ctx* ctx, gelo_kind kind, int n_data, int k_
     st = prepare_sampling(ctx, kind, n, dtype, max_attempts, &lanes);     // allocates on first use of a shape only (see gelo_reserve)
     if (st != GELO_OK) return st;
     FactorWorkspace ws = {};
-    const size_t ws_bytes = up256(factor_workspace_bytes(n));
+    const size_t ws_bytes = up256(factor_workspace_bytes(n, kind == GELO_REFLECTOR_PRODUCT));
     if (kind == GELO_BLOCK_ORTHOGONAL) ws.M = (float*)ctx->factor_ws;      // sample_into carves the blocks' workspaces from here
-    else if (kind != GELO_STRUCTURED) factor_workspace_carve(ctx->factor_ws, n, &ws);
+    else if (kind != GELO_STRUCTURED) factor_workspace_carve(ctx->factor_ws, n, &ws, kind == GELO_REFLECTOR_PRODUCT);
     gelo_mixing* m = nullptr;
     st = acquire_mixing(ctx, n_data, k_shield, d, dtype, form_of(kind), &m);
     if (st != GELO_OK) return st;
@@ -902,7 +902,8 @@ gelo_status gelo_sample_mixing_batch(gelo_ctx* ctx, gelo_kind kind, int n_data, 
     const bool blocked = kind == GELO_BLOCK_ORTHOGONAL;
     const bool small = kind == GELO_ORTHOGONAL && n <= kSmallMaxN;
     // larger matrices: up to kQrSideBySide factorisations share every launch, each in a workspace of its own
-    const size_t ws_bytes = up256(factor_workspace_bytes(n));
+    const bool direct = kind == GELO_REFLECTOR_PRODUCT;
+    const size_t ws_bytes = up256(factor_workspace_bytes(n, direct));
     int side = qr_side_by_side(count, ws_bytes);
     gelo_status st = small ? GELO_OK : blocked ? grow(ctx, &ctx->factor_ws, &ctx->factor_ws_bytes, block_workspace_bytes(n) * count) : grow_side_by_side(ctx, ws_bytes, &side);
     if (st != GELO_OK) return st;
@@ -940,11 +941,10 @@ gelo_status gelo_sample_mixing_batch(gelo_ctx* ctx, gelo_kind kind, int n_data, 
     }
     for (int base = 0; st == GELO_OK && !small && !blocked && base < count; base += side) {
         const int c = count - base < side ? count - base : side;
-        const bool direct = kind == GELO_REFLECTOR_PRODUCT;
         const int64_t stride = (int64_t)(ws_bytes / sizeof(float)), ldk = got[base]->ldk;
         const uint64_t id = first_batch_id + (uint64_t)base;
         FactorWorkspace w;
-        factor_workspace_carve(ctx->factor_ws, n, &w);
+        factor_workspace_carve(ctx->factor_ws, n, &w, direct);
         small_targets_layout(got[base], &t);
         for (int i = 0; i < c; ++i) t.block[i] = got[base + i]->block;
         ps.c1 = kStreamMixing << 8; ps.c2 = (uint32_t)id; ps.c3 = (uint32_t)(id >> 32);
@@ -1109,7 +1109,7 @@ gelo_status gelo_qkv_forward_static(gelo_ctx* ctx, gelo_kind kind, gelo_dtype dt
     const bool structured = kind == GELO_STRUCTURED;
     if (n > GELO_STATIC_MAX_N) return fail(ctx, GELO_ESHAPE, "n = %d exceeds GELO_STATIC_MAX_N = %d", n, GELO_STATIC_MAX_N);
     const MixingLayout L = mixing_layout(n_data, k_shield, d, dtype, form_of(kind));
-    const size_t ws_bytes = structured ? 0 : kind == GELO_BLOCK_ORTHOGONAL ? block_workspace_bytes(n) : up256(factor_workspace_bytes(n));
+    const size_t ws_bytes = structured ? 0 : kind == GELO_BLOCK_ORTHOGONAL ? block_workspace_bytes(n) : up256(factor_workspace_bytes(n, kind == GELO_REFLECTOR_PRODUCT));
     if (L.total + ws_bytes > kStaticScratchBytes)
         return fail(ctx, GELO_ESHAPE, "this batch needs %zu bytes of scratch, the static buffer holds %zu (n <= %d, and k_shield * d bounded by it)",
                     L.total + ws_bytes, kStaticScratchBytes, GELO_STATIC_MAX_N);
@@ -1121,7 +1121,7 @@ gelo_status gelo_qkv_forward_static(gelo_ctx* ctx, gelo_kind kind, gelo_dtype dt
     carve_mixing(&local, base, n_data, k_shield, d, dtype, form_of(kind));
     FactorWorkspace ws = {};
     if (kind == GELO_BLOCK_ORTHOGONAL) ws.M = (float*)(base + up256(L.total));      // sample_into carves the blocks' workspaces from here
-    else if (!structured) factor_workspace_carve(base + up256(L.total), n, &ws);
+    else if (!structured) factor_workspace_carve(base + up256(L.total), n, &ws, kind == GELO_REFLECTOR_PRODUCT);
     st = sample_into(ctx, &local, ws, ws_bytes, 1, kind, 1.0, 1, batch_id, s);
     if (st == GELO_OK) batch_commit(ctx, batch_id);
     if (st == GELO_OK) st = mix_launch(ctx, &local, H, d, shield_scale, stat, U, d, s);
@@ -1154,7 +1154,7 @@ gelo_status gelo_reserve(gelo_ctx* ctx, gelo_kind kind, gelo_dtype dtype, int n_
     }
     if (((kind == GELO_ORTHOGONAL && n > kSmallMaxN) || kind == GELO_REFLECTOR_PRODUCT) && mixings > 1) {
         // a batched draw of `mixings` matrices factorises up to kQrSideBySide of them side by side
-        const size_t ws_bytes = up256(factor_workspace_bytes(n));
+        const size_t ws_bytes = up256(factor_workspace_bytes(n, kind == GELO_REFLECTOR_PRODUCT));
         int side = qr_side_by_side(mixings, ws_bytes);
         st = grow_side_by_side(ctx, ws_bytes, &side);
         if (st != GELO_OK) return st;

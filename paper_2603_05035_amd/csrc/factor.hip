@@ -900,19 +900,21 @@ bool wide_rows(int n_pad) { return n_pad >= 720; }
 // 1300 rows 747 / 741, 32 of 2150 rows 6916 / 5860.
 constexpr int kWideProduct = 1280;
 
-size_t factor_workspace_bytes(int n) {
+static bool wide_product(int n_pad, bool direct) { return direct ? n_pad >= kWideProduct : wide_rows(n_pad); }
+
+size_t factor_workspace_bytes(int n, bool direct) {
     const int64_t n_pad = round_up(n, NB), ld = round_up(n, 64);
     const int64_t floats = 3 * n_pad * ld + 2 * n_pad * NB + n_pad * kInvBlock + n_pad + 8 * ld + 256 + 64;
     size_t bytes = (size_t)floats * sizeof(float) + 8192;
-    if (wide_rows((int)n_pad)) {
+    if (wide_product((int)n_pad, direct)) {
         const int64_t nbr = n_pad / NB, blocks = (nbr + kWideTiles - 1) / kWideTiles, area = (int64_t)(kWideTiles * 16) * (kWideTiles * 16);
-        bytes += (size_t)wide_plane_values((int)n_pad) * 2 + (size_t)(nbr * 16 * kWideTiles * 16) * (3 * 2 + kWideChunks * 4) + (size_t)(blocks * area) * (4 + 8)
-               + (size_t)block_panel_values((int)n_pad) * 2 + (size_t)kCoreFloats * 4 + 4096;
+        bytes += (size_t)wide_plane_values((int)n_pad) * 2 + (size_t)(nbr * 16 * kWideTiles * 16) * (3 * 2 + kWideChunks * 4) + (size_t)(blocks * area) * (4 + 8) + 4096;
+        if (!direct) bytes += (size_t)block_panel_values((int)n_pad) * 2 + (size_t)kCoreFloats * 4;
     }
     return bytes;
 }
 
-void factor_workspace_carve(void* base, int n, FactorWorkspace* ws) {
+void factor_workspace_carve(void* base, int n, FactorWorkspace* ws, bool direct) {
     const int64_t n_pad = round_up(n, NB), ld = round_up(n, 64);
     float* p = (float*)base;
     auto take = [&](int64_t count) { float* q = p; p += round_up(count, 64); return q; };
@@ -928,7 +930,7 @@ void factor_workspace_carve(void* base, int n, FactorWorkspace* ws) {
     ws->scalars = take(16);
     ws->flag = (int*)take(16);
     ws->Yp = ws->Yr = ws->Wp = nullptr; ws->panel = nullptr; ws->Wpart = ws->Tbig = ws->core = nullptr; ws->wide_gram = nullptr;
-    if (wide_rows((int)n_pad)) {
+    if (wide_product((int)n_pad, direct)) {
         const int64_t nbr = n_pad / NB, blocks = (nbr + kWideTiles - 1) / kWideTiles, w = nbr * 16 * kWideTiles * 16, area = (int64_t)(kWideTiles * 16) * (kWideTiles * 16);
         p = (float*)(((uintptr_t)p + 1023) & ~(uintptr_t)1023);
         ws->Yp = (uint16_t*)take((wide_plane_values((int)n_pad) + 1) / 2);
@@ -937,8 +939,10 @@ void factor_workspace_carve(void* base, int n, FactorWorkspace* ws) {
         ws->Wpart = take(w * kWideChunks);
         ws->Tbig = take(blocks * area);
         ws->wide_gram = (double*)take(blocks * area * 2);
-        ws->panel = (uint16_t*)take((block_panel_values((int)n_pad) + 1) / 2);
-        ws->core = take(kCoreFloats);
+        if (!direct) {
+            ws->panel = (uint16_t*)take((block_panel_values((int)n_pad) + 1) / 2);
+            ws->core = take(kCoreFloats);
+        }
     }
     ws->n_pad = (int)n_pad;
     ws->ld = ld;
@@ -1091,7 +1095,7 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
         if (last) break;                                      // no panel and no column left
         GELO_TRY(launch_qr_step(a, count, s));
     }
-    if (direct ? n_pad >= kWideProduct : wide_rows(n_pad)) return form_product_wide(ws, count, batch_stride, s);
+    if (wide_product(n_pad, direct)) return form_product_wide(ws, count, batch_stride, s);
     {
         // X = I so far.  Block by block from the last: X[p0:, p0:] <- H_p0 (H_p0+1 (... X[p0:, p0:])), one 16-column
         // strip per workgroup, the block's reflectors newest first, each as I - V T V^T.

@@ -271,12 +271,13 @@ struct FactorWorkspace {
     float* tri;      // its tridiagonal coefficients (2 operators x (alpha, beta) x 32)
     int*   flag;     // R has a zero on its diagonal
     float* scalars;  // [0] kappa estimate, [1] sigma_max, [2] 1 / sigma_min
-    // wide_rows(n_pad) only: products of 256 reflectors at a time (block_reflect.hip)
+    // products of 256 reflectors at a time (block_reflect.hip): from wide_rows on, directly drawn ones from kWideProduct on
     uint16_t* Yp; uint16_t* Yr;      // the reflectors taken apart for either product
     uint16_t* Wp;                    // W' taken apart (n_pad / 16 tile columns)
     float* Wpart;                    // sums of ranges of rows, up to kWideChunks of them
     float* Tbig;                     // per wide block its 256 x 256 triangle
     double* wide_gram;               // per wide block Y^T Y, tiles above the diagonal
+    // the factorisation by blocks (block_factor.hip): from wide_rows on
     uint16_t* panel;                 // the panel of the block being factorised, taken apart
     float* core;                     // the 128 x 128 triangles of that block
     int n_pad; int64_t ld;
@@ -284,7 +285,7 @@ struct FactorWorkspace {
 constexpr int kWideTiles = 16;       // tile columns of a wide block: 256 reflectors
 constexpr int kWideChunks = 8, kWideParts = 4;
 constexpr int kWideCus = 256;
-bool wide_rows(int n_pad);           // are the reflectors of such a matrix applied 256 at a time while Q is formed?
+bool wide_rows(int n_pad);           // is such a matrix factorised by blocks of 128 columns, and its Q formed 256 reflectors at a time?
 int64_t wide_plane_values(int n_pad);        // 16-bit values of Yp and Yr together
 int64_t wide_yr_offset(int n_pad);           // Yr's start behind Yp's
 int64_t block_panel_values(int n_pad);       // 16-bit values of `panel`
@@ -294,8 +295,9 @@ constexpr int kCoreFloats = 3 * 128 * 128;
 hipError_t factor_blocks(const FactorWorkspace& ws, int count, int64_t batch_stride, int* panels_done, hipStream_t stream);
 // ws.X <- H_0 H_1 ... ws.X for the panels' reflectors householder_qr has left in ws.M and ws.Tmat
 hipError_t form_product_wide(const FactorWorkspace& ws, int count, int64_t batch_stride, hipStream_t stream);
-size_t factor_workspace_bytes(int n);
-void factor_workspace_carve(void* base, int n, FactorWorkspace* ws);
+// direct: for the product of directly drawn reflectors alone, which takes less
+size_t factor_workspace_bytes(int n, bool direct = false);
+void factor_workspace_carve(void* base, int n, FactorWorkspace* ws, bool direct = false);
 
 // ws.M holds an n x n matrix in 16 x 16 tiles (qr_tile_index with n_pad / 16 tile rows; what lies
 // beyond n need not be initialised).  On return ws.X holds the orthogonal factor Q of its Householder

@@ -164,6 +164,15 @@ int main() {
         if (std::memcmp(a0.data(), a1.data(), sizeof(float) * a0.size()) != 0) { std::printf("a batched draw in parts differs from a single one\n"); ++failures; }
         for (int i = 0; i < count; ++i) EXPECT(gelo_mixing_free(other, many[i]), GELO_OK);
         EXPECT(gelo_mixing_free(ctx, m), GELO_OK);
+        // a product of 1000 directly drawn reflectors takes no more than its three matrices and a little (13 MB)
+        gelo_ctx* third = nullptr;
+        EXPECT(gelo_create(&third, 0, 0xC0FFEEull, 0), GELO_OK);
+        malloc_most = (size_t)15 << 20;
+        EXPECT(gelo_reserve(third, GELO_REFLECTOR_PRODUCT, GELO_F32, 1000, 0, d, 0, 1, 1), GELO_OK);
+        EXPECT(gelo_sample_mixing(third, GELO_REFLECTOR_PRODUCT, 1000, 0, d, GELO_F32, 0.0, 1, 1, &m, nullptr), GELO_OK);
+        EXPECT(gelo_mixing_free(third, m), GELO_OK);
+        HIP_OK(hipDeviceSynchronize());
+        EXPECT(gelo_destroy(third), GELO_OK);
         malloc_most = (size_t)1 << 20;
         EXPECT(gelo_sample_mixing_batch(other, GELO_ORTHOGONAL, 1000, 0, d, GELO_F32, qid + 100, 2, many, nullptr), GELO_ENOMEM);
         EXPECT(gelo_sample_mixing(other, GELO_ORTHOGONAL, 20, 2, d, GELO_F32, 0.0, 1, qid + 102, &m, nullptr), GELO_OK);
