@@ -91,17 +91,21 @@ __device__ __forceinline__ void core_diagonal(CoreShared& sh, int q, int i, f32x
     }
     float scale_c = 0.f, beta_c = 0.f, ibeta_c = 0.f;
     float gj, pj, gjj, alpha, irn;                        // row j of S and of A at this lane's column; the pivots
+    bool some;
     auto pivot = [&](auto jc) {
         constexpr int j = decltype(jc)::value;
         first_two_rows(col[j], &gj, &pj);
         gjj = row_bcast<j>(gj); alpha = row_bcast<j>(pj);
-        irn = __builtin_amdgcn_rsqf(gjj);                 // hardware reciprocals and root (1 ulp), as in gram_panel_body
+        // hardware reciprocals and root (1 ulp), as in gram_panel_body.  Nothing left of a column (or less, by
+        // rounding): zeros in R, and a reflector that keeps Q orthogonal; no Gaussian panel of 272 rows and more comes near it
+        some = gjj > 0.f;
+        irn = some ? __builtin_amdgcn_rsqf(gjj) : 0.f;
     };
     pivot(std::integral_constant<int, 0>{});
     static_for<NB>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
         const float beta = -copysignf(gjj * irn, alpha), ibeta = -copysignf(irn, alpha);
-        const float scale = __builtin_amdgcn_rcpf(alpha - beta);
+        const float scale = some ? __builtin_amdgcn_rcpf(alpha - beta) : 0.f;
         const float later = g == 0 ? -gj * (irn * irn) : fmaf(gj, ibeta, -pj) * scale;
         // (L_ii^-1 grows column by column without its factor -scale_c)
         float down = g == 2 ? -scale * col[j] : 0.f;

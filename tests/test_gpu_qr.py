@@ -1,6 +1,7 @@
 """The QR kernels at the sizes where they change: A against LAPACK's QR of the oracle's Gaussian (positive diagonal of
 R makes the factor unique).  Bounds: A^T A = I to c sqrt(n) roundings of float in the Frobenius norm, A itself to that
 times the condition number of the Gaussian."""
+import ctypes
 import math
 
 import numpy as np
@@ -71,6 +72,39 @@ def test_blocks_of_128_columns(ctx, n):
     g.gelo_destroy(other)
     assert torch.equal(many[0], pair[0]) and torch.equal(many[1], pair[1]) and torch.equal(many[-1], alone)
     check_orthogonal(alone.double().cpu().numpy(), n, first + count - 1)
+
+
+# The factorisation by itself, through the library's own functions: columns of zeros (no draw has them) at the start, inside and at the end of
+# a block of 128 columns and behind the blocks.  R's diagonal has zeros there, which the kinds that invert R refuse, and Q is orthogonal
+@pytest.mark.parametrize("zeros", [[0], [127], [128, 200], [5, 6, 133, 600], list(range(16)), list(range(120, 140))])
+def test_factorisation_of_columns_of_zeros(zeros):
+    n, lib = 720, g.load_library()
+    size = lib["_ZN4gelo22factor_workspace_bytesEib"]
+    size.restype, size.argtypes = ctypes.c_size_t, [ctypes.c_int, ctypes.c_bool]
+    carve = lib["_ZN4gelo22factor_workspace_carveEPviPNS_15FactorWorkspaceEb"]
+    carve.restype, carve.argtypes = None, [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_bool]
+    qr = lib["_ZN4gelo14householder_qrERKNS_15FactorWorkspaceEiilP12ihipStream_tb"]
+    qr.restype, qr.argtypes = ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_void_p, ctypes.c_bool]
+    memory = torch.zeros(size(n, False) // 4, device="cuda")
+    parts = (ctypes.c_uint64 * 64)()
+    carve(memory.data_ptr(), n, parts, False)
+    tiles = n // 16
+
+    def tiled(i):                                             # the i-th matrix of the workspace, [column of tiles][row][column][row inside]
+        at = (parts[i] - memory.data_ptr()) // 4
+        return memory[at:at + n * n].view(tiles, tiles, 16, 16)
+
+    def dense(t):
+        return t.permute(1, 3, 0, 2).reshape(n, n).double()
+    G = torch.randn((n, n), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    G[:, zeros] = 0.0
+    tiled(0).copy_(G.view(tiles, 16, tiles, 16).permute(2, 0, 3, 1))
+    assert qr(parts, n, 1, 0, torch.cuda.current_stream().cuda_stream, False) == 0
+    torch.cuda.synchronize()
+    Q = dense(tiled(1))
+    assert float((Q.t().contiguous() @ Q - torch.eye(n, dtype=torch.float64, device="cuda")).norm()) / math.sqrt(n) < 20 * EPS * math.sqrt(n) + 1e-7
+    diagonal = memory[(parts[6] - memory.data_ptr()) // 4:][:n]
+    assert bool((diagonal[zeros] == 0).all()) and int((diagonal == 0).sum()) == len(zeros)
 
 
 # A^-1 = R^-1 Q^T by blocks of 128: whole and broken blocks and tiles.  kappa(A) is 2 to 4 here; a backward stable inverse
