@@ -1,5 +1,5 @@
-// Householder QR of a large matrix in blocks of 128 columns (Section 3.2 step 1.2's orthogonal factor): the columns down to the
-// last 256 rows or so; householder_qr's chain of panels takes the rest.  No panel is walked column by column.  With P the block's
+// Householder QR of a large matrix in blocks of 128 columns (Section 3.2 step 1.2's orthogonal factor): the columns until
+// 144 to 256 rows are left; householder_qr's chain of panels takes those.  No panel is walked column by column.  With P the block's
 // m x 128 panel, C the columns behind it, C1 and P1 their first 128 rows,
 //
 //   S  = P^T [P | C]                    launch_panel_products

@@ -904,7 +904,7 @@ static bool wide_product(int n_pad, bool direct) { return direct ? n_pad >= kWid
 
 size_t factor_workspace_bytes(int n, bool direct) {
     const int64_t n_pad = round_up(n, NB), ld = round_up(n, 64);
-    const int64_t floats = 3 * n_pad * ld + 2 * n_pad * NB + n_pad * kInvBlock + n_pad + 8 * ld + 256 + 64;
+    const int64_t floats = 3 * n_pad * ld + 2 * n_pad * NB + n_pad * kInvBlock + n_pad + 6 * ld + 256 + 64;
     size_t bytes = (size_t)floats * sizeof(float) + 8192;
     if (wide_product((int)n_pad, direct)) {
         const int64_t nbr = n_pad / NB, blocks = (nbr + kWideTiles - 1) / kWideTiles, area = (int64_t)(kWideTiles * 16) * (kWideTiles * 16);
@@ -925,7 +925,7 @@ void factor_workspace_carve(void* base, int n, FactorWorkspace* ws, bool direct)
     ws->Rd = take(n_pad * NB);
     ws->Dinv = take(n_pad * kInvBlock);
     ws->rdiag = take(n_pad);
-    ws->vec = take(8 * ld);
+    ws->vec = take(6 * ld);
     ws->tri = take(128);
     ws->scalars = take(16);
     ws->flag = (int*)take(16);

@@ -267,7 +267,7 @@ struct FactorWorkspace {
     float* Rd;       // QR: the 16 x 16 diagonal tiles of R, row-major (its other tiles stay in M, above the reflectors)
     float* Dinv;     // inverses of R's diagonal blocks (pitch kInvBlock, n_pad rows; beyond 128 rows)
     float* rdiag;    // n_pad: diagonal of R
-    float* vec;      // 8 * ld floats: the Lanczos vectors of the condition estimate
+    float* vec;      // 6 * ld floats: the Lanczos vectors of the condition estimate
     float* tri;      // its tridiagonal coefficients (2 operators x (alpha, beta) x 32)
     int*   flag;     // R has a zero on its diagonal
     float* scalars;  // [0] kappa estimate, [1] sigma_max, [2] 1 / sigma_min
@@ -290,7 +290,7 @@ int64_t wide_plane_values(int n_pad);        // 16-bit values of Yp and Yr toget
 int64_t wide_yr_offset(int n_pad);           // Yr's start behind Yp's
 int64_t block_panel_values(int n_pad);       // 16-bit values of `panel`
 constexpr int kCoreFloats = 3 * 128 * 128;
-// Factorises the columns down to the last 256 rows or a few more, 128 at a time: reflectors, R and its diagonal, T as
+// Factorises 128 columns at a time until 144 to 256 rows (9 to 16 tiles) are left: reflectors, R and its diagonal, T as
 // householder_qr's own panels leave them (but no row-major copies); *panels_done panels of 16
 hipError_t factor_blocks(const FactorWorkspace& ws, int count, int64_t batch_stride, int* panels_done, hipStream_t stream);
 // ws.X <- H_0 H_1 ... ws.X for the panels' reflectors householder_qr has left in ws.M and ws.Tmat
@@ -313,8 +313,8 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
 // *ws.flag != 0 if R has a zero on its diagonal.  Overwrites ws.M, ws.Vc and ws.Dinv.
 hipError_t inverse_from_qr(const FactorWorkspace& ws, int n, const float* A, int64_t ldk, float* Ainv32, uint16_t* Ainv16, hipStream_t stream);
 // kappa_2 estimate of the n x n matrix A (lda) with inverse Ainv: sigma_max of both by `steps`
-// (at most 32) Lanczos steps on A^T A and Ainv^T Ainv; uses ws.M / ws.X as scratch for the two
-// transposes; result in ws.scalars[0].
+// (at most 32) Lanczos steps on A^T A and Ainv^T Ainv; uses ws.M / ws.X as scratch for the
+// workgroups' sums of the two products; result in ws.scalars[0].
 hipError_t kappa_estimate(const float* A, const float* Ainv, int64_t lda, int n, const FactorWorkspace& ws,
                           int steps, hipStream_t stream);
 hipError_t set_identity(float* X, int64_t ld, int n_pad, hipStream_t stream);

@@ -369,7 +369,7 @@ __device__ __forceinline__ float block_sum_1024(float v, float* red) {
 
 constexpr int kVecPerThread = kMaxN / 1024;            // 5
 
-// Workgroup o (0: A, 1: A^-1) owns the vectors at vec + o * 4 * ld: v, v_prev, y, w.
+// Workgroup o (0: A, 1: A^-1) owns the vectors at vec + o * 3 * ld: v, v_prev, w = M^T (M v).
 // step < 0: v = a fixed pseudo-random unit vector, v_prev = 0.
 // step >= 0: alpha = w . v, r = w - alpha v - beta_prev v_prev, beta = |r|, v_prev = v, v = r / beta;
 //            tri[o][0][step] = alpha, tri[o][1][step] = beta.
@@ -377,9 +377,9 @@ __global__ __launch_bounds__(1024)
 void lanczos_vector_kernel(float* vec, int64_t ld, int n, float* tri, int step) {
     __shared__ float red[16];
     const int tid = threadIdx.x, o = blockIdx.x;
-    float* v = vec + (int64_t)o * 4 * ld;
+    float* v = vec + (int64_t)o * 3 * ld;
     float* vp = v + ld;
-    const float* w = v + 3 * ld;
+    const float* w = v + 2 * ld;
     float* tr = tri + o * 2 * kLanczosMax;
     float x[kVecPerThread], xp[kVecPerThread], r[kVecPerThread];
     if (step < 0) {
@@ -519,8 +519,8 @@ hipError_t kappa_estimate(const float* A, const float* Ainv, int64_t lda, int n,
     if (steps > n) steps = n;
     const int groups = (n + 3) / 4 < kProductGroups ? (n + 3) / 4 : kProductGroups;
     // the workgroups' sums go to the (now free) factorisation buffers, `groups` rows of each
-    float* va = ws.vec;            float* wa = va + 3 * ld;
-    float* vi = ws.vec + 4 * ld;   float* wi = vi + 3 * ld;
+    float* va = ws.vec;            float* wa = va + 2 * ld;
+    float* vi = ws.vec + 3 * ld;   float* wi = vi + 2 * ld;
     auto product = [&](auto chc) {
         hipLaunchKernelGGL((normal_product_kernel<decltype(chc)::value>), dim3(groups, 2), dim3(256), 0, s, A, va, ws.M, Ainv, vi, ws.X, lda, ld, n);
         return hipGetLastError();
