@@ -41,9 +41,10 @@ def test_one_workgroup_factorisation(ctx, n):
     check_orthogonal(A.double().cpu().numpy(), n, n)
 
 
-# panels built from their Gram matrix down to 64 rows: one and two of them, whole and broken tiles, and where the strips'
-# blocks per wave change (640, 1280, 1920, 2560 and 3840 rows).  One matrix alone applies each reflector to all columns at
-# once, several side by side a block of them in one pass: the same bits
+# panels built from their Gram matrix down to 64 rows: one and two of them, whole and broken tiles, where the strips' blocks per wave
+# change (640 rows), and sizes whose last 144 to 256 rows are left to the panels behind blocks of 128 columns (9 to 16 tile rows: 1280
+# and 1281, 1920 and 1921, 2561, 3841).  One matrix alone applies each reflector to all columns at once, several side by side a block
+# of them in one pass: the same bits
 @pytest.mark.parametrize("n", [129, 143, 144, 145, 160, 161, 191, 192, 640, 641, 1280, 1281, 1920, 1921, 2561, 3841])
 def test_panels_from_gram_matrices(ctx, n):
     first, count = 10 * n, 2
@@ -57,9 +58,9 @@ def test_panels_from_gram_matrices(ctx, n):
     check_orthogonal(alone.double().cpu().numpy(), n, first + 1)
 
 
-# blocks of 128 columns, from 720 rows of tiles on: the first such size, one and several rows and tiles beyond whole blocks, odd
-# numbers of tile rows, the last size before the blocks.  24 matrices take the kernels for many (those with few rows left still the
-# others), one alone and the pair those for few: the same sums in the same order, so the same bits
+# blocks of 128 columns, from 720 rows of tiles on: the last size before them (704), the first such sizes, one and several rows and tiles
+# beyond whole blocks, odd numbers of tile rows.  Q of 24 matrices is formed by the kernels for many, that of one and of two by those for
+# few; the blocks' products take those for few at all of these sizes.  The same sums in the same order, so the same bits
 @pytest.mark.parametrize("n", [704, 705, 720, 721, 769, 784, 896, 897, 1025])
 def test_blocks_of_128_columns(ctx, n):
     first, count = 100 * n, 24
@@ -72,6 +73,27 @@ def test_blocks_of_128_columns(ctx, n):
     g.gelo_destroy(other)
     assert torch.equal(many[0], pair[0]) and torch.equal(many[1], pair[1]) and torch.equal(many[-1], alone)
     check_orthogonal(alone.double().cpu().numpy(), n, first + count - 1)
+
+
+# so many matrices that the blocks' products take the kernels for many as well (tile rows left x matrices / 8 from 256 on): one, two and
+# four blocks of 32 matrices, those behind them by the kernels for few again; ranges of rows summed in three and four parts of two ranges, the
+# last one short, and (3425 rows) in parts of one range
+@pytest.mark.parametrize("n,count", [(897, 32), (1025, 32), (1137, 32), (1281, 32), (3425, 10)])
+def test_blocks_of_128_columns_of_many_matrices(ctx, n, count):
+    first = 100 * n
+    many = [g.gelo_mixing_export(ctx, m, n, 0, 64, want_shields=False)[0] for m in g.gelo_sample_mixing_batch(ctx, g.GELO_ORTHOGONAL, n, 0, 64, g.GELO_F32, first, count)]
+    other = g.gelo_create(0, 0xC0FFEE, allow_batch_reuse=False)
+    for i in (0, 7, 8, count - 1):
+        m = g.gelo_sample_mixing(other, g.GELO_ORTHOGONAL, n, 0, 64, g.GELO_F32, 1e3, 64, batch_id=first + i)
+        alone = g.gelo_mixing_export(other, m, n, 0, 64)[0]
+        torch.cuda.synchronize()
+        g.gelo_mixing_free(other, m)
+        assert torch.equal(many[i], alone)
+    g.gelo_destroy(other)
+    if n < 2000:
+        check_orthogonal(many[5].double().cpu().numpy(), n, first + 5)
+    A = many[6].double()
+    assert float((A.t().contiguous() @ A - torch.eye(n, dtype=torch.float64, device="cuda")).norm()) / math.sqrt(n) < 20 * EPS * math.sqrt(n) + 1e-7
 
 
 # The factorisation by itself, through the library's own functions: columns of zeros (no draw has them) at the start, inside and at the end of
