@@ -23,7 +23,8 @@
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *    Work is enqueued asynchronously on it; argument errors are reported
  *    synchronously and enqueue nothing.
- *  - dtype GELO_F32: H, W, U, Y, Z are float.  GELO_BF16: they are bfloat16
+ *  - dtype GELO_F32: H, W, U, Y, Z are float; the order of a product's sums goes by its size, so a product and the
+ *    same one in parts agree to rounding and not to the bit.  GELO_BF16: they are bfloat16
  *    (upper 16 bits of a float), products accumulate in float, A is generated
  *    in float and rounded once to bfloat16 for the two mixing products.
  *  - All calls return a gelo_status; gelo_last_error() gives a message for the

@@ -16,9 +16,8 @@
 // no worse than A (2 to 4).
 //
 // A draw alone is bound by the chain of these four launches, 8 to 15 + 31.5 + 7 + 5 to 25 us per 128 columns at 2150 rows; panel by
-// panel it was eight launches of 9 to 28.  A whole draw, panels / blocks: 720 rows 582 / 495 us, 1024 rows 892 / 661, 2150 rows
-// 2673 / 1422, 4301 rows 9540 / 4000 (with Q formed as before: 8310 panel by panel); 32 side by side 720 rows 1507 / 1533, 1024 rows
-// 2662 / 2519, 2150 rows 14740 / 10570.  Against 64 bits, panels / blocks (four draws): |A^T A - I| / sqrt(n) at 720, 1040, 2150 rows
+// panel it was eight launches of 9 to 28.  A whole draw, panels / blocks: 720 rows 570 / 461 us, 1024 rows 878 / 634, 2150 rows
+// 2661 / 1417, 4301 rows 9530 / 4020; 32 side by side 720 rows 1489 / 1460, 1024 rows 2642 / 2386, 2150 rows 14730 / 10590.  Against 64 bits, panels / blocks (four draws): |A^T A - I| / sqrt(n) at 720, 1040, 2150 rows
 // 7.5e-7 / 5.3e-7, 8.8e-7 / 5.7e-7, 1.24e-6 / 6.4e-7; part of A^T G below the diagonal, of |G|, 4.34e-7 / 3.79e-7, 5.14e-7 / 3.86e-7,
 // 7.3e-7 / 4.0e-7; distance of A from the exact factor at 1300 and 2150 rows 2.6e-6 / 1.9e-6, 3.4e-6 / 1.6e-6.
 #include "block_reflect.h"

@@ -893,11 +893,14 @@ hipError_t launch_direct_panels(int rows_per_thread, const FactorWorkspace& ws, 
 }  // namespace
 
 // From here on the QR goes by blocks of 128 columns (block_factor.hip) and Q is formed 256 reflectors at a time (block_reflect.hip);
-// below, and for the last 256 columns, panel by panel and by strips.
+// below, and for the last 144 to 256 columns, panel by panel and by strips.  One line for every count, since a matrix drawn alone and the
+// same one drawn among others agree bit for bit.  A whole draw of 720 rows, panels and strips / blocks: alone 570 / 461 us, 8 side by side
+// 838 / 685, 32 of them 1489 / 1460; 8 of 1024 rows 1343 / 1036 (of which forming Q by itself loses, 431 / 473: blocks leave no
+// row-major copies for the strips).
 bool wide_rows(int n_pad) { return n_pad >= 720; }
-// the product of directly drawn reflectors, which has no chain of panels to lose: 256 at a time from here on.  One alone, strips / blocks:
-// 640 rows 145 / 157 us, 1024 rows 240 / 199, 2150 rows 725 / 438, 4301 rows 2840 / 1440; 8 side by side 1024 rows 431 / 473,
-// 1300 rows 747 / 741, 32 of 2150 rows 6916 / 5860.
+// the product of directly drawn reflectors, which has no chain of panels to lose: 256 at a time from here on, again whatever the count.
+// One alone, strips / blocks: 640 rows 145 / 157 us, 1024 rows 240 / 199, 2150 rows 713 / 417, 4301 rows 2790 / 1390; 8 side by side 1024
+// rows 431 / 473, 1300 rows 692 / 681; 32 of 2150 rows 6870 / 5770.
 constexpr int kWideProduct = 1280;
 
 static bool wide_product(int n_pad, bool direct) { return direct ? n_pad >= kWideProduct : wide_rows(n_pad); }

@@ -1,7 +1,8 @@
 // float GEMM on the gfx950 matrix cores, used by the single-precision GELO chain (Section 3.2, eqs. 1-3) and the inverse:
 // C[M x N] = A[M x K] * B[K x N], all row-major, B optionally split into two row segments ([H ; S]); optionally C <- C - A * B.
 // Products of at least one 128 x 128 tile per CU go through the bf16 instructions (gemm_f32_split_kernel), smaller ones
-// through v_mfma_f32_32x32x2_f32 in 64 x 64 tiles.
+// through v_mfma_f32_32x32x2_f32 in 64 x 64 tiles: the sums run in another order there, so a product and its parts need not agree
+// to the last bit.
 // A 128 x 128 tile of gemm_f32_kernel reads all of its operands before it stores, so the product may overwrite B in place with M <= 128
 // (C == B0, K0 == K: the back substitution's multiplications by a diagonal-block inverse, a caller's un-mix into its Y) and A where
 // one tile spans N.  So does a tile of gemm_f32_split_kernel.  Smaller tiles would read what their neighbours have stored: they are not

@@ -4,10 +4,10 @@
 //
 // A^-1 = R^-1 Q^T from the Householder QR of A (factor.hip): no pivot searches and row interchanges, whose chain - two
 // barriers per column, 1.1 us of one workgroup - bounded a row-pivoted LU in this place (512 rows: 1.1 ms of kernels
-// without the condition estimate, here 0.48; 4096 rows: 15.5 ms, here 10.7).  Up to 128 rows everything behind the QR is one
+// without the condition estimate, here 0.48; 4096 rows: 15.5 ms, here 4.9).  Up to 128 rows everything behind the QR is one
 // launch (small_inverse_kernel).  Beyond, Q^T is the right-hand side of a block back substitution with R: the inverses of
 // R's 128 x 128 diagonal blocks come from one launch, everything else is float GEMMs with K = 128.  The QR needs no pivots
-// for its accuracy, whatever A is, except that its panels are built from Gram matrices (gram_panel_body): a panel's
+// for its accuracy, whatever A is, except that its panels are built from Gram matrices (gram_panel_body, block_core_kernel): a panel's
 // condition number is at most A's, times a panel of Gaussians' for the GAUSSIAN kind.
 #include "gelo_internal.h"
 

@@ -61,7 +61,8 @@ def test_bf16_rows_behind_the_last_whole_tile_of_a_mix(width):
         ref, size = left @ right, left.abs() @ right.abs()
         assert bool(((out[1:rows + 1].double() - ref).abs() <= 2.0 ** -8 * 1.01 * ref.abs() + n * 2.0 ** -24 * size).all())
 
-# 64 x 64 tiles up to one round of 128 x 128 ones, the large tiles beyond; broken tiles, and K that fills no step
+# 64 x 64 tiles below one round (256) of 128 x 128 ones, large tiles taken apart into bf16 values from there on (2048 x 40 x 2048 is one
+# round); broken tiles, and K that fills no step
 @pytest.mark.parametrize("m,k,n", [(1, 136, 8), (63, 136, 72), (64, 264, 64), (65, 136, 200), (543, 776, 1544), (1000, 64, 776),
                                    (2048, 40, 2048), (2049, 40, 2048), (2048, 40, 2056), (129, 512, 2304)])
 def test_float_tiles(m, k, n):
