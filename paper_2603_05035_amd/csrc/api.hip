@@ -1156,6 +1156,7 @@ gelo_status gelo_reserve(gelo_ctx* ctx, gelo_kind kind, gelo_dtype dtype, int n_
         // a batched draw of `mixings` matrices factorises up to kQrSideBySide of them side by side
         const size_t ws_bytes = up256(factor_workspace_bytes(n, kind == GELO_REFLECTOR_PRODUCT));
         int side = qr_side_by_side(mixings, ws_bytes);
+        ctx->factor_ws_refused = SIZE_MAX;      // there may be more memory now
         st = grow_side_by_side(ctx, ws_bytes, &side);
         if (st != GELO_OK) return st;
     }

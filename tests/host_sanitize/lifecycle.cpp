@@ -155,6 +155,7 @@ int main() {
         EXPECT(gelo_sample_mixing_batch(other, GELO_ORTHOGONAL, qn, 0, d, GELO_F32, qid, count, many, nullptr), GELO_OK);
         if (refused == 0 || malloc_refused != refused) { std::printf("%d allocations were refused, %d of them behind the reservation\n", malloc_refused, malloc_refused - refused); ++failures; }
         malloc_most = SIZE_MAX;
+        EXPECT(gelo_reserve(other, GELO_ORTHOGONAL, GELO_F32, qn, 0, d, 0, 1, count), GELO_OK);                 // asks for all of it again
         EXPECT(gelo_sample_mixing(ctx, GELO_ORTHOGONAL, qn, 0, d, GELO_F32, 0.0, 1, qid + count - 1, &m, nullptr), GELO_OK);
         EXPECT(gelo_mixing_export(ctx, m, A0, nullptr, nullptr, nullptr, nullptr, nullptr), GELO_OK);
         EXPECT(gelo_mixing_export(other, many[count - 1], A1, nullptr, nullptr, nullptr, nullptr, nullptr), GELO_OK);
