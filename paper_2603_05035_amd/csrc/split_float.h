@@ -17,8 +17,8 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 constexpr int kFrag = 512;                                // bf16 values one v_mfma_f32_16x16x32_bf16 takes of an operand: 64 lanes x 8
 
 struct Split { bf16x8_t h, m, l; };
-// of 2^SHIFT times the values.  With 16 nothing is lost anywhere: the last bit of the smallest float, 2^-149, is a bf16 then, but values
-// from 2^112 on leave the range.
+// of 2^SHIFT times the values.  With 16 nothing is lost anywhere: the last bit of the smallest float, 2^-149, is a bf16 then (a
+// subnormal one, which the instructions take as it is), but values from 2^112 on leave the range.
 template <int SHIFT = 0>
 __device__ __forceinline__ Split split3(f32x4_t a, f32x4_t b) {
     constexpr float scale = 1 << SHIFT;

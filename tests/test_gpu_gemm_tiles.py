@@ -178,9 +178,10 @@ def test_float_tiles_taken_apart_with_infinities():
 
 
 # A value that is not finite changes what it meets and nothing else, to the bit: the results without it elsewhere, in tiles that are computed
-# again for its sake as well.  One value, a column of K, whole K steps, the last k; with operands large enough for a sum to pass 2^96 too
+# again for its sake as well.  One value, a column of K, whole K steps, the last k, more than the 1024 steps that are told apart; with operands
+# large enough for a sum to pass 2^96 too
 @pytest.mark.parametrize("value", [float("inf"), -float("inf"), float("nan")])
-@pytest.mark.parametrize("k,at", [(40, slice(39, 40)), (104, slice(7, 8)), (104, slice(32, 64)), (200, slice(0, 200, 33))])
+@pytest.mark.parametrize("k,at", [(40, slice(39, 40)), (104, slice(7, 8)), (104, slice(32, 64)), (200, slice(0, 200, 33)), (33000, slice(20000, 20001))])
 @pytest.mark.parametrize("scale", [1.0, 2.0 ** 40])
 def test_float_tiles_taken_apart_keep_the_bits_beside_values_not_finite(value, k, at, scale):
     gen = torch.Generator(device="cuda").manual_seed(k)
