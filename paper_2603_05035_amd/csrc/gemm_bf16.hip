@@ -233,23 +233,32 @@ void gemm_bf16_kernel(Bf16Args g) {
 // Fast path: 256 x BN tile (BN = 256 or 192), 8 waves (wave tile 64 x BN/2), K step 64, two LDS
 // stages filled by direct-to-LDS loads (global_load_lds_dwordx4: no staging registers, no
 // ds_write), one barrier per K step.
+//   v_mfma_f32_16x16x32_bf16: under the chip's power limit it runs at 1.97 PFLOP/s with operands that look
+//     like data where v_mfma_f32_32x32x16_bf16 runs at 1.70 (registers only, the same operands).  With the
+//     instruction alone exchanged 2150 x 12288 x 4096 went from 194 to 177 us, 4096 x 12288 x 4096 from 327 to 297.
 //   A rows (128 bytes per stage) keep their 16-byte chunks XOR-swizzled so that the 16-byte
 //     fragment reads of 16 consecutive rows hit distinct banks.
 //   B rows (2 BN bytes, K-major as in memory) are read with ds_read_b64_tr_b16, which hands every
 //     lane the four K-consecutive values of one column: the MFMA operand layout, with no
 //     permutes.  The 16-byte chunks of a row are permuted (XOR for BN = 256, rotation for
-//     BN = 192, see b_chunk_pos) so that the four rows one transposing read touches are spread
-//     over all banks (measured: zero conflicts in the main loop).
+//     BN = 192, see b_chunk_pos) so that the eight rows half a wave's transposing read touches are
+//     spread over all banks.
+//   A K step is four quarters of matrix instructions (half of K, half of the wave's columns).  The reads of
+//     what the next quarter multiplies and the fetches of the next K step stand among them one by one, in
+//     an order the compiler keeps: bursts of either leave the matrix pipe idle.  177 -> 171 and 297 -> 284 us
+//     against the same loop with reads and fetches in front of the quarters; reads in the first half of
+//     a quarter 176 and 292, fetches spread over three quarters 184 and 301, raised wave priority around
+//     a quarter's instructions 177 and 293.  The last quarter runs behind the barrier that ends its step: its
+//     operands are in registers, and the first reads of the next stage are on their way beside it.
 //   The MFMA operands are swapped (B fragment first), so the accumulators hold blocks of C^T and a
 //     lane owns 4 consecutive columns of one row; the epilogue goes through LDS once more so that
 //     the global stores are 16 bytes per lane over whole row segments.
+// What bounds it: in the loop the matrix instructions take 77 % of the time at the rate above; the rest is the
+// meeting of eight waves once per K step beside 64 KB of fetches.
 // Out-of-range rows of A and columns of B are clamped to valid addresses (their products land in
 // outputs that are never stored); rows of B beyond K are fetched from a block of zeros and A is zero
 // in columns [K, round_up(K, 64)) (required by the dispatcher), so the K tail contributes exact zeros
-// whatever the data holds.  Measured on the 2150 x 12288 x 4096 projection against the
-// alternatives that were tried: K step 32 with four stages and prefetch distance 3 (-4 %),
-// per-lane address arithmetic for the fetches (-5 %), v_perm transposition of B in registers
-// with direct stores (-9 %).  BN = 192 exists for the tile count: 2048 x 12288 is 384 tiles of
+// whatever the data holds.  BN = 192 exists for the tile count: 2048 x 12288 is 384 tiles of
 // 256 x 256 (1.5 rounds on 256 CUs, so 2) but 512 of 256 x 192 (exactly 2 rounds of 0.87 the cost).
 namespace dma {
 
@@ -268,17 +277,23 @@ __device__ __forceinline__ void dma16(const void* gptr, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(gptr), "s"(lds_addr) : "memory", "m0");
 }
 
-// position (in 16-byte chunks) of chunk c of B row r inside the row, and its inverse.  BN = 256: rows r .. r + 3
-// of a transposing read differ in bits 1-2 of the 32-byte unit; BN = 192 (row pitch 384 bytes = 1.5 bank rounds):
-// rows r + 2, r + 3 are rotated by 64 bytes, which puts the four 64-byte spans on the four quarters of the banks.
+// the same from a scalar address and a byte offset per lane
+__device__ __forceinline__ void dma16s(uint32_t offset, const void* base, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(offset), "s"(base), "s"(lds_addr) : "memory", "m0");
+}
+
+// position (in 16-byte chunks) of chunk c of B row r inside the row, and its inverse.  Half a wave reads 32 bytes of rows r .. r + 3
+// and r + 8 .. r + 11.  BN = 256: those rows differ in the three bits of the 32-byte unit; BN = 192 (row pitch 384 bytes = 1.5
+// bank rounds): rows r + 2, r + 3 are rotated by 64 bytes, rows from r + 8 on by 32, which puts the eight spans on eight
+// eighths of the banks.
 template <int BN> __device__ __forceinline__ int b_chunk_pos(int r, int c) {
     if (BN == 256) return c ^ ((((r & 3) << 1) | ((r >> 3) & 1)) << 1);
-    const int p = c + 4 * ((r >> 1) & 1);
+    const int p = c + 4 * ((r >> 1) & 1) + 2 * ((r >> 3) & 1);
     return p >= BN / 8 ? p - BN / 8 : p;
 }
 template <int BN> __device__ __forceinline__ int b_chunk_of_pos(int r, int pos) {
     if (BN == 256) return pos ^ ((((r & 3) << 1) | ((r >> 3) & 1)) << 1);
-    const int c = pos - 4 * ((r >> 1) & 1);
+    const int c = pos - 4 * ((r >> 1) & 1) - 2 * ((r >> 3) & 1);
     return c < 0 ? c + BN / 8 : c;
 }
 
@@ -286,20 +301,20 @@ template <int BN> __device__ __forceinline__ int b_chunk_of_pos(int r, int pos) 
 template <int BN, int TM = BM>
 __device__ __forceinline__ void tile_body(const Bf16Args& g, uint8_t* lds, int m0, int n0) {
     constexpr int WN = TM == BM ? 2 : 4;                         // waves side by side
-    constexpr int NCT = BN / 32 / WN;
+    constexpr int NCT = BN / 16 / WN, HALF = NCT / 2;            // tile columns of a wave, taken in two halves
     constexpr int NAD = TM / 64;                                 // A fetches per wave and K step
     constexpr int ROWB = BN * 2;
     constexpr int B_BYTES = BKS * ROWB;
     constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
     constexpr int NBD = B_BYTES / 8192;
     constexpr int CPR = ROWB / 16;
-    constexpr int EPI_PITCH = NCT * 64 + 16;
+    constexpr int EPI_PITCH = NCT * 32 + 16;
     const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)lds);
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
-    const int j = lane & 31, grp = lane >> 5;
+    const int i16 = lane & 15, G = lane >> 4;
     auto uni32 = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
     auto uni64 = [&](int64_t x) {
         const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)x), hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)x >> 32));
@@ -308,165 +323,173 @@ __device__ __forceinline__ void tile_body(const Bf16Args& g, uint8_t* lds, int m
     const int K = uni32(g.K), K0 = uni32(g.K0);
     const int T = (K + BKS - 1) / BKS;
     const int64_t ldb0 = uni64(g.ldb0), ldb1 = uni64(g.ldb1);
+    const uint16_t* Ap = (const uint16_t*)uni64((int64_t)(g.A + (int64_t)m0 * g.lda));
     const uint16_t* B0p = (const uint16_t*)uni64((int64_t)g.B0);
     const uint16_t* B1p = (const uint16_t*)uni64((int64_t)g.B1);
 
-    const uint16_t* a_src[NAD];
-    const uint16_t* b0_src[NBD];
-    const uint16_t* b1_src[NBD];
-    int b_krow[NBD], b_gn[NBD];
+    // What this wave fetches of a stage.  A: byte offsets of its lanes from a scalar address per K step; B: addresses, moved on
+    // step by step.
+    uint32_t a_src[NAD];
+    const uint16_t* b_src[NBD];
 #pragma unroll
     for (int i = 0; i < NAD; ++i) {
-        const int blk = wave * NAD + i;
-        const int row = blk * 8 + (lane >> 3), cp = lane & 7;
-        const int c = cp ^ ((row ^ (row >> 3)) & 7);
-        int grow = m0 + row; grow = grow < g.M ? grow : g.M - 1;
-        a_src[i] = g.A + (int64_t)grow * g.lda + c * 8;
+        const int row = (wave * NAD + i) * 8 + (lane >> 3);
+        const int c = (lane & 7) ^ ((row ^ (row >> 3)) & 7);
+        a_src[i] = (uint32_t)(m0 + row < g.M ? row : g.M - 1 - m0) * (uint32_t)g.lda * 2 + c * 16;
     }
-#pragma unroll
-    for (int i = 0; i < NBD; ++i) {
-        const int e = (wave * NBD + i) * 64 + lane;             // 16-byte unit of the B stage this lane fills
-        const int br = e / CPR, cpos = e - br * CPR;
-        const int bc = b_chunk_of_pos<BN>(br, cpos);
-        int gn = n0 + bc * 8; gn = gn < g.N ? gn : g.N - 8;
-        b_krow[i] = br; b_gn[i] = gn;
-        b0_src[i] = B0p + (int64_t)br * ldb0 + gn;
-        b1_src[i] = B1p + (int64_t)(br - K0) * ldb1 + gn;
-    }
-
-    auto issue = [&](int t) {
+    auto aim = [&](int t) {                                      // b_src of K step t
         const int k0 = t * BKS;
-        const uint32_t st = lds_base + (t & 1) * STAGE_BYTES;
+        if (t > 0 && (k0 + BKS <= K0 || (k0 - BKS >= K0 && k0 + BKS <= K))) {        // on in the segment of step t - 1
+            const int64_t ldb = k0 < K0 ? ldb0 : ldb1;
 #pragma unroll
-        for (int i = 0; i < NAD; ++i) dma16(a_src[i] + k0, st + (wave * NAD + i) * 1024);
-        const uint32_t sb = st + A_BYTES + wave * NBD * 1024;
-        if (k0 + BKS <= K0) {
-            const int64_t off = (int64_t)k0 * ldb0;
+            for (int i = 0; i < NBD; ++i) b_src[i] += BKS * ldb;
+            return;
+        }
 #pragma unroll
-            for (int i = 0; i < NBD; ++i) dma16(b0_src[i] + off, sb + i * 1024);
-        } else if (k0 >= K0 && k0 + BKS <= K) {
-            const int64_t off = (int64_t)k0 * ldb1;
-#pragma unroll
-            for (int i = 0; i < NBD; ++i) dma16(b1_src[i] + off, sb + i * 1024);
-        } else {
-#pragma unroll
-            for (int i = 0; i < NBD; ++i) {
-                int gk = k0 + b_krow[i];
-                const bool beyond = gk >= K;                      // rows past the contraction length read zeros
-                gk = beyond ? K - 1 : gk;
-                const bool first = gk < K0;
-                const uint16_t* base = first ? B0p : B1p;
-                const int64_t off = first ? (int64_t)gk * ldb0 : (int64_t)(gk - K0) * ldb1;
-                dma16(beyond ? (const uint16_t*)g_zero16 : base + off + b_gn[i], sb + i * 1024);
-            }
+        for (int i = 0; i < NBD; ++i) {
+            int e = (wave * NBD + i) * 64 + lane;
+            asm volatile("" : "+v"(e));                           // (rarely here: nothing of this is to be kept across the loop)
+            const int br = e / CPR;                               // the 16-byte unit of B's stage this lane fills
+            const int gn = n0 + b_chunk_of_pos<BN>(br, e - br * CPR) * 8;
+            const int gk = k0 + br < K ? k0 + br : K - 1;
+            const uint16_t* src = (gk < K0 ? B0p + (int64_t)gk * ldb0 : B1p + (int64_t)(gk - K0) * ldb1) + (gn < g.N ? gn : g.N - 8);
+            b_src[i] = k0 + br < K ? src : (const uint16_t*)g_zero16;     // rows past the contraction length read zeros
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
+    constexpr int FETCHES = NAD + NBD;
+    auto fetch = [&](auto ic, int t) {
+        constexpr int i = decltype(ic)::value;
+        const uint32_t st = lds_base + (t & 1) * STAGE_BYTES;
+        if constexpr (i < NAD) dma16s(a_src[i], Ap + t * BKS, st + (wave * NAD + i) * 1024);
+        else dma16(b_src[i - NAD], st + A_BYTES + (wave * NBD + i - NAD) * 1024);
+    };
 
-    const int a_row0 = wm * 64 + j;
-    const int a_sw = (j ^ (j >> 3)) & 7;
-    const uint32_t a_frag_off0 = a_row0 * 128;
-    const int s16 = lane & 15, G = lane >> 4;
-    const int kg = G >> 1, nh = G & 1;
-    const int rl = kg * 8 + (s16 >> 2);                          // row of the first read; later reads add multiples of 4
+    // fragments of v_mfma_f32_16x16x32_bf16: lane (G, i) holds eight consecutive k of row (or column) i, from 8 G on
+    const int a_c0 = G ^ ((i16 ^ (i16 >> 3)) & 7);
+    uint32_t a_off[4];                                           // by (2 ks) ^ mt
+#pragma unroll
+    for (int q = 0; q < 4; ++q) a_off[q] = lds_base + (wm * 64 + i16) * 128 + (a_c0 ^ (2 * q)) * 16;
+    const int rl = G * 8 + (i16 >> 2);                           // row of the first transposing read; the second is 4 below
     uint32_t b_off[NCT];
 #pragma unroll
-    for (int ct = 0; ct < NCT; ++ct) {
-        const int m = wn * (NCT * 2) + ct * 2 + nh;
-        b_off[ct] = A_BYTES + rl * ROWB + b_chunk_pos<BN>(rl, 2 * m) * 16 + (s16 & 3) * 8;
-    }
+    for (int ct = 0; ct < NCT; ++ct)
+        b_off[ct] = lds_base + A_BYTES + rl * ROWB + b_chunk_pos<BN>(rl, 2 * (wn * NCT + ct)) * 16 + (i16 & 3) * 8;
 
-    f32x16_t acc[2][NCT];
+    f32x4_t acc[4][NCT];
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+    for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-        for (int c = 0; c < NCT; ++c)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mt][c][v] = 0.f;
+        for (int c = 0; c < NCT; ++c) acc[mt][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    constexpr bool DEFER = BN == 256;
-    bf16x8_t a_frag[2][2];
-    bf16x8_t b_frag[2][NCT];
-    auto mfma_group = [&](int fb) {
+    bf16x8_t a_frag[2][4];
+    bf16x8_t b_frag[2][HALF];
+    // (the addresses go from stage to stage in place: a sum per read would not fit the registers)
+    auto other_stage = [&](int t) {                              // from stage t to the next one
+        const uint32_t by = t & 1 ? (uint32_t)-STAGE_BYTES : (uint32_t)STAGE_BYTES;
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int q = 0; q < 4; ++q) a_off[q] += by;
 #pragma unroll
-            for (int c = 0; c < NCT; ++c)
-                acc[mt][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b_frag[fb][c], a_frag[fb][mt], acc[mt][c], 0, 0, 0);
+        for (int ct = 0; ct < NCT; ++ct) b_off[ct] += by;
     };
-
-    issue(0);
-    for (int t = 0; t < T; ++t) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    auto load_a = [&](int ks, int mt) {
+        typedef const bf16x8_t __attribute__((address_space(3))) * lds_ptr_t;
+        a_frag[ks][mt] = *(lds_ptr_t)(a_off[(2 * ks) ^ mt] + mt * 16 * 128);
+    };
+    auto load_b = [&](int ks, int half, int c) {
+        typedef s16x4_t __attribute__((address_space(3))) * lds_ptr_t;
+        const uint32_t at = b_off[half * HALF + c] + ks * 32 * ROWB;
+        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(at));
+        const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(at + 4 * ROWB));
+        const s16x8_t both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        b_frag[half][c] = __builtin_bit_cast(bf16x8_t, both);
+    };
+    // A quarter of a K step: the matrix instructions of (ks, half) and, spread among them in this order, `LOADS` reads of what the
+    // next quarter multiplies and the fetches F0 .. F1 of K step t.
+    constexpr int N = 4 * HALF;
+    auto quarter = [&](auto ksc, auto halfc, auto loads, auto&& load, auto f0, auto f1, int t) {
+        constexpr int ks = decltype(ksc)::value, half = decltype(halfc)::value, LOADS = decltype(loads)::value;
+        constexpr int F0 = decltype(f0)::value, FN = decltype(f1)::value - F0;
+        static_for<N>([&](auto ic) {
+            constexpr int i = decltype(ic)::value, c = i / 4, mt = i % 4;
+            static_for<(i + 1) * LOADS / N - i * LOADS / N>([&](auto x) { load(std::integral_constant<int, i * LOADS / N + decltype(x)::value>{}); });
+            static_for<(i + 1) * FN / N - i * FN / N>([&](auto x) { fetch(std::integral_constant<int, F0 + i * FN / N + decltype(x)::value>{}, t); });
+            acc[mt][half * HALF + c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b_frag[half][c], a_frag[ks][mt], acc[mt][half * HALF + c], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    auto load_00 = [&](auto x) {
+        constexpr int i = decltype(x)::value;
+        if constexpr (i < 4) load_a(0, i); else load_b(0, 0, i - 4);
+    };
+    auto load_10 = [&](auto x) {
+        constexpr int i = decltype(x)::value;
+        if constexpr (i < 4) load_a(1, i); else load_b(1, 0, i - 4);
+    };
+    auto load_01 = [&](auto x) { load_b(0, 1, decltype(x)::value); };
+    auto load_11 = [&](auto x) { load_b(1, 1, decltype(x)::value); };
+    const std::integral_constant<int, 0> c0;
+    const std::integral_constant<int, 1> c1;
+    const std::integral_constant<int, HALF> n_b;
+    const std::integral_constant<int, 4 + HALF> n_ab;
+    const std::integral_constant<int, FETCHES / 2> some;
+    const std::integral_constant<int, FETCHES> all;
+    auto meet = [&] {
+        // (lgkmcnt: what is still to be multiplied has left the stage that is refilled behind the barrier)
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
-        // The two waves of a SIMD (w and w + 4) would otherwise both spend the start of the K step issuing
-        // fetches while the matrix pipe idles: with the wide tile the second one issues after its first two
-        // MFMA groups instead (measured +3 %; no gain with the narrow tile).
-        constexpr bool STAGGER = BN == 256;
-        if ((!STAGGER || wave < 4) && t + 1 < T) issue(t + 1);
-        const uint8_t* st = lds + (t & 1) * STAGE_BYTES;
-        auto load_frags = [&](int fb, int ks) {
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
-                a_frag[fb][mt] = *reinterpret_cast<const bf16x8_t*>(st + a_frag_off0 + mt * 32 * 128 + (((ks * 2 + grp) ^ a_sw ^ (mt * 4)) * 16));
-#pragma unroll
-            for (int ct = 0; ct < NCT; ++ct) {
-                typedef s16x4_t __attribute__((address_space(3))) * lds_ptr_t;
-                const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(st + b_off[ct] + ks * 16 * ROWB));
-                const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(st + b_off[ct] + ks * 16 * ROWB + 4 * ROWB));
-                const s16x8_t both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                b_frag[fb][ct] = __builtin_bit_cast(bf16x8_t, both);
-            }
-        };
-        if (DEFER) {
-            // The matrix instructions of a K step's last fragment group wait until the next barrier has been
-            // passed: behind it every wave then has NCT * 2 of them ready in registers while the first fragments
-            // of the new stage are still on their way from LDS (the stage they came from is free to be refilled:
-            // its last fragments were read before the barrier).  Measured +2 ... 9 % with the wide tile, nothing
-            // with the narrow one.
-            load_frags(0, 0);
-            if (t > 0) mfma_group(1);
-            load_frags(1, 1);
-            mfma_group(0);
-            if (STAGGER && wave >= 4 && t + 1 < T) issue(t + 1);
-            load_frags(0, 2);
-            mfma_group(1);
-            load_frags(1, 3);
-            mfma_group(0);
-        } else {
-            load_frags(0, 0);
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const int fb = ks & 1;
-                if (ks + 1 < 4) load_frags(fb ^ 1, ks + 1);
-                mfma_group(fb);
-                if (STAGGER && wave >= 4 && ks == 1 && t + 1 < T) issue(t + 1);
-            }
-        }
+    };
+    aim(0);
+    static_for<FETCHES>([&](auto i) { fetch(i, 0); });
+    meet();
+    if (T > 1) {
+        aim(1);
+        static_for<FETCHES / 2>([&](auto i) { fetch(i, 1); });
     }
-    if (DEFER) mfma_group(1);
+    static_for<4 + HALF>(load_00);
+    // K step t, its last quarter behind the barrier at which step t + 1 has arrived and its own stage is free.  Ahead of it: the
+    // later steps whose fetches there are, 2 or more (all of step t + 1's that are left, the first of t + 2's), 1, 0.
+    auto step = [&](auto ahead, int t) {
+        constexpr int AHEAD = decltype(ahead)::value;
+        if constexpr (AHEAD > 0) quarter(c0, c0, n_b, load_01, some, all, t + 1);
+        else quarter(c0, c0, n_b, load_01, c0, c0, t);
+        quarter(c0, c1, n_ab, load_10, c0, c0, t);
+        quarter(c1, c0, n_b, load_11, c0, c0, t);
+        if constexpr (AHEAD > 0) {
+            if constexpr (AHEAD > 1) aim(t + 2);
+            meet();
+            other_stage(t);
+            if constexpr (AHEAD > 1) quarter(c1, c1, n_ab, load_00, c0, some, t + 2);
+            else quarter(c1, c1, n_ab, load_00, c0, c0, t);
+        } else quarter(c1, c1, c0, [](auto) {}, c0, c0, t);
+    };
+    for (int t = 0; t + 2 < T; ++t) step(std::integral_constant<int, 2>{}, t);
+    if (T > 1) step(c1, T - 2);
+    step(c0, T - 1);
 
     __builtin_amdgcn_s_barrier();
     uint8_t* patch = lds + wave * (32 * EPI_PITCH);
     const int rr = lane >> 4, cc = lane & 15;
-    const int col = n0 + wn * (NCT * 32) + cc * 8;
+    const int col = n0 + wn * (NCT * 16) + cc * 8;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
+    for (int mp = 0; mp < 2; ++mp) {
 #pragma unroll
-        for (int ct = 0; ct < NCT; ++ct)
+        for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int ct = 0; ct < NCT; ++ct) {
+                const f32x4_t v = acc[2 * mp + mt][ct];
                 u32x2_t out;
-                out[0] = pack_bf16x2(acc[mt][ct][4 * q], acc[mt][ct][4 * q + 1]);
-                out[1] = pack_bf16x2(acc[mt][ct][4 * q + 2], acc[mt][ct][4 * q + 3]);
-                *reinterpret_cast<u32x2_t*>(patch + j * EPI_PITCH + (ct * 32 + 8 * q + 4 * grp) * 2) = out;
+                out[0] = pack_bf16x2(v[0], v[1]);
+                out[1] = pack_bf16x2(v[2], v[3]);
+                *reinterpret_cast<u32x2_t*>(patch + (mt * 16 + i16) * EPI_PITCH + (ct * 16 + 4 * G) * 2) = out;
             }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (cc < NCT * 4) {
+        if (cc < NCT * 2) {
 #pragma unroll
             for (int it = 0; it < 8; ++it) {
                 const int r = it * 4 + rr;
                 const u32x4_t v = *reinterpret_cast<const u32x4_t*>(patch + r * EPI_PITCH + cc * 16);
-                const int row = m0 + wm * 64 + mt * 32 + r;
+                const int row = m0 + wm * 64 + mp * 32 + r;
                 if (row < g.M && col < g.N) *reinterpret_cast<u32x4_t*>(g.C + (int64_t)row * g.ldc + col) = v;
             }
         }

@@ -61,6 +61,37 @@ def test_bf16_rows_behind_the_last_whole_tile_of_a_mix(width):
         ref, size = left @ right, left.abs() @ right.abs()
         assert bool(((out[1:rows + 1].double() - ref).abs() <= 2.0 ** -8 * 1.01 * ref.abs() + n * 2.0 ** -24 * size).all())
 
+
+# one, two and three K steps and more (what is fetched ahead ends differently), in both widths of a whole tile
+@pytest.mark.parametrize("m,n", [(300, 520), (2048, 12288)])
+@pytest.mark.parametrize("k", [64, 128, 192, 320])
+def test_bf16_few_steps(m, n, k):
+    check(m, k, n, torch.bfloat16)
+
+
+# B in two segments of different pitch: they meet between two steps, on a step's first and last row; shield rows that fill no step, one
+# step, two
+@pytest.mark.parametrize("n_data,k", [(128, 1), (129, 0), (128, 64), (191, 65), (193, 64), (192, 128), (256, 130), (319, 66)])
+def test_bf16_segments_of_a_mix(n_data, k):
+    n, width = n_data + k, 520
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n_data + k)
+    H = torch.full((n_data, width + 24), float("nan"), device="cuda", dtype=torch.bfloat16)[:, :width]
+    H.copy_(torch.randn((n_data, width), generator=gen, device="cuda"))
+    U = torch.full((n + 2, width), float("nan"), device="cuda", dtype=torch.bfloat16)
+    ctx = g.gelo_create(0, 1)
+    m = g.gelo_sample_mixing(ctx, g.GELO_ORTHOGONAL, n_data, k, width, g.GELO_BF16, batch_id=1)
+    g.gelo_mix(ctx, m, H, U[1:n + 1])
+    A, _, S, _, _ = g.gelo_mixing_export(ctx, m, n, k, width)
+    torch.cuda.synchronize()
+    g.gelo_mixing_free(ctx, m)
+    g.gelo_destroy(ctx)
+    left, right = A.to(torch.bfloat16).double(), torch.cat([H.double(), S.double()]) if k else H.double()
+    ref, size = left @ right, left.abs() @ right.abs()
+    assert torch.isnan(U[0]).all() and torch.isnan(U[-1]).all()
+    assert bool(((U[1:n + 1].double() - ref).abs() <= 2.0 ** -8 * 1.01 * ref.abs() + n * 2.0 ** -24 * size).all())
+
+
 # 64 x 64 tiles below one round (256) of 128 x 128 ones, large tiles taken apart into bf16 values from there on (2048 x 40 x 2048 is one
 # round); broken tiles, and K that fills no step
 @pytest.mark.parametrize("m,k,n", [(1, 136, 8), (63, 136, 72), (64, 264, 64), (65, 136, 200), (543, 776, 1544), (1000, 64, 776),
