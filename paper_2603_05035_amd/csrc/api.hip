@@ -540,8 +540,12 @@ static gelo_status sample_into(gelo_ctx* ctx, gelo_mixing* m, FactorWorkspace ws
         GELO_HIP(ctx, fill_normal(ws.M, ws.n_pad / 16, n, n, ps, 1.0f, 1, s));
         GELO_HIP(ctx, perturb_tiles(ws.M, ws.X, ws.rdiag, ws.n_pad, kConditionedBeta / std::sqrt((float)n), s));
         GELO_HIP(ctx, emit_matrix(ws.M, ws.n_pad / 16, 1, nullptr, n, ldk, m->A32, m->A16, nullptr, nullptr, s));
-        GELO_HIP(ctx, householder_qr(ws, n, 1, 0, s));
-        GELO_HIP(ctx, inverse_from_qr(ws, n, m->A32, ldk, m->Ainv32, m->Ainv16, s));
+        if (n > kInvBlock) {
+            GELO_HIP(ctx, inverse_near_orthogonal(ws, n, m->A32, ldk, m->Ainv32, m->Ainv16, s));
+        } else {
+            GELO_HIP(ctx, householder_qr(ws, n, 1, 0, s));
+            GELO_HIP(ctx, inverse_from_qr(ws, n, m->A32, ldk, m->Ainv32, m->Ainv16, s));
+        }
         GELO_HIP(ctx, kappa_estimate(m->A32, m->Ainv32, ldk, n, ws, kKappaSteps, s));
         GELO_HIP(ctx, hipMemcpyAsync(m->stat + 1, ws.scalars, sizeof(float), hipMemcpyDeviceToDevice, s));
         m->kappa = -1.0f;                                     // stays on the device until someone asks

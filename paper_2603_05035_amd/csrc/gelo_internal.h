@@ -80,6 +80,24 @@ hipError_t gemm_bf16(const GemmOperands& g, hipStream_t stream);
 // or K a multiple of 64) and M <= 256 (one tile row); all share N.  hipErrorInvalidValue otherwise.
 constexpr int kGemmBatchMax = 20;
 hipError_t gemm_bf16_batched(const GemmOperands* g, int count, hipStream_t stream);
+// X + P or X - P with P = A[0] B[0] + A[1] B[1] + ..., in this order, all bf16 of pitch ld; X is x + x_low, the identity, or nothing.
+// Into out (rounded to bf16), out_low (what that rounding leaves, rounded), out32 (float): any may be null.  M rows, N columns (a
+// multiple of 16), contraction K; A readable and zero in columns [K, round_up(K, 64)); no output may share memory with A or B.
+constexpr int kGemmSumMax = 5;
+struct GemmSum {
+    const uint16_t* A[kGemmSumMax];
+    const uint16_t* B[kGemmSumMax];
+    int count = 0;
+    const uint16_t* x = nullptr;
+    const uint16_t* x_low = nullptr;
+    bool identity = false, subtract = false;
+    uint16_t* out = nullptr;
+    uint16_t* out_low = nullptr;
+    float* out32 = nullptr;
+    int64_t ld;
+    int M, N, K;
+};
+hipError_t gemm_bf16_sum(const GemmSum& g, hipStream_t stream);
 hipError_t gemm_f32(const GemmOperands& g, hipStream_t stream);
 hipError_t gemm_bf16_init();        // one-time kernel attribute set-up (large dynamic LDS)
 hipError_t gemm_f32_init();
@@ -312,6 +330,10 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
 // read up to 128 rows only): A^-1 = R^-1 Q^T into Ainv32 and, unless it is null, rounded into Ainv16, laid out like A;
 // *ws.flag != 0 if R has a zero on its diagonal.  Overwrites ws.M, ws.Vc and ws.Dinv.
 hipError_t inverse_from_qr(const FactorWorkspace& ws, int n, const float* A, int64_t ldk, float* Ainv32, uint16_t* Ainv16, hipStream_t stream);
+// A^-1 of A = Q diag(sign rdiag) + E (n > 128 rows of pitch ldk, ldk = round_up(n, 64), zero beyond column n), Q in ws.X and rdiag as
+// householder_qr leaves them, |E| well below 1 (CONDITIONED's: a Gaussian of spectral radius 0.25): into Ainv32 and, unless it is null,
+// rounded into Ainv16, laid out like A.  Overwrites ws.M, ws.X and ws.Vc.
+hipError_t inverse_near_orthogonal(const FactorWorkspace& ws, int n, const float* A, int64_t ldk, float* Ainv32, uint16_t* Ainv16, hipStream_t stream);
 // kappa_2 estimate of the n x n matrix A (lda) with inverse Ainv: sigma_max of both by `steps`
 // (at most 32) Lanczos steps on A^T A and Ainv^T Ainv; uses ws.M / ws.X as scratch for the
 // workgroups' sums of the two products; result in ws.scalars[0].

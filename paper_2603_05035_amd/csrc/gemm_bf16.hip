@@ -287,19 +287,31 @@ __device__ __forceinline__ void dma16s(uint32_t offset, const void* base, uint32
 // bank rounds): rows r + 2, r + 3 are rotated by 64 bytes, rows from r + 8 on by 32, which puts the eight spans on eight
 // eighths of the banks.
 template <int BN> __device__ __forceinline__ int b_chunk_pos(int r, int c) {
-    if (BN == 256) return c ^ ((((r & 3) << 1) | ((r >> 3) & 1)) << 1);
+    if (BN != 192) return c ^ ((((r & 3) << 1) | ((r >> 3) & 1)) << 1);
     const int p = c + 4 * ((r >> 1) & 1) + 2 * ((r >> 3) & 1);
     return p >= BN / 8 ? p - BN / 8 : p;
 }
 template <int BN> __device__ __forceinline__ int b_chunk_of_pos(int r, int pos) {
-    if (BN == 256) return pos ^ ((((r & 3) << 1) | ((r >> 3) & 1)) << 1);
+    if (BN != 192) return pos ^ ((((r & 3) << 1) | ((r >> 3) & 1)) << 1);
     const int c = pos - 4 * ((r >> 1) & 1) - 2 * ((r >> 3) & 1);
     return c < 0 ? c + BN / 8 : c;
 }
 
 // TM = 256 or 128 rows: 4 x 2 waves of 64 x BN / 2, or 2 x 4 of 64 x BN / 4.
-template <int BN, int TM = BM>
-__device__ __forceinline__ void tile_body(const Bf16Args& g, uint8_t* lds, int m0, int n0) {
+// what gemm_bf16_sum_kernel adds to the product: GemmSum's fields
+struct Sum {
+    const uint16_t* A[kGemmSumMax];
+    const uint16_t* B[kGemmSumMax];
+    int count;
+    const uint16_t* x; const uint16_t* x_low;
+    int identity; float sign;
+    uint16_t* out; uint16_t* out_low; float* out32;
+};
+struct NoSum {};
+
+template <int BN, int TM = BM, class More = NoSum>
+__device__ __forceinline__ void tile_body(const Bf16Args& g, uint8_t* lds, int m0, int n0, const More& more = More()) {
+    constexpr bool SUM = std::is_same<More, Sum>::value;
     constexpr int WN = TM == BM ? 2 : 4;                         // waves side by side
     constexpr int NCT = BN / 16 / WN, HALF = NCT / 2;            // tile columns of a wave, taken in two halves
     constexpr int NAD = TM / 64;                                 // A fetches per wave and K step
@@ -321,7 +333,9 @@ __device__ __forceinline__ void tile_body(const Bf16Args& g, uint8_t* lds, int m
         return (int64_t)(((uint64_t)hi << 32) | lo);
     };
     const int K = uni32(g.K), K0 = uni32(g.K0);
-    const int T = (K + BKS - 1) / BKS;
+    const int steps = (K + BKS - 1) / BKS;                       // of a product
+    int T = steps;
+    if constexpr (SUM) T *= uni32(more.count);
     const int64_t ldb0 = uni64(g.ldb0), ldb1 = uni64(g.ldb1);
     const uint16_t* Ap = (const uint16_t*)uni64((int64_t)(g.A + (int64_t)m0 * g.lda));
     const uint16_t* B0p = (const uint16_t*)uni64((int64_t)g.B0);
@@ -337,7 +351,29 @@ __device__ __forceinline__ void tile_body(const Bf16Args& g, uint8_t* lds, int m
         const int c = (lane & 7) ^ ((row ^ (row >> 3)) & 7);
         a_src[i] = (uint32_t)(m0 + row < g.M ? row : g.M - 1 - m0) * (uint32_t)g.lda * 2 + c * 16;
     }
+    const uint16_t* a_now = nullptr;                             // SUM: what a_src counts from
+    int product = 0, in_product = 0;                             // SUM: where K step t lies
     auto aim = [&](int t) {                                      // b_src of K step t
+        if constexpr (SUM) {
+            if (t > 0 && ++in_product == steps) { in_product = 0; ++product; }
+            a_now = (const uint16_t*)uni64((int64_t)(more.A[product] + (int64_t)m0 * g.lda)) + in_product * BKS;
+            if (in_product > 0 && in_product * BKS + BKS <= K) {
+#pragma unroll
+                for (int i = 0; i < NBD; ++i) b_src[i] += BKS * ldb0;
+                return;
+            }
+            const uint16_t* base = (const uint16_t*)uni64((int64_t)more.B[product]);
+#pragma unroll
+            for (int i = 0; i < NBD; ++i) {
+                int e = (wave * NBD + i) * 64 + lane;
+                asm volatile("" : "+v"(e));
+                const int br = e / CPR, gk = in_product * BKS + br;
+                const int gn = n0 + b_chunk_of_pos<BN>(br, e - br * CPR) * 8;
+                b_src[i] = gk < K ? base + (int64_t)gk * ldb0 + (gn < g.N ? gn : g.N - 8) : (const uint16_t*)g_zero16;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            return;
+        }
         const int k0 = t * BKS;
         if (t > 0 && (k0 + BKS <= K0 || (k0 - BKS >= K0 && k0 + BKS <= K))) {        // on in the segment of step t - 1
             const int64_t ldb = k0 < K0 ? ldb0 : ldb1;
@@ -361,7 +397,7 @@ __device__ __forceinline__ void tile_body(const Bf16Args& g, uint8_t* lds, int m
     auto fetch = [&](auto ic, int t) {
         constexpr int i = decltype(ic)::value;
         const uint32_t st = lds_base + (t & 1) * STAGE_BYTES;
-        if constexpr (i < NAD) dma16s(a_src[i], Ap + t * BKS, st + (wave * NAD + i) * 1024);
+        if constexpr (i < NAD) dma16s(a_src[i], SUM ? a_now : Ap + t * BKS, st + (wave * NAD + i) * 1024);
         else dma16(b_src[i - NAD], st + A_BYTES + (wave * NBD + i - NAD) * 1024);
     };
 
@@ -467,6 +503,45 @@ __device__ __forceinline__ void tile_body(const Bf16Args& g, uint8_t* lds, int m
     if (T > 1) step(c1, T - 2);
     step(c0, T - 1);
 
+    if constexpr (SUM) {
+        // A lane has four consecutive columns of a row: X comes and the results go as they are.
+        auto widen = [&](const uint16_t* p, int64_t at) {
+            const u32x2_t h = *reinterpret_cast<const u32x2_t*>(p + at);
+            return f32x4_t{__uint_as_float(h[0] << 16), __uint_as_float(h[0] & 0xffff0000u), __uint_as_float(h[1] << 16), __uint_as_float(h[1] & 0xffff0000u)};
+        };
+        auto narrow = [&](uint16_t* p, int64_t at, f32x4_t v) {
+            *reinterpret_cast<u32x2_t*>(p + at) = u32x2_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+        };
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+            const int row = m0 + wm * 64 + mt * 16 + i16;
+            if (row >= g.M) continue;
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct) {
+                const int col = n0 + (wn * NCT + ct) * 16 + 4 * G;
+                if (col >= g.N) continue;
+                const int64_t at = (int64_t)row * g.ldc + col;
+                f32x4_t x = {0.f, 0.f, 0.f, 0.f};
+                if (more.x != nullptr) {
+                    x = widen(more.x, at);
+                    if (more.x_low != nullptr) x += widen(more.x_low, at);        // exact
+                } else if (more.identity) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[e] = row == col + e ? 1.f : 0.f;
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = fmaf(more.sign, acc[mt][ct][e], x[e]);
+                if (more.out32 != nullptr) *reinterpret_cast<f32x4_t*>(more.out32 + at) = x;
+                if (more.out != nullptr) narrow(more.out, at, x);
+                if (more.out_low != nullptr) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[e] -= (float)(__bf16)x[e];
+                    narrow(more.out_low, at, x);
+                }
+            }
+        }
+        return;
+    }
     __builtin_amdgcn_s_barrier();
     uint8_t* patch = lds + wave * (32 * EPI_PITCH);
     const int rr = lane >> 4, cc = lane & 15;
@@ -554,6 +629,17 @@ void gemm_bf16_dma_batched_kernel(Bf16Batch b) {
     int tm, tn;
     tile_of_block(blockIdx.x, g.tiles_m, g.tiles_n, &tm, &tn);
     tile_body<BN>(g, lds, tm * BM, tn * BN);
+}
+
+// Sums of products (GemmSum): K steps run on from one product into the next, the accumulators stay.  4096 x 4096 x 4096 111 us (1.24
+// PFLOP/s, 256 x 256 tiles), as the plain product.
+template <int BN, int TM>
+__global__ __launch_bounds__(512)
+void gemm_bf16_sum_kernel(Bf16Args g, Sum more) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    int tm, tn;
+    tile_of_block(blockIdx.x, g.tiles_m, g.tiles_n, &tm, &tn);
+    tile_body<BN, TM>(g, lds, tm * TM, tn * BN, more);
 }
 
 }  // namespace dma
@@ -945,6 +1031,14 @@ hipError_t gemm_bf16_init() {
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dma::gemm_bf16_dma_batched_kernel<192>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, dma::lds_bytes<192>());
     if (e != hipSuccess) return e;
+    auto allow_sum = [](auto kernel, int bytes) {
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    };
+    e = allow_sum(&dma::gemm_bf16_sum_kernel<256, 256>, dma::lds_bytes<256>());
+    if (e == hipSuccess) e = allow_sum(&dma::gemm_bf16_sum_kernel<192, 256>, dma::lds_bytes<192>());
+    if (e == hipSuccess) e = allow_sum(&dma::gemm_bf16_sum_kernel<256, 128>, dma::lds_bytes<256>());
+    if (e == hipSuccess) e = allow_sum(&dma::gemm_bf16_sum_kernel<128, 128>, dma::lds_bytes<128>());
+    if (e != hipSuccess) return e;
     e = allow_big_lds<256, 256, 64>();
     if (e != hipSuccess) return e;
     e = allow_skinny_lds<1, 2, false>();
@@ -1081,6 +1175,39 @@ hipError_t gemm_bf16(const GemmOperands& o, hipStream_t stream) {
         }
     }
     return launch<128, 128, 32>(o, stream);
+}
+
+hipError_t gemm_bf16_sum(const GemmSum& o, hipStream_t stream) {
+    if (o.M < 1 || o.N < 16 || o.N % 16 != 0 || o.K < 1 || o.count < 1 || o.count > kGemmSumMax) return hipErrorInvalidValue;
+    Bf16Args a;
+    a.A = o.A[0];  a.lda = o.ld;
+    a.B0 = o.B[0]; a.ldb0 = o.ld; a.K0 = o.K;
+    a.B1 = o.B[0]; a.ldb1 = o.ld;
+    a.C = o.out;   a.ldc = o.ld;
+    a.M = o.M; a.N = o.N; a.K = o.K;
+    dma::Sum more;
+    for (int i = 0; i < kGemmSumMax; ++i) { more.A[i] = o.A[i < o.count ? i : 0]; more.B[i] = o.B[i < o.count ? i : 0]; }
+    more.count = o.count;
+    more.x = o.x; more.x_low = o.x_low; more.identity = o.identity ? 1 : 0; more.sign = o.subtract ? -1.f : 1.f;
+    more.out = o.out; more.out_low = o.out_low; more.out32 = o.out32;
+    auto run = [&](auto bnc, auto tmc) {
+        constexpr int BN = decltype(bnc)::value, TM = decltype(tmc)::value;
+        a.tiles_m = (o.M + TM - 1) / TM; a.tiles_n = (o.N + BN - 1) / BN;
+        hipLaunchKernelGGL((dma::gemm_bf16_sum_kernel<BN, TM>), dim3(a.tiles_m * a.tiles_n), dim3(512), (size_t)dma::lds_bytes<BN>(), stream, a, more);
+        return hipGetLastError();
+    };
+    const std::integral_constant<int, 256> c256;
+    const std::integral_constant<int, 192> c192;
+    const std::integral_constant<int, 128> c128;
+    // The shortest schedule on the chip's 256 CUs.  A CONDITIONED draw (13 such products and what is the same for all) with 256 x 256,
+    // 256 x 192, 128 x 256, 128 x 128 tiles, us: 600 rows 992, 943, 892, 842; 2048 2263, 2166, 2072, 2012 (one round of each); 2150 2463,
+    // 2363, 2274, 2498 (1, 1, 1, 2 rounds); 3000 3654, 3530, 3941, 4108 (1, 1, 2, 3); 4096 5902, 6365, 6133, 6809 (1, 2, 2, 4); 4300 7323, 7050,
+    // 7395, 8064 (2, 2, 3, 5).
+    auto rounds = [&](int tm, int bn) { return (double)(((int64_t)((o.M + tm - 1) / tm) * ((o.N + bn - 1) / bn) + 255) / 256); };
+    const double r256 = rounds(256, 256), r192 = 0.8 * rounds(256, 192), rhalf = 0.6 * rounds(128, 256), rquarter = 0.4 * rounds(128, 128);
+    if (rquarter <= rhalf && rquarter <= r192 && rquarter <= r256) return run(c128, c128);
+    if (rhalf <= r192 && rhalf <= r256) return run(c256, c128);
+    return r192 < r256 ? run(c192, c256) : run(c256, c256);
 }
 
 // One launch for all the products of a block-diagonal mix or unmix.  The tile width is the one with the shorter

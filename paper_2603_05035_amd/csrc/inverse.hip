@@ -2,6 +2,7 @@
 // Mitigation 1: a well-conditioned non-orthogonal A, generated and verified; Section 3.2 eq. 3 needs A^-1 explicitly so
 // that un-mixing is one GEMM).  Everything is float and deterministic: reductions run in a fixed order, no atomics.
 //
+// CONDITIONED beyond 128 rows: Newton's iteration from the orthogonal part's transpose (inverse_near_orthogonal).  Otherwise
 // A^-1 = R^-1 Q^T from the Householder QR of A (factor.hip): no pivot searches and row interchanges, whose chain - two
 // barriers per column, 1.1 us of one workgroup - bounded a row-pivoted LU in this place (512 rows: 1.1 ms of kernels
 // without the condition estimate, here 0.48; 4096 rows: 15.5 ms, here 4.9).  Up to 128 rows everything behind the QR is one
@@ -279,6 +280,27 @@ void small_inverse_kernel(const float* M, const float* Rd, const float* Q, const
     }
 }
 
+// ------------------------------------------------ the inverse of an orthogonal matrix and a perturbation --
+// A taken apart into three bf16 matrices h + m + l (split_float.h), pitch ld like A.  ld / 4 quads per row, zero beyond column n as A is.
+__global__ __launch_bounds__(256)
+void planes_kernel(const float* A, int64_t quads, uint16_t* h, uint16_t* m, uint16_t* l) {
+    typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (q >= quads) return;
+    const f32x4_t x = *reinterpret_cast<const f32x4_t*>(A + 4 * q);
+    bf16x4_t vh, vm, vl;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        vh[e] = (__bf16)x[e];
+        const float r = x[e] - (float)vh[e];
+        vm[e] = (__bf16)r;
+        vl[e] = (__bf16)(r - (float)vm[e]);
+    }
+    *reinterpret_cast<uint2*>(h + 4 * q) = __builtin_bit_cast(uint2, vh);
+    *reinterpret_cast<uint2*>(m + 4 * q) = __builtin_bit_cast(uint2, vm);
+    *reinterpret_cast<uint2*>(l + 4 * q) = __builtin_bit_cast(uint2, vl);
+}
+
 // ------------------------------------------------------------------ Lanczos --
 // sigma_max of a matrix M from a few steps of the Lanczos recurrence on M^T M (no
 // reorthogonalisation: the largest Ritz value converges first and never overshoots).  The two
@@ -510,6 +532,57 @@ hipError_t inverse_from_qr(const FactorWorkspace& ws, int n, const float* A, int
         GELO_TRY(gemm(R + c0, ld, X + (int64_t)c0 * ld, ld, X, ld, c0, n_pad, w, true, s));
     }
     return emit_matrix(X, ld, 0, nullptr, n, ldk, Ainv32, Ainv16, nullptr, nullptr, s);
+}
+
+// Newton's iteration X <- X + X (I - A X) from X = Q^T, whose residual I - A Q^T = -E Q^T has the eigenvalues of a Gaussian of
+// spectral radius 0.25: squared by every step, 2^-4, 2^-8, ... (2-norm 0.5, 0.16, 0.014 measured from 129 to 4096 rows; below 0.65 in
+// all but 1e-10 of the draws at 129 rows, so that the steps cannot diverge).  What a step adds need not be more
+// exact than what the next one removes: the first two steps run on bf16 matrices (the second one's residual is the first one's squared),
+// X's own rounding included; then two corrections from residuals of 16 bits of A, and of all of A and 16 bits of X, each a bf16 product:
+// residuals 5e-3, 2.6e-5, then what the sums of the last one round (Frobenius, of |I|): 1.0e-7 at 129 rows, 1.9e-7 at 1024, 3.8e-7 at 4096,
+// where R^-1 Q^T from a second QR left 4.3e-7, 6.1e-7, 8.8e-7.
+// Bound by the matrix instructions, thirteen products of n^3: 1.25 ms at 4096 rows (1.65 with the last residual as a float
+// product, whose sums also rounded more: 8.2e-7), where the second QR and the back substitution took 4.9.  A whole draw, us: 129 rows 504 -> 404, 512 1073 ->
+// 714, 1024 1680 -> 1068, 2150 3664 -> 2263, 4096 9414 -> 5813.
+hipError_t inverse_near_orthogonal(const FactorWorkspace& ws, int n, const float* A, int64_t ldk, float* Ainv32, uint16_t* Ainv16, hipStream_t s) {
+    const int64_t ld = ws.ld, half = (int64_t)ws.n_pad * ld;
+    if (n <= BW || ldk != ld) return hipErrorInvalidValue;
+    // Al lies where A^-1 will: it is read for the last time by the product before the last
+    uint16_t* Ah = (uint16_t*)ws.Vc;
+    uint16_t* Am = Ah + half;
+    uint16_t* Al = (uint16_t*)Ainv32;
+    uint16_t* m0 = (uint16_t*)ws.M;
+    uint16_t* m1 = m0 + half;
+    uint16_t* m2 = (uint16_t*)ws.X;
+    uint16_t* m3 = m2 + half;
+    GemmSum g;
+    g.ld = ld; g.M = n; g.N = (int)ld; g.K = n;
+    auto product = [&](const uint16_t* L, const uint16_t* R, uint16_t* out) { g.count = 1; g.A[0] = L; g.B[0] = R; g.out = out; return gemm_bf16_sum(g, s); };
+    GELO_TRY(emit_matrix(ws.X, ws.n_pad / NB, 1, ws.rdiag, n, ld, nullptr, nullptr, nullptr, m0, s));    // X0 = Q^T
+    const int64_t quads = (int64_t)n * ld / 4;
+    hipLaunchKernelGGL(planes_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, A, quads, Ah, Am, Al);
+    GELO_TRY(hipGetLastError());
+    g.identity = g.subtract = true;
+    GELO_TRY(product(Ah, m0, m2));                        // R0 = I - A X0
+    g.identity = g.subtract = false;
+    GELO_TRY(product(m2, m2, m1));                        // R1 = R0^2 = I - A X1
+    g.x = m0;
+    GELO_TRY(product(m0, m2, m3));                        // X1 = X0 + X0 R0
+    g.x = m3;
+    GELO_TRY(product(m3, m1, m0));                        // X2 = X1 + X1 R1
+    g.x = nullptr; g.identity = g.subtract = true;
+    g.A[1] = Ah; g.B[1] = m0;
+    g.count = 2; g.A[0] = Am; g.B[0] = m0; g.out = m2;
+    GELO_TRY(gemm_bf16_sum(g, s));                        // R2 = I - A X2
+    g.x = m0; g.identity = g.subtract = false; g.out_low = m1;
+    GELO_TRY(product(m0, m2, m3));                        // X3 = X2 + X2 R2
+    const uint16_t* left[kGemmSumMax] = {Al, Am, Am, Ah, Ah};
+    const uint16_t* right[kGemmSumMax] = {m3, m1, m3, m1, m3};
+    for (int i = 0; i < kGemmSumMax; ++i) { g.A[i] = left[i]; g.B[i] = right[i]; }
+    g.x = nullptr; g.identity = g.subtract = true; g.count = kGemmSumMax; g.out = m2; g.out_low = nullptr;
+    GELO_TRY(gemm_bf16_sum(g, s));                        // R3 = I - A X3, the small products first
+    g.x = m3; g.x_low = m1; g.identity = g.subtract = false; g.out32 = Ainv32;
+    return product(m3, m2, Ainv16);                       // A^-1 = X3 + X3 R3
 }
 
 hipError_t kappa_estimate(const float* A, const float* Ainv, int64_t lda, int n, const FactorWorkspace& ws,

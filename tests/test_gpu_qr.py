@@ -145,6 +145,21 @@ def test_inverse_of_a_conditioned_matrix(ctx, n):
         assert abs(kappa - exact) < 0.02 * exact
 
 
+# CONDITIONED beyond 128 rows (Newton's iteration on bf16 products): rows that fill no K step and no tile, the four tiles (128 x 128, 128 x 256,
+# 256 x 192, 256 x 256), each in one round and more, both pitches beyond n.  In the last product a result takes ceil(n / 32) sums of
+# what is at most 1 behind smaller ones, each rounded once; A^-1 is rounded itself.
+@pytest.mark.parametrize("n,dtype", [(n, g.GELO_F32) for n in (129, 191, 192, 193, 1000, 2048, 2049, 2150, 2817, 3009, 3500, 4097)]
+                         + [(n, g.GELO_BF16) for n in (129, 193, 2150)])
+def test_inverse_near_an_orthogonal_matrix(ctx, n, dtype):
+    m = g.gelo_sample_mixing(ctx, g.GELO_CONDITIONED, n, 0, 64, dtype, 1e3, 64, batch_id=10000 + 2 * n + (dtype == g.GELO_BF16))
+    A, A_inv, _, _, _ = g.gelo_mixing_export(ctx, m, n, 0, 64)
+    torch.cuda.synchronize()
+    g.gelo_mixing_free(ctx, m)
+    A, A_inv, eye = A.double(), A_inv.double(), torch.eye(n, dtype=torch.float64, device="cuda")
+    for product in (A @ A_inv, A_inv @ A):
+        assert float((product - eye).norm()) / math.sqrt(n) < (n / 32 + 8) * EPS
+
+
 # the condition estimate where its rows' registers change: rows of less than 256 columns, one to twenty blocks of them, whole and broken
 @pytest.mark.parametrize("n", [8, 64, 65, 129, 192, 193, 256, 257, 512, 513, 1025, 2049, 3073, 4097])
 def test_condition_estimate(ctx, n):
