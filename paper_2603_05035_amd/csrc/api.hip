@@ -425,11 +425,12 @@ static BlockPiece block_piece(int n_data, int k, int i) {
     b.data0 = r0 - s0; b.data_rows = b.rows - b.shield_rows;
     return b;
 }
-// factorisation workspaces of the blocks, one behind the other: the full blocks first (they share their launches), then the
-// last one if it is too large for the one-workgroup factorisation, which needs none (draw_blocks)
+// Blocks that share the launches of one batched factorisation (draw_blocks): the full ones, and the last one unless the
+// one-workgroup factorisation takes it.
+static int blocks_side_by_side(int n) { return n / GELO_BLOCK_ROWS + (n % GELO_BLOCK_ROWS > kSmallMaxN ? 1 : 0); }
+// their workspaces, one behind the other
 static size_t block_workspace_bytes(int n) {
-    const int full = n / GELO_BLOCK_ROWS, rest = n % GELO_BLOCK_ROWS;
-    return (size_t)full * up256(factor_workspace_bytes(GELO_BLOCK_ROWS)) + (rest > kSmallMaxN ? up256(factor_workspace_bytes(rest)) : 0);
+    return (size_t)blocks_side_by_side(n) * up256(factor_workspace_bytes(n < GELO_BLOCK_ROWS ? n : GELO_BLOCK_ROWS));
 }
 
 // Argument checks shared by the sampling entry points; on success *n_out = n_data + k_shield.
@@ -458,29 +459,27 @@ static gelo_status check_sample_args(gelo_ctx* ctx, gelo_kind kind, int n_data, 
 }
 
 // The blocks of `count` BLOCK_ORTHOGONAL objects (targets t, batch ids from `first` on; base: their factorisation workspaces,
-// object-major, the full blocks first): the full blocks share the launches of one batched factorisation, the last, shorter
-// ones those of a second one - or, up to kSmallMaxN rows, one launch of the one-workgroup factorisation (102 rows: 45 us
-// against 100 for the blocked one's launches).
+// object-major).  The full blocks share the launches of one batched factorisation.  A last, shorter one of more than kSmallMaxN rows takes
+// part in it as the end of a full-size matrix that begins with the identity; its panels start when the others' have as many rows
+// left.  With a chain of launches of its own behind the others', 1 and 32 draws: 129 rows (641 in all) 368 and 743 us, now 255 and
+// 658; 255 rows (767) 438 and 833, now 254 and 678.  Up to kSmallMaxN rows: one launch of the one-workgroup factorisation, 10 to 60 us and a
+// little more exact (102 rows beside eight blocks, as the end of a ninth: 308 -> 262 us, 32 draws 1026 -> 1058, |A^T A - I| 3.7e-7 -> 4.0e-7).
 static hipError_t draw_blocks(const SmallSampleTargets& t, int count, uint64_t first, PhiloxStream ps, int n, int d, int64_t ldk, char* base,
                               hipStream_t s) {
     constexpr int B = GELO_BLOCK_ROWS;
-    const int full = n / B, rest = n % B;
-    const size_t wb = up256(factor_workspace_bytes(B));
-    ps.c2 = (uint32_t)first; ps.c3 = (uint32_t)(first >> 32);
-    auto draw = [&](char* at, size_t ws_bytes, int rows, int per_object, int first_block) -> hipError_t {
+    const int full = n / B, rest = n % B, side = blocks_side_by_side(n);
+    ps.c1 = kStreamBlock << 8; ps.c2 = (uint32_t)first; ps.c3 = (uint32_t)(first >> 32);
+    if (side > 0) {
+        const int rows = n < B ? n : B, tail = full > 0 && side > full ? rest : 0;
         FactorWorkspace w;
-        factor_workspace_carve(at, rows, &w);
-        const int64_t stride = (int64_t)(ws_bytes / sizeof(float));
-        ps.c1 = (kStreamBlock << 8) | (uint32_t)first_block;
-        hipError_t e = fill_normal_batched(w.M, stride, w.n_pad / 16, rows, rows, ps, per_object, per_object * count, false, s);
-        if (e == hipSuccess) e = householder_qr(w, rows, per_object * count, stride, s);
-        if (e == hipSuccess)
-            e = emit_batched(w.X, w.rdiag, stride, w.n_pad / 16, rows, ldk, t, count, per_object, (int64_t)first_block * B * ldk, (int64_t)B * ldk, s);
-        return e;
-    };
-    hipError_t e = full > 0 ? draw(base, wb, B, full, 0) : hipSuccess;
-    if (e != hipSuccess || rest == 0) return e;
-    if (rest > kSmallMaxN) return draw(base + wb * (size_t)full * count, up256(factor_workspace_bytes(rest)), rest, 1, full);
+        factor_workspace_carve(base, rows, &w);
+        const int64_t stride = (int64_t)(up256(factor_workspace_bytes(rows)) / sizeof(float));
+        hipError_t e = fill_normal_batched(w.M, stride, w.n_pad / 16, rows, rows, ps, side, side * count, false, s, tail);
+        if (e == hipSuccess) e = householder_qr_tails(w, rows, side * count, stride, s, false, side, tail);
+        if (e == hipSuccess) e = emit_batched(w.X, w.rdiag, stride, w.n_pad / 16, rows, ldk, t, count, side, 0, (int64_t)B * ldk, s, tail);
+        if (e != hipSuccess) return e;
+    }
+    if (rest == 0 || rest > kSmallMaxN) return hipSuccess;
     SmallSampleTargets r = t;
     const int64_t at = (int64_t)full * B * ldk;
     r.off_A32 += 4 * at; r.off_Ainv32 += 4 * at;

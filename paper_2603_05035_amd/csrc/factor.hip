@@ -556,6 +556,7 @@ struct QrBulkArgs {
     Reflector refl[kMaxProduct]; int pending;
     float* Cout; float* X; int outer, acc;
     int64_t strip_stride; int nb_block; int64_t batch_stride; int count;
+    int per_object, skip_tail;           // skip_tail: the last of every per_object matrices has nothing here
 };
 // A strip fits the 128 registers of two workgroups per CU.
 template <int NBLK>
@@ -563,6 +564,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void qr_bulk_kernel(QrBulkArgs a) {
     int matrix, b;
     if (!deal_to_dies(blockIdx.x, a.outer + a.acc, a.count, &matrix, &b)) return;
+    if (a.skip_tail && matrix % a.per_object == a.per_object - 1) return;
     const int64_t off = (int64_t)matrix * a.batch_stride;
     float* Cs = b < a.outer ? a.Cout + (int64_t)b * a.strip_stride : a.X + (int64_t)(b - a.outer) * a.strip_stride;
     reflect_strip_lds_body<NBLK>(a.refl, a.pending, off, Cs + off, a.nb_block);
@@ -810,6 +812,7 @@ struct QrStepArgs {
     float* Vr_next; float* Vt_next; float* Tnext; float* Rd_next; float* rdiag_next;   // outputs of panel p + 1
     int m_next;                          // its row count (0: no further panel)
     int64_t batch_stride;                // floats from one matrix's workspace to the next one's (grid y = matrix)
+    int per_object, skip_tail;           // skip_tail: the last of every per_object matrices has nothing here
 };
 
 template <int NBLK>
@@ -817,6 +820,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBLK >= 10 
 void qr_step_kernel(QrStepArgs a) {
     __shared__ StripShared strip;
     const int b = blockIdx.x;
+    if (a.skip_tail && (int)blockIdx.y % a.per_object == a.per_object - 1) return;
     const int64_t off = (int64_t)blockIdx.y * a.batch_stride;
     if (b == 0) {
         if (a.m_next <= 0) return;
@@ -1028,13 +1032,21 @@ hipError_t launch_qr_step(const QrStepArgs& a, int count, hipStream_t s) {
 }  // namespace
 
 hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t batch_stride, hipStream_t s, bool direct) {
+    return householder_qr_tails(ws, n, count, batch_stride, s, direct, 1, 0);
+}
+
+hipError_t householder_qr_tails(const FactorWorkspace& ws, int n, int count, int64_t batch_stride, hipStream_t s, bool direct, int per_object, int tail_rows) {
     if (count < 1 || count > 65535) return hipErrorInvalidValue;
     const int n_pad = ws.n_pad;
+    if (tail_rows != 0 && (direct || n != n_pad || wide_product(n_pad, false) || tail_rows < 0 || tail_rows > n || per_object < 1 || count % per_object != 0)) return hipErrorInvalidValue;
     const int nbr = n_pad / NB;                               // tile rows (= tile columns)
     const int64_t strip_stride = (int64_t)nbr * 256;
     const int panels = nbr;
     // panels per block
     const int D = ws.ld >= 64 * kMaxDelay ? kMaxDelay : (ws.ld >= 128 ? 2 : 1);
+    // The tail matrices begin with the block of panels that holds their first column; what is before it is the identity, and its
+    // reflectors would meet rows where the columns behind them are zero.
+    const int tail_start = tail_rows > 0 ? tail_offset(nbr, tail_rows) / NB / D * D : 0;
     // Every panel's reflector block is kept until the end: the row-major copies side by side in ws.Vc (n_pad x 16 each,
     // n_pad x n_pad in all), the tiled copies IN PLACE of the panels they came from (a factored panel is dead: nobody
     // reads those columns of M again, and the panel kernel has all its rows in registers before it writes).
@@ -1061,6 +1073,12 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
         if (wide_rows(n_pad)) GELO_TRY(factor_blocks(ws, count, batch_stride, &start, s));
         GELO_TRY(launch_first_panel(Vt_of(start), Vr_of(start), Vt_of(start), ws.Tmat + (int64_t)start * NB * NB, ws.Rd + (int64_t)start * NB * NB, ws.rdiag + start * NB,
                                     n_pad - start * NB, count, batch_stride, s));
+        if (tail_start > 0) {
+            const int64_t first = (int64_t)(per_object - 1) * batch_stride;
+            GELO_TRY(launch_first_panel(Vt_of(tail_start) + first, Vr_of(tail_start) + first, Vt_of(tail_start) + first, ws.Tmat + (int64_t)tail_start * NB * NB + first,
+                                        ws.Rd + (int64_t)tail_start * NB * NB + first, ws.rdiag + tail_start * NB + first, n_pad - tail_start * NB,
+                                        count / per_object, per_object * batch_stride, s));
+        }
     }
     for (int p = start; p < panels && !direct; ++p) {
         const int p0 = p / D * D;                             // first panel of p's block
@@ -1087,12 +1105,14 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
         a.Tnext = ws.Tmat + (int64_t)(p + 1) * NB * NB; a.Rd_next = ws.Rd + (int64_t)(p + 1) * NB * NB; a.rdiag_next = ws.rdiag + (p + 1) * NB;
         a.m_next = last ? 0 : n_pad - (p + 1) * NB;
         a.batch_stride = batch_stride;
+        a.per_object = per_object; a.skip_tail = p < tail_start;
         if (delayed && block_done && from < nbr) {
             QrBulkArgs b;
             b.pending = p - p0 + 1;
             for (int q = 0; q < kMaxProduct; ++q) { const int i = q < b.pending ? q : 0; b.refl[q] = reflector(p0 + i, i); }
             b.Cout = behind; b.X = behind; b.outer = nbr - from; b.acc = 0;
             b.strip_stride = strip_stride; b.nb_block = a.nb_block; b.batch_stride = batch_stride; b.count = count;
+            b.per_object = per_object; b.skip_tail = a.skip_tail;
             GELO_TRY(launch_qr_bulk(b, count, s));
         }
         if (last) break;                                      // no panel and no column left
@@ -1116,6 +1136,7 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
             b.pending = pend; b.Cout = ws.X; b.X = ws.X + (int64_t)p0 * strip_stride + (int64_t)p0 * 256;
             b.outer = 0; b.acc = nbr - p0;
             b.strip_stride = strip_stride; b.nb_block = nbr - p0; b.batch_stride = batch_stride; b.count = count;
+            b.per_object = per_object; b.skip_tail = pend + p0 <= tail_start;
             GELO_TRY(launch_qr_bulk(b, count, s));
         }
     }

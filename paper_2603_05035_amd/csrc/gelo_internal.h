@@ -229,13 +229,17 @@ struct SmallSampleTargets {
 };
 // The pieces of a batched draw, one launch each for all its matrices (one at a time they cost a launch's 4 us each, 2150 rows
 // 13 - 15).  Matrix z belongs to object z / per_batch, whose batch id is z / per_batch after ps.c3:c2.
-// fill: matrix z at out + z out_stride, tiled like fill_normal's, stream word ps.c1 + z % per_batch
+// fill: matrix z at out + z out_stride, tiled like fill_normal's, stream word ps.c1 + z % per_batch.  tail_rows > 0: the last of every
+// per_batch matrices is a Gaussian of tail_rows rows and columns that starts at tail_offset(tile_rows, tail_rows), with the identity before it
+// and zeros behind it (square matrices of at most 256 rows)
 hipError_t fill_normal_batched(float* out, int64_t out_stride, int tile_rows, int rows, int cols, PhiloxStream ps, int per_batch, int count,
-                               bool lower_only, hipStream_t stream);
+                               bool lower_only, hipStream_t stream, int tail_rows = 0);
+__host__ __device__ inline int tail_offset(int tile_rows, int tail_rows) { return 16 * (tile_rows - (tail_rows + 15) / 16); }
 // emit: matrix z (tiles at src + z src_stride, column signs at rdiag + z src_stride) and its transpose into A32, Ainv32 (A16,
-// Ainv16) of its object, dst_first + (z % per_batch) dst_stride elements behind their start; `count` objects
+// Ainv16) of its object, dst_first + (z % per_batch) dst_stride elements behind their start; `count` objects; tail_rows as above: that part
+// of the last matrix alone
 hipError_t emit_batched(const float* src, const float* rdiag, int64_t src_stride, int tile_rows, int n, int64_t ldd, const SmallSampleTargets& t,
-                        int count, int per_batch, int64_t dst_first, int64_t dst_stride, hipStream_t stream);
+                        int count, int per_batch, int64_t dst_first, int64_t dst_stride, hipStream_t stream, int tail_rows = 0);
 hipError_t shield_directions_batched(const SmallSampleTargets& t, int count, int k, int d, PhiloxStream ps, hipStream_t stream);
 // For item i < count: batch id = first_batch + i; A = Q diag(sign r_ii) of the Householder QR of its n x n Philox
 // Gaussian (stream c1 of ps; ps.c2 / ps.c3 are ignored), written with its transpose (float, and bf16 if wanted;
@@ -326,6 +330,10 @@ void factor_workspace_carve(void* base, int n, FactorWorkspace* ws, bool direct 
 // stands (rows k onward), so ws.X becomes the product H_0 H_1 ... H_{n-1} of directly drawn reflectors and
 // ws.rdiag the values beta_k those reflectors map their columns to; no chain of dependent panels.
 hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t batch_stride, hipStream_t stream, bool direct = false);
+// The same where, with `tail_rows` > 0 (not `direct`, n a multiple of 16 below the blocks' sizes), of every `per_object` matrices the last is
+// the identity up to tail_offset(n / 16, tail_rows): only what is behind it is factorised, beside the others.
+hipError_t householder_qr_tails(const FactorWorkspace& ws, int n, int count, int64_t batch_stride, hipStream_t stream, bool direct,
+                                int per_object, int tail_rows);
 // Behind householder_qr(ws, n, 1, ..., direct = false) of the matrix A (n rows of pitch ldk, ldk % 64 == 0, zero beyond column n;
 // read up to 128 rows only): A^-1 = R^-1 Q^T into Ainv32 and, unless it is null, rounded into Ainv16, laid out like A;
 // *ws.flag != 0 if R has a zero on its diagonal.  Overwrites ws.M, ws.Vc and ws.Dinv.

@@ -33,9 +33,11 @@ void fill_normal_kernel(float* out, int64_t ld, int rows, int cols, PhiloxStream
 // row than the segment holds when its ends fall inside blocks), sets the values down in LDS and writes the 16
 // tiles out as they lie in memory, 16 bytes per lane.
 __global__ __launch_bounds__(256)
-void fill_normal_tiled_kernel(float* out, int64_t out_stride, int per_batch, int tile_rows, int rows, int cols, PhiloxStream ps, float scale, int lower_only) {
+void fill_normal_tiled_kernel(float* out, int64_t out_stride, int per_batch, int tile_rows, int rows, int cols, PhiloxStream ps, float scale, int lower_only,
+                              int tail_rows) {
     constexpr int CW = 256, PITCH = CW + 1, PER_ROW = CW / 4 + 1;
     __shared__ float tile[16 * PITCH];
+    const bool tail = tail_rows > 0 && (int)blockIdx.z % per_batch == per_batch - 1;
     {   // matrix z of the launch: the per_batch matrices of batch id c3:c2, of the id after it, ...
         const int item = blockIdx.z / per_batch;
         const uint64_t id = (((uint64_t)ps.c3 << 32) | ps.c2) + (uint64_t)item;
@@ -45,11 +47,22 @@ void fill_normal_tiled_kernel(float* out, int64_t out_stride, int per_batch, int
     const int tid = threadIdx.x;
     const int r0 = blockIdx.y * 16, c0 = blockIdx.x * CW;
     if (lower_only && c0 >= r0 + 16) return;                 // every column of this piece lies to the right of every row's diagonal entry
+    const int write_rows = rows, write_width = min(CW, cols - c0);
+    int row_shift = 0, col_shift = 0;                        // where the Gaussian starts
+    if (tail) {                                              // (one piece across: c0 = 0)
+        row_shift = col_shift = tail_offset(tile_rows, tail_rows);
+        for (int i = tid; i < 16 * CW; i += 256) {
+            const int ri = i / CW, c = i - ri * CW;
+            tile[ri * PITCH + c] = r0 + ri == c && c < col_shift ? 1.f : 0.f;
+        }
+        rows = cols = tail_rows;
+        __syncthreads();
+    }
     const int width = min(CW, cols - c0);
     for (int idx = tid; idx < 16 * PER_ROW; idx += 256) {
         const int ri = idx / PER_ROW, bi = idx - ri * PER_ROW;
-        const int r = r0 + ri;
-        if (r >= rows) break;
+        const int r = r0 + ri - row_shift;
+        if (r < 0 || r >= rows) break;                       // (row_shift is a multiple of 16)
         const uint32_t e_first = (uint32_t)r * (uint32_t)cols + (uint32_t)c0, e_last = e_first + (uint32_t)width - 1u;
         const uint32_t b = e_first / 4u + (uint32_t)bi;
         if (4u * b > e_last) continue;
@@ -61,22 +74,22 @@ void fill_normal_tiled_kernel(float* out, int64_t out_stride, int per_batch, int
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const uint32_t e = 4u * b + (uint32_t)t;
-            if (e >= e_first && e <= e_last) tile[ri * PITCH + (int)(e - e_first)] = scale * z[t];
+            if (e >= e_first && e <= e_last) tile[ri * PITCH + col_shift + (int)(e - e_first)] = scale * z[t];
         }
     }
     __syncthreads();
     // float4 item: rows 4 g .. 4 g + 3 of column c of the strip (16 bytes of a tile: index (c & 15) * 16 + 4 g)
     for (int it = tid; it < CW * 4; it += 256) {
         const int c = it >> 2, g = it & 3;
-        if (c >= width) continue;
+        if (c >= write_width) continue;
         float* dst = out + qr_tile_index(r0 + 4 * g, c0 + c, tile_rows);
         const float* src = tile + (4 * g) * PITCH + c;
-        if (r0 + 4 * g + 3 < rows) {
+        if (r0 + 4 * g + 3 < write_rows) {
             *reinterpret_cast<float4*>(dst) = make_float4(src[0], src[PITCH], src[2 * PITCH], src[3 * PITCH]);
         } else {
 #pragma unroll
             for (int t = 0; t < 4; ++t)
-                if (r0 + 4 * g + t < rows) dst[t] = src[t * PITCH];
+                if (r0 + 4 * g + t < write_rows) dst[t] = src[t * PITCH];
         }
     }
 }
@@ -265,7 +278,8 @@ void emit_matrix_kernel(const float* src, int64_t lds, int src_tiled, const floa
 // The same for a source in the factorisations' 16 x 16 tiles, 64 x 64 elements per workgroup: a wave reads a whole
 // source tile at a time (one contiguous kilobyte, 16 bytes per lane: four rows of a column), and both the matrix and
 // its transpose leave in pieces of four elements per lane over whole 64-element row segments.  ldd % 64 == 0.
-__device__ __forceinline__ void emit_tiled_body(const float* src, int tile_rows, const float* rdiag, int n, int64_t ldd,
+// The matrix starts at row and column `shift` (a multiple of 16) of the source.
+__device__ __forceinline__ void emit_tiled_body(const float* src, int tile_rows, const float* rdiag, int n, int64_t ldd, int shift,
                                                 float* dst32, uint16_t* dst16, float* dstT32, uint16_t* dstT16) {
     __shared__ float tile[64][65];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -275,8 +289,8 @@ __device__ __forceinline__ void emit_tiled_body(const float* src, int tile_rows,
         const int r = r0 + rl, c = c0 + cl;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (r < n && c < n) {
-            v = *reinterpret_cast<const float4*>(src + qr_tile_index(r, c, tile_rows));
-            if (rdiag != nullptr && rdiag[c] < 0.f) v = make_float4(-v.x, -v.y, -v.z, -v.w);
+            v = *reinterpret_cast<const float4*>(src + qr_tile_index(r + shift, c + shift, tile_rows));
+            if (rdiag != nullptr && rdiag[c + shift] < 0.f) v = make_float4(-v.x, -v.y, -v.z, -v.w);
             if (r + 1 >= n) v.y = 0.f;
             if (r + 2 >= n) v.z = 0.f;
             if (r + 3 >= n) v.w = 0.f;
@@ -313,18 +327,19 @@ __device__ __forceinline__ void emit_tiled_body(const float* src, int tile_rows,
 __global__ __launch_bounds__(256)
 void emit_tiled_kernel(const float* src, int tile_rows, const float* rdiag, int n, int64_t ldd,
                        float* dst32, uint16_t* dst16, float* dstT32, uint16_t* dstT16) {
-    emit_tiled_body(src, tile_rows, rdiag, n, ldd, dst32, dst16, dstT32, dstT16);
+    emit_tiled_body(src, tile_rows, rdiag, n, ldd, 0, dst32, dst16, dstT32, dstT16);
 }
 
 // grid z = matrix: per_batch of them (dst_stride elements apart) for every mixing object
 __global__ __launch_bounds__(256)
 void emit_tiled_batched_kernel(const float* src, const float* rdiag, int64_t src_stride, int tile_rows, int n, int64_t ldd,
-                               SmallSampleTargets t, int per_batch, int64_t dst_first, int64_t dst_stride) {
+                               SmallSampleTargets t, int per_batch, int64_t dst_first, int64_t dst_stride, int tail_rows) {
     const int item = blockIdx.z / per_batch, sub = blockIdx.z - item * per_batch;
     char* block = (char*)t.block[item];
     const int64_t at = dst_first + sub * dst_stride;
-    const bool bf = t.off_A16 >= 0;
-    emit_tiled_body(src + blockIdx.z * src_stride, tile_rows, rdiag + blockIdx.z * src_stride, n, ldd, (float*)(block + t.off_A32) + at,
+    const bool bf = t.off_A16 >= 0, tail = tail_rows > 0 && sub == per_batch - 1;
+    emit_tiled_body(src + blockIdx.z * src_stride, tile_rows, rdiag + blockIdx.z * src_stride, tail ? tail_rows : n, ldd,
+                    tail ? tail_offset(tile_rows, tail_rows) : 0, (float*)(block + t.off_A32) + at,
                     bf ? (uint16_t*)(block + t.off_A16) + at : nullptr, (float*)(block + t.off_Ainv32) + at,
                     bf ? (uint16_t*)(block + t.off_Ainv16) + at : nullptr);
 }
@@ -349,7 +364,7 @@ hipError_t fill_normal(float* out, int64_t ld, int rows, int cols, PhiloxStream 
     if (quads == 0) return hipSuccess;
     if (tiled && (int64_t)rows * cols < ((int64_t)1 << 32)) {
         hipLaunchKernelGGL(fill_normal_tiled_kernel, dim3((cols + 255) / 256, (rows + 15) / 16), dim3(256), 0, stream,
-                           out, (int64_t)0, 1, (int)ld, rows, cols, ps, scale, tiled == 2 ? 1 : 0);
+                           out, (int64_t)0, 1, (int)ld, rows, cols, ps, scale, tiled == 2 ? 1 : 0, 0);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(fill_normal_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream,
@@ -358,11 +373,12 @@ hipError_t fill_normal(float* out, int64_t ld, int rows, int cols, PhiloxStream 
 }
 
 hipError_t fill_normal_batched(float* out, int64_t out_stride, int tile_rows, int rows, int cols, PhiloxStream ps, int per_batch, int count,
-                               bool lower_only, hipStream_t stream) {
+                               bool lower_only, hipStream_t stream, int tail_rows) {
     if (rows <= 0 || cols <= 0 || count <= 0) return hipSuccess;
     if (count > 65535 || per_batch < 1 || (int64_t)rows * cols >= ((int64_t)1 << 32)) return hipErrorInvalidValue;
+    if (tail_rows != 0 && (tail_rows < 0 || tail_rows > rows || rows != cols || rows > 256 || tile_rows * 16 != rows || lower_only)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(fill_normal_tiled_kernel, dim3((cols + 255) / 256, (rows + 15) / 16, count), dim3(256), 0, stream,
-                       out, out_stride, per_batch, tile_rows, rows, cols, ps, 1.0f, lower_only ? 1 : 0);
+                       out, out_stride, per_batch, tile_rows, rows, cols, ps, 1.0f, lower_only ? 1 : 0, tail_rows);
     return hipGetLastError();
 }
 
@@ -432,11 +448,11 @@ hipError_t emit_matrix(const float* src, int64_t lds, int src_tiled, const float
 }
 
 hipError_t emit_batched(const float* src, const float* rdiag, int64_t src_stride, int tile_rows, int n, int64_t ldd, const SmallSampleTargets& t,
-                        int count, int per_batch, int64_t dst_first, int64_t dst_stride, hipStream_t stream) {
+                        int count, int per_batch, int64_t dst_first, int64_t dst_stride, hipStream_t stream, int tail_rows) {
     if (count < 1 || count > kSmallMaxBatch || per_batch < 1 || count * per_batch > 65535) return hipErrorInvalidValue;
     const int t64 = (int)((ldd + 63) / 64);
     hipLaunchKernelGGL(emit_tiled_batched_kernel, dim3(t64, t64, count * per_batch), dim3(256), 0, stream,
-                       src, rdiag, src_stride, tile_rows, n, ldd, t, per_batch, dst_first, dst_stride);
+                       src, rdiag, src_stride, tile_rows, n, ldd, t, per_batch, dst_first, dst_stride, tail_rows);
     return hipGetLastError();
 }
 

@@ -141,7 +141,26 @@ def test_static_entry_point_and_fresh_blocks(ctx):
     assert (mats[0] - mats[1]).abs().max() > 0.05
 
 
-@pytest.mark.parametrize("nd,k,d,count,picks", [(300, 15, 64, 5, (0, 4)), (2048, 102, 256, 6, (0, 3, 5)), (100, 0, 64, 3, (1,))])
+# a last block of more than 128 rows is the end of a full-size matrix beside the others: the panels it begins with (its first column in the
+# second, third and last panel of a group of four; nothing left out from 193 rows on), rows that fill no tile
+@pytest.mark.parametrize("rest", [129, 144, 145, 176, 192, 193, 255])
+def test_short_last_block_beside_the_others(ctx, rest):
+    n, eps = 512 + rest, 2.0 ** -24
+    many = g.gelo_sample_mixing_batch(ctx, g.GELO_BLOCK_ORTHOGONAL, n, 0, 64, g.GELO_F32, 100, 3)
+    for i, m in enumerate(many):
+        A = f64(g.gelo_mixing_export(ctx, m, n, 0, 64, want_shields=False)[0])
+        g.gelo_mixing_free(ctx, m)
+        assert np.linalg.norm(A.T @ A - np.eye(n)) / math.sqrt(n) < 1e-6      # 5e-7 with full blocks alone
+        A_ref, _ = o.sample_block_orthogonal(SEED, 100 + i, n, 0)
+        assert np.all(A[A_ref == 0.0] == 0.0)
+        for b, (r0, rows, *_) in enumerate(o.block_layout(n, 0)):
+            kappa_G = np.linalg.cond(o.gaussian_matrix(SEED, 100 + i, o.STREAM_BLOCK, b, rows, rows))
+            part = np.ix_(range(r0, r0 + rows), range(r0, r0 + rows))
+            assert o.rel_frobenius(A[part], A_ref[part]) < 10 * kappa_G * eps + 1e-6, f"draw {i}, block {b}"
+
+
+@pytest.mark.parametrize("nd,k,d,count,picks", [(300, 15, 64, 5, (0, 4)), (2048, 102, 256, 6, (0, 3, 5)), (100, 0, 64, 3, (1,)),
+                                                   (400, 20, 64, 5, (0, 4)), (200, 0, 64, 3, (2,))])
 def test_batched_draw_equals_single_draws(ctx, nd, k, d, count, picks):
     """All full blocks of all objects of a batched draw share one factorisation's launches; object i is still,
     bit for bit, the single draw of its batch id."""
