@@ -449,6 +449,162 @@ void lanczos_vector_kernel(float* vec, int64_t ld, int n, float* tri, int step) 
     if (tid == 0) { tr[step] = alpha; tr[kLanczosMax + step] = beta; }
 }
 
+// The same steps with one launch each, for small matrices: every workgroup forms the sum of the parts and the next vector itself (all the
+// same bits) before its rows of the product.  Launch j < steps leaves the parts of product j, launch `steps` the last coefficients; vector
+// j lies in slot j % 3, the parts of even and odd products in either half, so that nobody writes what others of the launch still read.
+// Bound by latency, a read of the parts, one of the rows and two sums over the workgroup: 5.3 us per step at 512 rows, where three launches
+// took 3.7 + 4.0 + 3.4 and the gaps between them.  Draw, us: CONDITIONED 64 rows 330 -> 258, 129 404 -> 315, 512 714 -> 632, 1024 1068 -> 990;
+// GAUSSIAN (one attempt) 512 728 -> 632, 1024 1083 -> 1006.  With 256 threads, the parts summed by one thread per column: 678 and 1098.  The parts that
+// every workgroup reads (32 rows) grow with n, the rows of few workgroups with n^2: beyond 1024 rows the launches stay apart.
+constexpr int kFusedGroups = 32;                       // workgroups per operator, at most
+constexpr int kFusedMaxN = 1024;
+
+constexpr int kFusedWaves = 8, kFusedThreads = 64 * kFusedWaves;
+
+__device__ __forceinline__ float block_sum_512(float v, float* red) {
+    v = wave_sum(v);
+    __syncthreads();                                   // red may still be read from the previous call
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < kFusedWaves; ++w) s += red[w];
+    return s;
+}
+
+template <int CH>
+__global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void lanczos_step_kernel(const float* Ma, const float* Mb, float* pa, float* pb, float* vec, int64_t lda, int64_t ld, int n, float* tri, int step, int steps,
+                         int groups) {
+    constexpr int COLS = CH * 256, QUADS = COLS / 4;
+    constexpr int SETS = kFusedThreads / QUADS;        // of parts: each is added up by QUADS threads
+    constexpr int PER = kFusedGroups / SETS;
+    constexpr int OWN = (COLS + kFusedThreads - 1) / kFusedThreads;      // elements of the vector per thread
+    constexpr int RB = 4;                              // rows whose reads are on their way together
+    __shared__ __attribute__((aligned(16))) float vs[COLS];
+    __shared__ __attribute__((aligned(16))) float sums[kFusedWaves][COLS];
+    __shared__ float red[kFusedWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), o = blockIdx.y;
+    const float* M = o ? Mb : Ma;
+    float* parts = o ? pb : pa;
+    float* slots = vec + (int64_t)o * 3 * ld;
+    float* tr = tri + o * 2 * kLanczosMax;
+    float x[OWN];
+    if (step == 0) {
+        float ss = 0.f;
+#pragma unroll
+        for (int k = 0; k < OWN; ++k) {
+            const int i = tid + kFusedThreads * k;
+            uint32_t h = (uint32_t)i * 2654435761u + 0x9E3779B9u;   // as lanczos_vector_kernel's first vector
+            h ^= h >> 15; h *= 2246822519u; h ^= h >> 13;
+            x[k] = i < n ? ((h & 1u) ? 1.f : -1.f) * (0.5f + (float)((h >> 8) & 0xFFFF) * (1.0f / 65536.0f)) : 0.f;
+            ss = fmaf(x[k], x[k], ss);
+        }
+        const float inv = rsqrtf(block_sum_512(ss, red));
+#pragma unroll
+        for (int k = 0; k < OWN; ++k) x[k] *= inv;
+    } else {
+        const float* before = parts + (int64_t)((step - 1) & 1) * groups * ld;
+        const float* v = slots + (int64_t)((step - 1) % 3) * ld;
+        const float* vp = slots + (int64_t)((step + 1) % 3) * ld;            // vector step - 2
+        const float beta_prev = step > 1 ? tr[kLanczosMax + step - 2] : 0.f;
+        float y[OWN], yp[OWN];
+#pragma unroll
+        for (int k = 0; k < OWN; ++k) {
+            const int i = tid + kFusedThreads * k;
+            y[k] = i < n ? v[i] : 0.f;
+            yp[k] = i < n && step > 1 ? vp[i] : 0.f;
+        }
+        {
+            const int q = tid % QUADS, set = tid / QUADS;
+            const int at = 4 * q < (int)ld ? 4 * q : 0;
+            f32x4_t p[PER], s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < PER; ++i) p[i] = *reinterpret_cast<const f32x4_t*>(before + (int64_t)(set * PER + i < groups ? set * PER + i : 0) * ld + at);
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s[e] += set * PER + i < groups ? p[i][e] : 0.f;
+            *reinterpret_cast<f32x4_t*>(&sums[set][4 * q]) = s;
+        }
+        __syncthreads();
+        float dot = 0.f;
+#pragma unroll
+        for (int k = 0; k < OWN; ++k) {
+            const int i = tid + kFusedThreads * k;
+            x[k] = 0.f;
+            if (i < n) {
+#pragma unroll
+                for (int t = 0; t < SETS; ++t) x[k] += sums[t][i];
+            }
+            dot = fmaf(x[k], y[k], dot);
+        }
+        const float alpha = block_sum_512(dot, red);
+        float ss = 0.f;
+#pragma unroll
+        for (int k = 0; k < OWN; ++k) {
+            x[k] = fmaf(-beta_prev, yp[k], fmaf(-alpha, y[k], x[k]));
+            ss = fmaf(x[k], x[k], ss);
+        }
+        const float beta = sqrtf(block_sum_512(ss, red));
+        const float inv = beta > 0.f ? 1.0f / beta : 0.f;
+#pragma unroll
+        for (int k = 0; k < OWN; ++k) x[k] *= inv;
+        if (blockIdx.x == 0 && tid == 0) { tr[step - 1] = alpha; tr[kLanczosMax + step - 1] = beta; }
+    }
+    if (step == steps) return;
+#pragma unroll
+    for (int k = 0; k < OWN; ++k) {
+        const int i = tid + kFusedThreads * k;
+        if (i < COLS) vs[i] = x[k];
+        if (blockIdx.x == 0 && i < n) slots[(int64_t)(step % 3) * ld + i] = x[k];
+    }
+    __syncthreads();
+    f32x4_t sum[CH];
+#pragma unroll
+    for (int j = 0; j < CH; ++j) sum[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const int stride = groups * kFusedWaves;
+    for (int r0 = blockIdx.x * kFusedWaves + wave; r0 < n; r0 += RB * stride) {
+        f32x4_t m[RB][CH];
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+            const int r = r0 + b * stride;
+            const float* row = M + (int64_t)(r < n ? r : r0) * lda;
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+                const int c = j * 256 + lane * 4;      // (beyond its end the row's start again, as in normal_product_kernel)
+                m[b][j] = *reinterpret_cast<const f32x4_t*>(row + (c < lda ? c : 0));
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+            if (r0 + b * stride >= n) break;           // (the same for the whole wave)
+            float dot = 0.f;
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+                const f32x4_t y = *reinterpret_cast<const f32x4_t*>(&vs[j * 256 + lane * 4]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dot = fmaf(m[b][j][e], y[e], dot);
+            }
+            dot = wave_sum(dot);
+#pragma unroll
+            for (int j = 0; j < CH; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[j][e] = fmaf(dot, m[b][j][e], sum[j][e]);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < CH; ++j) *reinterpret_cast<f32x4_t*>(&sums[wave][j * 256 + lane * 4]) = sum[j];
+    __syncthreads();
+    float* part = parts + ((int64_t)(step & 1) * groups + blockIdx.x) * ld;
+    for (int c = tid; c < n; c += kFusedThreads) {
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < kFusedWaves; ++w) s += sums[w][c];
+        part[c] = s;
+    }
+}
+
 // Largest eigenvalue of the symmetric tridiagonal matrix (alpha[0..k), beta[0..k-1)) by sectioning on
 // the Sturm count: one wave, lanes 0..31 work on A, lanes 32..63 on A^-1; each round every lane counts
 // the eigenvalues below its own trial value (32 trial values per bracket), and the bracket shrinks to
@@ -594,6 +750,22 @@ hipError_t kappa_estimate(const float* A, const float* Ainv, int64_t lda, int n,
     // the workgroups' sums go to the (now free) factorisation buffers, `groups` rows of each
     float* va = ws.vec;            float* wa = va + 2 * ld;
     float* vi = ws.vec + 3 * ld;   float* wi = vi + 2 * ld;
+    if (n <= kFusedMaxN) {
+        // (two halves of at most n / 8 + 1 rows of ld each)
+        const int few = (n + kFusedWaves - 1) / kFusedWaves < kFusedGroups ? (n + kFusedWaves - 1) / kFusedWaves : kFusedGroups;
+        for (int j = 0; j <= steps; ++j) {
+            auto step = [&](auto chc) {
+                hipLaunchKernelGGL((lanczos_step_kernel<decltype(chc)::value>), dim3(j < steps ? few : 1, 2), dim3(kFusedThreads), 0, s, A, Ainv, ws.M, ws.X, ws.vec, lda, ld, n,
+                                   ws.tri, j, steps, few);
+                return hipGetLastError();
+            };
+            if (n <= 256) GELO_TRY(step(std::integral_constant<int, 1>{}));
+            else if (n <= 512) GELO_TRY(step(std::integral_constant<int, 2>{}));
+            else GELO_TRY(step(std::integral_constant<int, 4>{}));
+        }
+        hipLaunchKernelGGL(lanczos_finish_kernel, dim3(1), dim3(64), 0, s, ws.tri, steps, ws.scalars);
+        return hipGetLastError();
+    }
     auto product = [&](auto chc) {
         hipLaunchKernelGGL((normal_product_kernel<decltype(chc)::value>), dim3(groups, 2), dim3(256), 0, s, A, va, ws.M, Ainv, vi, ws.X, lda, ld, n);
         return hipGetLastError();
@@ -602,10 +774,7 @@ hipError_t kappa_estimate(const float* A, const float* Ainv, int64_t lda, int n,
     GELO_TRY(hipGetLastError());
     for (int j = 0; j < steps; ++j) {
         // w = M^T (M v) for M = A and M = Ainv, then one step of the recurrence for both
-        if (n <= 256) GELO_TRY(product(std::integral_constant<int, 1>{}));
-        else if (n <= 512) GELO_TRY(product(std::integral_constant<int, 2>{}));
-        else if (n <= 1024) GELO_TRY(product(std::integral_constant<int, 4>{}));
-        else if (n <= 2048) GELO_TRY(product(std::integral_constant<int, 8>{}));
+        if (n <= 2048) GELO_TRY(product(std::integral_constant<int, 8>{}));
         else if (n <= 3072) GELO_TRY(product(std::integral_constant<int, 12>{}));
         else if (n <= 4096) GELO_TRY(product(std::integral_constant<int, 16>{}));
         else GELO_TRY(product(std::integral_constant<int, 20>{}));
