@@ -556,15 +556,15 @@ struct QrBulkArgs {
     Reflector refl[kMaxProduct]; int pending;
     float* Cout; float* X; int outer, acc;
     int64_t strip_stride; int nb_block; int64_t batch_stride; int count;
-    int per_object, skip_tail;           // skip_tail: the last of every per_object matrices has nothing here
+    int per_object; bool skip_tail;      // the last of every per_object matrices has nothing here
 };
 // A strip fits the 128 registers of two workgroups per CU.
-template <int NBLK>
+template <int NBLK, bool SKIP = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void qr_bulk_kernel(QrBulkArgs a) {
     int matrix, b;
     if (!deal_to_dies(blockIdx.x, a.outer + a.acc, a.count, &matrix, &b)) return;
-    if (a.skip_tail && matrix % a.per_object == a.per_object - 1) return;
+    if (SKIP && matrix % a.per_object == a.per_object - 1) return;
     const int64_t off = (int64_t)matrix * a.batch_stride;
     float* Cs = b < a.outer ? a.Cout + (int64_t)b * a.strip_stride : a.X + (int64_t)(b - a.outer) * a.strip_stride;
     reflect_strip_lds_body<NBLK>(a.refl, a.pending, off, Cs + off, a.nb_block);
@@ -812,15 +812,16 @@ struct QrStepArgs {
     float* Vr_next; float* Vt_next; float* Tnext; float* Rd_next; float* rdiag_next;   // outputs of panel p + 1
     int m_next;                          // its row count (0: no further panel)
     int64_t batch_stride;                // floats from one matrix's workspace to the next one's (grid y = matrix)
-    int per_object, skip_tail;           // skip_tail: the last of every per_object matrices has nothing here
+    int per_object; bool skip_tail;      // the last of every per_object matrices has nothing here
 };
 
-template <int NBLK>
+// SKIP (a kernel of its own: the argument's way alone took 0.3 us of every step's 9)
+template <int NBLK, bool SKIP = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBLK >= 10 ? 2 : 4, NBLK >= 10 ? 2 : 4)))
 void qr_step_kernel(QrStepArgs a) {
     __shared__ StripShared strip;
     const int b = blockIdx.x;
-    if (a.skip_tail && (int)blockIdx.y % a.per_object == a.per_object - 1) return;
+    if (SKIP && (int)blockIdx.y % a.per_object == a.per_object - 1) return;
     const int64_t off = (int64_t)blockIdx.y * a.batch_stride;
     if (b == 0) {
         if (a.m_next <= 0) return;
@@ -1014,6 +1015,10 @@ hipError_t launch_qr_bulk(const QrBulkArgs& b, int count, hipStream_t s) {
     // blocks per wave in steps of two, up to 10 (below kWideProduct): a strip kernel sized for 20 blocks spends a third more time
     // on a strip of 11 than one sized for 12 (it still requests and waits for the blocks that do not exist)
     const int per_wave = (b.nb_block + 7) / 8;
+    if (b.skip_tail) {                                        // (at most 256 rows)
+        hipLaunchKernelGGL((qr_bulk_kernel<2, true>), dim3(8 * dies_slots(b.outer + b.acc, count)), dim3(512), 0, s, b);
+        return hipGetLastError();
+    }
     switch ((per_wave + 1) / 2) {
         case 0: case 1: return launch_qr_bulk_t<2>(b, count, s);
         case 2: return launch_qr_bulk_t<4>(b, count, s);
@@ -1026,6 +1031,10 @@ hipError_t launch_qr_bulk(const QrBulkArgs& b, int count, hipStream_t s) {
 
 hipError_t launch_qr_step(const QrStepArgs& a, int count, hipStream_t s) {
     const int longest = a.outer > 0 ? a.nb_block : a.nb_single;
+    if (a.skip_tail) {                                        // (at most 256 rows)
+        hipLaunchKernelGGL((qr_step_kernel<5, true>), dim3(1 + a.inner + a.outer, count), dim3(512), 0, s, a);
+        return hipGetLastError();
+    }
     return for_strip_blocks((longest + 7) / 8, [&](auto nblk) { return launch_qr_step_t<decltype(nblk)::value>(a, count, s); });
 }
 
@@ -1038,7 +1047,7 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
 hipError_t householder_qr_tails(const FactorWorkspace& ws, int n, int count, int64_t batch_stride, hipStream_t s, bool direct, int per_object, int tail_rows) {
     if (count < 1 || count > 65535) return hipErrorInvalidValue;
     const int n_pad = ws.n_pad;
-    if (tail_rows != 0 && (direct || n != n_pad || wide_product(n_pad, false) || tail_rows < 0 || tail_rows > n || per_object < 1 || count % per_object != 0)) return hipErrorInvalidValue;
+    if (tail_rows != 0 && (direct || n != n_pad || n > 256 || tail_rows < 0 || tail_rows > n || per_object < 1 || count % per_object != 0)) return hipErrorInvalidValue;
     const int nbr = n_pad / NB;                               // tile rows (= tile columns)
     const int64_t strip_stride = (int64_t)nbr * 256;
     const int panels = nbr;
