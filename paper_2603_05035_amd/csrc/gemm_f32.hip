@@ -4,7 +4,7 @@
 // through v_mfma_f32_32x32x2_f32 in 64 x 64 tiles: the sums run in another order there, so a product and its parts need not agree
 // to the last bit.
 // A 128 x 128 tile of gemm_f32_kernel reads all of its operands before it stores, so the product may overwrite B in place with M <= 128
-// (C == B0, K0 == K: the back substitution's multiplications by a diagonal-block inverse, a caller's un-mix into its Y) and A where
+// (C == B0, K0 == K: a caller's un-mix into its Y) and A where
 // one tile spans N.  So does a tile of gemm_f32_split_kernel.  Smaller tiles would read what their neighbours have stored: they are not
 // taken where C meets an operand.
 //
@@ -202,8 +202,7 @@ void gemm_f32_kernel(F32Args g) {
         }
 }
 
-// M <= 128 and K <= 128 (K a multiple of 16): the back substitution's multiplications by the inverse of a
-// diagonal block.  One 128 x 128 tile per 128 columns would leave most of the chip idle and each
+// M <= 128 and K <= 128 (K a multiple of 16) where C meets an operand (a caller's un-mix into its Y).  One 128 x 128 tile per 128 columns would leave most of the chip idle and each
 // tile bound by the float MFMA rate of its one CU, so the tiles here are 128 x 32 (four times as
 // many workgroups, a wave owns 32 x 32), and with so few K steps both panels of the tile are
 // fetched at once (all loads in flight together) and stored to LDS behind ONE barrier.
@@ -546,11 +545,6 @@ hipError_t gemm_f32(const GemmOperands& o, hipStream_t stream) {
     a.M = o.M; a.N = o.N; a.K = o.K;
     a.tiles_m = (o.M + kTileM - 1) / kTileM;
     a.subtract = o.subtract ? 1 : 0;
-    if (o.M <= kTileM && o.K <= 128 && o.K % 16 == 0 && o.K0 >= o.K) {
-        a.tiles_n = (o.N + SN - 1) / SN;
-        hipLaunchKernelGGL(gemm_f32_short_kernel, dim3(a.tiles_n), dim3(NT), kShortLds, stream, a);
-        return hipGetLastError();
-    }
     // Does C share memory with an operand?  Slices of the columns of one buffer, which have the same pitch, do not where their columns
     // are apart; with different pitches the ranges from the first to the last element tell.
     auto meets_c = [&](const void* p, int64_t ld, int64_t rows, int64_t cols) {
@@ -563,7 +557,12 @@ hipError_t gemm_f32(const GemmOperands& o, hipStream_t stream) {
     };
     const int tiles = a.tiles_m * ((o.N + kTileM - 1) / kTileM);
     const bool in_place = tiles < kCus && (meets_c(o.A, o.lda, o.M, o.K) || meets_c(o.B0, o.ldb0, std::min(o.K0, o.K), o.N) || meets_c(o.B1, o.ldb1, o.K - o.K0, o.N));
-    if (in_place) {
+    if (in_place && o.M <= kTileM && o.K <= 128 && o.K % 16 == 0 && o.K0 >= o.K) {
+        // (where C meets no operand 64 x 64 tiles are faster at every size: 16 x 192 x 16 3.3 us against 4.9, 128 x 4096 x 128 7.7 and 8.4,
+        // 128 x 12288 x 128 10.4 and 15.0)
+        a.tiles_n = (o.N + SN - 1) / SN;
+        hipLaunchKernelGGL(gemm_f32_short_kernel, dim3(a.tiles_n), dim3(NT), kShortLds, stream, a);
+    } else if (in_place) {
         a.tiles_n = (o.N + kTileM - 1) / kTileM;
         hipLaunchKernelGGL((gemm_f32_kernel<kTileM>), dim3(a.tiles_m * a.tiles_n), dim3(NT), 0, stream, a);
     } else if (tiles < kCus) {

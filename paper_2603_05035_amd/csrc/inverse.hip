@@ -682,12 +682,14 @@ hipError_t inverse_from_qr(const FactorWorkspace& ws, int n, const float* A, int
     GELO_TRY(emit_matrix(ws.M, nbr, 1, nullptr, n, ld, R, nullptr, nullptr, nullptr, s));
     GELO_TRY(emit_matrix(ws.X, nbr, 1, nullptr, n, ld, nullptr, nullptr, X, nullptr, s));
     if (n < n_pad) GELO_TRY(pad_matrix(X, ld, n, n_pad, s));
+    // a finished block of rows goes straight to its place in A^-1
     for (int c0 = (n_pad - 1) / BW * BW; c0 >= 0; c0 -= BW) {
-        const int w = n_pad - c0 < BW ? n_pad - c0 : BW;
-        GELO_TRY(gemm(ws.Dinv + (int64_t)c0 * BW, BW, X + (int64_t)c0 * ld, ld, X + (int64_t)c0 * ld, ld, w, n_pad, w, false, s));
-        GELO_TRY(gemm(R + c0, ld, X + (int64_t)c0 * ld, ld, X, ld, c0, n_pad, w, true, s));
+        const int w = n - c0 < BW ? n - c0 : BW;
+        GELO_TRY(gemm(ws.Dinv + (int64_t)c0 * BW, BW, X + (int64_t)c0 * ld, ld, Ainv32 + (int64_t)c0 * ldk, ldk, w, (int)ldk, w, false, s));
+        GELO_TRY(gemm(R + c0, ld, Ainv32 + (int64_t)c0 * ldk, ldk, X, ld, c0, n_pad, w, true, s));
     }
-    return emit_matrix(X, ld, 0, nullptr, n, ldk, Ainv32, Ainv16, nullptr, nullptr, s);
+    if (Ainv16 == nullptr) return hipSuccess;
+    return emit_matrix(Ainv32, ldk, 0, nullptr, n, ldk, nullptr, Ainv16, nullptr, nullptr, s);
 }
 
 // Newton's iteration X <- X + X (I - A X) from X = Q^T, whose residual I - A Q^T = -E Q^T has the eigenvalues of a Gaussian of
