@@ -703,6 +703,14 @@ gelo_status gelo_sample_mixing(gelo_ctx* ctx, gelo_kind kind, int n_data, int k_
     return GELO_OK;
 }
 
+// Float batches whose mix is one launch: beyond kSmallMixCols columns four waves of float products per workgroup are more than one per
+// CU, and the launches apart are faster (122 + 6 rows of 11008: 17.2 us against 18.7; 90 + 5 15.2 and 14.5; of 8192 all rows win).
+constexpr int kSmallMixRows = 96, kSmallMixCols = 32 * 256;
+// Row norms in the mix itself: one round of reads per wave (eight rows each) of what the mix reads again (64 rows of 64: 10.5 us, with a
+// launch of their own 8.4; 32 of 256 7.5 and 8.5)
+constexpr int kNormsInMixRows = 32;
+constexpr size_t kNormsInMixValues = 8192;
+
 // Launches of eq. 1 / eqs. 7-8 on the buffers of `m`: shield rows, then U = A [H ; S].
 static gelo_status mix_launch(gelo_ctx* ctx, gelo_mixing* m, const void* H, int64_t ldh, float shield_scale,
                               gelo_norm_stat stat, void* U, int64_t ldu, hipStream_t s) {
@@ -712,6 +720,20 @@ static gelo_status mix_launch(gelo_ctx* ctx, gelo_mixing* m, const void* H, int6
         if (m->k > 0) GELO_HIP(ctx, row_norms(H, 1, ldh, m->n_data, m->d, m->rownorm, s));
         GELO_HIP(ctx, small_mix(m->A16, m->ldk, (const uint16_t*)H, ldh, m->GS, m->gsnorm, m->rownorm, (int)stat, shield_scale,
                                 m->n_data, m->k, m->d, (uint16_t*)m->S, (uint16_t*)U, ldu, s));
+        return GELO_OK;
+    }
+    const auto apart = [&] {
+        const char* h0 = (const char*)H;
+        const char* u0 = (const char*)U;
+        return u0 + ((size_t)(m->n - 1) * ldu + m->d) * 4 <= h0 || h0 + ((size_t)(m->n_data - 1) * ldh + m->d) * 4 <= u0;
+    };
+    if (!bf && m->k > 0 && !m->structured && !m->blocked && (m->n <= kSmallMixRows || (m->n <= kSmallMaxN && m->d <= kSmallMixCols)) && apart()) {
+        // The same in float, unless U overwrites H while other workgroups read it (without shields the product is one launch as it is).
+        // The norms of few rows and values are taken there too.
+        const bool norms_there = m->n_data <= kNormsInMixRows && (size_t)m->n_data * m->d <= kNormsInMixValues;
+        if (!norms_there) GELO_HIP(ctx, row_norms(H, 0, ldh, m->n_data, m->d, m->rownorm, s));
+        GELO_HIP(ctx, small_mix_f32(m->A32, m->ldk, (const float*)H, ldh, m->GS, m->gsnorm, norms_there ? nullptr : m->rownorm, (int)stat, shield_scale,
+                                    m->n_data, m->k, m->d, (float*)m->S, (float*)U, ldu, s));
         return GELO_OK;
     }
     if (m->k > 0) {

@@ -253,6 +253,11 @@ hipError_t small_init();
 hipError_t small_mix(const uint16_t* A16, int64_t ldk, const uint16_t* H, int64_t ldh, const float* GS, const float* gsnorm,
                      const float* rownorm, int stat_kind, float shield_scale, int n_data, int k, int d,
                      uint16_t* S, uint16_t* U, int64_t ldu, hipStream_t stream);
+// The same in float, k >= 1; A zero beyond column n up to the next multiple of 8.  rownorm null: every workgroup takes the norms from H.
+// U and H share no memory.
+hipError_t small_mix_f32(const float* A, int64_t ldk, const float* H, int64_t ldh, const float* GS, const float* gsnorm,
+                         const float* rownorm, int stat_kind, float shield_scale, int n_data, int k, int d,
+                         float* S, float* U, int64_t ldu, hipStream_t stream);
 
 // ------------------------------------------------- structured orthogonal A --
 constexpr int kStructuredRounds = 3;

@@ -267,6 +267,161 @@ void small_mix_kernel(SmallMixArgs a) {
     }
 }
 
+struct SmallMixF32Args {
+    const float* A; int64_t ldk;
+    const float* H; int64_t ldh;
+    const float* GS; const float* gsnorm; const float* rownorm;
+    int stat_kind; float shield_scale;
+    int n_data, k, d;
+    float* S; float* U; int64_t ldu;
+};
+
+// || row ||_2 of `cols` floats for up to kRowsTogether rows of pitch `ld` by one wave, in every lane; cols a multiple of 8, the rows
+// 16-byte aligned, their reads on their way together.  Rows from `rows` on repeat the last one.  The sums run as in row_norms (sampler.hip).
+constexpr int kRowsTogether = 8;
+__device__ __forceinline__ void row_norms_of_wave(const float* first, int64_t ld, int rows, int cols, int lane, float (&norm)[kRowsTogether]) {
+#pragma unroll
+    for (int i = 0; i < kRowsTogether; ++i) norm[i] = 0.f;
+#pragma unroll 1
+    for (int c = lane * 4; c < cols; c += 64 * 4) {
+        f32x4_t v[kRowsTogether];
+#pragma unroll
+        for (int i = 0; i < kRowsTogether; ++i) v[i] = *reinterpret_cast<const f32x4_t*>(first + (int64_t)(i < rows ? i : rows - 1) * ld + c);
+#pragma unroll
+        for (int i = 0; i < kRowsTogether; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) norm[i] = fmaf(v[i][e], v[i][e], norm[i]);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int i = 0; i < kRowsTogether; ++i) norm[i] += __shfl_xor(norm[i], off, 64);
+#pragma unroll
+    for (int i = 0; i < kRowsTogether; ++i) norm[i] = sqrtf(norm[i]);
+}
+
+// The factors of the k shield rows from the row norms, 256 threads: thread t brings norm t (t < n_data) and the norm of
+// shield direction t (t < k).  NORMS: the norms are taken here, from H.
+struct SmallStatistic { float norms[kSmallMaxN], factor[kSmallMaxN], stat; };
+template <bool NORMS>
+__device__ __forceinline__ void shield_factors(SmallStatistic& sh, const SmallMixF32Args& a, float my_norm, float my_gsnorm) {
+    const int tid = threadIdx.x;
+    if (!NORMS) {
+        if (tid < a.n_data) sh.norms[tid] = my_norm;
+        __syncthreads();
+    } else {
+        const int lane = tid & 63, wave = tid >> 6;
+        for (int r0 = wave; r0 < a.n_data; r0 += 4 * kRowsTogether) {
+            float norm[kRowsTogether];
+            row_norms_of_wave(a.H + (int64_t)r0 * a.ldh, 4 * a.ldh, (a.n_data - r0 + 3) / 4, a.d, lane, norm);
+#pragma unroll
+            for (int i = 0; i < kRowsTogether; ++i) if (lane == 0 && r0 + 4 * i < a.n_data) sh.norms[r0 + 4 * i] = norm[i];
+        }
+        __syncthreads();
+        my_norm = tid < a.n_data ? sh.norms[tid] : 0.f;
+    }
+    if (a.stat_kind == 0) {
+        // median by rank: every value counts the (value, index) pairs below it; the two of middle rank meet in the mean
+        if (tid < a.n_data) {
+            const uint32_t mine = __float_as_uint(my_norm);
+            int below = 0;
+            for (int i = 0; i < a.n_data; ++i) {
+                const uint32_t o = __float_as_uint(sh.norms[i]);
+                below += (o < mine || (o == mine && i < tid)) ? 1 : 0;
+            }
+            if (below == (a.n_data - 1) / 2) sh.factor[0] = my_norm;
+            if (below == a.n_data / 2) sh.factor[1] = my_norm;
+        }
+        __syncthreads();
+        if (tid == 0) sh.stat = 0.5f * (sh.factor[0] + sh.factor[1]);
+    } else {                                                     // a tree sum, as mean_kernel's
+        if (tid < kSmallMaxN) sh.factor[tid] = tid < a.n_data ? sh.norms[tid] : 0.f;
+        __syncthreads();
+        for (int half = kSmallMaxN / 2; half > 0; half >>= 1) {
+            if (tid < half) sh.factor[tid] += sh.factor[tid + half];
+            __syncthreads();
+        }
+        if (tid == 0) sh.stat = sh.factor[0] / (float)a.n_data;
+    }
+    __syncthreads();
+    const float m = sh.stat;
+    __syncthreads();
+    if (tid < a.k) sh.factor[tid] = a.shield_scale * m / my_gsnorm;
+}
+
+// The same in float, on v_mfma_f32_32x32x2_f32 and in the order of gemm_f32_kernel (the same bits).  The operand tile lies in LDS row by row: a lane's
+// values of B are single dwords, contiguous across lanes.  It takes the place of three launches (statistic, shield rows, product), NORMS of
+// four, each of which costs the host about 2.5 us and the GPU 2 to 3.  mix, us from the host / in a graph, launches apart -> here: 16 + 2 rows of
+// 64 (NORMS) 18.8 / 8.5 -> 11.5 / 5.8, 64 + 4 of 4096 18.8 / 11.9 -> 13.7 / 9.2, 120 + 6 of 4096 18.8 / 13.2 -> 13.6 / 12.7.  Tiny layer (16 + 2 x 64 x 192), the whole step
+// 34.6 -> 28.2.  With 64 columns per workgroup 12.7 and 18.2 for the latter two: twice the float products per wave.
+constexpr int MIX_FN = 32;           // columns of U per workgroup
+constexpr int MIX_FP = MIX_FN + 4;   // pitch (floats) of a row of the operand tile in LDS
+template <bool NORMS>
+__global__ __launch_bounds__(256)
+void small_mix_f32_kernel(SmallMixF32Args a) {
+    __shared__ __attribute__((aligned(16))) float B[kSmallMaxN * MIX_FP];
+    __shared__ SmallStatistic sh;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = a.n_data + a.k, c0 = blockIdx.x * MIX_FN;
+    const int kp = (n + 7) & ~7;
+    const int j = lane & 31, grp = lane >> 5;
+    const float my_norm = (a.k > 0 && !NORMS && tid < a.n_data) ? a.rownorm[tid] : 0.f;
+    const float my_gsnorm = tid < a.k ? a.gsnorm[tid] : 1.f;
+    constexpr int CPR = MIX_FN / 4, HR = kSmallMaxN * CPR / 256;  // 16-byte chunks per row, of H per thread: at most 4
+    f32x4_t hreg[HR];
+#pragma unroll
+    for (int it = 0; it < HR; ++it) {
+        const int i = tid + it * 256;
+        const int r = i / CPR, col = c0 + (i % CPR) * 4;
+        hreg[it] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        if (r < a.n_data && col < a.d) hreg[it] = *reinterpret_cast<const f32x4_t*>(a.H + (int64_t)r * a.ldh + col);
+    }
+    f32x4_t af[kSmallMaxN / 8];
+    {
+        int arow = wave * 32 + j; arow = arow < n ? arow : n - 1;
+        const float* ap = a.A + (int64_t)arow * a.ldk + grp * 4;
+#pragma unroll
+        for (int ks = 0; ks < kSmallMaxN / 8; ++ks)
+            if (ks * 8 < kp && wave * 32 < n) af[ks] = *reinterpret_cast<const f32x4_t*>(ap + ks * 8);
+    }
+    if (a.k > 0) shield_factors<NORMS>(sh, a, my_norm, my_gsnorm);
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < HR; ++it) {                            // rows n .. kp - 1 are cleared, shield rows follow
+        const int i = tid + it * 256;
+        const int r = i / CPR;
+        if (r < a.n_data || (r >= n && r < kp)) *reinterpret_cast<f32x4_t*>(&B[r * MIX_FP + (i % CPR) * 4]) = hreg[it];
+    }
+    for (int i = tid; i < a.k * MIX_FN; i += 256) {
+        const int r = i / MIX_FN, cc = i - r * MIX_FN;
+        const int col = c0 + cc;
+        float x = 0.f;
+        if (col < a.d) {
+            x = a.GS[(int64_t)r * a.d + col] * sh.factor[r];
+            a.S[(int64_t)r * a.d + col] = x;
+        }
+        B[(a.n_data + r) * MIX_FP + cc] = x;
+    }
+    __syncthreads();
+    if (wave * 32 >= n) return;
+    f32x16_t acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < kSmallMaxN / 8; ++ks) {
+        if (ks * 8 < kp) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[ks][e], B[(ks * 8 + grp * 4 + e) * MIX_FP + j], acc, 0, 0, 0);
+        }
+    }
+    const int col = c0 + j;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int row = wave * 32 + 8 * (v >> 2) + 4 * grp + (v & 3);
+        if (row < n && col < a.d) a.U[(int64_t)row * a.ldu + col] = acc[v];
+    }
+}
+
 }  // namespace
 
 namespace {
@@ -325,6 +480,21 @@ hipError_t small_mix(const uint16_t* A16, int64_t ldk, const uint16_t* H, int64_
     a.stat_kind = stat_kind; a.shield_scale = shield_scale; a.n_data = n_data; a.k = k; a.d = d;
     a.S = S; a.U = U; a.ldu = ldu;
     hipLaunchKernelGGL(small_mix_kernel, dim3((unsigned)((d + MIX_BN - 1) / MIX_BN)), dim3(256), 0, stream, a);
+    return hipGetLastError();
+}
+
+hipError_t small_mix_f32(const float* A, int64_t ldk, const float* H, int64_t ldh, const float* GS, const float* gsnorm,
+                         const float* rownorm, int stat_kind, float shield_scale, int n_data, int k, int d,
+                         float* S, float* U, int64_t ldu, hipStream_t stream) {
+    const int n = n_data + k;
+    if (n < 1 || n > kSmallMaxN || k < 1 || d < 8 || d % 8 != 0 || ldk < ((n + 7) & ~7)) return hipErrorInvalidValue;
+    SmallMixF32Args a;
+    a.A = A; a.ldk = ldk; a.H = H; a.ldh = ldh; a.GS = GS; a.gsnorm = gsnorm; a.rownorm = rownorm;
+    a.stat_kind = stat_kind; a.shield_scale = shield_scale; a.n_data = n_data; a.k = k; a.d = d;
+    a.S = S; a.U = U; a.ldu = ldu;
+    const dim3 grid((unsigned)((d + MIX_FN - 1) / MIX_FN));
+    if (rownorm == nullptr) hipLaunchKernelGGL(small_mix_f32_kernel<true>, grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL(small_mix_f32_kernel<false>, grid, dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -569,6 +569,33 @@ def test_prefill_sweep_all_32_layers(ctx):
     print("worst layer", worst)
 
 
+# float batches of at most 128 rows mix in one launch: rows and columns that fill no tile, one to four waves, norms taken there (up to 32 rows and
+# 8192 values) and before, the largest widths; 97 rows of more than 8192 columns keep their launches.  So does a mix over its own H, which
+# gives the same bits.
+@pytest.mark.parametrize("stat", [g.GELO_NORM_MEDIAN, g.GELO_NORM_MEAN])
+@pytest.mark.parametrize("n_data,k,d", [(1, 1, 8), (8, 1, 40), (30, 2, 256), (32, 1, 256), (33, 2, 64), (32, 2, 264), (64, 32, 72), (65, 32, 104),
+                                        (126, 2, 136), (100, 28, 8192), (94, 2, 8200), (95, 2, 8200)])
+def test_small_float_mix(n_data, k, d, stat):
+    n = n_data + k
+    H = torch.randn((n_data, d), generator=torch.Generator(device="cuda").manual_seed(n * d), device="cuda")
+    U = torch.full((n + 2, d), float("nan"), device="cuda")
+    both = torch.full((n, d), float("nan"), device="cuda")
+    both[:n_data] = H
+    again = g.gelo_create(0, 5, allow_batch_reuse=True)
+    for X, out in ((H, U[1:n + 1]), (both[:n_data], both)):
+        m = g.gelo_sample_mixing(again, g.GELO_ORTHOGONAL, n_data, k, d, g.GELO_F32, 0.0, 1, batch_id=9)
+        g.gelo_mix(again, m, X, out, stat=stat)
+        A, _, S, _, _ = g.gelo_mixing_export(again, m, n, k, d)
+        torch.cuda.synchronize()
+        g.gelo_mixing_free(again, m)
+    g.gelo_destroy(again)
+    assert torch.isnan(U[0]).all() and torch.isnan(U[-1]).all() and torch.equal(U[1:n + 1], both)
+    target = 10.0 * o.row_norm_statistic(f64(H), stat)
+    assert np.abs(np.linalg.norm(f64(S), axis=1) / target - 1).max() < 1e-5
+    left, right = A.double(), torch.cat([H, S]).double()
+    assert bool(((U[1:n + 1].double() - left @ right).abs() <= (n + 2) * 2.0 ** -24 * (left.abs() @ right.abs())).all())
+
+
 def test_decode_sweep_one_full_step(ctx):
     """One step of the decode-shaped config: 32 layers, 64 tokens + 4 shield rows each, a fresh orthogonal
     68 x 68 A per layer-step with batch id = step * 32 + layer, 32 resident weights.  Every layer-step by
