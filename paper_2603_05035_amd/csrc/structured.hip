@@ -239,21 +239,20 @@ constexpr int table_pieces(int cw) { return cw == 4 ? 4 : cw == 8 ? 2 : 1; }
 // and writes the rows back in place: the permutation between two rounds costs no pass of its own and the
 // first pass of every round no trip through LDS.  The table of the next step is fetched from memory before
 // the passes of a round and parked in LDS behind them.
+// Workgroup `block` of those that share the columns from first_col to end_col.
 template <typename T, int CW>
-__global__ __launch_bounds__(kThreads)
-void structured_apply_kernel(StructuredArgs a) {
+__device__ __forceinline__ void apply_strip(const StructuredArgs& a, float4* X, int first_col, int end_col, int block) {
     constexpr int QW = CW / 4;
-    extern __shared__ float4 X[];
     const int tid = threadIdx.x, n = a.n, R = a.rounds;
     const int np = (n + 3) & ~3;                             // words per table
     uint32_t* tbl = reinterpret_cast<uint32_t*>(X + (size_t)lds_row(((n + 15) & ~15)) * QW);
     // consecutive strips go to consecutive workgroups of ONE accelerator die (workgroups are dealt
     // round-robin over the 8 dies): neighbours in a row share cache lines of the operand
-    const int nstrips = (a.ncols + CW - 1) / CW, per_die = (nstrips + 7) / 8;
-    const int strip = (blockIdx.x & 7) * per_die + (blockIdx.x >> 3);
+    const int nstrips = (end_col - first_col + CW - 1) / CW, per_die = (nstrips + 7) / 8;
+    const int strip = (block & 7) * per_die + (block >> 3);
     if (strip >= nstrips) return;
-    const int col0 = strip * CW;
-    const int quads = min(QW, (a.ncols - col0) / 4);         // a ragged last strip has fewer
+    const int col0 = first_col + strip * CW;
+    const int quads = min(QW, (end_col - col0) / 4);         // a ragged last strip has fewer
     // table of step s: forward table s; transposed the inverse table R - s (they lie behind the R + 1 forward ones)
     auto table_of = [&](int s) { return a.table + (int64_t)(a.inverse ? (R + 1) + (R - s) : s) * np; };
 
@@ -365,6 +364,23 @@ void structured_apply_kernel(StructuredArgs a) {
     }
 }
 
+template <typename T, int CW>
+__global__ __launch_bounds__(kThreads)
+void structured_apply_kernel(StructuredArgs a) {
+    extern __shared__ float4 X[];
+    apply_strip<T, CW>(a, X, 0, a.ncols, blockIdx.x);
+}
+
+// whole rounds of strips of CW columns (wide_cols of them, a multiple of 8 CW), then strips of half the width
+template <typename T, int CW>
+__global__ __launch_bounds__(kThreads)
+void structured_apply_tail_kernel(StructuredArgs a, int wide_cols) {
+    extern __shared__ float4 X[];
+    const int wide = wide_cols / CW;
+    if ((int)blockIdx.x < wide) apply_strip<T, CW>(a, X, 0, wide_cols, blockIdx.x);
+    else apply_strip<T, CW / 2>(a, X, wide_cols, a.ncols, blockIdx.x - wide);
+}
+
 int g_lds_cap = 0;                 // bytes of LDS one workgroup may use (set by structured_init)
 
 template <typename T, int CW>
@@ -374,9 +390,28 @@ hipError_t allow_lds() {
 }
 
 template <typename T, int CW>
+hipError_t allow_tail_lds() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&structured_apply_tail_kernel<T, CW>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, g_lds_cap);
+}
+
+template <typename T, int CW>
 hipError_t launch_apply(const StructuredArgs& a, size_t lds, hipStream_t s) {
     const int nstrips = (a.ncols + CW - 1) / CW;
     hipLaunchKernelGGL((structured_apply_kernel<T, CW>), dim3(((nstrips + 7) / 8) * 8), dim3(kThreads), lds, s, a);
+    return hipGetLastError();
+}
+
+// One workgroup per CU (what it needs of the LDS leaves no room for a second one) and a last round of at most half of them: that round as
+// twice as many strips of half the width.  unmix, us: 2150 x 22016 (5 rounds and 96 strips) 185 -> 180, 2150 x 4608 (1 and 32) 62.8 -> 57.6, 2150 x 6144 (1
+// and 128) 63.7 -> 59.4, float 2150 x 22016 242 -> 229.  With 8 columns taken as 4 it was 1 to 3% (3000 x 2560 58.9, 58.3): not done.
+constexpr int kCus = 256;
+template <typename T, int CW>
+hipError_t launch_in_rounds(const StructuredArgs& a, size_t lds, hipStream_t s) {
+    const int nstrips = (a.ncols + CW - 1) / CW, left = nstrips % kCus;
+    if (2 * lds <= (size_t)g_lds_cap || nstrips < kCus || left == 0 || left > kCus / 2) return launch_apply<T, CW>(a, lds, s);
+    const int wide = nstrips - left, wide_cols = wide * CW, narrow = (a.ncols - wide_cols + CW / 2 - 1) / (CW / 2);
+    hipLaunchKernelGGL((structured_apply_tail_kernel<T, CW>), dim3(wide + ((narrow + 7) / 8) * 8), dim3(kThreads), lds, s, a, wide_cols);
     return hipGetLastError();
 }
 
@@ -398,7 +433,7 @@ template <typename T>
 hipError_t dispatch_apply(const StructuredArgs& a, hipStream_t s) {
     size_t lds;
     if (a.n <= 512 && a.ncols >= 2048 && (lds = strip_lds_bytes(a.n, 64)) != 0) return launch_apply<T, 64>(a, lds, s);
-    if ((lds = strip_lds_bytes(a.n, 16)) != 0) return launch_apply<T, 16>(a, lds, s);
+    if ((lds = strip_lds_bytes(a.n, 16)) != 0) return launch_in_rounds<T, 16>(a, lds, s);
     if ((lds = strip_lds_bytes(a.n, 8)) != 0) return launch_apply<T, 8>(a, lds, s);
     if ((lds = strip_lds_bytes(a.n, 4)) != 0) return launch_apply<T, 4>(a, lds, s);
     return hipErrorInvalidValue;
@@ -421,6 +456,8 @@ hipError_t structured_init() {
     if ((e = allow_lds<float, 4>()) != hipSuccess) return e;
     if ((e = allow_lds<uint16_t, 16>()) != hipSuccess) return e;
     if ((e = allow_lds<uint16_t, 8>()) != hipSuccess) return e;
+    if ((e = allow_tail_lds<float, 16>()) != hipSuccess) return e;
+    if ((e = allow_tail_lds<uint16_t, 16>()) != hipSuccess) return e;
     return allow_lds<uint16_t, 4>();
 }
 

@@ -186,6 +186,29 @@ def test_structured_kind_rejects_what_it_cannot_hold(ctx):
     assert g.STATUS_NAMES[e.value.status] == "GELO_ESHAPE"
 
 
+# whole rounds of 256 strips of 16 columns, the rest (up to 128 of them) as strips of 8 where one workgroup fills a CU's LDS: columns do not
+# depend on the strips they lie in, so a call's last columns are those of a call with one round of strips, bit for bit
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("n,left", [(2150, 8), (2150, 16), (2150, 24), (2150, 2040), (2150, 2048), (2150, 2056), (2272, 136), (1200, 136), (1000, 136)])
+def test_last_round_in_narrow_strips(n, left, dtype):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + left)
+    Y = torch.randn((n, 4096 + left), generator=gen, device="cuda").to(dtype)
+    Z = torch.full((n + 1, 4096 + left), float("nan"), device="cuda", dtype=dtype)
+    again = g.gelo_create(0, 3, allow_batch_reuse=True)
+    m = g.gelo_sample_mixing(again, g.GELO_STRUCTURED, n, 0, 64, g.GELO_F32 if dtype == torch.float32 else g.GELO_BF16, batch_id=1)
+    g.gelo_mix(again, m, Y[:, :64].contiguous(), torch.empty((n, 64), device="cuda", dtype=dtype))
+    g.gelo_unmix(again, m, Y, Z[:n])
+    for first in (0, left):
+        part = torch.empty((n, 4096), device="cuda", dtype=dtype)
+        g.gelo_unmix(again, m, Y[:, first:first + 4096].contiguous(), part)
+        torch.cuda.synchronize()
+        assert torch.equal(Z[:n, first:first + 4096], part)
+    assert torch.isnan(Z[n]).all()
+    g.gelo_mixing_free(again, m)
+    g.gelo_destroy(again)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_strided_operands(ctx, dtype):
     """Leading dimensions larger than the width (views into bigger buffers): the transform must keep to
