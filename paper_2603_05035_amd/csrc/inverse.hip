@@ -307,22 +307,104 @@ void planes_kernel(const float* A, int64_t quads, uint16_t* h, uint16_t* m, uint
 // operators the condition number needs, A and A^-1, share every launch.
 constexpr int kLanczosMax = 32;      // coefficient slots per operator
 
+template <int WAVES>
+__device__ __forceinline__ float block_sum(float v, float* red) {       // the same value in every thread, fixed order
+    v = wave_sum(v);
+    __syncthreads();                                   // red may still be read from the previous call
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) s += red[w];
+    return s;
+}
+
+// Vector `step` of the recurrence, OWN elements per thread (threadIdx.x, + 64 WAVES, ...), by every workgroup of a launch for itself (all the same
+// bits): for step 0 a fixed pseudo-random unit vector, else from x = w = M^T (M v) of vector v, step - 1,
+//   alpha = w . v, r = w - alpha v - beta_prev v_prev, beta = |r|, x = r / beta; tr[0][step - 1] = alpha, tr[1][step - 1] = beta.
+// Vector j lies in slot j % 3, where the caller's first workgroup (`writes`) keeps it: nobody writes what others of the launch still read.
+// `before`: the two vectors ahead of it, asked for before x is formed.
+template <int OWN, int WAVES>
+struct LanczosBefore {
+    float v[OWN], v_prev[OWN], beta;
+    __device__ __forceinline__ LanczosBefore(const float* slots, int64_t ld, int n, const float* tr, int step) {
+        const float* p = slots + (int64_t)((step + 2) % 3) * ld;             // vector step - 1
+        const float* q = slots + (int64_t)((step + 1) % 3) * ld;             // vector step - 2
+#pragma unroll
+        for (int k = 0; k < OWN; ++k) {
+            const int i = threadIdx.x + 64 * WAVES * k;
+            v[k] = i < n && step > 0 ? p[i] : 0.f;
+            v_prev[k] = i < n && step > 1 ? q[i] : 0.f;
+        }
+        beta = step > 1 ? tr[kLanczosMax + step - 2] : 0.f;
+    }
+};
+template <int OWN, int WAVES>
+__device__ __forceinline__ void next_vector(float (&x)[OWN], const LanczosBefore<OWN, WAVES>& before, int n, float* tr, int step, bool writes, float* red) {
+    constexpr int THREADS = 64 * WAVES;
+    const int tid = threadIdx.x;
+    if (step == 0) {
+        float ss = 0.f;
+#pragma unroll
+        for (int k = 0; k < OWN; ++k) {
+            const int i = tid + THREADS * k;
+            uint32_t h = (uint32_t)i * 2654435761u + 0x9E3779B9u;   // fixed pseudo-random signs and sizes
+            h ^= h >> 15; h *= 2246822519u; h ^= h >> 13;
+            x[k] = i < n ? ((h & 1u) ? 1.f : -1.f) * (0.5f + (float)((h >> 8) & 0xFFFF) * (1.0f / 65536.0f)) : 0.f;
+            ss = fmaf(x[k], x[k], ss);
+        }
+        const float inv = rsqrtf(block_sum<WAVES>(ss, red));
+#pragma unroll
+        for (int k = 0; k < OWN; ++k) x[k] *= inv;
+        return;
+    }
+    float dot = 0.f;
+#pragma unroll
+    for (int k = 0; k < OWN; ++k) dot = fmaf(x[k], before.v[k], dot);
+    const float alpha = block_sum<WAVES>(dot, red);
+    float ss = 0.f;
+#pragma unroll
+    for (int k = 0; k < OWN; ++k) {
+        x[k] = fmaf(-before.beta, before.v_prev[k], fmaf(-alpha, before.v[k], x[k]));
+        ss = fmaf(x[k], x[k], ss);
+    }
+    const float beta = sqrtf(block_sum<WAVES>(ss, red));
+    const float inv = beta > 0.f ? 1.0f / beta : 0.f;
+#pragma unroll
+    for (int k = 0; k < OWN; ++k) x[k] *= inv;
+    if (writes && tid == 0) { tr[step - 1] = alpha; tr[kLanczosMax + step - 1] = beta; }
+}
+
 // M^T (M v) for M = A (grid y 0) and A^-1 (1), every row read once: a wave holds a row in registers, takes its product with v and adds
-// that many times the row to its sum; the workgroup's sum goes to part[workgroup][ld].  CH: blocks of 256 columns (n <= 256 CH).
+// that many times the row to its sum; the workgroup's sum goes to part[workgroup][ld].  The vector itself is formed first, by every workgroup.  CH: blocks of 256 columns (n <= 256 CH).
 // Bound by the last-level cache: 4 n^2 bytes per operator.  With a product by rows of M and one by rows of a transposed copy
 // (8 n^2, and more than the 256 MB the cache holds at 4096 rows) a Lanczos step took 62 us at 4096 rows, now 36; the whole
-// condition estimate 1.32 ms, now 0.74.
-constexpr int kProductGroups = 128;                    // workgroups per operator, at most
+// condition estimate 1.32 ms, then 0.74; with the vector formed here instead of in a launch of its own between the products a draw of 1025 rows
+// went from 1120 to 1060 us, of 4096 from 5819 to 5718.
+constexpr int kProductGroups = 128;                    // workgroups per operator
 
 template <int CH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2)))
-void normal_product_kernel(const float* Ma, const float* va, float* pa, const float* Mb, const float* vb, float* pb, int64_t lda, int64_t ld, int n) {
+void normal_product_kernel(const float* Ma, const float* Mb, float* pa, float* pb, int64_t w_at, float* vec, int64_t lda, int64_t ld, int n, float* tri, int step, int steps) {
     __shared__ __attribute__((aligned(16))) float vs[CH * 256];
+    __shared__ float red[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float* M = blockIdx.y ? Mb : Ma;
-    const float* v = blockIdx.y ? vb : va;
+    const float* w = (blockIdx.y ? pb : pa) + w_at;
+    float* slots = vec + (int64_t)blockIdx.y * 3 * ld;
     float* part = (blockIdx.y ? pb : pa) + (int64_t)blockIdx.x * ld;
-    for (int c = tid; c < CH * 256; c += 256) vs[c] = c < n ? v[c] : 0.f;
+    float* tr = tri + blockIdx.y * 2 * kLanczosMax;
+    const LanczosBefore<CH, 4> before(slots, ld, n, tr, step);
+    float v[CH];
+#pragma unroll
+    for (int k = 0; k < CH; ++k) v[k] = step > 0 && tid + 256 * k < n ? w[tid + 256 * k] : 0.f;
+    next_vector<CH, 4>(v, before, n, tr, step, blockIdx.x == 0, red);
+    if (step == steps) return;
+#pragma unroll
+    for (int k = 0; k < CH; ++k) {
+        vs[tid + 256 * k] = v[k];
+        if (blockIdx.x == 0 && tid + 256 * k < n) slots[(int64_t)(step % 3) * ld + tid + 256 * k] = v[k];
+    }
     __syncthreads();
     f32x4_t sum[CH];
 #pragma unroll
@@ -377,78 +459,6 @@ void sum_parts_kernel(const float* pa, float* wa, const float* pb, float* wb, in
     if (wave == 0 && c < n) (blockIdx.y ? wb : wa)[c] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
 }
 
-// sum over the 1024 threads of a workgroup, the same value in every thread, fixed order
-__device__ __forceinline__ float block_sum_1024(float v, float* red) {
-    v = wave_sum(v);
-    __syncthreads();                                   // red may still be read from the previous call
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float s = 0.f;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) s += red[w];
-    return s;
-}
-
-constexpr int kVecPerThread = kMaxN / 1024;            // 5
-
-// Workgroup o (0: A, 1: A^-1) owns the vectors at vec + o * 3 * ld: v, v_prev, w = M^T (M v).
-// step < 0: v = a fixed pseudo-random unit vector, v_prev = 0.
-// step >= 0: alpha = w . v, r = w - alpha v - beta_prev v_prev, beta = |r|, v_prev = v, v = r / beta;
-//            tri[o][0][step] = alpha, tri[o][1][step] = beta.
-__global__ __launch_bounds__(1024)
-void lanczos_vector_kernel(float* vec, int64_t ld, int n, float* tri, int step) {
-    __shared__ float red[16];
-    const int tid = threadIdx.x, o = blockIdx.x;
-    float* v = vec + (int64_t)o * 3 * ld;
-    float* vp = v + ld;
-    const float* w = v + 2 * ld;
-    float* tr = tri + o * 2 * kLanczosMax;
-    float x[kVecPerThread], xp[kVecPerThread], r[kVecPerThread];
-    if (step < 0) {
-        float ss = 0.f;
-#pragma unroll
-        for (int k = 0; k < kVecPerThread; ++k) {
-            const int i = tid + 1024 * k;
-            uint32_t h = (uint32_t)i * 2654435761u + 0x9E3779B9u;   // fixed pseudo-random signs and sizes
-            h ^= h >> 15; h *= 2246822519u; h ^= h >> 13;
-            x[k] = i < n ? ((h & 1u) ? 1.f : -1.f) * (0.5f + (float)((h >> 8) & 0xFFFF) * (1.0f / 65536.0f)) : 0.f;
-            ss = fmaf(x[k], x[k], ss);
-        }
-        const float inv = rsqrtf(block_sum_1024(ss, red));
-#pragma unroll
-        for (int k = 0; k < kVecPerThread; ++k) {
-            const int i = tid + 1024 * k;
-            if (i < n) { v[i] = x[k] * inv; vp[i] = 0.f; }
-        }
-        return;
-    }
-    float dot = 0.f;
-#pragma unroll
-    for (int k = 0; k < kVecPerThread; ++k) {
-        const int i = tid + 1024 * k;
-        x[k] = i < n ? v[i] : 0.f;
-        xp[k] = i < n ? vp[i] : 0.f;
-        r[k] = i < n ? w[i] : 0.f;
-        dot = fmaf(r[k], x[k], dot);
-    }
-    const float alpha = block_sum_1024(dot, red);
-    const float beta_prev = step > 0 ? tr[kLanczosMax + step - 1] : 0.f;
-    float ss = 0.f;
-#pragma unroll
-    for (int k = 0; k < kVecPerThread; ++k) {
-        r[k] = fmaf(-beta_prev, xp[k], fmaf(-alpha, x[k], r[k]));
-        ss = fmaf(r[k], r[k], ss);
-    }
-    const float beta = sqrtf(block_sum_1024(ss, red));
-    const float inv = beta > 0.f ? 1.0f / beta : 0.f;
-#pragma unroll
-    for (int k = 0; k < kVecPerThread; ++k) {
-        const int i = tid + 1024 * k;
-        if (i < n) { vp[i] = x[k]; v[i] = r[k] * inv; }
-    }
-    if (tid == 0) { tr[step] = alpha; tr[kLanczosMax + step] = beta; }
-}
-
 // The same steps with one launch each, for small matrices: every workgroup forms the sum of the parts and the next vector itself (all the
 // same bits) before its rows of the product.  Launch j < steps leaves the parts of product j, launch `steps` the last coefficients; vector
 // j lies in slot j % 3, the parts of even and odd products in either half, so that nobody writes what others of the launch still read.
@@ -460,17 +470,6 @@ constexpr int kFusedGroups = 32;                       // workgroups per operato
 constexpr int kFusedMaxN = 1024;
 
 constexpr int kFusedWaves = 8, kFusedThreads = 64 * kFusedWaves;
-
-__device__ __forceinline__ float block_sum_512(float v, float* red) {
-    v = wave_sum(v);
-    __syncthreads();                                   // red may still be read from the previous call
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float s = 0.f;
-#pragma unroll
-    for (int w = 0; w < kFusedWaves; ++w) s += red[w];
-    return s;
-}
 
 template <int CH>
 __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -489,38 +488,16 @@ void lanczos_step_kernel(const float* Ma, const float* Mb, float* pa, float* pb,
     float* parts = o ? pb : pa;
     float* slots = vec + (int64_t)o * 3 * ld;
     float* tr = tri + o * 2 * kLanczosMax;
+    const LanczosBefore<OWN, kFusedWaves> before(slots, ld, n, tr, step);
     float x[OWN];
-    if (step == 0) {
-        float ss = 0.f;
-#pragma unroll
-        for (int k = 0; k < OWN; ++k) {
-            const int i = tid + kFusedThreads * k;
-            uint32_t h = (uint32_t)i * 2654435761u + 0x9E3779B9u;   // as lanczos_vector_kernel's first vector
-            h ^= h >> 15; h *= 2246822519u; h ^= h >> 13;
-            x[k] = i < n ? ((h & 1u) ? 1.f : -1.f) * (0.5f + (float)((h >> 8) & 0xFFFF) * (1.0f / 65536.0f)) : 0.f;
-            ss = fmaf(x[k], x[k], ss);
-        }
-        const float inv = rsqrtf(block_sum_512(ss, red));
-#pragma unroll
-        for (int k = 0; k < OWN; ++k) x[k] *= inv;
-    } else {
-        const float* before = parts + (int64_t)((step - 1) & 1) * groups * ld;
-        const float* v = slots + (int64_t)((step - 1) % 3) * ld;
-        const float* vp = slots + (int64_t)((step + 1) % 3) * ld;            // vector step - 2
-        const float beta_prev = step > 1 ? tr[kLanczosMax + step - 2] : 0.f;
-        float y[OWN], yp[OWN];
-#pragma unroll
-        for (int k = 0; k < OWN; ++k) {
-            const int i = tid + kFusedThreads * k;
-            y[k] = i < n ? v[i] : 0.f;
-            yp[k] = i < n && step > 1 ? vp[i] : 0.f;
-        }
+    if (step > 0) {
+        const float* last = parts + (int64_t)((step - 1) & 1) * groups * ld;
         {
             const int q = tid % QUADS, set = tid / QUADS;
             const int at = 4 * q < (int)ld ? 4 * q : 0;
             f32x4_t p[PER], s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int i = 0; i < PER; ++i) p[i] = *reinterpret_cast<const f32x4_t*>(before + (int64_t)(set * PER + i < groups ? set * PER + i : 0) * ld + at);
+            for (int i = 0; i < PER; ++i) p[i] = *reinterpret_cast<const f32x4_t*>(last + (int64_t)(set * PER + i < groups ? set * PER + i : 0) * ld + at);
 #pragma unroll
             for (int i = 0; i < PER; ++i)
 #pragma unroll
@@ -528,7 +505,6 @@ void lanczos_step_kernel(const float* Ma, const float* Mb, float* pa, float* pb,
             *reinterpret_cast<f32x4_t*>(&sums[set][4 * q]) = s;
         }
         __syncthreads();
-        float dot = 0.f;
 #pragma unroll
         for (int k = 0; k < OWN; ++k) {
             const int i = tid + kFusedThreads * k;
@@ -537,21 +513,9 @@ void lanczos_step_kernel(const float* Ma, const float* Mb, float* pa, float* pb,
 #pragma unroll
                 for (int t = 0; t < SETS; ++t) x[k] += sums[t][i];
             }
-            dot = fmaf(x[k], y[k], dot);
         }
-        const float alpha = block_sum_512(dot, red);
-        float ss = 0.f;
-#pragma unroll
-        for (int k = 0; k < OWN; ++k) {
-            x[k] = fmaf(-beta_prev, yp[k], fmaf(-alpha, y[k], x[k]));
-            ss = fmaf(x[k], x[k], ss);
-        }
-        const float beta = sqrtf(block_sum_512(ss, red));
-        const float inv = beta > 0.f ? 1.0f / beta : 0.f;
-#pragma unroll
-        for (int k = 0; k < OWN; ++k) x[k] *= inv;
-        if (blockIdx.x == 0 && tid == 0) { tr[step - 1] = alpha; tr[kLanczosMax + step - 1] = beta; }
     }
+    next_vector<OWN, kFusedWaves>(x, before, n, tr, step, blockIdx.x == 0, red);
     if (step == steps) return;
 #pragma unroll
     for (int k = 0; k < OWN; ++k) {
@@ -748,10 +712,6 @@ hipError_t kappa_estimate(const float* A, const float* Ainv, int64_t lda, int n,
     const int64_t ld = ws.ld;
     if (steps < 1 || steps > kLanczosMax) return hipErrorInvalidValue;
     if (steps > n) steps = n;
-    const int groups = (n + 3) / 4 < kProductGroups ? (n + 3) / 4 : kProductGroups;
-    // the workgroups' sums go to the (now free) factorisation buffers, `groups` rows of each
-    float* va = ws.vec;            float* wa = va + 2 * ld;
-    float* vi = ws.vec + 3 * ld;   float* wi = vi + 2 * ld;
     if (n <= kFusedMaxN) {
         // (two halves of at most n / 8 + 1 rows of ld each)
         const int few = (n + kFusedWaves - 1) / kFusedWaves < kFusedGroups ? (n + kFusedWaves - 1) / kFusedWaves : kFusedGroups;
@@ -768,21 +728,21 @@ hipError_t kappa_estimate(const float* A, const float* Ainv, int64_t lda, int n,
         hipLaunchKernelGGL(lanczos_finish_kernel, dim3(1), dim3(64), 0, s, ws.tri, steps, ws.scalars);
         return hipGetLastError();
     }
-    auto product = [&](auto chc) {
-        hipLaunchKernelGGL((normal_product_kernel<decltype(chc)::value>), dim3(groups, 2), dim3(256), 0, s, A, va, ws.M, Ainv, vi, ws.X, lda, ld, n);
-        return hipGetLastError();
-    };
-    hipLaunchKernelGGL(lanczos_vector_kernel, dim3(2), dim3(1024), 0, s, ws.vec, ld, n, ws.tri, -1);
-    GELO_TRY(hipGetLastError());
-    for (int j = 0; j < steps; ++j) {
-        // w = M^T (M v) for M = A and M = Ainv, then one step of the recurrence for both
+    // the workgroups' sums go to the (now free) factorisation buffers, kProductGroups rows of each, their sum behind them
+    const int64_t w_at = (int64_t)kProductGroups * ld;
+    for (int j = 0; j <= steps; ++j) {
+        // the next vector, w = M^T (M v) for M = A and M = Ainv
+        auto product = [&](auto chc) {
+            hipLaunchKernelGGL((normal_product_kernel<decltype(chc)::value>), dim3(j < steps ? kProductGroups : 1, 2), dim3(256), 0, s, A, Ainv, ws.M, ws.X, w_at, ws.vec, lda, ld, n,
+                               ws.tri, j, steps);
+            return hipGetLastError();
+        };
         if (n <= 2048) GELO_TRY(product(std::integral_constant<int, 8>{}));
         else if (n <= 3072) GELO_TRY(product(std::integral_constant<int, 12>{}));
         else if (n <= 4096) GELO_TRY(product(std::integral_constant<int, 16>{}));
         else GELO_TRY(product(std::integral_constant<int, 20>{}));
-        hipLaunchKernelGGL(sum_parts_kernel, dim3((n + 63) / 64, 2), dim3(256), 0, s, ws.M, wa, ws.X, wi, ld, n, groups);
-        GELO_TRY(hipGetLastError());
-        hipLaunchKernelGGL(lanczos_vector_kernel, dim3(2), dim3(1024), 0, s, ws.vec, ld, n, ws.tri, j);
+        if (j == steps) break;
+        hipLaunchKernelGGL(sum_parts_kernel, dim3((n + 63) / 64, 2), dim3(256), 0, s, ws.M, ws.M + w_at, ws.X, ws.X + w_at, ld, n, kProductGroups);
         GELO_TRY(hipGetLastError());
     }
     hipLaunchKernelGGL(lanczos_finish_kernel, dim3(1), dim3(64), 0, s, ws.tri, steps, ws.scalars);
