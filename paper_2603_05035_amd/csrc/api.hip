@@ -719,7 +719,10 @@ gelo_status gelo_sample_mixing(gelo_ctx* ctx, gelo_kind kind, int n_data, int k_
 
 // Float batches whose mix is one launch: beyond kSmallMixCols columns four waves of float products per workgroup are more than one per
 // CU, and the launches apart are faster (122 + 6 rows of 11008: 17.2 us against 18.7; 90 + 5 15.2 and 14.5; of 8192 all rows win).
-constexpr int kSmallMixRows = 96, kSmallMixCols = 32 * 256;
+// From kSmallMixEnd on the product apart has a 128 x 128 tile per CU and takes its operands apart for the bf16 instructions (gemm_f32),
+// which is more exact than the float instructions here (64 + 4 rows of 32768: 5.0e-8 and 6.8e-8 from 64 bits, 90 + 5 5.8e-8 and 8.2e-8) and, with many
+// rows, faster (90 + 5 rows of 40960: 28.0 us, 32.5; 64 + 4 25.2 and 24.4; of 32640, on the float instructions in both, 28.3 and 26.0).
+constexpr int kSmallMixRows = 96, kSmallMixCols = 32 * 256, kSmallMixEnd = 255 * 128 + 1;
 // Row norms in the mix itself: one round of reads per wave (eight rows each) of what the mix reads again (64 rows of 64: 10.5 us, with a
 // launch of their own 8.4; 32 of 256 7.5 and 8.5)
 constexpr int kNormsInMixRows = 32;
@@ -741,7 +744,7 @@ static gelo_status mix_launch(gelo_ctx* ctx, gelo_mixing* m, const void* H, int6
         const char* u0 = (const char*)U;
         return u0 + ((size_t)(m->n - 1) * ldu + m->d) * 4 <= h0 || h0 + ((size_t)(m->n_data - 1) * ldh + m->d) * 4 <= u0;
     };
-    if (!bf && m->k > 0 && !m->structured && !m->blocked && (m->n <= kSmallMixRows || (m->n <= kSmallMaxN && m->d <= kSmallMixCols)) && apart()) {
+    if (!bf && m->k > 0 && !m->structured && !m->blocked && m->n <= kSmallMaxN && m->d < (m->n <= kSmallMixRows ? kSmallMixEnd : kSmallMixCols + 1) && apart()) {
         // The same in float, unless U overwrites H while other workgroups read it (without shields the product is one launch as it is).
         // The norms of few rows and values are taken there too.
         const bool norms_there = m->n_data <= kNormsInMixRows && (size_t)m->n_data * m->d <= kNormsInMixValues;

@@ -596,6 +596,23 @@ def test_small_float_mix(n_data, k, d, stat):
     assert bool(((U[1:n + 1].double() - left @ right).abs() <= (n + 2) * 2.0 ** -24 * (left.abs() @ right.abs())).all())
 
 
+# where the product of the mix gets a 128 x 128 tile per CU, beyond 32640 columns, it takes its operands apart, in one launch with the shield rows
+# or not: the bits of that product by itself on either side of the line
+@pytest.mark.parametrize("n_data,k", [(7, 1), (67, 5), (91, 5)])
+@pytest.mark.parametrize("d", [32640, 32648])
+def test_small_float_mix_of_wide_rows_is_the_product(ctx, n_data, k, d):
+    n = n_data + k
+    H = torch.randn((n_data, d), generator=torch.Generator(device="cuda").manual_seed(n + d), device="cuda")
+    U, again = torch.empty((n, d), device="cuda"), torch.empty((n, d), device="cuda")
+    m = g.gelo_sample_mixing(ctx, g.GELO_ORTHOGONAL, n_data, k, d, g.GELO_F32, 0.0, 1, batch_id=9)
+    g.gelo_mix(ctx, m, H, U)
+    A, _, S, _, _ = g.gelo_mixing_export(ctx, m, n, k, d)
+    g.gelo_project(ctx, A, torch.cat([H, S]), again)
+    torch.cuda.synchronize()
+    g.gelo_mixing_free(ctx, m)
+    assert torch.equal(U, again)
+
+
 def test_decode_sweep_one_full_step(ctx):
     """One step of the decode-shaped config: 32 layers, 64 tokens + 4 shield rows each, a fresh orthogonal
     68 x 68 A per layer-step with batch id = step * 32 + layer, 32 resident weights.  Every layer-step by
