@@ -202,8 +202,8 @@ void gemm_f32_kernel(F32Args g) {
         }
 }
 
-// M <= 128 and K <= 128 (K a multiple of 16) where C meets an operand (a caller's un-mix into its Y).  One 128 x 128 tile per 128 columns would leave most of the chip idle and each
-// tile bound by the float MFMA rate of its one CU, so the tiles here are 128 x 32 (four times as
+// M <= 128 and K <= 128 (K a multiple of 16) where C meets B (a caller's un-mix into its Y).  One 128 x 128 tile per 128 columns would leave
+// most of the chip idle and each tile bound by the float MFMA rate of its one CU, so the tiles here are 128 x 32 (four times as
 // many workgroups, a wave owns 32 x 32), and with so few K steps both panels of the tile are
 // fetched at once (all loads in flight together) and stored to LDS behind ONE barrier.
 constexpr int SN = 32;             // tile width
@@ -556,10 +556,12 @@ hipError_t gemm_f32(const GemmOperands& o, hipStream_t stream) {
         return ld != o.ldc || behind < (intptr_t)(o.N * sizeof(float)) || behind + (intptr_t)(cols * sizeof(float)) > pitch;
     };
     const int tiles = a.tiles_m * ((o.N + kTileM - 1) / kTileM);
-    const bool in_place = tiles < kCus && (meets_c(o.A, o.lda, o.M, o.K) || meets_c(o.B0, o.ldb0, std::min(o.K0, o.K), o.N) || meets_c(o.B1, o.ldb1, o.K - o.K0, o.N));
-    if (in_place && o.M <= kTileM && o.K <= 128 && o.K % 16 == 0 && o.K0 >= o.K) {
-        // (where C meets no operand 64 x 64 tiles are faster at every size: 16 x 192 x 16 3.3 us against 4.9, 128 x 4096 x 128 7.7 and 8.4,
-        // 128 x 12288 x 128 10.4 and 15.0)
+    const bool over_a = meets_c(o.A, o.lda, o.M, o.K);
+    const bool in_place = tiles < kCus && (over_a || meets_c(o.B0, o.ldb0, std::min(o.K0, o.K), o.N) || meets_c(o.B1, o.ldb1, o.K - o.K0, o.N));
+    if (in_place && !over_a && o.M <= kTileM && o.K <= 128 && o.K % 16 == 0 && o.K0 >= o.K) {
+        // (not over A: every tile reads all of it.)  Against 128 x 128 tiles, us: 16 x 1024 x 16 4.5 and 6.9, 128 x 64 x 128 7.3 and 15.6, 128 x 4096 x 128
+        // 8.0 and 16.1, 128 x 12288 x 128 14.4 and 17.0; only beyond does one round of large tiles win, 128 x 22016 x 128 21.1 and 17.5.  Where C meets no
+        // operand 64 x 64 tiles are faster at every size: 16 x 192 x 16 3.5 us against 4.4, 128 x 12288 x 128 10.2 and 14.4.
         a.tiles_n = (o.N + SN - 1) / SN;
         hipLaunchKernelGGL(gemm_f32_short_kernel, dim3(a.tiles_n), dim3(NT), kShortLds, stream, a);
     } else if (in_place) {

@@ -133,6 +133,20 @@ def test_float_results_in_place_of_their_operands(n_data, k, p):
     g.gelo_destroy(ctx)
 
 
+# the same projection of at most 128 rows and columns, one tile too: narrower ones would each read all of A
+@pytest.mark.parametrize("rows", [1, 5, 64, 128])
+@pytest.mark.parametrize("p", [16, 40, 48, 64, 96, 128])
+def test_float_projection_of_few_rows_into_its_operand(rows, p):
+    gen = torch.Generator(device="cuda").manual_seed(rows + p)
+    X, W, Y = torch.randn((rows, p), generator=gen, device="cuda"), torch.randn((p, p), generator=gen, device="cuda"), torch.empty((rows, p), device="cuda")
+    ctx = g.gelo_create(0, 1)
+    g.gelo_project(ctx, X, W, Y)
+    g.gelo_project(ctx, X, W, X)
+    torch.cuda.synchronize()
+    g.gelo_destroy(ctx)
+    assert torch.equal(X, Y)
+
+
 # float products taken apart into bf16 values (256 tiles of 128 x 128 and more; one tile less beside them): rows, columns and K that
 # fill no tile, fragment or step, the fewest k
 @pytest.mark.parametrize("m,k,n", [(2048, 32, 2048), (2047, 40, 2040), (2033, 8, 2048), (1921, 104, 2056), (513, 264, 8200), (130, 1000, 16392), (2048, 64, 1920)])
