@@ -198,8 +198,8 @@ def test_orthogonal_mixing_matrix_at_the_largest_n(ctx):
 
 
 def test_conditioned_inverse_at_the_largest_n(ctx):
-    """n = GELO_MAX_N through the QR and the inverse from it: forty blocks per wave in the strips and panels, forty
-    blocks of 128 in the back substitution.  A^-1 is pinned by what defines it (both products give the identity to
+    """n = GELO_MAX_N through the QR (forty blocks per wave in the strips and panels) and the iteration for the inverse.
+    A^-1 is pinned by what defines it (both products give the identity to
     float rounding times n), the condition estimate by the bounds of the construction
     (singular values within 1 +- 2 * 0.25 up to fluctuations) and by ||A||_2 ||A^-1||_2 from a few
     float64 power iterations on the exported matrices."""
@@ -458,9 +458,9 @@ def test_conditioned_matrix_construction(ctx):
 
 @pytest.mark.parametrize("n", [16, 130, 928, 1100, 2070])
 def test_pivoted_lu_inverse_across_block_boundaries(ctx, n):
-    """The explicit inverse behind the non-orthogonal kinds (R^-1 Q^T from the QR, where a pivoted LU stood), at one
-    tile, just beyond the 128 rows of the one-launch inverse (a block of 128 and a broken tile), and with 8, 9 and 17
-    blocks of 128, the last one broken: A^-1 against the float64 inverse of the SAME matrix, the residual of
+    """The explicit inverse behind the non-orthogonal kinds, at one tile, just beyond the 128 rows of the one-launch
+    inverse and at sizes of 8, 9 and 17 blocks of 128 rows, the last one broken: A^-1 (R^-1 Q^T from the QR, block by block, for
+    GAUSSIAN; Newton's iteration for CONDITIONED beyond 128 rows) against the float64 inverse of the SAME matrix, the residual of
     the product, and the condition estimate against numpy's."""
     for kind, cond_max in ((g.GELO_CONDITIONED, 0.0), (g.GELO_GAUSSIAN, 1e12)):
         if kind == g.GELO_GAUSSIAN and n > 1000:

@@ -129,8 +129,8 @@ def test_factorisation_of_columns_of_zeros(zeros):
     assert bool((diagonal[zeros] == 0).all()) and int((diagonal == 0).sum()) == len(zeros)
 
 
-# A^-1 = R^-1 Q^T by blocks of 128: whole and broken blocks and tiles.  kappa(A) is 2 to 4 here; a backward stable inverse
-# leaves A A^-1 = I to kappa c sqrt(n) roundings (rows scaled to 1)
+# The kind's inverse at all sizes, up to 128 rows from the QR factors in one launch, beyond by Newton's iteration.  kappa(A) is 2 to 4 here; a
+# backward stable inverse leaves A A^-1 = I to kappa c sqrt(n) roundings (rows scaled to 1)
 @pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 64, 65, 127, 128, 129, 144, 255, 256, 257, 400, 641, 721, 1301])
 def test_inverse_of_a_conditioned_matrix(ctx, n):
     m = g.gelo_sample_mixing(ctx, g.GELO_CONDITIONED, n, 0, 64, g.GELO_F32, 1e3, 64, batch_id=n)
@@ -145,10 +145,135 @@ def test_inverse_of_a_conditioned_matrix(ctx, n):
         assert abs(kappa - exact) < 0.02 * exact
 
 
-# CONDITIONED beyond 128 rows (Newton's iteration on bf16 products): rows that fill no K step and no tile, the four tiles (128 x 128, 128 x 256,
-# 256 x 192, 256 x 256), each in one round and more, both pitches beyond n.  In the last product a result takes ceil(n / 32) sums of
-# what is at most 1 behind smaller ones, each rounded once; A^-1 is rounded itself.
-@pytest.mark.parametrize("n,dtype", [(n, g.GELO_F32) for n in (129, 191, 192, 193, 1000, 2048, 2049, 2150, 2817, 3009, 3500, 4097)]
+class Workspace:
+    """A factorisation workspace of the library in memory filled with NaN, through the library's own functions."""
+
+    def __init__(self, n):
+        self.n, self.pad, self.lib = n, (n + 15) // 16 * 16, g.load_library()
+        size = self.lib["_ZN4gelo22factor_workspace_bytesEib"]
+        size.restype, size.argtypes = ctypes.c_size_t, [ctypes.c_int, ctypes.c_bool]
+        carve = self.lib["_ZN4gelo22factor_workspace_carveEPviPNS_15FactorWorkspaceEb"]
+        carve.restype, carve.argtypes = None, [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_bool]
+        self.memory = torch.full((size(n, False) // 4,), float("nan"), device="cuda")
+        self.parts = (ctypes.c_uint64 * 64)()
+        carve(self.memory.data_ptr(), n, self.parts, False)
+
+    def at(self, part, count):
+        first = (self.parts[part] - self.memory.data_ptr()) // 4
+        return self.memory[first:first + count]
+
+    def call(self, name, types, *args):
+        f = self.lib[name]
+        f.restype, f.argtypes = ctypes.c_int, [ctypes.c_void_p, *types, ctypes.c_void_p]
+        assert f(self.parts, *args, torch.cuda.current_stream().cuda_stream) == 0
+
+    def factorise(self, A):
+        """QR of A (n x n), which goes to the first matrix of the workspace: [column of tiles][row][column][row inside]"""
+        tiles = self.pad // 16
+        M = torch.full((self.pad, self.pad), float("nan"), device="cuda")
+        M[:self.n, :self.n] = A
+        self.at(0, self.pad * self.pad).copy_(M.view(tiles, 16, tiles, 16).permute(2, 0, 3, 1).reshape(-1))
+        qr = self.lib["_ZN4gelo14householder_qrERKNS_15FactorWorkspaceEiilP12ihipStream_tb"]
+        qr.restype, qr.argtypes = ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_void_p, ctypes.c_bool]
+        assert qr(self.parts, self.n, 1, 0, torch.cuda.current_stream().cuda_stream, False) == 0
+
+
+# A^-1 = R^-1 Q^T by blocks of 128 rows, which beyond 128 rows only the kind that is drawn again for its condition takes: on well-conditioned
+# matrices (kappa 2 to 4), through the library's own functions, so that a wrong block shows.  One to seventeen blocks, the last one whole, of one row, an
+# odd number, whole tiles; the QR by panels and by blocks of 128 columns; pitches of n and beyond it; with and without the rounded copy
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("n", [129, 144, 191, 192, 255, 256, 257, 400, 641, 721, 1301, 2070])
+def test_inverse_from_the_factors(ctx, n, bf16):             # (ctx: brings the kernels onto the device)
+    ldk = (n + 63) // 64 * 64
+    gen = torch.Generator().manual_seed(n)
+    A = torch.linalg.qr(torch.randn((n, n), generator=gen, dtype=torch.float64))[0] + 0.25 * torch.randn((n, n), generator=gen, dtype=torch.float64) / math.sqrt(n)
+    A = A.float()
+    exact = torch.linalg.inv(A.double())
+    kappa = float(torch.linalg.matrix_norm(A.double(), 2) * torch.linalg.matrix_norm(exact, 2))
+    A, exact = A.cuda(), exact.cuda()
+    ws = Workspace(n)
+    ws.factorise(A)
+    padded = torch.zeros((n, ldk), device="cuda")
+    padded[:, :n] = A
+    out32 = torch.full((n + 1, ldk), float("nan"), device="cuda")
+    out16 = torch.full((n + 1, ldk), float("nan"), device="cuda", dtype=torch.bfloat16)
+    ws.call("_ZN4gelo15inverse_from_qrERKNS_15FactorWorkspaceEiPKflPfPtP12ihipStream_t",
+            [ctypes.c_int, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p],
+            n, padded.data_ptr(), ldk, out32.data_ptr(), out16.data_ptr() if bf16 else None)
+    torch.cuda.synchronize()
+    assert int(ws.at(9, 1).view(torch.int32)) == 0
+    assert torch.isnan(out32[n]).all() and torch.isnan(out16[n]).all() and bool((out32[:n, n:] == 0).all())
+    if bf16:
+        assert torch.equal(out16[:n], out32[:n].to(torch.bfloat16))
+    else:
+        assert torch.isnan(out16).all()
+    X, eye = out32[:n, :n].double(), torch.eye(n, dtype=torch.float64, device="cuda")
+    bound = kappa * EPS * (2 * math.sqrt(n) + 4)
+    assert float((A.double() @ X - eye).norm()) / math.sqrt(n) < bound
+    assert float((X - exact).norm() / exact.norm()) < bound
+
+
+class GemmSum(ctypes.Structure):
+    _fields_ = [("A", ctypes.c_void_p * 5), ("B", ctypes.c_void_p * 5), ("count", ctypes.c_int), ("x", ctypes.c_void_p), ("x_low", ctypes.c_void_p),
+                ("identity", ctypes.c_bool), ("subtract", ctypes.c_bool), ("out", ctypes.c_void_p), ("out_low", ctypes.c_void_p), ("out32", ctypes.c_void_p),
+                ("ld", ctypes.c_int64), ("M", ctypes.c_int), ("N", ctypes.c_int), ("K", ctypes.c_int)]
+
+
+# The sums of products the iteration is made of, by themselves: every tile (128 x 128, 128 x 256, 256 x 192 in one and two rounds of the chip, 256 x 256 in
+# one and two) and rows, columns and K that fill none; one, two and three K steps per product; one, two and five products; what is added.  Bound per element:
+# a rounding of float per product and sum on the sum of the absolute values; out and out_low are out32's roundings
+@pytest.mark.parametrize("m,n,k", [(129, 144, 129), (300, 320, 70), (2100, 2112, 64), (2300, 2320, 130), (3009, 3056, 70), (4097, 4112, 40), (3500, 3504, 130), (4865, 4880, 70)])
+@pytest.mark.parametrize("count,added,subtract", [(1, "x", False), (1, "both", False), (1, "nothing", False), (1, "identity", True), (2, "identity", True), (5, "identity", True),
+                                                  (5, "both", True)])
+def test_sums_of_products(ctx, m, n, k, count, added, subtract):
+    k_pad = (k + 63) // 64 * 64
+    ld = max((n + 63) // 64 * 64, k_pad)
+    gen = torch.Generator(device="cuda").manual_seed(m + k + count)
+
+    def draw(rows, cols, zero_to, scale=1.0):
+        t = torch.full((rows, ld), float("nan"), device="cuda", dtype=torch.bfloat16)
+        t[:, :zero_to] = 0
+        t[:, :cols] = torch.randn((rows, cols), generator=gen, device="cuda") * scale
+        return t
+    A, B = [draw(m, k, k_pad, 4.0 ** -i) for i in range(count)], [draw(k, n, n) for _ in range(count)]
+    x, low = draw(m, n, n), draw(m, n, n, 2.0 ** -9)
+    out, out_low = (torch.full((m + 1, ld), float("nan"), device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    out32 = torch.full((m + 1, ld), float("nan"), device="cuda")
+    s = GemmSum()
+    for i in range(count):
+        s.A[i], s.B[i] = A[i].data_ptr(), B[i].data_ptr()
+    s.count, s.identity, s.subtract = count, added == "identity", subtract
+    s.x, s.x_low = (x.data_ptr() if added in ("x", "both") else None), (low.data_ptr() if added == "both" else None)
+    s.out, s.out_low, s.out32 = out.data_ptr(), out_low.data_ptr(), out32.data_ptr()
+    s.ld, s.M, s.N, s.K = ld, m, n, k
+    f = g.load_library()["_ZN4gelo13gemm_bf16_sumERKNS_7GemmSumEP12ihipStream_t"]
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p]
+    assert f(ctypes.byref(s), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    product = sum(a[:, :k].double() @ b[:, :n].double() for a, b in zip(A, B))
+    size = sum(a[:, :k].double().abs() @ b[:, :n].double().abs() for a, b in zip(A, B))
+    base = torch.zeros((m, n), device="cuda", dtype=torch.float64)
+    if added in ("x", "both"):
+        base += x[:, :n].double()
+    if added == "both":
+        base += low[:, :n].double()
+    if added == "identity":
+        base += torch.eye(m, n, device="cuda", dtype=torch.float64)
+    ref = base - product if subtract else base + product
+    got = out32[:m, :n]
+    for t in (out, out_low, out32):
+        assert torch.isnan(t[m]).all() and torch.isnan(t[:, n:]).all()
+    assert bool(((got.double() - ref).abs() <= (count * k + 2) * EPS * (size + base.abs())).all())
+    assert torch.equal(out[:m, :n], got.to(torch.bfloat16))
+    assert torch.equal(out_low[:m, :n], (got - out[:m, :n].float()).to(torch.bfloat16))
+
+
+# CONDITIONED beyond 128 rows (Newton's iteration on bf16 products): rows that fill no K step and no tile, the tiles of 128 x 128 (up to 2048
+# rows) and 128 x 256 (2049 to 2816), which are one round of the chip, of 256 x 192 (3009: one, 4097: two) and 256 x 256 (3500: one, 4865 and 5120: two), both
+# pitches beyond n, the largest matrix.  The last residual is a sum over ceil(n / 32) matrix instructions of what is at most 1 behind smaller
+# ones, whose roundings (at most EPS each) come with either sign: EPS sqrt(n / 32), and 2 EPS for the rounding of A^-1 and the correction's.
+# 0.43 to 0.52 of that is measured (1.0e-7 at 129 rows, 2.9e-7 at 2150, 4.5e-7 at 5120); without one of the small products of the residual it is 2.6e-6 and more
+@pytest.mark.parametrize("n,dtype", [(n, g.GELO_F32) for n in (129, 191, 192, 193, 1000, 2048, 2049, 2150, 2816, 2817, 3009, 3500, 4097, 4865, 5120)]
                          + [(n, g.GELO_BF16) for n in (129, 193, 2150)])
 def test_inverse_near_an_orthogonal_matrix(ctx, n, dtype):
     m = g.gelo_sample_mixing(ctx, g.GELO_CONDITIONED, n, 0, 64, dtype, 1e3, 64, batch_id=10000 + 2 * n + (dtype == g.GELO_BF16))
@@ -157,7 +282,7 @@ def test_inverse_near_an_orthogonal_matrix(ctx, n, dtype):
     g.gelo_mixing_free(ctx, m)
     A, A_inv, eye = A.double(), A_inv.double(), torch.eye(n, dtype=torch.float64, device="cuda")
     for product in (A @ A_inv, A_inv @ A):
-        assert float((product - eye).norm()) / math.sqrt(n) < (n / 32 + 8) * EPS
+        assert float((product - eye).norm()) / math.sqrt(n) < (math.sqrt(n / 32) + 2) * EPS
 
 
 # the condition estimate where its rows' registers change: rows of less than 256 columns, one to twenty blocks of them, whole and broken
