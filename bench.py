@@ -622,7 +622,7 @@ def main() -> int:
         sec, flop = g.gelo_measure_matrix_rate(ctx, False, 20000, 5)
         result["roofline"]["matrix_only_ceiling"] = {"achieved": flop / sec / 1e12, "unit": "TFLOP/s", "frac_of_peak": flop / sec / 1e12 / peak,
                                                      "kernel_frac_of_ceiling": f_proj / t_proj / (flop / sec),
-                                                     "note": "v_mfma_f32_32x32x16_bf16 only, 8 accumulator tiles per wave, 2 waves per SIMD, 256 CUs"}
+                                                     "note": "v_mfma_f32_16x16x32_bf16 only, 32 accumulator tiles per wave, 2 waves per SIMD, 256 CUs"}
 
     if w.dtype == "bf16" and d % 128 == 0 and n > 128:
         # the same projection with E4M3 operands (not part of the step above: its error is outside the bf16 contract):

@@ -74,7 +74,9 @@ typedef enum { GELO_F32 = 0, GELO_BF16 = 1 } gelo_dtype;
 /* How A is drawn (Section 3.2 step 1.2; Section 3.2.1).
  *  ORTHOGONAL   A = Q diag(sign r_ii) from the Householder QR of a Philox Gaussian; A^-1 = A^T.
  *  GAUSSIAN     A = G/sqrt(n); redrawn until kappa_2(A) <= cond_max; A^-1 from its QR factors.
- *  CONDITIONED  A = Q + 0.25 G2/sqrt(n): dense, A^T A != I, kappa of a few; A^-1 from its QR factors.
+ *  CONDITIONED  A = Q + 0.25 G2/sqrt(n): dense, A^T A != I, kappa of a few; A^-1 from its QR factors up to 128 rows
+ *               (exact to its rounding); beyond by Newton's iteration from Q^T on bf16 products whose last residual takes all bits of A:
+ *               |I - A A^-1| / sqrt(n) (Frobenius) is 1.0e-7 at 129 rows, 1.9e-7 at 1024, 3.8e-7 at 4096, in either dtype.
  *  STRUCTURED   A = P_3 (B D_2 P_2)(B D_1 P_1)(B D_0 P_0): Philox-drawn row permutations P_r and sign
  *               flips D_r around B, the normalised Walsh-Hadamard transform on the row blocks of the
  *               binary expansion of n.  Orthogonal (A^-1 = A^T), never formed: mix and unmix apply it in
@@ -277,8 +279,8 @@ gelo_status gelo_debug_philox_words(gelo_ctx* ctx, uint32_t stream_id, uint32_t 
 gelo_status gelo_mixing_export_table(gelo_ctx* ctx, const gelo_mixing* mixing, uint32_t* table, void* stream);
 /* Measurement aid (for the caller that reports a kernel against the matrix-core peak, as Section 4.2 style
  * "fraction of peak" figures do): what the matrix cores of this device deliver when every wave issues nothing
- * but independent matrix instructions from registers - v_mfma_f32_32x32x16_bf16 (fp8 = 0) or
- * v_mfma_f32_32x32x64_f8f6f4 on E4M3 (fp8 = 1), eight accumulator tiles per wave, two waves per SIMD, as in a K
+ * but independent matrix instructions from registers - v_mfma_f32_16x16x32_bf16 (fp8 = 0, 32 accumulator tiles per
+ * wave) or v_mfma_f32_32x32x64_f8f6f4 on E4M3 (fp8 = 1, eight), two waves per SIMD, as in a K
  * step of the projection kernels; no memory traffic.  Runs one warm-up launch and `launches` (1..1000) timed
  * launches of `iters` (1..2^20) loop passes each on `stream`, WAITS for them, and returns the mean time of one
  * launch (HOST double) and the floating-point operations one launch executes (HOST double).  Uses the static
