@@ -233,8 +233,8 @@ void gemm_bf16_kernel(Bf16Args g) {
 // Fast path: 256 x BN tile (BN = 256 or 192), 8 waves (wave tile 64 x BN/2), K step 64, two LDS
 // stages filled by direct-to-LDS loads (global_load_lds_dwordx4: no staging registers, no
 // ds_write), one barrier per K step.
-//   v_mfma_f32_16x16x32_bf16: under the chip's power limit it runs at 1.97 PFLOP/s with operands that look
-//     like data where v_mfma_f32_32x32x16_bf16 runs at 1.70 (registers only, the same operands).  With the
+//   v_mfma_f32_16x16x32_bf16: under the chip's power limit it runs at 1.98 PFLOP/s with operands that look
+//     like data where v_mfma_f32_32x32x16_bf16 runs at 1.76 (registers only: calibrate.hip).  With the
 //     instruction alone exchanged 2150 x 12288 x 4096 went from 194 to 177 us, 4096 x 12288 x 4096 from 327 to 297.
 //   A rows (128 bytes per stage) keep their 16-byte chunks XOR-swizzled so that the 16-byte
 //     fragment reads of 16 consecutive rows hit distinct banks.
@@ -242,7 +242,9 @@ void gemm_bf16_kernel(Bf16Args g) {
 //     lane the four K-consecutive values of one column: the MFMA operand layout, with no
 //     permutes.  The 16-byte chunks of a row are permuted (XOR for BN = 256, rotation for
 //     BN = 192, see b_chunk_pos) so that the eight rows half a wave's transposing read touches are
-//     spread over all banks.
+//     spread over all banks.  The counters still show 0.28 conflict cycles per cycle in which the LDS is at
+//     work (0.03 with v_mfma_f32_32x32x16_bf16, whose reads took four rows at a time); which reads they belong to
+//     has not been measured.
 //   A K step is four quarters of matrix instructions (half of K, half of the wave's columns).  The reads of
 //     what the next quarter multiplies and the fetches of the next K step stand among them one by one, in
 //     an order the compiler keeps: bursts of either leave the matrix pipe idle.  177 -> 171 and 297 -> 284 us
@@ -253,8 +255,11 @@ void gemm_bf16_kernel(Bf16Args g) {
 //   The MFMA operands are swapped (B fragment first), so the accumulators hold blocks of C^T and a
 //     lane owns 4 consecutive columns of one row; the epilogue goes through LDS once more so that
 //     the global stores are 16 bytes per lane over whole row segments.
-// What bounds it: in the loop the matrix instructions take 77 % of the time at the rate above; the rest is the
-// meeting of eight waves once per K step beside 64 KB of fetches.
+// What bounds it: 2150 x 12288 x 4096 executes 232 GFLOP in whole tiles, 117 of its 171 us at the rate above; the matrix
+// pipes are busy in 61 % of all SIMD cycles of the launch, CUs without a tile in the last round among them.  The rest is the
+// meeting of eight waves once per K step beside 64 KB of fetches.  With one K step there is no loop, and
+// 129 x 64 x 64 takes 5.13 us, 2150 x 12288 x 64 16.1, where the loop of v_mfma_f32_32x32x16_bf16 took 5.05 and 15.7; two steps 9.3 where it
+// took 9.55 (2150 x 4096 x 128).
 // Out-of-range rows of A and columns of B are clamped to valid addresses (their products land in
 // outputs that are never stored); rows of B beyond K are fetched from a block of zeros and A is zero
 // in columns [K, round_up(K, 64)) (required by the dispatcher), so the K tail contributes exact zeros
@@ -297,7 +302,6 @@ template <int BN> __device__ __forceinline__ int b_chunk_of_pos(int r, int pos) 
     return c < 0 ? c + BN / 8 : c;
 }
 
-// TM = 256 or 128 rows: 4 x 2 waves of 64 x BN / 2, or 2 x 4 of 64 x BN / 4.
 // what gemm_bf16_sum_kernel adds to the product: GemmSum's fields
 struct Sum {
     const uint16_t* A[kGemmSumMax];
@@ -309,6 +313,7 @@ struct Sum {
 };
 struct NoSum {};
 
+// TM = 256 or 128 rows: 4 x 2 waves of 64 x BN / 2, or 2 x 4 of 64 x BN / 4.
 template <int BN, int TM = BM, class More = NoSum>
 __device__ __forceinline__ void tile_body(const Bf16Args& g, uint8_t* lds, int m0, int n0, const More& more = More()) {
     constexpr bool SUM = std::is_same<More, Sum>::value;
@@ -475,8 +480,10 @@ __device__ __forceinline__ void tile_body(const Bf16Args& g, uint8_t* lds, int m
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
     };
-    aim(0);
-    static_for<FETCHES>([&](auto i) { fetch(i, 0); });
+    if constexpr (SUM) aim(0);
+    static_for<NAD>([&](auto i) { fetch(i, 0); });
+    if constexpr (!SUM) aim(0);                                  // (A is on its way while B's addresses are made: 0.1 us of every tile)
+    static_for<NBD>([&](auto i) { fetch(std::integral_constant<int, NAD + decltype(i)::value>{}, 0); });
     meet();
     if (T > 1) {
         aim(1);
@@ -631,8 +638,8 @@ void gemm_bf16_dma_batched_kernel(Bf16Batch b) {
     tile_body<BN>(g, lds, tm * BM, tn * BN);
 }
 
-// Sums of products (GemmSum): K steps run on from one product into the next, the accumulators stay.  4096 x 4096 x 4096 111 us (1.24
-// PFLOP/s, 256 x 256 tiles), as the plain product.
+// Sums of products (GemmSum): K steps run on from one product into the next, the accumulators stay.  4096 x 4096 x 4096 103 to 111 us
+// (1.24 to 1.33 PFLOP/s, 256 x 256 tiles), as the plain product.
 template <int BN, int TM>
 __global__ __launch_bounds__(512)
 void gemm_bf16_sum_kernel(Bf16Args g, Sum more) {
