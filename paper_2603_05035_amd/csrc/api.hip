@@ -476,7 +476,8 @@ static gelo_status check_sample_args(gelo_ctx* ctx, gelo_kind kind, int n_data, 
 // object-major).  The full blocks share the launches of one batched factorisation.  A last, shorter one of more than kSmallMaxN rows takes
 // part in it as the end of a full-size matrix that begins with the identity; its panels start when the others' have as many rows
 // left.  With a chain of launches of its own behind the others', 1 and 32 draws: 129 rows (641 in all) 368 and 743 us, now 255 and
-// 658; 255 rows (767) 438 and 833, now 254 and 678.  Up to kSmallMaxN rows: one launch of the one-workgroup factorisation, 10 to 60 us and a
+// 658; 255 rows (767) 438 and 833, now 254 and 678; |A^T A - I| / sqrt(rows) over 48 draws 4.18e-7 and 4.17e-7 at 129 rows, 4.62e-7 and 4.64e-7 at 200.
+// Up to kSmallMaxN rows: one launch of the one-workgroup factorisation, 10 to 60 us and a
 // little more exact (102 rows beside eight blocks, as the end of a ninth: 308 -> 262 us, 32 draws 1026 -> 1058, |A^T A - I| 3.7e-7 -> 4.0e-7).
 static hipError_t draw_blocks(const SmallSampleTargets& t, int count, uint64_t first, PhiloxStream ps, int n, int d, int64_t ldk, char* base,
                               hipStream_t s) {

@@ -1,8 +1,9 @@
 // The explicit inverse and the kappa_2 estimate (Lanczos) behind the non-orthogonal mixing matrices (Section 3.2.1,
 // Mitigation 1: a well-conditioned non-orthogonal A, generated and verified; Section 3.2 eq. 3 needs A^-1 explicitly so
-// that un-mixing is one GEMM).  Everything is float and deterministic: reductions run in a fixed order, no atomics.
+// that un-mixing is one GEMM).  Everything is deterministic: reductions run in a fixed order, no atomics.
 //
-// CONDITIONED beyond 128 rows: Newton's iteration from the orthogonal part's transpose (inverse_near_orthogonal).  Otherwise
+// CONDITIONED beyond 128 rows: Newton's iteration from the orthogonal part's transpose, on bf16 products with float sums, the last residual
+// from all 24 bits of A (inverse_near_orthogonal).  Otherwise, and in the condition estimate, everything is float (the refinement of up to 128 rows double):
 // A^-1 = R^-1 Q^T from the Householder QR of A (factor.hip): no pivot searches and row interchanges, whose chain - two
 // barriers per column, 1.1 us of one workgroup - bounded a row-pivoted LU in this place (512 rows: 1.1 ms of kernels
 // without the condition estimate, here 0.48; 4096 rows: 15.5 ms, here 4.9).  Up to 128 rows everything behind the QR is one
@@ -658,14 +659,17 @@ hipError_t inverse_from_qr(const FactorWorkspace& ws, int n, const float* A, int
 
 // Newton's iteration X <- X + X (I - A X) from X = Q^T, whose residual I - A Q^T = -E Q^T has the eigenvalues of a Gaussian of
 // spectral radius 0.25: squared by every step, 2^-4, 2^-8, ... (2-norm 0.5, 0.16, 0.014 measured from 129 to 4096 rows; below 0.65 in
-// all but 1e-10 of the draws at 129 rows, so that the steps cannot diverge).  What a step adds need not be more
+// all but 1e-10 of the draws at 129 rows, so that the steps cannot diverge; the residual of X3, whose square is left at the end, would show
+// from a radius of 0.45 on, 0.45^16 = 3e-6 in one direction: a real eigenvalue of a Gaussian there has the probability exp(-n (x^2 - 1 - 2 ln x) / 2) with x =
+// 0.45 / 0.25, e^-68 at 129 rows).  What a step adds need not be more
 // exact than what the next one removes: the first two steps run on bf16 matrices (the second one's residual is the first one's squared),
 // X's own rounding included; then two corrections from residuals of 16 bits of A, and of all of A and 16 bits of X, each a bf16 product:
 // residuals 5e-3, 2.6e-5, then what the sums of the last one round (Frobenius, of |I|): 1.0e-7 at 129 rows, 1.9e-7 at 1024, 3.8e-7 at 4096,
-// where R^-1 Q^T from a second QR left 4.3e-7, 6.1e-7, 8.8e-7.
-// Bound by the matrix instructions, thirteen products of n^3: 1.25 ms at 4096 rows (1.65 with the last residual as a float
-// product, whose sums also rounded more: 8.2e-7), where the second QR and the back substitution took 4.9.  A whole draw, us: 129 rows 504 -> 404, 512 1073 ->
-// 714, 1024 1680 -> 1068, 2150 3664 -> 2263, 4096 9414 -> 5813.
+// where R^-1 Q^T from a second QR left 4.3e-7, 6.1e-7, 8.7e-7; I - X A and X itself against 64 bits likewise, the largest error of an element (of the elements' root
+// mean square) 8e-7 at 129 rows and 4.5e-6 at 4096, where it was 3.8e-6 and 4.8e-5.
+// Bound by the matrix instructions, thirteen products of n^3: 1.42 ms at 4096 rows (0.4 more with the last residual as a float
+// product, whose sums also rounded more: 8.2e-7), where the second QR and the back substitution took 4.9.  A whole draw, us, then and now: 129 rows 500 and 310,
+// 512 1071 and 625, 1024 1684 and 985, 2150 3664 and 2207, 4301 10380 and 6965 (the condition estimate's launches are fewer now, too).
 hipError_t inverse_near_orthogonal(const FactorWorkspace& ws, int n, const float* A, int64_t ldk, float* Ainv32, uint16_t* Ainv16, hipStream_t s) {
     const int64_t ld = ws.ld, half = (int64_t)ws.n_pad * ld;
     if (n <= BW || ldk != ld) return hipErrorInvalidValue;
