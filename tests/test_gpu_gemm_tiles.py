@@ -62,18 +62,21 @@ def test_bf16_rows_behind_the_last_whole_tile_of_a_mix(width):
         assert bool(((out[1:rows + 1].double() - ref).abs() <= 2.0 ** -8 * 1.01 * ref.abs() + n * 2.0 ** -24 * size).all())
 
 
-# one, two and three K steps and more (what is fetched ahead ends differently), in both widths of a whole tile
-@pytest.mark.parametrize("m,n", [(300, 520), (2048, 12288)])
+# one, two and three K steps and more (what is fetched ahead ends differently), in both widths of a whole tile (192: as few rounds as with 256; 256: 3900 x
+# 4088 is one round of them and two of the others)
+@pytest.mark.parametrize("m,n", [(300, 520), (2048, 12288), (3900, 4088)])
 @pytest.mark.parametrize("k", [64, 128, 192, 320])
 def test_bf16_few_steps(m, n, k):
     check(m, k, n, torch.bfloat16)
 
 
 # B in two segments of different pitch: they meet between two steps, on a step's first and last row; shield rows that fill no step, one
-# step, two
+# step, two; in tiles of 192 columns and, where those are one more round than tiles of 256, in these
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("n_data,k", [(128, 1), (129, 0), (128, 64), (191, 65), (193, 64), (192, 128), (256, 130), (319, 66)])
-def test_bf16_segments_of_a_mix(n_data, k):
-    n, width = n_data + k, 520
+def test_bf16_segments_of_a_mix(n_data, k, wide):
+    n = n_data + k
+    width = (49160 if n <= 384 else 24584) if wide else 520
     gen = torch.Generator(device="cuda")
     gen.manual_seed(n_data + k)
     H = torch.full((n_data, width + 24), float("nan"), device="cuda", dtype=torch.bfloat16)[:, :width]
