@@ -490,7 +490,7 @@ static hipError_t draw_blocks(const SmallSampleTargets& t, int count, uint64_t f
         factor_workspace_carve(base, rows, &w);
         const int64_t stride = (int64_t)(up256(factor_workspace_bytes(rows)) / sizeof(float));
         hipError_t e = fill_normal_batched(w.M, stride, w.n_pad / 16, rows, rows, ps, side, side * count, false, s, tail);
-        if (e == hipSuccess) e = householder_qr_tails(w, rows, side * count, stride, s, false, side, tail);
+        if (e == hipSuccess) e = householder_qr(w, rows, side * count, stride, s);
         if (e == hipSuccess) e = emit_batched(w.X, w.rdiag, stride, w.n_pad / 16, rows, ldk, t, count, side, 0, (int64_t)B * ldk, s, tail);
         if (e != hipSuccess) return e;
     }

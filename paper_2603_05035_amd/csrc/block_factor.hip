@@ -28,7 +28,6 @@ namespace {
 
 constexpr int NB = kPanel;
 constexpr int BT = 8;                                     // tile columns of a block
-constexpr int kTailTiles = 16;                            // blocks are taken while more tile rows than this are left
 constexpr int kTurn = NB + 4;                             // LDS pitch of a tile that is turned around, floats
 constexpr int kCoreTiles = BT * BT;                       // tiles of each of the core's three triangles
 
@@ -332,7 +331,7 @@ void block_apply_kernel(BlockArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[(int64_t)i * a.w.nbr * 256 + (4 * g + e) * NB] = acc[e];
         if (i < BT / 2)
-            put_split(a.Yr + 2 * off + (int64_t)row * kUnitYr + i * 3 * kFrag + lane * 8, kFrag,
+            put_split(a.Yr + 2 * off + (int64_t)row * kYrBlock + i * 3 * kFrag + lane * 8, kFrag,
                       split3(*reinterpret_cast<const f32x4_t*>(&part[0][2 * i][lane * 4]), *reinterpret_cast<const f32x4_t*>(&part[0][2 * i + 1][lane * 4])));
     }
 }
@@ -348,9 +347,10 @@ void first_panel_kernel(const float* M, uint16_t* out, int nbr, int64_t batch_st
     put_split(out + 2 * (int64_t)blockIdx.y * batch_stride + (int64_t)blockIdx.x * kUnitPanel + f * kFrag + lane * 8, 8 * kFrag, split3(v0, v1));
 }
 
-// T of every panel of 16 finished reflectors, from V^T V in double precision (see gram_panel_body): a workgroup per panel
+// T of every panel of 16 finished reflectors, from V^T V in double precision (see gram_panel_body), and V row by row (Vc, unless it is
+// null): a workgroup per panel
 __global__ __launch_bounds__(512)
-void panel_triangle_kernel(const float* M, float* Tmat, int nbr, int64_t batch_stride) {
+void panel_triangle_kernel(const float* M, float* Vc, float* Tmat, int nbr, int64_t batch_stride) {
     __shared__ double part[8][256];
     __shared__ __attribute__((aligned(16))) float m[NB * kTurn];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -359,6 +359,11 @@ void panel_triangle_kernel(const float* M, float* Tmat, int nbr, int64_t batch_s
     f64x4_t acc = {0., 0., 0., 0.};
     for (int r = f + wave; r < nbr; r += 8) {
         const f32x4_t x = *reinterpret_cast<const f32x4_t*>(v + (int64_t)r * 256);
+        if (Vc != nullptr) {
+            float* row = Vc + (int64_t)blockIdx.y * batch_stride + ((int64_t)f * nbr + r - f) * 256 + 4 * g * NB + c;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) row[e * NB] = x[e];
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[e], (double)x[e], acc, 0, 0, 0);
     }
@@ -404,27 +409,24 @@ hipError_t block_factor_init() {    // brings this file's code onto the device (
     return hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&first_panel_kernel));
 }
 
-hipError_t factor_blocks(const FactorWorkspace& ws, int count, int64_t batch_stride, int* panels_done, hipStream_t s) {
+hipError_t factor_blocks(const FactorWorkspace& ws, float* Vc, int count, int64_t batch_stride, int* panels_done, hipStream_t s) {
     const int nbr = ws.n_pad / NB;
     int done = 0;
     hipLaunchKernelGGL(first_panel_kernel, dim3((nbr + 1) / 2, count), dim3(512), 0, s, ws.M, ws.panel, nbr, batch_stride);
     GELO_TRY(hipGetLastError());
-    for (; nbr - done > kTailTiles; done += BT) {
+    for (const int last = last_block_tiles(nbr); nbr - done >= last; done += BT) {
         BlockArgs b;
         WideArgs& a = b.w;
         a.nbr = nbr; a.t0 = done; a.mt = nbr - done; a.nt = BT;
         a.Yp = ws.panel; a.T = nullptr;
         a.X = ws.M + ((int64_t)done * nbr + done) * 256;
-        a.Wpart = ws.Wpart; a.Wp = ws.Wp; a.wp_unit = 3 * (BT / 2) * kFrag;
+        a.Wpart = ws.Wpart; a.Wp = ws.Wp; a.wp_unit = a.yr_unit = kYrBlock;
         a.next = nullptr;
         a.batch_stride = batch_stride; a.count = count;
         cut_into_ranges(a, 1, (a.mt + 3) / 4);
         GELO_TRY(launch_panel_products(a, s));
-        // Y2's place among the reflectors of the wide block these 128 belong to
-        const int wide = done / kWideTiles, second = done % kWideTiles != 0;
         b.core = ws.core; b.Rd = ws.Rd + (int64_t)done * 256; b.rdiag = ws.rdiag + done * NB;
-        b.Yr = ws.Yr + (rows_before(nbr, wide) + (done + BT - wide * kWideTiles)) * kUnitYr + (second ? 3 * (BT / 2) * kFrag : 0);
-        a.Yr = b.Yr;
+        a.Yr = b.Yr = ws.Yr;
         if (a.by_part) hipLaunchKernelGGL((block_core_kernel<kWideParts>), dim3(count), dim3(kCoreThreads), 0, s, b);
         else hipLaunchKernelGGL((block_core_kernel<kWideChunks>), dim3(count), dim3(kCoreThreads), 0, s, b);
         GELO_TRY(hipGetLastError());
@@ -433,11 +435,11 @@ hipError_t factor_blocks(const FactorWorkspace& ws, int count, int64_t batch_str
         GELO_TRY(hipGetLastError());
         a.X += (int64_t)BT * nbr * 256 + BT * 256;
         a.mt -= BT; a.t0 += BT;
-        a.next = a.mt > kTailTiles ? ws.panel : nullptr;
+        a.next = a.mt >= last ? ws.panel : nullptr;
         GELO_TRY(launch_block_update(a, s));
     }
     if (done > 0) {
-        hipLaunchKernelGGL(panel_triangle_kernel, dim3(done, count), dim3(512), 0, s, ws.M, ws.Tmat, nbr, batch_stride);
+        hipLaunchKernelGGL(panel_triangle_kernel, dim3(done, count), dim3(512), 0, s, ws.M, Vc, ws.Tmat, nbr, batch_stride);
         GELO_TRY(hipGetLastError());
     }
     *panels_done = done;

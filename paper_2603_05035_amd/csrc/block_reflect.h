@@ -7,7 +7,8 @@
 namespace gelo {
 
 constexpr int kUnitYp = 3 * kWideTiles * kFrag;           // bf16 values of a pair of tile rows in Yp
-constexpr int kUnitYr = 3 * (kWideTiles / 2) * kFrag;     // of a tile row in Yr, and of a tile column in Wp
+constexpr int kUnitYr = 3 * (kWideTiles / 2) * kFrag;     // of a tile row in a wide block's Yr, and of a tile column in its Wp
+static_assert(kYrBlock == 3 * 4 * kFrag, "a tile row of a block of 128 reflectors");
 static_assert(kWideChunks <= 2 * kWideParts, "a part has at most two ranges");
 constexpr int kUnitPanel = 3 * 8 * kFrag;                 // of a pair of tile rows of a panel of 128 columns
 
@@ -19,7 +20,7 @@ struct WideArgs {
     const uint16_t* Yp; const uint16_t* Yr;               // of this block
     const float* T;                                       // of this block, 256 x 256 (forming Q)
     float* X;                                             // the matrix the reflectors meet, from its tile (t0, t0) on
-    float* Wpart; uint16_t* Wp; int wp_unit;              // bf16 values of a tile column in Wp
+    float* Wpart; uint16_t* Wp; int wp_unit, yr_unit;     // bf16 values of a tile column in Wp, of a tile row in Yr
     uint16_t* next;                                       // where the update leaves the next panel taken apart (the factorisation)
     int nbr, t0, mt;                                      // tile rows of the matrix, the first one taken, those from it on (as many columns)
     int nt;                                               // tile columns of the block

@@ -401,7 +401,7 @@ void reflect_update_direct_kernel(WideArgs a) {
     const uint16_t* wb[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        ya[i] = a.Yr + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(r0 + i < a.mt ? r0 + i : a.mt - 1) * kUnitYr + lane * 8;
+        ya[i] = a.Yr + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(r0 + i < a.mt ? r0 + i : a.mt - 1) * a.yr_unit + lane * 8;
         wb[i] = a.Wp + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(c0 + i < a.mt ? c0 + i : a.mt - 1) * a.wp_unit + lane * 8;
     }
     bf16x8_t y[3][3][2];
@@ -467,7 +467,7 @@ void reflect_update_kernel(WideArgs a) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int row = rg * 8 + wave * 2 + i, col = cg * 8 + wave * 2 + i;
-        src[i] = a.Yr + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(row < a.mt ? row : a.mt - 1) * kUnitYr + lane * 8;
+        src[i] = a.Yr + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(row < a.mt ? row : a.mt - 1) * a.yr_unit + lane * 8;
         src[2 + i] = a.Wp + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(col < a.mt ? col : a.mt - 1) * a.wp_unit + lane * 8;
     }
     u32x4_t st[4][3];
@@ -590,7 +590,7 @@ hipError_t form_product_wide(const FactorWorkspace& ws, int count, int64_t batch
         a.Yr = ws.Yr + rows_before(nbr, q) * kUnitYr;
         a.T = ws.Tbig + (int64_t)q * (WT * 16) * (WT * 16);
         a.X = ws.X + ((int64_t)a.t0 * nbr + a.t0) * 256;
-        a.Wpart = ws.Wpart; a.Wp = ws.Wp; a.wp_unit = kUnitYr; a.next = nullptr;
+        a.Wpart = ws.Wpart; a.Wp = ws.Wp; a.wp_unit = a.yr_unit = kUnitYr; a.next = nullptr;
         a.batch_stride = batch_stride; a.count = count;
         cut_into_ranges(a, 2, 2 * ((a.mt + 7) / 8));
         GELO_TRY(launch_wt<WT>(a, s));

@@ -3,16 +3,15 @@
 // with the inverse of the non-orthogonal kinds, which is built on the same factorisation.  Everything is float and deterministic: reductions run in a fixed order, no
 // atomics.
 //
-// Matrices from 720 rows on are factorised by blocks of 128 columns down to their last 256 rows (block_factor.hip), and their Q is
-// formed by blocks of 256 (block_reflect.hip); what follows is the rest and everything smaller.
-//
-// Column panels are 16 wide.  A panel is factorised by ONE workgroup, from its 16 x 16 Gram matrix while it is tall
-// (gram_panel_body), by a loop over its columns at the end (qr_panel_body); the block reflectors are applied on the
-// matrix cores.
+// Matrices from 416 rows on are factorised by blocks of 128 columns (block_factor.hip); smaller ones, and what the blocks leave (112 to 304
+// rows), by panels of 16 columns, each by ONE workgroup from its 16 x 16 Gram matrix (gram_panel_body); the last 128 rows, or a matrix of no
+// more, by one workgroup in registers (square_qr_kernel).  Reflectors are applied on the matrix cores.  From 720 rows on Q is formed by
+// blocks of 256 reflectors (block_reflect.hip), below by strips of 16 columns.
 #include <type_traits>
 #include <utility>
 
 #include "gelo_internal.h"
+#include "tile_qr.h"
 #include "wave_tile.h"
 
 namespace gelo {
@@ -79,28 +78,22 @@ __device__ __forceinline__ float lane_value(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), LANE));
 }
 
-// ------------------------------------------------------------------ QR panel --
-// Factorises the m x 16 panel at Mp (read only; R on and above the diagonal and the reflector tails below, as
-// in LAPACK, exist in registers only) and writes for the block reflector I - V T V^T:
-// Vc = V with explicit unit diagonal and zeros above (m x 16, row stride ld), T (16 x 16,
-// dense row-major at Tg) and rdiag[0:16] = diag(R).  Reflector j: beta = -sign(alpha) ||x||,
-// tau = (beta - alpha)/beta, v = x / (alpha - beta) below the diagonal; a zero tail gets tau = 0.
+// ------------------------------------------------------------------ directly drawn panels --
+// The reflectors of an m x 16 panel, every one from its column as it stands in memory (the later columns of the panel do not see the
+// earlier reflectors: what the product of directly drawn reflectors needs, householder_qr with `direct`), and what the block reflector
+// I - V T V^T takes: V with explicit unit diagonal and zeros above, T (16 x 16, dense row-major at Tg) and rdiag[0:16] = the beta_j.
+// Reflector j: beta = -sign(alpha) ||x||, tau = (beta - alpha)/beta, v = x / (alpha - beta) below the diagonal; a zero tail gets tau = 0.
 //
 // One workgroup reduction and one barrier per column: with x the column below the diagonal,
 // t[s] = x . P[below, s] for all 16 columns s gives the tail norm (s = j) and, with the broadcast
-// pivot row, v . P[:, s] = scale * t[s] + P[j][s], which is both the update coefficient (s > j)
-// and the Gram entry v_s . v_j that the T factor needs (s < j).  After the reduction lane s of
-// every wave holds the quantities of column s; the update coefficients are then read into
-// scalar registers.  The column loop is unrolled so that all register indices are constants.
+// pivot row, v . P[:, s] = scale * t[s] + P[j][s], for s < j the Gram entry v_s . v_j that the T factor needs.  After the reduction
+// lane s of every wave holds the quantities of column s.  The column loop is unrolled so that all register indices are constants.
 // Mp: the panel's first 16 x 16 tile; the tiles of the rows below follow at 256 floats each
 // (element (r, c) at Mp[(r / 16) * 256 + c * 16 + r % 16]).  The reflector block is written twice,
 // compactly: Vr[r * 16 + c] (row-major, the A operand of C += V W') and Vt in the same tiles as
 // the panel (the A operand of W = V^T C), both with explicit unit diagonal and zeros above.
-// UPDATE = false builds every reflector from the column as it stands in memory - the later columns of the panel do
-// not see the earlier reflectors - which is what the product of directly drawn reflectors needs (householder_qr with
-// `direct`): the same reflector formulas, the same T, no factorisation.
-template <int NTHR, int R, bool UPDATE = true>
-__device__ __forceinline__ void qr_panel_body(float* Mp, float* Vr, float* Vt, float* Tg, float* Rd, float* rdiag, int m) {
+template <int NTHR, int R>
+__device__ __forceinline__ void direct_panel_body(float* Mp, float* Vr, float* Vt, float* Tg, float* rdiag, int m) {
     constexpr int NW = NTHR / 64;
     __shared__ float red[2][NW][NB];
     __shared__ float prow[2][NB];
@@ -162,31 +155,10 @@ __device__ __forceinline__ void qr_panel_body(float* Mp, float* Vr, float* Vt, f
             Z[j][tid] = wl;
             if (tid == 0) { tau_s[j] = tau; rdiag[j] = beta; }
         }
-        float w[NB];
-        static_for<NB>([&](auto sc) {
-            constexpr int s = decltype(sc)::value;
-            if constexpr (s > j) w[s] = lane_value<s>(wl);
-        });
-        {
-            // register row 0: below the diagonal v = x * scale, on it v = 1 and the entry becomes beta, above it nothing
-            const float v = tid > j ? P[0][j] * scale : (tid == j ? 1.f : 0.f);
-            P[0][j] = tid > j ? v : (tid == j ? beta : P[0][j]);
-            const float tv = tau * v;
-            if constexpr (UPDATE) {
+        // register row 0: below the diagonal v = x * scale, on it and above it nothing reads the column again
+        P[0][j] = tid > j ? P[0][j] * scale : P[0][j];
 #pragma unroll
-                for (int s = j + 1; s < NB; ++s) P[0][s] = fmaf(-tv, w[s], P[0][s]);
-            }
-        }
-#pragma unroll
-        for (int i = 1; i < R; ++i) {
-            const float v = P[i][j] * scale;
-            P[i][j] = v;
-            const float tv = tau * v;
-            if constexpr (UPDATE) {
-#pragma unroll
-                for (int s = j + 1; s < NB; ++s) P[i][s] = fmaf(-tv, w[s], P[i][s]);
-            }
-        }
+        for (int i = 1; i < R; ++i) P[i][j] *= scale;
     });
     __syncthreads();
 
@@ -210,16 +182,7 @@ __device__ __forceinline__ void qr_panel_body(float* Mp, float* Vr, float* Vt, f
                 make_float4(Trow[c4 * 4], Trow[c4 * 4 + 1], Trow[c4 * 4 + 2], Trow[c4 * 4 + 3]);
     }
 
-    // R's diagonal tile: thread t < 16 has row t in its first register row
-    if constexpr (UPDATE) {
-        if (tid < NB) {
-#pragma unroll
-            for (int s = 0; s < NB; ++s) Rd[tid * NB + s] = s >= tid ? P[0][s] : 0.f;
-        }
-    }
-
-    // write the clean reflector block in its two layouts, in place of the factored panel (nobody reads these columns
-    // again; R's tile went to Rd, its diagonal to rdiag)
+    // write the clean reflector block in its two layouts, in place of the panel (nobody reads these columns again)
 #pragma unroll
     for (int i = 0; i < R; ++i) {
         const int r = tid + i * NTHR;
@@ -239,14 +202,6 @@ __device__ __forceinline__ void qr_panel_body(float* Mp, float* Vr, float* Vt, f
     }
 }
 
-// a matrix of one short panel, or the first panel of such a matrix
-template <int NTHR, int R>
-__global__ __launch_bounds__(NTHR)
-void qr_panel_kernel(float* Mp, float* Vr, float* Vt, float* Tg, float* Rd, float* rdiag, int m, int64_t batch_stride) {
-    const int64_t off = (int64_t)blockIdx.y * batch_stride;
-    qr_panel_body<NTHR, R>(Mp + off, Vr + off, Vt + off, Tg + off, Rd + off, rdiag + off, m);
-}
-
 // All the panels of a matrix at once, every reflector from the raw column (grid x = panel, grid y = matrix): panel p
 // is the tile column p from its diagonal tile down, 16 (panels - p) rows; its reflector block goes where
 // householder_qr keeps panel p's (Vr side by side in Vc, Vt in place of the panel, T and diag(R) in their arrays).
@@ -256,7 +211,7 @@ void direct_panels_kernel(float* M, float* Vc, float* Tmat, float* rdiag, int nb
     const int p = blockIdx.x;
     const int64_t off = (int64_t)blockIdx.y * batch_stride;
     float* Mp = M + off + (int64_t)p * nbr * 256 + (int64_t)p * 256;
-    qr_panel_body<NTHR, R, false>(Mp, Vc + off + (int64_t)p * nbr * 16 * NB, Mp, Tmat + off + (int64_t)p * NB * NB, nullptr, rdiag + off + p * NB, (nbr - p) * NB);
+    direct_panel_body<NTHR, R>(Mp, Vc + off + (int64_t)p * nbr * 16 * NB, Mp, Tmat + off + (int64_t)p * NB * NB, rdiag + off + p * NB, (nbr - p) * NB);
 }
 
 // ------------------------------------------------- fused block-reflector update --
@@ -274,14 +229,14 @@ void direct_panels_kernel(float* M, float* Vc, float* Tmat, float* rdiag, int nb
 // One block reflector I - V op(T) V^T as a strip sees it: V in both layouts, its triangle, and `shift`, the
 // number of 16-row blocks by which its first row lies below the strip's first row (a strip behind a block of panels
 // starts at the first row of the block's oldest reflector).
-struct Reflector { const float* Vr; const float* Vt; const float* T; int shift; int plain_t; };
-// plain_t: op(T) = T (the reflector itself, I - V T V^T: what forming Q applies) instead of T^T (its transpose: what
-// the factorisation applies to the columns behind it); reflect_strip_body takes T^T only
+struct Reflector { const float* Vr; const float* Vt; const float* T; int shift; };
+// op(T): T^T, what the factorisation applies to the columns behind a panel (reflect_strip_body, whose strips start at the
+// reflector's first row), or T, the reflector itself: what forming Q applies (reflect_strip_lds_body)
 // (the pointers are those of the first matrix of a batch; `off` below is the distance to this workgroup's matrix)
 
-constexpr int kBulkFromCount = 2;         // from this many factorisations side by side the block strips get launches of their own
+constexpr int kStepBlocks = 4;           // strip blocks per wave of the panels by themselves: less than kBlockTiles tile rows
+static_assert(8 * kStepBlocks >= kBlockTiles - 1, "a strip's blocks");
 constexpr int kPanelRows256 = 1024;      // panels of directly drawn reflectors: up to this many rows by 256 threads, longer ones by 512
-constexpr int kMaxDelay = 4;             // panels per block: most reflectors a strip pass of the factorisation applies (several matrices)
 constexpr int kMaxProduct = 8;           // most reflectors a strip pass applies while Q is formed (qr_bulk_kernel: all reflectors exist by then,
                                          // so the passes can be longer: measured 10% less time for the same reflectors than passes of four)
 
@@ -319,7 +274,7 @@ __device__ __forceinline__ void reflect_strip_body(StripShared& sh, const Reflec
     // soon as a group has been consumed the group two places further on is requested into the same registers.  Two
     // groups are always on their way, across the barrier too: a load consumed right behind its issue would expose
     // one memory latency per group.
-    constexpr int GRP = 5, NG = NBLK / GRP;
+    constexpr int GRP = NBLK < 5 ? NBLK : 5, NG = NBLK / GRP;
     static_assert(NBLK % GRP == 0, "blocks per wave must be a multiple of the load group");
     f32x4_t va[2][GRP];
     const float* zero_l = g_zero_tile + c * 16 + 4 * g;
@@ -330,8 +285,8 @@ __device__ __forceinline__ void reflect_strip_body(StripShared& sh, const Reflec
             const float* base = (phase == 0 ? R.Vt : R.Vr) + off + c * 16 + 4 * g;
 #pragma unroll
             for (int k = 0; k < GRP; ++k) {
-                const int blk = wave + 8 * (grp * GRP + k), vb = blk - R.shift;      // strip block blk meets reflector block blk - shift
-                const float* src = (vb >= 0 && blk <= last) ? base + 256 * vb : zero_l;
+                const int blk = wave + 8 * (grp * GRP + k);
+                const float* src = blk <= last ? base + 256 * blk : zero_l;
                 va[j & 1][k] = *reinterpret_cast<const f32x4_t*>(src);
             }
         }
@@ -510,12 +465,12 @@ __device__ __forceinline__ void reflect_strip_lds_body(const Reflector* refl, in
             });
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the operands are in registers before their ring slot is refilled
         });
-        if (tid < NB * NB) { if (R.plain_t) Ts[q & 1][tid & 15][tid >> 4] = t_mine; else Ts[q & 1][tid >> 4][tid & 15] = t_mine; }
+        if (tid < NB * NB) Ts[q & 1][tid & 15][tid >> 4] = t_mine;
         if (more && tid < NB * NB) t_next = Rn.T[off + tid];
 #pragma unroll
         for (int v = 0; v < 4; ++v) Wp[q & 1][wave][4 * g + v][c] = w0[v] + w1[v];
         __syncthreads();
-        float bq[4];                                          // W' = -T^T W, formed by every wave (see reflect_strip_body)
+        float bq[4];                                          // W' = -T W, formed by every wave (see reflect_strip_body)
         {
             f32x4_t wn = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -549,25 +504,21 @@ __device__ __forceinline__ void reflect_strip_lds_body(const Reflector* refl, in
     }
 }
 
-// A block of panels applied to `outer` strips from Cout (the factorisation: the columns behind a finished block)
-// or to `acc` strips from X (forming Q), for `count` matrices, one strip per workgroup, dealt to the dies matrix by matrix
-// (deal_to_dies; a matrix's reflectors of a block of four panels are 1.1 MB).
+// A block of panels' reflectors applied to strips of X (forming Q), for `count` matrices, one strip per workgroup, dealt to the dies
+// matrix by matrix (deal_to_dies; a matrix's reflectors of a block of four panels are 1.1 MB).
 struct QrBulkArgs {
     Reflector refl[kMaxProduct]; int pending;
-    float* Cout; float* X; int outer, acc;
+    float* X; int strips;
     int64_t strip_stride; int nb_block; int64_t batch_stride; int count;
-    int per_object; bool skip_tail;      // the last of every per_object matrices has nothing here
 };
 // A strip fits the 128 registers of two workgroups per CU.
-template <int NBLK, bool SKIP = false>
+template <int NBLK>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void qr_bulk_kernel(QrBulkArgs a) {
     int matrix, b;
-    if (!deal_to_dies(blockIdx.x, a.outer + a.acc, a.count, &matrix, &b)) return;
-    if (SKIP && matrix % a.per_object == a.per_object - 1) return;
+    if (!deal_to_dies(blockIdx.x, a.strips, a.count, &matrix, &b)) return;
     const int64_t off = (int64_t)matrix * a.batch_stride;
-    float* Cs = b < a.outer ? a.Cout + (int64_t)b * a.strip_stride : a.X + (int64_t)(b - a.outer) * a.strip_stride;
-    reflect_strip_lds_body<NBLK>(a.refl, a.pending, off, Cs + off, a.nb_block);
+    reflect_strip_lds_body<NBLK>(a.refl, a.pending, off, a.X + (int64_t)b * a.strip_stride + off, a.nb_block);
 }
 
 
@@ -584,12 +535,11 @@ void qr_bulk_kernel(QrBulkArgs a) {
 // diagonal (what makes I - V T V^T orthogonal for ANY V), V^T V = L^T L + X^T (P2^T P2) X.
 // The Gram matrix squares the panel's condition number, which for m x 16 independent Gaussians is about
 // (sqrt(m) + 4) / (sqrt(m) - 4): 3 at 64 rows, 1.2 at 2000.  So this is for tall panels of a matrix drawn as independent
-// Gaussians (a panel behind its reflectors is such a matrix again); the last panels take qr_panel_body.
-// Bound by the latency of one workgroup.  With the strip in front, per launch: 9 us at 500 rows (15 with a reduction and a
-// barrier per column), of which the launch itself is 4; a whole draw alone, 543 rows: 591 -> 412 us.  Against 64 bits, compared with a reduction per column on the same Gaussians (24 draws at each of 12 sizes from
+// Gaussians (a panel behind its reflectors is such a matrix again); the last panels are square_qr_kernel's.
+// Bound by the latency of one workgroup.  With the strip in front, per launch: 9 us (15 with a reduction and a
+// barrier per column), of which the launch itself is 4.  Against 64 bits, compared with a reduction per column on the same Gaussians (24 draws at each of 12 sizes from
 // 129 to 517 rows, 8 at 1000, 4 at 2150, 2 at 4096): |A^T A - I| 0.95 to 0.99 of it, part of A^T G below the diagonal 0.99 to 1.00,
 // distance of A from the exact factor 0.90 to 1.05 (geometric means; the factor itself moves by the Gaussian's condition number).
-constexpr int kGramPanelRows = 64;       // panels of more rows than this are built from their Gram matrix
 
 constexpr int kTilePitch = NB + 4;       // floats per row of a 16 x 16 tile in LDS: row-wise 16-byte reads and column-wise 4-byte
                                          // writes of a wave are then both free of bank conflicts
@@ -604,7 +554,7 @@ struct GramShared {
 };
 
 // The panel is the strip cr (block wave + 8 b in cr[b], accumulator layout) from block FIRST on (its top tile) to block
-// `last`.  Outputs as qr_panel_body's: block FIRST of the panel goes to tile 0 of Vr and Vt.  512 threads.
+// `last`.  Outputs as direct_panel_body's, R's diagonal tile at Rd: block FIRST of the panel goes to tile 0 of Vr and Vt.  512 threads.
 // The steps on the 16 x 16 matrices are the work of wave 0 alone (on every wave they took twice as long: two waves share
 // a SIMD's issue slots); the others turn their tiles around meanwhile.
 template <int NBLK, int FIRST>
@@ -669,7 +619,7 @@ __device__ __forceinline__ void gram_panel_body(GramShared<NBLK>& sh, f32x4_t (&
             constexpr int j = decltype(jc)::value;
             const float gjj = row_bcast<j>(Gc[j]), alpha = row_bcast<j>(Pc[j]);
             const bool some = gjj > 0.f;                      // a column of zeros needs no reflector
-            // hardware reciprocals and root (1 ulp), as in qr_panel_body
+            // hardware reciprocals and root (1 ulp) keep this dependent chain short
             const float irn = some ? __builtin_amdgcn_rsqf(gjj) : 0.f;
             const float beta = -copysignf(gjj * irn, alpha), ibeta = -copysignf(irn, alpha);
             const float scale = some ? __builtin_amdgcn_rcpf(alpha - beta) : 0.f;
@@ -714,7 +664,7 @@ __device__ __forceinline__ void gram_panel_body(GramShared<NBLK>& sh, f32x4_t (&
         // T, while the other waves form V (this one has a block less than they have).  V^T V in double precision, from the
         // float Gram matrix: its rounding would be what the orthogonality of I - V T V^T is lost to (|A^T A - I| / sqrt(n) at
         // 129, 300 and 1000 rows: 4.8e-7, 5.9e-7, 9.1e-7 with float products, 4.2e-7, 5.3e-7, 8.65e-7 this way, 4.3e-7, 5.5e-7,
-        // 8.8e-7 with the sums of qr_panel_body).  The double instruction leaves row 4 v + g of column c in element v.
+        // 8.8e-7 with a reduction per column).  The double instruction leaves row 4 v + g of column c in element v.
         f64x4_t gx = {0., 0., 0., 0.}, m = {0., 0., 0., 0.};
 #pragma unroll
         for (int e = 0; e < 4; ++e) gx = __builtin_amdgcn_mfma_f64_16x16x4f64((double)gb[e], (double)xd[e], gx, 0, 0, 0);
@@ -782,75 +732,99 @@ void gram_panel_kernel(float* Mp, float* Vr, float* Vt, float* Tg, float* Rd, fl
 }
 
 // One launch per QR step p.  The chain of panel factorisations (one workgroup each) is the critical path, so
-// the launch that follows the factorisation of panel p also factorises panel p + 1.  Panels come in blocks of D.
-//   workgroup 0          applies reflector p to the 16 columns of panel p + 1, then factorises them;
-//   `inner` workgroups   (inside a block) apply reflector p to the block's later panels and to the first panel
-//                        of the next block: its columns then lack only the newest reflector when workgroup 0
-//                        gets to them, as everywhere else on the chain;
-//   `outer`              (one matrix alone) apply reflector p to the columns further on.
-// One matrix alone meets every reflector at once, everywhere: the strips of a launch then take less time than the panel
-// beside them, where strips of four reflectors took twice as long.  With several matrices side by side the columns behind a
-// block wait until it is complete (delayed update) and get all its reflectors in one pass over the strip, in a launch of
-// strips only (qr_bulk_kernel, two workgroups per compute unit, which the panel's registers rule out here): that divides the
-// memory traffic, which is what bounds several factorisations side by side, by almost D.
-// One matrix at once / delayed: 517 rows 401 / 478 us; two, three, four streams of four draws each 1.77 / 2.24, 2.09 / 2.50, 2.36 / 2.74 ms.
-// Either way a column sees the same sums in the same order, so the bits are the same: that is why the outer strips start at
-// the block's first row, although only reflector p meets them (the blocks of a strip are dealt to the waves from its
-// first row on, and each wave sums its own).
-// Every strip reads only reflectors and its own columns; panel p + 1 writes its own columns, reflector buffers
-// no strip of this launch reads, and its own T: the workgroups of one launch never touch the same data.  Waves
-// of workgroup 0 that the panel does not use leave after the strip.  Q is formed afterwards (householder_qr).
+// the launch that follows the factorisation of panel p also factorises panel p + 1.
+//   workgroup 0          applies reflector p to the 16 columns of panel p + 1, then factorises them (if they are one of these panels);
+//   the others           apply reflector p to a tile column each.
+// Every strip reads only the reflector and its own columns; panel p + 1 writes its own columns and its own reflector
+// buffers: the workgroups of one launch never touch the same data.  Q is formed afterwards (householder_qr).
 struct QrStepArgs {
-    Reflector newest;                    // reflector p, shift 0
-    int block_shift;                     // its shift as the outer strips see it: p's position in its block
-    float* C0;                           // the columns of panel p + 1: tile (row block p, column block p + 1)
-    float* Cin;                          // tile (row block p, column block p + 2): `inner` strips from here
-    float* Cout;                         // `outer` strips from here: tile (row block of the block's first panel, first column block they take)
+    Reflector reflector;                 // p
+    float* C;                            // tile (row block p, column block p + 1)
     int64_t strip_stride;                // floats between the tiles of neighbouring column blocks
-    int nb_single, nb_block;             // rows / 16 below the first row of reflector p / of the block's first reflector
-    int inner, outer;                    // strip counts
-    float* Vr_next; float* Vt_next; float* Tnext; float* Rd_next; float* rdiag_next;   // outputs of panel p + 1
-    int m_next;                          // its row count (0: no further panel)
+    int nblocks;                         // rows / 16 from reflector p's first on
+    float* Vr_next; float* Vt_next; float* Tnext; float* Rd_next; float* rdiag_next;   // outputs of panel p + 1 (Vr_next null: it is none)
     int64_t batch_stride;                // floats from one matrix's workspace to the next one's (grid y = matrix)
-    int per_object; bool skip_tail;      // the last of every per_object matrices has nothing here
 };
 
-// SKIP (a kernel of its own: the argument's way alone took 0.3 us of every step's 9)
-template <int NBLK, bool SKIP = false>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBLK >= 10 ? 2 : 4, NBLK >= 10 ? 2 : 4)))
+template <int NBLK>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void qr_step_kernel(QrStepArgs a) {
     __shared__ StripShared strip;
     const int b = blockIdx.x;
-    if (SKIP && (int)blockIdx.y % a.per_object == a.per_object - 1) return;
     const int64_t off = (int64_t)blockIdx.y * a.batch_stride;
-    if (b == 0) {
-        if (a.m_next <= 0) return;
-        // the panel starts one tile (16 rows) below reflector p's first row
-        if (a.m_next > kGramPanelRows) {
-            __shared__ GramShared<NBLK> gram;
-            reflect_strip_body<NBLK>(strip, a.newest, off, a.C0 + off, a.nb_single, [&](f32x4_t (&cr)[NBLK]) {
-                // block 0 is a finished tile of R; the rest becomes the reflectors
-                if (threadIdx.x < 64) *reinterpret_cast<f32x4_t*>(a.C0 + off + (threadIdx.x & 15) * 16 + 4 * (threadIdx.x >> 4)) = cr[0];
-                gram_panel_body<NBLK, 1>(gram, cr, a.nb_single - 1, a.Vr_next + off, a.Vt_next + off, a.Tnext + off, a.Rd_next + off, a.rdiag_next + off);
-            });
-            return;
-        }
-        if constexpr (NBLK <= 5) {
-            reflect_strip_in_place<NBLK>(strip, a.newest, off, a.C0 + off, a.nb_single);
-            __threadfence_block();
-            __syncthreads();             // the strip's stores are visible to the whole workgroup
-            if (threadIdx.x >= kGramPanelRows) return;
-            qr_panel_body<kGramPanelRows, 1>(a.C0 + off + 256, a.Vr_next + off, a.Vt_next + off, a.Tnext + off, a.Rd_next + off, a.rdiag_next + off, a.m_next);
-        }
+    float* C = a.C + off + (int64_t)b * a.strip_stride;
+    if (b > 0 || a.Vr_next == nullptr) {
+        reflect_strip_in_place<NBLK>(strip, a.reflector, off, C, a.nblocks);
         return;
     }
-    if (b <= a.inner) {
-        reflect_strip_in_place<NBLK>(strip, a.newest, off, a.Cin + off + (int64_t)(b - 1) * a.strip_stride, a.nb_single);
-        return;
+    __shared__ GramShared<NBLK> gram;
+    reflect_strip_body<NBLK>(strip, a.reflector, off, C, a.nblocks, [&](f32x4_t (&cr)[NBLK]) {
+        // block 0 is a finished tile of R; the rest becomes the reflectors
+        if (threadIdx.x < 64) *reinterpret_cast<f32x4_t*>(C + (threadIdx.x & 15) * 16 + 4 * (threadIdx.x >> 4)) = cr[0];
+        gram_panel_body<NBLK, 1>(gram, cr, a.nblocks - 1, a.Vr_next + off, a.Vt_next + off, a.Tnext + off, a.Rd_next + off, a.rdiag_next + off);
+    });
+}
+
+// ------------------------------------------------------------- the last rows, or a small matrix -- 
+// What is left of every matrix from its tile (t0, t0) on, at most 8 x 8 tiles, by one workgroup (tile_qr.h).
+// 128 rows 44 us, 64 rows 17, where a launch per panel took 8.5 each: draw alone of 144 rows 135 -> 103 us, 256 rows 203 -> 167; CONDITIONED,
+// 64 rows 257 -> 199.  Bound by the chain of 16 x 8 columns, 340 cycles each (two sums over the rows of lanes, the root, the reciprocal) and
+// 30 more for every tile it walks over, and of 1500 to 5500 per 16 columns for the reflectors of the tile column before.  Up to 16 x 16 tiles it was tried:
+// at 9 to 16 the matrix instructions of all tile columns on one CU (16 000 cycles a tile column) cost more than the launches they save (256 rows 220 us).
+// Against 64 bits, panels to the end / this (24 draws): |A^T A - I| / sqrt(n) at 129, 160, 200, 256 rows 4.18e-7 / 3.93e-7, 4.38 / 4.18, 4.64 / 4.47, 5.01 /
+// 4.92; part of A^T G below the diagonal at 129 and 256 rows 2.24e-7 / 2.0e-7, 2.81 / 2.76.
+struct SquareQrArgs {
+    float *M, *Vc, *Tmat, *Rd, *rdiag;   // Vc: null where nobody reads the reflectors row by row
+    int nbr, t0;
+    int64_t batch_stride;                // (grid x = matrix)
+};
+template <int NT>
+__global__ __launch_bounds__(64 * NT)
+void square_qr_kernel(SquareQrArgs a) {
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    const int t0 = a.t0, nbt = a.nbr - t0, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (w >= nbt) return;
+    const TileQrShared sh(lds, nbt);
+    const int64_t off = (int64_t)blockIdx.x * a.batch_stride;
+    float* column = a.M + off + ((int64_t)(t0 + w) * a.nbr + t0) * 256 + c * NB + 4 * g;
+    float y[4 * NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+        f32x4_t x = {0.f, 0.f, 0.f, 0.f};
+        if (i < nbt) x = *reinterpret_cast<const f32x4_t*>(column + i * 256);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[4 * i + e] = x[e];
     }
-    Reflector behind = a.newest;
-    behind.shift = a.block_shift;
-    reflect_strip_in_place<NBLK>(strip, behind, off, a.Cout + off + (int64_t)(b - 1 - a.inner) * a.strip_stride, a.nb_block);
+    if (w == 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sh.zero[lane * 4 + e] = 0.f;
+    }
+    const int panel = t0 + w;
+    factorise_tile_column<NT>(sh, y, w, nbt, NB, lane, [&](auto last) {
+#pragma unroll
+        for (int i = 0; i <= decltype(last)::value; ++i) *reinterpret_cast<f32x4_t*>(column + i * 256) = f32x4_t{y[4 * i], y[4 * i + 1], y[4 * i + 2], y[4 * i + 3]};      // R
+    }, [&](const ColumnEnds& ends, f32x4_t diagonal, auto tiles) {
+        constexpr int TC = decltype(tiles)::value;
+        float* v = a.Vc + off + (int64_t)panel * a.nbr * 256 + 64 * g + c;
+        float* down = column + w * 256;
+#pragma unroll
+        for (int b = 0; b < TC; ++b) {
+            if (b >= nbt - w) continue;
+            *reinterpret_cast<f32x4_t*>(down + b * 256) = f32x4_t{y[4 * b], y[4 * b + 1], y[4 * b + 2], y[4 * b + 3]};
+            if (a.Vc != nullptr) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[b * 256 + e * NB] = y[4 * b + e];
+            }
+        }
+        const f32x4_t t = exact_triangle<TC>(y, ends.some, sh.turn + (w & 1) * NB * kTurnPitch, lane);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            a.Tmat[off + panel * 256 + (4 * g + e) * NB + c] = t[e];
+            a.Rd[off + panel * 256 + (4 * g + e) * NB + c] = diagonal[e];
+        }
+        if (g == 0) a.rdiag[off + panel * NB + c] = ends.r;
+    });
 }
 
 // zeroes what lies beyond n x n of the tiled matrix M (n_pad x n_pad) and sets the tiled X to the identity
@@ -897,11 +871,8 @@ hipError_t launch_direct_panels(int rows_per_thread, const FactorWorkspace& ws, 
 
 }  // namespace
 
-// From here on the QR goes by blocks of 128 columns (block_factor.hip) and Q is formed 256 reflectors at a time (block_reflect.hip);
-// below, and for the last 144 to 256 columns, panel by panel and by strips.  One line for every count, since a matrix drawn alone and the
-// same one drawn among others agree bit for bit.  A whole draw of 720 rows, panels and strips / blocks: alone 570 / 461 us, 8 side by side
-// 838 / 685, 32 of them 1489 / 1460; 8 of 1024 rows 1343 / 1036 (of which forming Q by itself loses, 431 / 473: blocks leave no
-// row-major copies for the strips).
+// From here on Q is formed 256 reflectors at a time (block_reflect.hip), below by strips.  One line for every count, since a matrix drawn
+// alone and the same one drawn among others agree bit for bit.
 bool wide_rows(int n_pad) { return n_pad >= 720; }
 // the product of directly drawn reflectors, which has no chain of panels to lose: 256 at a time from here on, again whatever the count.
 // One alone, strips / blocks: 640 rows 145 / 157 us, 1024 rows 240 / 199, 2150 rows 713 / 417, 4301 rows 2790 / 1390; 8 side by side 1024
@@ -917,7 +888,10 @@ size_t factor_workspace_bytes(int n, bool direct) {
     if (wide_product((int)n_pad, direct)) {
         const int64_t nbr = n_pad / NB, blocks = (nbr + kWideTiles - 1) / kWideTiles, area = (int64_t)(kWideTiles * 16) * (kWideTiles * 16);
         bytes += (size_t)wide_plane_values((int)n_pad) * 2 + (size_t)(nbr * 16 * kWideTiles * 16) * (3 * 2 + kWideChunks * 4) + (size_t)(blocks * area) * (4 + 8) + 4096;
-        if (!direct) bytes += (size_t)block_panel_values((int)n_pad) * 2 + (size_t)kCoreFloats * 4;
+    }
+    if (!direct && n_pad / NB >= kBlockTiles) {
+        bytes += (size_t)block_panel_values((int)n_pad) * 2 + (size_t)kCoreFloats * 4 + 1024;
+        if (!wide_rows((int)n_pad)) bytes += (size_t)n_pad * 128 * (3 * 2 + kWideChunks * 4) + (size_t)(n_pad / NB) * kYrBlock * 2 + 1024;
     }
     return bytes;
 }
@@ -947,9 +921,15 @@ void factor_workspace_carve(void* base, int n, FactorWorkspace* ws, bool direct)
         ws->Wpart = take(w * kWideChunks);
         ws->Tbig = take(blocks * area);
         ws->wide_gram = (double*)take(blocks * area * 2);
-        if (!direct) {
-            ws->panel = (uint16_t*)take((block_panel_values((int)n_pad) + 1) / 2);
-            ws->core = take(kCoreFloats);
+    }
+    if (!direct && n_pad / NB >= kBlockTiles) {
+        p = (float*)(((uintptr_t)p + 1023) & ~(uintptr_t)1023);
+        ws->panel = (uint16_t*)take((block_panel_values((int)n_pad) + 1) / 2);
+        ws->core = take(kCoreFloats);
+        if (!wide_rows((int)n_pad)) {
+            ws->Wp = (uint16_t*)take(n_pad * 128 * 3 / 2);
+            ws->Wpart = take(n_pad * 128 * kWideChunks);
+            ws->Yr = (uint16_t*)take(n_pad / NB * kYrBlock / 2);
         }
     }
     ws->n_pad = (int)n_pad;
@@ -979,35 +959,25 @@ hipError_t pad_matrix(float* M, int64_t ld, int n, int n_pad, hipStream_t stream
 
 namespace {
 
-template <int NBLK>
-hipError_t launch_qr_step_t(const QrStepArgs& a, int count, hipStream_t s) {
-    hipLaunchKernelGGL((qr_step_kernel<NBLK>), dim3(1 + a.inner + a.outer, count), dim3(512), 0, s, a);
-    return hipGetLastError();
-}
-
-// strip blocks per wave the step and panel kernels are built for: 5 and 10 (up to 704 rows, 44 tile rows, come here: wide_rows)
+constexpr int kSquareTiles = 8;           // what one workgroup takes of the end of a matrix, or a whole one
 template <class F>
-hipError_t for_strip_blocks(int per_wave, F&& f) {
-    if (per_wave <= 5) return f(std::integral_constant<int, 5>{});
-    if (per_wave <= 10) return f(std::integral_constant<int, 10>{});
+hipError_t for_square_tiles(int tiles, F&& f) {
+    if (tiles <= 4) return f(std::integral_constant<int, 4>{});
+    if (tiles <= kSquareTiles) return f(std::integral_constant<int, kSquareTiles>{});
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_first_panel(float* Mp, float* Vr, float* Vt, float* Tg, float* Rd, float* rdiag, int m, int count, int64_t batch_stride, hipStream_t s) {
-    if (m <= kGramPanelRows) {
-        hipLaunchKernelGGL((qr_panel_kernel<kGramPanelRows, 1>), dim3(1, count), dim3(kGramPanelRows), 0, s, Mp, Vr, Vt, Tg, Rd, rdiag, m, batch_stride);
-        return hipGetLastError();
-    }
-    const int nblocks = m / NB;
-    return for_strip_blocks((nblocks + 7) / 8, [&](auto nblk) {
-        hipLaunchKernelGGL((gram_panel_kernel<decltype(nblk)::value>), dim3(1, count), dim3(512), 0, s, Mp, Vr, Vt, Tg, Rd, rdiag, nblocks, batch_stride);
+hipError_t launch_square_qr(const SquareQrArgs& a, int count, hipStream_t s) {
+    const int tiles = a.nbr - a.t0;
+    return for_square_tiles(tiles, [&](auto nt) {
+        hipLaunchKernelGGL((square_qr_kernel<decltype(nt)::value>), dim3(count), dim3(64 * tiles), tile_qr_floats(tiles) * sizeof(float), s, a);
         return hipGetLastError();
     });
 }
 
 template <int NBLK>
 hipError_t launch_qr_bulk_t(const QrBulkArgs& b, int count, hipStream_t s) {
-    hipLaunchKernelGGL((qr_bulk_kernel<NBLK>), dim3(8 * dies_slots(b.outer + b.acc, count)), dim3(512), 0, s, b);
+    hipLaunchKernelGGL((qr_bulk_kernel<NBLK>), dim3(8 * dies_slots(b.strips, count)), dim3(512), 0, s, b);
     return hipGetLastError();
 }
 
@@ -1015,10 +985,6 @@ hipError_t launch_qr_bulk(const QrBulkArgs& b, int count, hipStream_t s) {
     // blocks per wave in steps of two, up to 10 (below kWideProduct): a strip kernel sized for 20 blocks spends a third more time
     // on a strip of 11 than one sized for 12 (it still requests and waits for the blocks that do not exist)
     const int per_wave = (b.nb_block + 7) / 8;
-    if (b.skip_tail) {                                        // (at most 256 rows)
-        hipLaunchKernelGGL((qr_bulk_kernel<2, true>), dim3(8 * dies_slots(b.outer + b.acc, count)), dim3(512), 0, s, b);
-        return hipGetLastError();
-    }
     switch ((per_wave + 1) / 2) {
         case 0: case 1: return launch_qr_bulk_t<2>(b, count, s);
         case 2: return launch_qr_bulk_t<4>(b, count, s);
@@ -1029,33 +995,14 @@ hipError_t launch_qr_bulk(const QrBulkArgs& b, int count, hipStream_t s) {
     }
 }
 
-hipError_t launch_qr_step(const QrStepArgs& a, int count, hipStream_t s) {
-    const int longest = a.outer > 0 ? a.nb_block : a.nb_single;
-    if (a.skip_tail) {                                        // (at most 256 rows)
-        hipLaunchKernelGGL((qr_step_kernel<5, true>), dim3(1 + a.inner + a.outer, count), dim3(512), 0, s, a);
-        return hipGetLastError();
-    }
-    return for_strip_blocks((longest + 7) / 8, [&](auto nblk) { return launch_qr_step_t<decltype(nblk)::value>(a, count, s); });
-}
-
 }  // namespace
 
 hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t batch_stride, hipStream_t s, bool direct) {
-    return householder_qr_tails(ws, n, count, batch_stride, s, direct, 1, 0);
-}
-
-hipError_t householder_qr_tails(const FactorWorkspace& ws, int n, int count, int64_t batch_stride, hipStream_t s, bool direct, int per_object, int tail_rows) {
     if (count < 1 || count > 65535) return hipErrorInvalidValue;
     const int n_pad = ws.n_pad;
-    if (tail_rows != 0 && (direct || n != n_pad || n > 256 || tail_rows < 0 || tail_rows > n || per_object < 1 || count % per_object != 0)) return hipErrorInvalidValue;
     const int nbr = n_pad / NB;                               // tile rows (= tile columns)
     const int64_t strip_stride = (int64_t)nbr * 256;
     const int panels = nbr;
-    // panels per block
-    const int D = ws.ld >= 64 * kMaxDelay ? kMaxDelay : (ws.ld >= 128 ? 2 : 1);
-    // The tail matrices begin with the block of panels that holds their first column; what is before it is the identity, and its
-    // reflectors would meet rows where the columns behind them are zero.
-    const int tail_start = tail_rows > 0 ? tail_offset(nbr, tail_rows) / NB / D * D : 0;
     // Every panel's reflector block is kept until the end: the row-major copies side by side in ws.Vc (n_pad x 16 each,
     // n_pad x n_pad in all), the tiled copies IN PLACE of the panels they came from (a factored panel is dead: nobody
     // reads those columns of M again, and the panel kernel has all its rows in registers before it writes).
@@ -1070,82 +1017,57 @@ hipError_t householder_qr_tails(const FactorWorkspace& ws, int n, int count, int
         hipLaunchKernelGGL(qr_prepare_kernel, dim3((unsigned)((elems + 255) / 256), count), dim3(256), 0, s, ws.M, ws.X, n, n_pad, batch_stride);
         GELO_TRY(hipGetLastError());
     }
+    const bool wide = wide_product(n_pad, direct);
     if (direct) {
         // every panel's reflectors from the raw columns, in one launch: nothing to factorise, no chain of panels
         const int m = n_pad;
         if (m <= kPanelRows256) GELO_TRY(launch_direct_panels<256>((m + 255) / 256, ws, nbr, count, batch_stride, s));
         else GELO_TRY(launch_direct_panels<512>((m + 511) / 512, ws, nbr, count, batch_stride, s));
-    }
-    // large matrices: blocks of 128 columns down to the last rows; then the first panel on its own and one launch per step
-    int start = 0;
-    if (!direct) {
-        if (wide_rows(n_pad)) GELO_TRY(factor_blocks(ws, count, batch_stride, &start, s));
-        GELO_TRY(launch_first_panel(Vt_of(start), Vr_of(start), Vt_of(start), ws.Tmat + (int64_t)start * NB * NB, ws.Rd + (int64_t)start * NB * NB, ws.rdiag + start * NB,
-                                    n_pad - start * NB, count, batch_stride, s));
-        if (tail_start > 0) {
-            const int64_t first = (int64_t)(per_object - 1) * batch_stride;
-            GELO_TRY(launch_first_panel(Vt_of(tail_start) + first, Vr_of(tail_start) + first, Vt_of(tail_start) + first, ws.Tmat + (int64_t)tail_start * NB * NB + first,
-                                        ws.Rd + (int64_t)tail_start * NB * NB + first, ws.rdiag + tail_start * NB + first, n_pad - tail_start * NB,
-                                        count / per_object, per_object * batch_stride, s));
+    } else {
+        // blocks of 128 columns, panels by themselves until one workgroup can take the rest
+        int start = 0;
+        if (nbr >= kBlockTiles) GELO_TRY(factor_blocks(ws, wide ? nullptr : ws.Vc, count, batch_stride, &start, s));
+        const int stop = nbr - start > kSquareTiles ? nbr - kSquareTiles : start;
+        if (start < stop) {
+            hipLaunchKernelGGL((gram_panel_kernel<kStepBlocks>), dim3(1, count), dim3(512), 0, s, Vt_of(start), Vr_of(start), Vt_of(start),
+                               ws.Tmat + (int64_t)start * NB * NB, ws.Rd + (int64_t)start * NB * NB, ws.rdiag + start * NB, nbr - start, batch_stride);
+            GELO_TRY(hipGetLastError());
         }
-    }
-    for (int p = start; p < panels && !direct; ++p) {
-        const int p0 = p / D * D;                             // first panel of p's block
-        const bool last = p + 1 == panels;
-        const int block_end = p0 + D < panels ? p0 + D : panels;     // one past the block's last panel
-        QrStepArgs a;
-        auto reflector = [&](int q, int shift) { return Reflector{Vr_of(q), Vt_of(q), ws.Tmat + (int64_t)q * NB * NB, shift, 0}; };
-        const bool block_done = p + 1 == block_end;           // panel p is the last of its block (or of the matrix)
-        a.newest = reflector(p, 0);
-        a.strip_stride = strip_stride;
-        a.nb_single = nbr - p; a.nb_block = nbr - p0;
-        a.C0 = last ? ws.M : ws.M + (int64_t)(p + 1) * strip_stride + (int64_t)p * 256;
-        a.Cin = ws.M + (int64_t)(p + 2 < nbr ? p + 2 : 0) * strip_stride + (int64_t)p * 256;
-        // the block's panels behind p + 1 and the first panel of the next block
-        a.inner = block_done ? 0 : (block_end < nbr ? block_end : nbr - 1) - (p + 1);
-        // the columns further on: one matrix alone, at once; several matrices, once the block is complete (see QrStepArgs)
-        const bool delayed = count >= kBulkFromCount;
-        const int from = block_done ? p + 2 : block_end + 1;
-        float* behind = ws.M + (int64_t)(from < nbr ? from : 0) * strip_stride + (int64_t)p0 * 256;
-        a.outer = !delayed && from < nbr ? nbr - from : 0;
-        a.Cout = behind;
-        a.block_shift = p - p0;
-        a.Vr_next = Vr_of(p + 1); a.Vt_next = Vt_of(p + 1);
-        a.Tnext = ws.Tmat + (int64_t)(p + 1) * NB * NB; a.Rd_next = ws.Rd + (int64_t)(p + 1) * NB * NB; a.rdiag_next = ws.rdiag + (p + 1) * NB;
-        a.m_next = last ? 0 : n_pad - (p + 1) * NB;
-        a.batch_stride = batch_stride;
-        a.per_object = per_object; a.skip_tail = p < tail_start;
-        if (delayed && block_done && from < nbr) {
-            QrBulkArgs b;
-            b.pending = p - p0 + 1;
-            for (int q = 0; q < kMaxProduct; ++q) { const int i = q < b.pending ? q : 0; b.refl[q] = reflector(p0 + i, i); }
-            b.Cout = behind; b.X = behind; b.outer = nbr - from; b.acc = 0;
-            b.strip_stride = strip_stride; b.nb_block = a.nb_block; b.batch_stride = batch_stride; b.count = count;
-            b.per_object = per_object; b.skip_tail = a.skip_tail;
-            GELO_TRY(launch_qr_bulk(b, count, s));
+        for (int p = start; p < stop; ++p) {
+            QrStepArgs a;
+            a.reflector = Reflector{Vr_of(p), Vt_of(p), ws.Tmat + (int64_t)p * NB * NB, 0};
+            a.C = ws.M + (int64_t)(p + 1) * strip_stride + (int64_t)p * 256;
+            a.strip_stride = strip_stride;
+            a.nblocks = nbr - p;
+            a.Vr_next = p + 1 < stop ? Vr_of(p + 1) : nullptr; a.Vt_next = Vt_of(p + 1);
+            a.Tnext = ws.Tmat + (int64_t)(p + 1) * NB * NB; a.Rd_next = ws.Rd + (int64_t)(p + 1) * NB * NB; a.rdiag_next = ws.rdiag + (p + 1) * NB;
+            a.batch_stride = batch_stride;
+            hipLaunchKernelGGL((qr_step_kernel<kStepBlocks>), dim3(nbr - p - 1, count), dim3(512), 0, s, a);
+            GELO_TRY(hipGetLastError());
         }
-        if (last) break;                                      // no panel and no column left
-        GELO_TRY(launch_qr_step(a, count, s));
+        SquareQrArgs a;
+        a.M = ws.M; a.Vc = wide ? nullptr : ws.Vc; a.Tmat = ws.Tmat; a.Rd = ws.Rd; a.rdiag = ws.rdiag;
+        a.nbr = nbr; a.t0 = stop; a.batch_stride = batch_stride;
+        GELO_TRY(launch_square_qr(a, count, s));
     }
-    if (wide_product(n_pad, direct)) return form_product_wide(ws, count, batch_stride, s);
+    if (wide) return form_product_wide(ws, count, batch_stride, s);
     {
         // X = I so far.  Block by block from the last: X[p0:, p0:] <- H_p0 (H_p0+1 (... X[p0:, p0:])), one 16-column
         // strip per workgroup, the block's reflectors newest first, each as I - V T V^T.
         // (Columns that a pass meets before their own block's turn hold the identity below the pass's first row: the
         // reflectors beyond their block leave them as they are, bit for bit, so the grouping does not show in Q.)
-        const int Dq = ws.ld >= 64 * kMaxProduct ? kMaxProduct : D;
+        const int Dq = ws.ld >= 64 * kMaxProduct ? kMaxProduct : ws.ld >= 256 ? 4 : ws.ld >= 128 ? 2 : 1;
         for (int p0 = (panels - 1) / Dq * Dq; p0 >= 0; p0 -= Dq) {
             const int pend = panels - p0 < Dq ? panels - p0 : Dq;
             QrBulkArgs b;
             for (int q = 0; q < kMaxProduct; ++q) {
                 const int src = q < pend ? pend - 1 - q : 0;
                 b.refl[q].Vr = Vr_of(p0 + src); b.refl[q].Vt = Vt_of(p0 + src);
-                b.refl[q].T = ws.Tmat + (int64_t)(p0 + src) * NB * NB; b.refl[q].shift = src; b.refl[q].plain_t = 1;
+                b.refl[q].T = ws.Tmat + (int64_t)(p0 + src) * NB * NB; b.refl[q].shift = src;
             }
-            b.pending = pend; b.Cout = ws.X; b.X = ws.X + (int64_t)p0 * strip_stride + (int64_t)p0 * 256;
-            b.outer = 0; b.acc = nbr - p0;
+            b.pending = pend; b.X = ws.X + (int64_t)p0 * strip_stride + (int64_t)p0 * 256;
+            b.strips = nbr - p0;
             b.strip_stride = strip_stride; b.nb_block = nbr - p0; b.batch_stride = batch_stride; b.count = count;
-            b.per_object = per_object; b.skip_tail = pend + p0 <= tail_start;
             GELO_TRY(launch_qr_bulk(b, count, s));
         }
     }

@@ -304,7 +304,7 @@ struct FactorWorkspace {
     float* Wpart;                    // sums of ranges of rows, up to kWideChunks of them
     float* Tbig;                     // per wide block its 256 x 256 triangle
     double* wide_gram;               // per wide block Y^T Y, tiles above the diagonal
-    // the factorisation by blocks (block_factor.hip): from wide_rows on
+    // the factorisation by blocks (block_factor.hip): from kBlockTiles tile rows on (with Wp, Wpart and Yr)
     uint16_t* panel;                 // the panel of the block being factorised, taken apart
     float* core;                     // the 128 x 128 triangles of that block
     int n_pad; int64_t ld;
@@ -312,14 +312,21 @@ struct FactorWorkspace {
 constexpr int kWideTiles = 16;       // tile columns of a wide block: 256 reflectors
 constexpr int kWideChunks = 8, kWideParts = 4;
 constexpr int kWideCus = 256;
-bool wide_rows(int n_pad);           // is such a matrix factorised by blocks of 128 columns, and its Q formed 256 reflectors at a time?
+bool wide_rows(int n_pad);           // is such a matrix's Q formed 256 reflectors at a time?
 int64_t wide_plane_values(int n_pad);        // 16-bit values of Yp and Yr together
 int64_t wide_yr_offset(int n_pad);           // Yr's start behind Yp's
 int64_t block_panel_values(int n_pad);       // 16-bit values of `panel`
 constexpr int kCoreFloats = 3 * 128 * 128;
-// Factorises 128 columns at a time until 144 to 256 rows (9 to 16 tiles) are left: reflectors, R and its diagonal, T as
-// householder_qr's own panels leave them (but no row-major copies); *panels_done panels of 16
-hipError_t factor_blocks(const FactorWorkspace& ws, int count, int64_t batch_stride, int* panels_done, hipStream_t stream);
+// Factorises 128 columns at a time, matrices from kBlockTiles tile rows on, while last_block_tiles and more of them are left: reflectors
+// (row by row where Vc is not null), R and its diagonal, T as householder_qr's own panels leave them; *panels_done panels of 16.
+// The lines are drawn by accuracy: a block's Gram matrix squares its panel's condition number, and what that costs shows the less the more
+// of the matrix is behind better blocks.  Part of A^T G below the diagonal, of |G| (24 draws), panels by themselves / a last block of 16,
+// 20 or more tile rows: 256 rows 2.81e-7 / 3.52e-7, 300 2.99 / 3.46, 400 3.35 / 3.37 (of 25 tile rows), 430 3.46 / 3.40 (of 27), 512 3.72 / 3.59,
+// 543 3.82 / 3.69, 600 4.00 / 3.83.  A draw alone, panels / blocks: 430 rows 335 / 285 us, 543 rows 416 / 338, 700 rows 555 / 428.
+constexpr int kBlockTiles = 26;
+inline int last_block_tiles(int nbr) { return nbr >= 45 ? 15 : 20; }
+constexpr int kYrBlock = 3 * 4 * 512;        // 16-bit values of a tile row of a block's reflectors taken apart
+hipError_t factor_blocks(const FactorWorkspace& ws, float* Vc, int count, int64_t batch_stride, int* panels_done, hipStream_t stream);
 // ws.X <- H_0 H_1 ... ws.X for the panels' reflectors householder_qr has left in ws.M and ws.Tmat
 hipError_t form_product_wide(const FactorWorkspace& ws, int count, int64_t batch_stride, hipStream_t stream);
 // direct: for the product of directly drawn reflectors alone, which takes less
@@ -335,10 +342,6 @@ void factor_workspace_carve(void* base, int n, FactorWorkspace* ws, bool direct 
 // stands (rows k onward), so ws.X becomes the product H_0 H_1 ... H_{n-1} of directly drawn reflectors and
 // ws.rdiag the values beta_k those reflectors map their columns to; no chain of dependent panels.
 hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t batch_stride, hipStream_t stream, bool direct = false);
-// The same where, with `tail_rows` > 0 (not `direct`, n a multiple of 16 below the blocks' sizes), of every `per_object` matrices the last is
-// the identity up to tail_offset(n / 16, tail_rows): only what is behind it is factorised, beside the others.
-hipError_t householder_qr_tails(const FactorWorkspace& ws, int n, int count, int64_t batch_stride, hipStream_t stream, bool direct,
-                                int per_object, int tail_rows);
 // Behind householder_qr(ws, n, 1, ..., direct = false) of the matrix A (n rows of pitch ldk, ldk % 64 == 0, zero beyond column n;
 // read up to 128 rows only): A^-1 = R^-1 Q^T into Ainv32 and, unless it is null, rounded into Ainv16, laid out like A;
 // *ws.flag != 0 if R has a zero on its diagonal.  Overwrites ws.M, ws.Vc and ws.Dinv.

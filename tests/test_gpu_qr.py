@@ -213,6 +213,34 @@ def test_inverse_from_the_factors(ctx, n, bf16):             # (ctx: brings the 
     assert float((X - exact).norm() / exact.norm()) < bound
 
 
+# R and Q of matrices that are factorised in different parts: one workgroup alone (one to eight tiles, whole and broken), panels in front of it (one to
+# seventeen of them), blocks of 128 columns in front of those.  Q^T A leaves R: its part below the diagonal and what it differs from R's
+# tiles by are rounding, c sqrt(n) of it
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 64, 65, 81, 100, 127, 128, 129, 145, 250, 256, 400, 415, 417, 545, 703])
+def test_factors_of_a_gaussian(ctx, n):
+    A = torch.randn((n, n), generator=torch.Generator().manual_seed(n)).cuda()
+    ws = Workspace(n)
+    ws.factorise(A)
+    torch.cuda.synchronize()
+    tiles = ws.pad // 16
+
+    def dense(part):
+        return ws.at(part, ws.pad * ws.pad).view(tiles, tiles, 16, 16).permute(1, 3, 0, 2).reshape(ws.pad, ws.pad).double()
+    Q, above, diagonal = dense(1), dense(0), ws.at(4, ws.pad * 16).view(tiles, 16, 16).double()
+    bound = 20 * EPS * math.sqrt(n) + 1e-7
+    assert float((Q.t().contiguous() @ Q - torch.eye(ws.pad, dtype=torch.float64, device="cuda")).norm()) / math.sqrt(n) < bound
+    padded = torch.zeros((ws.pad, ws.pad), dtype=torch.float64, device="cuda")
+    padded[:n, :n] = A.double()
+    R = Q.t().contiguous() @ padded
+    kept = torch.zeros_like(R)
+    for j in range(tiles):
+        kept[:16 * j, 16 * j:16 * j + 16] = above[:16 * j, 16 * j:16 * j + 16]
+        kept[16 * j:16 * j + 16, 16 * j:16 * j + 16] = diagonal[j]
+    assert float(torch.tril(R, -1).norm() / padded.norm()) < bound
+    assert float((torch.triu(R) - kept).norm() / padded.norm()) < bound
+    assert torch.equal(torch.diagonal(kept).float(), ws.at(6, ws.pad))
+
+
 class GemmSum(ctypes.Structure):
     _fields_ = [("A", ctypes.c_void_p * 5), ("B", ctypes.c_void_p * 5), ("count", ctypes.c_int), ("x", ctypes.c_void_p), ("x_low", ctypes.c_void_p),
                 ("identity", ctypes.c_bool), ("subtract", ctypes.c_bool), ("out", ctypes.c_void_p), ("out_low", ctypes.c_void_p), ("out32", ctypes.c_void_p),
