@@ -439,9 +439,8 @@ static BlockPiece block_piece(int n_data, int k, int i) {
     b.data0 = r0 - s0; b.data_rows = b.rows - b.shield_rows;
     return b;
 }
-// Blocks that share the launches of one batched factorisation (draw_blocks): the full ones, and the last one unless the
-// one-workgroup factorisation takes it.
-static int blocks_side_by_side(int n) { return n / GELO_BLOCK_ROWS + (n % GELO_BLOCK_ROWS > kSmallMaxN ? 1 : 0); }
+// Blocks that share the launches of one batched factorisation (draw_blocks): all, unless there is one that the one-workgroup draw takes.
+static int blocks_side_by_side(int n) { return n <= kSmallMaxN ? 0 : block_count(n); }
 // their workspaces, one behind the other
 static size_t block_workspace_bytes(int n) {
     return (size_t)blocks_side_by_side(n) * up256(factor_workspace_bytes(n < GELO_BLOCK_ROWS ? n : GELO_BLOCK_ROWS));
@@ -473,34 +472,24 @@ static gelo_status check_sample_args(gelo_ctx* ctx, gelo_kind kind, int n_data, 
 }
 
 // The blocks of `count` BLOCK_ORTHOGONAL objects (targets t, batch ids from `first` on; base: their factorisation workspaces,
-// object-major).  The full blocks share the launches of one batched factorisation.  A last, shorter one of more than kSmallMaxN rows takes
-// part in it as the end of a full-size matrix that begins with the identity; its panels start when the others' have as many rows
-// left.  With a chain of launches of its own behind the others', 1 and 32 draws: 129 rows (641 in all) 368 and 743 us, now 255 and
-// 658; 255 rows (767) 438 and 833, now 254 and 678; |A^T A - I| / sqrt(rows) over 48 draws 4.18e-7 and 4.17e-7 at 129 rows, 4.62e-7 and 4.64e-7 at 200.
-// Up to kSmallMaxN rows: one launch of the one-workgroup factorisation, 10 to 60 us and a
-// little more exact (102 rows beside eight blocks, as the end of a ninth: 308 -> 262 us, 32 draws 1026 -> 1058, |A^T A - I| 3.7e-7 -> 4.0e-7).
+// object-major).  The blocks share the launches of one batched factorisation.  A last, shorter one takes part in it as the end of a full-size
+// matrix that begins with the identity.  With one up to kSmallMaxN rows left to a launch of the one-workgroup draw behind the others, 10 to 60 us: one draw of
+// 300 rows 225 -> 171 us, 2150 rows 240 -> 177, 32 of 300 rows 568 -> 543, of 2150 rows 974 -> 970.  |A^T A - I| / sqrt(rows) of the last block by the
+// one-workgroup draw / here (48 draws): 8 rows 2.12e-7 / 2.22e-7, 16 2.47 / 2.88, 36 2.83 / 2.91, 64 3.20 / 3.02, 100 3.62 / 3.02, 128 3.90 / 3.08 (the whole blocks 3.31).
 static hipError_t draw_blocks(const SmallSampleTargets& t, int count, uint64_t first, PhiloxStream ps, int n, int d, int64_t ldk, char* base,
                               hipStream_t s) {
     constexpr int B = GELO_BLOCK_ROWS;
     const int full = n / B, rest = n % B, side = blocks_side_by_side(n);
     ps.c1 = kStreamBlock << 8; ps.c2 = (uint32_t)first; ps.c3 = (uint32_t)(first >> 32);
-    if (side > 0) {
-        const int rows = n < B ? n : B, tail = full > 0 && side > full ? rest : 0;
-        FactorWorkspace w;
-        factor_workspace_carve(base, rows, &w);
-        const int64_t stride = (int64_t)(up256(factor_workspace_bytes(rows)) / sizeof(float));
-        hipError_t e = fill_normal_batched(w.M, stride, w.n_pad / 16, rows, rows, ps, side, side * count, false, s, tail);
-        if (e == hipSuccess) e = householder_qr(w, rows, side * count, stride, s);
-        if (e == hipSuccess) e = emit_batched(w.X, w.rdiag, stride, w.n_pad / 16, rows, ldk, t, count, side, 0, (int64_t)B * ldk, s, tail);
-        if (e != hipSuccess) return e;
-    }
-    if (rest == 0 || rest > kSmallMaxN) return hipSuccess;
-    SmallSampleTargets r = t;
-    const int64_t at = (int64_t)full * B * ldk;
-    r.off_A32 += 4 * at; r.off_Ainv32 += 4 * at;
-    if (r.off_A16 >= 0) { r.off_A16 += 2 * at; r.off_Ainv16 += 2 * at; }
-    ps.c1 = (kStreamBlock << 8) | (uint32_t)full;
-    return small_sample(r, count, first, ps, 0, rest, 0, d, ldk, s);
+    if (side == 0) return small_sample(t, count, first, ps, 0, n, 0, d, ldk, s);
+    const int rows = n < B ? n : B, tail = full > 0 ? rest : 0;
+    FactorWorkspace w;
+    factor_workspace_carve(base, rows, &w);
+    const int64_t stride = (int64_t)(up256(factor_workspace_bytes(rows)) / sizeof(float));
+    hipError_t e = fill_normal_batched(w.M, stride, w.n_pad / 16, rows, rows, ps, side, side * count, false, s, tail);
+    if (e == hipSuccess) e = householder_qr(w, rows, side * count, stride, s);
+    if (e == hipSuccess) e = emit_batched(w.X, w.rdiag, stride, w.n_pad / 16, rows, ldk, t, count, side, 0, (int64_t)B * ldk, s, tail);
+    return e;
 }
 
 // Enqueues the draw of batch `batch_id` into the buffers `m` points at, with `ws` as factorisation

@@ -3,7 +3,7 @@
 // with the inverse of the non-orthogonal kinds, which is built on the same factorisation.  Everything is float and deterministic: reductions run in a fixed order, no
 // atomics.
 //
-// Matrices from 416 rows on are factorised by blocks of 128 columns (block_factor.hip); smaller ones, and what the blocks leave (112 to 304
+// Matrices from 336 rows on are factorised by blocks of 128 columns (block_factor.hip); smaller ones, and what the blocks leave (112 to 272
 // rows), by panels of 16 columns, each by ONE workgroup from its 16 x 16 Gram matrix (gram_panel_body); the last 128 rows, or a matrix of no
 // more, by one workgroup in registers (square_qr_kernel).  Reflectors are applied on the matrix cores.  From 720 rows on Q is formed by
 // blocks of 256 reflectors (block_reflect.hip), below by strips of 16 columns.
@@ -220,7 +220,9 @@ void direct_panels_kernel(float* M, float* Vc, float* Tmat, float* rdiag, int nb
 // v_mfma_f32_16x16x4_f32, so the same registers serve as the B operand of W = V^T C (K = rows)
 // and as the accumulator of C -= V W' (K = the 16 reflectors).  Wave w of 8 owns blocks
 // w, w+8, ...; the 8 partial W are added in wave order (fixed order, reproducible), then
-// W' = -op(T) W is formed once per strip.
+// W' = -op(T) W is formed once per strip.  V W' is summed by itself and added to C once: with C in the accumulator every
+// instruction rounds at its size (|A^T A - I| / sqrt(n) at 129, 256, 400, 700 rows 3.93e-7, 4.92e-7, 5.82e-7, 7.33e-7 that way, 3.12e-7, 3.31e-7, 3.51e-7, 3.74e-7
+// now; part of A^T G below the diagonal at 256 rows 2.76e-7, now 1.82e-7; 1% of a draw's time).
 // Layouts, chosen so that every global access of a wave is one contiguous kilobyte, 16 bytes per
 // lane: the strip is a column of 16 x 16 tiles (256 floats each, [column][row] inside: the four
 // rows 4 g .. 4 g + 3 a lane owns are adjacent), the reflectors come in the same tiles (Vt) for the
@@ -342,8 +344,10 @@ __device__ __forceinline__ void reflect_strip_body(StripShared& sh, const Reflec
             const int b = grp * GRP + k;
             const f32x4_t a4 = va[j & 1][k];
             if (wave + 8 * b > last) continue;
+            f32x4_t sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) cr[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[kk], bq[kk], cr[b], 0, 0, 0);
+            for (int kk = 0; kk < 4; ++kk) sum = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[kk], bq[kk], sum, 0, 0, 0);
+            cr[b] += sum;
         }
         request(std::integral_constant<int, j + 2>{});
     });
@@ -491,8 +495,10 @@ __device__ __forceinline__ void reflect_strip_lds_body(const Reflector* refl, in
                 if (wave + 8 * b > last) return;
                 landed(std::integral_constant<int, j>{}, kc);
                 const f32x4_t a4 = *reinterpret_cast<const f32x4_t*>(mine + (((2 * NG * q + j) % DEPTH) * GRP + k) * 256);
+                f32x4_t sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) cr[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[kk], bq[kk], cr[b], 0, 0, 0);
+                for (int kk = 0; kk < 4; ++kk) sum = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[kk], bq[kk], sum, 0, 0, 0);
+                cr[b] += sum;
             });
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         });
@@ -771,15 +777,15 @@ void qr_step_kernel(QrStepArgs a) {
 // 64 rows 257 -> 199.  Bound by the chain of 16 x 8 columns, 340 cycles each (two sums over the rows of lanes, the root, the reciprocal) and
 // 30 more for every tile it walks over, and of 1500 to 5500 per 16 columns for the reflectors of the tile column before.  Up to 16 x 16 tiles it was tried:
 // at 9 to 16 the matrix instructions of all tile columns on one CU (16 000 cycles a tile column) cost more than the launches they save (256 rows 220 us).
-// Against 64 bits, panels to the end / this (24 draws): |A^T A - I| / sqrt(n) at 129, 160, 200, 256 rows 4.18e-7 / 3.93e-7, 4.38 / 4.18, 4.64 / 4.47, 5.01 /
-// 4.92; part of A^T G below the diagonal at 129 and 256 rows 2.24e-7 / 2.0e-7, 2.81 / 2.76.
+// Against 64 bits, panels to the end / this (24 draws, other things equal): |A^T A - I| / sqrt(n) at 129, 160, 200, 256 rows 4.18e-7 / 3.93e-7, 4.38 / 4.18,
+// 4.64 / 4.47, 5.01 / 4.92; part of A^T G below the diagonal at 129 and 256 rows 2.24e-7 / 2.0e-7, 2.81 / 2.76.
 struct SquareQrArgs {
     float *M, *Vc, *Tmat, *Rd, *rdiag;   // Vc: null where nobody reads the reflectors row by row
     int nbr, t0;
     int64_t batch_stride;                // (grid x = matrix)
 };
-template <int NT>
-__global__ __launch_bounds__(64 * NT)
+template <int NT, int WAVES>                                // WAVES: on a SIMD
+__global__ __launch_bounds__(64 * NT) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES)))
 void square_qr_kernel(SquareQrArgs a) {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
@@ -960,19 +966,15 @@ hipError_t pad_matrix(float* M, int64_t ld, int n, int n_pad, hipStream_t stream
 namespace {
 
 constexpr int kSquareTiles = 8;           // what one workgroup takes of the end of a matrix, or a whole one
-template <class F>
-hipError_t for_square_tiles(int tiles, F&& f) {
-    if (tiles <= 4) return f(std::integral_constant<int, 4>{});
-    if (tiles <= kSquareTiles) return f(std::integral_constant<int, kSquareTiles>{});
-    return hipErrorInvalidValue;
-}
-
 hipError_t launch_square_qr(const SquareQrArgs& a, int count, hipStream_t s) {
     const int tiles = a.nbr - a.t0;
-    return for_square_tiles(tiles, [&](auto nt) {
-        hipLaunchKernelGGL((square_qr_kernel<decltype(nt)::value>), dim3(count), dim3(64 * tiles), tile_qr_floats(tiles) * sizeof(float), s, a);
-        return hipGetLastError();
-    });
+    const dim3 grid(count), block(64 * tiles);
+    const size_t lds = tile_qr_floats(tiles) * sizeof(float);
+    if (tiles <= 4) hipLaunchKernelGGL((square_qr_kernel<4, 4>), grid, block, lds, s, a);
+    // more matrices than CUs: two workgroups on one, for which a few registers are spilled (32 draws in nine blocks each 998 -> 965 us, one 177 -> 180)
+    else if (count > kWideCus) hipLaunchKernelGGL((square_qr_kernel<kSquareTiles, 4>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((square_qr_kernel<kSquareTiles, 2>), grid, block, lds, s, a);
+    return hipGetLastError();
 }
 
 template <int NBLK>

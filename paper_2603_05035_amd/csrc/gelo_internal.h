@@ -320,11 +320,11 @@ constexpr int kCoreFloats = 3 * 128 * 128;
 // Factorises 128 columns at a time, matrices from kBlockTiles tile rows on, while last_block_tiles and more of them are left: reflectors
 // (row by row where Vc is not null), R and its diagonal, T as householder_qr's own panels leave them; *panels_done panels of 16.
 // The lines are drawn by accuracy: a block's Gram matrix squares its panel's condition number, and what that costs shows the less the more
-// of the matrix is behind better blocks.  Part of A^T G below the diagonal, of |G| (24 draws), panels by themselves / a last block of 16,
-// 20 or more tile rows: 256 rows 2.81e-7 / 3.52e-7, 300 2.99 / 3.46, 400 3.35 / 3.37 (of 25 tile rows), 430 3.46 / 3.40 (of 27), 512 3.72 / 3.59,
-// 543 3.82 / 3.69, 600 4.00 / 3.83.  A draw alone, panels / blocks: 430 rows 335 / 285 us, 543 rows 416 / 338, 700 rows 555 / 428.
-constexpr int kBlockTiles = 26;
-inline int last_block_tiles(int nbr) { return nbr >= 45 ? 15 : 20; }
+// of the matrix is behind better blocks.  Part of A^T G below the diagonal, of |G|, and distance of A from the exact factor (24 draws), panels
+// by themselves / blocks down to 15 tile rows: 256 rows 1.82e-7 and 7.3e-7 / 3.14e-7 and 14.1e-7, 300 rows 1.87 and 7.2 / 2.96 and 13.6, 400 rows 1.96 and 8.6 / 3.05
+// and 16.6.  A draw alone: 360 rows 233 / 220 us, 430 rows 335 / 262, 543 rows 416 / 326, 700 rows 555 / 428.
+constexpr int kBlockTiles = 21;
+inline int last_block_tiles(int nbr) { return nbr >= 45 ? 15 : 18; }
 constexpr int kYrBlock = 3 * 4 * 512;        // 16-bit values of a tile row of a block's reflectors taken apart
 hipError_t factor_blocks(const FactorWorkspace& ws, float* Vc, int count, int64_t batch_stride, int* panels_done, hipStream_t stream);
 // ws.X <- H_0 H_1 ... ws.X for the panels' reflectors householder_qr has left in ws.M and ws.Tmat
