@@ -1,13 +1,14 @@
 // Householder QR of a large matrix in blocks of 128 columns (Section 3.2 step 1.2's orthogonal factor): the columns until
-// 144 to 256 rows are left; householder_qr's chain of panels takes those.  No panel is walked column by column.  With P the block's
+// 112 to 272 rows are left; householder_qr's panels take those.  No panel is walked column by column.  With P the block's
 // m x 128 panel, C the columns behind it, C1 and P1 their first 128 rows,
 //
-//   S  = P^T [P | C]                    launch_panel_products
-//   P^T P = R^T R,  P1 - R = L U        block_core_kernel, one workgroup: Cholesky and LU elimination together, the sign of every
+//   S  = P^T [P | C]                    launch_panel_products; of C, behind the first block, block_overlap_kernel
+//   P^T P = R^T R,  P1 - R = L U        block_core, one workgroup: Cholesky and LU elimination together, the sign of every
 //                                       row of R opposite to the pivot it meets; R^-T, L^-1 and U^-1 beside them
 //   Y  = [L ; P2 U^-1]                  the Householder vectors: I - Y T Y^T maps P to [R ; 0]
 //   R1 = R^-T S,  N = L^-1 (C1 - R1)    block_apply_kernel: R's rows behind the block; T^T Y^T C without T
-//   C2 <- C2 - Y2 N                     launch_block_update, which also takes the next panel apart for the next S
+//   C2 <- C2 - Y2 N                     the next panel's columns by launch_block_update, which also takes the panel apart for the next S;
+//                                       the others in block_overlap_kernel, beside the next panel's 128 x 128 part
 //
 // The LU elimination of the panel's top minus R is how Householder vectors are had from an orthogonal factor (Ballard, Demmel,
 // Grigori, Jacquelin, Knight, Nguyen, "Reconstructing Householder vectors from tall-skinny QR", 2015), here with R from the Gram
@@ -15,11 +16,12 @@
 // (sqrt(m) + 11.3) / (sqrt(m) - 11.3): 1.6 at 2150 rows, 5.8 at 256, where the blocks end.  CONDITIONED matrices' panels are
 // no worse than A (2 to 4).
 //
-// A draw alone is bound by the chain of these four launches, 8 to 15 + 31.5 + 7 + 5 to 25 us per 128 columns at 2150 rows; panel by
-// panel it was eight launches of 9 to 28.  A whole draw, panels / blocks: 720 rows 570 / 461 us, 1024 rows 878 / 634, 2150 rows
-// 2661 / 1417, 4301 rows 9530 / 4020; 32 side by side 720 rows 1489 / 1460, 1024 rows 2642 / 2386, 2150 rows 14730 / 10590.  Against 64 bits, panels / blocks (four draws): |A^T A - I| / sqrt(n) at 720, 1040, 2150 rows
-// 7.5e-7 / 5.3e-7, 8.8e-7 / 5.7e-7, 1.24e-6 / 6.4e-7; part of A^T G below the diagonal, of |G|, 4.34e-7 / 3.79e-7, 5.14e-7 / 3.86e-7,
-// 7.3e-7 / 4.0e-7; distance of A from the exact factor at 1300 and 2150 rows 2.6e-6 / 1.9e-6, 3.4e-6 / 1.6e-6.
+// A draw alone is bound by the chain of four launches per 128 columns, at 2150 rows 5.5 (panel update) + 9 (P^T P) + 34 (the core, with the columns
+// further on beside it) + 7.5 us; with those columns in the chain it was 8 to 15 + 31.5 + 7 + 5 to 25.  A whole draw, that way / now: 1024 rows 584 / 581 us,
+// 2150 rows 1371 / 1342, 4301 rows 4000 / 3622; 8 side by side 2150 rows 3680 / 3227; 32, whose columns pass through memory once a block instead of twice, 10 420 /
+// 10 150; up to 720 rows it makes no difference.  Panel by panel 2150 rows took 2661, 32 side by side 14 730.  Against 64 bits, panels / blocks (four
+// draws): |A^T A - I| / sqrt(n) at 720, 1040, 2150 rows 7.5e-7 / 5.3e-7, 8.8e-7 / 5.7e-7, 1.24e-6 / 6.4e-7; part of A^T G below the diagonal, of |G|,
+// 4.34e-7 / 3.77e-7, 5.14e-7 / 3.86e-7, 7.3e-7 / 4.0e-7; distance of A from the exact factor at 1300 and 2150 rows 2.6e-6 / 1.9e-6, 3.4e-6 / 1.6e-6.
 #include "block_reflect.h"
 #include "wave_tile.h"
 
@@ -166,14 +168,12 @@ __device__ __forceinline__ void core_diagonal(CoreShared& sh, int q, int i, f32x
 // beside it its 16 columns took 6700 cycles instead of 4900).
 constexpr int kCoreThreads = 640;
 template <int RANGES>
-__global__ __launch_bounds__(kCoreThreads)
-void block_core_kernel(BlockArgs a) {
-    __shared__ CoreShared sh;
+__device__ __forceinline__ void block_core(const BlockArgs& a, CoreShared& sh, int matrix) {
     const int tid = threadIdx.x, lane = tid & 63, number = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (number == 7) return;
     const int wave = number == 3 ? BT : number < 3 ? number : number < 7 ? number - 1 : number - 2;
     const int c = lane & 15, g = lane >> 4;
-    const int64_t off = (int64_t)blockIdx.x * a.w.batch_stride;
+    const int64_t off = (int64_t)matrix * a.w.batch_stride;
     float* X = a.w.X + off;
     float* core = a.core + off;
     auto tile = [&](int k, int l) { return X + ((int64_t)l * a.w.nbr + k) * 256; };
@@ -274,6 +274,130 @@ void block_core_kernel(BlockArgs a) {
         ++i;
         asm volatile("" : "+s"(i));                       // (the compiler would peel the first steps off)
     }
+}
+
+template <int RANGES>
+__global__ __launch_bounds__(kCoreThreads)
+void block_core_kernel(BlockArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    block_core<RANGES>(a, *reinterpret_cast<CoreShared*>(lds), blockIdx.x);
+}
+
+// ------------------------------------------------------------ beside it: the columns further on --
+// The columns behind the panel do not hold up its 128 x 128 part: while one workgroup is at that, the others bring them up to date with
+// the block before (C <- C - Y2 N) and, with the rows still in registers, take P^T C of them.  A workgroup has eight tile columns,
+// a wave each, of one range of rows (one part of ranges, many matrices); what they share, Y2's and P's fragments of 32 rows, goes through
+// LDS, fetched by all ten waves a unit ahead.
+struct OverlapArgs {
+    BlockArgs b;                                          // w: the block's own, ranges of all columns
+    const uint16_t* P;                                    // the panel taken apart; w.Yr, w.Wp: still those of the block before
+    int core_slots, groups, items, per_item;              // workgroups before the others; groups of columns, ranges or parts, pairs of tile rows in each
+};
+constexpr int kOverlapWaves = kCoreThreads / 64;
+constexpr int kOverlapFrags = 24 + 24;                    // of a unit: two tile rows of Y2, four units of three planes; three planes of eight tile columns of P
+constexpr int kOverlapLds = 2 * kOverlapFrags * kFrag * 2;
+static_assert(kOverlapLds >= (int)sizeof(CoreShared), "the core's share");
+
+__device__ __forceinline__ void fetch_fragment(const uint16_t* from, uint32_t lds_addr) {      // lds_addr wave-uniform (travels in M0)
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(from), "s"(lds_addr) : "memory", "m0");
+}
+
+__device__ __forceinline__ void columns_behind(const OverlapArgs& o, uint8_t* lds, int block) {
+    const WideArgs& a = o.b.w;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int matrix, item;
+    if (!deal_to_dies(block, o.groups * o.items, a.count, &matrix, &item)) return;
+    const int cg = item / o.items, part = item % o.items;
+    const int units = (a.mt + 1) / 2, t_begin = part * o.per_item, t_end = t_begin + o.per_item < units ? t_begin + o.per_item : units;
+    const int own = BT + cg * 8 + wave, col = own < a.mt ? own : a.mt - 1;
+    const bool works = wave < 8, there = works && own < a.mt;
+    const uint32_t base = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)lds);
+    const uint16_t* Yr = a.Yr + 2 * (int64_t)matrix * a.batch_stride + lane * 8;
+    const uint16_t* P = o.P + 2 * (int64_t)matrix * a.batch_stride + lane * 8;
+    float* x_at = a.X + (int64_t)matrix * a.batch_stride + (int64_t)col * a.nbr * 256 + (lane & 15) * NB + 4 * (lane >> 4);
+    auto fetch = [&](int t, int buf) {
+#pragma unroll
+        for (int i = 0; i < (kOverlapFrags + kOverlapWaves - 1) / kOverlapWaves; ++i) {
+            const int id = wave + kOverlapWaves * i;
+            if (id >= kOverlapFrags) continue;            // wave-uniform
+            const int e = id / 12, row = 2 * t + e < a.mt ? 2 * t + e : a.mt - 1;       // the odd last tile row: P is zero there
+            const uint16_t* from = id < 24 ? Yr + (int64_t)row * kYrBlock + (id - 12 * e) * kFrag : P + (int64_t)t * kUnitPanel + (id - 24) * kFrag;
+            fetch_fragment(from, base + (uint32_t)((buf * kOverlapFrags + id) * kFrag * 2));
+        }
+    };
+    auto load = [&](int t, f32x4_t (&x)[2]) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int r = 2 * t + e < a.mt ? 2 * t + e : a.mt - 1;
+            x[e] = *reinterpret_cast<const f32x4_t*>(x_at + (int64_t)r * 256);
+        }
+    };
+    Split n[BT / 2][1];                                   // -N of this wave's column
+    f32x4_t x[2], acc[2][4][1];
+    if (works) {
+        const uint16_t* w = a.Wp + 2 * (int64_t)matrix * a.batch_stride + (int64_t)col * a.wp_unit + lane * 8;
+#pragma unroll
+        for (int u = 0; u < BT / 2; ++u) { n[u][0].h = frag_of(w + u * 3 * kFrag); n[u][0].m = frag_of(w + (u * 3 + 1) * kFrag); n[u][0].l = frag_of(w + (u * 3 + 2) * kFrag); }
+        load(t_begin, x);
+    }
+    fetch(t_begin, 0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // (from here on the fetches are counted by what is issued behind them)
+    float* sums = a.Wpart + (int64_t)matrix * a.batch_stride + ((int64_t)part * a.mt + col) * BT * 256 + lane * 4;
+    int in_range = 0;                                     // units of the present range that are done
+    bool first = true;
+    for (int t = t_begin; t < t_end; ++t) {
+        const int buf = (t - t_begin) & 1;
+        // This unit's fragments have landed (two loads at least were issued behind them), nobody reads the other stage any more
+        if (works) asm volatile("s_waitcnt vmcnt(2) lgkmcnt(0)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (t + 1 < t_end) fetch(t + 1, buf ^ 1);
+        if (works) {
+            f32x4_t ahead[2];
+            load(t + 1 < t_end ? t + 1 : t, ahead);
+            const uint16_t* mine = reinterpret_cast<const uint16_t*>(lds) + buf * kOverlapFrags * kFrag + lane * 8;
+            f32x4_t change[2][1];
+            change[0][0] = change[1][0] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int u = 0; u < BT / 2; ++u) products([&](int plane, int f) { return frag_of(mine + ((f * (BT / 2) + u) * 3 + plane) * kFrag); }, n[u], change);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) x[e] = x[e] + change[e][0];
+            Split xs[1];
+            xs[0] = split3(x[0], x[1]);
+            if (in_range == 0) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int f = 0; f < 4; ++f) acc[h][f][0] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) products([&](int plane, int f) { return frag_of(mine + (24 + plane * 8 + 4 * h + f) * kFrag); }, xs, acc[h]);
+            if (there) {
+#pragma unroll
+                for (int e = 0; e < 2; ++e) if (2 * t + e < a.mt) *reinterpret_cast<f32x4_t*>(x_at + (int64_t)(2 * t + e) * 256) = x[e];
+            }
+            if (++in_range == a.per_chunk || t + 1 == t_end) {
+                if (there) {
+#pragma unroll
+                    for (int f = 0; f < BT; ++f) {
+                        f32x4_t* at = reinterpret_cast<f32x4_t*>(sums + f * 256);
+                        *at = first ? acc[f / 4][f % 4][0] : *at + acc[f / 4][f % 4][0];
+                    }
+                }
+                first = false; in_range = 0;
+            }
+            x[0] = ahead[0]; x[1] = ahead[1];
+        }
+    }
+}
+
+template <int RANGES>
+__global__ __launch_bounds__(kCoreThreads)
+void block_overlap_kernel(OverlapArgs o) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    if ((int)blockIdx.x >= o.core_slots) { columns_behind(o, lds, blockIdx.x - o.core_slots); return; }
+    if ((int)blockIdx.x < o.b.w.count) block_core<RANGES>(o.b, *reinterpret_cast<CoreShared*>(lds), blockIdx.x);
 }
 
 // ------------------------------------------------------------ the columns behind the block, the rows below it --
@@ -405,8 +529,9 @@ void panel_triangle_kernel(const float* M, float* Vc, float* Tmat, int nbr, int6
 int64_t block_panel_values(int n_pad) { return (int64_t)((n_pad / NB + 1) / 2) * kUnitPanel; }
 
 hipError_t block_factor_init() {    // brings this file's code onto the device (see factor_init)
-    hipFuncAttributes attr;
-    return hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&first_panel_kernel));
+    for (const void* f : {reinterpret_cast<const void*>(&block_overlap_kernel<kWideParts>), reinterpret_cast<const void*>(&block_overlap_kernel<kWideChunks>)})
+        GELO_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kOverlapLds));
+    return hipSuccess;
 }
 
 hipError_t factor_blocks(const FactorWorkspace& ws, float* Vc, int count, int64_t batch_stride, int* panels_done, hipStream_t s) {
@@ -414,30 +539,48 @@ hipError_t factor_blocks(const FactorWorkspace& ws, float* Vc, int count, int64_
     int done = 0;
     hipLaunchKernelGGL(first_panel_kernel, dim3((nbr + 1) / 2, count), dim3(512), 0, s, ws.M, ws.panel, nbr, batch_stride);
     GELO_TRY(hipGetLastError());
+    WideArgs update;                                          // the last block's, where it has not been applied yet
     for (const int last = last_block_tiles(nbr); nbr - done >= last; done += BT) {
-        BlockArgs b;
+        OverlapArgs o;
+        BlockArgs& b = o.b;
         WideArgs& a = b.w;
-        a.nbr = nbr; a.t0 = done; a.mt = nbr - done; a.nt = BT;
+        a.nbr = nbr; a.t0 = done; a.mt = a.cols = nbr - done; a.nt = BT;
         a.Yp = ws.panel; a.T = nullptr;
         a.X = ws.M + ((int64_t)done * nbr + done) * 256;
         a.Wpart = ws.Wpart; a.Wp = ws.Wp; a.wp_unit = a.yr_unit = kYrBlock;
         a.next = nullptr;
         a.batch_stride = batch_stride; a.count = count;
-        cut_into_ranges(a, 1, (a.mt + 3) / 4);
-        GELO_TRY(launch_panel_products(a, s));
-        b.core = ws.core; b.Rd = ws.Rd + (int64_t)done * 256; b.rdiag = ws.rdiag + done * NB;
         a.Yr = b.Yr = ws.Yr;
-        if (a.by_part) hipLaunchKernelGGL((block_core_kernel<kWideParts>), dim3(count), dim3(kCoreThreads), 0, s, b);
-        else hipLaunchKernelGGL((block_core_kernel<kWideChunks>), dim3(count), dim3(kCoreThreads), 0, s, b);
+        o.groups = (a.mt - BT + 7) / 8;
+        cut_into_ranges(a, 1, done == 0 ? (a.mt + 3) / 4 : o.groups);
+        b.core = ws.core; b.Rd = ws.Rd + (int64_t)done * 256; b.rdiag = ws.rdiag + done * NB;
+        if (done == 0) {
+            GELO_TRY(launch_panel_products(a, s));
+            if (a.by_part) hipLaunchKernelGGL((block_core_kernel<kWideParts>), dim3(count), dim3(kCoreThreads), sizeof(CoreShared), s, b);
+            else hipLaunchKernelGGL((block_core_kernel<kWideChunks>), dim3(count), dim3(kCoreThreads), sizeof(CoreShared), s, b);
+        } else {
+            update.cols = BT; update.next = ws.panel;
+            GELO_TRY(launch_block_update(update, s));
+            WideArgs own = a;
+            own.cols = BT; own.groups = 1; own.by_part = count >= kWideCus;
+            GELO_TRY(launch_panel_products(own, s));
+            o.P = ws.panel;
+            o.core_slots = (count + 7) / 8 * 8;
+            o.items = a.by_part ? a.parts : a.chunks;
+            o.per_item = a.by_part ? a.per_chunk * a.part_chunks : a.per_chunk;
+            const dim3 grid(o.core_slots + 8 * dies_slots(o.groups * o.items, count));
+            if (own.by_part) hipLaunchKernelGGL((block_overlap_kernel<kWideParts>), grid, dim3(kCoreThreads), kOverlapLds, s, o);
+            else hipLaunchKernelGGL((block_overlap_kernel<kWideChunks>), grid, dim3(kCoreThreads), kOverlapLds, s, o);
+        }
         GELO_TRY(hipGetLastError());
         if (a.by_part) hipLaunchKernelGGL((block_apply_kernel<kWideParts>), dim3(2 * (a.mt - BT), count), dim3(512), 0, s, b);
         else hipLaunchKernelGGL((block_apply_kernel<kWideChunks>), dim3(2 * (a.mt - BT), count), dim3(512), 0, s, b);
         GELO_TRY(hipGetLastError());
-        a.X += (int64_t)BT * nbr * 256 + BT * 256;
-        a.mt -= BT; a.t0 += BT;
-        a.next = a.mt >= last ? ws.panel : nullptr;
-        GELO_TRY(launch_block_update(a, s));
+        update = a;
+        update.X += (int64_t)BT * nbr * 256 + BT * 256;
+        update.mt -= BT; update.cols = update.mt; update.t0 += BT;
     }
+    if (done > 0) GELO_TRY(launch_block_update(update, s));
     if (done > 0) {
         hipLaunchKernelGGL(panel_triangle_kernel, dim3(done, count), dim3(512), 0, s, ws.M, Vc, ws.Tmat, nbr, batch_stride);
         GELO_TRY(hipGetLastError());

@@ -23,8 +23,9 @@ struct WideArgs {
     float* Wpart; uint16_t* Wp; int wp_unit, yr_unit;     // bf16 values of a tile column in Wp, of a tile row in Yr
     uint16_t* next;                                       // where the update leaves the next panel taken apart (the factorisation)
     int nbr, t0, mt;                                      // tile rows of the matrix, the first one taken, those from it on (as many columns)
+    int cols;                                             // the tile columns of X this launch takes, the first ones (Wpart's pitch is mt)
     int nt;                                               // tile columns of the block
-    int groups;                                           // of eight tile columns
+    int groups;                                           // of eight of them
     int chunks, per_chunk;                                // the rows are cut into so many ranges of pairs of tile rows
     int part_chunks, parts;                               // ranges per part, parts
     int by_part;                                          // Wpart holds sums of parts (many matrices), not of ranges

@@ -203,7 +203,7 @@ void reflect_wt_kernel(WideArgs a) {
     float* w[2];
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
-        const int col = cg * 8 + wave * 2 + n < a.mt ? cg * 8 + wave * 2 + n : a.mt - 1;
+        const int col = cg * 8 + wave * 2 + n < a.cols ? cg * 8 + wave * 2 + n : a.cols - 1;
         xc[n] = a.X + (int64_t)matrix * a.batch_stride + (int64_t)col * a.nbr * 256 + (lane & 15) * 16 + 4 * (lane >> 4);
         // as the lanes hold it: only reflect_w_kernel reads it
         w[n] = a.Wpart + (int64_t)matrix * a.batch_stride + (((int64_t)part * a.mt + col) * TC + half * 8) * 256 + lane * 4;
@@ -265,7 +265,7 @@ void reflect_wt_kernel(WideArgs a) {
         for (int n = 0; n < 2; ++n)
 #pragma unroll
             for (int f = 0; f < 8; ++f) {
-                if (cg * 8 + wave * 2 + n < a.mt) {       // (a clamped column belongs to another wave)
+                if (cg * 8 + wave * 2 + n < a.cols) {     // (a clamped column belongs to another wave)
                     f32x4_t* at = reinterpret_cast<f32x4_t*>(w[n] + f * 256);
                     *at = range == 0 ? acc[f][n] : *at + acc[f][n];
                 }
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void reflect_wt_direct_kernel(WideArgs a) {
     constexpr int RG = TC / 4, CP = 4 / RG;               // waves along the reflectors, along the columns
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int pairs = (a.mt + 1) / 2, sets = (pairs + CP - 1) / CP;
+    const int pairs = (a.mt + 1) / 2, sets = ((a.cols + 1) / 2 + CP - 1) / CP;      // pairs of tile rows
     int matrix, b;
     if (!deal_to_dies(blockIdx.x, sets * a.chunks, a.count, &matrix, &b)) return;
     const int cp = b % sets * CP + wave / RG, fr = wave % RG * 4, chunk = b / sets;
@@ -290,7 +290,7 @@ void reflect_wt_direct_kernel(WideArgs a) {
     const float* xc[2];
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
-        const int col = 2 * cp + n < a.mt ? 2 * cp + n : a.mt - 1;
+        const int col = 2 * cp + n < a.cols ? 2 * cp + n : a.cols - 1;
         xc[n] = a.X + (int64_t)matrix * a.batch_stride + (int64_t)col * a.nbr * 256 + (lane & 15) * 16 + 4 * (lane >> 4);
     }
     bf16x8_t y[2][3][4];
@@ -331,7 +331,7 @@ void reflect_wt_direct_kernel(WideArgs a) {
     }
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
-        if (2 * cp + n >= a.mt) continue;
+        if (2 * cp + n >= a.cols) continue;
 #pragma unroll
         for (int f = 0; f < 4; ++f)
             *reinterpret_cast<f32x4_t*>(a.Wpart + (int64_t)matrix * a.batch_stride + (((int64_t)chunk * a.mt + 2 * cp + n) * TC + fr + f) * 256 + lane * 4) = acc[f][n];
@@ -392,9 +392,9 @@ __device__ __forceinline__ void next_panel(const WideArgs& a, int matrix, int r,
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void reflect_update_direct_kernel(WideArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int quads = (a.mt + 3) / 4;
+    const int quads = (a.cols + 3) / 4;                   // of tile columns
     int matrix, b;
-    if (!deal_to_dies(blockIdx.x, quads * quads, a.count, &matrix, &b)) return;
+    if (!deal_to_dies(blockIdx.x, (a.mt + 3) / 4 * quads, a.count, &matrix, &b)) return;
     const int r0 = b / quads * 4 + (wave & 1) * 2, c0 = b % quads * 4 + (wave >> 1) * 2;
     const int units = (a.nt + 1) / 2;
     const uint16_t* ya[2];
@@ -402,7 +402,7 @@ void reflect_update_direct_kernel(WideArgs a) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         ya[i] = a.Yr + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(r0 + i < a.mt ? r0 + i : a.mt - 1) * a.yr_unit + lane * 8;
-        wb[i] = a.Wp + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(c0 + i < a.mt ? c0 + i : a.mt - 1) * a.wp_unit + lane * 8;
+        wb[i] = a.Wp + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(c0 + i < a.cols ? c0 + i : a.cols - 1) * a.wp_unit + lane * 8;
     }
     bf16x8_t y[3][3][2];
     Split w[3][2];
@@ -421,7 +421,7 @@ void reflect_update_direct_kernel(WideArgs a) {
     fetch(1, y[1], w[1]);
     f32x4_t x[2][2], acc[2][2];
     auto tile = [&](int f, int n) {
-        const int r = r0 + f < a.mt ? r0 + f : a.mt - 1, c = c0 + n < a.mt ? c0 + n : a.mt - 1;
+        const int r = r0 + f < a.mt ? r0 + f : a.mt - 1, c = c0 + n < a.cols ? c0 + n : a.cols - 1;
         return a.X + (int64_t)matrix * a.batch_stride + ((int64_t)c * a.nbr + r) * 256 + (lane & 15) * 16 + 4 * (lane >> 4);
     };
 #pragma unroll
@@ -443,7 +443,7 @@ void reflect_update_direct_kernel(WideArgs a) {
 #pragma unroll
         for (int n = 0; n < 2; ++n) {
             acc[f][n] = x[f][n] + acc[f][n];
-            if (r0 + f < a.mt && c0 + n < a.mt) *reinterpret_cast<f32x4_t*>(tile(f, n)) = acc[f][n];
+            if (r0 + f < a.mt && c0 + n < a.cols) *reinterpret_cast<f32x4_t*>(tile(f, n)) = acc[f][n];
         }
     if (a.next != nullptr && c0 < 8) {                    // wave-uniform
 #pragma unroll
@@ -460,7 +460,7 @@ void reflect_update_kernel(WideArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave & 1, wn = wave >> 1;
     int matrix, b;
-    if (!deal_to_dies(blockIdx.x, a.groups * a.groups, a.count, &matrix, &b)) return;
+    if (!deal_to_dies(blockIdx.x, (a.mt + 7) / 8 * a.groups, a.count, &matrix, &b)) return;
     const int rg = b / a.groups, cg = b % a.groups;
     const int units = (a.nt + 1) / 2;
     const uint16_t* src[4];                               // this wave's two tile rows of Y, two tile columns of W'
@@ -468,7 +468,7 @@ void reflect_update_kernel(WideArgs a) {
     for (int i = 0; i < 2; ++i) {
         const int row = rg * 8 + wave * 2 + i, col = cg * 8 + wave * 2 + i;
         src[i] = a.Yr + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(row < a.mt ? row : a.mt - 1) * a.yr_unit + lane * 8;
-        src[2 + i] = a.Wp + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(col < a.mt ? col : a.mt - 1) * a.wp_unit + lane * 8;
+        src[2 + i] = a.Wp + 2 * (int64_t)matrix * a.batch_stride + (int64_t)(col < a.cols ? col : a.cols - 1) * a.wp_unit + lane * 8;
     }
     u32x4_t st[4][3];
     auto fetch = [&](int u) {
@@ -481,7 +481,7 @@ void reflect_update_kernel(WideArgs a) {
     f32x4_t acc[4][4];
     auto tile = [&](int f, int n) {
         const int r = rg * 8 + wm * 4 + f, cc = cg * 8 + wn * 4 + n;
-        return a.X + (int64_t)matrix * a.batch_stride + ((int64_t)(cc < a.mt ? cc : a.mt - 1) * a.nbr + (r < a.mt ? r : a.mt - 1)) * 256 + (lane & 15) * 16 + 4 * (lane >> 4);
+        return a.X + (int64_t)matrix * a.batch_stride + ((int64_t)(cc < a.cols ? cc : a.cols - 1) * a.nbr + (r < a.mt ? r : a.mt - 1)) * 256 + (lane & 15) * 16 + 4 * (lane >> 4);
     };
 #pragma unroll
     for (int f = 0; f < 4; ++f)
@@ -518,7 +518,7 @@ void reflect_update_kernel(WideArgs a) {
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
             acc[f][n] = before[f][n] + acc[f][n];
-            if (rg * 8 + wm * 4 + f < a.mt && cg * 8 + wn * 4 + n < a.mt) *reinterpret_cast<f32x4_t*>(tile(f, n)) = acc[f][n];
+            if (rg * 8 + wm * 4 + f < a.mt && cg * 8 + wn * 4 + n < a.cols) *reinterpret_cast<f32x4_t*>(tile(f, n)) = acc[f][n];
         }
     if (a.next != nullptr && cg == 0) {
 #pragma unroll
@@ -550,7 +550,7 @@ void cut_into_ranges(WideArgs& a, int halves, int workgroups) {
     // ranges of rows so that one matrix alone fills the chip about once, an even number of pairs of tile rows each
     const int units = (a.mt + 1) / 2, want = kWideCus / workgroups;
     const int chunks = want < 1 ? 1 : want > kWideChunks ? kWideChunks : want;
-    a.groups = (a.mt + 7) / 8;
+    a.groups = (a.cols + 7) / 8;
     a.per_chunk = ((units + chunks - 1) / chunks + 1) / 2 * 2;
     a.chunks = (units + a.per_chunk - 1) / a.per_chunk;
     a.part_chunks = (a.chunks + kWideParts - 1) / kWideParts;
@@ -560,7 +560,7 @@ void cut_into_ranges(WideArgs& a, int halves, int workgroups) {
 
 template <int TC>
 static hipError_t launch_wt(const WideArgs& a, hipStream_t s) {
-    const int pairs = (a.mt + 1) / 2;
+    const int pairs = (a.cols + 1) / 2;
     constexpr int CP = 16 / TC;
     if (a.by_part) hipLaunchKernelGGL((reflect_wt_kernel<TC>), dim3(8 * dies_slots(TC / 8 * a.groups * a.parts, a.count)), dim3(256), 0, s, a);
     else hipLaunchKernelGGL((reflect_wt_direct_kernel<TC>), dim3(8 * dies_slots((pairs + CP - 1) / CP * a.chunks, a.count)), dim3(256), 0, s, a);
@@ -569,10 +569,10 @@ static hipError_t launch_wt(const WideArgs& a, hipStream_t s) {
 hipError_t launch_panel_products(const WideArgs& a, hipStream_t s) { return launch_wt<8>(a, s); }
 
 hipError_t launch_block_update(WideArgs a, hipStream_t s) {
-    a.groups = (a.mt + 7) / 8;
-    const int quads = (a.mt + 3) / 4;
-    if (a.groups * a.groups * a.count >= 2 * kWideCus) hipLaunchKernelGGL(reflect_update_kernel, dim3(8 * dies_slots(a.groups * a.groups, a.count)), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(reflect_update_direct_kernel, dim3(8 * dies_slots(quads * quads, a.count)), dim3(256), 0, s, a);
+    a.groups = (a.cols + 7) / 8;
+    const int items = (a.mt + 7) / 8 * a.groups, small = (a.mt + 3) / 4 * ((a.cols + 3) / 4);
+    if (items * a.count >= 2 * kWideCus) hipLaunchKernelGGL(reflect_update_kernel, dim3(8 * dies_slots(items, a.count)), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(reflect_update_direct_kernel, dim3(8 * dies_slots(small, a.count)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -585,7 +585,7 @@ hipError_t form_product_wide(const FactorWorkspace& ws, int count, int64_t batch
     GELO_TRY(hipGetLastError());
     for (int q = blocks - 1; q >= 0; --q) {
         WideArgs a;
-        a.nbr = nbr; a.t0 = q * WT; a.mt = nbr - a.t0; a.nt = a.mt < WT ? a.mt : WT;
+        a.nbr = nbr; a.t0 = q * WT; a.mt = a.cols = nbr - a.t0; a.nt = a.mt < WT ? a.mt : WT;
         a.Yp = ws.Yp + pairs_before(nbr, q) * kUnitYp;
         a.Yr = ws.Yr + rows_before(nbr, q) * kUnitYr;
         a.T = ws.Tbig + (int64_t)q * (WT * 16) * (WT * 16);

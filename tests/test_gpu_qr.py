@@ -214,9 +214,10 @@ def test_inverse_from_the_factors(ctx, n, bf16):             # (ctx: brings the 
 
 
 # R and Q of matrices that are factorised in different parts: one workgroup alone (one to eight tiles, whole and broken), panels in front of it (one to
-# seventeen of them), blocks of 128 columns in front of those.  Q^T A leaves R: its part below the diagonal and what it differs from R's
+# twelve of them), blocks of 128 columns in front of those (one; several, whose columns further on are brought up to date beside the next block's
+# 128 x 128 part: an odd number of tile rows, groups of columns and ranges of rows that are not full).  Q^T A leaves R: its part below the diagonal and what it differs from R's
 # tiles by are rounding, c sqrt(n) of it
-@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 64, 65, 81, 100, 127, 128, 129, 145, 250, 256, 400, 415, 417, 545, 703])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 64, 65, 81, 100, 127, 128, 129, 145, 250, 256, 320, 321, 400, 417, 545, 703, 721, 1040, 1041, 2070])
 def test_factors_of_a_gaussian(ctx, n):
     A = torch.randn((n, n), generator=torch.Generator().manual_seed(n)).cuda()
     ws = Workspace(n)
