@@ -355,9 +355,10 @@ void reflect_w_kernel(WideArgs a) {
         for (int k = 0; k < 2; ++k)
             *reinterpret_cast<f32x4_t*>(&W[n][wave * 2 + k][lane * 4]) = sum_of_ranges<RANGES>(wp + k * 256, (int64_t)a.mt * WT * 256, a);
     }
-    f32x4_t t[2][WT];                                     // its rows of T, all requested at once (zeros below the diagonal)
+    f32x4_t t[2][WT];                                     // its rows of T from the diagonal on, all requested at once
 #pragma unroll
     for (int s = 0; s < WT; ++s)
+        if (s >= wave * 2)
 #pragma unroll
         for (int k = 0; k < 2; ++k) t[k][s] = *reinterpret_cast<const f32x4_t*>(T + k * 16 * (WT * 16) + s * 16);
     __syncthreads();

@@ -25,59 +25,6 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
-template <int CTRL>
-__device__ __forceinline__ float dpp_mov(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
-}
-template <int PATTERN>
-__device__ __forceinline__ float swizzle(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), PATTERN));
-}
-
-// Index of the value that lane `lane` ends up holding after wave_reduce16.
-__device__ __forceinline__ int reduce16_slot(int lane) {
-    return ((lane >> 2) & 1) * 8 + ((lane >> 3) & 1) * 4 + ((lane >> 1) & 1) * 2 + (lane & 1);
-}
-
-// Sums 16 per-lane values over the 64 lanes of a wave in ~50 instructions: each exchange step
-// halves the number of values a lane carries (the lane keeps the half its partner does not),
-// so after four steps inside a row of 16 lanes every lane holds ONE value, summed over its row;
-// two more exchanges add the four rows.  Returns, in every lane, the wave total of value
-// reduce16_slot(lane).  All 64 lanes must be active.  The order of additions is fixed.
-__device__ __forceinline__ float wave_reduce16(const float (&t)[NB], int lane) {
-    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
-    float a[8], c[4], e[2];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const float keep = b0 ? t[2 * k + 1] : t[2 * k];
-        const float give = b0 ? t[2 * k] : t[2 * k + 1];
-        a[k] = keep + dpp_mov<0xB1>(give);              // lane ^ 1  (quad_perm [1,0,3,2])
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const float keep = b1 ? a[2 * k + 1] : a[2 * k];
-        const float give = b1 ? a[2 * k] : a[2 * k + 1];
-        c[k] = keep + dpp_mov<0x4E>(give);              // lane ^ 2  (quad_perm [2,3,0,1])
-    }
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const float keep = b3 ? c[2 * k + 1] : c[2 * k];
-        const float give = b3 ? c[2 * k] : c[2 * k + 1];
-        e[k] = keep + dpp_mov<0x128>(give);             // lane ^ 8  (row_ror:8)
-    }
-    const float keep = b2 ? e[1] : e[0];
-    const float give = b2 ? e[0] : e[1];
-    float f = keep + swizzle<0x101F>(give);             // lane ^ 4
-    f += swizzle<0x401F>(f);                            // lane ^ 16
-    f += __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((lane ^ 32) << 2, __builtin_bit_cast(int, f)));
-    return f;
-}
-
-template <int LANE>
-__device__ __forceinline__ float lane_value(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), LANE));
-}
-
 // ------------------------------------------------------------------ directly drawn panels --
 // The reflectors of an m x 16 panel, every one from its column as it stands in memory (the later columns of the panel do not see the
 // earlier reflectors: what the product of directly drawn reflectors needs, householder_qr with `direct`), and what the block reflector

@@ -12,6 +12,7 @@
 // for its accuracy, whatever A is, except that its panels are built from Gram matrices (gram_panel_body, block_core_kernel): a panel's
 // condition number is at most A's, times a panel of Gaussians' for the GAUSSIAN kind.
 #include "gelo_internal.h"
+#include "wave_tile.h"
 
 namespace gelo {
 namespace {
@@ -575,12 +576,8 @@ void lanczos_step_kernel(const float* Ma, const float* Mb, float* pa, float* pb,
 // the eigenvalues below its own trial value (32 trial values per bracket), and the bracket shrinks to
 // the interval between the last trial with an eigenvalue at or above it and the first one above all.
 // out[0] = sqrt(lambda_A lambda_Ainv) = the kappa_2 estimate, out[1], out[2] its factors.
-__global__ __launch_bounds__(64)
-void lanczos_finish_kernel(const float* tri, int k, float* out) {
-    __shared__ float co[2 * 2 * kLanczosMax];
-    const int lane = threadIdx.x, o = lane >> 5, l = lane & 31;
-    co[lane] = tri[lane]; co[lane + 64] = tri[lane + 64];
-    __syncthreads();
+__device__ __forceinline__ void largest_ritz_values(const float* co, int k, float* out) {      // one wave; co: as tri
+    const int lane = threadIdx.x & 63, o = lane >> 5, l = lane & 31;
     const float* al = co + o * 2 * kLanczosMax;
     const float* be = al + kLanczosMax;
     float hi = 0.f;
@@ -609,6 +606,82 @@ void lanczos_finish_kernel(const float* tri, int k, float* out) {
     const float sigma = sqrtf(0.5f * (lo + hi));
     const float s0 = __shfl(sigma, 0, 64), s1 = __shfl(sigma, 32, 64);
     if (lane == 0) { out[1] = s0; out[2] = s1; out[0] = s0 * s1; }
+}
+__global__ __launch_bounds__(64)
+void lanczos_finish_kernel(const float* tri, int k, float* out) {
+    __shared__ float co[2 * 2 * kLanczosMax];
+    co[threadIdx.x] = tri[threadIdx.x]; co[threadIdx.x + 64] = tri[threadIdx.x + 64];
+    __syncthreads();
+    largest_ritz_values(co, k, out);
+}
+
+// The whole estimate of a matrix of at most 128 rows in one workgroup: eight waves for each operator, a wave with every eighth row in
+// registers (two columns a lane) and the vectors too, every wave all of them (the same bits); the waves' sums of a product meet in LDS at one
+// barrier per step.  Bound by that chain, about 0.9 us per step, where a launch per step takes 5.2.  Draw of a CONDITIONED matrix, us: 16 rows 135 -> 90,
+// 64 rows 199 -> 149, 128 rows 289 -> 237; GAUSSIAN, 64 rows 400 -> 246.
+__global__ __launch_bounds__(1024)
+void small_kappa_kernel(const float* A, const float* Ainv, int64_t lda, int n, int steps, float* out) {
+    __shared__ float parts[2][2][8][128];
+    __shared__ float co[2 * 2 * kLanczosMax];
+    const int lane = threadIdx.x & 63, number = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), o = number >> 3, wave = number & 7;
+    const float* M = o ? Ainv : A;
+    float* tr = co + o * 2 * kLanczosMax;
+    constexpr int ROWS = 16;
+    float m[ROWS][2], v[2], v_prev[2] = {0.f, 0.f}, beta = 0.f;
+    auto total = [](float x) {                            // over the wave, the same in every lane
+        x += dpp_mov<0x128>(x); x += dpp_mov<0x124>(x); x += dpp_mov<0x122>(x); x += dpp_mov<0x121>(x);      // row_ror 8, 4, 2, 1
+        return sum_of_rows(x);
+    };
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int r = wave + 8 * i, c = 2 * lane + e;
+            m[i][e] = r < n && c < n ? M[(int64_t)r * lda + c] : 0.f;
+        }
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {                         // as next_vector's
+        const int i = 2 * lane + e;
+        uint32_t h = (uint32_t)i * 2654435761u + 0x9E3779B9u;
+        h ^= h >> 15; h *= 2246822519u; h ^= h >> 13;
+        v[e] = i < n ? ((h & 1u) ? 1.f : -1.f) * (0.5f + (float)((h >> 8) & 0xFFFF) * (1.0f / 65536.0f)) : 0.f;
+    }
+    {
+        const float inv = rsqrtf(total(fmaf(v[0], v[0], v[1] * v[1])));
+        v[0] *= inv; v[1] *= inv;
+    }
+    for (int step = 0; step < steps; ++step) {
+        float t[ROWS];
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) t[i] = fmaf(m[i][0], v[0], m[i][1] * v[1]);
+        const float dots = wave_reduce16(t, lane);
+        float s0 = 0.f, s1 = 0.f;
+        static_for<ROWS>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            const float d = lane_value<(i >> 3 & 1) * 4 + (i >> 2 & 1) * 8 + (i & 3)>(dots);      // reduce16_slot's inverse
+            s0 = fmaf(d, m[i][0], s0); s1 = fmaf(d, m[i][1], s1);
+        });
+        *reinterpret_cast<float2*>(&parts[step & 1][o][wave][2 * lane]) = make_float2(s0, s1);
+        __syncthreads();
+        float w[2] = {0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const float2 p = *reinterpret_cast<const float2*>(&parts[step & 1][o][k][2 * lane]);
+            w[0] += p.x; w[1] += p.y;
+        }
+        const float alpha = total(fmaf(w[0], v[0], w[1] * v[1]));
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            w[e] = fmaf(-beta, v_prev[e], fmaf(-alpha, v[e], w[e]));
+            v_prev[e] = v[e];
+        }
+        beta = sqrtf(total(fmaf(w[0], w[0], w[1] * w[1])));
+        const float inv = beta > 0.f ? 1.0f / beta : 0.f;
+        v[0] = w[0] * inv; v[1] = w[1] * inv;
+        if (wave == 0 && lane == 0) { tr[step] = alpha; tr[kLanczosMax + step] = beta; }
+    }
+    __syncthreads();
+    if (number == 0) largest_ritz_values(co, steps, out);
 }
 
 #define GELO_TRY(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) return e_; } while (0)
@@ -716,6 +789,10 @@ hipError_t kappa_estimate(const float* A, const float* Ainv, int64_t lda, int n,
     const int64_t ld = ws.ld;
     if (steps < 1 || steps > kLanczosMax) return hipErrorInvalidValue;
     if (steps > n) steps = n;
+    if (n <= 128) {
+        hipLaunchKernelGGL(small_kappa_kernel, dim3(1), dim3(1024), 0, s, A, Ainv, lda, n, steps, ws.scalars);
+        return hipGetLastError();
+    }
     if (n <= kFusedMaxN) {
         // (two halves of at most n / 8 + 1 rows of ld each)
         const int few = (n + kFusedWaves - 1) / kFusedWaves < kFusedGroups ? (n + kFusedWaves - 1) / kFusedWaves : kFusedGroups;

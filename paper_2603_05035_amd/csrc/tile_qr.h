@@ -105,19 +105,6 @@ __device__ __forceinline__ void add_terms(float& acc, float d, const float (&t)[
 }
 #undef GELO_TERM
 
-// a value summed over the four rows of 16 lanes; that of row Q in all of them
-__device__ __forceinline__ float sum_of_rows(float v) {
-    const auto a = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
-    v = __builtin_bit_cast(float, (unsigned)a[0]) + __builtin_bit_cast(float, (unsigned)a[1]);
-    const auto b = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
-    return __builtin_bit_cast(float, (unsigned)b[0]) + __builtin_bit_cast(float, (unsigned)b[1]);
-}
-template <int Q>
-__device__ __forceinline__ float row_to_all(float v) {
-    const unsigned x = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false)[Q & 1];
-    return __builtin_bit_cast(float, (unsigned)__builtin_amdgcn_permlane32_swap(x, x, false, false)[Q >> 1]);
-}
-
 // Householder QR of TC tiles of 16 columns, y[4 b + e] row 16 b + 4 g + e of the lane's column (the first `cols` of them; the others are
 // zero).  On return R above the diagonal, u below it; of the lane's column u's entry on the diagonal, R's, and whether there is
 // anything to reflect (the reflector is I - 2 u u^T / u^T u); t: row c of the triangle T of I - U T U^T = H_0 H_1 .., whose inner products

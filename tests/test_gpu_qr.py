@@ -326,8 +326,9 @@ def test_condition_estimate(ctx, n):
     assert -0.01 * exact < kappa - exact < 1e-4 * exact       # a largest Ritz value comes from below: measured within 0.5 %
 
 
-# up to 1024 rows one launch per step: fewer rows than a workgroup's waves, fewer parts than are read at a time, broken rounds of rows, the largest
-@pytest.mark.parametrize("n", [1, 2, 7, 9, 248, 249, 1000, 1024])
+# up to 128 rows one launch for all steps: fewer rows than waves, rows and columns that fill no wave, the largest.  Up to 1024 rows one launch per step:
+# fewer parts than are read at a time, broken rounds of rows, the largest
+@pytest.mark.parametrize("n", [1, 2, 7, 9, 17, 100, 127, 128, 248, 249, 1000, 1024])
 def test_condition_estimate_with_one_launch_per_step(ctx, n):
     test_condition_estimate(ctx, n)
 
