@@ -477,7 +477,7 @@ static gelo_status check_sample_args(gelo_ctx* ctx, gelo_kind kind, int n_data, 
 // 300 rows 225 -> 171 us, 2150 rows 240 -> 177, 32 of 300 rows 568 -> 543, of 2150 rows 974 -> 970.  |A^T A - I| / sqrt(rows) of the last block by the
 // one-workgroup draw / here (48 draws): 8 rows 2.12e-7 / 2.22e-7, 16 2.47 / 2.88, 36 2.83 / 2.91, 64 3.20 / 3.02, 100 3.62 / 3.02, 128 3.90 / 3.08 (the whole blocks 3.31).
 static hipError_t draw_blocks(const SmallSampleTargets& t, int count, uint64_t first, PhiloxStream ps, int n, int d, int64_t ldk, char* base,
-                              hipStream_t s) {
+                              hipStream_t s, const ShieldRows& shields = ShieldRows()) {
     constexpr int B = GELO_BLOCK_ROWS;
     const int full = n / B, rest = n % B, side = blocks_side_by_side(n);
     ps.c1 = kStreamBlock << 8; ps.c2 = (uint32_t)first; ps.c3 = (uint32_t)(first >> 32);
@@ -486,8 +486,8 @@ static hipError_t draw_blocks(const SmallSampleTargets& t, int count, uint64_t f
     FactorWorkspace w;
     factor_workspace_carve(base, rows, &w);
     const int64_t stride = (int64_t)(up256(factor_workspace_bytes(rows)) / sizeof(float));
-    hipError_t e = fill_normal_batched(w.M, stride, w.n_pad / 16, rows, rows, ps, side, side * count, false, s, tail);
-    if (e == hipSuccess) e = householder_qr(w, rows, side * count, stride, s);
+    hipError_t e = fill_normal_batched(w.M, stride, w.n_pad / 16, rows, rows, ps, side, side * count, false, s, tail, 1.f, w.X, shields);
+    if (e == hipSuccess) e = householder_qr_prepared(w, side * count, stride, s);
     if (e == hipSuccess) e = emit_batched(w.X, w.rdiag, stride, w.n_pad / 16, rows, ldk, t, count, side, 0, (int64_t)B * ldk, s, tail);
     return e;
 }
@@ -507,11 +507,15 @@ static gelo_status sample_into(gelo_ctx* ctx, gelo_mixing* m, FactorWorkspace ws
     const bool bf = m->dtype == GELO_BF16;
     m->kind = kind; m->attempt = 0; m->kappa = 1.0f;
 
+    ShieldRows shields;                                       // drawn beside the Gaussian, where that is one launch
+    if (k_shield > 0) { shields.GS = m->GS; shields.gsnorm = m->gsnorm; shields.k = k_shield; shields.d = d; shields.c1 = kStreamShield << 8; }
+    bool shields_drawn = false;
     auto orthogonal_into_X = [&](bool direct) -> hipError_t {
         ps.c1 = kStreamMixing << 8;
         // straight into the QR's tiles; the product of reflectors reads column k from row k down only
-        hipError_t e = fill_normal(ws.M, ws.n_pad / 16, n, n, ps, 1.0f, direct ? 2 : 1, s);
-        if (e == hipSuccess) e = householder_qr(ws, n, 1, 0, s, direct);
+        hipError_t e = fill_normal_batched(ws.M, 0, ws.n_pad / 16, n, n, ps, 1, 1, direct, s, 0, 1.f, ws.X, shields);
+        shields_drawn = true;
+        if (e == hipSuccess) e = householder_qr_prepared(ws, 1, 0, s, direct);
         return e;
     };
 
@@ -532,7 +536,8 @@ static gelo_status sample_into(gelo_ctx* ctx, gelo_mixing* m, FactorWorkspace ws
         SmallSampleTargets t;
         small_targets_layout(m, &t);
         t.block[0] = m->block;
-        GELO_HIP(ctx, draw_blocks(t, 1, batch_id, ps, n, d, ldk, (char*)ws.M, s));
+        shields_drawn = blocks_side_by_side(n) > 0;
+        GELO_HIP(ctx, draw_blocks(t, 1, batch_id, ps, n, d, ldk, (char*)ws.M, s, shields));
     } else if (kind == GELO_ORTHOGONAL || kind == GELO_REFLECTOR_PRODUCT) {
         GELO_HIP(ctx, orthogonal_into_X(kind == GELO_REFLECTOR_PRODUCT));
         // A = Q diag(sign r_ii) (sign beta_k for the product of reflectors); A^-1 = A^T
@@ -585,11 +590,11 @@ static gelo_status sample_into(gelo_ctx* ctx, gelo_mixing* m, FactorWorkspace ws
                     lw[i] = ws; cA32[i] = m->A32; cAi32[i] = m->Ainv32; cA16[i] = m->A16; cAi16[i] = m->Ainv16;
                 }
                 ps.c1 = (kStreamMixing << 8) | (uint32_t)(base + i);
-                GELO_HIP(ctx, fill_normal(lw[i].M, lw[i].n_pad / 16, n, n, ps, 1.0f / std::sqrt((float)n), 1, ls));
+                GELO_HIP(ctx, fill_normal_batched(lw[i].M, 0, lw[i].n_pad / 16, n, n, ps, 1, 1, false, ls, 0, 1.0f / std::sqrt((float)n), lw[i].X));
                 // everything behind the fill: the same launches for every attempt of this lane
                 auto factorise = [&]() -> hipError_t {
                     hipError_t e = emit_matrix(lw[i].M, lw[i].n_pad / 16, 1, nullptr, n, ldk, cA32[i], cA16[i], nullptr, nullptr, ls);
-                    if (e == hipSuccess) e = householder_qr(lw[i], n, 1, 0, ls);
+                    if (e == hipSuccess) e = householder_qr_prepared(lw[i], 1, 0, ls);
                     if (e == hipSuccess) e = inverse_from_qr(lw[i], n, cA32[i], ldk, cAi32[i], cAi16[i], ls);
                     if (e == hipSuccess) e = kappa_estimate(cA32[i], cAi32[i], ldk, n, lw[i], kKappaSteps, ls);
                     if (e == hipSuccess) e = hipMemcpyAsync(ctx->host_scalars + i, lw[i].scalars, sizeof(float), hipMemcpyDeviceToHost, ls);
@@ -650,7 +655,7 @@ static gelo_status sample_into(gelo_ctx* ctx, gelo_mixing* m, FactorWorkspace ws
             return fail(ctx, GELO_ECOND, "no draw with kappa <= %g within %d attempts", cond_max, max_attempts);
         }
     }
-    if (k_shield > 0) {
+    if (k_shield > 0 && !shields_drawn) {
         ps.c1 = kStreamShield << 8;
         GELO_HIP(ctx, shield_directions(m->GS, k_shield, d, ps, m->gsnorm, s));
     }
@@ -980,8 +985,8 @@ gelo_status gelo_sample_mixing_batch(gelo_ctx* ctx, gelo_kind kind, int n_data, 
         small_targets_layout(got[base], &t);
         for (int i = 0; i < c; ++i) t.block[i] = got[base + i]->block;
         ps.c1 = kStreamMixing << 8; ps.c2 = (uint32_t)id; ps.c3 = (uint32_t)(id >> 32);
-        hipError_t e = fill_normal_batched(w.M, stride, w.n_pad / 16, n, n, ps, 1, c, direct, s);      // straight into the QR's tiles
-        if (e == hipSuccess) e = householder_qr(w, n, c, stride, s, direct);
+        hipError_t e = fill_normal_batched(w.M, stride, w.n_pad / 16, n, n, ps, 1, c, direct, s, 0, 1.f, w.X);      // straight into the QR's tiles
+        if (e == hipSuccess) e = householder_qr_prepared(w, c, stride, s, direct);
         // A = Q diag(sign r_ii); A^-1 = A^T
         if (e == hipSuccess) e = emit_batched(w.X, w.rdiag, stride, w.n_pad / 16, n, ldk, t, c, 1, 0, 0, s);
         if (e == hipSuccess) {

@@ -948,6 +948,14 @@ hipError_t launch_qr_bulk(const QrBulkArgs& b, int count, hipStream_t s) {
 
 hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t batch_stride, hipStream_t s, bool direct) {
     if (count < 1 || count > 65535) return hipErrorInvalidValue;
+    const int64_t elems = (int64_t)ws.n_pad * ws.n_pad;
+    hipLaunchKernelGGL(qr_prepare_kernel, dim3((unsigned)((elems + 255) / 256), count), dim3(256), 0, s, ws.M, ws.X, n, ws.n_pad, batch_stride);
+    GELO_TRY(hipGetLastError());
+    return householder_qr_prepared(ws, count, batch_stride, s, direct);
+}
+
+hipError_t householder_qr_prepared(const FactorWorkspace& ws, int count, int64_t batch_stride, hipStream_t s, bool direct) {
+    if (count < 1 || count > 65535) return hipErrorInvalidValue;
     const int n_pad = ws.n_pad;
     const int nbr = n_pad / NB;                               // tile rows (= tile columns)
     const int64_t strip_stride = (int64_t)nbr * 256;
@@ -961,11 +969,6 @@ hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t b
     // Q is formed AFTER the factorisation, last block first: block b then only meets the columns from its own first
     // one on - the rest of H_b+1 ... H_N is still the identity there - which is 4/3 n^3 operations instead of the
     // 2 n^3 of carrying Q^T along with the factorisation.
-    {
-        const int64_t elems = (int64_t)n_pad * n_pad;
-        hipLaunchKernelGGL(qr_prepare_kernel, dim3((unsigned)((elems + 255) / 256), count), dim3(256), 0, s, ws.M, ws.X, n, n_pad, batch_stride);
-        GELO_TRY(hipGetLastError());
-    }
     const bool wide = wide_product(n_pad, direct);
     if (direct) {
         // every panel's reflectors from the raw columns, in one launch: nothing to factorise, no chain of panels

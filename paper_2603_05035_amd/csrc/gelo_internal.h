@@ -231,9 +231,11 @@ struct SmallSampleTargets {
 // 13 - 15).  Matrix z belongs to object z / per_batch, whose batch id is z / per_batch after ps.c3:c2.
 // fill: matrix z at out + z out_stride, tiled like fill_normal's, stream word ps.c1 + z % per_batch.  tail_rows > 0: the last of every
 // per_batch matrices is a Gaussian of tail_rows rows and columns that starts at tail_offset(tile_rows, tail_rows), with the identity before it
-// and zeros behind it (square matrices of at most 256 rows)
+// and zeros behind it (square matrices of at most 256 rows).  X: as householder_qr_prepared wants M and X; then also the shield directions of
+// the only object (stream word shields.c1)
+struct ShieldRows { float* GS = nullptr; float* gsnorm = nullptr; int k = 0, d = 0; uint32_t c1 = 0; };
 hipError_t fill_normal_batched(float* out, int64_t out_stride, int tile_rows, int rows, int cols, PhiloxStream ps, int per_batch, int count,
-                               bool lower_only, hipStream_t stream, int tail_rows = 0);
+                               bool lower_only, hipStream_t stream, int tail_rows = 0, float scale = 1.f, float* X = nullptr, const ShieldRows& shields = ShieldRows());
 __host__ __device__ inline int tail_offset(int tile_rows, int tail_rows) { return 16 * (tile_rows - (tail_rows + 15) / 16); }
 // emit: matrix z (tiles at src + z src_stride, column signs at rdiag + z src_stride) and its transpose into A32, Ainv32 (A16,
 // Ainv16) of its object, dst_first + (z % per_batch) dst_stride elements behind their start; `count` objects; tail_rows as above: that part
@@ -342,6 +344,8 @@ void factor_workspace_carve(void* base, int n, FactorWorkspace* ws, bool direct 
 // stands (rows k onward), so ws.X becomes the product H_0 H_1 ... H_{n-1} of directly drawn reflectors and
 // ws.rdiag the values beta_k those reflectors map their columns to; no chain of dependent panels.
 hipError_t householder_qr(const FactorWorkspace& ws, int n, int count, int64_t batch_stride, hipStream_t stream, bool direct = false);
+// the same where M's tiles are zero beyond n and ws.X is the identity already
+hipError_t householder_qr_prepared(const FactorWorkspace& ws, int count, int64_t batch_stride, hipStream_t stream, bool direct = false);
 // Behind householder_qr(ws, n, 1, ..., direct = false) of the matrix A (n rows of pitch ldk, ldk % 64 == 0, zero beyond column n;
 // read up to 128 rows only): A^-1 = R^-1 Q^T into Ainv32 and, unless it is null, rounded into Ainv16, laid out like A;
 // *ws.flag != 0 if R has a zero on its diagonal.  Overwrites ws.M, ws.Vc and ws.Dinv.

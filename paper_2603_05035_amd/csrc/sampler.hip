@@ -32,20 +32,35 @@ void fill_normal_kernel(float* out, int64_t ld, int rows, int cols, PhiloxStream
 // instead takes 16 rows x 256 columns, computes the blocks that cover each of its row segments (one more per
 // row than the segment holds when its ends fall inside blocks), sets the values down in LDS and writes the 16
 // tiles out as they lie in memory, 16 bytes per lane.
+// With X: all of what the factorisation starts from, the tiles to their end (zeros beyond the matrix) and X = I; and, behind the rows of
+// tiles, rows of shield directions (of the only object of the launch).  As launches of their own these took 8.5 and 4.3 us at 2150 rows, 3.3 and 4 at 543.
 __global__ __launch_bounds__(256)
 void fill_normal_tiled_kernel(float* out, int64_t out_stride, int per_batch, int tile_rows, int rows, int cols, PhiloxStream ps, float scale, int lower_only,
-                              int tail_rows) {
+                              int tail_rows, float* X, ShieldRows shields) {
     constexpr int CW = 256, PITCH = CW + 1, PER_ROW = CW / 4 + 1;
     __shared__ float tile[16 * PITCH];
+    if ((int)blockIdx.y >= tile_rows) {                      // (X only)
+        if (blockIdx.x > 0 || blockIdx.z > 0) return;
+        ps.c1 = shields.c1;
+        shield_direction_row(shields.GS, shields.d, blockIdx.y - tile_rows, ps, shields.gsnorm, tile);
+        return;
+    }
     const bool tail = tail_rows > 0 && (int)blockIdx.z % per_batch == per_batch - 1;
     {   // matrix z of the launch: the per_batch matrices of batch id c3:c2, of the id after it, ...
         const int item = blockIdx.z / per_batch;
         const uint64_t id = (((uint64_t)ps.c3 << 32) | ps.c2) + (uint64_t)item;
         ps.c1 += blockIdx.z - item * per_batch; ps.c2 = (uint32_t)id; ps.c3 = (uint32_t)(id >> 32);
         out += (int64_t)blockIdx.z * out_stride;
+        if (X != nullptr) X += (int64_t)blockIdx.z * out_stride;
     }
     const int tid = threadIdx.x;
     const int r0 = blockIdx.y * 16, c0 = blockIdx.x * CW;
+    const int padded = X != nullptr ? 16 * tile_rows : 0;    // rows and columns of the tiles
+    if (X != nullptr)
+        for (int it = tid; it < CW * 4; it += 256) {
+            const int c = c0 + (it >> 2), r = r0 + (it & 3) * 4;
+            if (c < padded) *reinterpret_cast<float4*>(X + qr_tile_index(r, c, tile_rows)) = make_float4(r == c ? 1.f : 0.f, r + 1 == c ? 1.f : 0.f, r + 2 == c ? 1.f : 0.f, r + 3 == c ? 1.f : 0.f);
+        }
     if (lower_only && c0 >= r0 + 16) return;                 // every column of this piece lies to the right of every row's diagonal entry
     const int write_rows = rows, write_width = min(CW, cols - c0);
     int row_shift = 0, col_shift = 0;                        // where the Gaussian starts
@@ -59,7 +74,7 @@ void fill_normal_tiled_kernel(float* out, int64_t out_stride, int per_batch, int
         __syncthreads();
     }
     const int width = min(CW, cols - c0);
-    for (int idx = tid; idx < 16 * PER_ROW; idx += 256) {
+    for (int idx = tid; idx < 16 * PER_ROW && width > 0; idx += 256) {
         const int ri = idx / PER_ROW, bi = idx - ri * PER_ROW;
         const int r = r0 + ri - row_shift;
         if (r < 0 || r >= rows) break;                       // (row_shift is a multiple of 16)
@@ -81,6 +96,14 @@ void fill_normal_tiled_kernel(float* out, int64_t out_stride, int per_batch, int
     // float4 item: rows 4 g .. 4 g + 3 of column c of the strip (16 bytes of a tile: index (c & 15) * 16 + 4 g)
     for (int it = tid; it < CW * 4; it += 256) {
         const int c = it >> 2, g = it & 3;
+        if (padded > 0) {
+            if (c0 + c >= padded) continue;
+            float v[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[t] = c < write_width && r0 + 4 * g + t < write_rows ? tile[(4 * g + t) * PITCH + c] : 0.f;
+            *reinterpret_cast<float4*>(out + qr_tile_index(r0 + 4 * g, c0 + c, tile_rows)) = make_float4(v[0], v[1], v[2], v[3]);
+            continue;
+        }
         if (c >= write_width) continue;
         float* dst = out + qr_tile_index(r0 + 4 * g, c0 + c, tile_rows);
         const float* src = tile + (4 * g) * PITCH + c;
@@ -364,7 +387,7 @@ hipError_t fill_normal(float* out, int64_t ld, int rows, int cols, PhiloxStream 
     if (quads == 0) return hipSuccess;
     if (tiled && (int64_t)rows * cols < ((int64_t)1 << 32)) {
         hipLaunchKernelGGL(fill_normal_tiled_kernel, dim3((cols + 255) / 256, (rows + 15) / 16), dim3(256), 0, stream,
-                           out, (int64_t)0, 1, (int)ld, rows, cols, ps, scale, tiled == 2 ? 1 : 0, 0);
+                           out, (int64_t)0, 1, (int)ld, rows, cols, ps, scale, tiled == 2 ? 1 : 0, 0, (float*)nullptr, ShieldRows());
         return hipGetLastError();
     }
     hipLaunchKernelGGL(fill_normal_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream,
@@ -373,12 +396,14 @@ hipError_t fill_normal(float* out, int64_t ld, int rows, int cols, PhiloxStream 
 }
 
 hipError_t fill_normal_batched(float* out, int64_t out_stride, int tile_rows, int rows, int cols, PhiloxStream ps, int per_batch, int count,
-                               bool lower_only, hipStream_t stream, int tail_rows) {
+                               bool lower_only, hipStream_t stream, int tail_rows, float scale, float* X, const ShieldRows& shields) {
     if (rows <= 0 || cols <= 0 || count <= 0) return hipSuccess;
     if (count > 65535 || per_batch < 1 || (int64_t)rows * cols >= ((int64_t)1 << 32)) return hipErrorInvalidValue;
+    if (X != nullptr && (rows != cols || tile_rows != (rows + 15) / 16)) return hipErrorInvalidValue;
+    if (shields.k > 0 && (X == nullptr || count != per_batch)) return hipErrorInvalidValue;
     if (tail_rows != 0 && (tail_rows < 0 || tail_rows > rows || rows != cols || rows > 256 || tile_rows * 16 != rows || lower_only)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(fill_normal_tiled_kernel, dim3((cols + 255) / 256, (rows + 15) / 16, count), dim3(256), 0, stream,
-                       out, out_stride, per_batch, tile_rows, rows, cols, ps, 1.0f, lower_only ? 1 : 0, tail_rows);
+    hipLaunchKernelGGL(fill_normal_tiled_kernel, dim3((cols + 255) / 256, (rows + 15) / 16 + shields.k, count), dim3(256), 0, stream,
+                       out, out_stride, per_batch, tile_rows, rows, cols, ps, scale, lower_only ? 1 : 0, tail_rows, X, shields);
     return hipGetLastError();
 }
 
