@@ -134,134 +134,134 @@ struct SmallMixArgs {
 };
 
 constexpr int MIX_BN = 64;           // columns of U per workgroup
-constexpr int MIX_KP = 128 + 8;      // pitch (bf16) of a column of the transposed operand tile in LDS
 
-// One workgroup: 64 columns of U.  The operand tile [H ; S] (n x 64) is stored transposed in LDS (column-major,
-// K contiguous) so that a lane's eight contraction values are one 16-byte read; wave w owns rows 32 w .. 32 w + 31
-// of U and reads its rows of A straight from memory (A is zero beyond column n up to its pitch).
+// The median of `count` row norms (count <= kSmallMaxN; norms[count .. rounded up to 4 - 1] all ones in bits) as its two middle elements,
+// by 256 threads: two per norm count the (value, index) pairs below it, four at a time.
+__device__ __forceinline__ void middle_norms(const float* norms, int count, float* middle) {
+    const int e = threadIdx.x >> 1, half = threadIdx.x & 1;
+    const float value = norms[e < count ? e : 0];
+    const uint32_t mine = __float_as_uint(value);
+    int below = 0;
+#pragma unroll 2
+    for (int i = 4 * half; i < count; i += 8) {
+        const u32x4_t o = *reinterpret_cast<const u32x4_t*>(norms + i);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) below += (o[t] < mine || (o[t] == mine && i + t < e)) ? 1 : 0;
+    }
+    below += __shfl_xor(below, 1, 64);
+    if (half == 0 && e < count) {
+        if (below == (count - 1) / 2) middle[0] = value;
+        if (below == count / 2) middle[1] = value;
+    }
+}
+__device__ __forceinline__ float norm_or_padding(float norm, int i, int count) { return i < count ? norm : __uint_as_float(0xFFFFFFFFu); }
+
+// The operand tile of a product with at most kSmallMaxN contraction rows: 64 columns of bf16, row after row in LDS, 128 bytes each, in
+// chunks of 16; the halves of rows 2, 3, 6, 7, ... are swapped, which puts the four rows of a transposing read on distinct banks.
+__device__ __forceinline__ int tile_chunk(int r, int c) { return r * 8 + (c ^ (4 * ((r >> 1) & 1))); }
+
+// One workgroup: 64 columns of U, contraction over 16 KS >= n rows; wave w owns rows 32 w .. 32 w + 31.
+//
+// A chain of latencies, and most of all of instruction fetches: between the projections of a decode step, each of which sends a whole
+// weight through the caches, the code of this kernel is cold, and straight-line code then runs at some 30 ns per 64 bytes (cycle
+// stamps).  So the code is kept short: sizes by template and clamped addresses instead of a test per load, loops over shield rows and
+// norms, immediate offsets: 3.6 KB of it for 96 rows; one body for all sizes, with a test per load, took 11.7.  64 + 4 rows of 4096
+// between such projections 8.7 -> 5.2 us (by themselves 8.4 -> 4.9); ranking the norms by more threads and the transposing reads, in
+// the long body, 0.2 of that.
+template <int KS>
 __global__ __launch_bounds__(256)
 void small_mix_kernel(SmallMixArgs a) {
-    __shared__ __attribute__((aligned(16))) uint16_t Bt[MIX_BN * MIX_KP];
-    __shared__ float norms[kSmallMaxN];
-    __shared__ float factor[kSmallMaxN];
-    __shared__ float stat_s;
+    typedef short s16x4_t __attribute__((ext_vector_type(4)));
+    typedef short s16x8_t __attribute__((ext_vector_type(8)));
+    typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+    typedef s16x4_t __attribute__((address_space(3))) * lds_ptr_t;
+    __shared__ __attribute__((aligned(16))) uint16_t tile[KS * 16 * MIX_BN];
+    __shared__ __attribute__((aligned(16))) float norms[kSmallMaxN];
+    __shared__ float middle[2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = a.n_data + a.k, c0 = blockIdx.x * MIX_BN;
-    const int kp = (n + 15) & ~15;
     const int j = lane & 31, grp = lane >> 5;
 
-    // Every load from memory is issued before anything waits: the kernel is a chain of a few dependent steps, and
-    // one memory latency per step would be most of its run time.
-    const float my_norm = (a.k > 0 && tid < a.n_data) ? a.rownorm[tid] : 0.f;
-    const float my_gsnorm = tid < a.k ? a.gsnorm[tid] : 1.f;
-    constexpr int HR = kSmallMaxN * (MIX_BN / 8) / 256;          // 16-byte chunks of H per thread: at most 4
+    // every load from memory is issued before anything waits; columns from d on repeat others and are not stored
+    float my_norm = 0.f, direction = 0.f, length = 1.f;
+    const int gc = c0 + lane, gcl = gc < a.d ? gc : a.d - 1;
+    if (a.k > 0) {
+        my_norm = a.rownorm[tid < a.n_data ? tid : 0];
+        const int r = wave < a.k ? wave : 0;                     // wave w: shield rows w, w + 4, ...
+        direction = a.GS[(int64_t)r * a.d + gcl];
+        length = a.gsnorm[r];
+    }
+    constexpr int HR = KS / 2;                                   // 16-byte chunks of H per thread
+    const int hr = tid >> 3, ch = tid & 7;
+    const int hc = c0 + ch * 8 < a.d ? c0 + ch * 8 : a.d - 8;
     u32x4_t hreg[HR];
 #pragma unroll
     for (int it = 0; it < HR; ++it) {
-        const int i = tid + it * 256;
-        const int r = i >> 3, col = c0 + (i & 7) * 8;
-        hreg[it] = u32x4_t{0u, 0u, 0u, 0u};
-        if (r < a.n_data && col < a.d) hreg[it] = *reinterpret_cast<const u32x4_t*>(a.H + (int64_t)r * a.ldh + col);
+        const int r = hr + it * 32;
+        hreg[it] = *reinterpret_cast<const u32x4_t*>(a.H + (int64_t)(r < a.n_data ? r : a.n_data - 1) * a.ldh + hc);
     }
-    constexpr int GR = 4;                                        // shield values per thread held in registers (k <= 16)
-    float gsv[GR];
+    bf16x8_t af[KS];                                             // the wave's rows of A, zero beyond column n up to their pitch
+    const int row = wave * 32 + j;
+    const uint16_t* ap = a.A16 + (int64_t)(row < n ? row : n - 1) * a.ldk + grp * 8;
 #pragma unroll
-    for (int it = 0; it < GR; ++it) {
-        const int i = tid + it * 256;
-        const int r = i / MIX_BN, col = c0 + (i - r * MIX_BN);
-        gsv[it] = (r < a.k && col < a.d) ? a.GS[(int64_t)r * a.d + col] : 0.f;
-    }
-    bf16x8_t af[kSmallMaxN / 16];
-    {
-        int arow = wave * 32 + j; arow = arow < n ? arow : n - 1;
-        const uint16_t* ap = a.A16 + (int64_t)arow * a.ldk + grp * 8;
-#pragma unroll
-        for (int ks = 0; ks < kSmallMaxN / 16; ++ks)
-            if (ks * 16 < kp && wave * 32 < n) af[ks] = *reinterpret_cast<const bf16x8_t*>(ap + ks * 16);
-    }
+    for (int ks = 0; ks < KS; ++ks) af[ks] = *reinterpret_cast<const bf16x8_t*>(ap + ks * 16);
 
+    if (tid < kSmallMaxN) norms[tid] = norm_or_padding(my_norm, tid, a.n_data);
+#pragma unroll
+    for (int it = 0; it < HR; ++it) {                            // rows from n on are cleared, shield rows follow
+        const int r = hr + it * 32;
+        const u32x4_t zero = {0u, 0u, 0u, 0u};
+        if (r < a.n_data || r >= n) *reinterpret_cast<u32x4_t*>(tile + tile_chunk(r, ch) * 8) = r < n ? hreg[it] : zero;
+    }
+    __syncthreads();
     if (a.k > 0) {
-        if (tid < a.n_data) norms[tid] = my_norm;
-        __syncthreads();
+        float m;
         if (a.stat_kind == 0) {
-            // median by rank: every value counts the (value, index) pairs below it; the two of middle rank meet in the mean
-            if (tid < a.n_data) {
-                const uint32_t mine = __float_as_uint(my_norm);
-                int below = 0;
-                for (int i = 0; i < a.n_data; ++i) {
-                    const uint32_t o = __float_as_uint(norms[i]);
-                    below += (o < mine || (o == mine && i < tid)) ? 1 : 0;
-                }
-                if (below == (a.n_data - 1) / 2) factor[0] = my_norm;
-                if (below == a.n_data / 2) factor[1] = my_norm;
-            }
+            middle_norms(norms, a.n_data, middle);
             __syncthreads();
-            if (tid == 0) stat_s = 0.5f * (factor[0] + factor[1]);
-        } else if (tid == 0) {
+            m = 0.5f * (middle[0] + middle[1]);
+        } else {
             float s = 0.f;
+#pragma unroll 1
             for (int i = 0; i < a.n_data; ++i) s += norms[i];
-            stat_s = s / (float)a.n_data;
+            m = s / (float)a.n_data;
+        }
+#pragma unroll 1
+        for (int r = wave; r < a.k; r += 4) {
+            const __bf16 h = (__bf16)(direction * (a.shield_scale * m / length));
+            const uint16_t bits = __builtin_bit_cast(uint16_t, h);
+            const int next = r + 4 < a.k ? r + 4 : r;
+            direction = a.GS[(int64_t)next * a.d + gcl];
+            length = a.gsnorm[next];
+            if (gc < a.d) a.S[(int64_t)r * a.d + gc] = bits;
+            tile[tile_chunk(a.n_data + r, lane >> 3) * 8 + (lane & 7)] = bits;
         }
         __syncthreads();
-        const float m = stat_s;
-        __syncthreads();
-        if (tid < a.k) factor[tid] = a.shield_scale * m / my_gsnorm;
     }
-    // zero the K padding of the tile, then fill it: rows of H as 16-byte chunks of 8 columns, shield rows scaled on the way
-    for (int i = tid; i < MIX_BN * (MIX_KP / 2); i += 256) reinterpret_cast<uint32_t*>(Bt)[i] = 0u;
-    __syncthreads();
-#pragma unroll
-    for (int it = 0; it < HR; ++it) {
-        const int i = tid + it * 256;
-        const int r = i >> 3, ch = i & 7;
-        if (r < a.n_data && c0 + ch * 8 < a.d) {                 // d is a multiple of 8: a chunk is inside or outside
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                Bt[(ch * 8 + 2 * t) * MIX_KP + r] = (uint16_t)(hreg[it][t] & 0xFFFFu);
-                Bt[(ch * 8 + 2 * t + 1) * MIX_KP + r] = (uint16_t)(hreg[it][t] >> 16);
-            }
-        }
-    }
-    for (int i = tid, it = 0; i < a.k * MIX_BN; i += 256, ++it) {
-        const int r = i / MIX_BN, cc = i - r * MIX_BN;
-        const int col = c0 + cc;
-        if (col >= a.d) continue;
-        float gsx;
-        switch (it) { case 0: gsx = gsv[0]; break; case 1: gsx = gsv[1]; break; case 2: gsx = gsv[2]; break; case 3: gsx = gsv[3]; break;
-                      default: gsx = a.GS[(int64_t)r * a.d + col]; }
-        const __bf16 h = (__bf16)(gsx * factor[r]);
-        const uint16_t bits = __builtin_bit_cast(uint16_t, h);
-        a.S[(int64_t)r * a.d + col] = bits;
-        Bt[cc * MIX_KP + a.n_data + r] = bits;
-    }
-    __syncthreads();
     if (wave * 32 >= n) return;
-    // v_mfma_f32_32x32x16_bf16: lane l supplies row l % 32 of A and column l % 32 of B, contraction values
-    // 8 (l / 32) .. + 7; it receives column l % 32, rows 8 (v / 4) + 4 (l / 32) + v % 4
-    f32x16_t acc[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < kSmallMaxN / 16; ++ks) {
-        if (ks * 16 < kp) {
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const bf16x8_t bf = *reinterpret_cast<const bf16x8_t*>(Bt + (t * 32 + j) * MIX_KP + ks * 16 + grp * 8);
-                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks], bf, acc[t], 0, 0, 0);
-            }
-        }
-    }
+    // v_mfma_f32_32x32x16_bf16 with the tile as first operand: lane l supplies column l % 32 of the tile and row l % 32 of A, contraction
+    // values 8 (l / 32) .. + 7; it receives row l % 32, columns 8 (v / 4) + 4 (l / 32) + v % 4: four neighbours are one 8-byte store.
+    const int s16 = lane & 15, nh = (lane >> 4) & 1;
+    const int rl = grp * 8 + (s16 >> 2);                         // row of the first transposing read; the second is 4 below
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-        const int col = c0 + t * 32 + j;
+        const uint16_t* at = tile + tile_chunk(rl, t * 4 + nh * 2) * 8 + (s16 & 3) * 4;
+        f32x16_t acc;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = wave * 32 + 8 * (v >> 2) + 4 * grp + (v & 3);
-            if (row < n && col < a.d) {
-                const __bf16 h = (__bf16)acc[t][v];
-                a.U[(int64_t)row * a.ldu + col] = __builtin_bit_cast(uint16_t, h);
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(at + ks * 16 * MIX_BN));
+            const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(at + (ks * 16 + 4) * MIX_BN));
+            const s16x8_t both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, both), af[ks], acc, 0, 0, 0);
+        }
+        if (row < n) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int col = c0 + t * 32 + 8 * q + 4 * grp;   // d is a multiple of 8
+                const bf16x4_t h = {(__bf16)acc[4 * q], (__bf16)acc[4 * q + 1], (__bf16)acc[4 * q + 2], (__bf16)acc[4 * q + 3]};
+                if (col < a.d) *reinterpret_cast<uint2*>(a.U + (int64_t)row * a.ldu + col) = __builtin_bit_cast(uint2, h);
             }
         }
     }
@@ -302,14 +302,12 @@ __device__ __forceinline__ void row_norms_of_wave(const float* first, int64_t ld
 
 // The factors of the k shield rows from the row norms, 256 threads: thread t brings norm t (t < n_data) and the norm of
 // shield direction t (t < k).  NORMS: the norms are taken here, from H.
-struct SmallStatistic { float norms[kSmallMaxN], factor[kSmallMaxN], stat; };
+struct SmallStatistic { __attribute__((aligned(16))) float norms[kSmallMaxN]; float factor[kSmallMaxN], middle[2]; };
 template <bool NORMS>
 __device__ __forceinline__ void shield_factors(SmallStatistic& sh, const SmallMixF32Args& a, float my_norm, float my_gsnorm) {
     const int tid = threadIdx.x;
-    if (!NORMS) {
-        if (tid < a.n_data) sh.norms[tid] = my_norm;
-        __syncthreads();
-    } else {
+    if (tid < kSmallMaxN && (!NORMS || tid >= a.n_data)) sh.norms[tid] = norm_or_padding(my_norm, tid, a.n_data);
+    if (NORMS) {
         const int lane = tid & 63, wave = tid >> 6;
         for (int r0 = wave; r0 < a.n_data; r0 += 4 * kRowsTogether) {
             float norm[kRowsTogether];
@@ -317,23 +315,13 @@ __device__ __forceinline__ void shield_factors(SmallStatistic& sh, const SmallMi
 #pragma unroll
             for (int i = 0; i < kRowsTogether; ++i) if (lane == 0 && r0 + 4 * i < a.n_data) sh.norms[r0 + 4 * i] = norm[i];
         }
-        __syncthreads();
-        my_norm = tid < a.n_data ? sh.norms[tid] : 0.f;
     }
+    __syncthreads();
+    float m;
     if (a.stat_kind == 0) {
-        // median by rank: every value counts the (value, index) pairs below it; the two of middle rank meet in the mean
-        if (tid < a.n_data) {
-            const uint32_t mine = __float_as_uint(my_norm);
-            int below = 0;
-            for (int i = 0; i < a.n_data; ++i) {
-                const uint32_t o = __float_as_uint(sh.norms[i]);
-                below += (o < mine || (o == mine && i < tid)) ? 1 : 0;
-            }
-            if (below == (a.n_data - 1) / 2) sh.factor[0] = my_norm;
-            if (below == a.n_data / 2) sh.factor[1] = my_norm;
-        }
+        middle_norms(sh.norms, a.n_data, sh.middle);
         __syncthreads();
-        if (tid == 0) sh.stat = 0.5f * (sh.factor[0] + sh.factor[1]);
+        m = 0.5f * (sh.middle[0] + sh.middle[1]);
     } else {                                                     // a tree sum, as mean_kernel's
         if (tid < kSmallMaxN) sh.factor[tid] = tid < a.n_data ? sh.norms[tid] : 0.f;
         __syncthreads();
@@ -341,11 +329,9 @@ __device__ __forceinline__ void shield_factors(SmallStatistic& sh, const SmallMi
             if (tid < half) sh.factor[tid] += sh.factor[tid + half];
             __syncthreads();
         }
-        if (tid == 0) sh.stat = sh.factor[0] / (float)a.n_data;
+        m = sh.factor[0] / (float)a.n_data;
+        __syncthreads();
     }
-    __syncthreads();
-    const float m = sh.stat;
-    __syncthreads();
     if (tid < a.k) sh.factor[tid] = a.shield_scale * m / my_gsnorm;
 }
 
@@ -474,12 +460,18 @@ hipError_t small_mix(const uint16_t* A16, int64_t ldk, const uint16_t* H, int64_
                      const float* rownorm, int stat_kind, float shield_scale, int n_data, int k, int d,
                      uint16_t* S, uint16_t* U, int64_t ldu, hipStream_t stream) {
     const int n = n_data + k;
-    if (n < 1 || n > kSmallMaxN || d < 8 || d % 8 != 0 || ldk < ((n + 15) & ~15)) return hipErrorInvalidValue;
+    if (n < 1 || n > kSmallMaxN || d < 8 || d % 8 != 0 || ldk < ((n + 31) & ~31)) return hipErrorInvalidValue;
     SmallMixArgs a;
     a.A16 = A16; a.ldk = ldk; a.H = H; a.ldh = ldh; a.GS = GS; a.gsnorm = gsnorm; a.rownorm = rownorm;
     a.stat_kind = stat_kind; a.shield_scale = shield_scale; a.n_data = n_data; a.k = k; a.d = d;
     a.S = S; a.U = U; a.ldu = ldu;
-    hipLaunchKernelGGL(small_mix_kernel, dim3((unsigned)((d + MIX_BN - 1) / MIX_BN)), dim3(256), 0, stream, a);
+    const dim3 grid((unsigned)((d + MIX_BN - 1) / MIX_BN));
+    switch ((n + 31) / 32) {
+        case 1: hipLaunchKernelGGL(small_mix_kernel<2>, grid, dim3(256), 0, stream, a); break;
+        case 2: hipLaunchKernelGGL(small_mix_kernel<4>, grid, dim3(256), 0, stream, a); break;
+        case 3: hipLaunchKernelGGL(small_mix_kernel<6>, grid, dim3(256), 0, stream, a); break;
+        default: hipLaunchKernelGGL(small_mix_kernel<8>, grid, dim3(256), 0, stream, a); break;
+    }
     return hipGetLastError();
 }
 

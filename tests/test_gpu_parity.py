@@ -596,6 +596,38 @@ def test_small_float_mix(n_data, k, d, stat):
     assert bool(((U[1:n + 1].double() - left @ right).abs() <= (n + 2) * 2.0 ** -24 * (left.abs() @ right.abs())).all())
 
 
+# bf16 batches of at most 128 rows mix in one launch as well, a body per 32 rows: one row, the last and first of each body, shield rows beyond the
+# sixteen whose directions are read ahead of the norms' statistic, columns that fill no tile, an output over its own H
+@pytest.mark.parametrize("stat", [g.GELO_NORM_MEDIAN, g.GELO_NORM_MEAN])
+@pytest.mark.parametrize("n_data,k,d", [(1, 0, 8), (1, 1, 8), (3, 4, 64), (30, 2, 136), (31, 2, 72), (64, 0, 200), (60, 4, 264), (44, 21, 64), (92, 4, 104),
+                                        (61, 36, 1032), (127, 1, 72), (64, 64, 136)])
+def test_small_bf16_mix(n_data, k, d, stat):
+    n = n_data + k
+    H = torch.randn((n_data, d), generator=torch.Generator(device="cuda").manual_seed(n * d), device="cuda").bfloat16()
+    wide = torch.full((n + 2, d + 8), float("nan"), device="cuda", dtype=torch.bfloat16)
+    both = torch.full((n, d), float("nan"), device="cuda", dtype=torch.bfloat16)
+    both[:n_data] = H
+    again = g.gelo_create(0, 5, allow_batch_reuse=True)
+    for X, out in ((H, wide[1:n + 1, :d]), (both[:n_data], both)):
+        m = g.gelo_sample_mixing(again, g.GELO_ORTHOGONAL, n_data, k, d, g.GELO_BF16, 0.0, 1, batch_id=9)
+        g.gelo_mix(again, m, X, out, stat=stat)
+        A, _, S, _, _ = g.gelo_mixing_export(again, m, n, k, d)
+        torch.cuda.synchronize()
+        g.gelo_mixing_free(again, m)
+    g.gelo_destroy(again)
+    U = wide[1:n + 1, :d].clone()
+    wide[1:n + 1, :d] = float("nan")
+    assert torch.isnan(wide).all() and torch.equal(U, both)
+    right = H.double()
+    if k > 0:
+        right = torch.cat([right, S.double()])
+        target = 10.0 * o.row_norm_statistic(f64(H), stat)
+        assert np.abs(np.linalg.norm(f64(S), axis=1) / target - 1).max() < 2.0 ** -8 + 1e-5      # bf16 holds 8 bits: each element is rounded by at most 2^-8 of itself
+    left = A.bfloat16().double()
+    exact, sums = left @ right, (n + 2) * 2.0 ** -24 * (left.abs() @ right.abs())          # float sums, then one rounding to bf16
+    assert bool(((U.double() - exact).abs() <= 2.0 ** -8 * exact.abs() + 1.01 * sums).all())
+
+
 # where the product of the mix gets a 128 x 128 tile per CU, beyond 32640 columns, it takes its operands apart, in one launch with the shield rows
 # or not: the bits of that product by itself on either side of the line
 @pytest.mark.parametrize("n_data,k", [(7, 1), (67, 5), (91, 5)])
