@@ -190,7 +190,7 @@ gelo_status gelo_mix(gelo_ctx* ctx, gelo_mixing* mixing, gelo_dtype dtype, const
 
 /* Accelerator side, eq. 2.  Y[n x p] = U[n x d] * W[d x p].  Touches no secret: it takes no
  * mixing object.  Also serves as the plain baseline H*W (pass H as U, n = n_data).  A bf16 product
- * of at most 96 rows whose width leaves most of the chip idle (p < 8192) cuts d over workgroups and
+ * of at most 96 rows whose width leaves most of the chip idle (p < 8192) cuts a long d over workgroups and
  * keeps their float partial sums in a context workspace (gelo_reserve with p sizes it): two such
  * calls on one context must not overlap in time on different streams. */
 gelo_status gelo_project(gelo_ctx* ctx, gelo_dtype dtype, int n, int d, int p,

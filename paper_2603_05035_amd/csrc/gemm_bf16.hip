@@ -663,11 +663,12 @@ void gemm_bf16_sum_kernel(Bf16Args g, Sum more) {
 // matrix cores make of the stale LDS words lands in rows that are never stored).  The four partial
 // sums meet in LDS after the loop and are added in wave order.
 //
-// Two shapes of launch.  Measured on MI355X, one CU streams at most 26 - 28 GB/s from HBM whatever
+// Three shapes of launch.  Measured on MI355X, one CU streams at most 26 - 28 GB/s from HBM whatever
 // the depth of its ring (3 to 13 stages made no difference, nor did a panel-contiguous copy of B),
 // and every byte of A a CU fetches (all of A, once per workgroup) counts against the same limit:
 // 68 x 12288 x 4096 took 30 us on 192 workgroups of 64 columns, 20 us with 8 rows.
-//  - NCT = 2 (64 columns), all of K per workgroup: no workspace, any shape.
+//  - NCT = 2 (64 columns), all of K per workgroup: no workspace, any shape; NCT = 4 (128 columns) in its place for widths that
+//    take 64-column groups more than one round (the rule stands at the launch).
 //  - NCT = 6 (192 columns = three whole 128-byte lines per row of B), K cut into `slices` ranges of
 //    K steps so that columns x slices fills the chip: every CU streams its share of B and only
 //    1 / slices of A.  The workgroups write float partial sums; a second small kernel adds them in
@@ -970,6 +971,11 @@ int gemm_bf16_skinny_slices(int M, int N, int K) {
     // 12288 x 4096: 30 us either way; 68 x 4096 x 4096: 28 -> 20 us; 68 x 4096 x 11008: 70 -> 29 us); beyond three
     // row tiles the 192-column accumulators no longer fit the registers.
     if (M > 96 || N < 192 || (N + 63) / 64 > 128) return 1;
+    // A short K is over before the second launch and the longer epilogue pay: one launch / the two, us, weights from memory,
+    // 512 and 4096 columns: 20 rows, K = 1024 7.0 / 8.2 and 7.3 / 9.5, 1536 9.4 / 9.2 and 9.8 / 11.1, 2048 11.4 / 9.7 and 12.3 / 12.2, 3072
+    // 15.8 / 11.0 and 17.0 / 14.8; 68 rows 10.0 / 12.7 and 10.3 / 14.8, 13.2 / 13.6 and 13.8 / 17.1, 16.3 / 14.1 and 17.2 / 19.1, 22.5 / 15.4 and
+    // 23.7 / 20.3; 96 rows of 2048 16.4 / 14.8 and 17.7 / 20.8.
+    if (K <= 1536 + N / 8) return 1;
     const int groups = (N + 191) / 192;
     const int T = (K + 63) / 64;
     int slices = 256 / groups;
@@ -991,11 +997,11 @@ hipError_t allow_skinny_lds() {
                                hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
 }
 
-template <int RT>
+template <int RT, int NCT>
 hipError_t launch_skinny(const Bf16Args& a, hipStream_t stream) {
-    using C = skinny::Cfg<RT, 2>;
+    using C = skinny::Cfg<RT, NCT>;
     skinny::SkinnyArgs sa{a, nullptr, 0, 1};
-    hipLaunchKernelGGL((skinny::gemm_bf16_skinny_kernel<RT, 2, false>), dim3((a.N + C::BN - 1) / C::BN), dim3(skinny::NWAVES * 64),
+    hipLaunchKernelGGL((skinny::gemm_bf16_skinny_kernel<RT, NCT, false>), dim3((a.N + C::BN - 1) / C::BN), dim3(skinny::NWAVES * 64),
                        (size_t)C::LDS_BYTES, stream, sa);
     return hipGetLastError();
 }
@@ -1052,6 +1058,10 @@ hipError_t gemm_bf16_init() {
     if (e == hipSuccess) e = allow_skinny_lds<2, 2, false>();
     if (e == hipSuccess) e = allow_skinny_lds<3, 2, false>();
     if (e == hipSuccess) e = allow_skinny_lds<4, 2, false>();
+    if (e == hipSuccess) e = allow_skinny_lds<1, 4, false>();
+    if (e == hipSuccess) e = allow_skinny_lds<2, 4, false>();
+    if (e == hipSuccess) e = allow_skinny_lds<3, 4, false>();
+    if (e == hipSuccess) e = allow_skinny_lds<4, 4, false>();
     if (e == hipSuccess) e = allow_skinny_lds<1, 6, true>();
     if (e == hipSuccess) e = allow_skinny_lds<2, 6, true>();
     if (e == hipSuccess) e = allow_skinny_lds<3, 6, true>();
@@ -1174,11 +1184,18 @@ hipError_t gemm_bf16(const GemmOperands& o, hipStream_t stream) {
                 default: return launch_skinny_split<3>(a, slices, ws, stream);
             }
         }
+        // Column groups of 128 where those of 64 take more rounds on the chip's 256 CUs (one workgroup each): half the fetches of A,
+        // longer pieces of B's rows.  68 x 4096 with 64 / 128 columns, us: 16384 35.5 / 49 (one round of each), 16392 63.6 / 44.6,
+        // 22016 62.5 / 49.4, 32768 66.1 / 52.3 (2, 1), 40960 100 / 91 (3, 2), 57344 131 / 105 (4, 2), 73728 166 / 145 (5, 3); 128 rows of
+        // 22016 75.7 / 52.8, 8 49.0 / 37.6.  A short K keeps three rounds of 64 before two of 128: K = 64, 68 x 40960 10.6 / 11.1 (20480
+        // 7.4 / 6.3, 57344 13.5 / 11.6), 1024 33.1 / 30.2.
+        const int r64 = (a.tiles_n + 255) / 256, r128 = ((o.N + 127) / 128 + 255) / 256;
+        const bool wide = r64 > r128 && (o.K > 512 || 3 * r128 < 2 * r64);
         switch ((o.M + 31) / 32) {
-            case 1: return launch_skinny<1>(a, stream);
-            case 2: return launch_skinny<2>(a, stream);
-            case 3: return launch_skinny<3>(a, stream);
-            default: return launch_skinny<4>(a, stream);
+            case 1: return wide ? launch_skinny<1, 4>(a, stream) : launch_skinny<1, 2>(a, stream);
+            case 2: return wide ? launch_skinny<2, 4>(a, stream) : launch_skinny<2, 2>(a, stream);
+            case 3: return wide ? launch_skinny<3, 4>(a, stream) : launch_skinny<3, 2>(a, stream);
+            default: return wide ? launch_skinny<4, 4>(a, stream) : launch_skinny<4, 2>(a, stream);
         }
     }
     return launch<128, 128, 32>(o, stream);

@@ -762,6 +762,22 @@ def test_project_bf16_fast_path_edges(ctx, M, K, N, ldy_extra):
         assert torch.all(parent[:, N:] == 3.0)
 
 
+# K is cut beyond 1536 + N / 8: both sides of that line at the narrowest, an odd and the widest N, with one and three row tiles.  Beyond 16384
+# columns a workgroup takes 128 of them: either side of that line, ragged last groups, one to four row tiles, three rounds with a short and a longer K
+@pytest.mark.parametrize("M,K,N", [(8, 1536, 192), (20, 1600, 192), (68, 1664, 1032), (96, 1728, 1032), (5, 2496, 7744), (96, 2560, 8192), (96, 2624, 8192),
+                                   (1, 64, 16384), (1, 64, 16392), (40, 320, 16456), (96, 1088, 22016), (128, 640, 20488), (33, 512, 32776), (33, 576, 32776)])
+def test_project_bf16_launch_rules(ctx, M, K, N):
+    U = torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(M), device="cuda").bfloat16()
+    W = (0.05 * torch.randn((K, N), generator=torch.Generator(device="cuda").manual_seed(N), device="cuda")).bfloat16()
+    parent = torch.full((M + 1, N + 8), 3.0, dtype=torch.bfloat16, device="cuda")
+    Y = parent[:M, :N]
+    g.gelo_project(ctx, U, W, Y)
+    torch.cuda.synchronize()
+    exact, sums = U.double() @ W.double(), (K + 4) * 2.0 ** -24 * (U.double().abs() @ W.double().abs())
+    assert bool(((Y.double() - exact).abs() <= 2.0 ** -8 * exact.abs() + 1.01 * sums).all())
+    assert torch.all(parent[M] == 3.0) and torch.all(parent[:, N:] == 3.0)
+
+
 @pytest.mark.parametrize("M,K,N,ldy_extra", [
     (512, 256, 12288, 0),      # 128 x 192 tiles (one round of the CUs)
     (500, 1024, 6152, 8),      # 128 x 96 tiles, ragged in M and N
