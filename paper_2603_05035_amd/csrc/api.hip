@@ -58,6 +58,11 @@ namespace {
 void* g_scratch_ptr[kStaticMaxDevices] = {};
 }
 
+// Recorded when a draw has been enqueued.  The objects of one batched draw share the mark: an event of its own for each of 32 cost the
+// host and the queue 31 records more behind a launch of 32 us.  There is a mark per pooled object, so that an object that has to leave a shared one
+// finds one that nobody holds.
+struct ReadyMark { hipEvent_t event; int holders; };
+
 struct gelo_mixing {
     int kind, n_data, k, n, d, dtype;
     int64_t ldk;                 // leading dimension of A / A^-1 (n rounded up to 64), zero padded
@@ -77,7 +82,7 @@ struct gelo_mixing {
     float kappa;                 // host copy (GAUSSIAN); < 0: still only on the device
     bool in_use, mixed, consumed;
     uint64_t batch_id;
-    hipEvent_t ready;            // recorded when sampling has been enqueued
+    ReadyMark* ready;
     hipEvent_t released;         // recorded when the object went back to the pool
     hipStream_t sample_stream, last_stream;
 };
@@ -99,6 +104,7 @@ struct gelo_ctx {
     float* host_scalars;         // pinned: kappa read-back, one slot per lane
     int* host_flag;
     std::vector<gelo_mixing*> pool;
+    std::vector<ReadyMark*> marks;     // one per object of the pool
     hipStream_t lane_stream[kLanes];   // created on the first GAUSSIAN draw
     hipEvent_t lane_fork, lane_done[kLanes];
     hipEvent_t lane_join;              // the winner's copies out of `cand` (on the caller's stream) are done
@@ -261,15 +267,36 @@ gelo_status acquire_mixing(gelo_ctx* ctx, int n_data, int k, int d, int dtype, M
         return fail(ctx, GELO_ENOMEM, "hipMalloc(%zu) failed: %s", L.total, hipGetErrorString(e));
     }
     carve_mixing(m, block, n_data, k, d, dtype, form);
-    if (hipEventCreateWithFlags(&m->ready, hipEventDisableTiming) != hipSuccess ||
+    m->ready = new (std::nothrow) ReadyMark{nullptr, 1};
+    if (!m->ready || hipEventCreateWithFlags(&m->ready->event, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&m->released, hipEventDisableTiming) != hipSuccess) {
-        hipFree(m->block); delete m;
+        if (m->ready && m->ready->event) (void)hipEventDestroy(m->ready->event);
+        delete m->ready; (void)hipFree(m->block); delete m;
         return fail(ctx, GELO_EHIP, "hipEventCreate failed");
     }
     m->last_stream = nullptr;
     ctx->pool.push_back(m);
+    ctx->marks.push_back(m->ready);
     *out = m;
     return GELO_OK;
+}
+
+// A mark that only `m` holds, to be recorded for a new draw.
+ReadyMark* own_mark(gelo_ctx* ctx, gelo_mixing* m) {
+    if (m->ready->holders > 1) {
+        for (ReadyMark* free_mark : ctx->marks) {
+            if (free_mark->holders > 0) continue;
+            --m->ready->holders;
+            free_mark->holders = 1;
+            m->ready = free_mark;
+            break;
+        }
+    }
+    return m->ready;
+}
+void share_mark(gelo_mixing* m, ReadyMark* mark) {
+    ++mark->holders; --m->ready->holders;
+    m->ready = mark;
 }
 
 void drop_lane_graphs(gelo_ctx* ctx) {
@@ -403,10 +430,11 @@ gelo_status gelo_destroy(gelo_ctx* ctx) {
     hipSetDevice(ctx->device);
     hipDeviceSynchronize();
     for (gelo_mixing* m : ctx->pool) {
-        hipEventDestroy(m->ready); hipEventDestroy(m->released);
+        hipEventDestroy(m->released);
         hipFree(m->block);
         delete m;
     }
+    for (ReadyMark* mark : ctx->marks) { (void)hipEventDestroy(mark->event); delete mark; }
     drop_lane_graphs(ctx);
     if (ctx->lanes_ready) {
         (void)hipEventDestroy(ctx->lane_fork); (void)hipEventDestroy(ctx->lane_join);
@@ -704,7 +732,7 @@ gelo_status gelo_sample_mixing(gelo_ctx* ctx, gelo_kind kind, int n_data, int k_
     if (m->last_stream != nullptr || m->mixed) GELO_HIP(ctx, hipStreamWaitEvent(s, m->released, 0));
     st = sample_into(ctx, m, ws, ws_bytes, lanes, kind, cond_max, max_attempts, batch_id, s);
     if (st != GELO_OK) return st;
-    GELO_HIP(ctx, hipEventRecord(m->ready, s));
+    GELO_HIP(ctx, hipEventRecord(own_mark(ctx, m)->event, s));
     m->in_use = true; m->mixed = false; m->consumed = false;
     m->sample_stream = s; m->last_stream = s;
     batch_commit(ctx, batch_id);
@@ -840,7 +868,7 @@ gelo_status gelo_mix(gelo_ctx* ctx, gelo_mixing* m, gelo_dtype dtype, const void
     if (!ctx->allow_reuse && m->mixed) return fail(ctx, GELO_EREUSE, "this mixing object has already mixed a batch");
     GELO_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t s = (hipStream_t)stream;
-    if (s != m->sample_stream) GELO_HIP(ctx, hipStreamWaitEvent(s, m->ready, 0));
+    if (s != m->sample_stream) GELO_HIP(ctx, hipStreamWaitEvent(s, m->ready->event, 0));
     st = mix_launch(ctx, m, H, ldh, shield_scale, stat, U, ldu, s);
     if (st != GELO_OK) return st;
     m->mixed = true; m->last_stream = s;
@@ -901,7 +929,7 @@ gelo_status gelo_unmix(gelo_ctx* ctx, gelo_mixing* m, gelo_dtype dtype, int p, c
     if (!m->mixed) return fail(ctx, GELO_ESTATE, "gelo_unmix before gelo_mix");
     GELO_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t s = (hipStream_t)stream;
-    if (s != m->sample_stream) GELO_HIP(ctx, hipStreamWaitEvent(s, m->ready, 0));
+    if (s != m->sample_stream) GELO_HIP(ctx, hipStreamWaitEvent(s, m->ready->event, 0));
     st = unmix_launch(ctx, m, p, Y, ldy, Z, ldz, s);
     if (st != GELO_OK) return st;
     m->consumed = true; m->last_stream = s;
@@ -995,16 +1023,19 @@ gelo_status gelo_sample_mixing_batch(gelo_ctx* ctx, gelo_kind kind, int n_data, 
         }
         if (e != hipSuccess) st = hip_fail(ctx, e, "batched orthogonal draw");
     }
+    if (st == GELO_OK) {
+        hipError_t e = hipEventRecord(own_mark(ctx, got[0])->event, s);
+        if (e != hipSuccess) st = hip_fail(ctx, e, "hipEventRecord");
+    }
     if (st != GELO_OK) {
         for (int i = 0; i < have; ++i) got[i]->in_use = false;
         return st;
     }
     for (int i = 0; i < count; ++i) {
         gelo_mixing* m = got[i];
+        if (i > 0) share_mark(m, got[0]->ready);
         m->kind = kind; m->attempt = 0; m->kappa = 1.0f; m->batch_id = first_batch_id + (uint64_t)i;
         m->mixed = false; m->consumed = false; m->sample_stream = s; m->last_stream = s;
-        hipError_t e = hipEventRecord(m->ready, s);
-        if (e != hipSuccess) return hip_fail(ctx, e, "hipEventRecord");
         batch_commit(ctx, m->batch_id);
         out[i] = m;
     }
@@ -1071,7 +1102,7 @@ gelo_status gelo_mixing_export(gelo_ctx* ctx, const gelo_mixing* m, float* A, fl
     if (S && m->k > 0 && !m->mixed) return fail(ctx, GELO_ESTATE, "shield rows exist only after gelo_mix");
     GELO_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t s = (hipStream_t)stream;
-    if (s != m->sample_stream) GELO_HIP(ctx, hipStreamWaitEvent(s, m->ready, 0));
+    if (s != m->sample_stream) GELO_HIP(ctx, hipStreamWaitEvent(s, m->ready->event, 0));
     if (m->structured && (A || A_inv)) {
         // the dense matrices exist only here: A = (the transform applied to the identity), in float
         const int64_t ldn = round_up(m->n, 8);
@@ -1250,7 +1281,7 @@ gelo_status gelo_mixing_export_table(gelo_ctx* ctx, const gelo_mixing* m, uint32
     if (!table) return fail(ctx, GELO_EINVAL, "table is NULL");
     GELO_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t s = (hipStream_t)stream;
-    if (s != m->sample_stream) GELO_HIP(ctx, hipStreamWaitEvent(s, m->ready, 0));
+    if (s != m->sample_stream) GELO_HIP(ctx, hipStreamWaitEvent(s, m->ready->event, 0));
     // the library's tables start on 16-byte boundaries; the caller's are packed
     GELO_HIP(ctx, hipMemcpy2DAsync(table, (size_t)m->n * sizeof(uint32_t), m->table, (size_t)round_up(m->n, 4) * sizeof(uint32_t),
                                    (size_t)m->n * sizeof(uint32_t), kStructuredRounds + 1, hipMemcpyDeviceToDevice, s));

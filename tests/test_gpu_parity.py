@@ -800,6 +800,43 @@ def test_project_f32_tile_variants(ctx, M, K, N, ldy_extra):
         assert torch.all(parent[:, N:] == 3.0)
 
 
+@pytest.mark.parametrize("n_data,k", [(20, 2), (150, 6)])
+def test_batched_draws_on_a_side_stream_are_waited_for(n_data, k):
+    """The objects of a batched draw share the event that another stream waits for; redrawn ones, singly or by another batch, leave it to those
+    that are still out.  Everything mixed on this stream is, bit for bit, what one stream gives."""
+    d = 512
+    H = torch.randn((n_data, d), generator=torch.Generator(device="cuda").manual_seed(3), device="cuda").bfloat16()
+
+    def run(stream):
+        ctx = g.gelo_create(0, 77)
+        got = []
+
+        def mix(m):
+            U = torch.empty((n_data + k, d), dtype=torch.bfloat16, device="cuda")
+            g.gelo_mix(ctx, m, H, U)
+            got.append(U)
+
+        def batch(first, count):
+            return g.gelo_sample_mixing_batch(ctx, g.GELO_ORTHOGONAL, n_data, k, d, g.GELO_BF16, first, count, stream=stream)
+
+        first = batch(0, 5)
+        mix(first[0]); g.gelo_mixing_free(ctx, first[0])
+        single = g.gelo_sample_mixing(ctx, g.GELO_ORTHOGONAL, n_data, k, d, g.GELO_BF16, 0.0, 1, batch_id=5, stream=stream)
+        mix(first[1]); g.gelo_mixing_free(ctx, first[1])
+        second = batch(6, 4)
+        for m in [second[0], first[2], single, first[3]]:
+            mix(m); g.gelo_mixing_free(ctx, m)
+        third = batch(10, 6)
+        for m in third + [first[4]] + second[1:]:
+            mix(m); g.gelo_mixing_free(ctx, m)
+        torch.cuda.synchronize()
+        g.gelo_destroy(ctx)
+        return got
+
+    for a, b in zip(run(None), run(torch.cuda.Stream())):
+        assert torch.equal(a, b)
+
+
 def test_sampling_ahead_on_side_streams_matches_one_stream():
     """The mixing matrix does not depend on the data, so it may be drawn ahead on another stream and
     context while earlier batches run; the chain then waits for it through the mixing object.  The
