@@ -718,14 +718,16 @@ void qr_step_kernel(QrStepArgs a) {
     });
 }
 
-// ------------------------------------------------------------- the last rows, or a small matrix -- 
+// ------------------------------------------------------------- the last rows, or a small matrix --
 // What is left of every matrix from its tile (t0, t0) on, at most 8 x 8 tiles, by one workgroup (tile_qr.h).
-// 128 rows 44 us, 64 rows 17, where a launch per panel took 8.5 each: draw alone of 144 rows 135 -> 103 us, 256 rows 203 -> 167; CONDITIONED,
-// 64 rows 257 -> 199.  Bound by the chain of 16 x 8 columns, 340 cycles each (two sums over the rows of lanes, the root, the reciprocal) and
-// 30 more for every tile it walks over, and of 1500 to 5500 per 16 columns for the reflectors of the tile column before.  Up to 16 x 16 tiles it was tried:
+// 128 rows 49 us, 64 rows 18, where a launch per panel took 8.5 each: draw alone of 144 rows 135 -> 104 us, 256 rows 203 -> 170; CONDITIONED,
+// 64 rows 257 -> 200.  Bound by the chain of 16 x 8 columns, 340 cycles each (two sums over the rows of lanes, the root, the reciprocal) and
+// 30 more for every tile it walks over, by the triangle of each 16 (5 us of the 49), and by 1500 to 5500 cycles per 16 columns for the reflectors of the
+// tile column before.  Up to 16 x 16 tiles it was tried:
 // at 9 to 16 the matrix instructions of all tile columns on one CU (16 000 cycles a tile column) cost more than the launches they save (256 rows 220 us).
-// Against 64 bits, panels to the end / this (24 draws, other things equal): |A^T A - I| / sqrt(n) at 129, 160, 200, 256 rows 4.18e-7 / 3.93e-7, 4.38 / 4.18,
-// 4.64 / 4.47, 5.01 / 4.92; part of A^T G below the diagonal at 129 and 256 rows 2.24e-7 / 2.0e-7, 2.81 / 2.76.
+// Against 64 bits, panels to the end / this (16 to 48 draws; of the first figures a part is that strips sum V W' by itself, above): |A^T A - I| / sqrt(n) at
+// 129, 160, 256 rows 4.16e-7 / 3.11e-7, 4.37 / 3.14, 5.02 / 3.31; part of A^T G below the diagonal 2.24e-7 / 1.65e-7, 2.39 / 1.71, 2.81 / 1.81; distance of
+// A from the exact factor 8.4e-7 / 6.0e-7, 8.8 / 6.8, 11.7 / 7.3.
 struct SquareQrArgs {
     float *M, *Vc, *Tmat, *Rd, *rdiag;   // Vc: null where nobody reads the reflectors row by row
     int nbr, t0;
@@ -757,7 +759,7 @@ void square_qr_kernel(SquareQrArgs a) {
     factorise_tile_column<NT>(sh, y, w, nbt, NB, lane, [&](auto last) {
 #pragma unroll
         for (int i = 0; i <= decltype(last)::value; ++i) *reinterpret_cast<f32x4_t*>(column + i * 256) = f32x4_t{y[4 * i], y[4 * i + 1], y[4 * i + 2], y[4 * i + 3]};      // R
-    }, [&](const ColumnEnds& ends, f32x4_t diagonal, auto tiles) {
+    }, [&](const ColumnEnds& ends, f32x4_t diagonal, f32x4_t t, auto tiles) {
         constexpr int TC = decltype(tiles)::value;
         float* v = a.Vc + off + (int64_t)panel * a.nbr * 256 + 64 * g + c;
         float* down = column + w * 256;
@@ -770,7 +772,6 @@ void square_qr_kernel(SquareQrArgs a) {
                 for (int e = 0; e < 4; ++e) v[b * 256 + e * NB] = y[4 * b + e];
             }
         }
-        const f32x4_t t = exact_triangle<TC>(y, ends.some, sh.turn + (w & 1) * NB * kTurnPitch, lane);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             a.Tmat[off + panel * 256 + (4 * g + e) * NB + c] = t[e];

@@ -18,15 +18,15 @@ constexpr int kTurnPitch = kPanel + 4;                    // of a tile that is t
 
 // Of `tiles` tile columns: the reflectors of tile column p, tiles p .. of it.
 __host__ __device__ inline int tile_qr_before(int tiles, int p) { return p * tiles - p * (p - 1) / 2; }
-// U, a tile of zeros, two triangles for the columns still to be factorised, two tiles to turn around in, two triangles for Q
-__host__ __device__ inline int tile_qr_floats(int tiles) { return (tile_qr_before(tiles, tiles) + 1 + 2 + 2) * 256 + 2 * kPanel * kTurnPitch; }
+// U, a tile of zeros, two triangles, a tile to turn around in
+__host__ __device__ inline int tile_qr_floats(int tiles) { return (tile_qr_before(tiles, tiles) + 1 + 2) * 256 + kPanel * kTurnPitch; }
 struct TileQrShared {
-    float *U, *zero, *T, *exact, *turn;
+    float *U, *zero, *T, *turn;
     int tiles;
     __device__ __forceinline__ TileQrShared(float* base, int tiles_) : tiles(tiles_) {
         U = base;
         zero = U + tile_qr_before(tiles, tiles) * 256;
-        T = zero + 256; exact = T + 512; turn = exact + 512;
+        T = zero + 256; turn = T + 512;
     }
     __device__ __forceinline__ float* tile(int p, int i) const { return U + (tile_qr_before(tiles, p) + i - p) * 256; }
 };
@@ -92,31 +92,16 @@ __device__ __forceinline__ void add_tiles(float (&y)[N], float f) {
             : "v"(f), "n"(J));
 }
 #undef GELO_ADD
-// acc += sum over b < J of t[b] x (d of lane b of the row of 16)
-#define GELO_TERM(b, x) ".if " #b " < %c17\n\tv_fmac_f32_dpp %0, %1, %" #x " row_newbcast:" #b " row_mask:0xf bank_mask:0xf\n.endif\n\t"
-template <int J>
-__device__ __forceinline__ void add_terms(float& acc, float d, const float (&t)[kPanel]) {
-    if constexpr (J > 0)
-        asm("s_nop 1\n\t" GELO_TERM(0, 2) GELO_TERM(1, 3) GELO_TERM(2, 4) GELO_TERM(3, 5) GELO_TERM(4, 6) GELO_TERM(5, 7) GELO_TERM(6, 8) GELO_TERM(7, 9)
-            GELO_TERM(8, 10) GELO_TERM(9, 11) GELO_TERM(10, 12) GELO_TERM(11, 13) GELO_TERM(12, 14) GELO_TERM(13, 15) GELO_TERM(14, 16)
-            : "+v"(acc)
-            : "v"(d), "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]), "v"(t[7]), "v"(t[8]), "v"(t[9]), "v"(t[10]), "v"(t[11]),
-              "v"(t[12]), "v"(t[13]), "v"(t[14]), "n"(J));
-}
-#undef GELO_TERM
 
 // Householder QR of TC tiles of 16 columns, y[4 b + e] row 16 b + 4 g + e of the lane's column (the first `cols` of them; the others are
 // zero).  On return R above the diagonal, u below it; of the lane's column u's entry on the diagonal, R's, and whether there is
-// anything to reflect (the reflector is I - 2 u u^T / u^T u); t: row c of the triangle T of I - U T U^T = H_0 H_1 .., whose inner products
-// u_i^T u_j the walks leave (float).
+// anything to reflect (the reflector is I - 2 u u^T / u^T u).
 struct ColumnEnds { float ut, r; bool some; };
 template <int TC, int N>
-__device__ __forceinline__ ColumnEnds columns_qr(float (&y)[N], float (&t)[kPanel], int cols, int c) {
+__device__ __forceinline__ ColumnEnds columns_qr(float (&y)[N], int cols, int c) {
     static_assert(4 * TC <= N, "tiles that are not there");
     constexpr int GROUPS = (TC - 1) / 4;                  // of four tiles below the first; what is left over one by one
     float pivot_c = 0.f, below_c = 0.f;
-#pragma unroll
-    for (int k = 0; k < kPanel; ++k) t[k] = 0.f;
     static_for<kPanel>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
         if (j >= cols) return;
@@ -133,14 +118,11 @@ __device__ __forceinline__ ColumnEnds columns_qr(float (&y)[N], float (&t)[kPane
         const float uu = fmaf(ut, ut, nn), r = __builtin_amdgcn_rcpf(uu);
         float inv = 2.f * fmaf(fmaf(-uu, r, 1.f), r, r);
         inv = nn > 0.f ? inv : 0.f;
-        const float d = fmaf(ut, p, below);               // u^T x; of an earlier column u_c: u^T u_c
+        const float d = fmaf(ut, p, below);               // u^T x
         const float f = c > j ? -inv * d : 0.f;
         add_first<j>(y[0], y[1], y[2], y[3], f, ut);
         static_for<GROUPS>([&](auto bc) { add_tiles<j, 1 + 4 * decltype(bc)::value>(y, f); });
         static_for<TC - 1 - 4 * GROUPS>([&](auto kc) { constexpr int k = 4 * (1 + 4 * GROUPS + decltype(kc)::value); add_tile<j>(y[k], y[k + 1], y[k + 2], y[k + 3], f); });
-        float sum = 0.f;
-        add_terms<j>(sum, d, t);
-        t[j] = c < j ? -inv * sum : (c == j ? inv : 0.f);
         pivot_c = c == j ? p : pivot_c;
         below_c = c == j ? below : below_c;
     });
@@ -152,7 +134,9 @@ __device__ __forceinline__ ColumnEnds columns_qr(float (&y)[N], float (&t)[kPane
     return ends;
 }
 
-// T once more, from U^T U in double precision: what the orthogonality of I - U T U^T is lost to is U^T U's rounding.  u: the
+// The triangle T of I - U T U^T = H_0 H_1 .., from U^T U in double precision: what the orthogonality of I - U T U^T is lost to is
+// U^T U's rounding.  The same T takes the columns behind to R and forms Q.  (The inner products that the walks leave anyhow are
+// float: 6 us of 103 at 129 rows less with a T from those for R, and 1 to 3% more of A^T G below the diagonal, 44 to 160 rows.)  u: the
 // reflectors in accumulator layout, zeros above their diagonal; turn: kPanel x kTurnPitch floats.  Returns T in accumulator layout.
 template <int TC, int N>
 __device__ __forceinline__ f32x4_t exact_triangle(const float (&u)[N], bool some, float* turn, int lane) {
@@ -189,7 +173,7 @@ __device__ __forceinline__ f32x4_t exact_triangle(const float (&u)[N], bool some
 }
 
 // X <- (I - U T U^T)^T X for the reflectors of tile column p and a wave's tiles p .. nbt - 1; x[4 i + e]: row 16 i + 4 g + e of its column;
-// T: a tile in LDS, plain.  U T^T U^T X is summed by itself and subtracted once.
+// T: a tile in LDS, column after column.  U T^T U^T X is summed by itself and subtracted once.
 template <int NT>
 __device__ __forceinline__ void apply_reflectors(const TileQrShared& sh, float (&x)[4 * NT], const float* T, int p, int nbt, int lane) {
     constexpr int GRP = 2, NG = (NT + GRP - 1) / GRP;
@@ -259,9 +243,10 @@ __device__ __forceinline__ void shift_tiles(float (&x)[4 * NT], int by, Above&& 
 }
 
 // One wave's tile column `w` of nbt: the reflectors before it, its own, which it publishes at the barrier behind them (number w, one per
-// tile column).  y: its tiles.  above(i): tiles 0 .. i, those above the diagonal, are R's.  done(ends, diagonal, tiles): behind the barrier; tile w + b is
-// in y[4 b ..], U's below the diagonal and zeros above, `diagonal` R's, and no more than `tiles` of them are there.  cols: columns of
-// the last tile column that are there.
+// tile column).  y: its tiles.  above(i): tiles 0 .. i, those above the diagonal, are R's.  done(ends, diagonal, triangle, tiles): behind the
+// barrier; tile w + b is in y[4 b ..], U's below the diagonal and zeros above, `diagonal` R's, `triangle` T, and no more than `tiles` of
+// them are there.  cols: columns of the last tile column that are there.  (Two triangles in LDS: the one before is still read while this
+// one is written.  One tile to turn around in: the wave before is behind its barrier.)
 template <int NT, class Above, class Done>
 __device__ __forceinline__ void factorise_tile_column(const TileQrShared& sh, float (&y)[4 * NT], int w, int nbt, int cols, int lane, Above&& above, Done&& done) {
     const int c = lane & 15, g = lane >> 4;
@@ -277,8 +262,7 @@ __device__ __forceinline__ void factorise_tile_column(const TileQrShared& sh, fl
     static_for<NT / STEP>([&](auto sc) {
         constexpr int TC = STEP * (decltype(sc)::value + 1);
         if (nt <= TC - STEP || nt > TC) return;           // wave-uniform
-        float t[kPanel];
-        const ColumnEnds ends = columns_qr<TC>(y, t, w == nbt - 1 ? cols : kPanel, c);
+        const ColumnEnds ends = columns_qr<TC>(y, w == nbt - 1 ? cols : kPanel, c);
         f32x4_t diagonal;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -286,17 +270,15 @@ __device__ __forceinline__ void factorise_tile_column(const TileQrShared& sh, fl
             diagonal[e] = r < c ? y[e] : (r == c ? ends.r : 0.f);
             y[e] = r > c ? y[e] : (r == c ? ends.ut : 0.f);
         }
-        const f32x4_t mine = rows_of_group(t, g);         // T[c][4 g ..]
-        float* T = sh.T + (w & 1) * 256;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) T[(4 * g + e) * 16 + c] = mine[e];
+        const f32x4_t triangle = exact_triangle<TC>(y, ends.some, sh.turn, lane);
+        *reinterpret_cast<f32x4_t*>(sh.T + (w & 1) * 256 + c * 16 + 4 * g) = triangle;
         float* u = sh.tile(w, w) + 16 * tile_slot(c) + 4 * g;
 #pragma unroll
         for (int b = 0; b < TC; ++b)
             if (b < nt) *reinterpret_cast<f32x4_t*>(u + b * 256) = f32x4_t{y[4 * b], y[4 * b + 1], y[4 * b + 2], y[4 * b + 3]};
         __builtin_amdgcn_s_setprio(0);
         __syncthreads();
-        done(ends, diagonal, std::integral_constant<int, TC>{});
+        done(ends, diagonal, triangle, std::integral_constant<int, TC>{});
     });
 }
 
