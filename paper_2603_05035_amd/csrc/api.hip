@@ -467,8 +467,12 @@ static BlockPiece block_piece(int n_data, int k, int i) {
     b.data0 = r0 - s0; b.data_rows = b.rows - b.shield_rows;
     return b;
 }
-// Blocks that share the launches of one batched factorisation (draw_blocks): all, unless there is one that the one-workgroup draw takes.
-static int blocks_side_by_side(int n) { return n <= kSmallMaxN ? 0 : block_count(n); }
+// A last block of up to so many rows is left to the one-workgroup draw (draw_blocks), and a batch of one block of up to kSmallMaxN rows.
+constexpr int kLastAlone = 41;
+// Blocks that share the launches of one batched factorisation: the others.
+static int blocks_side_by_side(int n) {
+    return n <= kSmallMaxN ? 0 : n / GELO_BLOCK_ROWS + (n % GELO_BLOCK_ROWS > kLastAlone ? 1 : 0);
+}
 // their workspaces, one behind the other
 static size_t block_workspace_bytes(int n) {
     return (size_t)blocks_side_by_side(n) * up256(factor_workspace_bytes(n < GELO_BLOCK_ROWS ? n : GELO_BLOCK_ROWS));
@@ -500,24 +504,35 @@ static gelo_status check_sample_args(gelo_ctx* ctx, gelo_kind kind, int n_data, 
 }
 
 // The blocks of `count` BLOCK_ORTHOGONAL objects (targets t, batch ids from `first` on; base: their factorisation workspaces,
-// object-major).  The blocks share the launches of one batched factorisation.  A last, shorter one takes part in it as the end of a full-size
-// matrix that begins with the identity.  With one up to kSmallMaxN rows left to a launch of the one-workgroup draw behind the others, 10 to 60 us: one draw of
-// 300 rows 225 -> 171 us, 2150 rows 240 -> 177, 32 of 300 rows 568 -> 543, of 2150 rows 974 -> 970.  |A^T A - I| / sqrt(rows) of the last block by the
-// one-workgroup draw / here (48 draws): 8 rows 2.12e-7 / 2.22e-7, 16 2.47 / 2.88, 36 2.83 / 2.91, 64 3.20 / 3.02, 100 3.62 / 3.02, 128 3.90 / 3.08 (the whole blocks 3.31).
+// object-major).  The blocks share the launches of one batched factorisation.  A last, shorter one of more than kLastAlone rows takes part in it
+// as the end of a full-size matrix that begins with the identity; with a launch of the one-workgroup draw behind the others for it (up to 128 rows, 10 to 60
+// us): one draw of 2150 rows 240 -> 177 us, 32 of them 974 -> 970.  Up to kLastAlone rows it is left to that launch: few rows lose by
+// the products that apply 16 reflectors at once (us, that launch / beside the others: one draw of 264 rows 177 / 169, 297 rows 194 / 169, 32 of them 362 / 403
+// and 379 / 406).  The last block alone / beside the others, |A^T A - I| / sqrt(rows) and part of A^T G below the diagonal (96 draws):
+// 8 rows 2.14e-7 and 0.89e-7 / 2.30 and 1.21, 16 2.48 and 1.14 / 2.91 and 1.76, 32 2.75 and 1.41 / 2.90 and 1.57, 40 2.86 and 1.50 / 2.88 and 1.51,
+// 42 2.91 and 1.53 / 2.87 and 1.51, 48 2.99 and 1.60 / 2.98 and 1.54, 64 3.20 and 1.78 / 3.01 and 1.55, 128 3.90 and 2.29 / 3.09 and 1.64.
 static hipError_t draw_blocks(const SmallSampleTargets& t, int count, uint64_t first, PhiloxStream ps, int n, int d, int64_t ldk, char* base,
                               hipStream_t s, const ShieldRows& shields = ShieldRows()) {
     constexpr int B = GELO_BLOCK_ROWS;
     const int full = n / B, rest = n % B, side = blocks_side_by_side(n);
     ps.c1 = kStreamBlock << 8; ps.c2 = (uint32_t)first; ps.c3 = (uint32_t)(first >> 32);
-    if (side == 0) return small_sample(t, count, first, ps, 0, n, 0, d, ldk, s);
-    const int rows = n < B ? n : B, tail = full > 0 ? rest : 0;
-    FactorWorkspace w;
-    factor_workspace_carve(base, rows, &w);
-    const int64_t stride = (int64_t)(up256(factor_workspace_bytes(rows)) / sizeof(float));
-    hipError_t e = fill_normal_batched(w.M, stride, w.n_pad / 16, rows, rows, ps, side, side * count, false, s, tail, 1.f, w.X, shields);
-    if (e == hipSuccess) e = householder_qr_prepared(w, side * count, stride, s);
-    if (e == hipSuccess) e = emit_batched(w.X, w.rdiag, stride, w.n_pad / 16, rows, ldk, t, count, side, 0, (int64_t)B * ldk, s, tail);
-    return e;
+    if (side > 0) {
+        const int rows = n < B ? n : B, tail = full > 0 && side > full ? rest : 0;
+        FactorWorkspace w;
+        factor_workspace_carve(base, rows, &w);
+        const int64_t stride = (int64_t)(up256(factor_workspace_bytes(rows)) / sizeof(float));
+        hipError_t e = fill_normal_batched(w.M, stride, w.n_pad / 16, rows, rows, ps, side, side * count, false, s, tail, 1.f, w.X, shields);
+        if (e == hipSuccess) e = householder_qr_prepared(w, side * count, stride, s);
+        if (e == hipSuccess) e = emit_batched(w.X, w.rdiag, stride, w.n_pad / 16, rows, ldk, t, count, side, 0, (int64_t)B * ldk, s, tail);
+        if (e != hipSuccess) return e;
+    }
+    if (rest == 0 || side > full) return hipSuccess;
+    SmallSampleTargets r = t;                                  // the last block, or the only one
+    const int64_t at = (int64_t)full * B * ldk;
+    r.off_A32 += 4 * at; r.off_Ainv32 += 4 * at;
+    if (r.off_A16 >= 0) { r.off_A16 += 2 * at; r.off_Ainv16 += 2 * at; }
+    ps.c1 = (kStreamBlock << 8) | (uint32_t)full;
+    return small_sample(r, count, first, ps, 0, rest, 0, d, ldk, s);
 }
 
 // Enqueues the draw of batch `batch_id` into the buffers `m` points at, with `ws` as factorisation
