@@ -1,5 +1,5 @@
 // Householder QR of a large matrix in blocks of 128 columns (Section 3.2 step 1.2's orthogonal factor): the columns until
-// 112 to 272 rows are left; householder_qr's panels take those.  No panel is walked column by column.  With P the block's
+// 144 to 272 rows are left; householder_qr's panels take those.  No panel is walked column by column.  With P the block's
 // m x 128 panel, C the columns behind it, C1 and P1 their first 128 rows,
 //
 //   S  = P^T [P | C]                    launch_panel_products; of C, behind the first block, block_overlap_kernel
@@ -13,7 +13,7 @@
 // The LU elimination of the panel's top minus R is how Householder vectors are had from an orthogonal factor (Ballard, Demmel,
 // Grigori, Jacquelin, Knight, Nguyen, "Reconstructing Householder vectors from tall-skinny QR", 2015), here with R from the Gram
 // matrix: an m x 128 panel of a Gaussian matrix behind its reflectors is Gaussian again, with a condition number of about
-// (sqrt(m) + 11.3) / (sqrt(m) - 11.3): 1.6 at 2150 rows, 5.8 at 256, where the blocks end.  CONDITIONED matrices' panels are
+// (sqrt(m) + 11.3) / (sqrt(m) - 11.3): 1.6 at 2150 rows, 5.4 at 272, where the blocks end.  CONDITIONED matrices' panels are
 // no worse than A (2 to 4).
 //
 // A draw alone is bound by the chain of four launches per 128 columns, at 2150 rows 5.5 (panel update) + 9 (P^T P) + 34 (the core, with the columns

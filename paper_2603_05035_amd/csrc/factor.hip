@@ -3,7 +3,7 @@
 // with the inverse of the non-orthogonal kinds, which is built on the same factorisation.  Everything is float and deterministic: reductions run in a fixed order, no
 // atomics.
 //
-// Matrices from 336 rows on are factorised by blocks of 128 columns (block_factor.hip); smaller ones, and what the blocks leave (112 to 272
+// Matrices from 321 rows on are factorised by blocks of 128 columns (block_factor.hip); smaller ones, and what the blocks leave (144 to 272
 // rows), by panels of 16 columns, each by ONE workgroup from its 16 x 16 Gram matrix (gram_panel_body); the last 128 rows, or a matrix of no
 // more, by one workgroup in registers (square_qr_kernel).  Reflectors are applied on the matrix cores.  From 720 rows on Q is formed by
 // blocks of 256 reflectors (block_reflect.hip), below by strips of 16 columns.
@@ -720,9 +720,9 @@ void qr_step_kernel(QrStepArgs a) {
 
 // ------------------------------------------------------------- the last rows, or a small matrix --
 // What is left of every matrix from its tile (t0, t0) on, at most 8 x 8 tiles, by one workgroup (tile_qr.h).
-// 128 rows 49 us, 64 rows 18, where a launch per panel took 8.5 each: draw alone of 144 rows 135 -> 104 us, 256 rows 203 -> 170; CONDITIONED,
+// 128 rows 50 us, 64 rows 18, where a launch per panel took 8.5 each: draw alone of 144 rows 135 -> 104 us, 256 rows 203 -> 170; CONDITIONED,
 // 64 rows 257 -> 200.  Bound by the chain of 16 x 8 columns, 340 cycles each (two sums over the rows of lanes, the root, the reciprocal) and
-// 30 more for every tile it walks over, by the triangle of each 16 (5 us of the 49), and by 1500 to 5500 cycles per 16 columns for the reflectors of the
+// 30 more for every tile it walks over, by the triangle of each 16 (5 us of the 50), and by 1500 to 5500 cycles per 16 columns for the reflectors of the
 // tile column before.  Up to 16 x 16 tiles it was tried:
 // at 9 to 16 the matrix instructions of all tile columns on one CU (16 000 cycles a tile column) cost more than the launches they save (256 rows 220 us).
 // Against 64 bits, panels to the end / this (16 to 48 draws; of the first figures a part is that strips sum V W' by itself, above): |A^T A - I| / sqrt(n) at

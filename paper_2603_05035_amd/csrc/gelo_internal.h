@@ -321,12 +321,17 @@ int64_t block_panel_values(int n_pad);       // 16-bit values of `panel`
 constexpr int kCoreFloats = 3 * 128 * 128;
 // Factorises 128 columns at a time, matrices from kBlockTiles tile rows on, while last_block_tiles and more of them are left: reflectors
 // (row by row where Vc is not null), R and its diagonal, T as householder_qr's own panels leave them; *panels_done panels of 16.
-// The lines are drawn by accuracy: a block's Gram matrix squares its panel's condition number, and what that costs shows the less the more
-// of the matrix is behind better blocks.  Part of A^T G below the diagonal, of |G|, and distance of A from the exact factor (24 draws), panels
-// by themselves / blocks down to 15 tile rows: 256 rows 1.82e-7 and 7.3e-7 / 3.14e-7 and 14.1e-7, 300 rows 1.87 and 7.2 / 2.96 and 13.6, 400 rows 1.96 and 8.6 / 3.05
-// and 16.6.  A draw alone: 360 rows 233 / 220 us, 430 rows 335 / 262, 543 rows 416 / 326, 700 rows 555 / 428.
+// A block's Gram matrix squares its panel's condition number, so blocks cost accuracy where panels of few rows are left.  The lines are the
+// smallest at which no error is larger than with panels as they were before strips summed V W' by themselves (factor.hip); panels as they
+// are now would be more exact still.  Part of A^T G below the diagonal, of |G|, and distance of A from the exact factor, 1e-7 (12 to 64 draws), panels then /
+// panels now / blocks: 321 rows 3.07 and 12.9 / 1.89 and 7.6 / 2.85 and 12.7, 352 rows 3.19 and 13.6 / 1.92 and 7.9 / 2.71 and 11.9, 400 rows 3.35 and
+// 14.4 / 1.96 and 8.8 / 2.56 and 12.2, 543 rows 3.82 and 17.5 / 2.08 and 8.7 / 3.03 and 14.9, 700 rows 4.28 and 19.7 / 2.22 and 9.3 / 2.98 and 15.9.  A draw
+// alone, us: 321 rows 261 / 227 / 214, 400 rows 309 / 276 / 260, 543 rows 412 / 379 / 322, 700 rows 551 / 513 / 425; 32 draws 655 / 495 / 448, 758 / 609 / 542, 1056
+// / 941 / 728, 1459 / 1415 / 1036.  From 45 tile rows on, which went by blocks before, down to 17 tile rows / to 15 (15 to 20 us less where 15 or 16
+// are left): 752 rows 3.74 and 15.1 / 3.84 and 17.9 (before 3.76 and 15.8), 1024 rows 3.69 and 16.6 / 3.75 and 18.4 (3.71 and 17.0), 2150 rows 4.00 /
+// 4.01 (4.01).
 constexpr int kBlockTiles = 21;
-inline int last_block_tiles(int nbr) { return nbr >= 45 ? 15 : 18; }
+inline int last_block_tiles(int nbr) { return nbr >= 45 ? 17 : 18; }
 constexpr int kYrBlock = 3 * 4 * 512;        // 16-bit values of a tile row of a block's reflectors taken apart
 hipError_t factor_blocks(const FactorWorkspace& ws, float* Vc, int count, int64_t batch_stride, int* panels_done, hipStream_t stream);
 // ws.X <- H_0 H_1 ... ws.X for the panels' reflectors householder_qr has left in ws.M and ws.Tmat
