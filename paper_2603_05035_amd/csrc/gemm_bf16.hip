@@ -971,11 +971,15 @@ int gemm_bf16_skinny_slices(int M, int N, int K) {
     // 12288 x 4096: 30 us either way; 68 x 4096 x 4096: 28 -> 20 us; 68 x 4096 x 11008: 70 -> 29 us); beyond three
     // row tiles the 192-column accumulators no longer fit the registers.
     if (M > 96 || N < 192 || (N + 63) / 64 > 128) return 1;
-    // A short K is over before the second launch and the longer epilogue pay: one launch / the two, us, weights from memory,
-    // 512 and 4096 columns: 20 rows, K = 1024 7.0 / 8.2 and 7.3 / 9.5, 1536 9.4 / 9.2 and 9.8 / 11.1, 2048 11.4 / 9.7 and 12.3 / 12.2, 3072
-    // 15.8 / 11.0 and 17.0 / 14.8; 68 rows 10.0 / 12.7 and 10.3 / 14.8, 13.2 / 13.6 and 13.8 / 17.1, 16.3 / 14.1 and 17.2 / 19.1, 22.5 / 15.4 and
-    // 23.7 / 20.3; 96 rows of 2048 16.4 / 14.8 and 17.7 / 20.8.
-    if (K <= 1536 + N / 8) return 1;
+    // A short K is over before the second launch and the longer epilogue pay.  The cut's partial sums go by the rows, the other launch's fetches of
+    // A by tiles of 32 of them, so the line lies lower where a tile is filled by half or less, and higher with three tiles.  One launch / the two, us, weights
+    // from memory, K = 1024, 1536, 1792, 2048: 512 columns, 1 row 7.3 / 8.7, 9.5 / 9.1, cut from here on; 20 rows 7.5 / 9.4, 9.6 / 9.9, cut; 33 rows 9.0 /
+    // 10.9, 11.7 / 11.6, cut; 68 rows 10.5 / 13.5, 13.6 / 14.2, cut; 2048 columns, 1 row 7.4 / 8.9, 9.5 / 9.6, 10.6 / 10.0; 20 rows 7.6 / 9.8, 9.7 / 10.6, 10.9 / 10.9;
+    // 33 rows 9.1 / 11.2, 11.8 / 12.0, 13.1 / 12.5; 68 rows 10.6 / 14.4, 13.9 / 15.5, 15.3 / 15.9; 4096 columns, 1 row 7.6 / 9.5, 9.7 / 10.4, 10.9 / 10.8, 11.9 / 11.3;
+    // 20 rows 7.8 / 10.1, 10.0 / 11.2, 11.1 / 11.8, 12.2 / 12.3; 33 rows 9.3 / 11.8, 11.9 / 13.0, 13.3 / 13.5, 14.6 / 13.8; 68 rows 10.8 / 15.5, 14.0 / 17.2,
+    // 15.5 / 18.0, 17.1 / 18.9; beyond, 3072: 68 rows of 512 and 4096 22.5 / 15.4 and 23.7 / 20.3.
+    const int line = M > 64 ? 1536 + N / 8 : (M - 1) % 32 >= 16 ? 1520 + N / 8 : 1470 + N / 16;
+    if (K <= line) return 1;
     const int groups = (N + 191) / 192;
     const int T = (K + 63) / 64;
     int slices = 256 / groups;

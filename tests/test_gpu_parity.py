@@ -740,9 +740,11 @@ def test_strided_operands(ctx):
     (700, 4096, 520, 8),       # long K (64 K steps), three row tiles with a ragged last one
     (1, 64, 8, 0), (33, 128, 520, 8), (97, 1024, 72, 0), (128, 640, 136, 16),   # the skinny kernel with 1, 2, 4, 4 waves
     (68, 64, 200, 0),          # 3 row tiles, a single K step
+    (97, 1024, 776, 8),        # 4 row tiles, padded output rows
+    (8, 512, 200, 0),          # one row tile
     # the skinny launch that cuts K over workgroups (192-column groups x slices of K steps, float partial sums):
-    (97, 1024, 776, 8),        # 5 column groups (the last one 8 columns wide) x 4 slices, padded output rows
-    (8, 512, 200, 0),          # 2 groups x 2 slices, one row tile
+    (90, 2560, 776, 8),        # 5 column groups (the last one 8 columns wide) x 10 slices, padded output rows
+    (8, 1600, 200, 0),         # 2 groups x 6 slices, one row tile
     (96, 2112, 392, 0),        # 33 K steps over 8 slices (4 or 5 steps each), three full row tiles
     (128, 2112, 392, 0),       # four row tiles: K is not cut
     (68, 4096, 4096, 0),       # the decode-shaped O projection: 22 groups x 11 slices
@@ -762,9 +764,10 @@ def test_project_bf16_fast_path_edges(ctx, M, K, N, ldy_extra):
         assert torch.all(parent[:, N:] == 3.0)
 
 
-# K is cut beyond 1536 + N / 8: both sides of that line at the narrowest, an odd and the widest N, with one and three row tiles.  Beyond 16384
+# K is cut beyond 1536 + N / 8 with three row tiles, 1520 + N / 8 with the last one more than half full, else 1470 + N / 16: both sides of
+# these lines at the narrowest, an odd and the widest N.  Beyond 16384
 # columns a workgroup takes 128 of them: either side of that line, ragged last groups, one to four row tiles, three rounds with a short and a longer K
-@pytest.mark.parametrize("M,K,N", [(8, 1536, 192), (20, 1600, 192), (68, 1664, 1032), (96, 1728, 1032), (5, 2496, 7744), (96, 2560, 8192), (96, 2624, 8192),
+@pytest.mark.parametrize("M,K,N", [(8, 1472, 192), (8, 1536, 192), (20, 1536, 192), (20, 1600, 192), (48, 1920, 7744), (5, 1984, 7744), (68, 1664, 1032), (96, 1728, 1032), (5, 2496, 7744), (96, 2560, 8192), (96, 2624, 8192),
                                    (1, 64, 16384), (1, 64, 16392), (40, 320, 16456), (96, 1088, 22016), (128, 640, 20488), (33, 512, 32776), (33, 576, 32776)])
 def test_project_bf16_launch_rules(ctx, M, K, N):
     U = torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(M), device="cuda").bfloat16()
