@@ -77,8 +77,9 @@ def test_blocks_of_128_columns(ctx, n):
 
 # so many matrices that the blocks' products take the kernels for many as well (tile rows left x matrices / 8 from 256 on): one, two and
 # four blocks of 32 matrices, those behind them by the kernels for few again; ranges of rows summed in three and four parts of two ranges, the
-# last one short, and (3425 rows) in parts of one range
-@pytest.mark.parametrize("n,count", [(897, 32), (1025, 32), (1137, 32), (1281, 32), (3425, 10)])
+# last one short, and (3425 rows) in parts of one range.  The update of the next panel's 8 tile columns takes its kernel for many from 512 = tile rows left x
+# matrices / 8 on: 2150 and 2172 rows, behind their first block, with an odd and an even number of tile rows (127 and 128)
+@pytest.mark.parametrize("n,count", [(897, 32), (1025, 32), (1137, 32), (1281, 32), (3425, 10), (2150, 32), (2172, 32)])
 def test_blocks_of_128_columns_of_many_matrices(ctx, n, count):
     first = 100 * n
     many = [g.gelo_mixing_export(ctx, m, n, 0, 64, want_shields=False)[0] for m in g.gelo_sample_mixing_batch(ctx, g.GELO_ORTHOGONAL, n, 0, 64, g.GELO_F32, first, count)]
