@@ -141,9 +141,10 @@ def test_static_entry_point_and_fresh_blocks(ctx):
     assert (mats[0] - mats[1]).abs().max() > 0.05
 
 
-# a last block of more than 128 rows is the end of a full-size matrix beside the others: the panels it begins with (its first column in the
-# second, third and last panel of a group of four; nothing left out from 193 rows on), rows that fill no tile
-@pytest.mark.parametrize("rest", [129, 144, 145, 176, 192, 193, 255])
+# a last block of more than 41 rows is the end of a full-size matrix beside the others, a shorter one is drawn by itself: the smallest and the
+# largest of both, rows that fill a tile, one less and one more.  The identity before it ends inside the last 128 rows, which one workgroup factorises (up to
+# 112), where they begin (113 to 128), and among the panels before them
+@pytest.mark.parametrize("rest", [1, 15, 16, 17, 41, 42, 48, 49, 112, 113, 127, 128, 129, 144, 145, 176, 192, 193, 255])
 def test_short_last_block_beside_the_others(ctx, rest):
     n, eps = 512 + rest, 2.0 ** -24
     many = g.gelo_sample_mixing_batch(ctx, g.GELO_BLOCK_ORTHOGONAL, n, 0, 64, g.GELO_F32, 100, 3)
@@ -177,10 +178,12 @@ def test_last_block_of_few_rows_keeps_its_accuracy(ctx, rest, loss, below):
 
 
 @pytest.mark.parametrize("nd,k,d,count,picks", [(300, 15, 64, 5, (0, 4)), (2048, 102, 256, 6, (0, 3, 5)), (100, 0, 64, 3, (1,)),
-                                                   (400, 20, 64, 5, (0, 4)), (200, 0, 64, 3, (2,))])
+                                                   (400, 20, 64, 5, (0, 4)), (200, 0, 64, 3, (2,)),
+                                                   (2048, 102, 64, 32, (0, 15, 31)), (2304, 25, 64, 32, (0, 31))])
 def test_batched_draw_equals_single_draws(ctx, nd, k, d, count, picks):
-    """All full blocks of all objects of a batched draw share one factorisation's launches; object i is still,
-    bit for bit, the single draw of its batch id."""
+    """All full blocks of all objects of a batched draw, and a last one of more than 41 rows, share one factorisation's launches; object
+    i is still, bit for bit, the single draw of its batch id.  32 objects of nine such blocks are more matrices than the chip has CUs,
+    whose last 128 rows are factorised by a kernel of fewer registers."""
     first = 40
     n = nd + k
     single = g.gelo_create(0, SEED, allow_batch_reuse=False)
