@@ -41,11 +41,10 @@ def test_one_workgroup_factorisation(ctx, n):
     check_orthogonal(A.double().cpu().numpy(), n, n)
 
 
-# panels built from their Gram matrix down to 64 rows: one and two of them, whole and broken tiles, where the strips' blocks per wave
-# change (640 rows), and sizes whose last 144 to 256 rows are left to the panels behind blocks of 128 columns (9 to 16 tile rows: 1280
-# and 1281, 1920 and 1921, 2561, 3841).  One matrix alone applies each reflector to all columns at once, several side by side a block
-# of them in one pass: the same bits
-@pytest.mark.parametrize("n", [129, 143, 144, 145, 160, 161, 191, 192, 640, 641, 1280, 1281, 1920, 1921, 2561, 3841])
+# panels built from their Gram matrix in front of the last 128 rows: one and two of them, whole and broken tiles, the most there are by themselves (320)
+# and the first matrices with a block of 128 columns in front (321, 336, 337).  What the blocks leave: 10 and 17 tile rows of matrices of up to 44
+# (401, 640, 704 and 400, 641, the most), 9 and 16 of larger ones (1281 and 1280, 1921, 1920, 2561, 3841).  A matrix alone and beside another one: the same bits
+@pytest.mark.parametrize("n", [129, 143, 144, 145, 160, 161, 191, 192, 320, 321, 336, 337, 400, 401, 640, 641, 704, 1280, 1281, 1920, 1921, 2561, 3841])
 def test_panels_from_gram_matrices(ctx, n):
     first, count = 10 * n, 2
     pair = g.gelo_sample_mixing_batch(ctx, g.GELO_ORTHOGONAL, n, 0, 64, g.GELO_F32, first, count)
@@ -58,10 +57,10 @@ def test_panels_from_gram_matrices(ctx, n):
     check_orthogonal(alone.double().cpu().numpy(), n, first + 1)
 
 
-# blocks of 128 columns, from 720 rows of tiles on: the last size before them (704), the first such sizes, one and several rows and tiles
-# beyond whole blocks, odd numbers of tile rows.  Q of 24 matrices is formed by the kernels for many, that of one and of two by those for
-# few; the blocks' products take those for few at all of these sizes.  The same sums in the same order, so the same bits
-@pytest.mark.parametrize("n", [704, 705, 720, 721, 769, 784, 896, 897, 1025])
+# blocks of 128 columns: the last size before them (320), the first such sizes, the last size whose Q is formed by strips (704) and the first by 256 reflectors at
+# a time, one and several rows and tiles beyond whole blocks, odd numbers of tile rows.  From 705 rows on Q of 24 matrices is formed by the kernels for many,
+# that of one and of two by those for few; the blocks' products take those for few at all of these sizes.  The same sums in the same order, so the same bits
+@pytest.mark.parametrize("n", [320, 321, 337, 401, 545, 704, 705, 720, 721, 769, 784, 896, 897, 1025])
 def test_blocks_of_128_columns(ctx, n):
     first, count = 100 * n, 24
     many = [g.gelo_mixing_export(ctx, m, n, 0, 64, want_shields=False)[0] for m in g.gelo_sample_mixing_batch(ctx, g.GELO_ORTHOGONAL, n, 0, 64, g.GELO_F32, first, count)]
