@@ -392,12 +392,11 @@ __device__ __forceinline__ void columns_behind(const OverlapArgs& o, uint8_t* ld
     }
 }
 
-template <int RANGES>
 __global__ __launch_bounds__(kCoreThreads)
 void block_overlap_kernel(OverlapArgs o) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     if ((int)blockIdx.x >= o.core_slots) { columns_behind(o, lds, blockIdx.x - o.core_slots); return; }
-    if ((int)blockIdx.x < o.b.w.count) block_core<RANGES>(o.b, *reinterpret_cast<CoreShared*>(lds), blockIdx.x);
+    if ((int)blockIdx.x < o.b.w.count) block_core<kWideChunks>(o.b, *reinterpret_cast<CoreShared*>(lds), blockIdx.x);
 }
 
 // ------------------------------------------------------------ the columns behind the block, the rows below it --
@@ -529,9 +528,7 @@ void panel_triangle_kernel(const float* M, float* Vc, float* Tmat, int nbr, int6
 int64_t block_panel_values(int n_pad) { return (int64_t)((n_pad / NB + 1) / 2) * kUnitPanel; }
 
 hipError_t block_factor_init() {    // brings this file's code onto the device (see factor_init)
-    for (const void* f : {reinterpret_cast<const void*>(&block_overlap_kernel<kWideParts>), reinterpret_cast<const void*>(&block_overlap_kernel<kWideChunks>)})
-        GELO_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kOverlapLds));
-    return hipSuccess;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&block_overlap_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kOverlapLds);
 }
 
 hipError_t factor_blocks(const FactorWorkspace& ws, float* Vc, int count, int64_t batch_stride, int* panels_done, hipStream_t s) {
@@ -562,15 +559,14 @@ hipError_t factor_blocks(const FactorWorkspace& ws, float* Vc, int count, int64_
             update.cols = BT; update.next = ws.panel;
             GELO_TRY(launch_block_update(update, s));
             WideArgs own = a;
-            own.cols = BT; own.groups = 1; own.by_part = count >= kWideCus;
+            own.cols = BT; own.groups = 1; own.by_part = false;      // few columns: ranges fill the chip
             GELO_TRY(launch_panel_products(own, s));
             o.P = ws.panel;
             o.core_slots = (count + 7) / 8 * 8;
             o.items = a.by_part ? a.parts : a.chunks;
             o.per_item = a.by_part ? a.per_chunk * a.part_chunks : a.per_chunk;
             const dim3 grid(o.core_slots + 8 * dies_slots(o.groups * o.items, count));
-            if (own.by_part) hipLaunchKernelGGL((block_overlap_kernel<kWideParts>), grid, dim3(kCoreThreads), kOverlapLds, s, o);
-            else hipLaunchKernelGGL((block_overlap_kernel<kWideChunks>), grid, dim3(kCoreThreads), kOverlapLds, s, o);
+            hipLaunchKernelGGL(block_overlap_kernel, grid, dim3(kCoreThreads), kOverlapLds, s, o);
         }
         GELO_TRY(hipGetLastError());
         if (a.by_part) hipLaunchKernelGGL((block_apply_kernel<kWideParts>), dim3(2 * (a.mt - BT), count), dim3(512), 0, s, b);
