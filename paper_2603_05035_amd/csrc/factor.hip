@@ -19,12 +19,6 @@ namespace {
 
 constexpr int NB = kPanel;
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
 // ------------------------------------------------------------------ directly drawn panels --
 // The reflectors of an m x 16 panel, every one from its column as it stands in memory (the later columns of the panel do not see the
 // earlier reflectors: what the product of directly drawn reflectors needs, householder_qr with `direct`), and what the block reflector
@@ -756,7 +750,7 @@ void square_qr_kernel(SquareQrArgs a) {
         for (int e = 0; e < 4; ++e) sh.zero[lane * 4 + e] = 0.f;
     }
     const int panel = t0 + w;
-    factorise_tile_column<NT>(sh, y, w, nbt, NB, lane, [&](auto last) {
+    factorise_tile_column<NT>(sh, y, w, nbt, lane, [&](auto last) {
 #pragma unroll
         for (int i = 0; i <= decltype(last)::value; ++i) *reinterpret_cast<f32x4_t*>(column + i * 256) = f32x4_t{y[4 * i], y[4 * i + 1], y[4 * i + 2], y[4 * i + 3]};      // R
     }, [&](const ColumnEnds& ends, f32x4_t diagonal, f32x4_t t, auto tiles) {

@@ -93,18 +93,16 @@ __device__ __forceinline__ void add_tiles(float (&y)[N], float f) {
 }
 #undef GELO_ADD
 
-// Householder QR of TC tiles of 16 columns, y[4 b + e] row 16 b + 4 g + e of the lane's column (the first `cols` of them; the others are
-// zero).  On return R above the diagonal, u below it; of the lane's column u's entry on the diagonal, R's, and whether there is
-// anything to reflect (the reflector is I - 2 u u^T / u^T u).
+// Householder QR of TC tiles of 16 columns, y[4 b + e] row 16 b + 4 g + e of the lane's column.  On return R above the diagonal, u below
+// it; of the lane's column u's entry on the diagonal, R's, and whether there is anything to reflect (the reflector is I - 2 u u^T / u^T u).
 struct ColumnEnds { float ut, r; bool some; };
 template <int TC, int N>
-__device__ __forceinline__ ColumnEnds columns_qr(float (&y)[N], int cols, int c) {
+__device__ __forceinline__ ColumnEnds columns_qr(float (&y)[N], int c) {
     static_assert(4 * TC <= N, "tiles that are not there");
     constexpr int GROUPS = (TC - 1) / 4;                  // of four tiles below the first; what is left over one by one
     float pivot_c = 0.f, below_c = 0.f;
     static_for<kPanel>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
-        if (j >= cols) return;
         const float p = row_to_all<j / 4>(y[j % 4]);      // the pivot's row
         float a0 = 0.f, a1 = 0.f;
         // from the bottom up: u's large entry on the diagonal comes last
@@ -245,10 +243,10 @@ __device__ __forceinline__ void shift_tiles(float (&x)[4 * NT], int by, Above&& 
 // One wave's tile column `w` of nbt: the reflectors before it, its own, which it publishes at the barrier behind them (number w, one per
 // tile column).  y: its tiles.  above(i): tiles 0 .. i, those above the diagonal, are R's.  done(ends, diagonal, triangle, tiles): behind the
 // barrier; tile w + b is in y[4 b ..], U's below the diagonal and zeros above, `diagonal` R's, `triangle` T, and no more than `tiles` of
-// them are there.  cols: columns of the last tile column that are there.  (Two triangles in LDS: the one before is still read while this
+// them are there.  (Two triangles in LDS: the one before is still read while this
 // one is written.  One tile to turn around in: the wave before is behind its barrier.)
 template <int NT, class Above, class Done>
-__device__ __forceinline__ void factorise_tile_column(const TileQrShared& sh, float (&y)[4 * NT], int w, int nbt, int cols, int lane, Above&& above, Done&& done) {
+__device__ __forceinline__ void factorise_tile_column(const TileQrShared& sh, float (&y)[4 * NT], int w, int nbt, int lane, Above&& above, Done&& done) {
     const int c = lane & 15, g = lane >> 4;
 #pragma unroll 1
     for (int p = 0; p < w; ++p) {
@@ -262,7 +260,7 @@ __device__ __forceinline__ void factorise_tile_column(const TileQrShared& sh, fl
     static_for<NT / STEP>([&](auto sc) {
         constexpr int TC = STEP * (decltype(sc)::value + 1);
         if (nt <= TC - STEP || nt > TC) return;           // wave-uniform
-        const ColumnEnds ends = columns_qr<TC>(y, w == nbt - 1 ? cols : kPanel, c);
+        const ColumnEnds ends = columns_qr<TC>(y, c);
         f32x4_t diagonal;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
