@@ -588,7 +588,7 @@ static gelo_status sample_into(gelo_ctx* ctx, gelo_mixing* m, FactorWorkspace ws
     } else if (kind == GELO_CONDITIONED) {
         GELO_HIP(ctx, orthogonal_into_X(false));
         ps.c1 = kStreamPerturb << 8;
-        GELO_HIP(ctx, fill_normal(ws.M, ws.n_pad / 16, n, n, ps, 1.0f, 1, s));
+        GELO_HIP(ctx, fill_normal_batched(ws.M, 0, ws.n_pad / 16, n, n, ps, 1, 1, false, s));
         GELO_HIP(ctx, perturb_tiles(ws.M, ws.X, ws.rdiag, ws.n_pad, kConditionedBeta / std::sqrt((float)n), s));
         GELO_HIP(ctx, emit_matrix(ws.M, ws.n_pad / 16, 1, nullptr, n, ldk, m->A32, m->A16, nullptr, nullptr, s));
         if (n > kInvBlock) {

@@ -183,18 +183,12 @@ __device__ __forceinline__ void shield_direction_row(float* GS, int d, int i, Ph
 __host__ __device__ inline int64_t qr_tile_index(int r, int c, int tile_rows) {
     return ((int64_t)(c >> 4) * tile_rows + (r >> 4)) * 256 + (c & 15) * 16 + (r & 15);
 }
-// out = scale * N(0,1) for r < rows, c < cols; element e = r*cols + c is output e % 4 of Philox
-// block e / 4 (counter word 0 = block index).  tiled == 0: out[r * ld + c]; tiled != 0: the same
-// element goes to out[qr_tile_index(r, c, ld)] (ld = number of tile rows); tiled == 2: the same, but pieces of 16 rows x
-// 256 columns that lie wholly above the diagonal are left as they are (for a reader of the lower triangle only).
-hipError_t fill_normal(float* out, int64_t ld, int rows, int cols, PhiloxStream ps, float scale,
-                       int tiled, hipStream_t stream);
 // words[4 i .. 4 i + 3] = the four output words of Philox block first_block + i (counter word 0), 16-byte aligned
 // calibrate.hip: matrix instructions from registers only (0: bf16 32x32x16, 1: E4M3 32x32x64)
 size_t matrix_rate_scratch_bytes();
 hipError_t matrix_rate_launch(int fp8, int iters, float* scratch, double* flop, hipStream_t stream);
 hipError_t philox_words(uint32_t* words, uint32_t first_block, uint32_t blocks, PhiloxStream ps, hipStream_t stream);
-// GS[k x d] (pitch d) = N(0,1) with fill_normal's element order, gsnorm[i] = || GS[i, :] ||_2; d % 8 == 0
+// GS[k x d] (pitch d) = N(0,1) in fill_normal_batched's order of elements, gsnorm[i] = || GS[i, :] ||_2; d % 8 == 0
 hipError_t shield_directions(float* GS, int k, int d, PhiloxStream ps, float* gsnorm, hipStream_t stream);
 // tiles of A = Q diag(sign rdiag) + scale G: G (in 16 x 16 tiles with n_pad / 16 tile rows) is overwritten by A
 hipError_t perturb_tiles(float* G, const float* Q, const float* rdiag, int n_pad, float scale, hipStream_t stream);
@@ -229,7 +223,9 @@ struct SmallSampleTargets {
 };
 // The pieces of a batched draw, one launch each for all its matrices (one at a time they cost a launch's 4 us each, 2150 rows
 // 13 - 15).  Matrix z belongs to object z / per_batch, whose batch id is z / per_batch after ps.c3:c2.
-// fill: matrix z at out + z out_stride, tiled like fill_normal's, stream word ps.c1 + z % per_batch.  tail_rows > 0: the last of every
+// fill: scale * N(0,1) for r < rows, c < cols; element e = r cols + c is output e % 4 of Philox block e / 4 (counter word 0 = block
+// index) and goes to qr_tile_index(r, c, tile_rows).  Matrix z at out + z out_stride, stream word ps.c1 + z % per_batch.  lower_only: pieces of 16 rows x
+// 256 columns that lie wholly above the diagonal are left as they are (for a reader of the lower triangle only).  tail_rows > 0: the last of every
 // per_batch matrices is a Gaussian of tail_rows rows and columns that starts at tail_offset(tile_rows, tail_rows), with the identity before it
 // and zeros behind it (square matrices of at most 256 rows).  X: as householder_qr_prepared wants M and X; then also the shield directions of
 // the only object (stream word shields.c1)

@@ -7,26 +7,7 @@
 namespace gelo {
 namespace {
 
-__global__ __launch_bounds__(256)
-void fill_normal_kernel(float* out, int64_t ld, int rows, int cols, PhiloxStream ps, float scale, int tiled) {
-    const int64_t total = (int64_t)rows * cols;
-    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (q * 4 >= total) return;
-    uint32_t c0 = (uint32_t)q, c1 = ps.c1, c2 = ps.c2, c3 = ps.c3;
-    philox4x32_10(c0, c1, c2, c3, ps.key0, ps.key1);
-    float z[4];
-    box_muller(c0, c1, &z[0], &z[1]);
-    box_muller(c2, c3, &z[2], &z[3]);
-    int64_t e = q * 4;
-    int r = (int)(e / cols), c = (int)(e % cols);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        if (e + t < total) out[tiled ? qr_tile_index(r, c, (int)ld) : (int64_t)r * ld + c] = scale * z[t];
-        if (++c == cols) { c = 0; ++r; }
-    }
-}
-
-// The same values into the QR's 16 x 16 tiles (qr_tile_index).  Element e = r cols + c is output e % 4 of
+// Normal values into the QR's 16 x 16 tiles (qr_tile_index).  Element e = r cols + c is output e % 4 of
 // Philox block e / 4, so a block's four values are neighbours in a ROW while a tile keeps a COLUMN's 16 rows
 // together: written straight from the registers every store of a wave would touch 64 cache lines.  A workgroup
 // instead takes 16 rows x 256 columns, computes the blocks that cover each of its row segments (one more per
@@ -128,7 +109,7 @@ void philox_words_kernel(uint32_t* words, uint32_t first, uint32_t blocks, Philo
 }
 
 // The k x d shield directions (row-major, pitch d, the same element-to-Philox-word map as
-// fill_normal_kernel) and their norms in one launch: one workgroup per row, partial sums of squares
+// fill_normal_tiled_kernel) and their norms in one launch: one workgroup per row, partial sums of squares
 // added in a fixed order (lanes by halving, then the four waves in turn).
 __global__ __launch_bounds__(256)
 void shield_directions_kernel(float* GS, int d, PhiloxStream ps, float* gsnorm) {
@@ -381,20 +362,6 @@ void export_dense_kernel(const void* src, int64_t ld, int rows, int cols, float*
 
 }  // namespace
 
-hipError_t fill_normal(float* out, int64_t ld, int rows, int cols, PhiloxStream ps, float scale,
-                       int tiled, hipStream_t stream) {
-    const int64_t quads = ((int64_t)rows * cols + 3) / 4;
-    if (quads == 0) return hipSuccess;
-    if (tiled && (int64_t)rows * cols < ((int64_t)1 << 32)) {
-        hipLaunchKernelGGL(fill_normal_tiled_kernel, dim3((cols + 255) / 256, (rows + 15) / 16), dim3(256), 0, stream,
-                           out, (int64_t)0, 1, (int)ld, rows, cols, ps, scale, tiled == 2 ? 1 : 0, 0, (float*)nullptr, ShieldRows());
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(fill_normal_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream,
-                       out, ld, rows, cols, ps, scale, tiled);
-    return hipGetLastError();
-}
-
 hipError_t fill_normal_batched(float* out, int64_t out_stride, int tile_rows, int rows, int cols, PhiloxStream ps, int per_batch, int count,
                                bool lower_only, hipStream_t stream, int tail_rows, float scale, float* X, const ShieldRows& shields) {
     if (rows <= 0 || cols <= 0 || count <= 0) return hipSuccess;
@@ -492,7 +459,7 @@ hipError_t export_dense(const void* src, int is_bf16, int64_t ld, int rows, int 
 
 hipError_t sampler_init() {    // brings this file's code onto the device (see factor_init)
     hipFuncAttributes attr;
-    return hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&fill_normal_kernel));
+    return hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&fill_normal_tiled_kernel));
 }
 
 }  // namespace gelo
