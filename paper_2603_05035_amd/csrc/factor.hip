@@ -913,7 +913,8 @@ hipError_t launch_square_qr(const SquareQrArgs& a, int count, hipStream_t s) {
     const dim3 grid(count), block(64 * tiles);
     const size_t lds = tile_qr_floats(tiles) * sizeof(float);
     if (tiles <= 4) hipLaunchKernelGGL((square_qr_kernel<4, 4>), grid, block, lds, s, a);
-    // more matrices than CUs: two workgroups on one, for which a few registers are spilled (32 draws in nine blocks each 998 -> 965 us, one 177 -> 180)
+    // more matrices than CUs: two workgroups on one, for which 30 registers are spilled.  32 draws in 9, 10 and 17 blocks each 887 -> 846 us, 920 -> 880,
+    // 1419 -> 1388; one draw, which has them all, 177 -> 180
     else if (count > kWideCus) hipLaunchKernelGGL((square_qr_kernel<kSquareTiles, 4>), grid, block, lds, s, a);
     else hipLaunchKernelGGL((square_qr_kernel<kSquareTiles, 2>), grid, block, lds, s, a);
     return hipGetLastError();
