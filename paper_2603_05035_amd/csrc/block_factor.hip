@@ -18,10 +18,11 @@
 //
 // A draw alone is bound by the chain of four launches per 128 columns, at 2150 rows 5.5 (panel update) + 9 (P^T P) + 34 (the core, with the columns
 // further on beside it) + 7.5 us; with those columns in the chain it was 8 to 15 + 31.5 + 7 + 5 to 25.  A whole draw, that way / this, both down to
-// 15 tile rows: 1024 rows 584 / 581 us, 2150 rows 1371 / 1342 (down to 17, as it is, 602 and 1361), 4301 rows 4000 / 3622; 8 side by side 2150 rows 3680 / 3227; 32, whose columns pass through memory once a block instead of twice, 10 420 /
-// 10 150; up to 720 rows it makes no difference.  Panel by panel 2150 rows took 2661, 32 side by side 14 730.  Against 64 bits, panels / blocks (four
-// draws): |A^T A - I| / sqrt(n) at 720, 1040, 2150 rows 7.5e-7 / 5.3e-7, 8.8e-7 / 5.7e-7, 1.24e-6 / 6.4e-7; part of A^T G below the diagonal, of |G|,
-// 4.34e-7 / 3.77e-7, 5.14e-7 / 3.86e-7, 7.3e-7 / 4.0e-7; distance of A from the exact factor at 1300 and 2150 rows 2.6e-6 / 1.9e-6, 3.4e-6 / 1.6e-6.
+// 15 tile rows: 1024 rows 584 / 581 us, 2150 rows 1371 / 1342 (down to 17, as it is, 602 and 1361), 4301 rows 4000 / 3622; 8 side by side 2150 rows 3680 /
+// 3227; 32, whose columns pass through memory once a block instead of twice, 10 420 / 10 150; up to 720 rows it makes no difference.  Panel by panel 2150
+// rows took 2661, 32 side by side 14 730.  Against 64 bits, panels / blocks (four draws): |A^T A - I| / sqrt(n) at 720, 1040, 2150 rows 7.5e-7 / 5.3e-7, 8.8e-7 /
+// 5.7e-7, 1.24e-6 / 6.4e-7; part of A^T G below the diagonal, of |G|, 4.34e-7 / 3.77e-7, 5.14e-7 / 3.86e-7, 7.3e-7 / 4.0e-7; distance of A from the exact
+// factor at 1300 and 2150 rows 2.6e-6 / 1.9e-6, 3.4e-6 / 1.6e-6.
 #include "block_reflect.h"
 #include "wave_tile.h"
 
