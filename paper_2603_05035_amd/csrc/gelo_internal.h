@@ -321,7 +321,9 @@ constexpr int kCoreFloats = 3 * 128 * 128;
 // smallest at which no error is larger than with panels as they were before strips summed V W' by themselves (factor.hip); panels as they
 // are now would be more exact still.  Part of A^T G below the diagonal, of |G|, and distance of A from the exact factor, 1e-7 (12 to 64 draws), panels then /
 // panels now / blocks: 321 rows 3.07 and 12.9 / 1.89 and 7.6 / 2.85 and 12.7, 352 rows 3.19 and 13.6 / 1.92 and 7.9 / 2.71 and 11.9, 400 rows 3.35 and
-// 14.4 / 1.96 and 8.8 / 2.56 and 12.2, 543 rows 3.82 and 17.5 / 2.08 and 8.7 / 3.03 and 14.9, 700 rows 4.28 and 19.7 / 2.22 and 9.3 / 2.98 and 15.9.  A draw
+// 14.4 / 1.96 and 8.8 / 2.56 and 12.2, 543 rows 3.82 and 17.5 / 2.08 and 8.7 / 3.03 and 14.9, 700 rows 4.28 and 19.7 / 2.22 and 9.3 / 2.98 and 15.9.  Inverses
+// of GAUSSIAN matrices (48 to 128 draws, panels then / blocks), of kappa: |A^-1 A - I| at 321, 401, 417, 657 rows 0.89, 0.94, 0.91, 0.82 of it, |A A^-1 - I|, which no
+// result meets, 1.02, 1.04, 1.00, 0.88; a float chain's Z at 321 and 401 rows 1.50e-5 / 1.39e-5 and 1.76e-5 / 1.69e-5 (orthogonal 7.6e-7 / 6.3e-7, 8.3e-7 / 6.8e-7).  A draw
 // alone, us: 321 rows 261 / 227 / 214, 400 rows 309 / 276 / 260, 543 rows 412 / 379 / 322, 700 rows 551 / 513 / 425; 32 draws 655 / 495 / 448, 758 / 609 / 542, 1056
 // / 941 / 728, 1459 / 1415 / 1036.  From 45 tile rows on, which went by blocks before, down to 17 tile rows / to 15 (15 to 20 us less where 15 or 16
 // are left): 752 rows 3.74 and 15.1 / 3.84 and 17.9 (before 3.76 and 15.8), 1024 rows 3.69 and 16.6 / 3.75 and 18.4 (3.71 and 17.0), 2150 rows 4.00 /
